@@ -2,9 +2,8 @@
 // segments, each inside one page, copied bit for bit.  HBM-bound (read n + write n bytes).
 //
 // grid.y walks the segments, grid.x the fixed-size chunks of a segment; chunks beyond a segment's end
-// exit at once.  Segments whose source and destination are both 16-byte aligned move 128 bits per
-// lane with contiguous wavefront accesses; any other alignment falls back to the widest unit that
-// divides both addresses and the length.
+// exit at once.  Every lane moves 128 bits with contiguous wavefront accesses, whatever the
+// alignment of the two addresses (see apm_seg_copy_kernel).
 #include <cstdlib>
 #include "apm_internal.h"
 
@@ -24,51 +23,67 @@ constexpr int kVecPerLane = APM_COPY_U;
 constexpr int64_t kChunk = (int64_t)kThreads * 16 * kVecPerLane;
 constexpr int kMaxGridY = 65535;
 
-// Fallback for segments whose addresses are not both 16-byte aligned: the widest unit that
-// divides both addresses and the length.  Kept out of line and not unrolled so that it does not
-// inflate the register footprint of the aligned path.
-template <typename T>
-__device__ __noinline__ void copy_units(const char* src, char* dst, int64_t n_units) {
-    const T* s = reinterpret_cast<const T*>(src);
-    T* d = reinterpret_cast<T*>(dst);
-#pragma unroll 1
-    for (int64_t k = threadIdx.x; k < n_units; k += kThreads) d[k] = s[k];
+// One vector of a lane.  SRC_ALIGNED false: the source address is any byte address; the target's
+// unaligned access mode (which the compiler relies on for this type) serves it with one 128-bit load.
+typedef u32x4 __attribute__((aligned(1))) u32x4_any;
+template <bool SRC_ALIGNED>
+__device__ __forceinline__ u32x4 load_vec(const char* src, int vi) {
+    if (SRC_ALIGNED) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src) + vi);
+    return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(src + (int64_t)vi * 16));
 }
 
+template <bool SRC_ALIGNED>
+__device__ __forceinline__ void copy_chunk(const char* src, u32x4* dst, int nvec) {
+    u32x4 r[kVecPerLane];
+#pragma unroll
+    for (int k = 0; k < kVecPerLane; ++k) {
+        const int vi = k * kThreads + (int)threadIdx.x;
+        if (vi < nvec) r[k] = load_vec<SRC_ALIGNED>(src, vi);
+    }
+#pragma unroll
+    for (int k = 0; k < kVecPerLane; ++k) {
+        const int vi = k * kThreads + (int)threadIdx.x;
+        if (vi < nvec) __builtin_nontemporal_store(r[k], dst + vi);
+    }
+}
+
+// Both addresses 16-byte aligned: vector for vector.  Otherwise (views of one flat buffer, odd
+// numels) the stores are still aligned 128-bit vectors: the destination's first bytes up to a
+// multiple of 16 and its last ones go byte by byte (at most 15 each, by the segment's first
+// workgroup), and the vectors in between take whatever source alignment that leaves.  HBM-bound
+// either way.  122 M bf16 elements of odd-width tensors, views of one flat buffer, into pages:
+// a call took 145 us with 16-bit units on the odd addresses, 94 us like this.
 __global__ __launch_bounds__(kThreads) void apm_seg_copy_kernel(const SegDesc* descs, int64_t seg_offset) {
     const SegDesc d = descs[seg_offset + blockIdx.y];
     const int64_t start = (int64_t)blockIdx.x * kChunk;
     if (start >= d.nbytes) return;
-    const int64_t len = d.nbytes - start < kChunk ? d.nbytes - start : kChunk;
-    const char* src = static_cast<const char*>(d.src) + start;
-    char* dst = static_cast<char*>(d.dst) + start;
-    const uintptr_t mis = reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst);
-    if ((mis & 15u) == 0) {
+    const char* src = static_cast<const char*>(d.src);
+    char* dst = static_cast<char*>(d.dst);
+    if (((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15u) == 0) {
+        const int64_t len = d.nbytes - start < kChunk ? d.nbytes - start : kChunk;
+        src += start;
+        dst += start;
         const int nvec = (int)(len >> 4);
-        const u32x4* s = reinterpret_cast<const u32x4*>(src);
-        u32x4* o = reinterpret_cast<u32x4*>(dst);
-        u32x4 r[kVecPerLane];
-#pragma unroll
-        for (int k = 0; k < kVecPerLane; ++k) {
-            const int vi = k * kThreads + (int)threadIdx.x;
-            if (vi < nvec) r[k] = __builtin_nontemporal_load(s + vi);
-        }
-#pragma unroll
-        for (int k = 0; k < kVecPerLane; ++k) {
-            const int vi = k * kThreads + (int)threadIdx.x;
-            if (vi < nvec) __builtin_nontemporal_store(r[k], o + vi);
-        }
+        copy_chunk<true>(src, reinterpret_cast<u32x4*>(dst), nvec);
         const int tail = (int)(len & 15);  // only the last chunk of a segment can have one
         if ((int)threadIdx.x < tail) dst[((int64_t)nvec << 4) + threadIdx.x] = src[((int64_t)nvec << 4) + threadIdx.x];
-    } else if (((mis | (uintptr_t)len) & 7u) == 0) {
-        copy_units<uint64_t>(src, dst, len >> 3);
-    } else if (((mis | (uintptr_t)len) & 3u) == 0) {
-        copy_units<uint32_t>(src, dst, len >> 2);
-    } else if (((mis | (uintptr_t)len) & 1u) == 0) {
-        copy_units<uint16_t>(src, dst, len >> 1);
-    } else {
-        copy_units<uint8_t>(src, dst, len);
+        return;
     }
+    const int64_t to_vec = (int64_t)((16u - (uint32_t)(reinterpret_cast<uintptr_t>(dst) & 15u)) & 15u);
+    const int64_t head = to_vec < d.nbytes ? to_vec : d.nbytes;
+    const int64_t body = (d.nbytes - head) & ~(int64_t)15;
+    if (blockIdx.x == 0) {
+        const int64_t tail_at = head + body;
+        const int tail = (int)(d.nbytes - tail_at), t = (int)threadIdx.x;
+        if (t < (int)head) dst[t] = src[t];
+        if (t < tail) dst[tail_at + t] = src[tail_at + t];
+    }
+    if (start >= body) return;
+    const int64_t len = body - start < kChunk ? body - start : kChunk;
+    src += head + start;
+    dst += head + start;
+    if ((reinterpret_cast<uintptr_t>(src) & 15u) == 0) copy_chunk<true>(src, reinterpret_cast<u32x4*>(dst), (int)(len >> 4));
+    else copy_chunk<false>(src, reinterpret_cast<u32x4*>(dst), (int)(len >> 4));
 }
 
 // Both directions of a staged batch exchange in one kernel: the fp32 classes of an incoming batch

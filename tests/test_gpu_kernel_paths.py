@@ -1,0 +1,30 @@
+"""Small GPU tests of single kernel paths at the sizes and alignments where they can go wrong."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    import paper_2303_02868_amd as apm
+    from gpu_helpers import DEV
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n", [1, 7, 9, 2048, 2049, 4095, 4097, 3 * 4096 + 5])
+def test_pack_and_unpack_at_every_address_are_bit_exact_and_write_nothing_else(dtype, n):
+    """Any byte address on either side (vectors, head and tail of the copy kernel): pages and tensors
+    hold the same bytes, and the bytes around an unpacked tensor keep their value."""
+    E, eb = 4096, 2 if dtype == "bf16" else 4
+    kind, st = (apm.APM_BF16, apm.APM_G16) if dtype == "bf16" else (apm.APM_F32, apm.APM_P32)
+    raw = torch.randint(0, 256, (n * eb + 32,), dtype=torch.uint8, device=DEV,
+                        generator=torch.Generator(device=DEV).manual_seed(n))
+    for src_off in (0, 1, 2, 4, 6, 8, 13, 16):
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, 5, state_mask=1 << st)
+        apm.apm_pack_tensors(pool, st, apm.make_tensors([n], kind, [raw.data_ptr() + src_off]), 1)
+        for dst_off in (0, 1, 2, 4, 6, 8, 13):
+            out = torch.full((n * eb + 32,), 77, dtype=torch.uint8, device=DEV)
+            apm.apm_unpack(pool, st, apm.make_tensors([n], kind, [out.data_ptr() + dst_off]), 1)
+            torch.cuda.synchronize()
+            assert torch.equal(out[dst_off:dst_off + n * eb], raw[src_off:src_off + n * eb]), (src_off, dst_off)
+            assert (out[:dst_off] == 77).all() and (out[dst_off + n * eb:] == 77).all(), (src_off, dst_off)
+        pool.destroy()
