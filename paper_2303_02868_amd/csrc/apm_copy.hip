@@ -1,10 +1,10 @@
-// Gather / scatter between contiguous tensors and page storage: a list of (src, dst, nbytes)
-// segments, each inside one page, copied bit for bit.  HBM-bound (read n + write n bytes).
+// Gather / scatter between contiguous tensors and page storage: the layout's segments, each inside
+// one page, copied bit for bit.  HBM-bound (read n + write n bytes).
 //
 // grid.y walks the segments, grid.x the fixed-size chunks of a segment; chunks beyond a segment's end
 // exit at once.  Every lane moves 128 bits with contiguous wavefront accesses, whatever the
 // alignment of the two addresses (see apm_seg_copy_kernel).
-#include <cstdlib>
+#include <cstring>
 #include "apm_internal.h"
 
 namespace apm {
@@ -52,9 +52,46 @@ __device__ __forceinline__ void copy_chunk(const char* src, u32x4* dst, int nvec
 // multiple of 16 and its last ones go byte by byte (at most 15 each, by the segment's first
 // workgroup), and the vectors in between take whatever source alignment that leaves.  HBM-bound
 // either way.  122 M bf16 elements of odd-width tensors, views of one flat buffer, into pages:
-// a call took 145 us with 16-bit units on the odd addresses, 94 us like this.
-__global__ __launch_bounds__(kThreads) void apm_seg_copy_kernel(const SegDesc* descs, int64_t seg_offset) {
-    const SegDesc d = descs[seg_offset + blockIdx.y];
+// a call took 145 us with 16-bit units on the odd addresses, 94 us with vectors.
+//
+// A call brings nothing but the tensors' addresses, and these travel in the kernel arguments
+// (SegArgsInline): descriptors staged through a pinned ring cost the GPU an upload and two event packets,
+// 15 us between one call's copy and the next one's (122 M bf16 elements: 94 us a call, now 84;
+// 124 M fp32 elements out of their pages 177 us, now 160).  Long and short segments are launched
+// apart (group_by_extent): a GPT layout has as many bias and norm segments as full pages.
+struct SegArgs {
+    const SegRec* segs;   // from the first segment of the launch
+    char* region;
+    const uint64_t* ptrs; // the tensors' addresses, unless they follow inline
+    int32_t elem_bytes;
+    int32_t to_pages;
+    int32_t tensor_begin;
+};
+struct SegArgsInline {
+    SegArgs a;
+    uint64_t ptr[kArgWords];  // of tensors from a.tensor_begin
+};
+
+template <class Args>
+__global__ __launch_bounds__(kThreads) void apm_seg_copy_kernel(Args args) {
+    const SegArgs* ap;
+    uint64_t tensor;
+    SegRec r;
+    struct { const void* src; void* dst; int64_t nbytes; } d;
+    if constexpr (sizeof(Args) > sizeof(SegArgs)) {
+        ap = &args.a;
+        r = ap->segs[blockIdx.y];
+        tensor = args.ptr[r.tensor - ap->tensor_begin];
+    } else {
+        ap = &args;
+        r = ap->segs[blockIdx.y];
+        tensor = ap->ptrs[r.tensor];
+    }
+    char* in_tensor = reinterpret_cast<char*>(tensor) + r.tensor_off * ap->elem_bytes;
+    char* in_page = ap->region + r.page_elem * ap->elem_bytes;
+    d.src = ap->to_pages ? in_tensor : in_page;
+    d.dst = ap->to_pages ? in_page : in_tensor;
+    d.nbytes = (int64_t)r.n * ap->elem_bytes;
     const int64_t start = (int64_t)blockIdx.x * kChunk;
     if (start >= d.nbytes) return;
     const char* src = static_cast<const char*>(d.src);
@@ -274,14 +311,21 @@ hipError_t launch_duplex_copy(const DuplexCopy& d, int wavefronts, int per_wg, h
     return hipGetLastError();
 }
 
-hipError_t launch_seg_copy(const SegDesc* d_descs, int64_t n, int64_t max_bytes, hipStream_t s) {
-    if (n == 0 || max_bytes == 0) return hipSuccess;
-    const unsigned nx = (unsigned)((max_bytes + kChunk - 1) / kChunk);
-    for (int64_t off = 0; off < n; off += kMaxGridY) {
-        const int64_t ny = n - off < kMaxGridY ? n - off : kMaxGridY;
-        hipLaunchKernelGGL(apm_seg_copy_kernel, dim3(nx, (unsigned)ny), dim3(kThreads), 0, s, d_descs, off);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+hipError_t launch_seg_copy(const SegCopy& c, const SegLaunch* launches, int64_t n_launches, hipStream_t s) {
+    for (int64_t k = 0; k < n_launches; ++k) {
+        const SegLaunch& l = launches[k];
+        const int64_t max_bytes = l.max_n * c.elem_bytes;
+        const unsigned nx = (unsigned)((max_bytes + kChunk - 1) / kChunk);
+        SegArgsInline in;
+        if (!c.on_device) std::memcpy(in.ptr, c.ptrs + l.tensor_begin, (size_t)l.tensor_count * sizeof(uint64_t));
+        for (int64_t off = 0; off < l.count; off += kMaxGridY) {
+            const dim3 grid(nx, (unsigned)(l.count - off < kMaxGridY ? l.count - off : kMaxGridY));
+            in.a = SegArgs{c.segs + l.begin + off, c.region, c.on_device ? c.ptrs : nullptr, c.elem_bytes, c.to_pages, l.tensor_begin};
+            if (c.on_device) hipLaunchKernelGGL(apm_seg_copy_kernel<SegArgs>, grid, dim3(kThreads), 0, s, in.a);
+            else hipLaunchKernelGGL(apm_seg_copy_kernel<SegArgsInline>, grid, dim3(kThreads), 0, s, in);
+            hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
     }
     return hipSuccess;
 }

@@ -65,6 +65,43 @@ int make_plan(int64_t E, const int64_t* numels, int64_t n, Plan* out) {
     return APM_OK;
 }
 
+int group_by_extent(int64_t n, int64_t E, const std::function<int64_t(int64_t)>& size_of, int64_t* order,
+                    ExtentClass cls[kMaxExtentClasses]) {
+    auto class_of = [&](int64_t used) { return used * 4 > E ? 0 : used * 32 > E ? 1 : used * 512 > E ? 2 : 3; };
+    int64_t cnt[kMaxExtentClasses] = {}, mx[kMaxExtentClasses] = {};
+    for (int64_t k = 0; k < n; ++k) {
+        const int64_t u = size_of(k);
+        const int c = class_of(u);
+        ++cnt[c];
+        if (u > mx[c]) mx[c] = u;
+    }
+    // A class is worth its extra launches only if it saves enough idle workgroups (counted in
+    // 1024-element slices); otherwise it is folded into the next larger one.
+    int into[kMaxExtentClasses];
+    for (int c = 0; c < kMaxExtentClasses; ++c) into[c] = c;
+    constexpr int64_t kSpan = 1024, kWorthWorkgroups = 16384;
+    for (int c = kMaxExtentClasses - 1; c > 0; --c) {
+        if (cnt[c] == 0) continue;
+        int j = c - 1;
+        while (j > 0 && cnt[j] == 0) --j;
+        if (cnt[j] == 0) continue;
+        if (cnt[c] * ((mx[j] - mx[c]) / kSpan) < kWorthWorkgroups) {
+            for (int q = c; q < kMaxExtentClasses; ++q) if (into[q] == c) into[q] = j;
+            cnt[j] += cnt[c];
+            cnt[c] = 0;
+        }
+    }
+    int64_t fill[kMaxExtentClasses];
+    int n_cls = 0;
+    for (int64_t c = 0, at = 0; c < kMaxExtentClasses; ++c) {
+        fill[c] = at;
+        if (cnt[c] > 0) cls[n_cls++] = ExtentClass{at, cnt[c], mx[c]};
+        at += cnt[c];
+    }
+    for (int64_t k = 0; k < n; ++k) order[fill[into[class_of(size_of(k))]]++] = k;
+    return n_cls;
+}
+
 int emit_plan(const Plan& pl, apm_segment* segs, int64_t* n_segs, int64_t* n_pages,
               double* fragmentation) {
     const int64_t need = (int64_t)pl.segs.size();

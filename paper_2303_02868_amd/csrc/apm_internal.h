@@ -60,6 +60,26 @@ int emit_plan(const Plan& plan, apm_segment* segs, int64_t* n_segs, int64_t* n_p
 
 inline int elem_bytes(int state) { return state <= APM_V32 ? 4 : 2; }
 
+// ---- sizes launched together --------------------------------------------------------------
+// Items of very different sizes (a page's used extent, a segment) that share one grid are grouped
+// into at most this many classes, largest first, each launched with a grid sized for its largest
+// member: a nearly empty page (a small tensor alone in its page) does not cost a full page's worth
+// of workgroups that only find out they have nothing to do.
+constexpr int kMaxExtentClasses = 4;
+struct ExtentClass {
+    int64_t begin;     // first position
+    int64_t count;     // items
+    int64_t max_used;  // largest size among them (elements)
+};
+// order[pos] = index of the item at position pos (classes one after the other, the given order kept
+// inside each); returns the number of classes.  E = the size that the class limits are fractions of.
+int group_by_extent(int64_t n, int64_t E, const std::function<int64_t(int64_t)>& size_of, int64_t* order,
+                    ExtentClass cls[kMaxExtentClasses]);
+
+// Words of 8 bytes that a launch carries in its kernel arguments: 3.4 KB, which leaves room for the
+// rest under the 4 KB that argument blocks may have.
+constexpr int kArgWords = 440;
+
 // ---- pinned staging ring: small host arrays (page lists, copy descriptors) to the device ----
 struct StageRing {
     static constexpr int K = 8;
@@ -104,20 +124,9 @@ struct PageMeta {
     int64_t pad;
 };
 
-// The listed pages of one call, grouped by used extent: the pages of a class sit at consecutive
-// list positions and are launched together, with a grid sized for the class's largest extent, so
-// that a nearly empty page (a small tensor alone in its page) does not cost a full page's worth
-// of workgroups that only find out they have nothing to do.
 // Wavefronts of the update kernel when it reads and writes fp32 classes in host memory across
 // PCIe (the streamer's direct mode, the file tier's window); see apm_stream.hip for the sweep.
 constexpr int kDirectWavefronts = 48;
-
-constexpr int kMaxExtentClasses = 4;
-struct ExtentClass {
-    int64_t begin;     // first list position
-    int64_t count;     // pages
-    int64_t max_used;  // largest used extent among them (elements)
-};
 
 struct AdamwLaunch {
     float* p32;
@@ -163,12 +172,32 @@ hipError_t launch_grad_accum(uint16_t* acc, const uint16_t* g16, const int32_t* 
                              const int64_t* d_pages, int64_t first, int64_t n_listed, int64_t E,
                              hipStream_t s);
 
-struct SegDesc {
-    const void* src;
-    void* dst;
-    int64_t nbytes;
+// One segment of the layout as the copy kernel reads it: n elements from `tensor_off` of tensor
+// `tensor`, in the class region from element `page_elem`.  The table depends on the layout alone and
+// is uploaded with it; a call only brings the tensors' addresses.
+struct SegRec {
+    int64_t tensor_off;
+    int64_t page_elem;
+    int32_t tensor;
+    int32_t n;
 };
-hipError_t launch_seg_copy(const SegDesc* d_descs, int64_t n, int64_t max_bytes, hipStream_t s);
+// Segments [begin, begin + count) of the table, all of tensors [tensor_begin, tensor_begin + kArgWords),
+// the longest of max_n elements.
+struct SegLaunch {
+    int64_t begin, count, max_n;
+    int32_t tensor_begin, tensor_count;
+};
+// Pack (to_pages) or unpack over the given launches.  ptrs = the tensors' addresses: in host memory
+// (carried in the kernel arguments), or on_device: in device memory.
+struct SegCopy {
+    const SegRec* segs;
+    char* region;
+    int32_t elem_bytes;
+    bool to_pages;
+    const uint64_t* ptrs;
+    bool on_device;
+};
+hipError_t launch_seg_copy(const SegCopy& c, const SegLaunch* launches, int64_t n_launches, hipStream_t s);
 
 // One kernel that moves an incoming batch (3 fp32 classes, in_bytes each, host -> staging) and an
 // outgoing batch (out_bytes each, staging -> host) at once; either byte count may be 0.  All
@@ -207,6 +236,9 @@ struct apm_pool {
     int fd[APM_N_STATES] = {-1, -1, -1, -1, -1};  // FILE pools: one file per stored class
 
     int32_t* d_used = nullptr;      // device page table: used extent per page
+    apm::SegRec* d_segs = nullptr;  // the layout's segments, ordered as seg_launches lists them
+    std::vector<apm::SegLaunch> seg_launches;
+    int32_t seg_ranges = 0;         // groups of kArgWords tensors they are split into
     double* d_partials = nullptr;   // reduce scratch, n_pages * S
     uint32_t* d_nzflags = nullptr;
     apm::PageMeta* d_meta = nullptr;  // n_pages entries

@@ -116,6 +116,7 @@ void free_pool(apm_pool* pool) {
         }
     }
     if (pool->d_used) (void)hipFree(pool->d_used);
+    if (pool->d_segs) (void)hipFree(pool->d_segs);
     if (pool->d_partials) (void)hipFree(pool->d_partials);
     if (pool->d_nzflags) (void)hipFree(pool->d_nzflags);
     if (pool->d_meta) (void)hipFree(pool->d_meta);
@@ -134,9 +135,58 @@ void free_pool(apm_pool* pool) {
     delete pool;
 }
 
+// Groups of tensors beyond which pack / unpack stage the addresses instead of splitting the launch.
+constexpr int kMaxSegRanges = 2;
+
+// The layout's segments in launch order: per group of kArgWords tensors the long ones, then the short
+// ones (see group_by_extent).
+void order_segments(const Plan& plan, std::vector<SegRec>* recs, std::vector<SegLaunch>* launches, int32_t* ranges) {
+    const int64_t n = (int64_t)plan.segs.size();
+    recs->reserve((size_t)n);
+    const int64_t last = n ? plan.segs[(size_t)n - 1].tensor : -1;
+    // beyond kMaxSegRanges groups the addresses are staged: one group
+    const int64_t group = last / kArgWords < kMaxSegRanges ? kArgWords : last + 1;
+    *ranges = (int32_t)(last / kArgWords + 1);
+    std::vector<int64_t> order((size_t)n);
+    for (int64_t at = 0; at < n;) {
+        const int64_t t0 = plan.segs[(size_t)at].tensor / group * group;
+        int64_t end = at, mx = 0;
+        for (; end < n && plan.segs[(size_t)end].tensor < t0 + group; ++end)  // segments come in tensor order
+            if (plan.segs[(size_t)end].n > mx) mx = plan.segs[(size_t)end].n;
+        ExtentClass cls[kMaxExtentClasses];
+        const int n_cls = group_by_extent(end - at, mx, [&](int64_t k) { return plan.segs[(size_t)(at + k)].n; }, order.data(), cls);
+        const int64_t count = last + 1 - t0 < group ? last + 1 - t0 : group;
+        for (int c = 0; c < n_cls; ++c)
+            launches->push_back(SegLaunch{at + cls[c].begin, cls[c].count, cls[c].max_used, (int32_t)t0, (int32_t)count});
+        for (int64_t k = 0; k < end - at; ++k) {
+            const apm_segment& g = plan.segs[(size_t)(at + order[(size_t)k])];
+            recs->push_back(SegRec{g.tensor_off, g.page * plan.E + g.page_off, (int32_t)g.tensor, (int32_t)g.n});
+        }
+        at = end;
+    }
+}
+
 int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& plan, hipStream_t s) {
     if ((int64_t)plan.pages.size() > pool->desc.n_pages)
         return fail(APM_ENOMEM, "layout needs %lld pages, pool has %lld", (long long)plan.pages.size(), (long long)pool->desc.n_pages);
+    if (n > INT32_MAX) return fail(APM_EINVAL, "too many tensors");
+    std::vector<SegRec> recs;
+    std::vector<SegLaunch> launches;
+    int32_t ranges = 0;
+    order_segments(plan, &recs, &launches, &ranges);
+    struct Table {  // freed unless the pool takes it over at the end
+        SegRec* d = nullptr;
+        ~Table() { if (d) (void)hipFree(d); }
+    } table;
+    if (!recs.empty()) {
+        const size_t bytes = recs.size() * sizeof(SegRec);
+        hipError_t e = hipMalloc((void**)&table.d, bytes);
+        if (e == hipSuccess) e = hipMemcpy(table.d, recs.data(), bytes, hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(APM_ENOMEM, "uploading the layout's %zu segments failed: %s", recs.size(), hipGetErrorString(e));
+        }
+    }
     if (pool->has_layout) {  // a different layout replaces the old one: old contents would alias
         int rc = zero_regions(pool, s, false);
         if (rc != APM_OK) return rc;
@@ -153,6 +203,9 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
         pool->layout_ids[(size_t)i] = tensors[i].id;
     }
     pool->plan = std::move(plan);
+    std::swap(pool->d_segs, table.d);  // hipFree waits for kernels that still read the old one
+    pool->seg_launches.swap(launches);
+    pool->seg_ranges = ranges;
     pool->has_layout = true;
     return APM_OK;
 }
@@ -185,30 +238,30 @@ int move_segments(apm_pool* pool, int state, const apm_tensor* tensors, int64_t 
         if (tensors[i].dtype != want) return fail(APM_EINVAL, "tensor %lld: dtype %d does not match state class %d", (long long)i, tensors[i].dtype, state);
         if (!tensors[i].data) return fail(APM_EINVAL, "tensor %lld has no data pointer", (long long)i);
     }
-    const auto& segs = pool->plan.segs;
-    if (segs.empty()) return APM_OK;
-    int slot;
-    int rc = pool->ring.acquire(segs.size() * sizeof(SegDesc), &slot);
-    if (rc != APM_OK) return rc;
-    SegDesc* h = static_cast<SegDesc*>(pool->ring.h[slot]);
-    char* region = static_cast<char*>(pool->base[state]);
-    int64_t max_bytes = 0;
-    for (size_t k = 0; k < segs.size(); ++k) {
-        const apm_segment& g = segs[k];
-        char* in_tensor = static_cast<char*>(tensors[g.tensor].data) + g.tensor_off * eb;
-        char* in_page = region + (g.page * pool->desc.page_elems + g.page_off) * eb;
-        h[k].src = to_pages ? in_tensor : in_page;
-        h[k].dst = to_pages ? in_page : in_tensor;
-        h[k].nbytes = g.n * eb;
-        if (h[k].nbytes > max_bytes) max_bytes = h[k].nbytes;
+    if (pool->plan.segs.empty()) return APM_OK;
+    std::vector<uint64_t> ptrs((size_t)n);
+    for (int64_t i = 0; i < n; ++i) ptrs[(size_t)i] = reinterpret_cast<uint64_t>(tensors[i].data);
+    SegCopy c{pool->d_segs, static_cast<char*>(pool->base[state]), eb, to_pages, ptrs.data(), false};
+    // Up to kMaxSegRanges launches carry the addresses themselves.  The staging ring costs the GPU 15 us
+    // a call; each further launch costs the host 1.5 us, and a call with this many tensors takes the
+    // host longer than the GPU when they are small (1024 each, staged / carried: 800 tensors
+    // 103 / 104 us, 1300 162 / 166, 1700 211 / 217), so from the third launch on they are staged.
+    int slot = -1;
+    if (pool->seg_ranges > kMaxSegRanges) {
+        const size_t bytes = (size_t)n * sizeof(uint64_t);
+        int rc = pool->ring.acquire(bytes, &slot);
+        if (rc != APM_OK) return rc;
+        std::memcpy(pool->ring.h[slot], ptrs.data(), bytes);
+        rc = pool->ring.commit(slot, bytes, s);
+        if (rc != APM_OK) return rc;
+        c.ptrs = static_cast<const uint64_t*>(pool->ring.d[slot]);
+        c.on_device = true;
     }
-    rc = pool->ring.commit(slot, segs.size() * sizeof(SegDesc), s);
-    if (rc != APM_OK) return rc;
     {
         ScopedTiming t(pool, APM_K_SEGCOPY, s);
-        APM_HIP(launch_seg_copy(static_cast<const SegDesc*>(pool->ring.d[slot]), (int64_t)segs.size(), max_bytes, s));
+        APM_HIP(launch_seg_copy(c, pool->seg_launches.data(), (int64_t)pool->seg_launches.size(), s));
     }
-    return pool->ring.seal(slot, s);
+    return slot >= 0 ? pool->ring.seal(slot, s) : APM_OK;
 }
 
 }  // namespace

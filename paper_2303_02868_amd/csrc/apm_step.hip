@@ -91,48 +91,10 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
             for (int64_t k = 0; k < n_pages; ++k)
                 if (pages[k] >= in_use) return fail(APM_ERANGE, "pages[%lld] = %lld is not in use by the layout", (long long)k, (long long)pages[k]);
     }
-    auto class_of = [&](int64_t used) { return used * 4 > E ? 0 : used * 32 > E ? 1 : used * 512 > E ? 2 : 3; };
-    int64_t cnt[kMaxExtentClasses] = {}, mx[kMaxExtentClasses] = {};
-    for (int64_t k = 0; k < n_pages; ++k) {
-        const int64_t u = used_of(page_at(k));
-        const int c = class_of(u);
-        ++cnt[c];
-        if (u > mx[c]) mx[c] = u;
-    }
-    // A class is worth its extra launches only if it saves enough idle workgroups (counted in
-    // 1024-element update slices); otherwise it is folded into the next larger one.
-    int into[kMaxExtentClasses];
-    for (int c = 0; c < kMaxExtentClasses; ++c) into[c] = c;
-    constexpr int64_t kUpdateSpan = 1024, kWorthWorkgroups = 16384;
-    for (int c = kMaxExtentClasses - 1; c > 0; --c) {
-        if (cnt[c] == 0) continue;
-        int j = c - 1;
-        while (j > 0 && cnt[j] == 0) --j;
-        if (cnt[j] == 0) continue;
-        if (cnt[c] * ((mx[j] - mx[c]) / kUpdateSpan) < kWorthWorkgroups) {
-            for (int q = c; q < kMaxExtentClasses; ++q) if (into[q] == c) into[q] = j;
-            cnt[j] += cnt[c];
-            cnt[c] = 0;
-        }
-    }
-    int64_t begin[kMaxExtentClasses];
-    for (int64_t c = 0, at = 0; c < kMaxExtentClasses; ++c) {
-        begin[c] = at;
-        if (cnt[c] > 0) L.cls[L.n_cls++] = ExtentClass{at, cnt[c], mx[c]};
-        at += cnt[c];
-    }
     std::vector<int64_t> order((size_t)n_pages);
+    L.n_cls = group_by_extent(n_pages, E, [&](int64_t k) { return used_of(page_at(k)); }, order.data(), L.cls);
     bool identity = true;
-    {
-        int64_t fill[kMaxExtentClasses];
-        for (int c = 0; c < kMaxExtentClasses; ++c) fill[c] = begin[c];
-        for (int64_t k = 0; k < n_pages; ++k) {
-            const int c = into[class_of(used_of(page_at(k)))];
-            const int64_t pos = fill[c]++;
-            order[(size_t)pos] = k;
-            if (pos != k) identity = false;
-        }
-    }
+    for (int64_t k = 0; identity && k < n_pages; ++k) identity = order[(size_t)k] == k;
 
     // A list that is an ascending run launched in the caller's order needs no indirection;
     // anything else is staged to the device: page indices, then the output indices.

@@ -28,3 +28,23 @@ def test_pack_and_unpack_at_every_address_are_bit_exact_and_write_nothing_else(d
             assert torch.equal(out[dst_off:dst_off + n * eb], raw[src_off:src_off + n * eb]), (src_off, dst_off)
             assert (out[:dst_off] == 77).all() and (out[dst_off + n * eb:] == 77).all(), (src_off, dst_off)
         pool.destroy()
+
+
+@pytest.mark.parametrize("n_t", [1, 439, 440, 441, 880, 881, 2500])
+def test_pack_and_unpack_of_many_tensors_are_bit_exact(n_t):
+    """Tensor counts around what one launch carries in its arguments and around the count from which
+    the addresses are staged; empty tensors, tiny ones and ones of several pages, in mixed order."""
+    E = 512
+    numels = [(0, 3, E - 1, E, 2 * E + 5, 17)[(7 * k) % 6] for k in range(n_t)]
+    numels[-1] = E + 9
+    off = [sum(numels[:k]) for k in range(n_t)]
+    src = torch.arange(sum(numels), device=DEV, dtype=torch.float32)
+    dst = torch.full_like(src, -1.0)
+    n_pages = sum(-(-n // E) for n in numels)
+    pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n_pages, state_mask=1)
+    lists = [apm.make_tensors(numels, apm.APM_F32, [t.data_ptr() + 4 * o for o in off]) for t in (src, dst)]
+    apm.apm_pack_tensors(pool, apm.APM_P32, lists[0], n_t)
+    apm.apm_unpack(pool, apm.APM_P32, lists[1], n_t)
+    torch.cuda.synchronize()
+    assert torch.equal(src, dst)
+    pool.destroy()
