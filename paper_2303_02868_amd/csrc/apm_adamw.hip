@@ -17,6 +17,8 @@
 // slices that start beyond the page's used extent exit at once.  The page table (`used`) is read
 // on the device; the host, which knows the extents from the layout, only sizes the grids (pages
 // grouped into extent classes) so that few workgroups are launched for nothing.
+#include <cstring>
+
 #include "apm_internal.h"
 
 namespace apm {
@@ -325,6 +327,80 @@ __global__ __launch_bounds__(kThreads) void apm_page_meta_kernel(FinalizeArgs a)
     pm.spage = a.state_pages ? a.state_pages[i] : a.state_first + i;
     pm.pad = 0;
     a.meta[i] = pm;
+}
+
+// Brings a call's page list and tensor addresses to where the kernels below read them, one thread per
+// listed page.  The words travel in the kernel arguments (an upload from pinned memory would cost
+// an extra kernel and two event packets, 20 us and more of idle GPU per call: 124 M parameters from
+// and to tensors 582 us a call staged that way, 560 like this; 5 M in small pages with clipping 48 and 41); bound by launch latency.
+struct StageArgs {
+    const int32_t* used;
+    const int64_t* pages;       // positions' pages, or nullptr: first + i
+    int64_t first;
+    int64_t n_listed;
+    const TenantRec* tenants;
+    PageSegs* segs;
+    int64_t* list;              // written from the list words
+    int32_t* out;
+    PageMeta* meta;             // nullptr: left to the reduce pass
+    const uint64_t* words;      // list, g, q words, unless they follow inline
+    int64_t list_begin;         // the list words are those of positions [list_begin, + list_n)
+    int32_t list_n;
+    int32_t t_begin, t_n;       // the g / q words are those of tensors [t_begin, + t_n)
+    int32_t has_g, has_q;
+};
+struct StageArgsInline {
+    StageArgs a;
+    uint64_t word[kArgWords];
+};
+
+template <class Args>
+__global__ __launch_bounds__(kThreads) void apm_stage_kernel(Args args) {
+    const StageArgs* ap;
+    if constexpr (sizeof(Args) > sizeof(StageArgs)) ap = &args.a;
+    else ap = &args;
+    const StageArgs& a = *ap;
+    auto word = [&](int64_t k) -> uint64_t {
+        if constexpr (sizeof(Args) > sizeof(StageArgs)) return args.word[k];
+        else return a.words[k];
+    };
+    int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    int64_t page;
+    if (a.list_n > 0) {
+        if (i >= a.list_n) return;
+        const uint64_t w = word(i);
+        i += a.list_begin;
+        page = (int64_t)(uint32_t)w;
+        a.list[i] = page;
+        a.out[i] = (int32_t)(w >> 32);
+    } else {
+        if (i >= a.n_listed) return;
+        page = a.pages ? a.pages[i] : a.first + i;
+    }
+    if (a.meta && a.t_begin == 0) {
+        PageMeta pm;
+        pm.used = a.used[page];
+        pm.scale = 1.0f;
+        pm.gpage = pm.spage = page;
+        pm.pad = 0;
+        a.meta[i] = pm;
+    }
+    if (a.t_n == 0) return;
+    const TenantRec t = a.tenants[page];
+    PageSegs* s = a.segs + i;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int64_t at = t.tensor[k] - a.t_begin;
+        if (t.tensor[k] < 0) {
+            s->off[k] = 0;
+            s->n[k] = 0;
+        } else if (at >= 0 && at < a.t_n) {
+            s->off[k] = t.off[k];
+            s->n[k] = t.n[k];
+            if (a.has_g) s->g[k] = reinterpret_cast<const uint16_t*>(word(a.list_n + at)) + t.tensor_off[k];
+            if (a.has_q) s->q[k] = reinterpret_cast<uint16_t*>(word(a.list_n + (a.has_g ? a.t_n : 0) + at)) + t.tensor_off[k];
+        }
+    }
 }
 
 struct UpdateArgs {
@@ -657,6 +733,55 @@ hipError_t launch_prepare(const AdamwLaunch& L, hipStream_t s) {
     hipLaunchKernelGGL(apm_page_meta_kernel, dim3((unsigned)((L.n_listed + kThreads - 1) / kThreads)),
                        dim3(kThreads), 0, s, f);
     return hipGetLastError();
+}
+
+int64_t stage_launches(const StageCall& c, int64_t n_listed) {
+    const int64_t n_list = c.list ? n_listed : 0, lists = (c.g_ptrs != nullptr) + (c.q_ptrs != nullptr);
+    if (n_list + lists * c.n_tensors <= kArgWords) return 1;
+    const int64_t per = lists ? kArgWords / lists : kArgWords;
+    return (n_list + kArgWords - 1) / kArgWords + (lists ? (c.n_tensors + per - 1) / per : 0);
+}
+
+hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s) {
+    const bool has_g = c.g_ptrs != nullptr, has_q = c.q_ptrs != nullptr;
+    const int64_t n_list = c.list ? L.n_listed : 0, n_t = has_g || has_q ? c.n_tensors : 0;
+    StageArgsInline in;
+    StageArgs& a = in.a;
+    a = StageArgs{L.used, c.list ? c.d_list : L.grad_pages, L.grad_first, L.n_listed, c.tenants, c.d_segs,
+                  c.d_list, c.d_out, c.meta ? L.meta : nullptr, c.d_words, 0, 0, 0, 0, has_g, has_q};
+    auto go = [&](int64_t list_begin, int64_t list_n, int64_t t_begin, int64_t t_n) -> hipError_t {
+        a.list_begin = list_begin;
+        a.list_n = (int32_t)list_n;
+        a.t_begin = (int32_t)t_begin;
+        a.t_n = (int32_t)t_n;
+        const int64_t threads = list_n > 0 ? list_n : L.n_listed;
+        const dim3 grid((unsigned)((threads + kThreads - 1) / kThreads));
+        if (c.d_words) {
+            hipLaunchKernelGGL(apm_stage_kernel<StageArgs>, grid, dim3(kThreads), 0, s, a);
+        } else {
+            uint64_t* w = in.word;
+            if (list_n > 0) std::memcpy(w, c.list + list_begin, (size_t)list_n * sizeof(uint64_t));
+            w += list_n;
+            if (t_n > 0 && has_g) std::memcpy(w, c.g_ptrs + t_begin, (size_t)t_n * sizeof(uint64_t));
+            if (has_g) w += t_n;
+            if (t_n > 0 && has_q) std::memcpy(w, c.q_ptrs + t_begin, (size_t)t_n * sizeof(uint64_t));
+            hipLaunchKernelGGL(apm_stage_kernel<StageArgsInline>, grid, dim3(kThreads), 0, s, in);
+        }
+        return hipGetLastError();
+    };
+    if (c.d_words || stage_launches(c, L.n_listed) == 1) return go(0, n_list, 0, n_t);
+    // list words first: the launches with the addresses read the list that they wrote
+    for (int64_t k = 0; k < n_list; k += kArgWords) {
+        hipError_t e = go(k, n_list - k < kArgWords ? n_list - k : kArgWords, 0, 0);
+        if (e != hipSuccess) return e;
+    }
+    if (n_list > 0) a.meta = nullptr;  // filled by the list launches
+    const int64_t per = has_g && has_q ? kArgWords / 2 : kArgWords;
+    for (int64_t k = 0; k < n_t; k += per) {
+        hipError_t e = go(0, 0, k, n_t - k < per ? n_t - k : per);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {

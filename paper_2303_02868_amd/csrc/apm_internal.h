@@ -113,6 +113,16 @@ struct PageSegs {
     uint16_t* q[2];
 };
 
+// The tenants of a page as the layout has them: tenant k is n[k] elements of tensor tensor[k] from
+// tensor_off[k] on, at page element off[k].  The table depends on the layout alone and is uploaded
+// with it; a fused call only brings the tensors' addresses.
+struct TenantRec {
+    int64_t tensor_off[2];
+    int32_t off[2];
+    int32_t n[2];
+    int32_t tensor[2];  // -1: no such tenant
+};
+
 // What one listed page needs in the update kernel, gathered into one 32-byte record so that a
 // workgroup fetches it with a single scalar load: written per call by the finalize kernel (after a
 // reduce pass) or by the prepare kernel (no reduce pass).
@@ -167,6 +177,25 @@ struct AdamwLaunch {
 // pass (fills meta with scale 1).  One of the two must precede launch_adamw on the same stream.
 hipError_t launch_grad_reduce(const AdamwLaunch& a, hipStream_t s);
 hipError_t launch_prepare(const AdamwLaunch& a, hipStream_t s);
+
+// What a call brings to the device besides scalars: its page list (a word per position: page, and the
+// index of its outputs in the upper half) and its tensors' addresses.  Written to where the step's
+// kernels read it (list / out / segs) by apm_stage_kernel.
+struct StageCall {
+    const uint64_t* list;         // n_listed words, or nullptr: positions as L.grad_pages / L.grad_first say
+    const uint64_t* g_ptrs;       // n_tensors addresses each, nullptr if not gathered / scattered
+    const uint64_t* q_ptrs;
+    int64_t n_tensors;
+    const TenantRec* tenants;
+    int64_t* d_list;              // written if `list`
+    int32_t* d_out;
+    PageSegs* d_segs;             // written if g_ptrs or q_ptrs
+    bool meta;                    // also fill L.meta with scale 1 (no reduce pass follows)
+    const uint64_t* d_words;      // list, g_ptrs, q_ptrs one after the other in device memory, or nullptr
+};
+// Launches it takes to carry a call's words in kernel arguments (StageCall::d_words == nullptr).
+int64_t stage_launches(const StageCall& c, int64_t n_listed);
+hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s);
 hipError_t launch_adamw(const AdamwLaunch& a, hipStream_t s);
 hipError_t launch_grad_accum(uint16_t* acc, const uint16_t* g16, const int32_t* used,
                              const int64_t* d_pages, int64_t first, int64_t n_listed, int64_t E,
@@ -239,9 +268,23 @@ struct apm_pool {
     apm::SegRec* d_segs = nullptr;  // the layout's segments, ordered as seg_launches lists them
     std::vector<apm::SegLaunch> seg_launches;
     int32_t seg_ranges = 0;         // groups of kArgWords tensors they are split into
+    apm::TenantRec* d_tenants = nullptr;  // by page in use
+    // All pages in use, grouped by extent (see group_by_extent): launch order, in host and device
+    // memory; d_order_out = the same as 32-bit output indices.  order_run: the order is 0, 1, 2, ...
+    std::vector<int64_t> order;
+    int64_t* d_order = nullptr;
+    int32_t* d_order_out = nullptr;
+    apm::ExtentClass order_cls[apm::kMaxExtentClasses] = {};
+    int order_n_cls = 0;
+    bool order_run = false;
     double* d_partials = nullptr;   // reduce scratch, n_pages * S
     uint32_t* d_nzflags = nullptr;
     apm::PageMeta* d_meta = nullptr;  // n_pages entries
+    // what a call's list and tensors come to (apm_stage_kernel), n_pages entries each, allocated on
+    // first use; like the scratch above they belong to the one step that is running on the pool
+    int64_t* d_list = nullptr;
+    int32_t* d_list_out = nullptr;
+    apm::PageSegs* d_page_segs = nullptr;
     int32_t S = 0;
     apm::StageRing ring;
 
@@ -280,7 +323,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
                  const apm_hyper* hyper, const uint16_t* g16_override, float* grad_norm,
                  uint8_t* skip_mask, hipStream_t stream, const apm_tensor* grad_tensors = nullptr,
                  const apm_tensor* p16_tensors = nullptr, int64_t n_tensors = 0);
-int ensure_scratch(apm_pool* pool);
+int ensure_scratch(apm_pool* pool, bool list = false, bool tensors = false);
 // Allocates the ping-pong gradient halves, the events and the update stream of the delayed path.
 // caller != nullptr-able: the stream the producer works on; the update stream is chosen so that
 // its kernels run beside that stream's (see make_overlapping_stream).

@@ -58,8 +58,7 @@ void StageRing::destroy() {
     }
 }
 
-int ensure_scratch(apm_pool* pool) {
-    if (pool->d_partials && pool->d_nzflags && pool->d_meta) return APM_OK;
+int ensure_scratch(apm_pool* pool, bool list, bool tensors) {
     const size_t n = (size_t)pool->desc.n_pages * (size_t)pool->S;
     auto get = [](void** p, size_t bytes) -> int {  // a buffer an earlier, failed attempt got is kept
         if (*p) return APM_OK;
@@ -71,7 +70,11 @@ int ensure_scratch(apm_pool* pool) {
     };
     int rc = get((void**)&pool->d_partials, n * sizeof(double));
     if (rc == APM_OK) rc = get((void**)&pool->d_nzflags, n * sizeof(uint32_t));
-    if (rc == APM_OK) rc = get((void**)&pool->d_meta, (size_t)pool->desc.n_pages * sizeof(PageMeta));
+    const size_t n_pages = (size_t)pool->desc.n_pages;
+    if (rc == APM_OK) rc = get((void**)&pool->d_meta, n_pages * sizeof(PageMeta));
+    if (rc == APM_OK && list) rc = get((void**)&pool->d_list, n_pages * sizeof(int64_t));
+    if (rc == APM_OK && list) rc = get((void**)&pool->d_list_out, n_pages * sizeof(int32_t));
+    if (rc == APM_OK && tensors) rc = get((void**)&pool->d_page_segs, n_pages * sizeof(PageSegs));
     return rc;
 }
 
@@ -117,9 +120,15 @@ void free_pool(apm_pool* pool) {
     }
     if (pool->d_used) (void)hipFree(pool->d_used);
     if (pool->d_segs) (void)hipFree(pool->d_segs);
+    if (pool->d_tenants) (void)hipFree(pool->d_tenants);
+    if (pool->d_order) (void)hipFree(pool->d_order);
+    if (pool->d_order_out) (void)hipFree(pool->d_order_out);
     if (pool->d_partials) (void)hipFree(pool->d_partials);
     if (pool->d_nzflags) (void)hipFree(pool->d_nzflags);
     if (pool->d_meta) (void)hipFree(pool->d_meta);
+    if (pool->d_list) (void)hipFree(pool->d_list);
+    if (pool->d_list_out) (void)hipFree(pool->d_list_out);
+    if (pool->d_page_segs) (void)hipFree(pool->d_page_segs);
     pool->ring.destroy();
     for (auto& t : pool->timed) {
         (void)hipEventDestroy(t.begin);
@@ -174,19 +183,38 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     std::vector<SegLaunch> launches;
     int32_t ranges = 0;
     order_segments(plan, &recs, &launches, &ranges);
-    struct Table {  // freed unless the pool takes it over at the end
-        SegRec* d = nullptr;
-        ~Table() { if (d) (void)hipFree(d); }
-    } table;
-    if (!recs.empty()) {
-        const size_t bytes = recs.size() * sizeof(SegRec);
-        hipError_t e = hipMalloc((void**)&table.d, bytes);
-        if (e == hipSuccess) e = hipMemcpy(table.d, recs.data(), bytes, hipMemcpyHostToDevice);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(APM_ENOMEM, "uploading the layout's %zu segments failed: %s", recs.size(), hipGetErrorString(e));
-        }
+    const size_t n_in_use = plan.pages.size();
+    std::vector<TenantRec> tenants(n_in_use, TenantRec{{0, 0}, {0, 0}, {0, 0}, {-1, -1}});
+    for (const apm_segment& g : plan.segs) {  // a page's tenants appear in offset order
+        TenantRec& t = tenants[(size_t)g.page];
+        const int k = t.tensor[0] < 0 ? 0 : 1;
+        t.tensor_off[k] = g.tensor_off;
+        t.off[k] = (int32_t)g.page_off;
+        t.n[k] = (int32_t)g.n;
+        t.tensor[k] = (int32_t)g.tensor;
     }
+    std::vector<int64_t> order(n_in_use);
+    ExtentClass cls[kMaxExtentClasses] = {};
+    const int n_cls = group_by_extent((int64_t)n_in_use, plan.E, [&](int64_t k) { return plan.pages[(size_t)k].used; }, order.data(), cls);
+    std::vector<int32_t> order_out(order.begin(), order.end());
+    // Device copies of the tables; freed unless the pool takes them over at the end.
+    struct Tables {
+        void* d[4] = {};
+        ~Tables() { for (void* x : d) if (x) (void)hipFree(x); }
+    } tables;
+    auto upload = [](void** d, const void* h, size_t bytes) -> int {
+        if (bytes == 0) return APM_OK;
+        hipError_t e = hipMalloc(d, bytes);
+        if (e == hipSuccess) e = hipMemcpy(*d, h, bytes, hipMemcpyHostToDevice);
+        if (e == hipSuccess) return APM_OK;
+        (void)hipGetLastError();
+        return fail(APM_ENOMEM, "uploading %zu bytes of the layout's tables failed: %s", bytes, hipGetErrorString(e));
+    };
+    int rc_up = upload(&tables.d[0], recs.data(), recs.size() * sizeof(SegRec));
+    if (rc_up == APM_OK) rc_up = upload(&tables.d[1], tenants.data(), n_in_use * sizeof(TenantRec));
+    if (rc_up == APM_OK) rc_up = upload(&tables.d[2], order.data(), n_in_use * sizeof(int64_t));
+    if (rc_up == APM_OK) rc_up = upload(&tables.d[3], order_out.data(), n_in_use * sizeof(int32_t));
+    if (rc_up != APM_OK) return rc_up;
     if (pool->has_layout) {  // a different layout replaces the old one: old contents would alias
         int rc = zero_regions(pool, s, false);
         if (rc != APM_OK) return rc;
@@ -203,7 +231,21 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
         pool->layout_ids[(size_t)i] = tensors[i].id;
     }
     pool->plan = std::move(plan);
-    std::swap(pool->d_segs, table.d);  // hipFree waits for kernels that still read the old one
+    auto take = [&](auto*& mine, int k) {  // the old table goes with `tables`; hipFree waits for its readers
+        void* old = mine;
+        mine = static_cast<std::remove_reference_t<decltype(mine)>>(tables.d[k]);
+        tables.d[k] = old;
+    };
+    take(pool->d_segs, 0);
+    take(pool->d_tenants, 1);
+    take(pool->d_order, 2);
+    take(pool->d_order_out, 3);
+    pool->order.swap(order);
+    pool->order_n_cls = n_cls;
+    pool->order_run = true;
+    for (int c = 0; c < kMaxExtentClasses; ++c) pool->order_cls[c] = cls[c];
+    for (size_t k = 0; k < n_in_use; ++k)
+        if (pool->order[k] != (int64_t)k) pool->order_run = false;
     pool->seg_launches.swap(launches);
     pool->seg_ranges = ranges;
     pool->has_layout = true;

@@ -2,6 +2,7 @@
 // one-step-stale (delayed) step.
 #include <chrono>
 #include <cmath>
+#include <cstring>
 
 #include "apm_internal.h"
 
@@ -42,6 +43,11 @@ int check_fused_list(const apm_pool* pool, const apm_tensor* t, int64_t n, const
     }
     return APM_OK;
 }
+
+// Launches that may carry a call's page list and tensor addresses in their arguments; beyond that
+// they are staged through the pinned ring.  The ring costs the GPU an upload and two event packets,
+// 20 us and more between one call's update and the next one's; a stage launch costs 3 us.
+constexpr int64_t kMaxStageLaunches = 4;
 }  // namespace
 
 int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t step,
@@ -91,63 +97,51 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
             for (int64_t k = 0; k < n_pages; ++k)
                 if (pages[k] >= in_use) return fail(APM_ERANGE, "pages[%lld] = %lld is not in use by the layout", (long long)k, (long long)pages[k]);
     }
-    std::vector<int64_t> order((size_t)n_pages);
-    L.n_cls = group_by_extent(n_pages, E, [&](int64_t k) { return used_of(page_at(k)); }, order.data(), L.cls);
-    bool identity = true;
-    for (int64_t k = 0; identity && k < n_pages; ++k) identity = order[(size_t)k] == k;
-
-    // A list that is an ascending run launched in the caller's order needs no indirection;
-    // anything else is staged to the device: page indices, then the output indices.
-    const int64_t first = page_at(0);
-    bool run = identity;
-    for (int64_t k = 0; run && k < n_pages; ++k)
-        if (page_at(k) != first + k) run = false;
-    int ring_slots[2], n_ring_slots = 0;  // sealed once the kernels that read them are enqueued
-    const int64_t* d_list = nullptr;
-    if (!run) {
-        const size_t list_bytes = (size_t)n_pages * sizeof(int64_t);
-        const size_t bytes = list_bytes + (size_t)n_pages * sizeof(int32_t);
-        int slot;
-        rc = pool->ring.acquire(bytes, &slot);
-        if (rc != APM_OK) return rc;
-        int64_t* h = static_cast<int64_t*>(pool->ring.h[slot]);
-        int32_t* ho = reinterpret_cast<int32_t*>(static_cast<char*>(pool->ring.h[slot]) + list_bytes);
-        for (int64_t k = 0; k < n_pages; ++k) {
-            h[k] = page_at(order[(size_t)k]);
-            ho[k] = (int32_t)order[(size_t)k];
-        }
-        rc = pool->ring.commit(slot, bytes, stream);
-        if (rc != APM_OK) return rc;
-        ring_slots[n_ring_slots++] = slot;
-        d_list = static_cast<const int64_t*>(pool->ring.d[slot]);
-        if (!identity) L.out_index = reinterpret_cast<const int32_t*>(static_cast<const char*>(pool->ring.d[slot]) + list_bytes);
+    // The whole layout in its own order is the common case: its launch order came with the layout.
+    const bool whole = !pages && n_pages == in_use;
+    std::vector<int64_t> order;
+    bool run = whole && pool->order_run;  // an ascending run launched in the caller's order needs no indirection
+    if (whole) {
+        L.n_cls = pool->order_n_cls;
+        for (int c = 0; c < L.n_cls; ++c) L.cls[c] = pool->order_cls[c];
+    } else {
+        order.resize((size_t)n_pages);
+        L.n_cls = group_by_extent(n_pages, E, [&](int64_t k) { return used_of(page_at(k)); }, order.data(), L.cls);
+        run = true;
+        for (int64_t k = 0; run && k < n_pages; ++k) run = order[(size_t)k] == k && page_at(k) == page_at(0) + k;
     }
+    const bool tensors = grad_tensors || p16_tensors;
+    const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
+    rc = ensure_scratch(pool, !run && !whole, tensors);
+    if (rc != APM_OK) return rc;
 
-    if (grad_tensors || p16_tensors) {
-        // One PageSegs entry per list position, rebuilt per call: the tensors are caller-owned and
-        // their addresses may change from step to step.
-        const size_t n_in_use = pool->plan.pages.size();
-        std::vector<PageSegs> by_page(n_in_use);
-        std::vector<uint8_t> filled(n_in_use, 0);
-        for (const apm_segment& sg : pool->plan.segs) {  // a page's tenants appear in offset order
-            PageSegs& e = by_page[(size_t)sg.page];
-            const int k = filled[(size_t)sg.page]++;
-            e.off[k] = (int32_t)sg.page_off;
-            e.n[k] = (int32_t)sg.n;
-            if (grad_tensors) e.g[k] = static_cast<const uint16_t*>(grad_tensors[sg.tensor].data) + sg.tensor_off;
-            if (p16_tensors) e.q[k] = static_cast<uint16_t*>(p16_tensors[sg.tensor].data) + sg.tensor_off;
-        }
-        int slot;
-        rc = pool->ring.acquire((size_t)n_pages * sizeof(PageSegs), &slot);
+    // What the kernels need of this call's list and tensors, as words (see StageCall).
+    StageCall sc{};
+    const int64_t n_list = run || whole ? 0 : n_pages;
+    const int64_t n_g = grad_tensors ? n_tensors : 0, n_q = p16_tensors ? n_tensors : 0;
+    std::vector<uint64_t> words((size_t)(n_list + n_g + n_q));
+    for (int64_t k = 0; k < n_list; ++k)
+        words[(size_t)k] = (uint64_t)page_at(order[(size_t)k]) | (uint64_t)order[(size_t)k] << 32;
+    for (int64_t i = 0; i < n_g; ++i) words[(size_t)(n_list + i)] = reinterpret_cast<uint64_t>(grad_tensors[i].data);
+    for (int64_t i = 0; i < n_q; ++i) words[(size_t)(n_list + n_g + i)] = reinterpret_cast<uint64_t>(p16_tensors[i].data);
+    sc.list = n_list ? words.data() : nullptr;
+    sc.g_ptrs = n_g ? words.data() + n_list : nullptr;
+    sc.q_ptrs = n_q ? words.data() + n_list + n_g : nullptr;
+    sc.n_tensors = tensors ? n_tensors : 0;
+    sc.tenants = pool->d_tenants;
+    sc.d_list = pool->d_list;
+    sc.d_out = pool->d_list_out;
+    sc.d_segs = pool->d_page_segs;
+    sc.meta = !need_reduce;
+    int ring_slot = -1;
+    if (stage_launches(sc, n_pages) > kMaxStageLaunches) {
+        const size_t bytes = words.size() * sizeof(uint64_t);
+        rc = pool->ring.acquire(bytes, &ring_slot);
         if (rc != APM_OK) return rc;
-        PageSegs* h = static_cast<PageSegs*>(pool->ring.h[slot]);
-        for (int64_t k = 0; k < n_pages; ++k) h[k] = by_page[(size_t)page_at(order[(size_t)k])];
-        rc = pool->ring.commit(slot, (size_t)n_pages * sizeof(PageSegs), stream);
+        std::memcpy(pool->ring.h[ring_slot], words.data(), bytes);
+        rc = pool->ring.commit(ring_slot, bytes, stream);
         if (rc != APM_OK) return rc;
-        ring_slots[n_ring_slots++] = slot;
-        L.segs = static_cast<const PageSegs*>(pool->ring.d[slot]);
-        L.gather = grad_tensors != nullptr;
-        L.scatter = p16_tensors != nullptr;
+        sc.d_words = static_cast<const uint64_t*>(pool->ring.d[ring_slot]);
     }
     L.p32 = static_cast<float*>(pool->base[APM_P32]);
     L.m32 = static_cast<float*>(pool->base[APM_M32]);
@@ -155,32 +149,39 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     L.g16 = g16_override ? g16_override : static_cast<const uint16_t*>(pool->base[APM_G16]);
     L.p16 = static_cast<uint16_t*>(pool->base[APM_P16]);
     L.used = pool->d_used;
-    L.state_pages = L.grad_pages = d_list;
-    L.state_first = L.grad_first = first;
+    if (!run) {
+        L.state_pages = L.grad_pages = whole ? pool->d_order : pool->d_list;
+        L.out_index = whole ? pool->d_order_out : pool->d_list_out;
+    }
+    L.state_first = L.grad_first = page_at(0);
+    L.gather = grad_tensors != nullptr;
+    L.scatter = p16_tensors != nullptr;
+    L.segs = tensors ? pool->d_page_segs : nullptr;
     L.n_listed = n_pages;
     L.E = E;
     L.S = pool->S;
     L.grad_norm = grad_norm;
     L.skip_mask = skip_mask;
-    const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
-    rc = ensure_scratch(pool);
-    if (rc != APM_OK) return rc;
     L.meta = pool->d_meta;
+    const bool staged = n_list > 0 || tensors;
+    if (staged) {
+        APM_HIP(launch_stage(L, sc, stream));
+        if (ring_slot >= 0) {  // only the stage kernel reads the slot
+            rc = pool->ring.seal(ring_slot, stream);
+            if (rc != APM_OK) return rc;
+        }
+    }
     if (need_reduce) {
         L.partials = pool->d_partials;
         L.nzflags = pool->d_nzflags;
         ScopedTiming t(pool, APM_K_REDUCE, stream);
         APM_HIP(launch_grad_reduce(L, stream));
-    } else {
+    } else if (!staged) {
         APM_HIP(launch_prepare(L, stream));
     }
     {
         ScopedTiming t(pool, APM_K_UPDATE, stream);
         APM_HIP(launch_adamw(L, stream));
-    }
-    for (int k = 0; k < n_ring_slots; ++k) {
-        rc = pool->ring.seal(ring_slots[k], stream);
-        if (rc != APM_OK) return rc;
     }
     return APM_OK;
 }

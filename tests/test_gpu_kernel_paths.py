@@ -48,3 +48,48 @@ def test_pack_and_unpack_of_many_tensors_are_bit_exact(n_t):
     torch.cuda.synchronize()
     assert torch.equal(src, dst)
     pool.destroy()
+
+
+@pytest.mark.parametrize("clip", [0.0, 0.01])
+@pytest.mark.parametrize("n_t,listed", [(1, "all"), (147, "odd"), (219, "all"), (221, "reversed"), (441, "all"), (450, "reversed"),
+                                        (700, "odd"), (900, "all"), (1500, "reversed")])
+def test_fused_step_equals_the_page_step_for_any_tensor_count_and_list(n_t, listed, clip):
+    """Gradients read from / parameters written to tensors against the same gradients packed into
+    pages: same kernels, so the same bits.  Counts around what one stage launch carries (440 words:
+    a listed page, a gradient address, a parameter address each take one), several launches, the ring."""
+    E = 512
+    numels = [(3, E - 1, E, 2 * E + 5, 17)[(3 * k) % 5] for k in range(n_t)]
+    off = [0]
+    for n in numels:
+        off.append(off[-1] + (n + 7) // 8 * 8)
+    gen = torch.Generator(device=DEV).manual_seed(n_t)
+    g = (torch.randn(off[-1], device=DEV, generator=gen) * 1e-3).bfloat16()
+    p0 = torch.randn(off[-1], device=DEV, generator=gen) * 0.02
+    lst = lambda t: apm.make_tensors(numels, apm.APM_F32 if t.dtype == torch.float32 else apm.APM_BF16,  # noqa: E731
+                                     [t.data_ptr() + t.element_size() * o for o in off[:-1]])
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, clip, apm.APM_SKIP_NONE)
+    got = []
+    for fused in (False, True):
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, sum(-(-n // E) for n in numels) + 3)
+        apm.apm_pack_tensors(pool, apm.APM_P32, lst(p0), n_t)
+        n = apm.lib().apm_pool_pages_in_use(pool.handle)
+        pages = {"all": None, "odd": list(range(1, n, 2)), "reversed": list(range(n))[::-1]}[listed]
+        count = n if pages is None else len(pages)
+        norm = torch.zeros(count, device=DEV) if count else torch.zeros(1, device=DEV)
+        q = torch.zeros_like(g)
+        if fused:
+            apm.apm_page_adamw_step_fused(pool, pages, count, 3, hyper, lst(g), lst(q), n_t, norm, None)
+        else:
+            apm.apm_pack_tensors(pool, apm.APM_G16, lst(g), n_t)
+            apm.apm_page_adamw_step(pool, pages, count, 3, hyper, norm, None)
+            apm.apm_unpack(pool, apm.APM_P16, lst(q), n_t)
+        out = [norm, q]
+        for st in (apm.APM_P32, apm.APM_M32, apm.APM_V32):
+            out.append(torch.zeros_like(p0))
+            apm.apm_unpack(pool, st, lst(out[-1]), n_t)
+        torch.cuda.synchronize()
+        got.append(out)
+        pool.destroy()
+    assert got[0][2].ne(p0).any() or listed == "odd"
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
