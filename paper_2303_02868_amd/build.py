@@ -17,6 +17,7 @@ HEADERS = [os.path.join(CSRC, "apm_internal.h"), os.path.join(CSRC, "apm_io.h"),
 # Packed-fp32 instruction selection is switched off for all device code.
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-kernarg-preload-count=14",  # leading scalar kernel arguments arrive in registers
          "-Wall", "-Wno-unused-command-line-argument",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 

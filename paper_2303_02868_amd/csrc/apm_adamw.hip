@@ -1,7 +1,7 @@
 // Page AdamW kernels for gfx950:
 //   apm_grad_reduce_kernel    per (page, slice) sum of squares (fp64) and any-nonzero of g16
 //   apm_grad_finalize_kernel  per page: norm, clip scale, skip decision -> the page's record
-//   apm_page_meta_kernel      the page records when no reduce pass is needed
+//   apm_page_recs_kernel      the page records when no reduce pass is needed
 //   apm_adamw_kernel          the fused update (optionally gathering g16 from / scattering p16 to
 //                             the caller's tensors), one workgroup per page slice
 //   apm_adamw_stride_kernel   the same slice body run by a fixed, small number of wavefronts that
@@ -74,88 +74,77 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float x) {
 #ifndef APM_REDUCE_U
 #define APM_REDUCE_U 4          // 128-bit loads in flight per lane in the reduce kernel
 #endif
-#ifndef APM_UPDATE_THREADS
-#define APM_UPDATE_THREADS 64   // one wavefront per page slice
-#endif
+// The update's wavefronts are workgroups of their own, one per page slice of U vectors per lane and
+// fp32 class, and request dynamic LDS for no purpose other than capping how many of them a CU
+// (160 KiB) holds: with four read and four write streams per wavefront, more resident wavefronts
+// lower the achieved HBM bandwidth, and short wavefronts started in address order keep the streams
+// closer together than long ones.  Measured on 1.07 G elements, TB/s, U = 1 at 16 / 12 / 10 wavefronts per
+// CU: 6.43 / 6.60 / 6.55; U = 2 at 10 / 8 / 6: 6.25 / 6.31 / 6.45; U = 4 at 5 / 4: 6.32 / 6.33; a
+// fixed grid of wavefronts that walk the slices with their next loads in flight: 5.3.
+// Whole calls, U = 4 at 5, U = 2 at 8, U = 1 at 12, U = 1 at 11: 124 M parameters 563 / 580 / 548 / 544 us, 1.3 B with
+// clipping 6308 / 6361 / 6050 / 5990.
 #ifndef APM_UPDATE_U
-#define APM_UPDATE_U 4          // 128-bit vectors per lane and fp32 class
-#endif
-#ifndef APM_UPDATE_SLICES_SKIP
-// Page slices one workgroup walks through when pages may be skipped on the device
-// (APM_SKIP_UNTOUCHED).  Dense launches use one slice per workgroup, which is fastest when every
-// workgroup has work (5.9 TB/s against 5.7 / 5.3 with 2 / 4 slices); when 7 of 8 pages are
-// skipped, the workgroups that only find that out and leave dominate, and 4 slices per workgroup
-// cut their number (MoE workload: update 3.03 ms -> 2.61 ms).
-#define APM_UPDATE_SLICES_SKIP 4
-#endif
-#ifndef APM_HOIST_LOADS
-#define APM_HOIST_LOADS 1
+#define APM_UPDATE_U 1
 #endif
 #ifndef APM_UPDATE_LDS
-// Dynamic LDS requested per workgroup for no purpose other than capping residency at
-// 160 KiB / 32 KiB = 5 wavefronts per CU: with four read and four write streams per wavefront,
-// more resident wavefronts lower the achieved HBM bandwidth.  Measured on the 1.3 B-parameter
-// workload with the single-block slice body (16 loads, then 16 stores in flight per wavefront):
-// 5.5 TB/s at 16 wavefronts per CU, 5.6 at 13, 5.9 at 10, 5.7-6.1 at 8, 6.1 at 6, 6.3 at 5,
-// 6.0-6.3 at 4, 6.1 at 3, 5.1 at 2.  (The earlier body, whose wavefronts waited for each vector's
-// stores, peaked at 8.)
-#define APM_UPDATE_LDS 32768
+#define APM_UPDATE_LDS 14848
 #endif
+// When pages may be skipped on the device (APM_SKIP_UNTOUCHED), workgroups that only find that out and
+// leave dominate; kSkipSlices longer slices per workgroup cut their number (7 of 8 of 1046 pages
+// skipped: 1046 us a call, 1079 with four of U = 1).
+constexpr int kSkipU = 4, kSkipSlices = 4, kSkipLds = 32768;
 
 // Gradient elements [e, e+8) of a page, read from its tenant tensors; elements that belong to no
 // tenant (alignment gap, padding) read as zero.  e is a multiple of 8, as every tenant offset is,
 // so a vector never straddles the start of the second tenant.
-__device__ __forceinline__ u32x4 gather_g8(const PageSegs& s, int e) {
-    const int k = (s.n[1] > 0 && e >= s.off[1]) ? 1 : 0;
-    const int rel = e - s.off[k];
-    const int n = s.n[k];
+__device__ __forceinline__ u32x4 gather_g8(const PageRec& r, int e) {
+    const int k = e >= r.off1 ? 1 : 0;
+    const int left = r.end[k] - e;
     u32x4 w = u32x4{0u, 0u, 0u, 0u};
-    if (rel >= 0 && rel + 8 <= n) {
-        w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(s.g[k] + rel));
-    } else if (rel >= 0 && rel < n) {  // last, partial vector of the tensor: never read past its end
-        const uint16_t* src = s.g[k] + rel;
+    if (left >= 8) {
+        w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(r.g[k] + e));
+    } else if (left > 0) {  // last, partial vector of the tensor: never read past its end
+        const uint16_t* src = r.g[k] + e;
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            if (rel + j < n) w[j >> 1] |= (uint32_t)src[j] << (16 * (j & 1));
+            if (j < left) w[j >> 1] |= (uint32_t)src[j] << (16 * (j & 1));
     }
     return w;
 }
 
-__device__ __forceinline__ u32x2 gather_g4(const PageSegs& s, int e) {
-    const int k = (s.n[1] > 0 && e >= s.off[1]) ? 1 : 0;
-    const int rel = e - s.off[k];
-    const int n = s.n[k];
+__device__ __forceinline__ u32x2 gather_g4(const PageRec& r, int e) {
+    const int k = e >= r.off1 ? 1 : 0;
+    const int left = r.end[k] - e;
     u32x2 w = u32x2{0u, 0u};
-    if (rel >= 0 && rel + 4 <= n) {
-        w = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(s.g[k] + rel));
-    } else if (rel >= 0 && rel < n) {
-        const uint16_t* src = s.g[k] + rel;
+    if (left >= 4) {
+        w = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(r.g[k] + e));
+    } else if (left > 0) {
+        const uint16_t* src = r.g[k] + e;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            if (rel + j < n) w[j >> 1] |= (uint32_t)src[j] << (16 * (j & 1));
+            if (j < left) w[j >> 1] |= (uint32_t)src[j] << (16 * (j & 1));
     }
     return w;
 }
 
 // bf16 parameters of page elements [e, e+4) written to the tenant tensor they belong to; elements
 // of no tenant are dropped.
-__device__ __forceinline__ void scatter_q4(const PageSegs& s, int e, u32x2 o) {
-    const int k = (s.n[1] > 0 && e >= s.off[1]) ? 1 : 0;
-    const int rel = e - s.off[k];
-    const int n = s.n[k];
-    if (rel >= 0 && rel + 4 <= n) {
-        __builtin_nontemporal_store(o, reinterpret_cast<u32x2*>(s.q[k] + rel));
-    } else if (rel >= 0 && rel < n) {
-        uint16_t* dst = s.q[k] + rel;
+__device__ __forceinline__ void scatter_q4(const PageRec& r, int e, u32x2 o) {
+    const int k = e >= r.off1 ? 1 : 0;
+    const int left = r.end[k] - e;
+    if (left >= 4) {
+        __builtin_nontemporal_store(o, reinterpret_cast<u32x2*>(r.q[k] + e));
+    } else if (left > 0) {
+        uint16_t* dst = r.q[k] + e;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            if (rel + j < n) dst[j] = (uint16_t)(o[j >> 1] >> (16 * (j & 1)));
+            if (j < left) dst[j] = (uint16_t)(o[j >> 1] >> (16 * (j & 1)));
     }
 }
 
 struct ReduceArgs {
     const uint16_t* g16;
-    const PageSegs* segs;
+    const PageRec* recs;  // gather only
     const int32_t* used;
     const int64_t* grad_pages;
     int64_t grad_first;
@@ -179,18 +168,16 @@ __global__ __launch_bounds__(kThreads) void apm_grad_reduce_kernel(ReduceArgs a)
     if (start >= used && blockIdx.x != 0) return;
     const int end = min(start + kReduceTile, used);
     const uint16_t* g = GATHER ? nullptr : a.g16 + page * a.E;
-    PageSegs segs{};
+    PageRec rec{};
     bool edge = false;  // gather only: this slice is not wholly inside one tenant
     if (GATHER) {
-        segs = a.segs[i];
-        const int k = (segs.n[1] > 0 && start >= segs.off[1]) ? 1 : 0;
-        const int rel = start - segs.off[k];
+        rec = a.recs[i];
+        const int k = start >= rec.off1 ? 1 : 0;
         // Wholly inside tenant k, counted in whole 8-element vectors (the fast path below loads
-        // 16 bytes at a time and must not read past the tensor's last element): address the
-        // tensor like a page whose element 0 sits at g[k] - off[k].  A slice that holds a tensor's
-        // ragged end takes the per-vector path, which reads that end element by element.
-        const int span8 = ((end - start) + 7) & ~7;
-        if (rel >= 0 && rel + span8 <= segs.n[k]) g = segs.g[k] - segs.off[k];
+        // 16 bytes at a time and must not read past the tensor's last element): the slice reads
+        // that tensor like a page.  A slice that holds a tensor's ragged end takes the per-vector
+        // path, which reads that end element by element.
+        if (start + (((end - start) + 7) & ~7) <= rec.end[k]) g = rec.g[k];
         else edge = true;
     }
 
@@ -209,7 +196,7 @@ __global__ __launch_bounds__(kThreads) void apm_grad_reduce_kernel(ReduceArgs a)
             const int e = e0 + u * (kThreads * 8);
             w[u] = u32x4{0u, 0u, 0u, 0u};
             if (e < end) {
-                if (GATHER && edge) w[u] = gather_g8(segs, e);
+                if (GATHER && edge) w[u] = gather_g8(rec, e);
                 else w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(g + e));
             }
         }
@@ -270,11 +257,32 @@ struct FinalizeArgs {
     int32_t S;
     int32_t skip_mode;
     double max_norm;
-    PageMeta* meta;    // [n_listed]
+    PageRec* recs;     // [n_listed]; as PageRun if `run`
+    const uint16_t* g16;
+    uint16_t* p16;
+    int64_t E;
+    bool run;
+    bool staged;       // the records hold everything but the scale already (caller's tensors)
     float* grad_norm;  // nullable
     uint8_t* skip_mask;  // nullable
     const int32_t* out_index;  // nullable: list position -> index into grad_norm / skip_mask
 };
+
+// The record of a page that is read from / written to the page classes.
+__device__ __forceinline__ PageRec class_rec(int used, float scale, int64_t gpage, int64_t spage, int64_t E,
+                                             const uint16_t* g16, uint16_t* p16) {
+    PageRec r;
+    r.used = used;
+    r.scale = scale;
+    r.pofs = spage * E;
+    r.g[0] = r.g[1] = g16 + gpage * E;
+    r.q[0] = r.q[1] = p16 + gpage * E;
+    r.off1 = INT32_MAX;
+    r.end[0] = (used + 7) & ~7;
+    r.end[1] = 0;
+    r.pad = 0;
+    return r;
+}
 
 // One wavefront per listed page: combines the page's slice partials in a fixed order and turns
 // them into the page's clip scale / skip decision and the optional outputs.
@@ -303,46 +311,42 @@ __global__ __launch_bounds__(kThreads) void apm_grad_finalize_kernel(FinalizeArg
         const double sc = a.max_norm / (norm + 1e-6);
         scale = sc > 1.0 ? 1.0f : (float)sc;
     }
-    PageMeta pm;
-    pm.used = used;
-    pm.scale = skip ? -1.0f : scale;
-    pm.gpage = page;
-    pm.spage = a.state_pages ? a.state_pages[i] : a.state_first + i;
-    pm.pad = 0;
-    a.meta[i] = pm;
+    const float sc = skip ? -1.0f : scale;
+    if (a.run) reinterpret_cast<PageRun*>(a.recs)[i] = PageRun{used, sc};
+    else if (a.staged) a.recs[i].scale = sc;
+    else a.recs[i] = class_rec(used, sc, page, a.state_pages ? a.state_pages[i] : a.state_first + i, a.E, a.g16, a.p16);
     const int64_t o = a.out_index ? (int64_t)a.out_index[i] : i;
     if (a.grad_norm) a.grad_norm[o] = skip ? 0.0f : (float)norm;
     if (a.skip_mask) a.skip_mask[o] = skip ? 1 : 0;
 }
 
 // No reduce pass: one thread per listed page fills its record with scale 1.
-__global__ __launch_bounds__(kThreads) void apm_page_meta_kernel(FinalizeArgs a) {
+__global__ __launch_bounds__(kThreads) void apm_page_recs_kernel(FinalizeArgs a) {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= a.n_listed) return;
     const int64_t page = a.grad_pages ? a.grad_pages[i] : a.grad_first + i;
-    PageMeta pm;
-    pm.used = a.used[page];
-    pm.scale = 1.0f;
-    pm.gpage = page;
-    pm.spage = a.state_pages ? a.state_pages[i] : a.state_first + i;
-    pm.pad = 0;
-    a.meta[i] = pm;
+    const int used = a.used[page];
+    if (a.run) reinterpret_cast<PageRun*>(a.recs)[i] = PageRun{used, 1.0f};
+    else a.recs[i] = class_rec(used, 1.0f, page, a.state_pages ? a.state_pages[i] : a.state_first + i, a.E, a.g16, a.p16);
 }
 
 // Brings a call's page list and tensor addresses to where the kernels below read them, one thread per
 // listed page.  The words travel in the kernel arguments (an upload from pinned memory would cost
 // an extra kernel and two event packets, 20 us and more of idle GPU per call: 124 M parameters from
-// and to tensors 582 us a call staged that way, 560 like this; 5 M in small pages with clipping 48 and 41); bound by launch latency.
+// and to tensors 582 us a call staged that way, 560 like this; 5 M in small pages
+// with clipping 48 and 41); bound by launch latency.
 struct StageArgs {
     const int32_t* used;
     const int64_t* pages;       // positions' pages, or nullptr: first + i
     int64_t first;
     int64_t n_listed;
     const TenantRec* tenants;
-    PageSegs* segs;
+    PageRec* recs;
+    const uint16_t* g16;        // the page classes, for what is not the caller's
+    uint16_t* p16;
+    int64_t E;
     int64_t* list;              // written from the list words
     int32_t* out;
-    PageMeta* meta;             // nullptr: left to the reduce pass
     const uint64_t* words;      // list, g, q words, unless they follow inline
     int64_t list_begin;         // the list words are those of positions [list_begin, + list_n)
     int32_t list_n;
@@ -377,42 +381,35 @@ __global__ __launch_bounds__(kThreads) void apm_stage_kernel(Args args) {
         if (i >= a.n_listed) return;
         page = a.pages ? a.pages[i] : a.first + i;
     }
-    if (a.meta && a.t_begin == 0) {
-        PageMeta pm;
-        pm.used = a.used[page];
-        pm.scale = 1.0f;
-        pm.gpage = pm.spage = page;
-        pm.pad = 0;
-        a.meta[i] = pm;
+    PageRec* out = a.recs + i;
+    const int used = a.used[page];
+    const PageRec own = class_rec(used, 1.0f, page, page, a.E, a.g16, a.p16);
+    if (!a.has_g && !a.has_q) {
+        *out = own;
+        return;
     }
     if (a.t_n == 0) return;
+    // Tenant by tenant: with several launches each fills in the tenants whose addresses it carries.
     const TenantRec t = a.tenants[page];
-    PageSegs* s = a.segs + i;
+    out->used = used;
+    out->scale = 1.0f;
+    out->pofs = own.pofs;
+    out->off1 = t.off1;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int64_t at = t.tensor[k] - a.t_begin;
         if (t.tensor[k] < 0) {
-            s->off[k] = 0;
-            s->n[k] = 0;
+            out->end[k] = 0;
         } else if (at >= 0 && at < a.t_n) {
-            s->off[k] = t.off[k];
-            s->n[k] = t.n[k];
-            if (a.has_g) s->g[k] = reinterpret_cast<const uint16_t*>(word(a.list_n + at)) + t.tensor_off[k];
-            if (a.has_q) s->q[k] = reinterpret_cast<uint16_t*>(word(a.list_n + (a.has_g ? a.t_n : 0) + at)) + t.tensor_off[k];
+            const int off = k == 0 ? 0 : t.off1;
+            out->end[k] = off + t.n[k];
+            out->g[k] = a.has_g ? reinterpret_cast<const uint16_t*>(word(a.list_n + at)) + t.tensor_off[k] - off : own.g[0];
+            out->q[k] = a.has_q ? reinterpret_cast<uint16_t*>(word(a.list_n + (a.has_g ? a.t_n : 0) + at)) + t.tensor_off[k] - off : own.q[0];
         }
     }
 }
 
 struct UpdateArgs {
-    float* p32;
-    float* m32;
-    float* v32;
-    const uint16_t* g16;
-    uint16_t* p16;
-    const PageMeta* meta;  // per listed page
-    const PageSegs* segs;  // per listed page (gather / scatter only)
-    int64_t list_offset;
-    int64_t E;
     float b1, omb1, b2, omb2, inv_sqrt_bc2, eps, step_size, lr_wd;
 };
 
@@ -434,157 +431,174 @@ __device__ __forceinline__ void adamw_elem(float& p, float& m, float& v, float g
     p = p - delta;
 }
 
-constexpr int kUpdThreads = APM_UPDATE_THREADS;
-constexpr int kUpdU = APM_UPDATE_U;
-constexpr int kUpdTile = kUpdThreads * 4 * kUpdU;  // elements per workgroup
+constexpr int kUpdThreads = kWave;
+template <int U> constexpr int kTile = kUpdThreads * 4 * U;  // elements per wavefront
 
-// The body of a slice.  EDGE_G / EDGE_Q: the slice is not wholly inside one tenant tensor, so g is
-// gathered / p16 scattered lane by lane through the tenant descriptors; otherwise G and P16 are
-// plain page-like pointers and the body is straight-line code (all loads issued back to back, one
-// wait, all stores issued back to back).  The two forms are separate instantiations on purpose:
-// with the per-lane paths as branches inside one body the compiler put a wait for all outstanding
-// memory operations -- the stores of the previous vector included -- in front of every vector.
-//
-// FULL: every lane's kUpdU vectors lie inside the used extent (all slices of a page but its last),
-// so no access is predicated and the whole body is one basic block.  That matters beyond the
-// saved compares: on this target loads and stores share one counter, and at the entry of a basic
-// block the compiler must assume the worst about what is outstanding -- with a predicate per
-// vector, each vector's arithmetic began with a wait for every earlier memory operation, the
-// previous vector's stores included, i.e. three extra store round trips per wavefront.
-// Stores of the fp32 state: non-temporal, or -- WT, for state in host memory while other kernels
-// run on the GPU -- written through at system scope.  A non-temporal store to host memory may rest
-// in the L2 as a dirty line; the write-back that ends every kernel of any other stream then has
-// to push it across PCIe, so those kernels pay for this kernel's writes.
+// The vectors of a slice that lies inside one tenant (all slices of a page but the last one or two) go
+// through buffer accesses: the five streams' addresses are scalar (a descriptor each, made from the
+// page record), the lanes share one 32-bit offset, and the cache policy is an operand.  The policy is
+// non-temporal, or -- WT, for stores of state in host memory while other kernels run on the GPU --
+// written through at system scope: a non-temporal store to host memory may rest in the L2 as a dirty
+// line; the write-back that ends every kernel of any other stream then has to push it across PCIe,
+// so those kernels pay for this kernel's writes.
+// (As an operand because the compiler drops the hint of its non-temporal builtin from stores that it
+// merges or moves between this body and the checked one below: 124 M parameters 599 us a call without
+// the hint at one vector per lane, 548 with it.)
+constexpr int kNT = 2, kSC1 = 16;
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+
+// [base, base + bytes): accesses beyond it read zero / are dropped.
+__device__ __forceinline__ Rsrc make_rsrc(const void* base, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00027000);
+}
+
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+    return f32_to_bf16_rne(lo) | (f32_to_bf16_rne(hi) << 16);
+}
+
+// All loads are issued back to back, one wait, all stores back to back, in one basic block: on this
+// target loads and stores share one counter, and at the entry of a basic block the compiler must
+// assume the worst about what is outstanding.
+template <int U, bool WT>
+__device__ __forceinline__ void full_slice(const UpdateArgs& a, float scale, int lane, float* p_, float* m_, float* v_,
+                                           const uint16_t* g_, uint16_t* q_) {
+    const Rsrc P = make_rsrc(p_, kTile<U> * 4), M = make_rsrc(m_, kTile<U> * 4), V = make_rsrc(v_, kTile<U> * 4);
+    const Rsrc G = make_rsrc(g_, kTile<U> * 2), Q = make_rsrc(q_, kTile<U> * 2);
+    f32x4 p[U], m[U], v[U];
+    u32x2 g[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int o = lane * 16 + u * (kWave * 16);
+        g[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(G, lane * 8 + u * (kWave * 8), 0, kNT));
+        p[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(P, o, 0, kNT));
+        m[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(M, o, 0, kNT));
+        v[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(V, o, 0, kNT));
+    }
+    // without the barrier the scheduler sinks half of the loads between the vectors' arithmetic to
+    // save registers
+    __builtin_amdgcn_sched_barrier(0);
+    constexpr int kPolicy = WT ? kSC1 : kNT;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int o = lane * 16 + u * (kWave * 16);
+        const float gf[4] = {bf16lo(g[u][0]), bf16hi(g[u][0]), bf16lo(g[u][1]), bf16hi(g[u][1])};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float pj = p[u][j], mj = m[u][j], vj = v[u][j];
+            adamw_elem(pj, mj, vj, gf[j], a, scale);
+            p[u][j] = pj;
+            m[u][j] = mj;
+            v[u][j] = vj;
+        }
+        const u32x2 q = {pack_bf16(p[u][0], p[u][1]), pack_bf16(p[u][2], p[u][3])};
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, p[u]), P, o, 0, kPolicy);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, m[u]), M, o, 0, kPolicy);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[u]), V, o, 0, kPolicy);
+        __builtin_amdgcn_raw_buffer_store_b64(q, Q, lane * 8 + u * (kWave * 8), 0, kNT);
+    }
+}
+
+// A store of fp32 state outside the body above (same policies).  The write-through form is
+// hand-written because no builtin takes that policy for a 128-bit global store; the wait states keep
+// the next instruction off the data registers, which a store of more than 64 bits still reads right
+// after issue (the compiler does that for its own stores, not for this one).
 template <bool WT>
 __device__ __forceinline__ void store_state(f32x4 x, f32x4* q) {
-    // Hand-written because no builtin takes a cache policy for a 128-bit global store; the wait
-    // states keep the next instruction off the data registers, which a store of more than 64 bits
-    // still reads right after issue (the compiler does that for its own stores, not for this one).
     if (WT) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(q), "v"(x) : "memory");
     else __builtin_nontemporal_store(x, q);
 }
 
-template <bool EDGE_G, bool EDGE_Q, bool FULL, bool WT = false>
-__device__ __forceinline__ void slice_body(const UpdateArgs& a, const PageSegs& segs, float scale, int nvec, int v0,
-                                           f32x4* __restrict__ P, f32x4* __restrict__ M, f32x4* __restrict__ V,
-                                           const u32x2* __restrict__ G_, u32x2* __restrict__ P16_) {
-    // The tenant pointers come out of memory, so the compiler knows no address space for them and
-    // would use flat accesses, which count against both memory counters and force full waits.
-    // They are device (or pinned host) memory: say so.
+// A slice that a tenant's end or the page's used extent cuts: one vector at a time, each checked against
+// the used extent; with GATHER / SCATTER g is gathered / p16 scattered lane by lane through the tenants.
+template <int U, bool GATHER, bool SCATTER, bool WT>
+__device__ __forceinline__ void cut_slice(const UpdateArgs& a, const PageRec& rec, int v0, float* p_, float* m_, float* v_) {
+    f32x4* P = reinterpret_cast<f32x4*>(p_);
+    f32x4* M = reinterpret_cast<f32x4*>(m_);
+    f32x4* V = reinterpret_cast<f32x4*>(v_);
+    // The class pointers come out of memory, so the compiler knows no address space for them and
+    // would use flat accesses.  They are device (or pinned host) memory: say so.
     typedef const u32x2 __attribute__((address_space(1))) * GlobalIn;
     typedef u32x2 __attribute__((address_space(1))) * GlobalOut;
-    const GlobalIn G = (GlobalIn)G_;
-    const GlobalOut P16 = (GlobalOut)P16_;
-    f32x4 p[kUpdU], m[kUpdU], v[kUpdU];
-    u32x2 g[kUpdU];
+    const GlobalIn G = (GlobalIn) reinterpret_cast<const u32x2*>(rec.g[0]);
+    const GlobalOut Q = (GlobalOut) reinterpret_cast<u32x2*>(rec.q[0]);
+    const int nvec = ((rec.used + 7) & ~7) >> 2;
+#pragma unroll 1
+    for (int u = 0; u < U; ++u) {
+        const int vi = v0 + u * kWave;
+        if (vi >= nvec) break;
+        const u32x2 g = GATHER ? gather_g4(rec, vi << 2) : __builtin_nontemporal_load(G + vi);
+        f32x4 p = __builtin_nontemporal_load(P + vi), m = __builtin_nontemporal_load(M + vi), v = __builtin_nontemporal_load(V + vi);
+        const float gf[4] = {bf16lo(g[0]), bf16hi(g[0]), bf16lo(g[1]), bf16hi(g[1])};
 #pragma unroll
-    for (int u = 0; u < kUpdU; ++u) {
-        const int vi = v0 + u * kUpdThreads;
-        if (FULL || vi < nvec) {
-            if (EDGE_G) g[u] = gather_g4(segs, vi << 2);
-            else g[u] = __builtin_nontemporal_load(G + vi);
-            p[u] = __builtin_nontemporal_load(P + vi);
-            m[u] = __builtin_nontemporal_load(M + vi);
-            v[u] = __builtin_nontemporal_load(V + vi);
+        for (int j = 0; j < 4; ++j) {
+            float pj = p[j], mj = m[j], vj = v[j];
+            adamw_elem(pj, mj, vj, gf[j], a, rec.scale);
+            p[j] = pj;
+            m[j] = mj;
+            v[j] = vj;
         }
-    }
-    // all loads are issued before any arithmetic: without the barrier the scheduler, now that the
-    // body is one block, sinks half of them between the vectors' arithmetic to save registers
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int u = 0; u < kUpdU; ++u) {
-        const int vi = v0 + u * kUpdThreads;
-        if (FULL || vi < nvec) {
-            const float gf[4] = {bf16lo(g[u][0]), bf16hi(g[u][0]), bf16lo(g[u][1]), bf16hi(g[u][1])};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                float pj = p[u][j], mj = m[u][j], vj = v[u][j];
-                adamw_elem(pj, mj, vj, gf[j], a, scale);
-                p[u][j] = pj;
-                m[u][j] = mj;
-                v[u][j] = vj;
-            }
-            u32x2 o;
-            o[0] = f32_to_bf16_rne(p[u][0]) | (f32_to_bf16_rne(p[u][1]) << 16);
-            o[1] = f32_to_bf16_rne(p[u][2]) | (f32_to_bf16_rne(p[u][3]) << 16);
-            store_state<WT>(p[u], P + vi);
-            store_state<WT>(m[u], M + vi);
-            store_state<WT>(v[u], V + vi);
-            if (EDGE_Q) scatter_q4(segs, vi << 2, o);
-            else __builtin_nontemporal_store(o, P16 + vi);
-        }
+        const u32x2 q = {pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3])};
+        store_state<WT>(p, P + vi);
+        store_state<WT>(m, M + vi);
+        store_state<WT>(v, V + vi);
+        if (SCATTER) scatter_q4(rec, vi << 2, q);
+        else __builtin_nontemporal_store(q, Q + vi);
     }
 }
 
-// Fused update of one slice (kUpdTile elements from `start`) of one page by one wavefront:
-// 12 B + 2 B read and 12 B + 2 B written per element.  Each lane keeps kUpdU 128-bit vectors per
+// Fused update of one slice (kTile<U> elements from `start`) of one page by one wavefront:
+// 12 B + 2 B read and 12 B + 2 B written per element.  Each lane keeps U 128-bit vectors per
 // fp32 class in flight; every wavefront-wide access is one contiguous 1 KiB (fp32) or 512 B (bf16)
-// span.  GATHER / SCATTER: read g from / write p16 to the tenant tensors instead of the page
-// classes.
-template <bool GATHER, bool SCATTER, bool WT = false>
-__device__ __forceinline__ void update_slice(const UpdateArgs& a, const PageSegs& segs, float scale,
-                                             int used8, int64_t gpage, int64_t spage, int start, int lane) {
-    f32x4* __restrict__ P = reinterpret_cast<f32x4*>(a.p32 + spage * a.E);
-    f32x4* __restrict__ M = reinterpret_cast<f32x4*>(a.m32 + spage * a.E);
-    f32x4* __restrict__ V = reinterpret_cast<f32x4*>(a.v32 + spage * a.E);
-    const u32x2* __restrict__ G = GATHER ? nullptr : reinterpret_cast<const u32x2*>(a.g16 + gpage * a.E);
-    u32x2* __restrict__ P16 = SCATTER ? nullptr : reinterpret_cast<u32x2*>(a.p16 + gpage * a.E);
-    const int nvec = used8 >> 2;
-    const int v0 = (start >> 2) + lane;
-    if (GATHER || SCATTER) {
-        const int k = (segs.n[1] > 0 && start >= segs.off[1]) ? 1 : 0;
-        const int rel = start - segs.off[k];
-        const int span = min(kUpdTile, used8 - start);
-        // Wholly inside tenant k (the common case): address the tensor like a page whose element 0
-        // sits at ptr - off[k]; the slice then runs the same code as the page-class path.
-        if (rel >= 0 && rel + span <= segs.n[k]) {
-            if (GATHER) G = reinterpret_cast<const u32x2*>(segs.g[k] - segs.off[k]);
-            if (SCATTER) P16 = reinterpret_cast<u32x2*>(segs.q[k] - segs.off[k]);
-        } else {
-            slice_body<GATHER, SCATTER, false, WT>(a, segs, scale, nvec, v0, P, M, V, G, P16);
-            return;
-        }
-    }
-    if (start + kUpdTile <= used8) slice_body<false, false, true, WT>(a, segs, scale, nvec, v0, P, M, V, G, P16);
-    else slice_body<false, false, false, WT>(a, segs, scale, nvec, v0, P, M, V, G, P16);
+// span.  p, m, v: the page's first element.
+template <int U, bool GATHER, bool SCATTER, bool WT = false>
+__device__ __forceinline__ void update_slice(const UpdateArgs& a, const PageRec& rec, int start, int lane,
+                                             float* p, float* m, float* v) {
+    const int k = start >= rec.off1 ? 1 : 0;
+    if (start + kTile<U> <= rec.end[k])
+        full_slice<U, WT>(a, rec.scale, lane, p + start, m + start, v + start, rec.g[k] + start, rec.q[k] + start);
+    else cut_slice<U, GATHER, SCATTER, WT>(a, rec, (start >> 2) + lane, p, m, v);
 }
 
-typedef long long i64x4 __attribute__((ext_vector_type(4)));
-static_assert(sizeof(PageMeta) == sizeof(i64x4), "PageMeta must be 32 bytes");
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+static_assert(sizeof(PageRec) == sizeof(i32x16) && sizeof(PageRun) == sizeof(i32x2), "a record is one scalar load");
+
+__device__ __forceinline__ PageRec load_rec(const PageRec* at) {
+    const i32x16 raw = *reinterpret_cast<const i32x16*>(at);
+    return __builtin_bit_cast(PageRec, raw);
+}
 
 // The HBM-resident form: grid.y walks the list positions, grid.x the slices (SLICES per
-// workgroup) of a page.
-template <bool GATHER, bool SCATTER, int SLICES>
-__global__ __launch_bounds__(kUpdThreads) void apm_adamw_kernel(UpdateArgs a) {
-    // Prologue: everything a workgroup needs about its page comes with one 32-byte scalar load
-    // (plus the tenant descriptors in gather / scatter mode, fetched alongside).  A workgroup holds
-    // a residency slot without memory traffic until this arrives, so the dependent-load chain is
-    // kept to kernel arguments -> page record.
-    const int64_t i = a.list_offset + blockIdx.y;
-    const i64x4 raw = *reinterpret_cast<const i64x4*>(a.meta + i);  // one load for the whole record
-    PageSegs segs{};
-    if (GATHER || SCATTER) segs = a.segs[i];
-#if APM_HOIST_LOADS
-    // The exits below would let the compiler sink every scalar load that only the working path
-    // needs (the tenant descriptors, the class base pointers) below them, which adds a third
-    // dependent memory round trip to the prologue.  Naming the values as inputs of an empty asm
-    // statement keeps those loads up here, in flight together with the page record.
-    asm volatile("" ::"s"(a.p32), "s"(a.m32), "s"(a.v32), "s"(a.g16), "s"(a.p16), "s"(a.E));
-    if (GATHER || SCATTER)
-        asm volatile("" ::"s"(segs.off[0]), "s"(segs.off[1]), "s"(segs.n[0]), "s"(segs.n[1]), "s"(segs.g[0]),
-                     "s"(segs.g[1]), "s"(segs.q[0]), "s"(segs.q[1]));
-#endif
-    const float scale = __uint_as_float((uint32_t)((uint64_t)raw[0] >> 32));
-    const int used8 = ((int32_t)(uint32_t)raw[0] + 7) & ~7;
-    // (Folding the two exits below into the lane predicate, so that all scalar loads of the
-    // prologue issue together, measured 2-3 % slower on the 1.3 B workload and 3 % faster on the
-    // fragmented 124 M one; the early exits stay.)
-    if (scale < 0.0f) return;  // a skipped page
+// workgroup) of a page.  The arguments are single values, what the prologue needs first, because
+// the hardware hands the leading 14 dwords of such an argument list to every wavefront in registers:
+// the record's load is then the only round trip before the first vector load.
+template <int U, bool GATHER, bool SCATTER, int SLICES>
+__global__ __launch_bounds__(kUpdThreads) void apm_adamw_kernel(const PageRec* recs, float* p32, float* m32, float* v32,
+                                                                UpdateArgs a) {
+    const PageRec rec = load_rec(recs + blockIdx.y);
+    if (rec.scale < 0.0f) return;  // a skipped page
+    const int used8 = (rec.used + 7) & ~7;
 #pragma unroll 1
     for (int it = 0; it < SLICES; ++it) {
-        const int start = ((int)blockIdx.x * SLICES + it) * kUpdTile;
+        const int start = ((int)blockIdx.x * SLICES + it) * kTile<U>;
         if (start >= used8) return;  // beyond the extent
-        update_slice<GATHER, SCATTER>(a, segs, scale, used8, raw[1], raw[2], start, (int)threadIdx.x);
+        update_slice<U, GATHER, SCATTER>(a, rec, start, (int)threadIdx.x, p32 + rec.pofs, m32 + rec.pofs, v32 + rec.pofs);
+    }
+}
+
+// The same for a run of pages in the page classes; all pointers are those of the launch's first page.
+template <int U, int SLICES>
+__global__ __launch_bounds__(kUpdThreads) void apm_adamw_run_kernel(const PageRun* runs, float* p32, float* m32, float* v32,
+                                                                    const uint16_t* g16, uint16_t* p16, int E, UpdateArgs a) {
+    const PageRun run = __builtin_bit_cast(PageRun, *reinterpret_cast<const i32x2*>(runs + blockIdx.y));
+    const int64_t at = (int64_t)blockIdx.y * E;
+    const PageRec rec = class_rec(run.used, run.scale, 0, 0, 0, g16 + at, p16 + at);
+    if (rec.scale < 0.0f) return;
+#pragma unroll 1
+    for (int it = 0; it < SLICES; ++it) {
+        const int start = ((int)blockIdx.x * SLICES + it) * kTile<U>;
+        if (start >= rec.end[0]) return;
+        update_slice<U, false, false>(a, rec, start, (int)threadIdx.x, p32 + at, m32 + at, v32 + at);
     }
 }
 
@@ -597,26 +611,43 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_kernel(UpdateArgs a) {
 // beside kernels whose workgroups need a CU's whole register file or LDS (dense matrix
 // products), because a wavefront that lives as long as the whole transfer keeps those off its CU.
 constexpr int kStrideMaxThreads = 1024;
+constexpr int kStrideU = 4;
 
-template <bool GATHER, bool SCATTER, bool WT>
-__global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(UpdateArgs a, int64_t count, int nx,
-                                                                             int n_workers) {
+struct StrideArgs {
+    const PageRec* recs;  // as PageRun if RUN
+    float* p32;           // RUN: of the launch's first page, as g16 and p16; otherwise of the class
+    float* m32;
+    float* v32;
+    const uint16_t* g16;
+    uint16_t* p16;
+    int64_t E;
+    int64_t count;
+    int nx, n_workers;
+};
+
+template <bool RUN, bool WT>
+__global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(StrideArgs s, UpdateArgs a) {
     const int lane = (int)threadIdx.x & (kWave - 1);
     const int waves_per_wg = (int)blockDim.x / kWave;
     const int worker = (int)blockIdx.x * waves_per_wg + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-    if (worker >= n_workers) return;
-    const int64_t n_items = count * nx;
+    if (worker >= s.n_workers) return;
+    const int64_t n_items = s.count * s.nx;
 #pragma unroll 1
-    for (int64_t w = worker; w < n_items; w += n_workers) {
-        const int64_t i = a.list_offset + w / nx;
-        const int start = (int)(w % nx) * kUpdTile;
-        const i64x4 raw = *reinterpret_cast<const i64x4*>(a.meta + i);
-        const float scale = __uint_as_float((uint32_t)((uint64_t)raw[0] >> 32));
-        const int used8 = ((int32_t)(uint32_t)raw[0] + 7) & ~7;
-        if (scale < 0.0f || start >= used8) continue;
-        PageSegs segs{};
-        if (GATHER || SCATTER) segs = a.segs[i];
-        update_slice<GATHER, SCATTER, WT>(a, segs, scale, used8, raw[1], raw[2], start, lane);
+    for (int64_t w = worker; w < n_items; w += s.n_workers) {
+        const int64_t i = w / s.nx;
+        const int start = (int)(w % s.nx) * kTile<kStrideU>;
+        PageRec rec;
+        int64_t at;
+        if (RUN) {
+            const PageRun run = __builtin_bit_cast(PageRun, *(reinterpret_cast<const i32x2*>(s.recs) + i));
+            at = i * s.E;
+            rec = class_rec(run.used, run.scale, 0, 0, 0, s.g16 + at, s.p16 + at);
+        } else {
+            rec = load_rec(s.recs + i);
+            at = rec.pofs;
+        }
+        if (rec.scale < 0.0f || start >= rec.end[0]) continue;
+        update_slice<kStrideU, false, false, WT>(a, rec, start, lane, s.p32 + at, s.m32 + at, s.v32 + at);
     }
 }
 
@@ -710,7 +741,7 @@ hipError_t for_each_launch(const AdamwLaunch& L, F&& f) {
 }  // namespace
 
 hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
-    ReduceArgs a{L.g16, L.segs, L.used, L.grad_pages, L.grad_first, 0, L.E, L.partials, L.nzflags, L.S};
+    ReduceArgs a{L.g16, L.recs, L.used, L.grad_pages, L.grad_first, 0, L.E, L.partials, L.nzflags, L.S};
     hipError_t e = for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used) {
         a.list_offset = begin;
         const dim3 grid((unsigned)((max_used + kReduceTile - 1) / kReduceTile), (unsigned)ny);
@@ -719,8 +750,8 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
     });
     if (e != hipSuccess) return e;
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
-                   L.partials, L.nzflags, L.S, L.skip_mode, L.max_norm, L.meta, L.grad_norm, L.skip_mask,
-                   L.out_index};
+                   L.partials, L.nzflags, L.S, L.skip_mode, L.max_norm, L.recs, L.g16, L.p16, L.E, L.is_run(),
+                   L.gather || L.scatter, L.grad_norm, L.skip_mask, L.out_index};
     const int per_wg = kThreads / kWave;
     hipLaunchKernelGGL(apm_grad_finalize_kernel, dim3((unsigned)((L.n_listed + per_wg - 1) / per_wg)),
                        dim3(kThreads), 0, s, f);
@@ -729,8 +760,9 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
 
 hipError_t launch_prepare(const AdamwLaunch& L, hipStream_t s) {
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
-                   nullptr, nullptr, L.S, L.skip_mode, 0.0, L.meta, nullptr, nullptr, nullptr};
-    hipLaunchKernelGGL(apm_page_meta_kernel, dim3((unsigned)((L.n_listed + kThreads - 1) / kThreads)),
+                   nullptr, nullptr, L.S, L.skip_mode, 0.0, L.recs, L.g16, L.p16, L.E, L.is_run(),
+                   false, nullptr, nullptr, nullptr};
+    hipLaunchKernelGGL(apm_page_recs_kernel, dim3((unsigned)((L.n_listed + kThreads - 1) / kThreads)),
                        dim3(kThreads), 0, s, f);
     return hipGetLastError();
 }
@@ -747,8 +779,8 @@ hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s)
     const int64_t n_list = c.list ? L.n_listed : 0, n_t = has_g || has_q ? c.n_tensors : 0;
     StageArgsInline in;
     StageArgs& a = in.a;
-    a = StageArgs{L.used, c.list ? c.d_list : L.grad_pages, L.grad_first, L.n_listed, c.tenants, c.d_segs,
-                  c.d_list, c.d_out, c.meta ? L.meta : nullptr, c.d_words, 0, 0, 0, 0, has_g, has_q};
+    a = StageArgs{L.used, c.list ? c.d_list : L.grad_pages, L.grad_first, L.n_listed, c.tenants, L.recs, L.g16, L.p16, L.E,
+                  c.d_list, c.d_out, c.d_words, 0, 0, 0, 0, has_g, has_q};
     auto go = [&](int64_t list_begin, int64_t list_n, int64_t t_begin, int64_t t_n) -> hipError_t {
         a.list_begin = list_begin;
         a.list_n = (int32_t)list_n;
@@ -775,7 +807,6 @@ hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s)
         hipError_t e = go(k, n_list - k < kArgWords ? n_list - k : kArgWords, 0, 0);
         if (e != hipSuccess) return e;
     }
-    if (n_list > 0) a.meta = nullptr;  // filled by the list launches
     const int64_t per = has_g && has_q ? kArgWords / 2 : kArgWords;
     for (int64_t k = 0; k < n_t; k += per) {
         hipError_t e = go(0, 0, k, n_t - k < per ? n_t - k : per);
@@ -785,42 +816,49 @@ hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s)
 }
 
 hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
-    UpdateArgs a{};
-    a.p32 = L.p32; a.m32 = L.m32; a.v32 = L.v32; a.g16 = L.g16; a.p16 = L.p16;
-    a.segs = L.segs;
-    a.meta = L.meta;
-    a.E = L.E;
-    a.b1 = L.b1; a.omb1 = L.omb1; a.b2 = L.b2; a.omb2 = L.omb2;
-    a.inv_sqrt_bc2 = L.inv_sqrt_bc2; a.eps = L.eps; a.step_size = L.step_size; a.lr_wd = L.lr_wd;
+    const UpdateArgs a{L.b1, L.omb1, L.b2, L.omb2, L.inv_sqrt_bc2, L.eps, L.step_size, L.lr_wd};
+    const bool run = L.is_run();
+    const PageRun* runs = reinterpret_cast<const PageRun*>(L.recs);
+    // of the page at list position `at` of a run
+    auto state = [&](float* c, int64_t at) { return run ? c + (L.state_first + at) * L.E : c; };
+    auto g16 = [&](int64_t at) { return L.g16 + (L.grad_first + at) * L.E; };
+    auto p16 = [&](int64_t at) { return L.p16 + (L.grad_first + at) * L.E; };
     if (L.stride_wavefronts > 0) {
+        if (L.gather || L.scatter) return hipErrorInvalidValue;  // host-resident state goes with the page classes
         return for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used) {
-            a.list_offset = begin;
-            const int nx = (int)((max_used + kUpdTile - 1) / kUpdTile);
+            const int nx = (int)((max_used + kTile<kStrideU> - 1) / kTile<kStrideU>);
             const int64_t items = ny * nx;
             const int workers = (int)(items < L.stride_wavefronts ? items : L.stride_wavefronts);
             const int per_wg = L.stride_waves_per_wg >= 1 && L.stride_waves_per_wg <= kStrideMaxThreads / kWave ? L.stride_waves_per_wg : 1;
             const dim3 grid((unsigned)((workers + per_wg - 1) / per_wg)), block((unsigned)(per_wg * kWave));
-#define APM_LAUNCH_STRIDE(G, Q)                                                                                       \
-    do {                                                                                                             \
-        if (L.host_write_through) hipLaunchKernelGGL((apm_adamw_stride_kernel<G, Q, true>), grid, block, 0, s, a, ny, nx, workers); \
-        else hipLaunchKernelGGL((apm_adamw_stride_kernel<G, Q, false>), grid, block, 0, s, a, ny, nx, workers);       \
-    } while (0)
-            if (L.gather && L.scatter) APM_LAUNCH_STRIDE(true, true);
-            else if (L.gather) APM_LAUNCH_STRIDE(true, false);
-            else if (L.scatter) APM_LAUNCH_STRIDE(false, true);
-            else APM_LAUNCH_STRIDE(false, false);
-#undef APM_LAUNCH_STRIDE
+            StrideArgs t{run ? reinterpret_cast<const PageRec*>(runs + begin) : L.recs + begin, state(L.p32, begin), state(L.m32, begin),
+                         state(L.v32, begin), nullptr, nullptr, L.E, ny, nx, workers};
+            if (run) {
+                t.g16 = g16(begin);
+                t.p16 = p16(begin);
+                if (L.host_write_through) hipLaunchKernelGGL((apm_adamw_stride_kernel<true, true>), grid, block, 0, s, t, a);
+                else hipLaunchKernelGGL((apm_adamw_stride_kernel<true, false>), grid, block, 0, s, t, a);
+            } else {
+                if (L.host_write_through) hipLaunchKernelGGL((apm_adamw_stride_kernel<false, true>), grid, block, 0, s, t, a);
+                else hipLaunchKernelGGL((apm_adamw_stride_kernel<false, false>), grid, block, 0, s, t, a);
+            }
         });
     }
     const bool may_skip = L.partials && L.skip_mode == APM_SKIP_UNTOUCHED;
-    const int64_t wg_span = (int64_t)kUpdTile * (may_skip ? APM_UPDATE_SLICES_SKIP : 1);
+    constexpr int U = APM_UPDATE_U;
+    const int64_t wg_span = may_skip ? kTile<kSkipU> * kSkipSlices : kTile<U>;
     return for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used) {
-        a.list_offset = begin;
         const dim3 grid((unsigned)((max_used + wg_span - 1) / wg_span), (unsigned)ny), block(kUpdThreads);
+        if (run) {
+            float *p = state(L.p32, begin), *m = state(L.m32, begin), *v = state(L.v32, begin);
+            if (may_skip) hipLaunchKernelGGL((apm_adamw_run_kernel<kSkipU, kSkipSlices>), grid, block, kSkipLds, s, runs + begin, p, m, v, g16(begin), p16(begin), (int)L.E, a);
+            else hipLaunchKernelGGL((apm_adamw_run_kernel<U, 1>), grid, block, APM_UPDATE_LDS, s, runs + begin, p, m, v, g16(begin), p16(begin), (int)L.E, a);
+            return;
+        }
 #define APM_LAUNCH_UPDATE(G, Q)                                                                         \
     do {                                                                                               \
-        if (may_skip) hipLaunchKernelGGL((apm_adamw_kernel<G, Q, APM_UPDATE_SLICES_SKIP>), grid, block, APM_UPDATE_LDS, s, a); \
-        else hipLaunchKernelGGL((apm_adamw_kernel<G, Q, 1>), grid, block, APM_UPDATE_LDS, s, a);       \
+        if (may_skip) hipLaunchKernelGGL((apm_adamw_kernel<kSkipU, G, Q, kSkipSlices>), grid, block, kSkipLds, s, L.recs + begin, L.p32, L.m32, L.v32, a); \
+        else hipLaunchKernelGGL((apm_adamw_kernel<U, G, Q, 1>), grid, block, APM_UPDATE_LDS, s, L.recs + begin, L.p32, L.m32, L.v32, a);       \
     } while (0)
         if (L.gather && L.scatter) APM_LAUNCH_UPDATE(true, true);
         else if (L.gather) APM_LAUNCH_UPDATE(true, false);

@@ -102,36 +102,39 @@ struct StageRing {
 // ---- kernels ------------------------------------------------------------------------------
 constexpr int kReduceTile = 16384;  // gradient elements per workgroup of the reduce kernel
 
-// Per-page view of the tenant tensors, for kernels that read gradients from / write bf16
-// parameters to the caller's contiguous tensors directly instead of the G16 / P16 page classes.
-// Tenant k covers page elements [off[k], off[k]+n[k]); g[k] / q[k] point at the tensor element
-// that sits at off[k].  off[k] is a multiple of 8 and the pointers are 16-byte aligned.
-struct PageSegs {
-    int32_t off[2];
-    int32_t n[2];
-    const uint16_t* g[2];
-    uint16_t* q[2];
-};
-
 // The tenants of a page as the layout has them: tenant k is n[k] elements of tensor tensor[k] from
-// tensor_off[k] on, at page element off[k].  The table depends on the layout alone and is uploaded
+// tensor_off[k] on; the first starts at page element 0, the second at off1 (a multiple of 8).  The table depends on the layout alone and is uploaded
 // with it; a fused call only brings the tensors' addresses.
 struct TenantRec {
     int64_t tensor_off[2];
-    int32_t off[2];
+    int32_t off1;
     int32_t n[2];
     int32_t tensor[2];  // -1: no such tenant
 };
 
-// What one listed page needs in the update kernel, gathered into one 32-byte record so that a
-// workgroup fetches it with a single scalar load: written per call by the finalize kernel (after a
-// reduce pass) or by the prepare kernel (no reduce pass).
-struct PageMeta {
+// What the update kernel needs to know of one listed page, in one record that a workgroup fetches with
+// a single scalar load: every workgroup is one wavefront with a few KB of work, so what it does
+// before its first vector load counts.
+//
+// Pages first, first + 1, ... read from and written to the page classes (a run) need this much; where
+// the page lies follows from the position.
+struct PageRun {
     int32_t used;   // used extent of the page (elements)
     float scale;    // clip scale; negative = the page is skipped
-    int64_t gpage;  // page index for the 16-bit classes (and the page table)
-    int64_t spage;  // page index for the fp32 classes
-    int64_t pad;
+};
+// Any other page, and pages whose gradient / bf16 parameters are the caller's tensors.  Element e of
+// the page has its gradient at g[k] + e and its bf16 parameter at q[k] + e, where k = 1 from the
+// second tenant's first element off1 on; tenant k ends before element end[k].  A page class is one
+// tenant over the used extent rounded up to 8.
+struct __attribute__((aligned(64))) PageRec {
+    int32_t used;
+    float scale;
+    int64_t pofs;   // the page's first element in the fp32 classes
+    const uint16_t* g[2];
+    uint16_t* q[2];
+    int32_t off1;   // INT32_MAX: no second tenant
+    int32_t end[2];
+    int32_t pad;
 };
 
 // Wavefronts of the update kernel when it reads and writes fp32 classes in host memory across
@@ -145,10 +148,10 @@ struct AdamwLaunch {
     const uint16_t* g16;
     uint16_t* p16;
     const int32_t* used;          // device, indexed by grad page id
-    const PageSegs* segs;         // device, indexed like the page list; needed if gather or scatter
-    PageMeta* meta;               // device scratch, [n_listed], filled by the reduce / prepare pass
-    bool gather;                  // read g from the tenant tensors (segs[].g) instead of g16
-    bool scatter;                 // write p16 to the tenant tensors (segs[].q) instead of p16
+    PageRec* recs;                // device scratch, [n_listed], filled by the stage / reduce / prepare
+                                  // pass; as PageRun [n_listed] if the pages are a run (see is_run)
+    bool gather;                  // read g from the tenant tensors instead of g16
+    bool scatter;                 // write p16 to the tenant tensors instead of p16
     const int64_t* state_pages;   // device list or nullptr (then state_first + i)
     const int64_t* grad_pages;    // device list or nullptr (then grad_first + i)
     int64_t state_first;
@@ -171,16 +174,17 @@ struct AdamwLaunch {
                                   // page slices (fp32 classes in host memory); 0: one per slice
     int32_t stride_waves_per_wg;  // how many of them share a workgroup, 1..16
     bool host_write_through;      // stride form: fp32 state stores written through at system scope
+    bool is_run() const { return !state_pages && !grad_pages && !gather && !scatter; }
 };
 
-// Reduce pass (fills meta with clip scale / skip); or, when no reduce pass is needed, the prepare
-// pass (fills meta with scale 1).  One of the two must precede launch_adamw on the same stream.
+// Reduce pass (fills the records with clip scale / skip); or, when no reduce pass is needed, the
+// prepare pass (fills them with scale 1).  One of the two must precede launch_adamw on the same stream.
 hipError_t launch_grad_reduce(const AdamwLaunch& a, hipStream_t s);
 hipError_t launch_prepare(const AdamwLaunch& a, hipStream_t s);
 
 // What a call brings to the device besides scalars: its page list (a word per position: page, and the
 // index of its outputs in the upper half) and its tensors' addresses.  Written to where the step's
-// kernels read it (list / out / segs) by apm_stage_kernel.
+// kernels read it (list / out / L.recs, with scale 1) by apm_stage_kernel.
 struct StageCall {
     const uint64_t* list;         // n_listed words, or nullptr: positions as L.grad_pages / L.grad_first say
     const uint64_t* g_ptrs;       // n_tensors addresses each, nullptr if not gathered / scattered
@@ -189,8 +193,6 @@ struct StageCall {
     const TenantRec* tenants;
     int64_t* d_list;              // written if `list`
     int32_t* d_out;
-    PageSegs* d_segs;             // written if g_ptrs or q_ptrs
-    bool meta;                    // also fill L.meta with scale 1 (no reduce pass follows)
     const uint64_t* d_words;      // list, g_ptrs, q_ptrs one after the other in device memory, or nullptr
 };
 // Launches it takes to carry a call's words in kernel arguments (StageCall::d_words == nullptr).
@@ -279,12 +281,10 @@ struct apm_pool {
     bool order_run = false;
     double* d_partials = nullptr;   // reduce scratch, n_pages * S
     uint32_t* d_nzflags = nullptr;
-    apm::PageMeta* d_meta = nullptr;  // n_pages entries
-    // what a call's list and tensors come to (apm_stage_kernel), n_pages entries each, allocated on
-    // first use; like the scratch above they belong to the one step that is running on the pool
+    apm::PageRec* d_recs = nullptr;   // n_pages entries
+    // what a call's list comes to (apm_stage_kernel), n_pages entries each, allocated on first use; like the scratch above they belong to the one step that is running on the pool
     int64_t* d_list = nullptr;
     int32_t* d_list_out = nullptr;
-    apm::PageSegs* d_page_segs = nullptr;
     int32_t S = 0;
     apm::StageRing ring;
 
@@ -323,7 +323,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
                  const apm_hyper* hyper, const uint16_t* g16_override, float* grad_norm,
                  uint8_t* skip_mask, hipStream_t stream, const apm_tensor* grad_tensors = nullptr,
                  const apm_tensor* p16_tensors = nullptr, int64_t n_tensors = 0);
-int ensure_scratch(apm_pool* pool, bool list = false, bool tensors = false);
+int ensure_scratch(apm_pool* pool, bool list = false);
 // Allocates the ping-pong gradient halves, the events and the update stream of the delayed path.
 // caller != nullptr-able: the stream the producer works on; the update stream is chosen so that
 // its kernels run beside that stream's (see make_overlapping_stream).

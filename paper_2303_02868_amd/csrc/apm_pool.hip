@@ -58,7 +58,7 @@ void StageRing::destroy() {
     }
 }
 
-int ensure_scratch(apm_pool* pool, bool list, bool tensors) {
+int ensure_scratch(apm_pool* pool, bool list) {
     const size_t n = (size_t)pool->desc.n_pages * (size_t)pool->S;
     auto get = [](void** p, size_t bytes) -> int {  // a buffer an earlier, failed attempt got is kept
         if (*p) return APM_OK;
@@ -71,10 +71,9 @@ int ensure_scratch(apm_pool* pool, bool list, bool tensors) {
     int rc = get((void**)&pool->d_partials, n * sizeof(double));
     if (rc == APM_OK) rc = get((void**)&pool->d_nzflags, n * sizeof(uint32_t));
     const size_t n_pages = (size_t)pool->desc.n_pages;
-    if (rc == APM_OK) rc = get((void**)&pool->d_meta, n_pages * sizeof(PageMeta));
+    if (rc == APM_OK) rc = get((void**)&pool->d_recs, n_pages * sizeof(PageRec));
     if (rc == APM_OK && list) rc = get((void**)&pool->d_list, n_pages * sizeof(int64_t));
     if (rc == APM_OK && list) rc = get((void**)&pool->d_list_out, n_pages * sizeof(int32_t));
-    if (rc == APM_OK && tensors) rc = get((void**)&pool->d_page_segs, n_pages * sizeof(PageSegs));
     return rc;
 }
 
@@ -125,10 +124,9 @@ void free_pool(apm_pool* pool) {
     if (pool->d_order_out) (void)hipFree(pool->d_order_out);
     if (pool->d_partials) (void)hipFree(pool->d_partials);
     if (pool->d_nzflags) (void)hipFree(pool->d_nzflags);
-    if (pool->d_meta) (void)hipFree(pool->d_meta);
+    if (pool->d_recs) (void)hipFree(pool->d_recs);
     if (pool->d_list) (void)hipFree(pool->d_list);
     if (pool->d_list_out) (void)hipFree(pool->d_list_out);
-    if (pool->d_page_segs) (void)hipFree(pool->d_page_segs);
     pool->ring.destroy();
     for (auto& t : pool->timed) {
         (void)hipEventDestroy(t.begin);
@@ -184,12 +182,12 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     int32_t ranges = 0;
     order_segments(plan, &recs, &launches, &ranges);
     const size_t n_in_use = plan.pages.size();
-    std::vector<TenantRec> tenants(n_in_use, TenantRec{{0, 0}, {0, 0}, {0, 0}, {-1, -1}});
+    std::vector<TenantRec> tenants(n_in_use, TenantRec{{0, 0}, INT32_MAX, {0, 0}, {-1, -1}});
     for (const apm_segment& g : plan.segs) {  // a page's tenants appear in offset order
         TenantRec& t = tenants[(size_t)g.page];
         const int k = t.tensor[0] < 0 ? 0 : 1;
         t.tensor_off[k] = g.tensor_off;
-        t.off[k] = (int32_t)g.page_off;
+        if (k == 1) t.off1 = (int32_t)g.page_off;
         t.n[k] = (int32_t)g.n;
         t.tensor[k] = (int32_t)g.tensor;
     }

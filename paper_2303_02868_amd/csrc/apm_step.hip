@@ -112,7 +112,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     }
     const bool tensors = grad_tensors || p16_tensors;
     const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
-    rc = ensure_scratch(pool, !run && !whole, tensors);
+    rc = ensure_scratch(pool, !run && !whole);
     if (rc != APM_OK) return rc;
 
     // What the kernels need of this call's list and tensors, as words (see StageCall).
@@ -131,8 +131,6 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     sc.tenants = pool->d_tenants;
     sc.d_list = pool->d_list;
     sc.d_out = pool->d_list_out;
-    sc.d_segs = pool->d_page_segs;
-    sc.meta = !need_reduce;
     int ring_slot = -1;
     if (stage_launches(sc, n_pages) > kMaxStageLaunches) {
         const size_t bytes = words.size() * sizeof(uint64_t);
@@ -156,13 +154,12 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     L.state_first = L.grad_first = page_at(0);
     L.gather = grad_tensors != nullptr;
     L.scatter = p16_tensors != nullptr;
-    L.segs = tensors ? pool->d_page_segs : nullptr;
     L.n_listed = n_pages;
     L.E = E;
     L.S = pool->S;
     L.grad_norm = grad_norm;
     L.skip_mask = skip_mask;
-    L.meta = pool->d_meta;
+    L.recs = pool->d_recs;
     const bool staged = n_list > 0 || tensors;
     if (staged) {
         APM_HIP(launch_stage(L, sc, stream));

@@ -331,7 +331,7 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
     L.m32 = s->stage[1];
     L.v32 = s->stage[2];
     const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
-    L.meta = dev->d_meta;
+    L.recs = dev->d_recs;
     if (need_reduce) {
         L.partials = dev->d_partials;
         L.nzflags = dev->d_nzflags;
@@ -371,7 +371,7 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
                 C.stride_waves_per_wg = s->direct_per_wg;
                 C.host_write_through = s->host_wt;
             }
-            C.meta = L.meta + first;
+            C.recs = L.recs + first;
             if (need_reduce) {
                 C.partials = L.partials + first * L.S;
                 C.nzflags = L.nzflags + first * L.S;
@@ -892,7 +892,7 @@ extern "C" int apm_streamer_step_scheduled(apm_streamer* s, const apm_task* task
         L.p32 = s->stage[0];
         L.m32 = s->stage[1];
         L.v32 = s->stage[2];
-        L.meta = dev->d_meta;
+        L.recs = dev->d_recs;
         const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
         if (need_reduce) {
             L.partials = dev->d_partials;
