@@ -2,8 +2,10 @@
 //   apm_grad_reduce_kernel    per (page, slice) sum of squares (fp64) and any-nonzero of g16
 //   apm_grad_finalize_kernel  per page: norm, clip scale, skip decision -> the page's record
 //   apm_page_recs_kernel      the page records when no reduce pass is needed
+//   apm_stage_kernel          the same from a call's page list and tensor addresses
 //   apm_adamw_kernel          the fused update (optionally gathering g16 from / scattering p16 to
 //                             the caller's tensors), one workgroup per page slice
+//   apm_adamw_clip_kernel     norms, clip scales and the update in one grid
 //   apm_adamw_stride_kernel   the same slice body run by a fixed, small number of wavefronts that
 //                             stride over all slices (fp32 classes in host memory across PCIe)
 //   apm_grad_accum_kernel     g' += g for the buffered gradient of the delayed path
@@ -263,6 +265,7 @@ struct FinalizeArgs {
     int64_t E;
     bool run;
     bool staged;       // the records hold everything but the scale already (caller's tensors)
+    uint64_t* sums;    // one-pass launches: [n_listed * S], to be marked as not there yet
     float* grad_norm;  // nullable
     uint8_t* skip_mask;  // nullable
     const int32_t* out_index;  // nullable: list position -> index into grad_norm / skip_mask
@@ -284,6 +287,20 @@ __device__ __forceinline__ PageRec class_rec(int used, float scale, int64_t gpag
     return r;
 }
 
+// min(1, c / (norm + 1e-6)) with plain IEEE propagation: an infinite norm gives 0, a NaN norm a NaN
+// scale (the comparison is false for NaN), as the library optimizers do.  c <= 0: no clipping.
+__device__ __forceinline__ float clip_scale(double norm, double c) {
+    if (!(c > 0.0)) return 1.0f;
+    const double sc = c / (norm + 1e-6);
+    return sc > 1.0 ? 1.0f : (float)sc;
+}
+
+// What the one-pass kernel's wavefronts read until the value is there: bit patterns that no sum of
+// squares and no scale has (a NaN with every bit set; the NaNs of the arithmetic carry at most the
+// payload of a bf16).
+constexpr uint64_t kNoSum = ~(uint64_t)0;
+constexpr uint32_t kNoScale = ~(uint32_t)0;
+
 // One wavefront per listed page: combines the page's slice partials in a fixed order and turns
 // them into the page's clip scale / skip decision and the optional outputs.
 __global__ __launch_bounds__(kThreads) void apm_grad_finalize_kernel(FinalizeArgs a) {
@@ -304,13 +321,7 @@ __global__ __launch_bounds__(kThreads) void apm_grad_finalize_kernel(FinalizeArg
     if (lane != 0) return;
     const bool skip = a.skip_mode == APM_SKIP_UNTOUCHED && nz == 0u;
     const double norm = sqrt(s);
-    float scale = 1.0f;
-    if (a.max_norm > 0.0) {
-        // min(1, c / (norm + 1e-6)) with plain IEEE propagation: an infinite norm gives 0, a NaN
-        // norm a NaN scale (the comparison below is false for NaN), as the library optimizers do
-        const double sc = a.max_norm / (norm + 1e-6);
-        scale = sc > 1.0 ? 1.0f : (float)sc;
-    }
+    const float scale = clip_scale(norm, a.max_norm);
     const float sc = skip ? -1.0f : scale;
     if (a.run) reinterpret_cast<PageRun*>(a.recs)[i] = PageRun{used, sc};
     else if (a.staged) a.recs[i].scale = sc;
@@ -320,14 +331,21 @@ __global__ __launch_bounds__(kThreads) void apm_grad_finalize_kernel(FinalizeArg
     if (a.skip_mask) a.skip_mask[o] = skip ? 1 : 0;
 }
 
-// No reduce pass: one thread per listed page fills its record with scale 1.
+__device__ __forceinline__ void clear_sums(uint64_t* sums, int64_t n) {
+    for (int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x; j < n; j += (int64_t)gridDim.x * kThreads) sums[j] = kNoSum;
+}
+
+// No reduce pass: one thread per listed page fills its record with scale 1, or with the mark that the
+// one-pass kernel waits on.
 __global__ __launch_bounds__(kThreads) void apm_page_recs_kernel(FinalizeArgs a) {
+    if (a.sums) clear_sums(a.sums, a.n_listed * a.S);
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= a.n_listed) return;
     const int64_t page = a.grad_pages ? a.grad_pages[i] : a.grad_first + i;
     const int used = a.used[page];
-    if (a.run) reinterpret_cast<PageRun*>(a.recs)[i] = PageRun{used, 1.0f};
-    else a.recs[i] = class_rec(used, 1.0f, page, a.state_pages ? a.state_pages[i] : a.state_first + i, a.E, a.g16, a.p16);
+    const float scale = a.sums ? __uint_as_float(kNoScale) : 1.0f;
+    if (a.run) reinterpret_cast<PageRun*>(a.recs)[i] = PageRun{used, scale};
+    else a.recs[i] = class_rec(used, scale, page, a.state_pages ? a.state_pages[i] : a.state_first + i, a.E, a.g16, a.p16);
 }
 
 // Brings a call's page list and tensor addresses to where the kernels below read them, one thread per
@@ -347,6 +365,8 @@ struct StageArgs {
     int64_t E;
     int64_t* list;              // written from the list words
     int32_t* out;
+    uint64_t* sums;             // one-pass launches: as in FinalizeArgs
+    int64_t n_sums;
     const uint64_t* words;      // list, g, q words, unless they follow inline
     int64_t list_begin;         // the list words are those of positions [list_begin, + list_n)
     int32_t list_n;
@@ -368,6 +388,7 @@ __global__ __launch_bounds__(kThreads) void apm_stage_kernel(Args args) {
         if constexpr (sizeof(Args) > sizeof(StageArgs)) return args.word[k];
         else return a.words[k];
     };
+    if (a.sums) clear_sums(a.sums, a.n_sums);
     int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     int64_t page;
     if (a.list_n > 0) {
@@ -383,7 +404,7 @@ __global__ __launch_bounds__(kThreads) void apm_stage_kernel(Args args) {
     }
     PageRec* out = a.recs + i;
     const int used = a.used[page];
-    const PageRec own = class_rec(used, 1.0f, page, page, a.E, a.g16, a.p16);
+    const PageRec own = class_rec(used, a.n_sums > 0 ? __uint_as_float(kNoScale) : 1.0f, page, page, a.E, a.g16, a.p16);
     if (!a.has_g && !a.has_q) {
         *out = own;
         return;
@@ -392,7 +413,7 @@ __global__ __launch_bounds__(kThreads) void apm_stage_kernel(Args args) {
     // Tenant by tenant: with several launches each fills in the tenants whose addresses it carries.
     const TenantRec t = a.tenants[page];
     out->used = used;
-    out->scale = 1.0f;
+    out->scale = own.scale;
     out->pofs = own.pofs;
     out->off1 = t.off1;
 #pragma unroll
@@ -459,8 +480,9 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 // All loads are issued back to back, one wait, all stores back to back, in one basic block: on this
 // target loads and stores share one counter, and at the entry of a basic block the compiler must
 // assume the worst about what is outstanding.
-template <int U, bool WT>
-__device__ __forceinline__ void full_slice(const UpdateArgs& a, float scale, int lane, float* p_, float* m_, float* v_,
+// get_scale() is called when the loads are under way.  GPOL: cache policy of the gradient loads.
+template <int U, bool WT, int GPOL, class GetScale>
+__device__ __forceinline__ void full_slice(const UpdateArgs& a, GetScale&& get_scale, int lane, float* p_, float* m_, float* v_,
                                            const uint16_t* g_, uint16_t* q_) {
     const Rsrc P = make_rsrc(p_, kTile<U> * 4), M = make_rsrc(m_, kTile<U> * 4), V = make_rsrc(v_, kTile<U> * 4);
     const Rsrc G = make_rsrc(g_, kTile<U> * 2), Q = make_rsrc(q_, kTile<U> * 2);
@@ -469,7 +491,7 @@ __device__ __forceinline__ void full_slice(const UpdateArgs& a, float scale, int
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int o = lane * 16 + u * (kWave * 16);
-        g[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(G, lane * 8 + u * (kWave * 8), 0, kNT));
+        g[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(G, lane * 8 + u * (kWave * 8), 0, GPOL));
         p[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(P, o, 0, kNT));
         m[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(M, o, 0, kNT));
         v[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(V, o, 0, kNT));
@@ -477,6 +499,7 @@ __device__ __forceinline__ void full_slice(const UpdateArgs& a, float scale, int
     // without the barrier the scheduler sinks half of the loads between the vectors' arithmetic to
     // save registers
     __builtin_amdgcn_sched_barrier(0);
+    const float scale = get_scale();
     constexpr int kPolicy = WT ? kSC1 : kNT;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -555,7 +578,7 @@ __device__ __forceinline__ void update_slice(const UpdateArgs& a, const PageRec&
                                              float* p, float* m, float* v) {
     const int k = start >= rec.off1 ? 1 : 0;
     if (start + kTile<U> <= rec.end[k])
-        full_slice<U, WT>(a, rec.scale, lane, p + start, m + start, v + start, rec.g[k] + start, rec.q[k] + start);
+        full_slice<U, WT, kNT>(a, [&] { return rec.scale; }, lane, p + start, m + start, v + start, rec.g[k] + start, rec.q[k] + start);
     else cut_slice<U, GATHER, SCATTER, WT>(a, rec, (start >> 2) + lane, p, m, v);
 }
 
@@ -563,9 +586,15 @@ typedef int i32x2 __attribute__((ext_vector_type(2)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 static_assert(sizeof(PageRec) == sizeof(i32x16) && sizeof(PageRun) == sizeof(i32x2), "a record is one scalar load");
 
+// Through the constant address space these are scalar loads also in kernels that store before them; what
+// they read was written by an earlier kernel (the one-pass kernel does not use the scale it gets this way).
 __device__ __forceinline__ PageRec load_rec(const PageRec* at) {
-    const i32x16 raw = *reinterpret_cast<const i32x16*>(at);
-    return __builtin_bit_cast(PageRec, raw);
+    typedef const i32x16 __attribute__((address_space(4))) * Const;
+    return __builtin_bit_cast(PageRec, *(Const)reinterpret_cast<const i32x16*>(at));
+}
+__device__ __forceinline__ PageRun load_run(const PageRun* at) {
+    typedef const i32x2 __attribute__((address_space(4))) * Const;
+    return __builtin_bit_cast(PageRun, *(Const)reinterpret_cast<const i32x2*>(at));
 }
 
 // The HBM-resident form: grid.y walks the list positions, grid.x the slices (SLICES per
@@ -590,7 +619,7 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_kernel(const PageRec* r
 template <int U, int SLICES>
 __global__ __launch_bounds__(kUpdThreads) void apm_adamw_run_kernel(const PageRun* runs, float* p32, float* m32, float* v32,
                                                                     const uint16_t* g16, uint16_t* p16, int E, UpdateArgs a) {
-    const PageRun run = __builtin_bit_cast(PageRun, *reinterpret_cast<const i32x2*>(runs + blockIdx.y));
+    const PageRun run = load_run(runs + blockIdx.y);
     const int64_t at = (int64_t)blockIdx.y * E;
     const PageRec rec = class_rec(run.used, run.scale, 0, 0, 0, g16 + at, p16 + at);
     if (rec.scale < 0.0f) return;
@@ -639,7 +668,7 @@ __global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(Str
         PageRec rec;
         int64_t at;
         if (RUN) {
-            const PageRun run = __builtin_bit_cast(PageRun, *(reinterpret_cast<const i32x2*>(s.recs) + i));
+            const PageRun run = load_run(reinterpret_cast<const PageRun*>(s.recs) + i);
             at = i * s.E;
             rec = class_rec(run.used, run.scale, 0, 0, 0, s.g16 + at, s.p16 + at);
         } else {
@@ -648,6 +677,234 @@ __global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(Str
         }
         if (rec.scale < 0.0f || start >= rec.end[0]) continue;
         update_slice<kStrideU, false, false, WT>(a, rec, start, lane, s.p32 + at, s.m32 + at, s.v32 + at);
+    }
+}
+
+// ---- norms, clip scales and update in one kernel -----------------------------------------------
+//
+// A page is updated with a scale that depends on its whole gradient, so the gradient is read twice.
+// As a reduce pass in front of the update pass that is another 2 B per element from HBM (30 instead
+// of 28).  Here both are in one grid, one wavefront per item, in this order:
+//
+//     sums of pages 0 .. D-1 | for every page j: sums of page j+D, update slices of page j
+//
+// where the sums of a page are its kReduceTile-element tiles and one wavefront that adds them up and
+// publishes the page's scale.  The second reading of a page's gradient follows the first by D pages;
+// the first reading uses ordinary loads and all else is non-temporal, so the gradient is still in the
+// memory-side cache (256 MiB) then: D pages are kLookAhead elements, 32 MiB of gradient (4, 8, 16, 32, 64, 100 M
+// elements ahead, 1.3 B parameters: 6567, 6005, 5862, 5970, 6000, 6100 us a call).  Against a reduce
+// pass, a pass over its results and the update: 1.3 B parameters 5963 -> 5780 us, 127 M 596 -> 568,
+// 4.8 M in small pages 38.4 -> 34.0; from 1 M to 256 M elements never slower.
+//
+// Wavefronts hand results on through single words in device memory (a tile's sum, a page's scale)
+// which the stage / prepare pass has marked as not there yet; value and mark are one word, so
+// nothing else needs ordering.  Workgroups start in grid order, so whoever waits waits for wavefronts
+// that are already running, and by its turn an update slice almost always finds its scale in place.
+// Nothing relies on that order, though: after wait_limit polls a wavefront computes what it waits for
+// by itself, with the same result.
+constexpr int64_t kLookAhead = (int64_t)16 << 20;
+constexpr int kClipLds = 13312;  // 12 wavefronts per CU: 5832 us; 16, 13, 11, 10: 6000, 5840, 5873, 6164
+
+typedef uint64_t __attribute__((address_space(1))) * GlobalU64;
+typedef uint32_t __attribute__((address_space(1))) * GlobalU32;
+__device__ __forceinline__ uint64_t poll64(GlobalU64 p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ uint32_t poll32(GlobalU32 p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Sum of squares of one tile by one wavefront, with the additions in the order of apm_grad_reduce_kernel
+// (its four wavefronts' accumulators side by side).  Every lane returns it.
+template <bool GATHER>
+__device__ __forceinline__ double tile_sum(const PageRec& rec, int tile, int lane) {
+    constexpr int kWaves = kThreads / kWave, U = APM_REDUCE_U, kSpan = kThreads * 8 * U;
+    const int start = tile * kReduceTile, end = min(start + kReduceTile, rec.used);
+    const int k = start >= rec.off1 ? 1 : 0;
+    const bool inside = !GATHER || start + (((end - start) + 7) & ~7) <= rec.end[k];
+    double acc0[kWaves], acc1[kWaves];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) acc0[w] = acc1[w] = 0.0;
+    // elements from `end` on read as zero: the descriptor ends with the last vector that holds one
+    const Rsrc G = make_rsrc(rec.g[k] + start, inside && end > start ? (((end - start) + 7) & ~7) * 2 : 0);
+#pragma unroll 1
+    for (int at = start; at < end; at += kSpan) {
+        u32x4 x[U * kWaves];
+        if (inside) {
+#pragma unroll
+            for (int u = 0; u < U * kWaves; ++u)
+                x[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(G, (at - start + (u * kWave + lane) * 8) * 2, 0, 0));
+        } else {
+            // a tenant ends in this tile: whole vectors, all under way at once ...
+            typedef const u32x4 __attribute__((address_space(1))) * GlobalIn;
+#pragma unroll
+            for (int u = 0; u < U * kWaves; ++u) {
+                const int e = at + (u * kWave + lane) * 8, kk = e >= rec.off1 ? 1 : 0;
+                x[u] = u32x4{0u, 0u, 0u, 0u};
+                if (e < end && e + 8 <= rec.end[kk]) x[u] = *(GlobalIn) reinterpret_cast<const u32x4*>(rec.g[kk] + e);
+            }
+            // ... and the one with a tenant's last few elements, never read past them
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+                const int last = rec.end[kk] & ~7;
+                if (last == rec.end[kk] || last < at || last >= min(at + kSpan, end)) continue;
+                const int at_u = (last - at) / (8 * kWave), at_lane = (last - at) / 8 % kWave;
+                const u32x4 y = lane == at_lane ? gather_g8(rec, last) : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int u = 0; u < U * kWaves; ++u)
+                    if (u == at_u && lane == at_lane) x[u] = y;
+            }
+        }
+        if (at + kSpan > end) {
+#pragma unroll
+            for (int u = 0; u < U * kWaves; ++u) {
+                const int left = end - (at + (u * kWave + lane) * 8);  // boundary vector: drop elements at or beyond the extent
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    x[u][j] = left <= 2 * j ? 0u : left == 2 * j + 1 ? x[u][j] & 0x0000FFFFu : x[u][j];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double lo = (double)bf16lo(x[u * kWaves + w][j]), hi = (double)bf16hi(x[u * kWaves + w][j]);
+                    acc0[w] = fma(lo, lo, acc0[w]);
+                    acc1[w] = fma(hi, hi, acc1[w]);
+                }
+    }
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        const double s = wave_sum_f64(acc0[w] + acc1[w]);
+        t = w == 0 ? s : t + s;
+    }
+    return t;
+}
+
+// A page's sum by one wavefront on its own, in the order of apm_grad_finalize_kernel.
+template <bool GATHER>
+__device__ __forceinline__ double page_sum(const PageRec& rec, int n_tiles, int lane) {
+    double s = 0.0;
+#pragma unroll 1
+    for (int t = 0; t < n_tiles; ++t) {
+        const double x = tile_sum<GATHER>(rec, t, lane);
+        if ((t & (kWave - 1)) == lane) s += x;
+    }
+    return wave_sum_f64(s);
+}
+
+struct ClipArgs {
+    PageRec* recs;         // of the launch's first page; as PageRun if RUN
+    float* p32;            // RUN: of the launch's first page, as g16 and p16; otherwise of the class
+    float* m32;
+    float* v32;
+    const uint16_t* g16;
+    uint16_t* p16;
+    int64_t E;
+    uint64_t* sums;        // [count * S] of the launch
+    float* grad_norm;      // nullable
+    uint8_t* skip_mask;    // nullable: nothing is skipped here
+    const int32_t* out_index;  // of the launch's first page, or nullptr: out_first + position
+    int64_t out_first;
+    double max_norm;
+    int32_t S;
+    int32_t count;         // pages
+    int32_t ahead;         // D
+    int32_t n_tiles, n_slices;  // of the launch's largest page
+    int32_t wait_limit;
+};
+
+template <bool RUN, bool GATHER, bool SCATTER>
+__global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c, UpdateArgs a) {
+    constexpr int U = APM_UPDATE_U;
+    const int lane = (int)threadIdx.x;
+    // item -> page, index among the page's sums (tiles, then the adder) or among its slices
+    const uint32_t n_sum = (uint32_t)c.n_tiles + 1, n_both = n_sum + (uint32_t)c.n_slices;
+    uint32_t w = blockIdx.x, i, x;
+    bool sums = true;
+    if (w < (uint32_t)c.ahead * n_sum) {
+        i = w / n_sum;
+        x = w - i * n_sum;
+    } else {
+        w -= (uint32_t)c.ahead * n_sum;
+        const uint32_t mixed = (uint32_t)(c.count - c.ahead) * n_both;
+        if (w < mixed) {
+            i = w / n_both;
+            x = w - i * n_both;
+            sums = x < n_sum;
+            if (sums) i += (uint32_t)c.ahead;
+            else x -= n_sum;
+        } else {
+            w -= mixed;
+            i = w / (uint32_t)c.n_slices;
+            x = w - i * (uint32_t)c.n_slices;
+            i += (uint32_t)(c.count - c.ahead);
+            sums = false;
+        }
+    }
+    PageRec rec;
+    int64_t at;
+    float* scale_at;
+    if (RUN) {
+        PageRun* r = reinterpret_cast<PageRun*>(c.recs) + i;
+        at = (int64_t)i * c.E;
+        rec = class_rec(load_run(r).used, 0.0f, 0, 0, 0, c.g16 + at, c.p16 + at);
+        scale_at = &r->scale;
+    } else {
+        rec = load_rec(c.recs + i);
+        at = rec.pofs;
+        scale_at = &c.recs[i].scale;
+    }
+    const GlobalU32 word = (GlobalU32) reinterpret_cast<uint32_t*>(scale_at);
+    const GlobalU64 sum = (GlobalU64)(c.sums + (int64_t)i * c.S);
+    const int n_tiles = max(1, (rec.used + kReduceTile - 1) / kReduceTile);
+    if (sums && x < (uint32_t)c.n_tiles) {
+        if ((int)x >= n_tiles) return;
+        const double t = tile_sum<GATHER>(rec, (int)x, lane);
+        if (lane == 0) __hip_atomic_store(sum + x, (uint64_t)__double_as_longlong(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
+    if (sums) {
+        double s = 0.0;
+        bool all = true;
+#pragma unroll 1
+        for (int t = 0; t < n_tiles && all; t += kWave) {
+            uint64_t v = 0;
+            for (int polls = 0;; ++polls) {
+                v = t + lane < n_tiles ? poll64(sum + t + lane) : 0;
+                all = __all(v != kNoSum);
+                if (all || polls >= c.wait_limit) break;
+                __builtin_amdgcn_s_sleep(4);
+            }
+            if (t + lane < n_tiles) s += __longlong_as_double((long long)v);
+        }
+        s = all ? wave_sum_f64(s) : page_sum<GATHER>(rec, n_tiles, lane);
+        const double norm = sqrt(s);
+        if (lane != 0) return;
+        __hip_atomic_store(word, __float_as_uint(clip_scale(norm, c.max_norm)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int64_t o = c.out_index ? (int64_t)c.out_index[i] : c.out_first + i;
+        if (c.grad_norm) c.grad_norm[o] = (float)norm;
+        if (c.skip_mask) c.skip_mask[o] = 0;
+        return;
+    }
+    const int start = (int)x * kTile<U>;
+    if (start >= ((rec.used + 7) & ~7)) return;
+    // called when the slice's loads are under way: the first poll comes back with them
+    auto get_scale = [&]() -> float {
+        uint32_t seen = (uint32_t)__builtin_amdgcn_readfirstlane((int)poll32(word));
+        for (int polls = 0; seen == kNoScale; ++polls) {
+            if (polls >= c.wait_limit) return clip_scale(sqrt(page_sum<GATHER>(rec, n_tiles, lane)), c.max_norm);
+            __builtin_amdgcn_s_sleep(2);
+            seen = (uint32_t)__builtin_amdgcn_readfirstlane((int)poll32(word));
+        }
+        return __uint_as_float(seen);
+    };
+    const int k = start >= rec.off1 ? 1 : 0;
+    float *p = c.p32 + at, *m = c.m32 + at, *v = c.v32 + at;
+    if (start + kTile<U> <= rec.end[k]) {
+        full_slice<U, false, kNT>(a, get_scale, lane, p + start, m + start, v + start, rec.g[k] + start, rec.q[k] + start);
+    } else {
+        rec.scale = get_scale();
+        cut_slice<U, GATHER, SCATTER, false>(a, rec, (start >> 2) + lane, p, m, v);
     }
 }
 
@@ -740,6 +997,13 @@ hipError_t for_each_launch(const AdamwLaunch& L, F&& f) {
 }
 }  // namespace
 
+// Workgroups for one thread per listed page, or, if sums have to be marked, up to eight of those per thread.
+static unsigned record_grid(const AdamwLaunch& L) {
+    int64_t threads = L.n_listed;
+    if (L.one_pass && threads < L.n_listed * L.S / 8) threads = L.n_listed * L.S / 8;
+    return (unsigned)((threads + kThreads - 1) / kThreads);
+}
+
 hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
     ReduceArgs a{L.g16, L.recs, L.used, L.grad_pages, L.grad_first, 0, L.E, L.partials, L.nzflags, L.S};
     hipError_t e = for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used) {
@@ -751,7 +1015,7 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
     if (e != hipSuccess) return e;
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
                    L.partials, L.nzflags, L.S, L.skip_mode, L.max_norm, L.recs, L.g16, L.p16, L.E, L.is_run(),
-                   L.gather || L.scatter, L.grad_norm, L.skip_mask, L.out_index};
+                   L.gather || L.scatter, nullptr, L.grad_norm, L.skip_mask, L.out_index};
     const int per_wg = kThreads / kWave;
     hipLaunchKernelGGL(apm_grad_finalize_kernel, dim3((unsigned)((L.n_listed + per_wg - 1) / per_wg)),
                        dim3(kThreads), 0, s, f);
@@ -761,8 +1025,8 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
 hipError_t launch_prepare(const AdamwLaunch& L, hipStream_t s) {
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
                    nullptr, nullptr, L.S, L.skip_mode, 0.0, L.recs, L.g16, L.p16, L.E, L.is_run(),
-                   false, nullptr, nullptr, nullptr};
-    hipLaunchKernelGGL(apm_page_recs_kernel, dim3((unsigned)((L.n_listed + kThreads - 1) / kThreads)),
+                   false, L.one_pass ? reinterpret_cast<uint64_t*>(L.partials) : nullptr, nullptr, nullptr, nullptr};
+    hipLaunchKernelGGL(apm_page_recs_kernel, dim3(record_grid(L)),
                        dim3(kThreads), 0, s, f);
     return hipGetLastError();
 }
@@ -780,14 +1044,16 @@ hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s)
     StageArgsInline in;
     StageArgs& a = in.a;
     a = StageArgs{L.used, c.list ? c.d_list : L.grad_pages, L.grad_first, L.n_listed, c.tenants, L.recs, L.g16, L.p16, L.E,
-                  c.d_list, c.d_out, c.d_words, 0, 0, 0, 0, has_g, has_q};
+                  c.d_list, c.d_out, L.one_pass ? reinterpret_cast<uint64_t*>(L.partials) : nullptr,
+                  L.one_pass ? L.n_listed * L.S : 0, c.d_words, 0, 0, 0, 0, has_g, has_q};
     auto go = [&](int64_t list_begin, int64_t list_n, int64_t t_begin, int64_t t_n) -> hipError_t {
         a.list_begin = list_begin;
         a.list_n = (int32_t)list_n;
         a.t_begin = (int32_t)t_begin;
         a.t_n = (int32_t)t_n;
         const int64_t threads = list_n > 0 ? list_n : L.n_listed;
-        const dim3 grid((unsigned)((threads + kThreads - 1) / kThreads));
+        const unsigned pages_grid = (unsigned)((threads + kThreads - 1) / kThreads), sums_grid = a.sums ? record_grid(L) : 0u;
+        const dim3 grid(pages_grid > sums_grid ? pages_grid : sums_grid);
         if (c.d_words) {
             hipLaunchKernelGGL(apm_stage_kernel<StageArgs>, grid, dim3(kThreads), 0, s, a);
         } else {
@@ -799,6 +1065,7 @@ hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s)
             if (t_n > 0 && has_q) std::memcpy(w, c.q_ptrs + t_begin, (size_t)t_n * sizeof(uint64_t));
             hipLaunchKernelGGL(apm_stage_kernel<StageArgsInline>, grid, dim3(kThreads), 0, s, in);
         }
+        a.sums = nullptr;  // marked by the first launch
         return hipGetLastError();
     };
     if (c.d_words || stage_launches(c, L.n_listed) == 1) return go(0, n_list, 0, n_t);
@@ -866,6 +1133,54 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         else APM_LAUNCH_UPDATE(false, false);
 #undef APM_LAUNCH_UPDATE
     });
+}
+
+hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {
+    const UpdateArgs a{L.b1, L.omb1, L.b2, L.omb2, L.inv_sqrt_bc2, L.eps, L.step_size, L.lr_wd};
+    const bool run = L.is_run();
+    if (!L.one_pass || !L.partials || L.skip_mode != APM_SKIP_NONE || L.stride_wavefronts > 0) return hipErrorInvalidValue;
+    const ExtentClass all{0, L.n_listed, L.E};
+    const ExtentClass* cls = L.n_cls > 0 ? L.cls : &all;
+    const int n_cls = L.n_cls > 0 ? L.n_cls : 1;
+    for (int k = 0; k < n_cls; ++k) {
+        const int64_t max_used = cls[k].max_used > 0 ? cls[k].max_used : 1;
+        ClipArgs c{};
+        c.E = L.E;
+        c.S = L.S;
+        c.grad_norm = L.grad_norm;
+        c.skip_mask = L.skip_mask;
+        c.max_norm = L.max_norm;
+        c.wait_limit = L.wait_limit;
+        c.n_tiles = (int32_t)((max_used + kReduceTile - 1) / kReduceTile);
+        c.n_slices = (int32_t)((max_used + kTile<APM_UPDATE_U> - 1) / kTile<APM_UPDATE_U>);
+        const int64_t items = c.n_tiles + 1 + c.n_slices;
+        const int64_t piece = ((int64_t)1 << 30) / items > 0 ? ((int64_t)1 << 30) / items : 1;  // a grid's worth of pages
+        for (int64_t off = 0; off < cls[k].count; off += piece) {
+            const int64_t begin = cls[k].begin + off, count = cls[k].count - off < piece ? cls[k].count - off : piece;
+            const int64_t ahead = (kLookAhead + max_used - 1) / max_used;
+            c.count = (int32_t)count;
+            c.ahead = (int32_t)(ahead < count ? ahead : count);
+            c.recs = run ? reinterpret_cast<PageRec*>(reinterpret_cast<PageRun*>(L.recs) + begin) : L.recs + begin;
+            c.sums = reinterpret_cast<uint64_t*>(L.partials) + begin * L.S;
+            c.out_index = L.out_index ? L.out_index + begin : nullptr;
+            c.out_first = begin;
+            const int64_t fp32 = run ? (L.state_first + begin) * L.E : 0, b16 = run ? (L.grad_first + begin) * L.E : 0;
+            c.p32 = L.p32 + fp32;
+            c.m32 = L.m32 + fp32;
+            c.v32 = L.v32 + fp32;
+            c.g16 = L.g16 + b16;
+            c.p16 = L.p16 + b16;
+            const dim3 grid((unsigned)(count * items)), block(kUpdThreads);
+            if (run) hipLaunchKernelGGL((apm_adamw_clip_kernel<true, false, false>), grid, block, kClipLds, s, c, a);
+            else if (L.gather && L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, true>), grid, block, kClipLds, s, c, a);
+            else if (L.gather) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, false>), grid, block, kClipLds, s, c, a);
+            else if (L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, false, true>), grid, block, kClipLds, s, c, a);
+            else hipLaunchKernelGGL((apm_adamw_clip_kernel<false, false, false>), grid, block, kClipLds, s, c, a);
+            hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+    }
+    return hipSuccess;
 }
 
 }  // namespace apm

@@ -174,6 +174,9 @@ struct AdamwLaunch {
                                   // page slices (fp32 classes in host memory); 0: one per slice
     int32_t stride_waves_per_wg;  // how many of them share a workgroup, 1..16
     bool host_write_through;      // stride form: fp32 state stores written through at system scope
+    bool one_pass;                // launch_clip_update follows: the stage / prepare pass marks every scale and
+                                  // every sum in `partials` as not there yet
+    int32_t wait_limit;           // polls after which a wavefront of it computes what it waits for by itself
     bool is_run() const { return !state_pages && !grad_pages && !gather && !scatter; }
 };
 
@@ -199,6 +202,12 @@ struct StageCall {
 int64_t stage_launches(const StageCall& c, int64_t n_listed);
 hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s);
 hipError_t launch_adamw(const AdamwLaunch& a, hipStream_t s);
+// Norms, clip scales and update in one kernel, after the stage / prepare pass of a launch with
+// one_pass set; for skip_mode NONE and fp32 classes in device memory.
+hipError_t launch_clip_update(const AdamwLaunch& a, hipStream_t s);
+// Pool flag for tests: wavefronts that would wait for another one's result never do (wait_limit 0).
+constexpr uint32_t kPoolNeverWait = 1u << 31;
+constexpr int32_t kWaitLimit = 4096;
 hipError_t launch_grad_accum(uint16_t* acc, const uint16_t* g16, const int32_t* used,
                              const int64_t* d_pages, int64_t first, int64_t n_listed, int64_t E,
                              hipStream_t s);

@@ -82,10 +82,11 @@ extern "C" int apm_page_adamw_step_noalloc(apm_pool* pool, int64_t n_pages, int6
         rc = scratch_for_device(pool->desc.hip_device, &base);
         if (rc != APM_OK) return rc;
 
-        // Carve the scratch: page records, per-slice sums, per-slice flags.  Nothing needs clearing:
-        // the reduce pass writes every slice entry the finalize pass reads (slice 0 of a page
-        // always, the others whenever they hold used elements) and the finalize / prepare pass
-        // writes every listed page's record before the update reads it.
+        // Carve the scratch: page records, per-slice sums, per-slice flags.  Nothing needs clearing
+        // here: the reduce pass writes every slice entry the finalize pass reads (slice 0 of a page
+        // always, the others whenever they hold used elements), the prepare pass marks every sum
+        // of a one-pass update, and the finalize / prepare pass writes every listed page's record
+        // before the update reads it.
         const size_t S = (size_t)pool->S;
         const size_t n = (size_t)n_pages;
         L.recs = reinterpret_cast<PageRec*>(base);  // a run: n PageRun entries
@@ -110,14 +111,15 @@ extern "C" int apm_page_adamw_step_noalloc(apm_pool* pool, int64_t n_pages, int6
         L.skip_mask = skip_mask;
         hipStream_t s = static_cast<hipStream_t>(stream);
         const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
-        if (need_reduce) {
-            APM_HIP(launch_grad_reduce(L, s));
-        } else {
+        L.one_pass = need_reduce && L.skip_mode == APM_SKIP_NONE;
+        L.wait_limit = pool->desc.flags & kPoolNeverWait ? 0 : kWaitLimit;
+        if (!need_reduce) {
             L.partials = nullptr;
             L.nzflags = nullptr;
-            APM_HIP(launch_prepare(L, s));
         }
-        APM_HIP(launch_adamw(L, s));
+        if (need_reduce && !L.one_pass) APM_HIP(launch_grad_reduce(L, s));
+        else APM_HIP(launch_prepare(L, s));
+        APM_HIP(L.one_pass ? launch_clip_update(L, s) : launch_adamw(L, s));
         return APM_OK;
     });
 }

@@ -160,6 +160,12 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     L.grad_norm = grad_norm;
     L.skip_mask = skip_mask;
     L.recs = pool->d_recs;
+    L.one_pass = need_reduce && L.skip_mode == APM_SKIP_NONE;
+    L.wait_limit = pool->desc.flags & kPoolNeverWait ? 0 : kWaitLimit;
+    if (need_reduce) {
+        L.partials = pool->d_partials;
+        L.nzflags = pool->d_nzflags;
+    }
     const bool staged = n_list > 0 || tensors;
     if (staged) {
         APM_HIP(launch_stage(L, sc, stream));
@@ -168,9 +174,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
             if (rc != APM_OK) return rc;
         }
     }
-    if (need_reduce) {
-        L.partials = pool->d_partials;
-        L.nzflags = pool->d_nzflags;
+    if (need_reduce && !L.one_pass) {
         ScopedTiming t(pool, APM_K_REDUCE, stream);
         APM_HIP(launch_grad_reduce(L, stream));
     } else if (!staged) {
@@ -178,7 +182,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     }
     {
         ScopedTiming t(pool, APM_K_UPDATE, stream);
-        APM_HIP(launch_adamw(L, stream));
+        APM_HIP(L.one_pass ? launch_clip_update(L, stream) : launch_adamw(L, stream));
     }
     return APM_OK;
 }

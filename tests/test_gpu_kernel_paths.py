@@ -5,6 +5,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
+    import oracle
     import paper_2303_02868_amd as apm
     from gpu_helpers import DEV
 
@@ -93,3 +94,51 @@ def test_fused_step_equals_the_page_step_for_any_tensor_count_and_list(n_t, list
     assert got[0][2].ne(p0).any() or listed == "odd"
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+NEVER_WAIT = 1 << 31   # wavefronts of the clipped update compute what they would wait for
+
+
+@pytest.mark.parametrize("E,numels", [(8, [8, 3, 17]), (16384, [16384, 16383, 40000, 5]), (32776, [32776 * 3 + 257, 16385, 70001, 1]),
+                                      (66 * 16384, [66 * 16384 + 12345, 64 * 16384 + 1, 66 * 16384 * 2, 300])])
+@pytest.mark.parametrize("form", ["run", "reversed", "fused"])
+def test_clipped_update_with_and_without_waiting(E, numels, form):
+    """The clipped update hands sums and scales from wavefront to wavefront: the same bits when every
+    wavefront computes them by itself; norms against 64 bits (an fp32 rounding of an fp64 sum)."""
+    n_t, off = len(numels), [0]
+    for n in numels:
+        off.append(off[-1] + (n + 7) // 8 * 8)
+    gen = torch.Generator(device=DEV).manual_seed(E)
+    g = (torch.randn(off[-1], device=DEV, generator=gen) * 1e-2).bfloat16()
+    p0 = torch.randn(off[-1], device=DEV, generator=gen) * 0.02
+    lst = lambda t: apm.make_tensors(numels, apm.APM_F32 if t.dtype == torch.float32 else apm.APM_BF16,  # noqa: E731
+                                     [t.data_ptr() + t.element_size() * o for o in off[:-1]])
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.05, apm.APM_SKIP_NONE)
+    got = []
+    for flags in (0, NEVER_WAIT):
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, sum(-(-n // E) for n in numels) + 1, flags=flags)
+        apm.apm_pack_tensors(pool, apm.APM_P32, lst(p0), n_t)
+        apm.apm_pack_tensors(pool, apm.APM_G16, lst(g), n_t)
+        n = apm.lib().apm_pool_pages_in_use(pool.handle)
+        norm, q = torch.full((n,), -1.0, device=DEV), torch.zeros_like(g)
+        pages = list(range(n))[::-1] if form == "reversed" else None
+        if form == "fused":
+            apm.apm_page_adamw_step_fused(pool, pages, n, 3, hyper, lst(g), lst(q), n_t, norm, None)
+        else:
+            apm.apm_page_adamw_step(pool, pages, n, 3, hyper, norm, None)
+            apm.apm_unpack(pool, apm.APM_P16, lst(q), n_t)
+        out = [norm, q]
+        for st in (apm.APM_P32, apm.APM_M32, apm.APM_V32):
+            out.append(torch.zeros_like(p0))
+            apm.apm_unpack(pool, st, lst(out[-1]), n_t)
+        torch.cuda.synchronize()
+        got.append(out)
+        pool.destroy()
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    plan = oracle.plan_pack(numels, E)
+    sq = torch.zeros(n, dtype=torch.float64, device=DEV)
+    for s in plan.segments:
+        sq[s.page] += g[off[s.tensor] + s.tensor_off:off[s.tensor] + s.tensor_off + s.n].double().square().sum()
+    want = sq.sqrt().flip(0) if form == "reversed" else sq.sqrt()
+    assert torch.allclose(got[0][0].double(), want, rtol=2.0 ** -23, atol=0.0)
