@@ -8,7 +8,7 @@
 //   apm_adamw_clip_kernel     norms, clip scales and the update in one grid
 //   apm_adamw_stride_kernel   the same slice body run by a fixed, small number of wavefronts that
 //                             stride over all slices (fp32 classes in host memory across PCIe)
-//   apm_grad_accum_kernel     g' += g for the buffered gradient of the delayed path
+//   apm_grad_take_kernel      g' <- g or g' += g for the buffered gradient of the delayed path
 //
 // All are HBM-bandwidth bound (no reuse, ~50 VALU operations per element at most), so the design
 // is about memory access only: every wavefront instruction touches one fully contiguous span
@@ -144,6 +144,28 @@ __device__ __forceinline__ void scatter_q4(const PageRec& r, int e, u32x2 o) {
     }
 }
 
+// The workgroup's sum (wavefront butterfly, then wave 0..3) and OR, written by thread 0.
+__device__ __forceinline__ void block_sum(double acc, uint32_t nz, double* s_acc, uint32_t* s_nz, double* sum, uint32_t* flag) {
+    acc = wave_sum_f64(acc);
+    nz = wave_or_u32(nz);
+    const int wave = threadIdx.x / kWave;
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        s_acc[wave] = acc;
+        s_nz[wave] = nz;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    double t = s_acc[0];
+    uint32_t z = s_nz[0];
+#pragma unroll
+    for (int k = 1; k < kThreads / kWave; ++k) {
+        t += s_acc[k];
+        z |= s_nz[k];
+    }
+    *sum = t;
+    *flag = z;
+}
+
 struct ReduceArgs {
     const uint16_t* g16;
     const PageRec* recs;  // gather only
@@ -224,27 +246,9 @@ __global__ __launch_bounds__(kThreads) void apm_grad_reduce_kernel(ReduceArgs a)
             }
         }
     }
-    double acc = wave_sum_f64(acc0 + acc1);
-    nz = wave_or_u32(nz);
     __shared__ double s_acc[kThreads / kWave];
     __shared__ uint32_t s_nz[kThreads / kWave];
-    const int wave = threadIdx.x / kWave;
-    if ((threadIdx.x & (kWave - 1)) == 0) {
-        s_acc[wave] = acc;
-        s_nz[wave] = nz;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = s_acc[0];
-        uint32_t z = s_nz[0];
-#pragma unroll
-        for (int k = 1; k < kThreads / kWave; ++k) {
-            t += s_acc[k];
-            z |= s_nz[k];
-        }
-        a.partials[i * a.S + blockIdx.x] = t;
-        a.nzflags[i * a.S + blockIdx.x] = z;
-    }
+    block_sum(acc0 + acc1, nz, s_acc, s_nz, a.partials + i * a.S + blockIdx.x, a.nzflags + i * a.S + blockIdx.x);
 }
 
 struct FinalizeArgs {
@@ -263,6 +267,7 @@ struct FinalizeArgs {
     const uint16_t* g16;
     uint16_t* p16;
     int64_t E;
+    bool by_page;      // partials and flags are indexed by page, not by position
     bool run;
     bool staged;       // the records hold everything but the scale already (caller's tensors)
     uint64_t* sums;    // one-pass launches: [n_listed * S], to be marked as not there yet
@@ -313,8 +318,9 @@ __global__ __launch_bounds__(kThreads) void apm_grad_finalize_kernel(FinalizeArg
     double s = 0.0;
     uint32_t nz = 0;
     for (int k = lane; k < n_slices; k += kWave) {
-        s += a.partials[i * a.S + k];
-        nz |= a.nzflags[i * a.S + k];
+        const int64_t at = (a.by_page ? page : i) * a.S + k;
+        s += a.partials[at];
+        nz |= a.nzflags[at];
     }
     s = wave_sum_f64(s);
     nz = wave_or_u32(nz);
@@ -908,71 +914,131 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c,
     }
 }
 
-struct AccumArgs {
-    uint16_t* acc;        // buffered gradient g' (page layout)
-    const uint16_t* g16;  // incoming gradient (page layout)
+struct TakeArgs {
+    uint16_t* dst;
+    const uint16_t* src;
     const int32_t* used;
-    const int64_t* pages;
+    const int64_t* order;  // of the launch's first position, or nullptr: first + position
     int64_t first;
-    int64_t list_offset;
     int64_t E;
+    double* sums;
+    uint32_t* nzflags;
+    int32_t S;
+};
+struct TakeArgsInline {
+    TakeArgs a;
+    int32_t page[2 * kArgWords];
 };
 
-// g' <- bf16_rne(fp32(g') + fp32(g)) over the used extent of each listed page (Alg. 2, buffering
-// thread: "accumulate buffered gradients").  6 B/element, HBM-bound; same slicing as the reduce.
-__global__ __launch_bounds__(kThreads) void apm_grad_accum_kernel(AccumArgs a) {
-    const int64_t i = a.list_offset + blockIdx.y;
-    const int64_t page = a.pages ? a.pages[i] : a.first + i;
-    const int used8 = (a.used[page] + 7) & ~7;
-    const int start = blockIdx.x * kReduceTile;
-    if (start >= used8) return;
-    const int end = min(start + kReduceTile, used8);
-    u32x4* acc = reinterpret_cast<u32x4*>(a.acc + page * a.E);
-    const u32x4* g = reinterpret_cast<const u32x4*>(a.g16 + page * a.E);
-    constexpr int U = 4;
+// dst <- src, or g' <- bf16_rne(fp32(g') + fp32(g)) (Alg. 2, buffering thread: "accumulate buffered
+// gradients"), over the used extent of each listed page; 4 or 6 B per element, HBM-bound.  Only used
+// extents move: of the 533 pages of a 24-layer model 195 hold a bias or a norm.
+// SUMS: also the tile's sum of squares and non-zero flag of what was written, with the additions in the
+// order of apm_grad_reduce_kernel, so that the update that follows does not read the gradient twice.
+// 355 M parameters with clipping, hand-over beside the update: 2041 us an iteration with copies of whole
+// pages and the sums worked out by the update, 1877 like this; 124 M, four micro-batches, no clipping: 1116
+// and 1030.  A workgroup then takes a tile; without, 8 elements per lane, the fastest form of a copy.
+template <bool ACCUM, bool SUMS, class Args>
+__global__ __launch_bounds__(kThreads) void apm_grad_take_kernel(Args args) {
+    const TakeArgs* ap;
+    int64_t page;
+    if constexpr (sizeof(Args) > sizeof(TakeArgs)) {
+        ap = &args.a;
+        page = args.page[blockIdx.y];
+    } else {
+        ap = &args;
+        page = ap->order ? ap->order[blockIdx.y] : ap->first + blockIdx.y;
+    }
+    const TakeArgs& a = *ap;
+    constexpr int U = SUMS ? APM_REDUCE_U : 1, kSpan = kThreads * 8 * U, kItem = SUMS ? kReduceTile : kSpan;
+    const int used = a.used[page], used8 = (used + 7) & ~7;
+    const int start = blockIdx.x * kItem;
+    if (start >= used8 && !(SUMS && blockIdx.x == 0)) return;
+    const int end = min(start + kItem, used8);
+    u32x4* dst = reinterpret_cast<u32x4*>(a.dst + page * a.E);
+    const u32x4* src = reinterpret_cast<const u32x4*>(a.src + page * a.E);
+    double acc0 = 0.0, acc1 = 0.0;
+    uint32_t nz = 0;
 #pragma unroll 1
-    for (int e0 = start + (int)threadIdx.x * 8; e0 - (int)threadIdx.x * 8 < end; e0 += kThreads * 8 * U) {
+    for (int at = start; at < end; at += kSpan) {
         u32x4 x[U], y[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int e = e0 + u * (kThreads * 8);
+            const int e = at + (u * kThreads + (int)threadIdx.x) * 8;
+            x[u] = u32x4{0u, 0u, 0u, 0u};
             if (e < end) {
-                x[u] = __builtin_nontemporal_load(acc + (e >> 3));
-                y[u] = __builtin_nontemporal_load(g + (e >> 3));
+                x[u] = __builtin_nontemporal_load(src + (e >> 3));
+                if (ACCUM) y[u] = __builtin_nontemporal_load(dst + (e >> 3));
             }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int e = e0 + u * (kThreads * 8);
+            const int e = at + (u * kThreads + (int)threadIdx.x) * 8;
             if (e < end) {
-                u32x4 o;
+                if (ACCUM) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float lo = bf16lo(y[u][j]) + bf16lo(x[u][j]);
+                        const float hi = bf16hi(y[u][j]) + bf16hi(x[u][j]);
+                        x[u][j] = f32_to_bf16_rne(lo) | (f32_to_bf16_rne(hi) << 16);
+                    }
+                }
+                __builtin_nontemporal_store(x[u], dst + (e >> 3));
+            }
+            if (SUMS) {
+                const int left = used - e;  // boundary vector: elements at or beyond the extent do not count
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const float lo = bf16lo(x[u][j]) + bf16lo(y[u][j]);
-                    const float hi = bf16hi(x[u][j]) + bf16hi(y[u][j]);
-                    o[j] = f32_to_bf16_rne(lo) | (f32_to_bf16_rne(hi) << 16);
+                    const uint32_t v = left >= 2 * j + 2 ? x[u][j] : left == 2 * j + 1 ? x[u][j] & 0x0000FFFFu : 0u;
+                    nz |= v & 0x7FFF7FFFu;
+                    const double lo = (double)bf16lo(v), hi = (double)bf16hi(v);
+                    acc0 = fma(lo, lo, acc0);
+                    acc1 = fma(hi, hi, acc1);
                 }
-                __builtin_nontemporal_store(o, acc + (e >> 3));
             }
         }
     }
+    if (!SUMS) return;
+    __shared__ double s_acc[kThreads / kWave];
+    __shared__ uint32_t s_nz[kThreads / kWave];
+    block_sum(acc0 + acc1, nz, s_acc, s_nz, a.sums + page * a.S + blockIdx.x, a.nzflags + page * a.S + blockIdx.x);
 }
 
 constexpr int kMaxGridY = 65535;
 
 }  // namespace
 
-hipError_t launch_grad_accum(uint16_t* acc, const uint16_t* g16, const int32_t* used,
-                             const int64_t* d_pages, int64_t first, int64_t n_listed, int64_t E,
-                             hipStream_t s) {
-    AccumArgs a{acc, g16, used, d_pages, first, 0, E};
-    const unsigned nx = (unsigned)((E + kReduceTile - 1) / kReduceTile);
-    for (int64_t off = 0; off < n_listed; off += kMaxGridY) {
-        const int64_t ny = n_listed - off < kMaxGridY ? n_listed - off : kMaxGridY;
-        a.list_offset = off;
-        hipLaunchKernelGGL(apm_grad_accum_kernel, dim3(nx, (unsigned)ny), dim3(kThreads), 0, s, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+hipError_t launch_grad_take(const GradTake& t, hipStream_t s) {
+    TakeArgsInline in;
+    in.a = TakeArgs{t.dst, t.src, t.used, nullptr, 0, t.E, t.sums, t.nzflags, t.S};
+    const int item = t.sums ? kReduceTile : kThreads * 8;
+    for (int k = 0; k < t.n_cls; ++k) {
+        const ExtentClass& c = t.cls[k];
+        if (c.max_used <= 0 && !t.sums) continue;
+        const int64_t piece = t.host_pages ? 2 * kArgWords : kMaxGridY;
+        for (int64_t off = 0; off < c.count; off += piece) {
+            const int64_t n = c.count - off < piece ? c.count - off : piece;
+            const int64_t nx = (c.max_used + item - 1) / item;
+            const dim3 grid((unsigned)(nx > 0 ? nx : 1), (unsigned)n);
+            if (t.host_pages) {
+                for (int64_t i = 0; i < n; ++i) in.page[i] = (int32_t)t.host_pages[c.begin + off + i];
+            } else {
+                in.a.order = t.order ? t.order + c.begin + off : nullptr;
+                in.a.first = c.begin + off;
+            }
+#define APM_TAKE(ACCUM, SUMS)                                                                                       \
+    do {                                                                                                           \
+        if (t.host_pages) hipLaunchKernelGGL((apm_grad_take_kernel<ACCUM, SUMS, TakeArgsInline>), grid, dim3(kThreads), 0, s, in); \
+        else hipLaunchKernelGGL((apm_grad_take_kernel<ACCUM, SUMS, TakeArgs>), grid, dim3(kThreads), 0, s, in.a);   \
+    } while (0)
+            if (t.accumulate && t.sums) APM_TAKE(true, true);
+            else if (t.accumulate) APM_TAKE(true, false);
+            else if (t.sums) APM_TAKE(false, true);
+            else APM_TAKE(false, false);
+#undef APM_TAKE
+            hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
     }
     return hipSuccess;
 }
@@ -1005,8 +1071,9 @@ static unsigned record_grid(const AdamwLaunch& L) {
 }
 
 hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
+    hipError_t e = hipSuccess;
     ReduceArgs a{L.g16, L.recs, L.used, L.grad_pages, L.grad_first, 0, L.E, L.partials, L.nzflags, L.S};
-    hipError_t e = for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used) {
+    if (!L.sums_ready) e = for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used) {
         a.list_offset = begin;
         const dim3 grid((unsigned)((max_used + kReduceTile - 1) / kReduceTile), (unsigned)ny);
         if (L.gather) hipLaunchKernelGGL(apm_grad_reduce_kernel<true>, grid, dim3(kThreads), 0, s, a);
@@ -1014,7 +1081,7 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
     });
     if (e != hipSuccess) return e;
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
-                   L.partials, L.nzflags, L.S, L.skip_mode, L.max_norm, L.recs, L.g16, L.p16, L.E, L.is_run(),
+                   L.partials, L.nzflags, L.S, L.skip_mode, L.max_norm, L.recs, L.g16, L.p16, L.E, L.sums_ready, L.is_run(),
                    L.gather || L.scatter, nullptr, L.grad_norm, L.skip_mask, L.out_index};
     const int per_wg = kThreads / kWave;
     hipLaunchKernelGGL(apm_grad_finalize_kernel, dim3((unsigned)((L.n_listed + per_wg - 1) / per_wg)),
@@ -1024,7 +1091,7 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
 
 hipError_t launch_prepare(const AdamwLaunch& L, hipStream_t s) {
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
-                   nullptr, nullptr, L.S, L.skip_mode, 0.0, L.recs, L.g16, L.p16, L.E, L.is_run(),
+                   nullptr, nullptr, L.S, L.skip_mode, 0.0, L.recs, L.g16, L.p16, L.E, false, L.is_run(),
                    false, L.one_pass ? reinterpret_cast<uint64_t*>(L.partials) : nullptr, nullptr, nullptr, nullptr};
     hipLaunchKernelGGL(apm_page_recs_kernel, dim3(record_grid(L)),
                        dim3(kThreads), 0, s, f);

@@ -174,6 +174,7 @@ struct AdamwLaunch {
                                   // page slices (fp32 classes in host memory); 0: one per slice
     int32_t stride_waves_per_wg;  // how many of them share a workgroup, 1..16
     bool host_write_through;      // stride form: fp32 state stores written through at system scope
+    bool sums_ready;              // partials / nzflags hold the sums already, indexed by page
     bool one_pass;                // launch_clip_update follows: the stage / prepare pass marks every scale and
                                   // every sum in `partials` as not there yet
     int32_t wait_limit;           // polls after which a wavefront of it computes what it waits for by itself
@@ -208,9 +209,26 @@ hipError_t launch_clip_update(const AdamwLaunch& a, hipStream_t s);
 // Pool flag for tests: wavefronts that would wait for another one's result never do (wait_limit 0).
 constexpr uint32_t kPoolNeverWait = 1u << 31;
 constexpr int32_t kWaitLimit = 4096;
-hipError_t launch_grad_accum(uint16_t* acc, const uint16_t* g16, const int32_t* used,
-                             const int64_t* d_pages, int64_t first, int64_t n_listed, int64_t E,
-                             hipStream_t s);
+// Takes a gradient in page layout over into a buffered half: dst <- src, or (accumulate) dst <- dst + src, over
+// the used extents of the listed pages, and if `sums` is set works out the tiles' sums of squares and
+// non-zero flags of what it wrote, as the reduce pass would, indexed by page.
+struct GradTake {
+    const uint16_t* src;
+    uint16_t* dst;
+    bool accumulate;
+    const int32_t* used;
+    int64_t E;
+    int32_t S;
+    double* sums;       // [pool pages * S] or nullptr
+    uint32_t* nzflags;
+    // The pages: the device list `order` (a layout's launch order) in the given classes, or host_pages, which
+    // are carried in the kernel arguments, kArgWords * 2 a launch.
+    const int64_t* order;
+    const int64_t* host_pages;
+    const ExtentClass* cls;
+    int n_cls;
+};
+hipError_t launch_grad_take(const GradTake& t, hipStream_t s);
 
 // One segment of the layout as the copy kernel reads it: n elements from `tensor_off` of tensor
 // `tensor`, in the class region from element `page_elem`.  The table depends on the layout alone and
@@ -288,6 +306,7 @@ struct apm_pool {
     apm::ExtentClass order_cls[apm::kMaxExtentClasses] = {};
     int order_n_cls = 0;
     bool order_run = false;
+    int64_t layout_epoch = 0;  // counts the layouts installed
     double* d_partials = nullptr;   // reduce scratch, n_pages * S
     uint32_t* d_nzflags = nullptr;
     apm::PageRec* d_recs = nullptr;   // n_pages entries
@@ -305,6 +324,13 @@ struct apm_pool {
     hipEvent_t ev_applied[2] = {};
     bool applied_valid[2] = {false, false};
     hipEvent_t ev_flush = nullptr;
+    // Sums of squares and non-zero flags of what each half holds, worked out while it was taken over
+    // (n_pages * S entries, allocated when first wanted); gsum_ok: complete for the half's contents
+    // under the layout of gsum_epoch.
+    double* gsum[2] = {nullptr, nullptr};
+    uint32_t* gnz[2] = {nullptr, nullptr};
+    bool gsum_ok[2] = {false, false};
+    int64_t gsum_epoch[2] = {0, 0};
     int cur = 0;
     bool buffered = false;
     int64_t applied = 0;
@@ -327,11 +353,13 @@ struct apm_pool {
 
 namespace apm {
 // Validates a page list and enqueues the two kernels of one step.  g16_override != nullptr
-// replaces the pool's G16 region as the gradient source.
+// replaces the pool's G16 region as the gradient source; page_sums / page_nzflags: its tiles' sums
+// and flags, indexed by page, if they are known.
 int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t step,
                  const apm_hyper* hyper, const uint16_t* g16_override, float* grad_norm,
                  uint8_t* skip_mask, hipStream_t stream, const apm_tensor* grad_tensors = nullptr,
-                 const apm_tensor* p16_tensors = nullptr, int64_t n_tensors = 0);
+                 const apm_tensor* p16_tensors = nullptr, int64_t n_tensors = 0,
+                 double* page_sums = nullptr, uint32_t* page_nzflags = nullptr);
 int ensure_scratch(apm_pool* pool, bool list = false);
 // Allocates the ping-pong gradient halves, the events and the update stream of the delayed path.
 // caller != nullptr-able: the stream the producer works on; the update stream is chosen so that
@@ -358,8 +386,9 @@ int file_page_copy(apm_pool* dst, int64_t dst_page, apm_pool* src, int64_t src_p
 // (nullptr = flush).
 using DelayedApply = std::function<int(const uint16_t* g16, int64_t step, hipStream_t upd_stream,
                                        const int64_t* pages, int64_t n_pages, const apm_hyper* hyper)>;
+// want_sums: the hand-over also leaves the sums of what it staged in gsum / gnz.
 int delayed_call(apm_pool* pool, const int64_t* pages, int64_t n_pages, const void* new_g16,
-                 const apm_hyper* hyper, hipStream_t caller, const DelayedApply& apply);
+                 const apm_hyper* hyper, hipStream_t caller, const DelayedApply& apply, bool want_sums = false);
 
 // Brackets one kernel launch with events when the pool's timing is on.
 struct ScopedTiming {

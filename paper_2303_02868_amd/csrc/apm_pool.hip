@@ -134,6 +134,8 @@ void free_pool(apm_pool* pool) {
     }
     for (int k = 0; k < 2; ++k) {
         if (pool->gbuf[k]) (void)hipFree(pool->gbuf[k]);
+        if (pool->gsum[k]) (void)hipFree(pool->gsum[k]);
+        if (pool->gnz[k]) (void)hipFree(pool->gnz[k]);
         if (pool->ev_staged[k]) (void)hipEventDestroy(pool->ev_staged[k]);
         if (pool->ev_applied[k]) (void)hipEventDestroy(pool->ev_applied[k]);
     }
@@ -240,6 +242,7 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     take(pool->d_order_out, 3);
     pool->order.swap(order);
     pool->order_n_cls = n_cls;
+    pool->layout_epoch += 1;
     pool->order_run = true;
     for (int c = 0; c < kMaxExtentClasses; ++c) pool->order_cls[c] = cls[c];
     for (size_t k = 0; k < n_in_use; ++k)

@@ -53,7 +53,7 @@ constexpr int64_t kMaxStageLaunches = 4;
 int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t step,
                  const apm_hyper* hyper, const uint16_t* g16_override, float* grad_norm,
                  uint8_t* skip_mask, hipStream_t stream, const apm_tensor* grad_tensors,
-                 const apm_tensor* p16_tensors, int64_t n_tensors) {
+                 const apm_tensor* p16_tensors, int64_t n_tensors, double* page_sums, uint32_t* page_nzflags) {
     if (!pool) return fail(APM_EINVAL, "NULL pool");
     if (pool->desc.device != APM_DEV_GPU) return fail(APM_EDEVICE, "the update runs on GPU pools only");
     for (int st = 0; st < APM_N_STATES; ++st) {
@@ -160,11 +160,12 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     L.grad_norm = grad_norm;
     L.skip_mask = skip_mask;
     L.recs = pool->d_recs;
-    L.one_pass = need_reduce && L.skip_mode == APM_SKIP_NONE;
+    L.sums_ready = need_reduce && page_sums;
+    L.one_pass = need_reduce && !page_sums && L.skip_mode == APM_SKIP_NONE;
     L.wait_limit = pool->desc.flags & kPoolNeverWait ? 0 : kWaitLimit;
     if (need_reduce) {
-        L.partials = pool->d_partials;
-        L.nzflags = pool->d_nzflags;
+        L.partials = page_sums ? page_sums : pool->d_partials;
+        L.nzflags = page_sums ? page_nzflags : pool->d_nzflags;
     }
     const bool staged = n_list > 0 || tensors;
     if (staged) {
@@ -292,6 +293,40 @@ int ensure_delayed(apm_pool* pool, hipStream_t caller, bool probe) {
     return APM_OK;
 }
 
+// Room for the sums of half k; without it the update works them out itself.
+static bool ensure_sums(apm_pool* pool, int k) {
+    const size_t n = (size_t)pool->desc.n_pages * (size_t)pool->S;
+    if (!pool->gsum[k] && hipMalloc((void**)&pool->gsum[k], n * sizeof(double)) != hipSuccess) pool->gsum[k] = nullptr;
+    if (!pool->gnz[k] && hipMalloc((void**)&pool->gnz[k], n * sizeof(uint32_t)) != hipSuccess) pool->gnz[k] = nullptr;
+    if (pool->gsum[k] && pool->gnz[k]) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Copies or adds the used extents of the listed pages of g16 into half k.
+static int take_gradient(apm_pool* pool, int k, const uint16_t* g16, const int64_t* pages, int64_t n_pages, bool accumulate,
+                         bool sums, hipStream_t s) {
+    const int64_t in_use = (int64_t)pool->plan.pages.size();
+    GradTake t{g16, pool->gbuf[k], accumulate, pool->d_used, pool->desc.page_elems, pool->S, sums ? pool->gsum[k] : nullptr,
+               sums ? pool->gnz[k] : nullptr, nullptr, nullptr, pool->order_cls, pool->order_n_cls};
+    if (!pages && n_pages == in_use) {
+        t.order = pool->order_run ? nullptr : pool->d_order;
+        APM_HIP(launch_grad_take(t, s));
+        return APM_OK;
+    }
+    auto page_at = [&](int64_t i) { return pages ? pages[i] : i; };
+    std::vector<int64_t> order((size_t)n_pages);
+    ExtentClass cls[kMaxExtentClasses];
+    t.n_cls = group_by_extent(n_pages, pool->desc.page_elems, [&](int64_t i) {
+        return page_at(i) < in_use ? pool->plan.pages[(size_t)page_at(i)].used : (int64_t)0;
+    }, order.data(), cls);
+    for (int64_t& i : order) i = page_at(i);
+    t.cls = cls;
+    t.host_pages = order.data();
+    APM_HIP(launch_grad_take(t, s));
+    return APM_OK;
+}
+
 // Applies the buffered gradient (half `cur`) on the update stream.
 static int apply_buffered(apm_pool* pool, const DelayedApply& apply) {
     const int k = pool->cur;
@@ -306,7 +341,7 @@ static int apply_buffered(apm_pool* pool, const DelayedApply& apply) {
 }
 
 int delayed_call(apm_pool* pool, const int64_t* pages, int64_t n_pages, const void* new_g16,
-                 const apm_hyper* hyper, hipStream_t s, const DelayedApply& apply) {
+                 const apm_hyper* hyper, hipStream_t s, const DelayedApply& apply, bool want_sums) {
     APM_HIP(hipSetDevice(pool->desc.hip_device));
     int rc = ensure_delayed(pool, s, true);
     if (rc != APM_OK) return rc;
@@ -334,13 +369,21 @@ int delayed_call(apm_pool* pool, const int64_t* pages, int64_t n_pages, const vo
     // apm_delayed_grad_buffer has already staged it (and waited for the half to be free there).
     const bool in_place = src == dst;
     if (!in_place && pool->applied_valid[nxt]) APM_HIP(hipStreamWaitEvent(s, pool->ev_applied[nxt], 0));
-    int64_t k = in_place ? n_pages : 0;
-    while (k < n_pages) {  // one copy per run of consecutive pages
-        const int64_t p0 = pages ? pages[k] : k;
-        int64_t len = 1;
-        while (k + len < n_pages && (pages ? pages[k + len] : k + len) == p0 + len) ++len;
-        APM_HIP(hipMemcpyAsync(dst + (size_t)p0 * pb, src + (size_t)p0 * pb, pb * (size_t)len, hipMemcpyDeviceToDevice, s));
-        k += len;
+    pool->gsum_ok[nxt] = false;
+    if (!in_place && pool->has_layout && (reinterpret_cast<uintptr_t>(new_g16) & 15u) == 0) {
+        want_sums = want_sums && ensure_sums(pool, nxt);
+        rc = take_gradient(pool, nxt, static_cast<const uint16_t*>(new_g16), pages, n_pages, false, want_sums, s);
+        if (rc != APM_OK) return rc;
+        pool->gsum_ok[nxt] = want_sums;
+        pool->gsum_epoch[nxt] = pool->layout_epoch;
+    } else if (!in_place) {  // no layout yet, so no extents, or no vectors: whole pages, a copy per run of consecutive ones
+        for (int64_t k = 0; k < n_pages;) {
+            const int64_t p0 = pages ? pages[k] : k;
+            int64_t len = 1;
+            while (k + len < n_pages && (pages ? pages[k + len] : k + len) == p0 + len) ++len;
+            APM_HIP(hipMemcpyAsync(dst + (size_t)p0 * pb, src + (size_t)p0 * pb, pb * (size_t)len, hipMemcpyDeviceToDevice, s));
+            k += len;
+        }
     }
     APM_HIP(hipEventRecord(pool->ev_staged[nxt], s));
     pool->buf_hyper = *hyper;
@@ -393,9 +436,13 @@ extern "C" int apm_step_delayed(apm_pool* pool, const int64_t* pages, int64_t n_
         return delayed_call(pool, pages, n_pages, new_g16, hyper, static_cast<hipStream_t>(stream),
                             [&](const uint16_t* g16, int64_t step, hipStream_t upd, const int64_t* b_pages,
                                 int64_t b_n, const apm_hyper* b_hyper) {
+                                const int k = g16 == pool->gbuf[1] ? 1 : 0;
+                                const bool sums = pool->gsum_ok[k] && pool->gsum_epoch[k] == pool->layout_epoch;
                                 return enqueue_step(pool, b_pages, b_n, step, b_hyper, g16, pool->delayed_norm,
-                                                    pool->delayed_skip, upd);
-                            });
+                                                    pool->delayed_skip, upd, nullptr, nullptr, 0,
+                                                    sums ? pool->gsum[k] : nullptr, sums ? pool->gnz[k] : nullptr);
+                            },
+                            hyper->max_grad_norm > 0.0 || hyper->skip_mode != APM_SKIP_NONE || pool->delayed_norm || pool->delayed_skip);
     });
 }
 
@@ -409,34 +456,19 @@ extern "C" int apm_delayed_accumulate(apm_pool* pool, const int64_t* pages, int6
         if (n_pages == 0) return APM_OK;
         APM_HIP(hipSetDevice(pool->desc.hip_device));
         hipStream_t s = static_cast<hipStream_t>(stream);
-        int64_t first = 0;
-        bool run = true;
-        if (pages) {
-            first = pages[0];
-            for (int64_t k = 0; k < n_pages; ++k) {
+        if (pages)
+            for (int64_t k = 0; k < n_pages; ++k)
                 if (pages[k] < 0 || pages[k] >= pool->desc.n_pages) return fail(APM_ERANGE, "pages[%lld] out of range", (long long)k);
-                if (pages[k] != first + k) run = false;
-            }
-        }
-        const int64_t* d_list = nullptr;
-        int slot = -1;
-        if (!run) {
-            int rc = pool->ring.acquire((size_t)n_pages * sizeof(int64_t), &slot);
-            if (rc != APM_OK) return rc;
-            int64_t* h = static_cast<int64_t*>(pool->ring.h[slot]);
-            for (int64_t k = 0; k < n_pages; ++k) h[k] = pages[k];
-            rc = pool->ring.commit(slot, (size_t)n_pages * sizeof(int64_t), s);
-            if (rc != APM_OK) return rc;
-            d_list = static_cast<const int64_t*>(pool->ring.d[slot]);
-        }
         // The collecting half was staged on the producer's stream; the sum is ordered after it there,
         // and the "staged" event moves behind the sum so that the update sees the accumulated values.
         const int k = pool->cur;
         APM_HIP(hipStreamWaitEvent(s, pool->ev_staged[k], 0));
-        APM_HIP(launch_grad_accum(pool->gbuf[k], static_cast<const uint16_t*>(g16), pool->d_used, d_list, first,
-                                  n_pages, pool->desc.page_elems, s));
+        if (pool->has_layout) {  // without a layout no page has a used extent
+            if (pool->gsum_epoch[k] != pool->layout_epoch) pool->gsum_ok[k] = false;
+            int rc = take_gradient(pool, k, static_cast<const uint16_t*>(g16), pages, n_pages, true, pool->gsum_ok[k], s);
+            if (rc != APM_OK) return rc;
+        }
         APM_HIP(hipEventRecord(pool->ev_staged[k], s));
-        if (slot >= 0) return pool->ring.seal(slot, s);
         return APM_OK;
     });
 }

@@ -375,6 +375,7 @@ extern "C" int apm_tiered_step_delayed(apm_tiered* t, const void* new_g16, const
         const int nxt = dev->cur ^ 1;
         const int64_t N = (int64_t)dev->plan.pages.size();
         const size_t bytes = (size_t)N * (size_t)dev->desc.page_elems * 2u;
+        dev->gsum_ok[nxt] = false;
         APM_HIP(hipMemcpyAsync(dev->gbuf[nxt], new_g16, bytes, hipMemcpyDeviceToDevice, s));
         APM_HIP(hipEventRecord(dev->ev_staged[nxt], s));
         dev->buf_hyper = *hyper;

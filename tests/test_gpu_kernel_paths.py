@@ -142,3 +142,67 @@ def test_clipped_update_with_and_without_waiting(E, numels, form):
         sq[s.page] += g[off[s.tensor] + s.tensor_off:off[s.tensor] + s.tensor_off + s.n].double().square().sum()
     want = sq.sqrt().flip(0) if form == "reversed" else sq.sqrt()
     assert torch.allclose(got[0][0].double(), want, rtol=2.0 ** -23, atol=0.0)
+
+
+@pytest.mark.parametrize("clip,skip,norms", [(0.0, 0, False), (0.02, 0, True), (0.02, 1, True)])
+@pytest.mark.parametrize("listed,micro,shift", [("all", 1, 0), ("all", 3, 0), ("reversed", 2, 0), ("odd", 2, 0), ("all", 2, 1)])
+@pytest.mark.parametrize("E,n_t", [(8, 3), (2056, 1000), (49160, 9)])
+def test_delayed_hand_over_equals_the_synchronous_step(E, n_t, listed, micro, shift, clip, skip, norms):
+    """The hand-over copies used extents and leaves sums for the update; further micro-batches are added in
+    bf16.  Same bits as a synchronous step on the summed gradient: extents around the copy's and the sums'
+    items, more listed pages than one launch carries, a source that is not 16-byte aligned (shift)."""
+    numels = [(E + 3, 3 * E, E // 2 + 1, 16385, 1)[k % 5] if E > 8 else 5 for k in range(n_t)]
+    n = oracle.plan_pack(numels, E).n_pages
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    flat = torch.randn(n * E, device=DEV, generator=gen) * 0.02
+    pools, norm = [], [torch.full((n,), -1.0, device=DEV) for _ in range(2)]
+    mask = [torch.full((n,), 9, device=DEV, dtype=torch.uint8) for _ in range(2)]
+    for _ in range(2):
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n + 2)
+        off = [sum(numels[:k]) for k in range(n_t)]
+        apm.apm_pack_tensors(pool, apm.APM_P32, apm.make_tensors(numels, apm.APM_F32, [flat.data_ptr() + 4 * o for o in off]), n_t)
+        pools.append(pool)
+    pages = {"all": None, "odd": list(range(1, n, 2)), "reversed": list(range(n))[::-1]}[listed]
+    count = n if pages is None else len(pages)
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, clip, skip)
+    if norms:
+        apm.apm_delayed_set_outputs(pools[1], norm[1], mask[1])
+    raw = [torch.zeros((n + 2) * E + 8, device=DEV, dtype=torch.bfloat16) for _ in range(micro)]
+    for t in (1, 2, 3):
+        gs = []
+        for k in range(micro):
+            raw[k] = torch.zeros((n + 2) * E + 8, device=DEV, dtype=torch.bfloat16)
+            g = raw[k][shift if k == 0 else 0:][:(n + 2) * E]
+            g.copy_((torch.randn((n + 2) * E, device=DEV, generator=gen) * 1e-2).bfloat16())
+            if skip:
+                g.view(n + 2, E)[::3] = 0
+            gs.append(g)
+        total = gs[0].clone()
+        for g in gs[1:]:
+            total = total + g
+        view = torch.as_tensor(_Region(pools[0], apm.APM_G16, (n + 2) * E), device=DEV)
+        view.copy_(total.view(torch.int16))
+        apm.apm_page_adamw_step(pools[0], pages, count, t, hyper, norm[0] if norms else None, mask[0] if norms else None)
+        apm.apm_step_delayed(pools[1], pages, count, gs[0].data_ptr(), hyper)
+        for g in gs[1:]:
+            apm.apm_delayed_accumulate(pools[1], pages, count, g.data_ptr())
+        torch.cuda.synchronize()
+    apm.apm_step_delayed(pools[1], pages, count, None, hyper)
+    torch.cuda.synchronize()
+    if norms:
+        assert torch.equal(norm[0][:count], norm[1][:count]) and torch.equal(mask[0][:count], mask[1][:count])
+    for st, kind in ((apm.APM_P32, apm.APM_F32), (apm.APM_M32, apm.APM_F32), (apm.APM_V32, apm.APM_F32), (apm.APM_P16, apm.APM_BF16)):
+        out = [torch.zeros(sum(numels), device=DEV, dtype=torch.float32 if st < 3 else torch.bfloat16) for _ in range(2)]
+        for pool, o in zip(pools, out):
+            apm.apm_unpack(pool, st, apm.make_tensors(numels, kind, [o.data_ptr() + o.element_size() * x for x in off]), n_t)
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], out[1]), st
+    for pool in pools:
+        pool.destroy()
+
+
+class _Region:
+    """A 16-bit class region of a pool as an array torch can wrap."""
+
+    def __init__(self, pool, state, numel):
+        self.__cuda_array_interface__ = {"shape": (numel,), "typestr": "<i2", "data": (apm.apm_pool_state_ptr(pool, state), False), "version": 3}
