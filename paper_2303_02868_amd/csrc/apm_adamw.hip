@@ -91,10 +91,14 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float x) {
 #ifndef APM_UPDATE_LDS
 #define APM_UPDATE_LDS 14848
 #endif
-// When pages may be skipped on the device (APM_SKIP_UNTOUCHED), workgroups that only find that out and
-// leave dominate; kSkipSlices longer slices per workgroup cut their number (7 of 8 of 1046 pages
-// skipped: 1046 us a call, 1079 with four of U = 1).
-constexpr int kSkipU = 4, kSkipSlices = 4, kSkipLds = 32768;
+// When pages may be skipped on the device (APM_SKIP_UNTOUCHED) the pages to update are known only there:
+// the finalize pass notes them, and a grid of 1 / kSkipSpread of all slices' wavefronts walks the slices of
+// the noted pages, so that workgroups without work are few when most pages are skipped and no
+// wavefront has more than kSkipSpread slices when none is.  A wavefront without work costs 0.2 ns of the
+// call, one with many slices loses the address order that keeps the streams together.  1046 pages, 1 / 64,
+// 1 / 8 of the experts live, and 16 of 16: spread 8: 525, 953, 1355 us a call; 12: 486, 955, 1360; 16: 467, 952,
+// 1400; a grid of all slices, four of U = 4 to a workgroup: 508, 1010, 1350.
+constexpr int kSkipU = 1, kSkipSpread = 12, kSkipLds = 14848;
 
 // Gradient elements [e, e+8) of a page, read from its tenant tensors; elements that belong to no
 // tenant (alignment gap, padding) read as zero.  e is a multiple of 8, as every tenant offset is,
@@ -177,6 +181,7 @@ struct ReduceArgs {
     double* partials;
     uint32_t* nzflags;
     int32_t S;
+    int32_t* live;        // nullable: its counts are to be cleared
 };
 
 // Per (page, slice): sum of squares in fp64 and OR of the magnitude bits of the slice's used
@@ -185,6 +190,7 @@ struct ReduceArgs {
 // makes the result independent of scheduling.
 template <bool GATHER>
 __global__ __launch_bounds__(kThreads) void apm_grad_reduce_kernel(ReduceArgs a) {
+    if (a.live && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kMaxExtentClasses) a.live[threadIdx.x] = 0;
     const int64_t i = a.list_offset + blockIdx.y;
     const int64_t page = a.grad_pages ? a.grad_pages[i] : a.grad_first + i;
     const int used = a.used[page];
@@ -267,6 +273,9 @@ struct FinalizeArgs {
     const uint16_t* g16;
     uint16_t* p16;
     int64_t E;
+    int32_t* live;     // nullable: see kLiveInts
+    int64_t cls_begin[kMaxExtentClasses];
+    int32_t n_cls;
     bool by_page;      // partials and flags are indexed by page, not by position
     bool run;
     bool staged;       // the records hold everything but the scale already (caller's tensors)
@@ -335,6 +344,16 @@ __global__ __launch_bounds__(kThreads) void apm_grad_finalize_kernel(FinalizeArg
     const int64_t o = a.out_index ? (int64_t)a.out_index[i] : i;
     if (a.grad_norm) a.grad_norm[o] = skip ? 0.0f : (float)norm;
     if (a.skip_mask) a.skip_mask[o] = skip ? 1 : 0;
+    if (a.live && !skip) {
+        int c = 0;
+        while (c + 1 < a.n_cls && i >= a.cls_begin[c + 1]) ++c;
+        a.live[kMaxExtentClasses + a.cls_begin[c] + atomicAdd(a.live + c, 1)] = (int32_t)i;
+    }
+}
+
+// Clears the counts where no reduce pass does it.
+__global__ void apm_live_clear_kernel(int32_t* live) {
+    if (threadIdx.x < kMaxExtentClasses) live[threadIdx.x] = 0;
 }
 
 __device__ __forceinline__ void clear_sums(uint64_t* sums, int64_t n) {
@@ -486,8 +505,8 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 // All loads are issued back to back, one wait, all stores back to back, in one basic block: on this
 // target loads and stores share one counter, and at the entry of a basic block the compiler must
 // assume the worst about what is outstanding.
-// get_scale() is called when the loads are under way.  GPOL: cache policy of the gradient loads.
-template <int U, bool WT, int GPOL, class GetScale>
+// get_scale() is called when the loads are under way.
+template <int U, bool WT, class GetScale>
 __device__ __forceinline__ void full_slice(const UpdateArgs& a, GetScale&& get_scale, int lane, float* p_, float* m_, float* v_,
                                            const uint16_t* g_, uint16_t* q_) {
     const Rsrc P = make_rsrc(p_, kTile<U> * 4), M = make_rsrc(m_, kTile<U> * 4), V = make_rsrc(v_, kTile<U> * 4);
@@ -497,7 +516,7 @@ __device__ __forceinline__ void full_slice(const UpdateArgs& a, GetScale&& get_s
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int o = lane * 16 + u * (kWave * 16);
-        g[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(G, lane * 8 + u * (kWave * 8), 0, GPOL));
+        g[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(G, lane * 8 + u * (kWave * 8), 0, kNT));
         p[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(P, o, 0, kNT));
         m[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(M, o, 0, kNT));
         v[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(V, o, 0, kNT));
@@ -584,7 +603,7 @@ __device__ __forceinline__ void update_slice(const UpdateArgs& a, const PageRec&
                                              float* p, float* m, float* v) {
     const int k = start >= rec.off1 ? 1 : 0;
     if (start + kTile<U> <= rec.end[k])
-        full_slice<U, WT, kNT>(a, [&] { return rec.scale; }, lane, p + start, m + start, v + start, rec.g[k] + start, rec.q[k] + start);
+        full_slice<U, WT>(a, [&] { return rec.scale; }, lane, p + start, m + start, v + start, rec.g[k] + start, rec.q[k] + start);
     else cut_slice<U, GATHER, SCATTER, WT>(a, rec, (start >> 2) + lane, p, m, v);
 }
 
@@ -603,37 +622,63 @@ __device__ __forceinline__ PageRun load_run(const PageRun* at) {
     return __builtin_bit_cast(PageRun, *(Const)reinterpret_cast<const i32x2*>(at));
 }
 
-// The HBM-resident form: grid.y walks the list positions, grid.x the slices (SLICES per
-// workgroup) of a page.  The arguments are single values, what the prologue needs first, because
-// the hardware hands the leading 14 dwords of such an argument list to every wavefront in registers:
-// the record's load is then the only round trip before the first vector load.
-template <int U, bool GATHER, bool SCATTER, int SLICES>
+// The HBM-resident form: grid.y walks the list positions, grid.x the slices of a page.  The arguments
+// are single values, what the prologue needs first, because the hardware hands the leading 14 dwords
+// of such an argument list to every wavefront in registers: the record's load is then the only round
+// trip before the first vector load.
+template <int U, bool GATHER, bool SCATTER>
 __global__ __launch_bounds__(kUpdThreads) void apm_adamw_kernel(const PageRec* recs, float* p32, float* m32, float* v32,
                                                                 UpdateArgs a) {
     const PageRec rec = load_rec(recs + blockIdx.y);
-    if (rec.scale < 0.0f) return;  // a skipped page
-    const int used8 = (rec.used + 7) & ~7;
-#pragma unroll 1
-    for (int it = 0; it < SLICES; ++it) {
-        const int start = ((int)blockIdx.x * SLICES + it) * kTile<U>;
-        if (start >= used8) return;  // beyond the extent
-        update_slice<U, GATHER, SCATTER>(a, rec, start, (int)threadIdx.x, p32 + rec.pofs, m32 + rec.pofs, v32 + rec.pofs);
-    }
+    const int start = (int)blockIdx.x * kTile<U>;
+    if (start >= ((rec.used + 7) & ~7)) return;  // beyond the extent
+    update_slice<U, GATHER, SCATTER>(a, rec, start, (int)threadIdx.x, p32 + rec.pofs, m32 + rec.pofs, v32 + rec.pofs);
 }
 
 // The same for a run of pages in the page classes; all pointers are those of the launch's first page.
-template <int U, int SLICES>
+template <int U>
 __global__ __launch_bounds__(kUpdThreads) void apm_adamw_run_kernel(const PageRun* runs, float* p32, float* m32, float* v32,
                                                                     const uint16_t* g16, uint16_t* p16, int E, UpdateArgs a) {
     const PageRun run = load_run(runs + blockIdx.y);
     const int64_t at = (int64_t)blockIdx.y * E;
     const PageRec rec = class_rec(run.used, run.scale, 0, 0, 0, g16 + at, p16 + at);
-    if (rec.scale < 0.0f) return;
+    const int start = (int)blockIdx.x * kTile<U>;
+    if (start >= rec.end[0]) return;
+    update_slice<U, false, false>(a, rec, start, (int)threadIdx.x, p32 + at, m32 + at, v32 + at);
+}
+
+// Over the pages that the finalize pass noted, nx slices each.  positions: those of the launch's class;
+// recs (as PageRun if RUN) and, if RUN, the other pointers are those of list position 0.
+template <int U, bool RUN, bool GATHER, bool SCATTER>
+__global__ __launch_bounds__(kUpdThreads) void apm_adamw_live_kernel(const int32_t* n_live, const int32_t* positions, int nx,
+                                                                     const PageRec* recs, float* p32, float* m32, float* v32,
+                                                                     const uint16_t* g16, uint16_t* p16, int64_t E, UpdateArgs a) {
+    typedef const int32_t __attribute__((address_space(4))) * Const;
+    const uint32_t n = *(Const)n_live;
+    if ((uint64_t)n * (uint32_t)nx <= blockIdx.x) return;
+    // a wavefront's items are gridDim.x apart; page and slice advance by that without another division
+    uint32_t i = blockIdx.x / (uint32_t)nx, x = blockIdx.x - i * (uint32_t)nx;
+    const uint32_t di = gridDim.x / (uint32_t)nx, dx = gridDim.x - di * (uint32_t)nx;
 #pragma unroll 1
-    for (int it = 0; it < SLICES; ++it) {
-        const int start = ((int)blockIdx.x * SLICES + it) * kTile<U>;
-        if (start >= rec.end[0]) return;
-        update_slice<U, false, false>(a, rec, start, (int)threadIdx.x, p32 + at, m32 + at, v32 + at);
+    for (; i < n; i += di, x += dx) {
+        if (x >= (uint32_t)nx) {
+            x -= (uint32_t)nx;
+            if (++i >= n) return;
+        }
+        const int64_t pos = ((Const)positions)[i];
+        PageRec rec;
+        int64_t at;
+        if (RUN) {
+            at = pos * E;
+            const PageRun run = load_run(reinterpret_cast<const PageRun*>(recs) + pos);
+            rec = class_rec(run.used, run.scale, 0, 0, 0, g16 + at, p16 + at);
+        } else {
+            rec = load_rec(recs + pos);
+            at = rec.pofs;
+        }
+        const int start = (int)x * kTile<U>;
+        if (start < ((rec.used + 7) & ~7))
+            update_slice<U, GATHER, SCATTER>(a, rec, start, (int)threadIdx.x, p32 + at, m32 + at, v32 + at);
     }
 }
 
@@ -907,7 +952,7 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c,
     const int k = start >= rec.off1 ? 1 : 0;
     float *p = c.p32 + at, *m = c.m32 + at, *v = c.v32 + at;
     if (start + kTile<U> <= rec.end[k]) {
-        full_slice<U, false, kNT>(a, get_scale, lane, p + start, m + start, v + start, rec.g[k] + start, rec.q[k] + start);
+        full_slice<U, false>(a, get_scale, lane, p + start, m + start, v + start, rec.g[k] + start, rec.q[k] + start);
     } else {
         rec.scale = get_scale();
         cut_slice<U, GATHER, SCATTER, false>(a, rec, (start >> 2) + lane, p, m, v);
@@ -1072,7 +1117,9 @@ static unsigned record_grid(const AdamwLaunch& L) {
 
 hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
     hipError_t e = hipSuccess;
-    ReduceArgs a{L.g16, L.recs, L.used, L.grad_pages, L.grad_first, 0, L.E, L.partials, L.nzflags, L.S};
+    int32_t* live = L.skip_mode == APM_SKIP_UNTOUCHED && L.stride_wavefronts == 0 ? L.live : nullptr;
+    ReduceArgs a{L.g16, L.recs, L.used, L.grad_pages, L.grad_first, 0, L.E, L.partials, L.nzflags, L.S, live};
+    if (L.sums_ready && live) hipLaunchKernelGGL(apm_live_clear_kernel, dim3(1), dim3(kWave), 0, s, live);
     if (!L.sums_ready) e = for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used) {
         a.list_offset = begin;
         const dim3 grid((unsigned)((max_used + kReduceTile - 1) / kReduceTile), (unsigned)ny);
@@ -1081,8 +1128,9 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
     });
     if (e != hipSuccess) return e;
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
-                   L.partials, L.nzflags, L.S, L.skip_mode, L.max_norm, L.recs, L.g16, L.p16, L.E, L.sums_ready, L.is_run(),
+                   L.partials, L.nzflags, L.S, L.skip_mode, L.max_norm, L.recs, L.g16, L.p16, L.E, live, {}, L.n_cls, L.sums_ready, L.is_run(),
                    L.gather || L.scatter, nullptr, L.grad_norm, L.skip_mask, L.out_index};
+    for (int c = 0; c < L.n_cls; ++c) f.cls_begin[c] = L.cls[c].begin;
     const int per_wg = kThreads / kWave;
     hipLaunchKernelGGL(apm_grad_finalize_kernel, dim3((unsigned)((L.n_listed + per_wg - 1) / per_wg)),
                        dim3(kThreads), 0, s, f);
@@ -1091,7 +1139,7 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
 
 hipError_t launch_prepare(const AdamwLaunch& L, hipStream_t s) {
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
-                   nullptr, nullptr, L.S, L.skip_mode, 0.0, L.recs, L.g16, L.p16, L.E, false, L.is_run(),
+                   nullptr, nullptr, L.S, L.skip_mode, 0.0, L.recs, L.g16, L.p16, L.E, nullptr, {}, 0, false, L.is_run(),
                    false, L.one_pass ? reinterpret_cast<uint64_t*>(L.partials) : nullptr, nullptr, nullptr, nullptr};
     hipLaunchKernelGGL(apm_page_recs_kernel, dim3(record_grid(L)),
                        dim3(kThreads), 0, s, f);
@@ -1178,23 +1226,39 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
             }
         });
     }
-    const bool may_skip = L.partials && L.skip_mode == APM_SKIP_UNTOUCHED;
-    constexpr int U = APM_UPDATE_U;
-    const int64_t wg_span = may_skip ? kTile<kSkipU> * kSkipSlices : kTile<U>;
-    return for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used) {
-        const dim3 grid((unsigned)((max_used + wg_span - 1) / wg_span), (unsigned)ny), block(kUpdThreads);
-        if (run) {
-            float *p = state(L.p32, begin), *m = state(L.m32, begin), *v = state(L.v32, begin);
-            if (may_skip) hipLaunchKernelGGL((apm_adamw_run_kernel<kSkipU, kSkipSlices>), grid, block, kSkipLds, s, runs + begin, p, m, v, g16(begin), p16(begin), (int)L.E, a);
-            else hipLaunchKernelGGL((apm_adamw_run_kernel<U, 1>), grid, block, APM_UPDATE_LDS, s, runs + begin, p, m, v, g16(begin), p16(begin), (int)L.E, a);
-            return;
+    if (L.partials && L.skip_mode == APM_SKIP_UNTOUCHED) {
+        constexpr int U = kSkipU;
+        const ExtentClass all{0, L.n_listed, L.E};
+        const ExtentClass* cls = L.n_cls > 0 ? L.cls : &all;
+        const int n_cls = L.n_cls > 0 ? L.n_cls : 1;
+        for (int c = 0; c < n_cls; ++c) {
+            const int nx = (int)((cls[c].max_used + kTile<U> - 1) / kTile<U>);
+            if (nx == 0) continue;
+            int64_t wgs = (cls[c].count * nx + kSkipSpread - 1) / kSkipSpread;
+            if (wgs > (int64_t)1 << 30) wgs = (int64_t)1 << 30;
+            const dim3 grid((unsigned)wgs), block(kUpdThreads);
+            const int32_t *n_live = L.live + c, *positions = L.live + kMaxExtentClasses + cls[c].begin;
+#define APM_LAUNCH_LIVE(RUN, G, Q) hipLaunchKernelGGL((apm_adamw_live_kernel<U, RUN, G, Q>), grid, block, kSkipLds, s, n_live, positions, nx, \
+                                                     L.recs, state(L.p32, 0), state(L.m32, 0), state(L.v32, 0), run ? g16(0) : nullptr,  \
+                                                     run ? p16(0) : nullptr, L.E, a)
+            if (run) APM_LAUNCH_LIVE(true, false, false);
+            else if (L.gather && L.scatter) APM_LAUNCH_LIVE(false, true, true);
+            else if (L.gather) APM_LAUNCH_LIVE(false, true, false);
+            else if (L.scatter) APM_LAUNCH_LIVE(false, false, true);
+            else APM_LAUNCH_LIVE(false, false, false);
+#undef APM_LAUNCH_LIVE
+            hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
         }
-#define APM_LAUNCH_UPDATE(G, Q)                                                                         \
-    do {                                                                                               \
-        if (may_skip) hipLaunchKernelGGL((apm_adamw_kernel<kSkipU, G, Q, kSkipSlices>), grid, block, kSkipLds, s, L.recs + begin, L.p32, L.m32, L.v32, a); \
-        else hipLaunchKernelGGL((apm_adamw_kernel<U, G, Q, 1>), grid, block, APM_UPDATE_LDS, s, L.recs + begin, L.p32, L.m32, L.v32, a);       \
-    } while (0)
-        if (L.gather && L.scatter) APM_LAUNCH_UPDATE(true, true);
+        return hipSuccess;
+    }
+    constexpr int U = APM_UPDATE_U;
+    return for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used) {
+        const dim3 grid((unsigned)((max_used + kTile<U> - 1) / kTile<U>), (unsigned)ny), block(kUpdThreads);
+#define APM_LAUNCH_UPDATE(G, Q) hipLaunchKernelGGL((apm_adamw_kernel<U, G, Q>), grid, block, APM_UPDATE_LDS, s, L.recs + begin, L.p32, L.m32, L.v32, a)
+        if (run) hipLaunchKernelGGL((apm_adamw_run_kernel<U>), grid, block, APM_UPDATE_LDS, s, runs + begin, state(L.p32, begin),
+                                    state(L.m32, begin), state(L.v32, begin), g16(begin), p16(begin), (int)L.E, a);
+        else if (L.gather && L.scatter) APM_LAUNCH_UPDATE(true, true);
         else if (L.gather) APM_LAUNCH_UPDATE(true, false);
         else if (L.scatter) APM_LAUNCH_UPDATE(false, true);
         else APM_LAUNCH_UPDATE(false, false);

@@ -141,6 +141,11 @@ struct __attribute__((aligned(64))) PageRec {
 // PCIe (the streamer's direct mode, the file tier's window); see apm_stream.hip for the sweep.
 constexpr int kDirectWavefronts = 48;
 
+// Where the pages that a launch does not skip are noted: a count per extent class, then their positions,
+// those of a class from its first position on.  Part of a pool's array belongs to every page
+// (kLiveInts(1)), so that launches over disjoint pages can run side by side.
+constexpr int64_t kLiveInts(int64_t n_listed) { return (kMaxExtentClasses + 1) * n_listed; }
+
 struct AdamwLaunch {
     float* p32;
     float* m32;
@@ -174,6 +179,7 @@ struct AdamwLaunch {
                                   // page slices (fp32 classes in host memory); 0: one per slice
     int32_t stride_waves_per_wg;  // how many of them share a workgroup, 1..16
     bool host_write_through;      // stride form: fp32 state stores written through at system scope
+    int32_t* live;                // scratch of a launch that may skip pages, kLiveInts(n_listed) entries
     bool sums_ready;              // partials / nzflags hold the sums already, indexed by page
     bool one_pass;                // launch_clip_update follows: the stage / prepare pass marks every scale and
                                   // every sum in `partials` as not there yet
@@ -310,6 +316,7 @@ struct apm_pool {
     double* d_partials = nullptr;   // reduce scratch, n_pages * S
     uint32_t* d_nzflags = nullptr;
     apm::PageRec* d_recs = nullptr;   // n_pages entries
+    int32_t* d_live = nullptr;        // kLiveInts(n_pages) entries
     // what a call's list comes to (apm_stage_kernel), n_pages entries each, allocated on first use; like the scratch above they belong to the one step that is running on the pool
     int64_t* d_list = nullptr;
     int32_t* d_list_out = nullptr;

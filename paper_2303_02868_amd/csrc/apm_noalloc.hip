@@ -54,8 +54,8 @@ extern "C" int64_t apm_noalloc_max_pages(int64_t page_elems) {
     if (page_elems <= 0) return 0;
     const int64_t S = (page_elems + kReduceTile - 1) / kReduceTile;
     // three 256-byte aligned sections: records, sums, flags
-    constexpr int64_t kPerPage = 32;  // of which the records of a run of pages take 8
-    static_assert(sizeof(PageRun) <= kPerPage, "records must fit");
+    constexpr int64_t kPerPage = 32;  // the records of a run of pages and the notes on those not skipped
+    static_assert(sizeof(PageRun) + kLiveInts(1) * sizeof(int32_t) <= kPerPage, "they must fit");
     const int64_t per_page = kPerPage + S * (int64_t)(sizeof(double) + sizeof(uint32_t));
     return ((int64_t)kScratchBytes - 3 * 256) / per_page;
 }
@@ -90,7 +90,8 @@ extern "C" int apm_page_adamw_step_noalloc(apm_pool* pool, int64_t n_pages, int6
         const size_t S = (size_t)pool->S;
         const size_t n = (size_t)n_pages;
         L.recs = reinterpret_cast<PageRec*>(base);  // a run: n PageRun entries
-        size_t at = round256(n * sizeof(PageRun));
+        L.live = reinterpret_cast<int32_t*>(base + n * sizeof(PageRun));
+        size_t at = round256(n * sizeof(PageRun) + (size_t)kLiveInts(n_pages) * sizeof(int32_t));
         L.partials = reinterpret_cast<double*>(base + at);
         at += round256(n * S * sizeof(double));
         L.nzflags = reinterpret_cast<uint32_t*>(base + at);

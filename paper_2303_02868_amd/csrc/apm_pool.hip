@@ -72,6 +72,7 @@ int ensure_scratch(apm_pool* pool, bool list) {
     if (rc == APM_OK) rc = get((void**)&pool->d_nzflags, n * sizeof(uint32_t));
     const size_t n_pages = (size_t)pool->desc.n_pages;
     if (rc == APM_OK) rc = get((void**)&pool->d_recs, n_pages * sizeof(PageRec));
+    if (rc == APM_OK) rc = get((void**)&pool->d_live, (size_t)kLiveInts(pool->desc.n_pages) * sizeof(int32_t));
     if (rc == APM_OK && list) rc = get((void**)&pool->d_list, n_pages * sizeof(int64_t));
     if (rc == APM_OK && list) rc = get((void**)&pool->d_list_out, n_pages * sizeof(int32_t));
     return rc;
@@ -125,6 +126,7 @@ void free_pool(apm_pool* pool) {
     if (pool->d_partials) (void)hipFree(pool->d_partials);
     if (pool->d_nzflags) (void)hipFree(pool->d_nzflags);
     if (pool->d_recs) (void)hipFree(pool->d_recs);
+    if (pool->d_live) (void)hipFree(pool->d_live);
     if (pool->d_list) (void)hipFree(pool->d_list);
     if (pool->d_list_out) (void)hipFree(pool->d_list_out);
     pool->ring.destroy();

@@ -160,6 +160,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     L.grad_norm = grad_norm;
     L.skip_mask = skip_mask;
     L.recs = pool->d_recs;
+    L.live = pool->d_live;
     L.sums_ready = need_reduce && page_sums;
     L.one_pass = need_reduce && !page_sums && L.skip_mode == APM_SKIP_NONE;
     L.wait_limit = pool->desc.flags & kPoolNeverWait ? 0 : kWaitLimit;

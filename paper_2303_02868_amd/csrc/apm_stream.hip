@@ -332,6 +332,7 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
     L.v32 = s->stage[2];
     const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
     L.recs = dev->d_recs;
+    L.live = dev->d_live;
     if (need_reduce) {
         L.partials = dev->d_partials;
         L.nzflags = dev->d_nzflags;
@@ -372,6 +373,7 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
                 C.host_write_through = s->host_wt;
             }
             C.recs = L.recs + first;
+            C.live = L.live + kLiveInts(first);
             if (need_reduce) {
                 C.partials = L.partials + first * L.S;
                 C.nzflags = L.nzflags + first * L.S;
@@ -893,6 +895,7 @@ extern "C" int apm_streamer_step_scheduled(apm_streamer* s, const apm_task* task
         L.m32 = s->stage[1];
         L.v32 = s->stage[2];
         L.recs = dev->d_recs;
+    L.live = dev->d_live;
         const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
         if (need_reduce) {
             L.partials = dev->d_partials;

@@ -206,3 +206,58 @@ class _Region:
 
     def __init__(self, pool, state, numel):
         self.__cuda_array_interface__ = {"shape": (numel,), "typestr": "<i2", "data": (apm.apm_pool_state_ptr(pool, state), False), "version": 3}
+
+
+@pytest.mark.parametrize("dead", ["none", "all", "most", "first"])
+@pytest.mark.parametrize("form", ["run", "reversed", "fused", "noalloc"])
+@pytest.mark.parametrize("E,n_t,per", [(8, 40, 8), (4104, 30, 4103), (1 << 20, 6, 3 << 19), (1 << 20, 40, 5000)])
+def test_skipping_updates_the_touched_pages_and_no_others(E, n_t, per, form, dead):
+    """The grid over the noted pages: none, all, few live pages, several extent classes.  Same bits as a step
+    without skipping on the live pages; the others keep theirs."""
+    numels = [per if k % 7 else max(1, per // 600) for k in range(n_t)]
+    off = [0]
+    for m in numels:
+        off.append(off[-1] + (m + 7) // 8 * 8)
+    gen = torch.Generator(device=DEV).manual_seed(E + n_t)
+    g = (torch.rand(off[-1], device=DEV, generator=gen) + 1e-3).bfloat16()
+    alive = {"none": lambda t: True, "all": lambda t: False, "most": lambda t: t % 9 == 4, "first": lambda t: t > 1}[dead]
+    for t in range(n_t):
+        if not alive(t):
+            g[off[t]:off[t + 1]] = 0
+    p0 = torch.randn(off[-1], device=DEV, generator=gen) * 0.02
+    lst = lambda t: apm.make_tensors(numels, apm.APM_F32 if t.dtype == torch.float32 else apm.APM_BF16,  # noqa: E731
+                                     [t.data_ptr() + t.element_size() * o for o in off[:-1]])
+    plan = oracle.plan_pack(numels, E)
+    n = plan.n_pages
+    live = torch.zeros(n, dtype=torch.bool)
+    for s in plan.segments:
+        live[s.page] |= alive(s.tensor)
+    pages = list(range(n))[::-1] if form == "reversed" else None
+    got, mask = [], torch.full((n,), 9, device=DEV, dtype=torch.uint8)
+    for skip in (0, 1):
+        hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.0, skip)
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n + 1)
+        for st in (apm.APM_P32, apm.APM_M32):
+            apm.apm_pack_tensors(pool, st, lst(p0), n_t)
+        apm.apm_pack_tensors(pool, apm.APM_G16, lst(g), n_t)
+        q = torch.zeros_like(g)
+        if form == "fused":
+            apm.apm_page_adamw_step_fused(pool, pages, n, 3, hyper, lst(g), lst(q), n_t, None, mask if skip else None)
+        elif form == "noalloc":
+            apm.apm_page_adamw_step_noalloc(pool, n, 3, hyper, None, mask if skip else None)
+        else:
+            apm.apm_page_adamw_step(pool, pages, n, 3, hyper, None, mask if skip else None)
+        out = [torch.zeros_like(p0) for _ in range(3)]
+        for st, o in zip((apm.APM_P32, apm.APM_M32, apm.APM_V32), out):
+            apm.apm_unpack(pool, st, lst(o), n_t)
+        torch.cuda.synchronize()
+        got.append(out + [q])
+        pool.destroy()
+    assert torch.equal(mask.cpu() == 1, ~(live.flip(0) if form == "reversed" else live)) and (mask < 2).all()
+    for s in plan.segments:
+        at = slice(off[s.tensor] + s.tensor_off, off[s.tensor] + s.tensor_off + s.n)
+        if live[s.page]:
+            assert all(torch.equal(a[at], b[at]) for a, b in zip(*got))
+        else:
+            assert torch.equal(got[1][0][at], p0[at]) and torch.equal(got[1][1][at], p0[at])
+            assert not got[1][2][at].any() and not got[1][3][at].any()
