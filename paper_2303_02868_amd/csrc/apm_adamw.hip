@@ -91,6 +91,12 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float x) {
 #ifndef APM_UPDATE_LDS
 #define APM_UPDATE_LDS 14848
 #endif
+// Few elements from and to tensors: here workgroups of short pages that find nothing to do weigh more, and
+// a CU takes 17 wavefronts (us a call at 11 / 17: 4 M elements in 64 K pages 26.9 / 24.5, 16 M in 1 M pages
+// 95.1 / 89.3, 64 M 326 / 343; with clipping, at 12 / 17: 35.8 / 31.5, 112 / 101; pages read from and written to the
+// classes gain nothing: 8 M 38.4 / 39.1).
+constexpr int64_t kFewElems = (int64_t)24 << 20;
+constexpr int kFewLds = 9216;
 // When pages may be skipped on the device (APM_SKIP_UNTOUCHED) the pages to update are known only there:
 // the finalize pass notes them, and a grid of 1 / kSkipSpread of all slices' wavefronts walks the slices of
 // the noted pages, so that workgroups without work are few when most pages are skipped and no
@@ -636,10 +642,14 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_kernel(const PageRec* r
 }
 
 // The same for a run of pages in the page classes; all pointers are those of the launch's first page.
-template <int U>
-__global__ __launch_bounds__(kUpdThreads) void apm_adamw_run_kernel(const PageRun* runs, float* p32, float* m32, float* v32,
+// BARE: nothing has written records, `runs` is the page table (int32_t) and the scale is 1: a launch less,
+// eight quarter pages 13.2 -> 10.8 us a call.
+template <int U, bool BARE>
+__global__ __launch_bounds__(kUpdThreads) void apm_adamw_run_kernel(const void* runs, float* p32, float* m32, float* v32,
                                                                     const uint16_t* g16, uint16_t* p16, int E, UpdateArgs a) {
-    const PageRun run = load_run(runs + blockIdx.y);
+    PageRun run{0, 1.0f};
+    if (BARE) run.used = static_cast<const int32_t*>(runs)[blockIdx.y];
+    else run = load_run(static_cast<const PageRun*>(runs) + blockIdx.y);
     const int64_t at = (int64_t)blockIdx.y * E;
     const PageRec rec = class_rec(run.used, run.scale, 0, 0, 0, g16 + at, p16 + at);
     const int start = (int)blockIdx.x * kTile<U>;
@@ -1089,17 +1099,17 @@ hipError_t launch_grad_take(const GradTake& t, hipStream_t s) {
 }
 
 namespace {
-// Calls f(first list position, pages, largest used extent) for every launch of a pass: per extent
+// Calls f(first list position, pages, largest used extent, the class's used elements) for every launch of a pass: per extent
 // class, in pieces of at most kMaxGridY pages.
 template <class F>
 hipError_t for_each_launch(const AdamwLaunch& L, F&& f) {
-    const ExtentClass all{0, L.n_listed, L.E};
+    const ExtentClass all{0, L.n_listed, L.E, L.n_listed * L.E};
     const ExtentClass* c = L.n_cls > 0 ? L.cls : &all;
     const int n = L.n_cls > 0 ? L.n_cls : 1;
     for (int k = 0; k < n; ++k) {
         for (int64_t off = 0; off < c[k].count; off += kMaxGridY) {
             const int64_t ny = c[k].count - off < kMaxGridY ? c[k].count - off : kMaxGridY;
-            f(c[k].begin + off, ny, c[k].max_used > 0 ? c[k].max_used : 1);
+            f(c[k].begin + off, ny, c[k].max_used > 0 ? c[k].max_used : 1, c[k].sum_used);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
@@ -1120,7 +1130,7 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
     int32_t* live = L.skip_mode == APM_SKIP_UNTOUCHED && L.stride_wavefronts == 0 ? L.live : nullptr;
     ReduceArgs a{L.g16, L.recs, L.used, L.grad_pages, L.grad_first, 0, L.E, L.partials, L.nzflags, L.S, live};
     if (L.sums_ready && live) hipLaunchKernelGGL(apm_live_clear_kernel, dim3(1), dim3(kWave), 0, s, live);
-    if (!L.sums_ready) e = for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used) {
+    if (!L.sums_ready) e = for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used, int64_t sum_used) {
         a.list_offset = begin;
         const dim3 grid((unsigned)((max_used + kReduceTile - 1) / kReduceTile), (unsigned)ny);
         if (L.gather) hipLaunchKernelGGL(apm_grad_reduce_kernel<true>, grid, dim3(kThreads), 0, s, a);
@@ -1207,7 +1217,7 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
     auto p16 = [&](int64_t at) { return L.p16 + (L.grad_first + at) * L.E; };
     if (L.stride_wavefronts > 0) {
         if (L.gather || L.scatter) return hipErrorInvalidValue;  // host-resident state goes with the page classes
-        return for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used) {
+        return for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used, int64_t sum_used) {
             const int nx = (int)((max_used + kTile<kStrideU> - 1) / kTile<kStrideU>);
             const int64_t items = ny * nx;
             const int workers = (int)(items < L.stride_wavefronts ? items : L.stride_wavefronts);
@@ -1228,7 +1238,7 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
     }
     if (L.partials && L.skip_mode == APM_SKIP_UNTOUCHED) {
         constexpr int U = kSkipU;
-        const ExtentClass all{0, L.n_listed, L.E};
+        const ExtentClass all{0, L.n_listed, L.E, L.n_listed * L.E};
         const ExtentClass* cls = L.n_cls > 0 ? L.cls : &all;
         const int n_cls = L.n_cls > 0 ? L.n_cls : 1;
         for (int c = 0; c < n_cls; ++c) {
@@ -1253,16 +1263,20 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         return hipSuccess;
     }
     constexpr int U = APM_UPDATE_U;
-    return for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used) {
+    return for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used, int64_t sum_used) {
         const dim3 grid((unsigned)((max_used + kTile<U> - 1) / kTile<U>), (unsigned)ny), block(kUpdThreads);
-#define APM_LAUNCH_UPDATE(G, Q) hipLaunchKernelGGL((apm_adamw_kernel<U, G, Q>), grid, block, APM_UPDATE_LDS, s, L.recs + begin, L.p32, L.m32, L.v32, a)
-        if (run) hipLaunchKernelGGL((apm_adamw_run_kernel<U>), grid, block, APM_UPDATE_LDS, s, runs + begin, state(L.p32, begin),
-                                    state(L.m32, begin), state(L.v32, begin), g16(begin), p16(begin), (int)L.E, a);
+#define APM_LAUNCH_UPDATE(G, Q) hipLaunchKernelGGL((apm_adamw_kernel<U, G, Q>), grid, block, lds, s, L.recs + begin, L.p32, L.m32, L.v32, a)
+        const unsigned lds = (L.gather || L.scatter) && sum_used <= kFewElems ? kFewLds : APM_UPDATE_LDS;
+#define APM_LAUNCH_RUN(BARE, RUNS) hipLaunchKernelGGL((apm_adamw_run_kernel<U, BARE>), grid, block, lds, s, RUNS, state(L.p32, begin), \
+                                                      state(L.m32, begin), state(L.v32, begin), g16(begin), p16(begin), (int)L.E, a)
+        if (run && L.bare_run) APM_LAUNCH_RUN(true, L.used + L.grad_first + begin);
+        else if (run) APM_LAUNCH_RUN(false, runs + begin);
         else if (L.gather && L.scatter) APM_LAUNCH_UPDATE(true, true);
         else if (L.gather) APM_LAUNCH_UPDATE(true, false);
         else if (L.scatter) APM_LAUNCH_UPDATE(false, true);
         else APM_LAUNCH_UPDATE(false, false);
 #undef APM_LAUNCH_UPDATE
+#undef APM_LAUNCH_RUN
     });
 }
 
@@ -1270,7 +1284,7 @@ hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {
     const UpdateArgs a{L.b1, L.omb1, L.b2, L.omb2, L.inv_sqrt_bc2, L.eps, L.step_size, L.lr_wd};
     const bool run = L.is_run();
     if (!L.one_pass || !L.partials || L.skip_mode != APM_SKIP_NONE || L.stride_wavefronts > 0) return hipErrorInvalidValue;
-    const ExtentClass all{0, L.n_listed, L.E};
+    const ExtentClass all{0, L.n_listed, L.E, L.n_listed * L.E};
     const ExtentClass* cls = L.n_cls > 0 ? L.cls : &all;
     const int n_cls = L.n_cls > 0 ? L.n_cls : 1;
     for (int k = 0; k < n_cls; ++k) {
@@ -1302,11 +1316,12 @@ hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {
             c.g16 = L.g16 + b16;
             c.p16 = L.p16 + b16;
             const dim3 grid((unsigned)(count * items)), block(kUpdThreads);
-            if (run) hipLaunchKernelGGL((apm_adamw_clip_kernel<true, false, false>), grid, block, kClipLds, s, c, a);
-            else if (L.gather && L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, true>), grid, block, kClipLds, s, c, a);
-            else if (L.gather) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, false>), grid, block, kClipLds, s, c, a);
-            else if (L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, false, true>), grid, block, kClipLds, s, c, a);
-            else hipLaunchKernelGGL((apm_adamw_clip_kernel<false, false, false>), grid, block, kClipLds, s, c, a);
+            const unsigned lds = (L.gather || L.scatter) && cls[k].sum_used <= kFewElems ? kFewLds : kClipLds;
+            if (run) hipLaunchKernelGGL((apm_adamw_clip_kernel<true, false, false>), grid, block, lds, s, c, a);
+            else if (L.gather && L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, true>), grid, block, lds, s, c, a);
+            else if (L.gather) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, false>), grid, block, lds, s, c, a);
+            else if (L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, false, true>), grid, block, lds, s, c, a);
+            else hipLaunchKernelGGL((apm_adamw_clip_kernel<false, false, false>), grid, block, lds, s, c, a);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }

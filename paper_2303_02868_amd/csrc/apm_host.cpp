@@ -68,11 +68,12 @@ int make_plan(int64_t E, const int64_t* numels, int64_t n, Plan* out) {
 int group_by_extent(int64_t n, int64_t E, const std::function<int64_t(int64_t)>& size_of, int64_t* order,
                     ExtentClass cls[kMaxExtentClasses]) {
     auto class_of = [&](int64_t used) { return used * 4 > E ? 0 : used * 32 > E ? 1 : used * 512 > E ? 2 : 3; };
-    int64_t cnt[kMaxExtentClasses] = {}, mx[kMaxExtentClasses] = {};
+    int64_t cnt[kMaxExtentClasses] = {}, mx[kMaxExtentClasses] = {}, sum[kMaxExtentClasses] = {};
     for (int64_t k = 0; k < n; ++k) {
         const int64_t u = size_of(k);
         const int c = class_of(u);
         ++cnt[c];
+        sum[c] += u;
         if (u > mx[c]) mx[c] = u;
     }
     // A class is worth its extra launches only if it saves enough idle workgroups (counted in
@@ -88,6 +89,7 @@ int group_by_extent(int64_t n, int64_t E, const std::function<int64_t(int64_t)>&
         if (cnt[c] * ((mx[j] - mx[c]) / kSpan) < kWorthWorkgroups) {
             for (int q = c; q < kMaxExtentClasses; ++q) if (into[q] == c) into[q] = j;
             cnt[j] += cnt[c];
+            sum[j] += sum[c];
             cnt[c] = 0;
         }
     }
@@ -95,7 +97,7 @@ int group_by_extent(int64_t n, int64_t E, const std::function<int64_t(int64_t)>&
     int n_cls = 0;
     for (int64_t c = 0, at = 0; c < kMaxExtentClasses; ++c) {
         fill[c] = at;
-        if (cnt[c] > 0) cls[n_cls++] = ExtentClass{at, cnt[c], mx[c]};
+        if (cnt[c] > 0) cls[n_cls++] = ExtentClass{at, cnt[c], mx[c], sum[c]};
         at += cnt[c];
     }
     for (int64_t k = 0; k < n; ++k) order[fill[into[class_of(size_of(k))]]++] = k;

@@ -70,6 +70,7 @@ struct ExtentClass {
     int64_t begin;     // first position
     int64_t count;     // items
     int64_t max_used;  // largest size among them (elements)
+    int64_t sum_used;  // and the sum of their sizes
 };
 // order[pos] = index of the item at position pos (classes one after the other, the given order kept
 // inside each); returns the number of classes.  E = the size that the class limits are fractions of.
@@ -179,6 +180,7 @@ struct AdamwLaunch {
                                   // page slices (fp32 classes in host memory); 0: one per slice
     int32_t stride_waves_per_wg;  // how many of them share a workgroup, 1..16
     bool host_write_through;      // stride form: fp32 state stores written through at system scope
+    bool bare_run;                // a run without a reduce or prepare pass: the update reads `used` itself
     int32_t* live;                // scratch of a launch that may skip pages, kLiveInts(n_listed) entries
     bool sums_ready;              // partials / nzflags hold the sums already, indexed by page
     bool one_pass;                // launch_clip_update follows: the stage / prepare pass marks every scale and

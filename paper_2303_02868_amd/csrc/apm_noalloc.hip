@@ -118,8 +118,9 @@ extern "C" int apm_page_adamw_step_noalloc(apm_pool* pool, int64_t n_pages, int6
             L.partials = nullptr;
             L.nzflags = nullptr;
         }
+        L.bare_run = !need_reduce;
         if (need_reduce && !L.one_pass) APM_HIP(launch_grad_reduce(L, s));
-        else APM_HIP(launch_prepare(L, s));
+        else if (!L.bare_run) APM_HIP(launch_prepare(L, s));
         APM_HIP(L.one_pass ? launch_clip_update(L, s) : launch_adamw(L, s));
         return APM_OK;
     });

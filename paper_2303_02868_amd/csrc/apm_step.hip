@@ -180,7 +180,8 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
         ScopedTiming t(pool, APM_K_REDUCE, stream);
         APM_HIP(launch_grad_reduce(L, stream));
     } else if (!staged) {
-        APM_HIP(launch_prepare(L, stream));
+        L.bare_run = run && !need_reduce;
+        if (!L.bare_run) APM_HIP(launch_prepare(L, stream));
     }
     {
         ScopedTiming t(pool, APM_K_UPDATE, stream);
