@@ -1152,8 +1152,8 @@ def main():
                     traffic = float(line.split("=", 1)[1])
         out["hbm_GBps_update_kernel"] = r["achieved"]
         out["hbm_frac_of_peak"] = r["achieved"] / HBM_PEAK_GBPS
-        out["roofline"] = {"bound": "hbm", "kernel": "apm_adamw_kernel", "achieved": r["achieved"],
-                           "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": r["achieved"] / HBM_PEAK_GBPS,
+        out["roofline"] = {"bound": "hbm", "kernel": "apm_adamw_clip_kernel" if clip > 0 else "apm_adamw_kernel",
+                           "achieved": r["achieved"], "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": r["achieved"] / HBM_PEAK_GBPS,
                            "traffic": traffic,
                            "algorithmic_bytes_per_launch": r["elems_update"] * BYTES_UPDATE,
                            "avg_launch_ms": r["upd_ms"]}
