@@ -302,6 +302,7 @@ struct apm_pool {
     int fd[APM_N_STATES] = {-1, -1, -1, -1, -1};  // FILE pools: one file per stored class
 
     int32_t* d_used = nullptr;      // device page table: used extent per page
+    char* d_tables = nullptr;       // the layout's tables below, in one allocation
     apm::SegRec* d_segs = nullptr;  // the layout's segments, ordered as seg_launches lists them
     std::vector<apm::SegLaunch> seg_launches;
     int32_t seg_ranges = 0;         // groups of kArgWords tensors they are split into

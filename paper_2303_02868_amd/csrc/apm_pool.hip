@@ -119,10 +119,7 @@ void free_pool(apm_pool* pool) {
         }
     }
     if (pool->d_used) (void)hipFree(pool->d_used);
-    if (pool->d_segs) (void)hipFree(pool->d_segs);
-    if (pool->d_tenants) (void)hipFree(pool->d_tenants);
-    if (pool->d_order) (void)hipFree(pool->d_order);
-    if (pool->d_order_out) (void)hipFree(pool->d_order_out);
+    if (pool->d_tables) (void)hipFree(pool->d_tables);
     if (pool->d_partials) (void)hipFree(pool->d_partials);
     if (pool->d_nzflags) (void)hipFree(pool->d_nzflags);
     if (pool->d_recs) (void)hipFree(pool->d_recs);
@@ -199,24 +196,29 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     ExtentClass cls[kMaxExtentClasses] = {};
     const int n_cls = group_by_extent((int64_t)n_in_use, plan.E, [&](int64_t k) { return plan.pages[(size_t)k].used; }, order.data(), cls);
     std::vector<int32_t> order_out(order.begin(), order.end());
-    // Device copies of the tables; freed unless the pool takes them over at the end.
+    // Device copies of the tables, in one allocation; freed unless the pool takes it over at the end.
     struct Tables {
-        void* d[4] = {};
-        ~Tables() { for (void* x : d) if (x) (void)hipFree(x); }
+        char* d = nullptr;
+        size_t at[4], bytes = 0;
+        ~Tables() { if (d) (void)hipFree(d); }
     } tables;
-    auto upload = [](void** d, const void* h, size_t bytes) -> int {
-        if (bytes == 0) return APM_OK;
-        hipError_t e = hipMalloc(d, bytes);
-        if (e == hipSuccess) e = hipMemcpy(*d, h, bytes, hipMemcpyHostToDevice);
-        if (e == hipSuccess) return APM_OK;
-        (void)hipGetLastError();
-        return fail(APM_ENOMEM, "uploading %zu bytes of the layout's tables failed: %s", bytes, hipGetErrorString(e));
-    };
-    int rc_up = upload(&tables.d[0], recs.data(), recs.size() * sizeof(SegRec));
-    if (rc_up == APM_OK) rc_up = upload(&tables.d[1], tenants.data(), n_in_use * sizeof(TenantRec));
-    if (rc_up == APM_OK) rc_up = upload(&tables.d[2], order.data(), n_in_use * sizeof(int64_t));
-    if (rc_up == APM_OK) rc_up = upload(&tables.d[3], order_out.data(), n_in_use * sizeof(int32_t));
-    if (rc_up != APM_OK) return rc_up;
+    const void* src[4] = {recs.data(), tenants.data(), order.data(), order_out.data()};
+    const size_t len[4] = {recs.size() * sizeof(SegRec), n_in_use * sizeof(TenantRec), n_in_use * sizeof(int64_t), n_in_use * sizeof(int32_t)};
+    for (int k = 0; k < 4; ++k) {
+        tables.at[k] = tables.bytes;
+        tables.bytes += (len[k] + 255) / 256 * 256;
+    }
+    if (tables.bytes > 0) {
+        std::vector<char> image(tables.bytes, 0);
+        for (int k = 0; k < 4; ++k)
+            if (len[k] > 0) std::memcpy(image.data() + tables.at[k], src[k], len[k]);
+        hipError_t e = hipMalloc((void**)&tables.d, tables.bytes);
+        if (e == hipSuccess) e = hipMemcpy(tables.d, image.data(), tables.bytes, hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(APM_ENOMEM, "uploading %zu bytes of the layout's tables failed: %s", tables.bytes, hipGetErrorString(e));
+        }
+    }
     if (pool->has_layout) {  // a different layout replaces the old one: old contents would alias
         int rc = zero_regions(pool, s, false);
         if (rc != APM_OK) return rc;
@@ -233,15 +235,11 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
         pool->layout_ids[(size_t)i] = tensors[i].id;
     }
     pool->plan = std::move(plan);
-    auto take = [&](auto*& mine, int k) {  // the old table goes with `tables`; hipFree waits for its readers
-        void* old = mine;
-        mine = static_cast<std::remove_reference_t<decltype(mine)>>(tables.d[k]);
-        tables.d[k] = old;
-    };
-    take(pool->d_segs, 0);
-    take(pool->d_tenants, 1);
-    take(pool->d_order, 2);
-    take(pool->d_order_out, 3);
+    std::swap(pool->d_tables, tables.d);  // the old tables go with `tables`; hipFree waits for their readers
+    pool->d_segs = reinterpret_cast<SegRec*>(pool->d_tables + tables.at[0]);
+    pool->d_tenants = reinterpret_cast<TenantRec*>(pool->d_tables + tables.at[1]);
+    pool->d_order = reinterpret_cast<int64_t*>(pool->d_tables + tables.at[2]);
+    pool->d_order_out = reinterpret_cast<int32_t*>(pool->d_tables + tables.at[3]);
     pool->order.swap(order);
     pool->order_n_cls = n_cls;
     pool->layout_epoch += 1;
