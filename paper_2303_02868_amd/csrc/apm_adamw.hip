@@ -1245,7 +1245,8 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
             const int nx = (int)((cls[c].max_used + kTile<U> - 1) / kTile<U>);
             if (nx == 0) continue;
             int64_t wgs = (cls[c].count * nx + kSkipSpread - 1) / kSkipSpread;
-            if (wgs > (int64_t)1 << 30) wgs = (int64_t)1 << 30;
+            const int64_t cap = L.max_workgroups > 0 ? L.max_workgroups : max_workgroups(kUpdThreads);
+            if (wgs > cap) wgs = cap;  // each walks further
             const dim3 grid((unsigned)wgs), block(kUpdThreads);
             const int32_t *n_live = L.live + c, *positions = L.live + kMaxExtentClasses + cls[c].begin;
 #define APM_LAUNCH_LIVE(RUN, G, Q) hipLaunchKernelGGL((apm_adamw_live_kernel<U, RUN, G, Q>), grid, block, kSkipLds, s, n_live, positions, nx, \
@@ -1299,7 +1300,7 @@ hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {
         c.n_tiles = (int32_t)((max_used + kReduceTile - 1) / kReduceTile);
         c.n_slices = (int32_t)((max_used + kTile<APM_UPDATE_U> - 1) / kTile<APM_UPDATE_U>);
         const int64_t items = c.n_tiles + 1 + c.n_slices;
-        const int64_t piece = ((int64_t)1 << 30) / items > 0 ? ((int64_t)1 << 30) / items : 1;  // a grid's worth of pages
+        const int64_t piece = pages_per_launch(items, kUpdThreads, L.max_workgroups);
         for (int64_t off = 0; off < cls[k].count; off += piece) {
             const int64_t begin = cls[k].begin + off, count = cls[k].count - off < piece ? cls[k].count - off : piece;
             const int64_t ahead = (kLookAhead + max_used - 1) / max_used;

@@ -104,6 +104,12 @@ int group_by_extent(int64_t n, int64_t E, const std::function<int64_t(int64_t)>&
     return n_cls;
 }
 
+int64_t pages_per_launch(int64_t per_page, int threads, int64_t limit) {
+    const int64_t cap = max_workgroups(threads);
+    const int64_t pages = (limit > 0 && limit < cap ? limit : cap) / per_page;
+    return pages > 0 ? pages : 1;
+}
+
 int emit_plan(const Plan& pl, apm_segment* segs, int64_t* n_segs, int64_t* n_pages,
               double* fragmentation) {
     const int64_t need = (int64_t)pl.segs.size();

@@ -77,6 +77,13 @@ struct ExtentClass {
 int group_by_extent(int64_t n, int64_t E, const std::function<int64_t(int64_t)>& size_of, int64_t* order,
                     ExtentClass cls[kMaxExtentClasses]);
 
+// One dimension of a grid holds fewer than 2^32 work-items (the runtime refuses more): the workgroups of
+// `threads` work-items that a one-dimensional launch can have.
+constexpr int64_t max_workgroups(int threads) { return (((int64_t)1 << 32) - 1) / threads; }
+// Pages that one such launch takes if a page is `per_page` workgroups; at least one (the largest page, 2^30
+// elements, is under 2^23 of any kernel here).  limit > 0: at most that many workgroups.
+int64_t pages_per_launch(int64_t per_page, int threads, int64_t limit = 0);
+
 // Words of 8 bytes that a launch carries in its kernel arguments: 3.4 KB, which leaves room for the
 // rest under the 4 KB that argument blocks may have.
 constexpr int kArgWords = 440;
@@ -186,6 +193,7 @@ struct AdamwLaunch {
     bool one_pass;                // launch_clip_update follows: the stage / prepare pass marks every scale and
                                   // every sum in `partials` as not there yet
     int32_t wait_limit;           // polls after which a wavefront of it computes what it waits for by itself
+    int64_t max_workgroups;       // of a one-dimensional launch; 0: what the hardware takes
     bool is_run() const { return !state_pages && !grad_pages && !gather && !scatter; }
 };
 
@@ -325,6 +333,7 @@ struct apm_pool {
     int32_t* d_list_out = nullptr;
     int32_t S = 0;
     apm::StageRing ring;
+    int64_t max_workgroups = 0;  // see AdamwLaunch; set by tests only
 
     // one-step-stale update state
     hipStream_t upd_stream = nullptr;
@@ -415,3 +424,7 @@ struct ScopedTiming {
     ~ScopedTiming() { if (end) (void)hipEventRecord(end, stream); }
 };
 }  // namespace apm
+
+// For tests, not part of the C ABI: caps the workgroups of the pool's one-dimensional update launches
+// (0: no cap), so that small pools exercise what otherwise takes tens of millions of pages.
+extern "C" int apm_test_set_max_workgroups(apm_pool* pool, int64_t max_workgroups);

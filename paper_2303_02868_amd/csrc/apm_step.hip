@@ -164,6 +164,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     L.sums_ready = need_reduce && page_sums;
     L.one_pass = need_reduce && !page_sums && L.skip_mode == APM_SKIP_NONE;
     L.wait_limit = pool->desc.flags & kPoolNeverWait ? 0 : kWaitLimit;
+    L.max_workgroups = pool->max_workgroups;
     if (need_reduce) {
         L.partials = page_sums ? page_sums : pool->d_partials;
         L.nzflags = page_sums ? page_nzflags : pool->d_nzflags;
@@ -500,4 +501,10 @@ extern "C" int apm_delayed_set_outputs(apm_pool* pool, float* grad_norm, uint8_t
         pool->delayed_skip = skip_mask;
         return APM_OK;
     });
+}
+
+extern "C" int apm_test_set_max_workgroups(apm_pool* pool, int64_t max_workgroups) {
+    if (!pool || max_workgroups < 0) return fail(APM_EINVAL, "bad argument");
+    pool->max_workgroups = max_workgroups;
+    return APM_OK;
 }

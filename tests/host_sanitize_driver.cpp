@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "apm.h"
+#include "apm_internal.h"
 
 namespace {
 
@@ -167,6 +168,29 @@ void plan_errors() {
     if (apm_schedule_plan(off2, pages2, bytes2, 2, nullptr, 1, 16, 100, nullptr, &n_tasks, nullptr) == APM_OK) die("decreasing offsets accepted");
 }
 
+// The pieces that a pass over many pages is launched in: every launch within what one grid dimension
+// holds (fewer than 2^32 work-items), every page in one of them.
+void launch_pieces(Rng& r) {
+    const int64_t E[] = {8, 64, 256, 1024, 16384, 65536, 1 << 20, 1 << 30};
+    for (int64_t e : E)
+        for (int64_t limit : {(int64_t)0, (int64_t)5, (int64_t)1000}) {
+            // the clipped update: sums of 16384 elements, their adder, slices of 256 elements
+            const int64_t per_page = (e + 16383) / 16384 + 1 + (e + 255) / 256;
+            const int64_t piece = apm::pages_per_launch(per_page, 64, limit);
+            if (piece < 1) die("no page fits a launch", e);
+            if (piece * per_page * 64 >= (int64_t)1 << 32) die("launch beyond a grid dimension", e, piece);
+            if (limit > 0 && piece > 1 && piece * per_page > limit) die("launch beyond its limit", e, piece);
+            if (limit == 0 && (piece + 1) * per_page * 64 < (int64_t)1 << 32) die("more pages would fit", e, piece);
+        }
+    for (int i = 0; i < 10000; ++i) {
+        const int threads = 64 << r.below(5);
+        const int64_t per_page = 1 + r.below((int64_t)1 << r.below(23));
+        const int64_t piece = apm::pages_per_launch(per_page, threads);
+        if (piece < 1 || (piece > 1 && piece * per_page * threads >= (int64_t)1 << 32)) die("launch beyond a grid dimension", per_page, threads);
+    }
+    if (apm::max_workgroups(64) * 64 >= (int64_t)1 << 32 || (apm::max_workgroups(64) + 1) * 64 < (int64_t)1 << 32) die("workgroup limit");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -174,6 +198,7 @@ int main(int argc, char** argv) {
     Rng r{0x2303028680ull};
     pack_errors();
     plan_errors();
+    launch_pieces(r);
     for (int i = 0; i < cases; ++i) pack_case(r);
     for (int i = 0; i < cases; ++i) plan_case(r);
     std::printf("ok %d\n", cases);

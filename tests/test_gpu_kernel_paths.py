@@ -1,4 +1,6 @@
 """Small GPU tests of single kernel paths at the sizes and alignments where they can go wrong."""
+import ctypes
+
 import pytest
 import torch
 
@@ -261,3 +263,46 @@ def test_skipping_updates_the_touched_pages_and_no_others(E, n_t, per, form, dea
         else:
             assert torch.equal(got[1][0][at], p0[at]) and torch.equal(got[1][1][at], p0[at])
             assert not got[1][2][at].any() and not got[1][3][at].any()
+
+
+@pytest.mark.parametrize("cap", [1, 7, 1000])
+@pytest.mark.parametrize("skip", [0, 1])
+@pytest.mark.parametrize("form", ["run", "reversed", "fused"])
+def test_updates_in_several_launches_equal_one_launch(form, skip, cap):
+    """Page counts beyond what one grid holds are launched in pieces; a low cap on the workgroups of a
+    launch gives several pieces per extent class at a small size.  Same bits as without the cap."""
+    E, numels = 1 << 18, [3, (1 << 18) * 5 + 77, 100, 1, 2000] + [40] * 300
+    n_t, off = len(numels), [0]
+    for m in numels:
+        off.append(off[-1] + (m + 7) // 8 * 8)
+    gen = torch.Generator(device=DEV).manual_seed(cap)
+    g = (torch.randn(off[-1], device=DEV, generator=gen) * 1e-2).bfloat16()
+    g[off[7]:off[100]] = 0
+    p0 = torch.randn(off[-1], device=DEV, generator=gen) * 0.02
+    lst = lambda t: apm.make_tensors(numels, apm.APM_F32 if t.dtype == torch.float32 else apm.APM_BF16,  # noqa: E731
+                                     [t.data_ptr() + t.element_size() * o for o in off[:-1]])
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.05, skip)
+    got = []
+    for c in (0, cap):
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, oracle.plan_pack(numels, E).n_pages)
+        assert apm.lib().apm_test_set_max_workgroups(ctypes.c_void_p(pool.handle), ctypes.c_int64(c)) == 0
+        apm.apm_pack_tensors(pool, apm.APM_P32, lst(p0), n_t)
+        apm.apm_pack_tensors(pool, apm.APM_G16, lst(g), n_t)
+        n = apm.lib().apm_pool_pages_in_use(pool.handle)
+        norm, q = torch.full((n,), -1.0, device=DEV), torch.zeros_like(g)
+        pages = list(range(n))[::-1] if form == "reversed" else None
+        if form == "fused":
+            apm.apm_page_adamw_step_fused(pool, pages, n, 3, hyper, lst(g), lst(q), n_t, norm, None)
+        else:
+            apm.apm_page_adamw_step(pool, pages, n, 3, hyper, norm, None)
+            apm.apm_unpack(pool, apm.APM_P16, lst(q), n_t)
+        out = [norm, q]
+        for st in (apm.APM_P32, apm.APM_M32, apm.APM_V32):
+            out.append(torch.zeros_like(p0))
+            apm.apm_unpack(pool, st, lst(out[-1]), n_t)
+        torch.cuda.synchronize()
+        got.append(out)
+        pool.destroy()
+    assert (got[0][0] >= 0).all() and got[0][2].ne(p0).any()
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
