@@ -97,14 +97,21 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float x) {
 // classes gain nothing: 8 M 38.4 / 39.1).
 constexpr int64_t kFewElems = (int64_t)24 << 20;
 constexpr int kFewLds = 9216;
-// When pages may be skipped on the device (APM_SKIP_UNTOUCHED) the pages to update are known only there:
-// the finalize pass notes them, and a grid of 1 / kSkipSpread of all slices' wavefronts walks the slices of
-// the noted pages, so that workgroups without work are few when most pages are skipped and no
-// wavefront has more than kSkipSpread slices when none is.  A wavefront without work costs 0.2 ns of the
-// call, one with many slices loses the address order that keeps the streams together.  1046 pages, 1 / 64,
-// 1 / 8 of the experts live, and 16 of 16: spread 8: 525, 953, 1355 us a call; 12: 486, 955, 1360; 16: 467, 952,
-// 1400; a grid of all slices, four of U = 4 to a workgroup: 508, 1010, 1350.
-constexpr int kSkipU = 1, kSkipSpread = 12, kSkipLds = 14848;
+// When pages may be skipped on the device (APM_SKIP_UNTOUCHED) the pages to update are known only there.
+// Few slices: the plain grid, whose wavefronts leave if their page's record says skipped.  More: the finalize
+// pass notes the other pages, and a grid of 1 / kSkipSpread of all slices' wavefronts (but kSkipWaves
+// where there are that many slices) walks the slices of the noted pages, so that workgroups without work are
+// few when most pages are skipped and no wavefront has more than kSkipSpread slices when none is.  A
+// wavefront without work costs 0.2 ns of the call, one with many slices loses the address order that keeps
+// the streams together, and in a small call its slices run one after the other on an idle chip.
+// us a call, every page / every eighth page / no page with a gradient:
+//   plain grid / grid of an eighth to a twelfth of the slices / two to four times that
+//   512 slices       12 / 12 / 11      27 / 14 / 12      17 / 13 / 12
+//   8 K              18 / 13 / 12      26 / 14 / 12      19 / 12 / 12
+//   32 K             48 / 19 / 16      59 / 18 / 12      51 / 18 / 12
+//   128 K           157 / 49 / 43     180 / 40 / 18     170 / 42 / 22
+//   4 M            4877 / 1448 / 1194 5919 / 907 / 392 5424 / 999 / 537
+constexpr int kSkipU = 1, kSkipSpread = 12, kSkipWaves = 8192, kSkipLds = 14848;
 
 // Gradient elements [e, e+8) of a page, read from its tenant tensors; elements that belong to no
 // tenant (alignment gap, padding) read as zero.  e is a multiple of 8, as every tenant offset is,
@@ -321,39 +328,65 @@ __device__ __forceinline__ float clip_scale(double norm, double c) {
 constexpr uint64_t kNoSum = ~(uint64_t)0;
 constexpr uint32_t kNoScale = ~(uint32_t)0;
 
-// One wavefront per listed page: combines the page's slice partials in a fixed order and turns
-// them into the page's clip scale / skip decision and the optional outputs.
-__global__ __launch_bounds__(kThreads) void apm_grad_finalize_kernel(FinalizeArgs a) {
-    const int64_t i = (int64_t)blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave;
-    if (i >= a.n_listed) return;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t page = a.grad_pages ? a.grad_pages[i] : a.grad_first + i;
-    const int used = a.used[page];
-    const int n_slices = max(1, (used + kReduceTile - 1) / kReduceTile);
-    double s = 0.0;
-    uint32_t nz = 0;
-    for (int k = lane; k < n_slices; k += kWave) {
-        const int64_t at = (a.by_page ? page : i) * a.S + k;
-        s += a.partials[at];
-        nz |= a.nzflags[at];
+// One wavefront per listed page (R pages, one after the other): combines the page's slice partials in a
+// fixed order and turns them into the page's clip scale / skip decision and the optional outputs.
+// The pages that are not skipped are noted by workgroup, WAVES * R pages with one atomic per extent
+// class: each atomic takes 10 ns of the one counter's time (131 072 pages of 64 elements, one atomic a page
+// 1780 us a call, 64 pages 330; 32 768 of 512 elements 522 and 159).  Small workgroups for few pages, where
+// the launch's own latency counts.
+template <int WAVES, int R>
+__global__ __launch_bounds__(WAVES * kWave) void apm_grad_finalize_kernel(FinalizeArgs a) {
+    static_assert(WAVES * R <= kWave, "one wavefront notes a workgroup's pages");
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int64_t first = (int64_t)blockIdx.x * (WAVES * R);
+    __shared__ int32_t s_cls[WAVES * R];  // extent class of a page to note, or -1
+#pragma unroll 1
+    for (int r = 0; r < R; ++r) {
+        const int slot = r * WAVES + wave;
+        const int64_t i = first + slot;
+        int c = -1;
+        if (i < a.n_listed) {
+            const int64_t page = a.grad_pages ? a.grad_pages[i] : a.grad_first + i;
+            const int used = a.used[page];
+            const int n_slices = max(1, (used + kReduceTile - 1) / kReduceTile);
+            double s = 0.0;
+            uint32_t nz = 0;
+            for (int k = lane; k < n_slices; k += kWave) {
+                const int64_t at = (a.by_page ? page : i) * a.S + k;
+                s += a.partials[at];
+                nz |= a.nzflags[at];
+            }
+            s = wave_sum_f64(s);
+            nz = wave_or_u32(nz);
+            const bool skip = a.skip_mode == APM_SKIP_UNTOUCHED && nz == 0u;
+            if (lane == 0) {
+                const double norm = sqrt(s);
+                const float scale = clip_scale(norm, a.max_norm);
+                const float sc = skip ? -1.0f : scale;
+                if (a.run) reinterpret_cast<PageRun*>(a.recs)[i] = PageRun{used, sc};
+                else if (a.staged) a.recs[i].scale = sc;
+                else a.recs[i] = class_rec(used, sc, page, a.state_pages ? a.state_pages[i] : a.state_first + i, a.E, a.g16, a.p16);
+                const int64_t o = a.out_index ? (int64_t)a.out_index[i] : i;
+                if (a.grad_norm) a.grad_norm[o] = skip ? 0.0f : (float)norm;
+                if (a.skip_mask) a.skip_mask[o] = skip ? 1 : 0;
+            }
+            if (!skip) {
+                c = 0;
+                while (c + 1 < a.n_cls && i >= a.cls_begin[c + 1]) ++c;
+            }
+        }
+        if (lane == 0) s_cls[slot] = c;
     }
-    s = wave_sum_f64(s);
-    nz = wave_or_u32(nz);
-    if (lane != 0) return;
-    const bool skip = a.skip_mode == APM_SKIP_UNTOUCHED && nz == 0u;
-    const double norm = sqrt(s);
-    const float scale = clip_scale(norm, a.max_norm);
-    const float sc = skip ? -1.0f : scale;
-    if (a.run) reinterpret_cast<PageRun*>(a.recs)[i] = PageRun{used, sc};
-    else if (a.staged) a.recs[i].scale = sc;
-    else a.recs[i] = class_rec(used, sc, page, a.state_pages ? a.state_pages[i] : a.state_first + i, a.E, a.g16, a.p16);
-    const int64_t o = a.out_index ? (int64_t)a.out_index[i] : i;
-    if (a.grad_norm) a.grad_norm[o] = skip ? 0.0f : (float)norm;
-    if (a.skip_mask) a.skip_mask[o] = skip ? 1 : 0;
-    if (a.live && !skip) {
-        int c = 0;
-        while (c + 1 < a.n_cls && i >= a.cls_begin[c + 1]) ++c;
-        a.live[kMaxExtentClasses + a.cls_begin[c] + atomicAdd(a.live + c, 1)] = (int32_t)i;
+    if (!a.live) return;
+    __syncthreads();
+    if (wave != 0) return;
+    const int mine = lane < WAVES * R ? s_cls[lane] : -1;
+    for (int c = 0; c < max(1, a.n_cls); ++c) {
+        const uint64_t noted = __ballot(mine == c);
+        if (noted == 0) continue;
+        int at = lane == 0 ? atomicAdd(a.live + c, __popcll(noted)) : 0;
+        at = __shfl(at, 0, kWave) + __popcll(noted & (((uint64_t)1 << lane) - 1));
+        if (mine == c) a.live[kMaxExtentClasses + a.cls_begin[c] + at] = (int32_t)(first + lane);
     }
 }
 
@@ -637,7 +670,7 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_kernel(const PageRec* r
                                                                 UpdateArgs a) {
     const PageRec rec = load_rec(recs + blockIdx.y);
     const int start = (int)blockIdx.x * kTile<U>;
-    if (start >= ((rec.used + 7) & ~7)) return;  // beyond the extent
+    if (rec.scale < 0.0f || start >= ((rec.used + 7) & ~7)) return;  // a skipped page, beyond the extent
     update_slice<U, GATHER, SCATTER>(a, rec, start, (int)threadIdx.x, p32 + rec.pofs, m32 + rec.pofs, v32 + rec.pofs);
 }
 
@@ -653,7 +686,7 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_run_kernel(const void* 
     const int64_t at = (int64_t)blockIdx.y * E;
     const PageRec rec = class_rec(run.used, run.scale, 0, 0, 0, g16 + at, p16 + at);
     const int start = (int)blockIdx.x * kTile<U>;
-    if (start >= rec.end[0]) return;
+    if ((!BARE && rec.scale < 0.0f) || start >= rec.end[0]) return;
     update_slice<U, false, false>(a, rec, start, (int)threadIdx.x, p32 + at, m32 + at, v32 + at);
 }
 
@@ -1125,9 +1158,19 @@ static unsigned record_grid(const AdamwLaunch& L) {
     return (unsigned)((threads + kThreads - 1) / kThreads);
 }
 
+// Whether the finalize pass notes the pages that are not skipped, for the grid over noted pages (see kSkipSpread).
+static bool notes_live(const AdamwLaunch& L) {
+    if (L.skip_mode != APM_SKIP_UNTOUCHED || L.stride_wavefronts > 0) return false;
+    auto slices = [](int64_t pages, int64_t elems) { return pages * ((elems + kTile<kSkipU> - 1) / kTile<kSkipU>); };
+    int64_t n = 0;
+    for (int c = 0; c < L.n_cls; ++c) n += slices(L.cls[c].count, L.cls[c].max_used);
+    if (L.n_cls == 0) n = slices(L.n_listed, L.E);
+    return n > kSkipWaves;
+}
+
 hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
     hipError_t e = hipSuccess;
-    int32_t* live = L.skip_mode == APM_SKIP_UNTOUCHED && L.stride_wavefronts == 0 ? L.live : nullptr;
+    int32_t* live = notes_live(L) ? L.live : nullptr;
     ReduceArgs a{L.g16, L.recs, L.used, L.grad_pages, L.grad_first, 0, L.E, L.partials, L.nzflags, L.S, live};
     if (L.sums_ready && live) hipLaunchKernelGGL(apm_live_clear_kernel, dim3(1), dim3(kWave), 0, s, live);
     if (!L.sums_ready) e = for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used, int64_t sum_used) {
@@ -1141,9 +1184,12 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
                    L.partials, L.nzflags, L.S, L.skip_mode, L.max_norm, L.recs, L.g16, L.p16, L.E, live, {}, L.n_cls, L.sums_ready, L.is_run(),
                    L.gather || L.scatter, nullptr, L.grad_norm, L.skip_mask, L.out_index};
     for (int c = 0; c < L.n_cls; ++c) f.cls_begin[c] = L.cls[c].begin;
-    const int per_wg = kThreads / kWave;
-    hipLaunchKernelGGL(apm_grad_finalize_kernel, dim3((unsigned)((L.n_listed + per_wg - 1) / per_wg)),
-                       dim3(kThreads), 0, s, f);
+    auto go = [&](auto kernel, int waves, int pages) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((L.n_listed + pages - 1) / pages)), dim3((unsigned)(waves * kWave)), 0, s, f);
+    };
+    if (L.n_listed <= 1024) go(apm_grad_finalize_kernel<4, 1>, 4, 4);
+    else if (L.n_listed <= 4096) go(apm_grad_finalize_kernel<16, 1>, 16, 16);
+    else go(apm_grad_finalize_kernel<16, 4>, 16, 64);
     return hipGetLastError();
 }
 
@@ -1236,7 +1282,7 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
             }
         });
     }
-    if (L.partials && L.skip_mode == APM_SKIP_UNTOUCHED) {
+    if (L.partials && notes_live(L)) {
         constexpr int U = kSkipU;
         const ExtentClass all{0, L.n_listed, L.E, L.n_listed * L.E};
         const ExtentClass* cls = L.n_cls > 0 ? L.cls : &all;
@@ -1244,7 +1290,9 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         for (int c = 0; c < n_cls; ++c) {
             const int nx = (int)((cls[c].max_used + kTile<U> - 1) / kTile<U>);
             if (nx == 0) continue;
-            int64_t wgs = (cls[c].count * nx + kSkipSpread - 1) / kSkipSpread;
+            const int64_t slices = cls[c].count * nx;
+            int64_t wgs = (slices + kSkipSpread - 1) / kSkipSpread;
+            if (wgs < kSkipWaves) wgs = slices < kSkipWaves ? slices : kSkipWaves;
             const int64_t cap = L.max_workgroups > 0 ? L.max_workgroups : max_workgroups(kUpdThreads);
             if (wgs > cap) wgs = cap;  // each walks further
             const dim3 grid((unsigned)wgs), block(kUpdThreads);

@@ -1,5 +1,6 @@
 """Small GPU tests of single kernel paths at the sizes and alignments where they can go wrong."""
 import ctypes
+import time
 
 import pytest
 import torch
@@ -212,7 +213,8 @@ class _Region:
 
 @pytest.mark.parametrize("dead", ["none", "all", "most", "first"])
 @pytest.mark.parametrize("form", ["run", "reversed", "fused", "noalloc"])
-@pytest.mark.parametrize("E,n_t,per", [(8, 40, 8), (4104, 30, 4103), (1 << 20, 6, 3 << 19), (1 << 20, 40, 5000)])
+@pytest.mark.parametrize("E,n_t,per", [(8, 40, 8), (4104, 30, 4103), (1 << 20, 6, 3 << 19), (1 << 20, 40, 5000),
+                                     (4104, 1500, 4103), (512, 5000, 500)])
 def test_skipping_updates_the_touched_pages_and_no_others(E, n_t, per, form, dead):
     """The grid over the noted pages: none, all, few live pages, several extent classes.  Same bits as a step
     without skipping on the live pages; the others keep theirs."""
@@ -306,3 +308,31 @@ def test_updates_in_several_launches_equal_one_launch(form, skip, cap):
     assert (got[0][0] >= 0).all() and got[0][2].ne(p0).any()
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+def _us(f, n):
+    """Best of five batches of n calls, microseconds a call."""
+    best = float("inf")
+    f()
+    for _ in range(5):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for _ in range(n):
+            f()
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t) / n)
+    return best * 1e6
+
+
+@pytest.mark.parametrize("E,n", [(64, 131072), (512, 32768)])
+def test_skipping_costs_little_where_every_small_page_has_a_gradient(E, n):
+    """Finding that no page is skipped is a few percent of a step with norms, however many pages: noting
+    each with an atomic of its own made it four times such a step (bound: twice)."""
+    pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n)
+    apm.lib().apm_pool_set_layout(pool.handle, apm.make_tensors([n * E], apm.APM_F32, [0]), 1, None, None, None, None, None)
+    torch.as_tensor(_Region(pool, apm.APM_G16, n * E), device=DEV).fill_(0x3a00)
+    norm = torch.zeros(n, device=DEV)
+    step = lambda skip: apm.apm_page_adamw_step(pool, None, n, 3, apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.0, skip), norm, None)  # noqa: E731
+    plain, skipping = _us(lambda: step(0), 20), _us(lambda: step(1), 20)
+    pool.destroy()
+    assert skipping < 2 * plain, (skipping, plain)
