@@ -1015,7 +1015,7 @@ struct TakeArgs {
 };
 struct TakeArgsInline {
     TakeArgs a;
-    int32_t page[2 * kArgWords];
+    int32_t page[kTakePages];
 };
 
 // dst <- src, or g' <- bf16_rne(fp32(g') + fp32(g)) (Alg. 2, buffering thread: "accumulate buffered
@@ -1103,7 +1103,7 @@ hipError_t launch_grad_take(const GradTake& t, hipStream_t s) {
     for (int k = 0; k < t.n_cls; ++k) {
         const ExtentClass& c = t.cls[k];
         if (c.max_used <= 0 && !t.sums) continue;
-        const int64_t piece = t.host_pages ? 2 * kArgWords : kMaxGridY;
+        const int64_t piece = t.host_pages ? kTakePages : kMaxGridY;
         for (int64_t off = 0; off < c.count; off += piece) {
             const int64_t n = c.count - off < piece ? c.count - off : piece;
             const int64_t nx = (c.max_used + item - 1) / item;
@@ -1112,7 +1112,7 @@ hipError_t launch_grad_take(const GradTake& t, hipStream_t s) {
                 for (int64_t i = 0; i < n; ++i) in.page[i] = (int32_t)t.host_pages[c.begin + off + i];
             } else {
                 in.a.order = t.order ? t.order + c.begin + off : nullptr;
-                in.a.first = c.begin + off;
+                in.a.first = t.first + c.begin + off;
             }
 #define APM_TAKE(ACCUM, SUMS)                                                                                       \
     do {                                                                                                           \

@@ -228,6 +228,7 @@ constexpr int32_t kWaitLimit = 4096;
 // Takes a gradient in page layout over into a buffered half: dst <- src, or (accumulate) dst <- dst + src, over
 // the used extents of the listed pages, and if `sums` is set works out the tiles' sums of squares and
 // non-zero flags of what it wrote, as the reduce pass would, indexed by page.
+constexpr int64_t kTakePages = 2 * kArgWords;
 struct GradTake {
     const uint16_t* src;
     uint16_t* dst;
@@ -237,10 +238,11 @@ struct GradTake {
     int32_t S;
     double* sums;       // [pool pages * S] or nullptr
     uint32_t* nzflags;
-    // The pages: the device list `order` (a layout's launch order) in the given classes, or host_pages, which
-    // are carried in the kernel arguments, kArgWords * 2 a launch.
+    // The pages: the device list `order` in the given classes, or host_pages, which are carried in the kernel
+    // arguments, kTakePages a launch, or neither: pages first, first + 1, ...
     const int64_t* order;
     const int64_t* host_pages;
+    int64_t first;
     const ExtentClass* cls;
     int n_cls;
 };

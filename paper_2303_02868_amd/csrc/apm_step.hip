@@ -296,8 +296,14 @@ int ensure_delayed(apm_pool* pool, hipStream_t caller, bool probe) {
     return APM_OK;
 }
 
+// Sums are worked out by the hand-over if a page fills the greater part of the workgroup that takes a tile (us
+// with and without, 16 M elements: pages of 512 elements 133 and 36 a sum, 283 and 400 an update; 2048: 81 and 63,
+// 378 and 386; 4096: 66 and 64, 343 and 357), else the update works them out itself.
+constexpr int64_t kSumsPage = 4096;
+
 // Room for the sums of half k; without it the update works them out itself.
 static bool ensure_sums(apm_pool* pool, int k) {
+    if (pool->desc.page_elems < kSumsPage) return false;
     const size_t n = (size_t)pool->desc.n_pages * (size_t)pool->S;
     if (!pool->gsum[k] && hipMalloc((void**)&pool->gsum[k], n * sizeof(double)) != hipSuccess) pool->gsum[k] = nullptr;
     if (!pool->gnz[k] && hipMalloc((void**)&pool->gnz[k], n * sizeof(uint32_t)) != hipSuccess) pool->gnz[k] = nullptr;
@@ -306,28 +312,57 @@ static bool ensure_sums(apm_pool* pool, int k) {
     return false;
 }
 
+// Launches that may carry a hand-over's page list in their arguments; beyond that it is staged through the
+// pinned ring (reversed lists, 4 / 5 / 8 launches of 880 pages of 512 elements against the ring: 31 and 35,
+// 37 and 37, 56 and 44 us).
+constexpr int64_t kMaxTakeLaunches = 4;
+
 // Copies or adds the used extents of the listed pages of g16 into half k.
 static int take_gradient(apm_pool* pool, int k, const uint16_t* g16, const int64_t* pages, int64_t n_pages, bool accumulate,
                          bool sums, hipStream_t s) {
     const int64_t in_use = (int64_t)pool->plan.pages.size();
     GradTake t{g16, pool->gbuf[k], accumulate, pool->d_used, pool->desc.page_elems, pool->S, sums ? pool->gsum[k] : nullptr,
-               sums ? pool->gnz[k] : nullptr, nullptr, nullptr, pool->order_cls, pool->order_n_cls};
+               sums ? pool->gnz[k] : nullptr, nullptr, nullptr, 0, pool->order_cls, pool->order_n_cls};
     if (!pages && n_pages == in_use) {
         t.order = pool->order_run ? nullptr : pool->d_order;
         APM_HIP(launch_grad_take(t, s));
         return APM_OK;
     }
     auto page_at = [&](int64_t i) { return pages ? pages[i] : i; };
-    std::vector<int64_t> order((size_t)n_pages);
     ExtentClass cls[kMaxExtentClasses];
+    t.cls = cls;
+    bool run = true;
+    for (int64_t i = 1; run && pages && i < n_pages; ++i) run = pages[i] == pages[0] + i;
+    // Consecutive pages need no list, and with the extents taken as the layout's largest no look-up, at the price of
+    // workgroups without work where pages differ much: a list in one launch per class is the better form then.
+    if (run && (n_pages > kTakePages || pool->order_n_cls <= 1)) {
+        cls[0] = ExtentClass{0, n_pages, pool->order_n_cls > 0 ? pool->order_cls[0].max_used : 0, 0};
+        t.n_cls = 1;
+        t.first = page_at(0);
+        APM_HIP(launch_grad_take(t, s));
+        return APM_OK;
+    }
+    std::vector<int64_t> order((size_t)n_pages);
     t.n_cls = group_by_extent(n_pages, pool->desc.page_elems, [&](int64_t i) {
         return page_at(i) < in_use ? pool->plan.pages[(size_t)page_at(i)].used : (int64_t)0;
     }, order.data(), cls);
     for (int64_t& i : order) i = page_at(i);
-    t.cls = cls;
-    t.host_pages = order.data();
+    int64_t launches = 0;
+    for (int c = 0; c < t.n_cls; ++c) launches += (cls[c].count + kTakePages - 1) / kTakePages;
+    int slot = -1;
+    if (launches > kMaxTakeLaunches) {
+        const size_t bytes = (size_t)n_pages * sizeof(int64_t);
+        int rc = pool->ring.acquire(bytes, &slot);
+        if (rc != APM_OK) return rc;
+        std::memcpy(pool->ring.h[slot], order.data(), bytes);
+        rc = pool->ring.commit(slot, bytes, s);
+        if (rc != APM_OK) return rc;
+        t.order = static_cast<const int64_t*>(pool->ring.d[slot]);
+    } else {
+        t.host_pages = order.data();
+    }
     APM_HIP(launch_grad_take(t, s));
-    return APM_OK;
+    return slot >= 0 ? pool->ring.seal(slot, s) : APM_OK;
 }
 
 // Applies the buffered gradient (half `cur`) on the update stream.
