@@ -65,12 +65,12 @@ int make_plan(int64_t E, const int64_t* numels, int64_t n, Plan* out) {
     return APM_OK;
 }
 
-int group_by_extent(int64_t n, int64_t E, const std::function<int64_t(int64_t)>& size_of, int64_t* order,
-                    ExtentClass cls[kMaxExtentClasses]) {
-    auto class_of = [&](int64_t used) { return used * 4 > E ? 0 : used * 32 > E ? 1 : used * 512 > E ? 2 : 3; };
+int group_by_extent(int64_t n, int64_t E, const int32_t* size, int64_t* order, ExtentClass cls[kMaxExtentClasses]) {
+    const int64_t limit[kMaxExtentClasses - 1] = {E / 4, E / 32, E / 512};  // sizes above: classes 0, 1, 2
+    auto class_of = [&](int64_t used) { return (used <= limit[0]) + (used <= limit[1]) + (used <= limit[2]); };
     int64_t cnt[kMaxExtentClasses] = {}, mx[kMaxExtentClasses] = {}, sum[kMaxExtentClasses] = {};
     for (int64_t k = 0; k < n; ++k) {
-        const int64_t u = size_of(k);
+        const int64_t u = size[k];
         const int c = class_of(u);
         ++cnt[c];
         sum[c] += u;
@@ -100,7 +100,10 @@ int group_by_extent(int64_t n, int64_t E, const std::function<int64_t(int64_t)>&
         if (cnt[c] > 0) cls[n_cls++] = ExtentClass{at, cnt[c], mx[c], sum[c]};
         at += cnt[c];
     }
-    for (int64_t k = 0; k < n; ++k) order[fill[into[class_of(size_of(k))]]++] = k;
+    if (n_cls == 1)
+        for (int64_t k = 0; k < n; ++k) order[k] = k;
+    else
+        for (int64_t k = 0; k < n; ++k) order[fill[into[class_of(size[k])]]++] = k;
     return n_cls;
 }
 

@@ -74,8 +74,8 @@ struct ExtentClass {
 };
 // order[pos] = index of the item at position pos (classes one after the other, the given order kept
 // inside each); returns the number of classes.  E = the size that the class limits are fractions of.
-int group_by_extent(int64_t n, int64_t E, const std::function<int64_t(int64_t)>& size_of, int64_t* order,
-                    ExtentClass cls[kMaxExtentClasses]);
+// Sizes come as an array: a call's host time is spent here when its pages are many and small.
+int group_by_extent(int64_t n, int64_t E, const int32_t* size, int64_t* order, ExtentClass cls[kMaxExtentClasses]);
 
 // One dimension of a grid holds fewer than 2^32 work-items (the runtime refuses more): the workgroups of
 // `threads` work-items that a one-dimensional launch can have.
@@ -308,6 +308,7 @@ struct apm_pool {
     std::vector<int64_t> layout_numels;
     std::vector<int64_t> layout_ids;
     apm::Plan plan;
+    std::vector<int32_t> used;  // used extent of every page of the pool (0 beyond the layout); empty before a layout
 
     int fd[APM_N_STATES] = {-1, -1, -1, -1, -1};  // FILE pools: one file per stored class
 
@@ -317,9 +318,8 @@ struct apm_pool {
     std::vector<apm::SegLaunch> seg_launches;
     int32_t seg_ranges = 0;         // groups of kArgWords tensors they are split into
     apm::TenantRec* d_tenants = nullptr;  // by page in use
-    // All pages in use, grouped by extent (see group_by_extent): launch order, in host and device
-    // memory; d_order_out = the same as 32-bit output indices.  order_run: the order is 0, 1, 2, ...
-    std::vector<int64_t> order;
+    // All pages in use, grouped by extent (see group_by_extent): launch order; d_order_out = the same as 32-bit
+    // output indices.  order_run: the order is 0, 1, 2, ... and has no tables.
     int64_t* d_order = nullptr;
     int32_t* d_order_out = nullptr;
     apm::ExtentClass order_cls[apm::kMaxExtentClasses] = {};

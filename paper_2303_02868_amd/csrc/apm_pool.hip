@@ -1,5 +1,6 @@
 // Page pool, page table, pack / unpack entry points and page copies (host side).
 #include <cstring>
+#include <memory>
 #include <thread>
 
 #include <unistd.h>
@@ -148,27 +149,31 @@ constexpr int kMaxSegRanges = 2;
 
 // The layout's segments in launch order: per group of kArgWords tensors the long ones, then the short
 // ones (see group_by_extent).
-void order_segments(const Plan& plan, std::vector<SegRec>* recs, std::vector<SegLaunch>* launches, int32_t* ranges) {
+void order_segments(const Plan& plan, SegRec* recs, std::vector<SegLaunch>* launches, int32_t* ranges) {
     const int64_t n = (int64_t)plan.segs.size();
-    recs->reserve((size_t)n);
     const int64_t last = n ? plan.segs[(size_t)n - 1].tensor : -1;
     // beyond kMaxSegRanges groups the addresses are staged: one group
     const int64_t group = last / kArgWords < kMaxSegRanges ? kArgWords : last + 1;
     *ranges = (int32_t)(last / kArgWords + 1);
     std::vector<int64_t> order((size_t)n);
+    std::vector<int32_t> size((size_t)n);
     for (int64_t at = 0; at < n;) {
         const int64_t t0 = plan.segs[(size_t)at].tensor / group * group;
-        int64_t end = at, mx = 0;
-        for (; end < n && plan.segs[(size_t)end].tensor < t0 + group; ++end)  // segments come in tensor order
-            if (plan.segs[(size_t)end].n > mx) mx = plan.segs[(size_t)end].n;
+        int64_t end = at;
+        int32_t mx = 0;
+        for (; end < n && plan.segs[(size_t)end].tensor < t0 + group; ++end) {  // segments come in tensor order
+            const int32_t u = (int32_t)plan.segs[(size_t)end].n;
+            size[(size_t)(end - at)] = u;
+            if (u > mx) mx = u;
+        }
         ExtentClass cls[kMaxExtentClasses];
-        const int n_cls = group_by_extent(end - at, mx, [&](int64_t k) { return plan.segs[(size_t)(at + k)].n; }, order.data(), cls);
+        const int n_cls = group_by_extent(end - at, mx, size.data(), order.data(), cls);
         const int64_t count = last + 1 - t0 < group ? last + 1 - t0 : group;
         for (int c = 0; c < n_cls; ++c)
             launches->push_back(SegLaunch{at + cls[c].begin, cls[c].count, cls[c].max_used, (int32_t)t0, (int32_t)count});
         for (int64_t k = 0; k < end - at; ++k) {
             const apm_segment& g = plan.segs[(size_t)(at + order[(size_t)k])];
-            recs->push_back(SegRec{g.tensor_off, g.page * plan.E + g.page_off, (int32_t)g.tensor, (int32_t)g.n});
+            *recs++ = SegRec{g.tensor_off, g.page * plan.E + g.page_off, (int32_t)g.tensor, (int32_t)g.n};
         }
         at = end;
     }
@@ -178,42 +183,49 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     if ((int64_t)plan.pages.size() > pool->desc.n_pages)
         return fail(APM_ENOMEM, "layout needs %lld pages, pool has %lld", (long long)plan.pages.size(), (long long)pool->desc.n_pages);
     if (n > INT32_MAX) return fail(APM_EINVAL, "too many tensors");
-    std::vector<SegRec> recs;
-    std::vector<SegLaunch> launches;
-    int32_t ranges = 0;
-    order_segments(plan, &recs, &launches, &ranges);
     const size_t n_in_use = plan.pages.size();
-    std::vector<TenantRec> tenants(n_in_use, TenantRec{{0, 0}, INT32_MAX, {0, 0}, {-1, -1}});
-    for (const apm_segment& g : plan.segs) {  // a page's tenants appear in offset order
-        TenantRec& t = tenants[(size_t)g.page];
-        const int k = t.tensor[0] < 0 ? 0 : 1;
-        t.tensor_off[k] = g.tensor_off;
-        if (k == 1) t.off1 = (int32_t)g.page_off;
-        t.n[k] = (int32_t)g.n;
-        t.tensor[k] = (int32_t)g.tensor;
-    }
+    std::vector<int32_t> used((size_t)pool->desc.n_pages, 0);
+    for (size_t k = 0; k < n_in_use; ++k) used[k] = (int32_t)plan.pages[k].used;
     std::vector<int64_t> order(n_in_use);
     ExtentClass cls[kMaxExtentClasses] = {};
-    const int n_cls = group_by_extent((int64_t)n_in_use, plan.E, [&](int64_t k) { return plan.pages[(size_t)k].used; }, order.data(), cls);
-    std::vector<int32_t> order_out(order.begin(), order.end());
-    // Device copies of the tables, in one allocation; freed unless the pool takes it over at the end.
+    const int n_cls = group_by_extent((int64_t)n_in_use, plan.E, used.data(), order.data(), cls);
+    bool run = true;
+    for (size_t k = 0; run && k < n_in_use; ++k) run = order[k] == (int64_t)k;
+    // Tables for the device, in one allocation and one upload; freed unless the pool takes it over at the end.
     struct Tables {
         char* d = nullptr;
         size_t at[4], bytes = 0;
         ~Tables() { if (d) (void)hipFree(d); }
     } tables;
-    const void* src[4] = {recs.data(), tenants.data(), order.data(), order_out.data()};
-    const size_t len[4] = {recs.size() * sizeof(SegRec), n_in_use * sizeof(TenantRec), n_in_use * sizeof(int64_t), n_in_use * sizeof(int32_t)};
+    const size_t n_order = run ? 0 : n_in_use;
+    const size_t len[4] = {plan.segs.size() * sizeof(SegRec), n_in_use * sizeof(TenantRec), n_order * sizeof(int64_t), n_order * sizeof(int32_t)};
     for (int k = 0; k < 4; ++k) {
         tables.at[k] = tables.bytes;
         tables.bytes += (len[k] + 255) / 256 * 256;
     }
+    std::vector<SegLaunch> launches;
+    int32_t ranges = 0;
     if (tables.bytes > 0) {
-        std::vector<char> image(tables.bytes, 0);
-        for (int k = 0; k < 4; ++k)
-            if (len[k] > 0) std::memcpy(image.data() + tables.at[k], src[k], len[k]);
+        std::unique_ptr<char[]> image(new char[tables.bytes]);
+        order_segments(plan, reinterpret_cast<SegRec*>(image.get() + tables.at[0]), &launches, &ranges);
+        TenantRec* tenants = reinterpret_cast<TenantRec*>(image.get() + tables.at[1]);
+        for (size_t k = 0; k < n_in_use; ++k) tenants[k] = TenantRec{{0, 0}, INT32_MAX, {0, 0}, {-1, -1}};
+        for (const apm_segment& g : plan.segs) {  // a page's tenants appear in offset order
+            TenantRec& t = tenants[g.page];
+            const int k = t.tensor[0] < 0 ? 0 : 1;
+            t.tensor_off[k] = g.tensor_off;
+            if (k == 1) t.off1 = (int32_t)g.page_off;
+            t.n[k] = (int32_t)g.n;
+            t.tensor[k] = (int32_t)g.tensor;
+        }
+        int64_t* d_order = reinterpret_cast<int64_t*>(image.get() + tables.at[2]);
+        int32_t* d_order_out = reinterpret_cast<int32_t*>(image.get() + tables.at[3]);
+        for (size_t k = 0; k < n_order; ++k) {
+            d_order[k] = order[k];
+            d_order_out[k] = (int32_t)order[k];
+        }
         hipError_t e = hipMalloc((void**)&tables.d, tables.bytes);
-        if (e == hipSuccess) e = hipMemcpy(tables.d, image.data(), tables.bytes, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(tables.d, image.get(), tables.bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             (void)hipGetLastError();
             return fail(APM_ENOMEM, "uploading %zu bytes of the layout's tables failed: %s", tables.bytes, hipGetErrorString(e));
@@ -223,8 +235,6 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
         int rc = zero_regions(pool, s, false);
         if (rc != APM_OK) return rc;
     }
-    std::vector<int32_t> used((size_t)pool->desc.n_pages, 0);
-    for (size_t k = 0; k < plan.pages.size(); ++k) used[k] = (int32_t)plan.pages[k].used;
     // The page table changes rarely; a synchronous upload keeps its lifetime trivial.
     APM_HIP(hipStreamSynchronize(s));
     APM_HIP(hipMemcpy(pool->d_used, used.data(), used.size() * sizeof(int32_t), hipMemcpyHostToDevice));
@@ -240,13 +250,11 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     pool->d_tenants = reinterpret_cast<TenantRec*>(pool->d_tables + tables.at[1]);
     pool->d_order = reinterpret_cast<int64_t*>(pool->d_tables + tables.at[2]);
     pool->d_order_out = reinterpret_cast<int32_t*>(pool->d_tables + tables.at[3]);
-    pool->order.swap(order);
+    pool->used.swap(used);
     pool->order_n_cls = n_cls;
-    pool->layout_epoch += 1;
-    pool->order_run = true;
+    pool->order_run = run;
     for (int c = 0; c < kMaxExtentClasses; ++c) pool->order_cls[c] = cls[c];
-    for (size_t k = 0; k < n_in_use; ++k)
-        if (pool->order[k] != (int64_t)k) pool->order_run = false;
+    pool->layout_epoch += 1;
     pool->seg_launches.swap(launches);
     pool->seg_ranges = ranges;
     pool->has_layout = true;

@@ -44,6 +44,15 @@ int check_fused_list(const apm_pool* pool, const apm_tensor* t, int64_t n, const
     return APM_OK;
 }
 
+// group_by_extent over the used extents of a call's pages.
+int group_pages(const apm_pool* pool, const int64_t* pages, int64_t n, int64_t* order, ExtentClass cls[kMaxExtentClasses]) {
+    std::vector<int32_t> size;
+    if (pool->used.empty()) size.assign((size_t)n, 0);
+    else if (pages) size.resize((size_t)n);
+    for (int64_t k = 0; pages && !pool->used.empty() && k < n; ++k) size[(size_t)k] = pool->used[(size_t)pages[k]];
+    return group_by_extent(n, pool->desc.page_elems, size.empty() ? pool->used.data() : size.data(), order, cls);
+}
+
 // Launches that may carry a call's page list and tensor addresses in their arguments; beyond that
 // they are staged through the pinned ring.  The ring costs the GPU an upload and two event packets,
 // 20 us and more between one call's update and the next one's; a stage launch costs 3 us.
@@ -81,7 +90,6 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     const int64_t E = pool->desc.page_elems;
     const int64_t in_use = pool->has_layout ? (int64_t)pool->plan.pages.size() : 0;
     auto page_at = [&](int64_t k) { return pages ? pages[k] : k; };
-    auto used_of = [&](int64_t page) { return page < in_use ? pool->plan.pages[(size_t)page].used : (int64_t)0; };
     if (pages) {
         // Two workgroups updating one page at once would race: a listed page is listed once.
         std::vector<uint8_t> seen((size_t)pool->desc.n_pages, 0);
@@ -106,7 +114,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
         for (int c = 0; c < L.n_cls; ++c) L.cls[c] = pool->order_cls[c];
     } else {
         order.resize((size_t)n_pages);
-        L.n_cls = group_by_extent(n_pages, E, [&](int64_t k) { return used_of(page_at(k)); }, order.data(), L.cls);
+        L.n_cls = group_pages(pool, pages, n_pages, order.data(), L.cls);
         run = true;
         for (int64_t k = 0; run && k < n_pages; ++k) run = order[(size_t)k] == k && page_at(k) == page_at(0) + k;
     }
@@ -343,9 +351,7 @@ static int take_gradient(apm_pool* pool, int k, const uint16_t* g16, const int64
         return APM_OK;
     }
     std::vector<int64_t> order((size_t)n_pages);
-    t.n_cls = group_by_extent(n_pages, pool->desc.page_elems, [&](int64_t i) {
-        return page_at(i) < in_use ? pool->plan.pages[(size_t)page_at(i)].used : (int64_t)0;
-    }, order.data(), cls);
+    t.n_cls = group_pages(pool, pages, n_pages, order.data(), cls);
     for (int64_t& i : order) i = page_at(i);
     int64_t launches = 0;
     for (int c = 0; c < t.n_cls; ++c) launches += (cls[c].count + kTakePages - 1) / kTakePages;

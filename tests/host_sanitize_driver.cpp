@@ -168,6 +168,37 @@ void plan_errors() {
     if (apm_schedule_plan(off2, pages2, bytes2, 2, nullptr, 1, 16, 100, nullptr, &n_tasks, nullptr) == APM_OK) die("decreasing offsets accepted");
 }
 
+// Items grouped by size: every item once, classes one after the other from the largest sizes down, the
+// given order kept inside each, counts, largest sizes and sums as stated.
+void group_case(Rng& r) {
+    const int64_t E = 8 * (1 + r.below((int64_t)1 << r.below(24))), n = r.below(600) * (r.below(3) == 0 ? 50 : 1);
+    std::vector<int32_t> size((size_t)n);
+    for (auto& x : size) x = (int32_t)(r.below(4) == 0 ? E >> r.below(12) : r.below((E >> r.below(12)) + 1));
+    std::vector<int64_t> order((size_t)n, -1);
+    apm::ExtentClass cls[apm::kMaxExtentClasses];
+    const int n_cls = apm::group_by_extent(n, E, size.data(), order.data(), cls);
+    if ((n == 0) != (n_cls == 0) || n_cls > apm::kMaxExtentClasses) die("class count", n_cls, n);
+    std::vector<char> seen((size_t)n, 0);
+    int64_t at = 0, above = INT64_MAX;
+    for (int c = 0; c < n_cls; ++c) {
+        if (cls[c].begin != at || cls[c].count <= 0) die("classes not one after the other", c, cls[c].begin);
+        int64_t mx = 0, mn = INT64_MAX, sum = 0;
+        for (; at < cls[c].begin + cls[c].count; ++at) {
+            const int64_t k = order[(size_t)at];
+            if (k < 0 || k >= n || seen[(size_t)k]++) die("item lost or listed twice", at, k);
+            if (at > cls[c].begin && k <= order[(size_t)at - 1]) die("order inside a class", at, k);
+            const int64_t u = size[(size_t)k];
+            sum += u;
+            if (u > mx) mx = u;
+            if (u < mn) mn = u;
+        }
+        if (mx != cls[c].max_used || sum != cls[c].sum_used) die("class sums", c, mx);
+        if (mx > above) die("a class above a larger one", c, mx);
+        above = mn;
+    }
+    if (at != n) die("items left over", at, n);
+}
+
 // The pieces that a pass over many pages is launched in: every launch within what one grid dimension
 // holds (fewer than 2^32 work-items), every page in one of them.
 void launch_pieces(Rng& r) {
@@ -201,6 +232,7 @@ int main(int argc, char** argv) {
     launch_pieces(r);
     for (int i = 0; i < cases; ++i) pack_case(r);
     for (int i = 0; i < cases; ++i) plan_case(r);
+    for (int i = 0; i < cases; ++i) group_case(r);
     std::printf("ok %d\n", cases);
     return 0;
 }
