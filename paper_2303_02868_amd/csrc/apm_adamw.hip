@@ -91,12 +91,15 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float x) {
 #ifndef APM_UPDATE_LDS
 #define APM_UPDATE_LDS 14848
 #endif
-// Few elements from and to tensors: here workgroups of short pages that find nothing to do weigh more, and
-// a CU takes 17 wavefronts (us a call at 11 / 17: 4 M elements in 64 K pages 26.9 / 24.5, 16 M in 1 M pages
-// 95.1 / 89.3, 64 M 326 / 343; with clipping, at 12 / 17: 35.8 / 31.5, 112 / 101; pages read from and written to the
-// classes gain nothing: 8 M 38.4 / 39.1).
-constexpr int64_t kFewElems = (int64_t)24 << 20;
+// Launches with few elements: here workgroups of short pages that find nothing to do weigh more, and a CU takes
+// 17 wavefronts.  From and to tensors (us a call at 11 / 17: 4 M elements in 64 K pages 26.9 / 24.5, 16 M in 1 M
+// pages 95.1 / 89.3, 64 M 326 / 343; with clipping, at 12 / 17: 35.8 / 31.5, 112 / 101) up to kFewElems; from and
+// to the page classes only where all wavefronts then run at once (1 M 5.9 / 5.5, 2 M 10.3 / 9.5, 8 M 36.7 / 37.1;
+// with clipping 14.3 / 13.9, 18.8 / 18.2, 45.2 / 45.5).
+constexpr int64_t kFewElems = (int64_t)24 << 20, kFewRunElems = (int64_t)2 << 20;
 constexpr int kFewLds = 9216;
+unsigned update_lds(bool tensors, int64_t elems, unsigned lds) { return elems <= (tensors ? kFewElems : kFewRunElems) ? kFewLds : lds; }
+
 // When pages may be skipped on the device (APM_SKIP_UNTOUCHED) the pages to update are known only there.
 // Few slices: the plain grid, whose wavefronts leave if their page's record says skipped.  More: the finalize
 // pass notes the other pages, and a grid of 1 / kSkipSpread of all slices' wavefronts (but kSkipWaves
@@ -788,7 +791,7 @@ __global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(Str
 // memory-side cache (256 MiB) then: D pages are kLookAhead elements, 32 MiB of gradient (4, 8, 16, 32, 64, 100 M
 // elements ahead, 1.3 B parameters: 6567, 6005, 5862, 5970, 6000, 6100 us a call).  Against a reduce
 // pass, a pass over its results and the update: 1.3 B parameters 5963 -> 5780 us, 127 M 596 -> 568,
-// 4.8 M in small pages 38.4 -> 34.0; from 1 M to 256 M elements never slower.
+// 4.8 M in small pages 38.4 -> 34.0; for smaller pages see one_pass_pays.
 //
 // Wavefronts hand results on through single words in device memory (a tile's sum, a page's scale)
 // which the stage / prepare pass has marked as not there yet; value and mark are one word, so
@@ -1315,7 +1318,7 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
     return for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used, int64_t sum_used) {
         const dim3 grid((unsigned)((max_used + kTile<U> - 1) / kTile<U>), (unsigned)ny), block(kUpdThreads);
 #define APM_LAUNCH_UPDATE(G, Q) hipLaunchKernelGGL((apm_adamw_kernel<U, G, Q>), grid, block, lds, s, L.recs + begin, L.p32, L.m32, L.v32, a)
-        const unsigned lds = (L.gather || L.scatter) && sum_used <= kFewElems ? kFewLds : APM_UPDATE_LDS;
+        const unsigned lds = update_lds(L.gather || L.scatter, sum_used, APM_UPDATE_LDS);
 #define APM_LAUNCH_RUN(BARE, RUNS) hipLaunchKernelGGL((apm_adamw_run_kernel<U, BARE>), grid, block, lds, s, RUNS, state(L.p32, begin), \
                                                       state(L.m32, begin), state(L.v32, begin), g16(begin), p16(begin), (int)L.E, a)
         if (run && L.bare_run) APM_LAUNCH_RUN(true, L.used + L.grad_first + begin);
@@ -1327,6 +1330,17 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
 #undef APM_LAUNCH_UPDATE
 #undef APM_LAUNCH_RUN
     });
+}
+
+// In one grid a page takes at least three wavefronts, two of them with next to nothing to do when the page is
+// small; with few pages a launch less counts for more, unless the form without a stage kernel has no more launches
+// either.  us a call, in one grid / as passes, pages of 512, 1024, 2048, 4096, 8192 elements:
+//   64 M elements, consecutive pages   811 / 521  461 / 411  362 / 353  323 / 324  310 / 316
+//   8 M, consecutive                    91 / 71    67 / 60    54 / 52    48 / 49    46 / 48
+//   256 K, from and to tensors        12.8 / 14.7  12.3 / 14.8  11.7 / 14.7
+//   4096 pages of 256, reversed / from and to tensors   47.6 / 43.7, 21.4 / 20.3; 2048 of 512   31.7 / 34.7, 16.5 / 18.9
+bool one_pass_pays(int skip_mode, int64_t page_elems, int64_t staged_pages) {
+    return skip_mode == APM_SKIP_NONE && (page_elems >= 4096 || (staged_pages >= 0 && staged_pages <= 2048));
 }
 
 hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {
@@ -1365,7 +1379,7 @@ hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {
             c.g16 = L.g16 + b16;
             c.p16 = L.p16 + b16;
             const dim3 grid((unsigned)(count * items)), block(kUpdThreads);
-            const unsigned lds = (L.gather || L.scatter) && cls[k].sum_used <= kFewElems ? kFewLds : kClipLds;
+            const unsigned lds = update_lds(L.gather || L.scatter, cls[k].sum_used, kClipLds);
             if (run) hipLaunchKernelGGL((apm_adamw_clip_kernel<true, false, false>), grid, block, lds, s, c, a);
             else if (L.gather && L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, true>), grid, block, lds, s, c, a);
             else if (L.gather) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, false>), grid, block, lds, s, c, a);

@@ -222,6 +222,9 @@ hipError_t launch_adamw(const AdamwLaunch& a, hipStream_t s);
 // Norms, clip scales and update in one kernel, after the stage / prepare pass of a launch with
 // one_pass set; for skip_mode NONE and fp32 classes in device memory.
 hipError_t launch_clip_update(const AdamwLaunch& a, hipStream_t s);
+// Whether that is the better form for pages of page_elems elements.  staged_pages: pages of a launch whose
+// records a stage kernel writes, else -1.
+bool one_pass_pays(int skip_mode, int64_t page_elems, int64_t staged_pages);
 // Pool flag for tests: wavefronts that would wait for another one's result never do (wait_limit 0).
 constexpr uint32_t kPoolNeverWait = 1u << 31;
 constexpr int32_t kWaitLimit = 4096;

@@ -128,10 +128,6 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     const int64_t n_list = run || whole ? 0 : n_pages;
     const int64_t n_g = grad_tensors ? n_tensors : 0, n_q = p16_tensors ? n_tensors : 0;
     std::vector<uint64_t> words((size_t)(n_list + n_g + n_q));
-    for (int64_t k = 0; k < n_list; ++k)
-        words[(size_t)k] = (uint64_t)page_at(order[(size_t)k]) | (uint64_t)order[(size_t)k] << 32;
-    for (int64_t i = 0; i < n_g; ++i) words[(size_t)(n_list + i)] = reinterpret_cast<uint64_t>(grad_tensors[i].data);
-    for (int64_t i = 0; i < n_q; ++i) words[(size_t)(n_list + n_g + i)] = reinterpret_cast<uint64_t>(p16_tensors[i].data);
     sc.list = n_list ? words.data() : nullptr;
     sc.g_ptrs = n_g ? words.data() + n_list : nullptr;
     sc.q_ptrs = n_q ? words.data() + n_list + n_g : nullptr;
@@ -140,14 +136,39 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     sc.d_list = pool->d_list;
     sc.d_out = pool->d_list_out;
     int ring_slot = -1;
-    if (stage_launches(sc, n_pages) > kMaxStageLaunches) {
-        const size_t bytes = words.size() * sizeof(uint64_t);
+    const bool by_ring = stage_launches(sc, n_pages) > kMaxStageLaunches;
+    // A list alone that goes through the ring is read there by the step's kernels: no stage kernel.
+    const bool staged = tensors || (n_list > 0 && !by_ring);
+    const int64_t* d_list = whole ? pool->d_order : pool->d_list;
+    const int32_t* d_out = whole ? pool->d_order_out : pool->d_list_out;
+    if (staged) {
+        for (int64_t k = 0; k < n_list; ++k)
+            words[(size_t)k] = (uint64_t)page_at(order[(size_t)k]) | (uint64_t)order[(size_t)k] << 32;
+        for (int64_t i = 0; i < n_g; ++i) words[(size_t)(n_list + i)] = reinterpret_cast<uint64_t>(grad_tensors[i].data);
+        for (int64_t i = 0; i < n_q; ++i) words[(size_t)(n_list + n_g + i)] = reinterpret_cast<uint64_t>(p16_tensors[i].data);
+    }
+    if (by_ring) {
+        const size_t bytes = staged ? words.size() * sizeof(uint64_t) : (size_t)n_list * (sizeof(int64_t) + sizeof(int32_t));
         rc = pool->ring.acquire(bytes, &ring_slot);
         if (rc != APM_OK) return rc;
-        std::memcpy(pool->ring.h[ring_slot], words.data(), bytes);
+        if (staged) {
+            std::memcpy(pool->ring.h[ring_slot], words.data(), bytes);
+        } else {
+            int64_t* list = static_cast<int64_t*>(pool->ring.h[ring_slot]);
+            int32_t* out = reinterpret_cast<int32_t*>(list + n_list);
+            for (int64_t k = 0; k < n_list; ++k) {
+                list[k] = page_at(order[(size_t)k]);
+                out[k] = (int32_t)order[(size_t)k];
+            }
+        }
         rc = pool->ring.commit(ring_slot, bytes, stream);
         if (rc != APM_OK) return rc;
-        sc.d_words = static_cast<const uint64_t*>(pool->ring.d[ring_slot]);
+        if (staged) {
+            sc.d_words = static_cast<const uint64_t*>(pool->ring.d[ring_slot]);
+        } else {
+            d_list = static_cast<const int64_t*>(pool->ring.d[ring_slot]);
+            d_out = reinterpret_cast<const int32_t*>(d_list + n_list);
+        }
     }
     L.p32 = static_cast<float*>(pool->base[APM_P32]);
     L.m32 = static_cast<float*>(pool->base[APM_M32]);
@@ -156,8 +177,8 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     L.p16 = static_cast<uint16_t*>(pool->base[APM_P16]);
     L.used = pool->d_used;
     if (!run) {
-        L.state_pages = L.grad_pages = whole ? pool->d_order : pool->d_list;
-        L.out_index = whole ? pool->d_order_out : pool->d_list_out;
+        L.state_pages = L.grad_pages = d_list;
+        L.out_index = d_out;
     }
     L.state_first = L.grad_first = page_at(0);
     L.gather = grad_tensors != nullptr;
@@ -170,21 +191,14 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     L.recs = pool->d_recs;
     L.live = pool->d_live;
     L.sums_ready = need_reduce && page_sums;
-    L.one_pass = need_reduce && !page_sums && L.skip_mode == APM_SKIP_NONE;
+    L.one_pass = need_reduce && !page_sums && one_pass_pays(L.skip_mode, E, staged ? n_pages : -1);
     L.wait_limit = pool->desc.flags & kPoolNeverWait ? 0 : kWaitLimit;
     L.max_workgroups = pool->max_workgroups;
     if (need_reduce) {
         L.partials = page_sums ? page_sums : pool->d_partials;
         L.nzflags = page_sums ? page_nzflags : pool->d_nzflags;
     }
-    const bool staged = n_list > 0 || tensors;
-    if (staged) {
-        APM_HIP(launch_stage(L, sc, stream));
-        if (ring_slot >= 0) {  // only the stage kernel reads the slot
-            rc = pool->ring.seal(ring_slot, stream);
-            if (rc != APM_OK) return rc;
-        }
-    }
+    if (staged) APM_HIP(launch_stage(L, sc, stream));
     if (need_reduce && !L.one_pass) {
         ScopedTiming t(pool, APM_K_REDUCE, stream);
         APM_HIP(launch_grad_reduce(L, stream));
@@ -196,7 +210,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
         ScopedTiming t(pool, APM_K_UPDATE, stream);
         APM_HIP(L.one_pass ? launch_clip_update(L, stream) : launch_adamw(L, stream));
     }
-    return APM_OK;
+    return ring_slot >= 0 ? pool->ring.seal(ring_slot, stream) : APM_OK;
 }
 
 namespace {

@@ -377,3 +377,56 @@ def test_a_list_of_many_small_pages_is_grouped_quickly():
     whole, general = (_us(lambda: apm.apm_page_adamw_step(pool, None, k, 3, hyper, None, None), 30) for k in (n, n + 1))
     pool.destroy()
     assert general < 3 * whole, (general, whole)
+
+
+@pytest.mark.parametrize("listed", ["all", "reversed", "odd"])
+@pytest.mark.parametrize("n", [2047, 2048, 2049, 4100])
+@pytest.mark.parametrize("E", [8, 520, 4088, 4096])
+def test_clipped_steps_around_the_rule_for_one_grid_agree(E, n, listed):
+    """Clipped steps in one grid and as passes (page sizes and page counts on both sides of the rule; lists in
+    kernel arguments and in the ring): norms against 64 bits (one fp32 rounding), p16 and moments against the
+    same pages stepped through tensors."""
+    tot = (n - 1) * E + E // 2 + 3
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    g = (torch.randn(n * E, device=DEV, generator=gen) * 1e-2).bfloat16()
+    g[tot:] = 0
+    p0 = torch.randn(n * E, device=DEV, generator=gen) * 0.02
+    one = lambda t: apm.make_tensors([tot], apm.APM_F32 if t.dtype == torch.float32 else apm.APM_BF16, [t.data_ptr()])  # noqa: E731
+    pages = {"all": None, "reversed": list(range(n))[::-1], "odd": list(range(1, n, 2))}[listed]
+    at = list(range(n)) if pages is None else pages
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.05, apm.APM_SKIP_NONE)
+    got = []
+    for fused in (False, True):
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n)
+        apm.apm_pack_tensors(pool, apm.APM_P32, one(p0), 1)
+        norm, q = torch.full((len(at),), -1.0, device=DEV), torch.zeros_like(g)
+        if fused:
+            apm.apm_page_adamw_step_fused(pool, pages, len(at), 3, hyper, one(g), one(q), 1, norm, None)
+        else:
+            apm.apm_pack_tensors(pool, apm.APM_G16, one(g), 1)
+            apm.apm_page_adamw_step(pool, pages, len(at), 3, hyper, norm, None)
+            apm.apm_unpack(pool, apm.APM_P16, one(q), 1)
+        out = [norm, q] + [torch.zeros_like(p0) for _ in range(3)]
+        for st, o in zip((apm.APM_P32, apm.APM_M32, apm.APM_V32), out[2:]):
+            apm.apm_unpack(pool, st, one(o), 1)
+        torch.cuda.synchronize()
+        got.append(out)
+        pool.destroy()
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    want = g.view(n, E).double().square().sum(1).sqrt()[torch.tensor(at, device=DEV)]
+    assert torch.allclose(got[0][0].double(), want, rtol=2.0 ** -23, atol=0.0)
+
+
+def test_norms_of_small_pages_cost_no_more_than_finding_skipped_ones():
+    """131072 pages of 512 elements: a step with norms in one grid, three wavefronts a page, took 1.55 times the
+    passes that a skipping step runs (bound 1.25)."""
+    E, n = 512, 131072
+    pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n)
+    apm.lib().apm_pool_set_layout(pool.handle, apm.make_tensors([n * E], apm.APM_F32, [0]), 1, None, None, None, None, None)
+    torch.as_tensor(_Region(pool, apm.APM_G16, n * E), device=DEV).fill_(0x3a00)
+    norm = torch.zeros(n, device=DEV)
+    step = lambda skip: apm.apm_page_adamw_step(pool, None, n, 3, apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.0, skip), norm, None)  # noqa: E731
+    norms, skipping = _us(lambda: step(0), 20), _us(lambda: step(1), 20)
+    pool.destroy()
+    assert norms < 1.25 * skipping, (norms, skipping)
