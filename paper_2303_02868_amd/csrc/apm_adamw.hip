@@ -98,6 +98,7 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float x) {
 // with clipping 14.3 / 13.9, 18.8 / 18.2, 45.2 / 45.5).
 constexpr int64_t kFewElems = (int64_t)24 << 20, kFewRunElems = (int64_t)2 << 20;
 constexpr int kFewLds = 9216;
+constexpr int kWideU = 4, kWideLds = 32768;
 unsigned update_lds(bool tensors, int64_t elems, unsigned lds) { return elems <= (tensors ? kFewElems : kFewRunElems) ? kFewLds : lds; }
 
 // When pages may be skipped on the device (APM_SKIP_UNTOUCHED) the pages to update are known only there.
@@ -1316,13 +1317,17 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
     }
     constexpr int U = APM_UPDATE_U;
     return for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used, int64_t sum_used) {
-        const dim3 grid((unsigned)((max_used + kTile<U> - 1) / kTile<U>), (unsigned)ny), block(kUpdThreads);
+        const bool wide = run && L.wide;
+        const int tile = wide ? kTile<kWideU> : kTile<U>;
+        const dim3 grid((unsigned)((max_used + tile - 1) / tile), (unsigned)ny), block(kUpdThreads);
 #define APM_LAUNCH_UPDATE(G, Q) hipLaunchKernelGGL((apm_adamw_kernel<U, G, Q>), grid, block, lds, s, L.recs + begin, L.p32, L.m32, L.v32, a)
-        const unsigned lds = update_lds(L.gather || L.scatter, sum_used, APM_UPDATE_LDS);
-#define APM_LAUNCH_RUN(BARE, RUNS) hipLaunchKernelGGL((apm_adamw_run_kernel<U, BARE>), grid, block, lds, s, RUNS, state(L.p32, begin), \
-                                                      state(L.m32, begin), state(L.v32, begin), g16(begin), p16(begin), (int)L.E, a)
-        if (run && L.bare_run) APM_LAUNCH_RUN(true, L.used + L.grad_first + begin);
-        else if (run) APM_LAUNCH_RUN(false, runs + begin);
+        const unsigned lds = wide ? kWideLds : update_lds(L.gather || L.scatter, sum_used, APM_UPDATE_LDS);
+#define APM_LAUNCH_RUN(U, BARE, RUNS) hipLaunchKernelGGL((apm_adamw_run_kernel<U, BARE>), grid, block, lds, s, RUNS, state(L.p32, begin), \
+                                                         state(L.m32, begin), state(L.v32, begin), g16(begin), p16(begin), (int)L.E, a)
+        if (wide && L.bare_run) APM_LAUNCH_RUN(kWideU, true, L.used + L.grad_first + begin);
+        else if (wide) APM_LAUNCH_RUN(kWideU, false, runs + begin);
+        else if (run && L.bare_run) APM_LAUNCH_RUN(U, true, L.used + L.grad_first + begin);
+        else if (run) APM_LAUNCH_RUN(U, false, runs + begin);
         else if (L.gather && L.scatter) APM_LAUNCH_UPDATE(true, true);
         else if (L.gather) APM_LAUNCH_UPDATE(true, false);
         else if (L.scatter) APM_LAUNCH_UPDATE(false, true);

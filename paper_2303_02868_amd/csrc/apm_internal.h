@@ -187,6 +187,7 @@ struct AdamwLaunch {
                                   // page slices (fp32 classes in host memory); 0: one per slice
     int32_t stride_waves_per_wg;  // how many of them share a workgroup, 1..16
     bool host_write_through;      // stride form: fp32 state stores written through at system scope
+    bool wide;                    // a run whose grid holds many workgroups without work: fewer, larger slices
     bool bare_run;                // a run without a reduce or prepare pass: the update reads `used` itself
     int32_t* live;                // scratch of a launch that may skip pages, kLiveInts(n_listed) entries
     bool sums_ready;              // partials / nzflags hold the sums already, indexed by page
@@ -312,6 +313,7 @@ struct apm_pool {
     std::vector<int64_t> layout_ids;
     apm::Plan plan;
     std::vector<int32_t> used;  // used extent of every page of the pool (0 beyond the layout); empty before a layout
+    std::vector<int64_t> used_sum;  // used_sum[k]: of pages [0, k) in use
 
     int fd[APM_N_STATES] = {-1, -1, -1, -1, -1};  // FILE pools: one file per stored class
 
@@ -385,6 +387,8 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
                  const apm_tensor* p16_tensors = nullptr, int64_t n_tensors = 0,
                  double* page_sums = nullptr, uint32_t* page_nzflags = nullptr);
 int ensure_scratch(apm_pool* pool, bool list = false);
+// AdamwLaunch::wide for pages [first, first + n) launched with a full page's grid each.
+bool wide_pays(const apm_pool* pool, int64_t first, int64_t n);
 // Allocates the ping-pong gradient halves, the events and the update stream of the delayed path.
 // caller != nullptr-able: the stream the producer works on; the update stream is chosen so that
 // its kernels run beside that stream's (see make_overlapping_stream).

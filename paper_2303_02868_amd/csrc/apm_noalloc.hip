@@ -112,7 +112,8 @@ extern "C" int apm_page_adamw_step_noalloc(apm_pool* pool, int64_t n_pages, int6
         L.skip_mask = skip_mask;
         hipStream_t s = static_cast<hipStream_t>(stream);
         const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
-        L.one_pass = need_reduce && one_pass_pays(L.skip_mode, L.E, -1);
+        L.wide = wide_pays(pool, 0, n_pages);
+        L.one_pass = need_reduce && !L.wide && one_pass_pays(L.skip_mode, L.E, -1);
         L.wait_limit = pool->desc.flags & kPoolNeverWait ? 0 : kWaitLimit;
         if (!need_reduce) {
             L.partials = nullptr;

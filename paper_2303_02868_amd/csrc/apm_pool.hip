@@ -186,6 +186,8 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     const size_t n_in_use = plan.pages.size();
     std::vector<int32_t> used((size_t)pool->desc.n_pages, 0);
     for (size_t k = 0; k < n_in_use; ++k) used[k] = (int32_t)plan.pages[k].used;
+    std::vector<int64_t> used_sum(n_in_use + 1, 0);
+    for (size_t k = 0; k < n_in_use; ++k) used_sum[k + 1] = used_sum[k] + used[k];
     std::vector<int64_t> order(n_in_use);
     ExtentClass cls[kMaxExtentClasses] = {};
     const int n_cls = group_by_extent((int64_t)n_in_use, plan.E, used.data(), order.data(), cls);
@@ -251,6 +253,7 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     pool->d_order = reinterpret_cast<int64_t*>(pool->d_tables + tables.at[2]);
     pool->d_order_out = reinterpret_cast<int32_t*>(pool->d_tables + tables.at[3]);
     pool->used.swap(used);
+    pool->used_sum.swap(used_sum);
     pool->order_n_cls = n_cls;
     pool->order_run = run;
     for (int c = 0; c < kMaxExtentClasses; ++c) pool->order_cls[c] = cls[c];

@@ -378,6 +378,7 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
                 C.partials = L.partials + first * L.S;
                 C.nzflags = L.nzflags + first * L.S;
             }
+            C.wide = wide_pays(dev, first, n);
             C.state_first = part == 0 ? first : first - H0;
             C.grad_first = first;
             C.n_listed = n;
@@ -436,6 +437,7 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
         C.p32 = static_cast<float*>(s->cache->base[APM_P32]);
         C.m32 = static_cast<float*>(s->cache->base[APM_M32]);
         C.v32 = static_cast<float*>(s->cache->base[APM_V32]);
+        C.wide = wide_pays(dev, r_done, nr);
         C.state_first = C.grad_first = r_done;
         C.n_listed = nr;
         C.grad_norm = grad_norm ? grad_norm + r_done : nullptr;
@@ -461,6 +463,7 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
         L.state_first = (int64_t)slot * s->B;
         L.grad_first = first;
         L.n_listed = nb;
+        L.wide = wide_pays(dev, first, nb);
         L.grad_norm = grad_norm ? grad_norm + first : nullptr;
         L.skip_mask = skip_mask ? skip_mask + first : nullptr;
         if (what & kDoUpdate) {

@@ -430,3 +430,53 @@ def test_norms_of_small_pages_cost_no_more_than_finding_skipped_ones():
     norms, skipping = _us(lambda: step(0), 20), _us(lambda: step(1), 20)
     pool.destroy()
     assert norms < 1.25 * skipping, (norms, skipping)
+
+
+@pytest.mark.parametrize("clip,skip,norms", [(0.0, 0, False), (0.02, 0, True), (0.02, 1, True)])
+@pytest.mark.parametrize("E,numels", [(1 << 19, [3, 1 << 19, 700, 1025, 5]), (1 << 19, [(1 << 19) + 9, 1 << 19, 3]), (8192, [4097] + [100] * 9),
+                                      (4096, [1] * 5)])
+def test_noalloc_step_over_nearly_empty_pages_equals_the_step(E, numels, clip, skip, norms):
+    """Pages launched with a full page's grid in larger slices where most of it is idle (both sides of the
+    rule): the bits of the step that sizes its grids by extent."""
+    n_t, off = len(numels), [0]
+    for m in numels:
+        off.append(off[-1] + (m + 7) // 8 * 8)
+    gen = torch.Generator(device=DEV).manual_seed(n_t)
+    g = (torch.randn(off[-1], device=DEV, generator=gen) * 1e-2).bfloat16()
+    g[off[n_t - 2]:off[n_t - 1]] = 0
+    p0 = torch.randn(off[-1], device=DEV, generator=gen) * 0.02
+    lst = lambda t: apm.make_tensors(numels, apm.APM_F32 if t.dtype == torch.float32 else apm.APM_BF16,  # noqa: E731
+                                     [t.data_ptr() + t.element_size() * o for o in off[:-1]])
+    n, got = oracle.plan_pack(numels, E).n_pages, []
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, clip, skip)
+    for noalloc in (False, True):
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n)
+        apm.apm_pack_tensors(pool, apm.APM_P32, lst(p0), n_t)
+        apm.apm_pack_tensors(pool, apm.APM_G16, lst(g), n_t)
+        norm = torch.full((n,), -1.0, device=DEV) if norms else None
+        if noalloc:
+            apm.apm_page_adamw_step_noalloc(pool, n, 3, hyper, norm, None)
+        else:
+            apm.apm_page_adamw_step(pool, None, n, 3, hyper, norm, None)
+        out = [torch.zeros_like(p0) for _ in range(3)] + [torch.zeros_like(g)]
+        for st, o in zip((apm.APM_P32, apm.APM_M32, apm.APM_V32, apm.APM_P16), out):
+            apm.apm_unpack(pool, st, lst(o), n_t)
+        torch.cuda.synchronize()
+        got.append(out + ([norm] if norms else []))
+        pool.destroy()
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
+def test_nearly_empty_pages_cost_the_noalloc_step_little():
+    """Two full pages of 2^20 elements and 60 nearly empty ones: four times the idle workgroups took 4.5 times the
+    two pages' time (larger slices 1.7; bound 3)."""
+    E, us = 1 << 20, []
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.0, 0)
+    for empty in (0, 60):
+        numels = [E, E] + [100] * empty
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, len(numels))
+        apm.lib().apm_pool_set_layout(pool.handle, apm.make_tensors(numels, apm.APM_F32, [0] * len(numels)), len(numels), None, None, None, None, None)
+        us.append(_us(lambda: apm.apm_page_adamw_step_noalloc(pool, len(numels), 3, hyper, None, None), 100))
+        pool.destroy()
+    assert us[1] < 3 * us[0], us
