@@ -576,6 +576,9 @@ int apm_tiered_step_delayed(apm_tiered* t, const void* new_g16, const apm_hyper*
  * per-call arguments.  The hyper-parameters passed with a flush are validated and otherwise unused.
  * P16 is rewritten asynchronously by the update stream: a reader that does not flush may see
  * parameters one step stale, which is the mechanism's stated trade-off.
+ * What is staged are the used extents of the layout installed at the call.  If a layout installed before
+ * the gradient is applied gives a listed page more elements than that, the call that would apply it
+ * returns APM_ESTATE, drops the gradient and does nothing else (flush before re-installing a layout).
  */
 int apm_step_delayed(apm_pool* pool, const int64_t* pages, int64_t n_pages, const void* new_g16,
                      const apm_hyper* hyper, void* stream);
@@ -611,7 +614,8 @@ int apm_streamer_overlap_report(const apm_streamer* s, int* update_stream, int* 
  * bf16_rne(fp32(g') + fp32(g)), the fp32 sum rounded to nearest, over the used extents of the
  * listed pages.  g16: device pointer, page layout, as new_g16 of apm_step_delayed.  Asynchronous
  * on `stream`; the caller may reuse g16 once `stream` has passed this point.
- * Errors: APM_ESTATE if no gradient is buffered; APM_EINVAL, APM_ERANGE.
+ * Errors: APM_ESTATE if no gradient is buffered, or not all of a listed page (see apm_step_delayed);
+ * APM_EINVAL, APM_ERANGE.
  */
 int apm_delayed_accumulate(apm_pool* pool, const int64_t* pages, int64_t n_pages, const void* g16,
                            void* stream);

@@ -366,6 +366,10 @@ struct apm_pool {
     std::vector<int64_t> buf_pages;  // copy of the caller's list (unused if buf_pages_null)
     bool buf_pages_null = true;      // the call listed pages [0, buf_n_pages)
     int64_t buf_n_pages = 0;
+    // Its half holds the used extents of the layout it was handed over under (buf_by_extent; else whole
+    // pages).  buf_extents: those extents, kept by the first layout that replaces that one; empty until then.
+    bool buf_by_extent = false;
+    std::vector<int32_t> buf_extents;
     float* delayed_norm = nullptr;
     uint8_t* delayed_skip = nullptr;
 

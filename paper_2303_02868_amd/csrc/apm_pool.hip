@@ -252,7 +252,8 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     pool->d_tenants = reinterpret_cast<TenantRec*>(pool->d_tables + tables.at[1]);
     pool->d_order = reinterpret_cast<int64_t*>(pool->d_tables + tables.at[2]);
     pool->d_order_out = reinterpret_cast<int32_t*>(pool->d_tables + tables.at[3]);
-    pool->used.swap(used);
+    pool->used.swap(used);  // `used`: the old layout's
+    if (pool->buffered && pool->buf_by_extent && pool->buf_extents.empty()) pool->buf_extents = std::move(used);
     pool->used_sum.swap(used_sum);
     pool->order_n_cls = n_cls;
     pool->order_run = run;

@@ -400,9 +400,25 @@ static int take_gradient(apm_pool* pool, int k, const uint16_t* g16, const int64
     return slot >= 0 ? pool->ring.seal(slot, s) : APM_OK;
 }
 
+// Whether the buffered gradient holds every element that the layout installed now gives the listed pages.
+static int check_buffered(const apm_pool* pool, const int64_t* pages, int64_t n_pages) {
+    if (pool->buf_extents.empty()) return APM_OK;
+    for (int64_t i = 0; i < n_pages; ++i) {
+        const int64_t p = pages ? pages[i] : i;
+        if (pool->used[(size_t)p] > ((pool->buf_extents[(size_t)p] + 7) & ~7))
+            return fail(APM_ESTATE, "page %lld has %d elements in the layout installed since the gradient was handed over, %d were handed over", (long long)p, pool->used[(size_t)p], pool->buf_extents[(size_t)p]);
+    }
+    return APM_OK;
+}
+
 // Applies the buffered gradient (half `cur`) on the update stream.
 static int apply_buffered(apm_pool* pool, const DelayedApply& apply) {
     const int k = pool->cur;
+    const int held = check_buffered(pool, pool->buf_pages_null ? nullptr : pool->buf_pages.data(), pool->buf_n_pages);
+    if (held != APM_OK) {  // it cannot be applied any more
+        pool->buffered = false;
+        return held;
+    }
     APM_HIP(hipStreamWaitEvent(pool->upd_stream, pool->ev_staged[k], 0));
     int rc = apply(pool->gbuf[k], pool->applied + 1, pool->upd_stream,
                    pool->buf_pages_null ? nullptr : pool->buf_pages.data(), pool->buf_n_pages, &pool->buf_hyper);
@@ -443,7 +459,8 @@ int delayed_call(apm_pool* pool, const int64_t* pages, int64_t n_pages, const vo
     const bool in_place = src == dst;
     if (!in_place && pool->applied_valid[nxt]) APM_HIP(hipStreamWaitEvent(s, pool->ev_applied[nxt], 0));
     pool->gsum_ok[nxt] = false;
-    if (!in_place && pool->has_layout && (reinterpret_cast<uintptr_t>(new_g16) & 15u) == 0) {
+    const bool by_extent = !in_place && pool->has_layout && (reinterpret_cast<uintptr_t>(new_g16) & 15u) == 0;
+    if (by_extent) {
         want_sums = want_sums && ensure_sums(pool, nxt);
         rc = take_gradient(pool, nxt, static_cast<const uint16_t*>(new_g16), pages, n_pages, false, want_sums, s);
         if (rc != APM_OK) return rc;
@@ -463,6 +480,8 @@ int delayed_call(apm_pool* pool, const int64_t* pages, int64_t n_pages, const vo
     pool->buf_pages.swap(list_copy);
     pool->buf_pages_null = pages == nullptr;
     pool->buf_n_pages = n_pages;
+    pool->buf_by_extent = by_extent;
+    pool->buf_extents.clear();
     pool->cur = nxt;
     pool->buffered = true;
     return APM_OK;
@@ -532,13 +551,15 @@ extern "C" int apm_delayed_accumulate(apm_pool* pool, const int64_t* pages, int6
         if (pages)
             for (int64_t k = 0; k < n_pages; ++k)
                 if (pages[k] < 0 || pages[k] >= pool->desc.n_pages) return fail(APM_ERANGE, "pages[%lld] out of range", (long long)k);
+        int rc = check_buffered(pool, pages, n_pages);
+        if (rc != APM_OK) return rc;
         // The collecting half was staged on the producer's stream; the sum is ordered after it there,
         // and the "staged" event moves behind the sum so that the update sees the accumulated values.
         const int k = pool->cur;
         APM_HIP(hipStreamWaitEvent(s, pool->ev_staged[k], 0));
         if (pool->has_layout) {  // without a layout no page has a used extent
             if (pool->gsum_epoch[k] != pool->layout_epoch) pool->gsum_ok[k] = false;
-            int rc = take_gradient(pool, k, static_cast<const uint16_t*>(g16), pages, n_pages, true, pool->gsum_ok[k], s);
+            rc = take_gradient(pool, k, static_cast<const uint16_t*>(g16), pages, n_pages, true, pool->gsum_ok[k], s);
             if (rc != APM_OK) return rc;
         }
         APM_HIP(hipEventRecord(pool->ev_staged[k], s));

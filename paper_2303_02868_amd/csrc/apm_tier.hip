@@ -383,6 +383,8 @@ extern "C" int apm_tiered_step_delayed(apm_tiered* t, const void* new_g16, const
         dev->buf_pages.clear();
         dev->buf_pages_null = true;
         dev->buf_n_pages = N;
+        dev->buf_by_extent = false;
+        dev->buf_extents.clear();
         dev->cur = nxt;
         dev->buffered = true;
         return APM_OK;

@@ -480,3 +480,45 @@ def test_nearly_empty_pages_cost_the_noalloc_step_little():
         us.append(_us(lambda: apm.apm_page_adamw_step_noalloc(pool, len(numels), 3, hyper, None, None), 100))
         pool.destroy()
     assert us[1] < 3 * us[0], us
+
+
+def test_a_buffered_gradient_is_not_applied_beyond_what_was_handed_over():
+    """The hand-over takes the used extents of its layout.  A layout with larger extents installed before the
+    update: an error and no update, once, instead of an older gradient's bytes; one with smaller extents: the
+    same bits as a synchronous step."""
+    E, gen = 1024, torch.Generator(device=DEV).manual_seed(5)
+    lists = {name: [n, n] for name, n in (("small", 40), ("large", 600))}
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.0, 0)
+    g = (torch.randn(2 * E, device=DEV, generator=gen) * 1e-2).bfloat16().view(2, E)
+
+    def lay(pool, name):
+        torch.cuda.synchronize()
+        apm.apm_pool_set_layout(pool, apm.make_tensors(lists[name], apm.APM_F32, [0, 0]), 2)
+
+    def moments(pool, name):
+        out = torch.zeros(2, E, device=DEV)
+        apm.apm_unpack(pool, apm.APM_M32, apm.make_tensors(lists[name], apm.APM_F32, [out.data_ptr(), out.data_ptr() + 4 * E]), 2)
+        torch.cuda.synchronize()
+        return out
+
+    pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, 2)
+    lay(pool, "large")
+    apm.apm_step_delayed(pool, None, 2, g.data_ptr(), hyper)
+    apm.apm_step_delayed(pool, None, 2, None, hyper)     # leaves an older gradient in one half
+    lay(pool, "small")
+    for _ in range(2):                                   # and small extents of a newer one in both
+        apm.apm_step_delayed(pool, None, 2, g.data_ptr(), hyper)
+    lay(pool, "large")
+    for call in (lambda: apm.apm_delayed_accumulate(pool, None, 2, g.data_ptr()), lambda: apm.apm_step_delayed(pool, None, 2, None, hyper)):
+        with pytest.raises(apm.ApmError) as e:
+            call()
+        assert e.value.code == apm.APM_ESTATE
+    assert not moments(pool, "large").any()
+    apm.apm_step_delayed(pool, None, 2, None, hyper)     # nothing is left to apply
+    assert not moments(pool, "large").any()
+    apm.apm_step_delayed(pool, None, 2, g.data_ptr(), hyper)
+    lay(pool, "small")
+    apm.apm_step_delayed(pool, None, 2, None, hyper)
+    got = moments(pool, "small")
+    assert torch.equal(got[:, :40], g[:, :40].float() * 0.1)
+    pool.destroy()
