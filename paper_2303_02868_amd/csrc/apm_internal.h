@@ -226,8 +226,6 @@ hipError_t launch_clip_update(const AdamwLaunch& a, hipStream_t s);
 // Whether that is the better form for pages of page_elems elements.  staged_pages: pages of a launch whose
 // records a stage kernel writes, else -1.
 bool one_pass_pays(int skip_mode, int64_t page_elems, int64_t staged_pages);
-// Pool flag for tests: wavefronts that would wait for another one's result never do (wait_limit 0).
-constexpr uint32_t kPoolNeverWait = 1u << 31;
 constexpr int32_t kWaitLimit = 4096;
 // Takes a gradient in page layout over into a buffered half: dst <- src, or (accumulate) dst <- dst + src, over
 // the used extents of the listed pages, and if `sums` is set works out the tiles' sums of squares and
@@ -340,7 +338,8 @@ struct apm_pool {
     int32_t* d_list_out = nullptr;
     int32_t S = 0;
     apm::StageRing ring;
-    int64_t max_workgroups = 0;  // see AdamwLaunch; set by tests only
+    int64_t max_workgroups = 0;  // see AdamwLaunch; set by tests only, as
+    int32_t wait_limit = apm::kWaitLimit;
 
     // one-step-stale update state
     hipStream_t upd_stream = nullptr;
@@ -441,3 +440,5 @@ struct ScopedTiming {
 // For tests, not part of the C ABI: caps the workgroups of the pool's one-dimensional update launches
 // (0: no cap), so that small pools exercise what otherwise takes tens of millions of pages.
 extern "C" int apm_test_set_max_workgroups(apm_pool* pool, int64_t max_workgroups);
+// The same for AdamwLaunch::wait_limit (0: wavefronts that would wait for another one's result never do).
+extern "C" int apm_test_set_wait_limit(apm_pool* pool, int32_t wait_limit);

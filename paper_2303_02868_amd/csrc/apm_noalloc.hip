@@ -114,7 +114,7 @@ extern "C" int apm_page_adamw_step_noalloc(apm_pool* pool, int64_t n_pages, int6
         const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
         L.wide = wide_pays(pool, 0, n_pages);
         L.one_pass = need_reduce && !L.wide && one_pass_pays(L.skip_mode, L.E, -1);
-        L.wait_limit = pool->desc.flags & kPoolNeverWait ? 0 : kWaitLimit;
+        L.wait_limit = pool->wait_limit;
         if (!need_reduce) {
             L.partials = nullptr;
             L.nzflags = nullptr;

@@ -207,7 +207,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     L.live = pool->d_live;
     L.sums_ready = need_reduce && page_sums;
     L.one_pass = need_reduce && !page_sums && one_pass_pays(L.skip_mode, E, staged ? n_pages : -1);
-    L.wait_limit = pool->desc.flags & kPoolNeverWait ? 0 : kWaitLimit;
+    L.wait_limit = pool->wait_limit;
     L.max_workgroups = pool->max_workgroups;
     if (need_reduce) {
         L.partials = page_sums ? page_sums : pool->d_partials;
@@ -597,5 +597,11 @@ extern "C" int apm_delayed_set_outputs(apm_pool* pool, float* grad_norm, uint8_t
 extern "C" int apm_test_set_max_workgroups(apm_pool* pool, int64_t max_workgroups) {
     if (!pool || max_workgroups < 0) return fail(APM_EINVAL, "bad argument");
     pool->max_workgroups = max_workgroups;
+    return APM_OK;
+}
+
+extern "C" int apm_test_set_wait_limit(apm_pool* pool, int32_t wait_limit) {
+    if (!pool || wait_limit < 0) return fail(APM_EINVAL, "bad argument");
+    pool->wait_limit = wait_limit;
     return APM_OK;
 }

@@ -99,9 +99,6 @@ def test_fused_step_equals_the_page_step_for_any_tensor_count_and_list(n_t, list
         assert torch.equal(a, b)
 
 
-NEVER_WAIT = 1 << 31   # wavefronts of the clipped update compute what they would wait for
-
-
 @pytest.mark.parametrize("E,numels", [(8, [8, 3, 17]), (16384, [16384, 16383, 40000, 5]), (32776, [32776 * 3 + 257, 16385, 70001, 1]),
                                       (66 * 16384, [66 * 16384 + 12345, 64 * 16384 + 1, 66 * 16384 * 2, 300])])
 @pytest.mark.parametrize("form", ["run", "reversed", "fused"])
@@ -118,8 +115,10 @@ def test_clipped_update_with_and_without_waiting(E, numels, form):
                                      [t.data_ptr() + t.element_size() * o for o in off[:-1]])
     hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.05, apm.APM_SKIP_NONE)
     got = []
-    for flags in (0, NEVER_WAIT):
-        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, sum(-(-n // E) for n in numels) + 1, flags=flags)
+    for wait in (True, False):
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, sum(-(-n // E) for n in numels) + 1)
+        if not wait:   # wavefronts compute what they would wait for
+            assert apm.lib().apm_test_set_wait_limit(ctypes.c_void_p(pool.handle), 0) == 0
         apm.apm_pack_tensors(pool, apm.APM_P32, lst(p0), n_t)
         apm.apm_pack_tensors(pool, apm.APM_G16, lst(g), n_t)
         n = apm.lib().apm_pool_pages_in_use(pool.handle)
@@ -522,3 +521,16 @@ def test_a_buffered_gradient_is_not_applied_beyond_what_was_handed_over():
     got = moments(pool, "small")
     assert torch.equal(got[:, :40], g[:, :40].float() * 0.1)
     pool.destroy()
+
+
+def test_unused_pool_flags_do_not_change_the_update():
+    """Bits that the interface does not define have no effect; the highest one used to make every wavefront of
+    a clipped update sum its page by itself, hundreds of times the work (bound: three times)."""
+    E, n, us = 1 << 20, 8, []
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 1.0, 0)
+    for flags in (0, 1 << 31 | 1 << 17):
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n, flags=flags)
+        apm.lib().apm_pool_set_layout(pool.handle, apm.make_tensors([n * E], apm.APM_F32, [0]), 1, None, None, None, None, None)
+        us.append(_us(lambda: apm.apm_page_adamw_step(pool, None, n, 3, hyper, None, None), 10))
+        pool.destroy()
+    assert us[1] < 3 * us[0], us
