@@ -798,8 +798,8 @@ __global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(Str
 // which the stage / prepare pass has marked as not there yet; value and mark are one word, so
 // nothing else needs ordering.  Workgroups start in grid order, so whoever waits waits for wavefronts
 // that are already running, and by its turn an update slice almost always finds its scale in place.
-// Nothing relies on that order, though: after wait_limit polls a wavefront computes what it waits for
-// by itself, with the same result.
+// Nothing relies on that order, though: after wait_limit polls (more for a page of many tiles) a wavefront
+// computes what it waits for by itself, with the same result, or until a look between two tiles finds it there.
 constexpr int64_t kLookAhead = (int64_t)16 << 20;
 constexpr int kClipLds = 13312;  // 12 wavefronts per CU: 5832 us; 16, 13, 11, 10: 6000, 5840, 5873, 6164
 
@@ -878,12 +878,14 @@ __device__ __forceinline__ double tile_sum(const PageRec& rec, int tile, int lan
     return t;
 }
 
-// A page's sum by one wavefront on its own, in the order of apm_grad_finalize_kernel.
-template <bool GATHER>
-__device__ __forceinline__ double page_sum(const PageRec& rec, int n_tiles, int lane) {
+// A page's sum by one wavefront on its own, in the order of apm_grad_finalize_kernel.  needless() is asked
+// before every tile: if it says yes, the page's scale has come after all.
+template <bool GATHER, class Needless>
+__device__ __forceinline__ double page_sum(const PageRec& rec, int n_tiles, int lane, Needless&& needless) {
     double s = 0.0;
 #pragma unroll 1
     for (int t = 0; t < n_tiles; ++t) {
+        if (needless()) return 0.0;
         const double x = tile_sum<GATHER>(rec, t, lane);
         if ((t & (kWave - 1)) == lane) s += x;
     }
@@ -975,7 +977,7 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c,
             }
             if (t + lane < n_tiles) s += __longlong_as_double((long long)v);
         }
-        s = all ? wave_sum_f64(s) : page_sum<GATHER>(rec, n_tiles, lane);
+        s = all ? wave_sum_f64(s) : page_sum<GATHER>(rec, n_tiles, lane, [] { return false; });
         const double norm = sqrt(s);
         if (lane != 0) return;
         __hip_atomic_store(word, __float_as_uint(clip_scale(norm, c.max_norm)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -988,11 +990,14 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c,
     if (start >= ((rec.used + 7) & ~7)) return;
     // called when the slice's loads are under way: the first poll comes back with them
     auto get_scale = [&]() -> float {
-        uint32_t seen = (uint32_t)__builtin_amdgcn_readfirstlane((int)poll32(word));
-        for (int polls = 0; seen == kNoScale; ++polls) {
-            if (polls >= c.wait_limit) return clip_scale(sqrt(page_sum<GATHER>(rec, n_tiles, lane)), c.max_norm);
+        uint32_t seen = kNoScale;
+        auto look = [&] { return (seen = (uint32_t)__builtin_amdgcn_readfirstlane((int)poll32(word))) != kNoScale; };
+        for (int polls = 0; !look(); ++polls) {
+            if (polls >= c.wait_limit) {
+                const double s = page_sum<GATHER>(rec, n_tiles, lane, [&] { return c.wait_limit > 0 && look(); });
+                return seen == kNoScale ? clip_scale(sqrt(s), c.max_norm) : __uint_as_float(seen);
+            }
             __builtin_amdgcn_s_sleep(2);
-            seen = (uint32_t)__builtin_amdgcn_readfirstlane((int)poll32(word));
         }
         return __uint_as_float(seen);
     };
@@ -1363,8 +1368,9 @@ hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {
         c.grad_norm = L.grad_norm;
         c.skip_mask = L.skip_mask;
         c.max_norm = L.max_norm;
-        c.wait_limit = L.wait_limit;
         c.n_tiles = (int32_t)((max_used + kReduceTile - 1) / kReduceTile);
+        // a page's sums are added up 64 at a time, a round trip each
+        c.wait_limit = L.wait_limit + (int32_t)((int64_t)L.wait_limit * c.n_tiles / 4096);
         c.n_slices = (int32_t)((max_used + kTile<APM_UPDATE_U> - 1) / kTile<APM_UPDATE_U>);
         const int64_t items = c.n_tiles + 1 + c.n_slices;
         const int64_t piece = pages_per_launch(items, kUpdThreads, L.max_workgroups);

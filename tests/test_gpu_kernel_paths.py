@@ -468,8 +468,8 @@ def test_noalloc_step_over_nearly_empty_pages_equals_the_step(E, numels, clip, s
 
 
 def test_nearly_empty_pages_cost_the_noalloc_step_little():
-    """Two full pages of 2^20 elements and 60 nearly empty ones: four times the idle workgroups took 4.5 times the
-    two pages' time (larger slices 1.7; bound 3)."""
+    """Two full pages of 2^20 elements and 60 nearly empty ones: four times the idle workgroups took 6.6 times the
+    two pages' time (larger slices 2.2; bound 3)."""
     E, us = 1 << 20, []
     hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.0, 0)
     for empty in (0, 60):
@@ -534,3 +534,17 @@ def test_unused_pool_flags_do_not_change_the_update():
         us.append(_us(lambda: apm.apm_page_adamw_step(pool, None, n, 3, hyper, None, None), 10))
         pool.destroy()
     assert us[1] < 3 * us[0], us
+
+
+def test_wavefronts_that_stop_waiting_do_not_all_sum_the_whole_page():
+    """A wait that ends after one look, large pages: wavefronts of a clipped update sum their page by themselves
+    only until its scale is there, 16 times the update's time; each summing the whole page, 58 times (bound 35)."""
+    E, n, us = 1 << 24, 4, []
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 1.0, 0)
+    for limit in (4096, 1):
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n)
+        assert apm.lib().apm_test_set_wait_limit(ctypes.c_void_p(pool.handle), limit) == 0
+        apm.lib().apm_pool_set_layout(pool.handle, apm.make_tensors([n * E], apm.APM_F32, [0]), 1, None, None, None, None, None)
+        us.append(_us(lambda: apm.apm_page_adamw_step(pool, None, n, 3, hyper, None, None), 5))
+        pool.destroy()
+    assert us[1] < 35 * us[0], us
