@@ -20,6 +20,8 @@
  *     from one thread at a time and, unless stated, be ordered by the caller's streams: the pool's
  *     internal scratch is shared by its calls.
  *   - Element counts are in elements, never bytes, unless the name says bytes.
+ *   - Calls put tables of the installed layout into what they enqueue.  A HIP graph that captured any of them
+ *     must not be replayed after the pool has got another layout or was destroyed.
  */
 #ifndef APM_H
 #define APM_H
@@ -180,8 +182,15 @@ int apm_pool_set_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, ap
 
 enum apm_kernel_class { APM_K_REDUCE = 0, APM_K_UPDATE = 1, APM_K_SEGCOPY = 2, APM_N_KERNEL_CLASSES = 3 };
 
-/* While enabled, every kernel the pool's calls launch (apm_page_adamw_step, apm_pack_tensors,
- * apm_unpack) is bracketed by a pair of HIP events on the stream it is launched on. */
+/* While enabled, the kernels that move the data of the pool's calls (apm_page_adamw_step and _fused,
+ * apm_step_delayed's update, apm_pack_tensors, apm_unpack) are bracketed by pairs of HIP events on the stream
+ * they are launched on:
+ *   APM_K_REDUCE   passes over the gradient in front of the update: norms and skip decisions.  A step that
+ *                  works its norms out in the update's own grid has none (clipping or norms without skipping,
+ *                  pages of 4096 elements and more, or few pages); they count as update then
+ *   APM_K_UPDATE   the update, one entry a step
+ *   APM_K_SEGCOPY  pack / unpack
+ * Kernels that only write a record per page, and the delayed hand-over's copy, are not. */
 int apm_pool_set_timing(apm_pool* pool, int enable);
 
 /* Waits for the recorded events, adds the elapsed milliseconds per kernel class into

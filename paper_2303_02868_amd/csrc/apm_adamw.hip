@@ -4,7 +4,9 @@
 //   apm_page_recs_kernel      the page records when no reduce pass is needed
 //   apm_stage_kernel          the same from a call's page list and tensor addresses
 //   apm_adamw_kernel          the fused update (optionally gathering g16 from / scattering p16 to
-//                             the caller's tensors), one workgroup per page slice
+//                             the caller's tensors), one workgroup per page slice;
+//                             apm_adamw_run_kernel the same over consecutive pages of the classes
+//   apm_adamw_live_kernel     the same over the pages that the finalize pass did not skip
 //   apm_adamw_clip_kernel     norms, clip scales and the update in one grid
 //   apm_adamw_stride_kernel   the same slice body run by a fixed, small number of wavefronts that
 //                             stride over all slices (fp32 classes in host memory across PCIe)
@@ -15,8 +17,8 @@
 // (1 KiB for the 128-bit fp32 accesses, 512 B for the 64-bit bf16 accesses), each lane keeps
 // several independent loads in flight, and a workgroup never straddles a page.
 //
-// Work decomposition: grid.y walks the listed pages, grid.x the fixed-size slices of a page;
-// slices that start beyond the page's used extent exit at once.  The page table (`used`) is read
+// Work decomposition: grid.y walks the listed pages, grid.x the fixed-size slices of a page (the live and
+// clip kernels lay both out along grid.x); slices that start beyond the page's used extent exit at once.  The page table (`used`) is read
 // on the device; the host, which knows the extents from the layout, only sizes the grids (pages
 // grouped into extent classes) so that few workgroups are launched for nothing.
 #include <cstring>
@@ -61,7 +63,7 @@ __device__ __forceinline__ float bf16hi(uint32_t w) { return __uint_as_float(w &
 __device__ __forceinline__ uint32_t f32_to_bf16_rne(float x) {
     const uint32_t u = __float_as_uint(x);
     // both forms are computed and one is selected: a branch here would split the update kernel's
-    // body into basic blocks (see slice_body)
+    // body into basic blocks (see full_slice)
     const uint32_t nan = (u >> 16) | 0x0040u;
     const uint32_t rne = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
     return (u & 0x7FFFFFFFu) > 0x7F800000u ? nan : rne;

@@ -76,8 +76,11 @@ int group_by_extent(int64_t n, int64_t E, const int32_t* size, int64_t* order, E
         sum[c] += u;
         if (u > mx[c]) mx[c] = u;
     }
-    // A class is worth its extra launches only if it saves enough idle workgroups (counted in
-    // 1024-element slices); otherwise it is folded into the next larger one.
+    // A class is worth its extra launches only if it saves enough idle workgroups; otherwise it is folded
+    // into the next larger one.  Counted in spans of 1024 elements, four workgroups of the update or half a
+    // copy's; from and to tensors, us a call with the line at 2048 / 4096 / 16384 / 65536 spans: 4.8 M elements in
+    // 64 K pages with clipping 41 / 33 / 33 / 33, in 256 K pages 30 / 30 / 28 / 28, in 1 M pages 32 / 32 / 32 / 53;
+    // 124 M 537 / 537 / 538 / 544; 350 M 1520 / 1518 / 1529 / 1555; packing 122 M 87 / 87 / 85 / 86.
     int into[kMaxExtentClasses];
     for (int c = 0; c < kMaxExtentClasses; ++c) into[c] = c;
     constexpr int64_t kSpan = 1024, kWorthWorkgroups = 16384;

@@ -381,7 +381,8 @@ struct apm_pool {
 };
 
 namespace apm {
-// Validates a page list and enqueues the two kernels of one step.  g16_override != nullptr
+// Validates a page list and enqueues the kernels of one step: what brings the call's list and addresses to
+// the device, the passes over the gradient, and the update, or the last two in one grid.  g16_override != nullptr
 // replaces the pool's G16 region as the gradient source; page_sums / page_nzflags: its tiles' sums
 // and flags, indexed by page, if they are known.
 int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t step,

@@ -283,7 +283,7 @@ int plan_of(const apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan* ou
     return make_plan(pool->desc.page_elems, numels.data(), n, out);
 }
 
-// Shared body of pack (to_pages) and unpack: one descriptor per segment, one kernel.
+// Shared body of pack (to_pages) and unpack: the layout's segments, long and short ones launched apart.
 int move_segments(apm_pool* pool, int state, const apm_tensor* tensors, int64_t n, bool to_pages,
                   hipStream_t s) {
     const int eb = elem_bytes(state);

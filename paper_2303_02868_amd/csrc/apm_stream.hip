@@ -898,7 +898,7 @@ extern "C" int apm_streamer_step_scheduled(apm_streamer* s, const apm_task* task
         L.m32 = s->stage[1];
         L.v32 = s->stage[2];
         L.recs = dev->d_recs;
-    L.live = dev->d_live;
+        L.live = dev->d_live;
         const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
         if (need_reduce) {
             L.partials = dev->d_partials;
