@@ -3,7 +3,7 @@
 
 Resident leg (the headline `value`): a step is one pass of the whole path over one batch of
 synthetic gradients,
-  per-page grad reduce -> fused page AdamW, both reading g16 from the gradient tensors, p16
+  per-page norms and fused page AdamW, both reading g16 from the gradient tensors, p16
   written to the parameter tensors (`--unfused`: separate pack g16 / unpack p16 kernels),
 with the pool and the packing plan set up once (the method pre-allocates them) and every input
 resident in HBM before the timed region.
@@ -1135,9 +1135,11 @@ def main():
         out["value"] = r["elems_update"] * args.steps / r["wall"]
         out["ms_per_step"] = r["wall"] * 1e3 / args.steps
         out["config"]["step"] = ("reduce+update on resident pages" if args.update_only else
-                                 "grad reduce + fused AdamW, both reading g16 from the tensors; p16 written to "
+                                 "norms + AdamW in one kernel, reading g16 from and writing p16 to the tensors "
+                                 "(pack/unpack fused into it)" if fused and clip > 0 and not skip else
+                                 "grad reduce (if pages are skipped) + fused AdamW, reading g16 from and writing p16 to "
                                  "the tensors (pack/unpack fused into the kernels)" if fused else
-                                 "pack_g16 + reduce + update + unpack_p16 (separate kernels)")
+                                 "pack_g16 + norms and update + unpack_p16 (separate kernels)")
         if fused:   # the same step with separate pack / unpack kernels, for comparison
             r2 = resident_leg(args, wl, pool, hyper, n_pages, False, max(3, args.steps // 4), 1, r["next_step"])
             out["unfused_step"] = {"ms_per_step": r2["wall"] * 1e3 / max(3, args.steps // 4),
@@ -1152,9 +1154,10 @@ def main():
                     traffic = float(line.split("=", 1)[1])
         out["hbm_GBps_update_kernel"] = r["achieved"]
         out["hbm_frac_of_peak"] = r["achieved"] / HBM_PEAK_GBPS
-        out["roofline"] = {"bound": "hbm", "kernel": "apm_adamw_clip_kernel" if clip > 0 else "apm_adamw_kernel",
+        # the update's form: over the pages that are not skipped, with the norms in its grid, or plain
+        out["roofline"] = {"bound": "hbm", "kernel": "apm_adamw_live_kernel" if skip else "apm_adamw_clip_kernel" if clip > 0 else "apm_adamw_kernel",
                            "achieved": r["achieved"], "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": r["achieved"] / HBM_PEAK_GBPS,
-                           "traffic": traffic,
+                           "traffic": traffic,   # between the L2s and the fabric, per step: a gradient read twice counts twice
                            "algorithmic_bytes_per_launch": r["elems_update"] * BYTES_UPDATE,
                            "avg_launch_ms": r["upd_ms"]}
         out["kernels"] = r["kernels"]
