@@ -1213,11 +1213,10 @@ hipError_t launch_prepare(const AdamwLaunch& L, hipStream_t s) {
     return hipGetLastError();
 }
 
-int64_t stage_launches(const StageCall& c, int64_t n_listed) {
-    const int64_t n_list = c.list ? n_listed : 0, lists = (c.g_ptrs != nullptr) + (c.q_ptrs != nullptr);
-    if (n_list + lists * c.n_tensors <= kArgWords) return 1;
+int64_t stage_launches(int64_t n_list, int64_t lists, int64_t n_tensors) {
+    if (n_list + lists * n_tensors <= kArgWords) return 1;
     const int64_t per = lists ? kArgWords / lists : kArgWords;
-    return (n_list + kArgWords - 1) / kArgWords + (lists ? (c.n_tensors + per - 1) / per : 0);
+    return (n_list + kArgWords - 1) / kArgWords + (lists ? (n_tensors + per - 1) / per : 0);
 }
 
 hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s) {
@@ -1250,7 +1249,7 @@ hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s)
         a.sums = nullptr;  // marked by the first launch
         return hipGetLastError();
     };
-    if (c.d_words || stage_launches(c, L.n_listed) == 1) return go(0, n_list, 0, n_t);
+    if (c.d_words || stage_launches(n_list, has_g + has_q, n_t) == 1) return go(0, n_list, 0, n_t);
     // list words first: the launches with the addresses read the list that they wrote
     for (int64_t k = 0; k < n_list; k += kArgWords) {
         hipError_t e = go(k, n_list - k < kArgWords ? n_list - k : kArgWords, 0, 0);

@@ -216,8 +216,9 @@ struct StageCall {
     int32_t* d_out;
     const uint64_t* d_words;      // list, g_ptrs, q_ptrs one after the other in device memory, or nullptr
 };
-// Launches it takes to carry a call's words in kernel arguments (StageCall::d_words == nullptr).
-int64_t stage_launches(const StageCall& c, int64_t n_listed);
+// Launches it takes to carry a call's words in kernel arguments (StageCall::d_words == nullptr): n_list list
+// words and `lists` (0..2) lists of n_tensors addresses.
+int64_t stage_launches(int64_t n_list, int64_t lists, int64_t n_tensors);
 hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s);
 hipError_t launch_adamw(const AdamwLaunch& a, hipStream_t s);
 // Norms, clip scales and update in one kernel, after the stage / prepare pass of a launch with

@@ -142,7 +142,13 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     StageCall sc{};
     const int64_t n_list = run || whole ? 0 : n_pages;
     const int64_t n_g = grad_tensors ? n_tensors : 0, n_q = p16_tensors ? n_tensors : 0;
-    std::vector<uint64_t> words((size_t)(n_list + n_g + n_q));
+    int ring_slot = -1;
+    const bool by_ring = stage_launches(n_list, (n_g > 0) + (n_q > 0), tensors ? n_tensors : 0) > kMaxStageLaunches;
+    // A list alone that goes through the ring is read there by the step's kernels: no stage kernel.
+    const bool staged = tensors || (n_list > 0 && !by_ring);
+    const int64_t* d_list = whole ? pool->d_order : pool->d_list;
+    const int32_t* d_out = whole ? pool->d_order_out : pool->d_list_out;
+    std::vector<uint64_t> words(staged ? (size_t)(n_list + n_g + n_q) : 0);
     sc.list = n_list ? words.data() : nullptr;
     sc.g_ptrs = n_g ? words.data() + n_list : nullptr;
     sc.q_ptrs = n_q ? words.data() + n_list + n_g : nullptr;
@@ -150,12 +156,6 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     sc.tenants = pool->d_tenants;
     sc.d_list = pool->d_list;
     sc.d_out = pool->d_list_out;
-    int ring_slot = -1;
-    const bool by_ring = stage_launches(sc, n_pages) > kMaxStageLaunches;
-    // A list alone that goes through the ring is read there by the step's kernels: no stage kernel.
-    const bool staged = tensors || (n_list > 0 && !by_ring);
-    const int64_t* d_list = whole ? pool->d_order : pool->d_list;
-    const int32_t* d_out = whole ? pool->d_order_out : pool->d_list_out;
     if (staged) {
         for (int64_t k = 0; k < n_list; ++k)
             words[(size_t)k] = (uint64_t)page_at(order[(size_t)k]) | (uint64_t)order[(size_t)k] << 32;
