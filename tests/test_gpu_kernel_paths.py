@@ -548,3 +548,53 @@ def test_wavefronts_that_stop_waiting_do_not_all_sum_the_whole_page():
         us.append(_us(lambda: apm.apm_page_adamw_step(pool, None, n, 3, hyper, None, None), 5))
         pool.destroy()
     assert us[1] < 35 * us[0], us
+
+
+@pytest.mark.parametrize("clip,skip", [(0.0, 0), (0.05, 0), (0.05, 1)])
+@pytest.mark.parametrize("E,numels", [(8, [5, 8, 3] * 9), (512, [300] * 5000), (1 << 20, [(1 << 20) * 2 + 77, 100, 1 << 20, 5]), (1 << 19, [9] * 6)])
+def test_noalloc_step_in_a_replayed_graph_equals_the_eager_call(E, numels, clip, skip):
+    """Every form of the step that may be captured (plain, passes, one grid, noted pages, larger slices): each of
+    several replays, with eager work and new gradients between them, gives the eager call's bits."""
+    n_t, off = len(numels), [0]
+    for m in numels:
+        off.append(off[-1] + (m + 7) // 8 * 8)
+    gen = torch.Generator(device=DEV).manual_seed(E)
+    p0 = torch.randn(off[-1], device=DEV, generator=gen) * 0.02
+    lst = lambda t: apm.make_tensors(numels, apm.APM_F32 if t.dtype == torch.float32 else apm.APM_BF16,  # noqa: E731
+                                     [t.data_ptr() + t.element_size() * o for o in off[:-1]])
+    n = oracle.plan_pack(numels, E).n_pages
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, clip, skip)
+    pools = [apm.apm_pool_create(apm.APM_DEV_GPU, E, n) for _ in range(2)]
+    norm = [torch.full((n,), -1.0, device=DEV) for _ in range(2)]
+    outs = [t if clip else None for t in norm]
+
+    def gradients():
+        g = (torch.randn(off[-1], device=DEV, generator=gen) * 1e-2).bfloat16()
+        g[off[1]:off[2]] = 0
+        for pool in pools:
+            apm.apm_pack_tensors(pool, apm.APM_G16, lst(g), n_t)
+        torch.cuda.synchronize()
+    for pool in pools:
+        apm.apm_pack_tensors(pool, apm.APM_P32, lst(p0), n_t)
+    gradients()
+    for pool, out in zip(pools, outs):
+        apm.apm_page_adamw_step_noalloc(pool, n, 2, hyper, out, None)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        apm.apm_page_adamw_step_noalloc(pools[1], n, 3, hyper, outs[1], None, torch.cuda.current_stream())
+    for _ in range(4):
+        gradients()
+        apm.apm_page_adamw_step_noalloc(pools[0], n, 3, hyper, outs[0], None)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(norm[0], norm[1])
+        for st in (apm.APM_P32, apm.APM_M32, apm.APM_V32, apm.APM_P16):
+            got = [torch.zeros(off[-1], device=DEV, dtype=torch.float32 if st < 3 else torch.bfloat16) for _ in range(2)]
+            for pool, t in zip(pools, got):
+                apm.apm_unpack(pool, st, lst(t), n_t)
+            torch.cuda.synchronize()
+            assert torch.equal(*got)
+    for pool in pools:
+        pool.destroy()
