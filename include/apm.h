@@ -187,7 +187,7 @@ enum apm_kernel_class { APM_K_REDUCE = 0, APM_K_UPDATE = 1, APM_K_SEGCOPY = 2, A
  * they are launched on:
  *   APM_K_REDUCE   passes over the gradient in front of the update: norms and skip decisions.  A step that
  *                  works its norms out in the update's own grid has none (clipping or norms without skipping,
- *                  pages of 4096 elements and more, or few pages); they count as update then
+ *                  pages with 4096 used elements and more on average, or few pages); they count as update then
  *   APM_K_UPDATE   the update, one entry a step
  *   APM_K_SEGCOPY  pack / unpack
  * Kernels that only write a record per page, and the delayed hand-over's copy, are not. */
@@ -262,7 +262,7 @@ int apm_page_adamw_step_fused(apm_pool* pool, const int64_t* pages, int64_t n_pa
  * apm_page_adamw_step for callers that cannot allocate: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same kernels and bit-identical results for the pages
  * [0, n_pages) of a GPU pool that stores all five classes (no page list; every page is launched
- * with a full page's grid, so nearly empty pages cost idle workgroups here).  The per-page scratch
+ * with the largest page's grid, so nearly empty pages cost idle workgroups here).  The per-page scratch
  * of the reduce and update kernels (page records, per-slice sums of squares and non-zero flags)
  * lives in a fixed device array of apm_noalloc_scratch_bytes() bytes that the library holds on
  * every GPU it runs on until the process ends, instead of buffers the pool allocates on first use;

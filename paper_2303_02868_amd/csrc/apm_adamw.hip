@@ -100,7 +100,7 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float x) {
 // with clipping 14.3 / 13.9, 18.8 / 18.2, 45.2 / 45.5).
 constexpr int64_t kFewElems = (int64_t)24 << 20, kFewRunElems = (int64_t)2 << 20;
 constexpr int kFewLds = 9216;
-constexpr int kWideU = 4, kWideLds = 32768;
+constexpr int kWideU = 4;  // see wide_pays
 unsigned update_lds(bool tensors, int64_t elems, unsigned lds) { return elems <= (tensors ? kFewElems : kFewRunElems) ? kFewLds : lds; }
 
 // When pages may be skipped on the device (APM_SKIP_UNTOUCHED) the pages to update are known only there.
@@ -1297,8 +1297,10 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         const ExtentClass all{0, L.n_listed, L.E, L.n_listed * L.E};
         const ExtentClass* cls = L.n_cls > 0 ? L.cls : &all;
         const int n_cls = L.n_cls > 0 ? L.n_cls : 1;
+        const bool wide = run && L.wide;
+        const int tile = wide ? kTile<kWideU> : kTile<U>;
         for (int c = 0; c < n_cls; ++c) {
-            const int nx = (int)((cls[c].max_used + kTile<U> - 1) / kTile<U>);
+            const int nx = (int)((cls[c].max_used + tile - 1) / tile);
             if (nx == 0) continue;
             const int64_t slices = cls[c].count * nx;
             int64_t wgs = (slices + kSkipSpread - 1) / kSkipSpread;
@@ -1307,14 +1309,15 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
             if (wgs > cap) wgs = cap;  // each walks further
             const dim3 grid((unsigned)wgs), block(kUpdThreads);
             const int32_t *n_live = L.live + c, *positions = L.live + kMaxExtentClasses + cls[c].begin;
-#define APM_LAUNCH_LIVE(RUN, G, Q) hipLaunchKernelGGL((apm_adamw_live_kernel<U, RUN, G, Q>), grid, block, kSkipLds, s, n_live, positions, nx, \
+#define APM_LAUNCH_LIVE(U, RUN, G, Q) hipLaunchKernelGGL((apm_adamw_live_kernel<U, RUN, G, Q>), grid, block, kSkipLds, s, n_live, positions, nx, \
                                                      L.recs, state(L.p32, 0), state(L.m32, 0), state(L.v32, 0), run ? g16(0) : nullptr,  \
                                                      run ? p16(0) : nullptr, L.E, a)
-            if (run) APM_LAUNCH_LIVE(true, false, false);
-            else if (L.gather && L.scatter) APM_LAUNCH_LIVE(false, true, true);
-            else if (L.gather) APM_LAUNCH_LIVE(false, true, false);
-            else if (L.scatter) APM_LAUNCH_LIVE(false, false, true);
-            else APM_LAUNCH_LIVE(false, false, false);
+            if (wide) APM_LAUNCH_LIVE(kWideU, true, false, false);
+            else if (run) APM_LAUNCH_LIVE(U, true, false, false);
+            else if (L.gather && L.scatter) APM_LAUNCH_LIVE(U, false, true, true);
+            else if (L.gather) APM_LAUNCH_LIVE(U, false, true, false);
+            else if (L.scatter) APM_LAUNCH_LIVE(U, false, false, true);
+            else APM_LAUNCH_LIVE(U, false, false, false);
 #undef APM_LAUNCH_LIVE
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
@@ -1327,7 +1330,7 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         const int tile = wide ? kTile<kWideU> : kTile<U>;
         const dim3 grid((unsigned)((max_used + tile - 1) / tile), (unsigned)ny), block(kUpdThreads);
 #define APM_LAUNCH_UPDATE(G, Q) hipLaunchKernelGGL((apm_adamw_kernel<U, G, Q>), grid, block, lds, s, L.recs + begin, L.p32, L.m32, L.v32, a)
-        const unsigned lds = wide ? kWideLds : update_lds(L.gather || L.scatter, sum_used, APM_UPDATE_LDS);
+        const unsigned lds = update_lds(L.gather || L.scatter, sum_used, APM_UPDATE_LDS);
 #define APM_LAUNCH_RUN(U, BARE, RUNS) hipLaunchKernelGGL((apm_adamw_run_kernel<U, BARE>), grid, block, lds, s, RUNS, state(L.p32, begin), \
                                                          state(L.m32, begin), state(L.v32, begin), g16(begin), p16(begin), (int)L.E, a)
         if (wide && L.bare_run) APM_LAUNCH_RUN(kWideU, true, L.used + L.grad_first + begin);
@@ -1350,8 +1353,11 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
 //   8 M, consecutive                    91 / 71    67 / 60    54 / 52    48 / 49    46 / 48
 //   256 K, from and to tensors        12.8 / 14.7  12.3 / 14.8  11.7 / 14.7
 //   4096 pages of 256, reversed / from and to tensors   47.6 / 43.7, 21.4 / 20.3; 2048 of 512   31.7 / 34.7, 16.5 / 18.9
-bool one_pass_pays(int skip_mode, int64_t page_elems, int64_t staged_pages) {
-    return skip_mode == APM_SKIP_NONE && (page_elems >= 4096 || (staged_pages >= 0 && staged_pages <= 2048));
+// What counts is what the pages hold on average: 30 000 tensors of 300 elements alone in pages of 4096, 160 / 113.
+bool one_pass_pays(const AdamwLaunch& L, bool staged) {
+    int64_t elems = 0;
+    for (int c = 0; c < L.n_cls; ++c) elems += L.cls[c].sum_used;
+    return L.skip_mode == APM_SKIP_NONE && (elems >= 4096 * L.n_listed || (staged && L.n_listed <= 2048));
 }
 
 hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {

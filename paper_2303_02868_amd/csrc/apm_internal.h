@@ -224,9 +224,8 @@ hipError_t launch_adamw(const AdamwLaunch& a, hipStream_t s);
 // Norms, clip scales and update in one kernel, after the stage / prepare pass of a launch with
 // one_pass set; for skip_mode NONE and fp32 classes in device memory.
 hipError_t launch_clip_update(const AdamwLaunch& a, hipStream_t s);
-// Whether that is the better form for pages of page_elems elements.  staged_pages: pages of a launch whose
-// records a stage kernel writes, else -1.
-bool one_pass_pays(int skip_mode, int64_t page_elems, int64_t staged_pages);
+// Whether that is the better form; staged: a stage kernel writes the launch's records.
+bool one_pass_pays(const AdamwLaunch& a, bool staged);
 constexpr int32_t kWaitLimit = 4096;
 // Takes a gradient in page layout over into a buffered half: dst <- src, or (accumulate) dst <- dst + src, over
 // the used extents of the listed pages, and if `sums` is set works out the tiles' sums of squares and
@@ -392,8 +391,9 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
                  const apm_tensor* p16_tensors = nullptr, int64_t n_tensors = 0,
                  double* page_sums = nullptr, uint32_t* page_nzflags = nullptr);
 int ensure_scratch(apm_pool* pool, bool list = false);
-// AdamwLaunch::wide for pages [first, first + n) launched with a full page's grid each.
-bool wide_pays(const apm_pool* pool, int64_t first, int64_t n);
+// Pages [first, first + n) as one class, each launched with the grid of the layout's largest page.
+ExtentClass run_class(const apm_pool* pool, int64_t first, int64_t n);
+bool wide_pays(const ExtentClass& c);  // AdamwLaunch::wide for it
 // Allocates the ping-pong gradient halves, the events and the update stream of the delayed path.
 // caller != nullptr-able: the stream the producer works on; the update stream is chosen so that
 // its kernels run beside that stream's (see make_overlapping_stream).

@@ -105,15 +105,16 @@ extern "C" int apm_page_adamw_step_noalloc(apm_pool* pool, int64_t n_pages, int6
         L.p16 = static_cast<uint16_t*>(pool->base[APM_P16]);
         L.used = pool->d_used;
         L.n_listed = n_pages;  // pages [0, n_pages) in order: no list, no output permutation,
-        L.n_cls = 0;           // one launch geometry sized for full pages
+        L.n_cls = 1;           // one launch geometry sized for the largest page
+        L.cls[0] = run_class(pool, 0, n_pages);
         L.E = pool->desc.page_elems;
         L.S = pool->S;
         L.grad_norm = grad_norm;
         L.skip_mask = skip_mask;
         hipStream_t s = static_cast<hipStream_t>(stream);
         const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
-        L.wide = wide_pays(pool, 0, n_pages);
-        L.one_pass = need_reduce && !L.wide && one_pass_pays(L.skip_mode, L.E, -1);
+        L.wide = wide_pays(L.cls[0]);
+        L.one_pass = need_reduce && !L.wide && one_pass_pays(L, false);
         L.wait_limit = pool->wait_limit;
         if (!need_reduce) {
             L.partials = nullptr;

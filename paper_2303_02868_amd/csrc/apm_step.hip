@@ -58,13 +58,20 @@ int group_pages(const apm_pool* pool, const int64_t* pages, int64_t n, int64_t* 
 // A workgroup that finds nothing to do costs 0.2 ns, hidden behind the others' work if they are not too many in a row.
 // Slices of four vectors per lane are a quarter as many, but move a few percent less (us a call, 64 full pages
 // and as many nearly empty ones as stated, with norms, one vector in one grid / four as passes; in brackets
-// without norms; 1 M elements a page, none 298 / 318 (289 / 292), 150 % 329 / 325 (303 / 297), 400 % 440 / 339
-// (395 / 301); 128 K elements a page, 400 % 57 / 60 (43 / 49), 1000 % 91 / 85 (79 / 66)).
-bool wide_pays(const apm_pool* pool, int64_t first, int64_t n) {
-    const int64_t E = pool->desc.page_elems, in_use = (int64_t)pool->used_sum.size() - 1;
-    auto upto = [&](int64_t k) { return in_use < 0 ? 0 : pool->used_sum[(size_t)(k < in_use ? k : in_use)]; };
-    const int64_t used = upto(first + n) - upto(first), idle = n * E - used;
-    return E >= 4096 && (E >= (int64_t)1 << 19 ? 2 * idle > 3 * used : idle > 4 * used);
+// without norms; 1 M elements a page, none 298 / 318 (289 / 292), 150 % 329 / 331 (303 / 300), 400 % 440 / 332
+// (395 / 298); 128 K elements a page, 400 % 57 / 57 (43 / 43), 1000 % 91 / 66 (79 / 49)).  Skipping: 1000 nearly empty
+// and 4 full pages of 1 M elements 336 / 148, 10 000 and 100 of 16 K 111 / 74.
+bool wide_pays(const ExtentClass& c) {
+    const int64_t idle = c.count * c.max_used - c.sum_used;
+    return c.max_used >= 4096 && (c.max_used >= (int64_t)1 << 19 ? 2 * idle > 3 * c.sum_used : idle > 4 * c.sum_used);
+}
+
+// (30 000 tensors of 300 elements in pages of 8192 without a list: 622 us a call with a full page's grid each, 125
+// with the largest page's; skipping 577 and 132.)
+ExtentClass run_class(const apm_pool* pool, int64_t first, int64_t n) {
+    const int64_t in_use = (int64_t)pool->used_sum.size() - 1;
+    auto upto = [&](int64_t k) { return in_use < 0 ? (int64_t)0 : pool->used_sum[(size_t)(k < in_use ? k : in_use)]; };
+    return ExtentClass{0, n, pool->order_n_cls > 0 ? pool->order_cls[0].max_used : 0, upto(first + n) - upto(first)};
 }
 
 namespace {
@@ -206,7 +213,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     L.recs = pool->d_recs;
     L.live = pool->d_live;
     L.sums_ready = need_reduce && page_sums;
-    L.one_pass = need_reduce && !page_sums && one_pass_pays(L.skip_mode, E, staged ? n_pages : -1);
+    L.one_pass = need_reduce && !page_sums && one_pass_pays(L, staged);
     L.wait_limit = pool->wait_limit;
     L.max_workgroups = pool->max_workgroups;
     if (need_reduce) {

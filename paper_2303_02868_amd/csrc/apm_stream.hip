@@ -378,7 +378,9 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
                 C.partials = L.partials + first * L.S;
                 C.nzflags = L.nzflags + first * L.S;
             }
-            C.wide = wide_pays(dev, first, n);
+            C.n_cls = 1;
+            C.cls[0] = run_class(dev, first, n);
+            C.wide = wide_pays(C.cls[0]);
             C.state_first = part == 0 ? first : first - H0;
             C.grad_first = first;
             C.n_listed = n;
@@ -437,7 +439,9 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
         C.p32 = static_cast<float*>(s->cache->base[APM_P32]);
         C.m32 = static_cast<float*>(s->cache->base[APM_M32]);
         C.v32 = static_cast<float*>(s->cache->base[APM_V32]);
-        C.wide = wide_pays(dev, r_done, nr);
+        C.n_cls = 1;
+        C.cls[0] = run_class(dev, r_done, nr);
+        C.wide = wide_pays(C.cls[0]);
         C.state_first = C.grad_first = r_done;
         C.n_listed = nr;
         C.grad_norm = grad_norm ? grad_norm + r_done : nullptr;
@@ -463,7 +467,9 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
         L.state_first = (int64_t)slot * s->B;
         L.grad_first = first;
         L.n_listed = nb;
-        L.wide = wide_pays(dev, first, nb);
+        L.n_cls = 1;
+        L.cls[0] = run_class(dev, first, nb);
+        L.wide = wide_pays(L.cls[0]);
         L.grad_norm = grad_norm ? grad_norm + first : nullptr;
         L.skip_mask = skip_mask ? skip_mask + first : nullptr;
         if (what & kDoUpdate) {
@@ -928,6 +934,8 @@ extern "C" int apm_streamer_step_scheduled(apm_streamer* s, const apm_task* task
                 C.state_pages = d_slots + first;
                 C.grad_first = first;
                 C.n_listed = n;
+                C.n_cls = 1;
+                C.cls[0] = run_class(dev, first, n);
                 C.grad_norm = grad_norm ? grad_norm + first : nullptr;
                 C.skip_mask = skip_mask ? skip_mask + first : nullptr;
                 if (need_reduce) APM_HIP(launch_grad_reduce(C, s->s_cmp));

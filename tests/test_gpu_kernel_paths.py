@@ -598,3 +598,19 @@ def test_noalloc_step_in_a_replayed_graph_equals_the_eager_call(E, numels, clip,
             assert torch.equal(*got)
     for pool in pools:
         pool.destroy()
+
+
+@pytest.mark.parametrize("skip", [0, 1])
+def test_a_small_tensor_alone_in_its_page_costs_the_steps_little(skip):
+    """30000 tensors of 300 elements in pages of 8192, every norm wanted: neither the step that launches all pages
+    alike (a full page's grid each: 4.5 times the other step's time) nor three wavefronts a page in one grid."""
+    E, n, us = 8192, 30000, []
+    pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n)
+    apm.lib().apm_pool_set_layout(pool.handle, apm.make_tensors([300] * n, apm.APM_F32, [0] * n), n, None, None, None, None, None)
+    torch.as_tensor(_Region(pool, apm.APM_G16, n * E), device=DEV).view(n, E)[:, :300] = 0x3a00
+    norm = torch.zeros(n, device=DEV)
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.0, skip)
+    us.append(_us(lambda: apm.apm_page_adamw_step(pool, None, n, 3, hyper, norm, None), 20))
+    us.append(_us(lambda: apm.apm_page_adamw_step_noalloc(pool, n, 3, hyper, norm, None), 20))
+    pool.destroy()
+    assert us[1] < 2 * us[0], us
