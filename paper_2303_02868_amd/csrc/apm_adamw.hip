@@ -527,15 +527,24 @@ template <int U> constexpr int kTile = kUpdThreads * 4 * U;  // elements per wav
 
 // The vectors of a slice that lies inside one tenant (all slices of a page but the last one or two) go
 // through buffer accesses: the five streams' addresses are scalar (a descriptor each, made from the
-// page record), the lanes share one 32-bit offset, and the cache policy is an operand.  The policy is
-// non-temporal, or -- WT, for stores of state in host memory while other kernels run on the GPU --
-// written through at system scope: a non-temporal store to host memory may rest in the L2 as a dirty
-// line; the write-back that ends every kernel of any other stream then has to push it across PCIe,
-// so those kernels pay for this kernel's writes.
+// page record), the lanes share one 32-bit offset, and the cache policy is an operand: of the loads
+// non-temporal, of the state's stores
+//   kStoreHbm   non-temporal and written through, for state in device memory.  Non-temporal alone leaves the
+//               lines in the L2 until they are evicted, in another order than the slices': 201 M parameters
+//               876 us a call without, 868 with; with clipping 907 and 892 (written through alone: 867, but
+//               with clipping 946);
+//   kStoreHost  non-temporal, for state in host memory;
+//   kStoreHostWT  written through, for the same while other kernels run on the GPU: a non-temporal store
+//               to host memory may rest in the L2 as a dirty line; the write-back that ends every kernel of any
+//               other stream then has to push it across PCIe, so those kernels pay for this kernel's writes.
+// Gradients are read with the default policy when the state is in device memory: a slice of a tensor that does not
+// start on a cache line shares its first and last line with its neighbours, and with clipping g is read a second time
+// (213 M parameters in tensors of odd sizes: 957 us non-temporal, 943 default; with clipping 987 and 967).
 // (As an operand because the compiler drops the hint of its non-temporal builtin from stores that it
 // merges or moves between this body and the checked one below: 124 M parameters 599 us a call without
 // the hint at one vector per lane, 548 with it.)
 constexpr int kNT = 2, kSC1 = 16;
+constexpr int kStoreHbm = kNT | kSC1, kStoreHost = kNT, kStoreHostWT = kSC1;
 typedef __amdgpu_buffer_rsrc_t Rsrc;
 
 // [base, base + bytes): accesses beyond it read zero / are dropped.
@@ -551,7 +560,7 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 // target loads and stores share one counter, and at the entry of a basic block the compiler must
 // assume the worst about what is outstanding.
 // get_scale() is called when the loads are under way.
-template <int U, bool WT, class GetScale>
+template <int U, int STORE, class GetScale>
 __device__ __forceinline__ void full_slice(const UpdateArgs& a, GetScale&& get_scale, int lane, float* p_, float* m_, float* v_,
                                            const uint16_t* g_, uint16_t* q_) {
     const Rsrc P = make_rsrc(p_, kTile<U> * 4), M = make_rsrc(m_, kTile<U> * 4), V = make_rsrc(v_, kTile<U> * 4);
@@ -561,7 +570,7 @@ __device__ __forceinline__ void full_slice(const UpdateArgs& a, GetScale&& get_s
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int o = lane * 16 + u * (kWave * 16);
-        g[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(G, lane * 8 + u * (kWave * 8), 0, kNT));
+        g[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(G, lane * 8 + u * (kWave * 8), 0, STORE == kStoreHbm ? 0 : kNT));
         p[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(P, o, 0, kNT));
         m[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(M, o, 0, kNT));
         v[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(V, o, 0, kNT));
@@ -570,7 +579,6 @@ __device__ __forceinline__ void full_slice(const UpdateArgs& a, GetScale&& get_s
     // save registers
     __builtin_amdgcn_sched_barrier(0);
     const float scale = get_scale();
-    constexpr int kPolicy = WT ? kSC1 : kNT;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int o = lane * 16 + u * (kWave * 16);
@@ -584,26 +592,26 @@ __device__ __forceinline__ void full_slice(const UpdateArgs& a, GetScale&& get_s
             v[u][j] = vj;
         }
         const u32x2 q = {pack_bf16(p[u][0], p[u][1]), pack_bf16(p[u][2], p[u][3])};
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, p[u]), P, o, 0, kPolicy);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, m[u]), M, o, 0, kPolicy);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[u]), V, o, 0, kPolicy);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, p[u]), P, o, 0, STORE);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, m[u]), M, o, 0, STORE);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[u]), V, o, 0, STORE);
         __builtin_amdgcn_raw_buffer_store_b64(q, Q, lane * 8 + u * (kWave * 8), 0, kNT);
     }
 }
 
-// A store of fp32 state outside the body above (same policies).  The write-through form is
+// A store of fp32 state outside the body above (slices that are few: written through, or non-temporal).  The write-through form is
 // hand-written because no builtin takes that policy for a 128-bit global store; the wait states keep
 // the next instruction off the data registers, which a store of more than 64 bits still reads right
 // after issue (the compiler does that for its own stores, not for this one).
-template <bool WT>
+template <int STORE>
 __device__ __forceinline__ void store_state(f32x4 x, f32x4* q) {
-    if (WT) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(q), "v"(x) : "memory");
+    if (STORE == kStoreHostWT) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(q), "v"(x) : "memory");
     else __builtin_nontemporal_store(x, q);
 }
 
 // A slice that a tenant's end or the page's used extent cuts: one vector at a time, each checked against
 // the used extent; with GATHER / SCATTER g is gathered / p16 scattered lane by lane through the tenants.
-template <int U, bool GATHER, bool SCATTER, bool WT>
+template <int U, bool GATHER, bool SCATTER, int STORE>
 __device__ __forceinline__ void cut_slice(const UpdateArgs& a, const PageRec& rec, int v0, float* p_, float* m_, float* v_) {
     f32x4* P = reinterpret_cast<f32x4*>(p_);
     f32x4* M = reinterpret_cast<f32x4*>(m_);
@@ -631,9 +639,9 @@ __device__ __forceinline__ void cut_slice(const UpdateArgs& a, const PageRec& re
             v[j] = vj;
         }
         const u32x2 q = {pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3])};
-        store_state<WT>(p, P + vi);
-        store_state<WT>(m, M + vi);
-        store_state<WT>(v, V + vi);
+        store_state<STORE>(p, P + vi);
+        store_state<STORE>(m, M + vi);
+        store_state<STORE>(v, V + vi);
         if (SCATTER) scatter_q4(rec, vi << 2, q);
         else __builtin_nontemporal_store(q, Q + vi);
     }
@@ -643,13 +651,13 @@ __device__ __forceinline__ void cut_slice(const UpdateArgs& a, const PageRec& re
 // 12 B + 2 B read and 12 B + 2 B written per element.  Each lane keeps U 128-bit vectors per
 // fp32 class in flight; every wavefront-wide access is one contiguous 1 KiB (fp32) or 512 B (bf16)
 // span.  p, m, v: the page's first element.
-template <int U, bool GATHER, bool SCATTER, bool WT = false>
+template <int U, bool GATHER, bool SCATTER, int STORE = kStoreHbm>
 __device__ __forceinline__ void update_slice(const UpdateArgs& a, const PageRec& rec, int start, int lane,
                                              float* p, float* m, float* v) {
     const int k = start >= rec.off1 ? 1 : 0;
     if (start + kTile<U> <= rec.end[k])
-        full_slice<U, WT>(a, [&] { return rec.scale; }, lane, p + start, m + start, v + start, rec.g[k] + start, rec.q[k] + start);
-    else cut_slice<U, GATHER, SCATTER, WT>(a, rec, (start >> 2) + lane, p, m, v);
+        full_slice<U, STORE>(a, [&] { return rec.scale; }, lane, p + start, m + start, v + start, rec.g[k] + start, rec.q[k] + start);
+    else cut_slice<U, GATHER, SCATTER, STORE>(a, rec, (start >> 2) + lane, p, m, v);
 }
 
 typedef int i32x2 __attribute__((ext_vector_type(2)));
@@ -776,7 +784,7 @@ __global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(Str
             at = rec.pofs;
         }
         if (rec.scale < 0.0f || start >= rec.end[0]) continue;
-        update_slice<kStrideU, false, false, WT>(a, rec, start, lane, s.p32 + at, s.m32 + at, s.v32 + at);
+        update_slice<kStrideU, false, false, WT ? kStoreHostWT : kStoreHost>(a, rec, start, lane, s.p32 + at, s.m32 + at, s.v32 + at);
     }
 }
 
@@ -1006,10 +1014,10 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c,
     const int k = start >= rec.off1 ? 1 : 0;
     float *p = c.p32 + at, *m = c.m32 + at, *v = c.v32 + at;
     if (start + kTile<U> <= rec.end[k]) {
-        full_slice<U, false>(a, get_scale, lane, p + start, m + start, v + start, rec.g[k] + start, rec.q[k] + start);
+        full_slice<U, kStoreHbm>(a, get_scale, lane, p + start, m + start, v + start, rec.g[k] + start, rec.q[k] + start);
     } else {
         rec.scale = get_scale();
-        cut_slice<U, GATHER, SCATTER, false>(a, rec, (start >> 2) + lane, p, m, v);
+        cut_slice<U, GATHER, SCATTER, kStoreHbm>(a, rec, (start >> 2) + lane, p, m, v);
     }
 }
 
@@ -1036,7 +1044,7 @@ struct TakeArgsInline {
 // order of apm_grad_reduce_kernel, so that the update that follows does not read the gradient twice.
 // 355 M parameters with clipping, hand-over beside the update: 2041 us an iteration with copies of whole
 // pages and the sums worked out by the update, 1877 like this; 124 M, four micro-batches, no clipping: 1116
-// and 1030.  A workgroup then takes a tile; without, 8 elements per lane, the fastest form of a copy.
+// and 1030.  Stores written through as the state's are (355 M, hand-over beside the update: 1766 -> 1760 us).  A workgroup then takes a tile; without, 8 elements per lane, the fastest form of a copy.
 template <bool ACCUM, bool SUMS, class Args>
 __global__ __launch_bounds__(kThreads) void apm_grad_take_kernel(Args args) {
     const TakeArgs* ap;
@@ -1055,6 +1063,7 @@ __global__ __launch_bounds__(kThreads) void apm_grad_take_kernel(Args args) {
     if (start >= used8 && !(SUMS && blockIdx.x == 0)) return;
     const int end = min(start + kItem, used8);
     u32x4* dst = reinterpret_cast<u32x4*>(a.dst + page * a.E);
+    const Rsrc D = make_rsrc(a.dst + page * a.E + start, end > start ? (end - start) * 2 : 0);
     const u32x4* src = reinterpret_cast<const u32x4*>(a.src + page * a.E);
     double acc0 = 0.0, acc1 = 0.0;
     uint32_t nz = 0;
@@ -1082,7 +1091,7 @@ __global__ __launch_bounds__(kThreads) void apm_grad_take_kernel(Args args) {
                         x[u][j] = f32_to_bf16_rne(lo) | (f32_to_bf16_rne(hi) << 16);
                     }
                 }
-                __builtin_nontemporal_store(x[u], dst + (e >> 3));
+                __builtin_amdgcn_raw_buffer_store_b128(x[u], D, (e - start) * 2, 0, kStoreHbm);
             }
             if (SUMS) {
                 const int left = used - e;  // boundary vector: elements at or beyond the extent do not count
