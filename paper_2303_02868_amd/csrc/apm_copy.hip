@@ -1,10 +1,11 @@
 // Gather / scatter between contiguous tensors and page storage: the layout's segments, each inside
 // one page, copied bit for bit.  HBM-bound (read n + write n bytes).
 //
-// grid.y walks the segments, grid.x the fixed-size chunks of a segment; chunks beyond a segment's end
-// exit at once.  Every lane moves 128 bits with contiguous wavefront accesses, whatever the
+// One grid over the fixed-size chunks of all segments (GridMap: classes of segment lengths); chunks beyond a
+// segment's end exit at once.  Every lane moves 128 bits with contiguous wavefront accesses, whatever the
 // alignment of the two addresses (see apm_seg_copy_kernel).
 #include <cstring>
+#include <type_traits>
 #include "apm_internal.h"
 
 namespace apm {
@@ -12,115 +13,139 @@ namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-#ifndef APM_COPY_THREADS
-#define APM_COPY_THREADS 256
-#endif
-#ifndef APM_COPY_U
-#define APM_COPY_U 1   // 128-bit vectors per lane; one per lane measured fastest for a plain copy
-#endif
-constexpr int kThreads = APM_COPY_THREADS;
-constexpr int kVecPerLane = APM_COPY_U;
-constexpr int64_t kChunk = (int64_t)kThreads * 16 * kVecPerLane;
-constexpr int kMaxGridY = 65535;
+constexpr int kNT = 2, kSC1 = 16;  // cache policies: non-temporal; written through
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+__device__ __forceinline__ Rsrc make_rsrc(const void* base, int bytes) {  // accesses beyond it read zero / are dropped
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00027000);
+}
 
-// One vector of a lane.  SRC_ALIGNED false: the source address is any byte address; the target's
-// unaligned access mode (which the compiler relies on for this type) serves it with one 128-bit load.
+// nvec vectors (at most a workgroup's), both addresses 16-byte aligned.
+__device__ __forceinline__ void copy_vectors(const char* src, char* dst, int nvec) {
+    const Rsrc S = make_rsrc(src, nvec * 16), D = make_rsrc(dst, nvec * 16);
+    const int o = (int)threadIdx.x * 16;
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_amdgcn_raw_buffer_load_b128(S, o, 0, kNT), D, o, 0, kNT | kSC1);
+}
+
+// The same from a source at any byte address, which the target's unaligned access mode (the compiler relies
+// on it for this type) serves with one 128-bit load.
 typedef u32x4 __attribute__((aligned(1))) u32x4_any;
-template <bool SRC_ALIGNED>
-__device__ __forceinline__ u32x4 load_vec(const char* src, int vi) {
-    if (SRC_ALIGNED) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src) + vi);
-    return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(src + (int64_t)vi * 16));
+__device__ __forceinline__ void copy_vectors_unaligned(const char* src, char* dst, int nvec) {
+    if ((int)threadIdx.x >= nvec) return;
+    const u32x4 x = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(src + (int)threadIdx.x * 16));
+    __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(dst) + (int)threadIdx.x);
 }
 
-template <bool SRC_ALIGNED>
-__device__ __forceinline__ void copy_chunk(const char* src, u32x4* dst, int nvec) {
-    u32x4 r[kVecPerLane];
+// The same from a source `off` bytes (1 .. 15) beyond the aligned address `base`; the vectors base[0 .. nvec] are
+// read, all of them inside the source.  A lane loads one aligned vector and takes the rest of what it
+// stores from the next lane (the last one loads it).
+template <int WORDS>
+__device__ __forceinline__ u32x4 shifted(const u32x4& x, const u32x4& edge, uint32_t bytes) {
+    uint32_t w[8] = {x[0], x[1], x[2], x[3], 0, 0, 0, 0};
 #pragma unroll
-    for (int k = 0; k < kVecPerLane; ++k) {
-        const int vi = k * kThreads + (int)threadIdx.x;
-        if (vi < nvec) r[k] = load_vec<SRC_ALIGNED>(src, vi);
-    }
+    for (int j = 0; j <= WORDS; ++j)  // lane i takes lane i + 1's word; the last lane keeps that of `edge`
+        w[4 + j] = (uint32_t)__builtin_amdgcn_update_dpp((int)edge[j], (int)x[j], 0x130, 0xf, 0xf, false);
+    u32x4 out;
 #pragma unroll
-    for (int k = 0; k < kVecPerLane; ++k) {
-        const int vi = k * kThreads + (int)threadIdx.x;
-        if (vi < nvec) __builtin_nontemporal_store(r[k], dst + vi);
+    for (int j = 0; j < 4; ++j) out[j] = __builtin_amdgcn_alignbyte(w[j + WORDS + 1], w[j + WORDS], bytes);
+    return out;
+}
+__device__ __forceinline__ void copy_vectors_shifted(const char* base, int off, char* dst, int nvec) {
+    const Rsrc S = make_rsrc(base, (nvec + 1) * 16), D = make_rsrc(dst, nvec * 16);
+    const int o = (int)threadIdx.x * 16;
+    const u32x4 x = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(S, o, 0, 0));
+    u32x4 edge = u32x4{0u, 0u, 0u, 0u};
+    if (((int)threadIdx.x & 63) == 63) edge = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(S, o + 16, 0, 0));
+    const uint32_t bytes = (uint32_t)off & 3u;
+    u32x4 y;
+    switch (off >> 2) {
+        case 0: y = shifted<0>(x, edge, bytes); break;
+        case 1: y = shifted<1>(x, edge, bytes); break;
+        case 2: y = shifted<2>(x, edge, bytes); break;
+        default: y = shifted<3>(x, edge, bytes); break;
     }
+    __builtin_amdgcn_raw_buffer_store_b128(y, D, o, 0, kNT | kSC1);
 }
 
-// Both addresses 16-byte aligned: vector for vector.  Otherwise (views of one flat buffer, odd
-// numels) the stores are still aligned 128-bit vectors: the destination's first bytes up to a
-// multiple of 16 and its last ones go byte by byte (at most 15 each, by the segment's first
-// workgroup), and the vectors in between take whatever source alignment that leaves.  HBM-bound
-// either way.  122 M bf16 elements of odd-width tensors, views of one flat buffer, into pages:
-// a call took 145 us with 16-bit units on the odd addresses, 94 us with vectors.
+// ALIGNED: every address is a multiple of 16; vector for vector, stores written through besides non-temporal: 840 M
+// bf16 elements 539 us a call without, 521 with.  From kManyBytes on in workgroups of one wavefront: 502
+// (of two, with one, two or four vectors a lane: 517 to 570); below, dispatching those takes longer than it gains (us, of one /
+// of four: 43 MB 20.3 / 16.6, 95 MB 34.6 / 33.5, 142 MB 45.2 / 47.4, 202 MB 64.1 / 65.7).
+// Otherwise (views of one flat buffer, odd numels) workgroups of four wavefronts; the stores are still aligned
+// 128-bit vectors, the destination's first and last bytes go byte by byte (by the segment's first
+// workgroup), and the vectors in between take whatever source alignment that leaves:
+//   into tensors  the stores start on a cache line, vectors are shifted between lanes, written through besides:
+//                 840 M bf16 elements, odd widths, 574 -> 544 us, 122 M fp32 162 -> 157;
+//   into pages    that is slower (561 -> 601 us, 159 -> 168): 128-bit loads at the address itself, plain
+//                 non-temporal stores.
 //
 // A call brings nothing but the tensors' addresses, and these travel in the kernel arguments
 // (SegArgsInline): descriptors staged through a pinned ring cost the GPU an upload and two event packets,
-// 15 us between one call's copy and the next one's (122 M bf16 elements: 94 us a call, now 84;
-// 124 M fp32 elements out of their pages 177 us, now 160).  Long and short segments are launched
-// apart (group_by_extent): a GPT layout has as many bias and norm segments as full pages.
+// 15 us between one call's copy and the next one's.  All classes are one grid.  Whole calls with all of the
+// above: 124 M fp32 elements out of their pages 160 us -> 151, 840 M bf16 539 -> 495; flat views, 122 M
+// bf16 into pages 83.8 -> 81.4, 122 M fp32 out of pages 161 -> 154.
 struct SegArgs {
-    const SegRec* segs;   // from the first segment of the launch
-    char* region;
-    const uint64_t* ptrs; // the tensors' addresses, unless they follow inline
-    int32_t elem_bytes;
-    int32_t to_pages;
-    int32_t tensor_begin;
+    GridClass small[kMaxExtentClasses - 1];
+    const uint64_t* ptrs;     // the tensors' addresses
 };
 struct SegArgsInline {
-    SegArgs a;
-    uint64_t ptr[kArgWords];  // of tensors from a.tensor_begin
+    GridClass small[kMaxExtentClasses - 1];
+    uint64_t ptrs[kArgWords]; // of the tensors from tensor_begin
 };
+constexpr int kThreads = 256, kManyThreads = 64;
+constexpr int64_t kManyBytes = (int64_t)128 << 20;
+template <int THREADS> constexpr int64_t kChunk = (int64_t)THREADS * 16;
 
-template <class Args>
-__global__ __launch_bounds__(kThreads) void apm_seg_copy_kernel(Args args) {
-    const SegArgs* ap;
-    uint64_t tensor;
-    SegRec r;
-    struct { const void* src; void* dst; int64_t nbytes; } d;
-    if constexpr (sizeof(Args) > sizeof(SegArgs)) {
-        ap = &args.a;
-        r = ap->segs[blockIdx.y];
-        tensor = args.ptr[r.tensor - ap->tensor_begin];
-    } else {
-        ap = &args;
-        r = ap->segs[blockIdx.y];
-        tensor = ap->ptrs[r.tensor];
-    }
-    char* in_tensor = reinterpret_cast<char*>(tensor) + r.tensor_off * ap->elem_bytes;
-    char* in_page = ap->region + r.page_elem * ap->elem_bytes;
-    d.src = ap->to_pages ? in_tensor : in_page;
-    d.dst = ap->to_pages ? in_page : in_tensor;
-    d.nbytes = (int64_t)r.n * ap->elem_bytes;
-    const int64_t start = (int64_t)blockIdx.x * kChunk;
-    if (start >= d.nbytes) return;
-    const char* src = static_cast<const char*>(d.src);
-    char* dst = static_cast<char*>(d.dst);
-    if (((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15u) == 0) {
-        const int64_t len = d.nbytes - start < kChunk ? d.nbytes - start : kChunk;
+template <int THREADS, bool ALIGNED, class Args>
+__global__ __launch_bounds__(THREADS) void apm_seg_copy_kernel(const SegRec* segs, char* region, uint32_t large_at,
+                                                                                    uint32_t per, uint32_t mul, uint32_t shift, int32_t elem_log2,
+                                                                                    int32_t to_pages, int32_t tensor_begin, Args args) {
+    typedef int i32x8 __attribute__((ext_vector_type(8)));
+    typedef const i32x8 __attribute__((address_space(4))) * Const;
+    static_assert(sizeof(SegRec) == sizeof(i32x8), "a segment is one scalar load");
+    int item;
+    uint32_t x;
+    grid_item(large_at, GridDiv{per, mul, shift}, args.small, blockIdx.x, &item, &x);
+    const SegRec r = __builtin_bit_cast(SegRec, *(Const)reinterpret_cast<const i32x8*>(segs + item));
+    char* in_tensor = reinterpret_cast<char*>(args.ptrs[r.tensor - tensor_begin]) + (r.tensor_off << elem_log2);
+    char* in_page = region + (r.page_elem << elem_log2);
+    const char* src = to_pages ? in_tensor : in_page;
+    char* dst = to_pages ? in_page : in_tensor;
+    const int64_t nbytes = (int64_t)r.n << elem_log2;
+    const int64_t start = (int64_t)x * kChunk<THREADS>;
+    if (start >= nbytes) return;
+    if (ALIGNED || ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15u) == 0) {
+        const int64_t len = nbytes - start < kChunk<THREADS> ? nbytes - start : kChunk<THREADS>;
         src += start;
         dst += start;
         const int nvec = (int)(len >> 4);
-        copy_chunk<true>(src, reinterpret_cast<u32x4*>(dst), nvec);
+        copy_vectors(src, dst, nvec);
         const int tail = (int)(len & 15);  // only the last chunk of a segment can have one
         if ((int)threadIdx.x < tail) dst[((int64_t)nvec << 4) + threadIdx.x] = src[((int64_t)nvec << 4) + threadIdx.x];
         return;
     }
-    const int64_t to_vec = (int64_t)((16u - (uint32_t)(reinterpret_cast<uintptr_t>(dst) & 15u)) & 15u);
-    const int64_t head = to_vec < d.nbytes ? to_vec : d.nbytes;
-    const int64_t body = (d.nbytes - head) & ~(int64_t)15;
-    if (blockIdx.x == 0) {
+    const uint32_t line = to_pages ? 16u : 128u;
+    int64_t head = (int64_t)(-(uint32_t)reinterpret_cast<uintptr_t>(dst) & (line - 1));
+    int off = 0;  // of the vectors to be shifted
+    if (!to_pages) {
+        off = (int)((reinterpret_cast<uintptr_t>(src) + (uint64_t)head) & 15u);
+        if (off > head) head += 16;  // the first vector read starts `off` bytes before the first byte stored
+    }
+    if (head > nbytes) head = nbytes;
+    int64_t body = (nbytes - head) & ~(int64_t)15;
+    if (off > 0 && body > 0 && nbytes - head - body < 16 - off) body -= 16;  // and the last one ends 16 - off beyond
+    if (x == 0) {
         const int64_t tail_at = head + body;
-        const int tail = (int)(d.nbytes - tail_at), t = (int)threadIdx.x;
+        const int tail = (int)(nbytes - tail_at), t = (int)threadIdx.x;
         if (t < (int)head) dst[t] = src[t];
         if (t < tail) dst[tail_at + t] = src[tail_at + t];
     }
     if (start >= body) return;
-    const int64_t len = body - start < kChunk ? body - start : kChunk;
+    const int nvec = (int)((body - start < kChunk<THREADS> ? body - start : kChunk<THREADS>) >> 4);
     src += head + start;
     dst += head + start;
-    if ((reinterpret_cast<uintptr_t>(src) & 15u) == 0) copy_chunk<true>(src, reinterpret_cast<u32x4*>(dst), (int)(len >> 4));
-    else copy_chunk<false>(src, reinterpret_cast<u32x4*>(dst), (int)(len >> 4));
+    if (off > 0) copy_vectors_shifted(src - off, off, dst, nvec);
+    else if (!to_pages) copy_vectors(src, dst, nvec);
+    else copy_vectors_unaligned(src, dst, nvec);
 }
 
 // Both directions of a staged batch exchange in one kernel: the fp32 classes of an incoming batch
@@ -312,20 +337,33 @@ hipError_t launch_duplex_copy(const DuplexCopy& d, int wavefronts, int per_wg, h
 }
 
 hipError_t launch_seg_copy(const SegCopy& c, const SegLaunch* launches, int64_t n_launches, hipStream_t s) {
-    for (int64_t k = 0; k < n_launches; ++k) {
-        const SegLaunch& l = launches[k];
-        const int64_t max_bytes = l.max_n * c.elem_bytes;
-        const unsigned nx = (unsigned)((max_bytes + kChunk - 1) / kChunk);
+    for (int64_t i = 0; i < n_launches; ++i) {
+        const SegLaunch& l = launches[i];
         SegArgsInline in;
-        if (!c.on_device) std::memcpy(in.ptr, c.ptrs + l.tensor_begin, (size_t)l.tensor_count * sizeof(uint64_t));
-        for (int64_t off = 0; off < l.count; off += kMaxGridY) {
-            const dim3 grid(nx, (unsigned)(l.count - off < kMaxGridY ? l.count - off : kMaxGridY));
-            in.a = SegArgs{c.segs + l.begin + off, c.region, c.on_device ? c.ptrs : nullptr, c.elem_bytes, c.to_pages, l.tensor_begin};
-            if (c.on_device) hipLaunchKernelGGL(apm_seg_copy_kernel<SegArgs>, grid, dim3(kThreads), 0, s, in.a);
-            else hipLaunchKernelGGL(apm_seg_copy_kernel<SegArgsInline>, grid, dim3(kThreads), 0, s, in);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
+        if (!c.on_device) std::memcpy(in.ptrs, c.ptrs + l.tensor_begin, (size_t)l.tensor_count * sizeof(uint64_t));
+        int64_t bytes = 0;
+        for (int k = 0; k < l.n_cls; ++k) bytes += l.cls[k].sum_used * c.elem_bytes;
+        auto go = [&](auto aligned, auto workgroup) -> int {
+            constexpr bool kAligned = decltype(aligned)::value;
+            constexpr int threads = decltype(workgroup)::value;
+            return for_each_grid(l.cls, l.n_cls, threads, 0,
+                [&](const ExtentClass& e) { return (e.max_used * c.elem_bytes + kChunk<threads> - 1) / kChunk<threads>; },
+                [&](const GridMap& map, int64_t workgroups, int64_t first) -> int {
+                    auto start = [&](auto kernel, auto& args, int32_t tensor_begin) {
+                        std::memcpy(args.small, map.small, sizeof map.small);
+                        hipLaunchKernelGGL(kernel, dim3((unsigned)workgroups), dim3(threads), 0, s, c.segs + first, c.region, map.large_at, map.large.per,
+                                           map.large.mul, map.large.shift, c.elem_bytes == 4 ? 2 : 1, c.to_pages, tensor_begin, args);
+                    };
+                    SegArgs on_device{{}, c.ptrs};
+                    if (c.on_device) start(apm_seg_copy_kernel<threads, kAligned, SegArgs>, on_device, 0);
+                    else start(apm_seg_copy_kernel<threads, kAligned, SegArgsInline>, in, l.tensor_begin);
+                    return (int)hipGetLastError();
+                });
+        };
+        const hipError_t e = (hipError_t)(!c.aligned ? go(std::false_type{}, std::integral_constant<int, kThreads>{})
+                                           : bytes < kManyBytes ? go(std::true_type{}, std::integral_constant<int, kThreads>{})
+                                                                : go(std::true_type{}, std::integral_constant<int, kManyThreads>{}));
+        if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }

@@ -65,7 +65,8 @@ int make_plan(int64_t E, const int64_t* numels, int64_t n, Plan* out) {
     return APM_OK;
 }
 
-int group_by_extent(int64_t n, int64_t E, const int32_t* size, int64_t* order, ExtentClass cls[kMaxExtentClasses]) {
+int group_by_extent(int64_t n, int64_t E, const int32_t* size, int64_t* order, ExtentClass cls[kMaxExtentClasses],
+                    int64_t worth) {
     const int64_t limit[kMaxExtentClasses - 1] = {E / 4, E / 32, E / 512};  // sizes above: classes 0, 1, 2
     auto class_of = [&](int64_t used) { return (used <= limit[0]) + (used <= limit[1]) + (used <= limit[2]); };
     int64_t cnt[kMaxExtentClasses] = {}, mx[kMaxExtentClasses] = {}, sum[kMaxExtentClasses] = {};
@@ -76,20 +77,19 @@ int group_by_extent(int64_t n, int64_t E, const int32_t* size, int64_t* order, E
         sum[c] += u;
         if (u > mx[c]) mx[c] = u;
     }
-    // A class is worth its extra launches only if it saves enough idle workgroups; otherwise it is folded
-    // into the next larger one.  Counted in spans of 1024 elements, four workgroups of the update or half a
+    // A class that saves fewer idle workgroups than it is worth is folded into the next larger one.  With launches of its own:  Counted in spans of 1024 elements, four workgroups of the update or half a
     // copy's; from and to tensors, us a call with the line at 2048 / 4096 / 16384 / 65536 spans: 4.8 M elements in
     // 64 K pages with clipping 41 / 33 / 33 / 33, in 256 K pages 30 / 30 / 28 / 28, in 1 M pages 32 / 32 / 32 / 53;
     // 124 M 537 / 537 / 538 / 544; 350 M 1520 / 1518 / 1529 / 1555; packing 122 M 87 / 87 / 85 / 86.
     int into[kMaxExtentClasses];
     for (int c = 0; c < kMaxExtentClasses; ++c) into[c] = c;
-    constexpr int64_t kSpan = 1024, kWorthWorkgroups = 16384;
+    constexpr int64_t kSpan = 1024;
     for (int c = kMaxExtentClasses - 1; c > 0; --c) {
         if (cnt[c] == 0) continue;
         int j = c - 1;
         while (j > 0 && cnt[j] == 0) --j;
         if (cnt[j] == 0) continue;
-        if (cnt[c] * ((mx[j] - mx[c]) / kSpan) < kWorthWorkgroups) {
+        if (cnt[c] * ((mx[j] - mx[c]) / kSpan) < worth) {
             for (int q = c; q < kMaxExtentClasses; ++q) if (into[q] == c) into[q] = j;
             cnt[j] += cnt[c];
             sum[j] += sum[c];
@@ -108,6 +108,13 @@ int group_by_extent(int64_t n, int64_t E, const int32_t* size, int64_t* order, E
     else
         for (int64_t k = 0; k < n; ++k) order[fill[into[class_of(size[k])]]++] = k;
     return n_cls;
+}
+
+GridDiv grid_div(int64_t per) {
+    uint32_t log2 = 0;
+    while (((int64_t)1 << log2) < per) ++log2;
+    const uint32_t shift = 26 + log2;
+    return GridDiv{(uint32_t)per, (uint32_t)((((uint64_t)1 << shift) + (uint64_t)per - 1) / (uint64_t)per), shift};
 }
 
 int64_t pages_per_launch(int64_t per_page, int threads, int64_t limit) {

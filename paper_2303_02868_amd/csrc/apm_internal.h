@@ -11,6 +11,12 @@
 
 #include "apm.h"
 
+#if defined(__HIPCC__)
+#define APM_HOST_DEVICE __host__ __device__ __forceinline__
+#else
+#define APM_HOST_DEVICE
+#endif
+
 namespace apm {
 
 // ---- errors -------------------------------------------------------------------------------
@@ -61,9 +67,9 @@ int emit_plan(const Plan& plan, apm_segment* segs, int64_t* n_segs, int64_t* n_p
 inline int elem_bytes(int state) { return state <= APM_V32 ? 4 : 2; }
 
 // ---- sizes launched together --------------------------------------------------------------
-// Items of very different sizes (a page's used extent, a segment) that share one grid are grouped
-// into at most this many classes, largest first, each launched with a grid sized for its largest
-// member: a nearly empty page (a small tensor alone in its page) does not cost a full page's worth
+// Items of very different sizes (a page's used extent, a segment) are grouped into at most this many
+// classes, largest first, in which an item takes as many workgroups as the class's largest needs:
+// a nearly empty page (a small tensor alone in its page) does not cost a full page's worth
 // of workgroups that only find out they have nothing to do.
 constexpr int kMaxExtentClasses = 4;
 struct ExtentClass {
@@ -75,7 +81,11 @@ struct ExtentClass {
 // order[pos] = index of the item at position pos (classes one after the other, the given order kept
 // inside each); returns the number of classes.  E = the size that the class limits are fractions of.
 // Sizes come as an array: a call's host time is spent here when its pages are many and small.
-int group_by_extent(int64_t n, int64_t E, const int32_t* size, int64_t* order, ExtentClass cls[kMaxExtentClasses]);
+// worth: idle spans of 1024 elements that a class has to save (kWorthLaunch, kWorthGrid).
+constexpr int64_t kWorthLaunch = 16384;  // for a launch, or a page list, of its own
+constexpr int64_t kWorthGrid = 64;       // for its part of a common grid
+int group_by_extent(int64_t n, int64_t E, const int32_t* size, int64_t* order, ExtentClass cls[kMaxExtentClasses],
+                    int64_t worth = kWorthLaunch);
 
 // One dimension of a grid holds fewer than 2^32 work-items (the runtime refuses more): the workgroups of
 // `threads` work-items that a one-dimensional launch can have.
@@ -83,6 +93,79 @@ constexpr int64_t max_workgroups(int threads) { return (((int64_t)1 << 32) - 1) 
 // Pages that one such launch takes if a page is `per_page` workgroups; at least one (the largest page, 2^30
 // elements, is under 2^23 of any kernel here).  limit > 0: at most that many workgroups.
 int64_t pages_per_launch(int64_t per_page, int threads, int64_t limit = 0);
+
+// All classes in one one-dimensional grid, the classes of small items first: a launch of its own for them
+// costs 5 to 9 us, because it starts when the last workgroup of the one before has ended.
+//
+// w / per for w < 2^26 (more workgroups than a grid of 64 work-items each has) as a multiplication:
+// mul = ceil(2^shift / per) with shift = 26 + ceil(log2 per) is off by less than 1 / per at any such w.
+struct GridDiv {
+    uint32_t per, mul, shift;
+    APM_HOST_DEVICE uint32_t quotient(uint32_t w) const { return (uint32_t)(((uint64_t)w * mul) >> shift); }
+};
+GridDiv grid_div(int64_t per);  // 1 <= per <= 2^23
+// Workgroups [0, large_at): the classes of small items, the smallest first, small[k] from workgroup `first` on, unused
+// entries (the last ones) with first = large_at; from large_at on the largest class.  begin: first position of the class, counted
+// from the largest class's.
+struct GridClass {
+    uint32_t first;
+    int32_t begin;
+    GridDiv div;
+};
+struct GridMap {
+    uint32_t large_at;
+    GridDiv large;
+    GridClass small[kMaxExtentClasses - 1];
+};
+// Workgroup w's item (a position, counted from the largest class's first) and its number within the item.
+// What the largest class needs are single kernel arguments: the leading ones arrive in registers.
+APM_HOST_DEVICE inline void grid_item(uint32_t large_at, GridDiv d, const GridClass* small, uint32_t w, int* item, uint32_t* x) {
+    int begin = 0;
+    uint32_t first = large_at;
+    if (w < large_at) {
+        const int c = (w >= small[1].first) + (w >= small[2].first);
+        d = small[c].div;
+        begin = small[c].begin;
+        first = small[c].first;
+    }
+    w -= first;
+    const uint32_t q = d.quotient(w);
+    *item = begin + (int)q;
+    *x = w - q * d.per;
+}
+// Calls launch(map, workgroups, first position of the largest class in it) for all classes at once, or, where
+// that is more than one grid holds (or more than `limit` > 0), class by class in pieces that it holds.
+// per(class): workgroups an item takes, >= 1.  Returns the first non-zero result.
+template <class Per, class Launch>
+int for_each_grid(const ExtentClass* cls, int n_cls, int threads, int64_t limit, Per&& per, Launch&& launch) {
+    int64_t total = 0;
+    const int64_t cap = limit > 0 ? limit : max_workgroups(threads);
+    for (int c = 0; c < n_cls; ++c) total += cls[c].count * per(cls[c]);
+    if (n_cls <= 0) return 0;
+    if (total <= cap) {
+        GridMap m{};
+        int64_t at = 0;
+        for (int c = n_cls - 1; c >= 1; --c) {
+            m.small[n_cls - 1 - c] = GridClass{(uint32_t)at, (int32_t)(cls[c].begin - cls[0].begin), grid_div(per(cls[c]))};
+            at += cls[c].count * per(cls[c]);
+        }
+        m.large_at = (uint32_t)at;
+        m.large = grid_div(per(cls[0]));
+        for (int k = n_cls - 1; k < kMaxExtentClasses - 1; ++k) m.small[k] = GridClass{m.large_at, 0, GridDiv{1, 0, 0}};
+        return launch(m, total, cls[0].begin);
+    }
+    for (int c = 0; c < n_cls; ++c) {
+        GridMap m{};
+        m.large = grid_div(per(cls[c]));
+        const int64_t piece = pages_per_launch(m.large.per, threads, limit);
+        for (int64_t off = 0; off < cls[c].count; off += piece) {
+            const int64_t n = cls[c].count - off < piece ? cls[c].count - off : piece;
+            const int rc = launch(m, n * m.large.per, cls[c].begin + off);
+            if (rc != 0) return rc;
+        }
+    }
+    return 0;
+}
 
 // Words of 8 bytes that a launch carries in its kernel arguments: 3.4 KB, which leaves room for the
 // rest under the 4 KB that argument blocks may have.
@@ -253,16 +336,17 @@ hipError_t launch_grad_take(const GradTake& t, hipStream_t s);
 // One segment of the layout as the copy kernel reads it: n elements from `tensor_off` of tensor
 // `tensor`, in the class region from element `page_elem`.  The table depends on the layout alone and
 // is uploaded with it; a call only brings the tensors' addresses.
-struct SegRec {
+struct __attribute__((aligned(32))) SegRec {  // one scalar load
     int64_t tensor_off;
     int64_t page_elem;
     int32_t tensor;
     int32_t n;
+    int64_t pad;
 };
-// Segments [begin, begin + count) of the table, all of tensors [tensor_begin, tensor_begin + kArgWords),
-// the longest of max_n elements.
+// Segments of the table in classes of their lengths, all of tensors [tensor_begin, tensor_begin + kArgWords).
 struct SegLaunch {
-    int64_t begin, count, max_n;
+    ExtentClass cls[kMaxExtentClasses];
+    int n_cls;
     int32_t tensor_begin, tensor_count;
 };
 // Pack (to_pages) or unpack over the given launches.  ptrs = the tensors' addresses: in host memory
@@ -274,6 +358,7 @@ struct SegCopy {
     bool to_pages;
     const uint64_t* ptrs;
     bool on_device;
+    bool aligned;  // every tensor starts on a multiple of 16 bytes
 };
 hipError_t launch_seg_copy(const SegCopy& c, const SegLaunch* launches, int64_t n_launches, hipStream_t s);
 

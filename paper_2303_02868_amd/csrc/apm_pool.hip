@@ -147,8 +147,7 @@ void free_pool(apm_pool* pool) {
 // Groups of tensors beyond which pack / unpack stage the addresses instead of splitting the launch.
 constexpr int kMaxSegRanges = 2;
 
-// The layout's segments in launch order: per group of kArgWords tensors the long ones, then the short
-// ones (see group_by_extent).
+// The layout's segments in launch order: per group of kArgWords tensors by classes of their lengths.
 void order_segments(const Plan& plan, SegRec* recs, std::vector<SegLaunch>* launches, int32_t* ranges) {
     const int64_t n = (int64_t)plan.segs.size();
     const int64_t last = n ? plan.segs[(size_t)n - 1].tensor : -1;
@@ -167,13 +166,17 @@ void order_segments(const Plan& plan, SegRec* recs, std::vector<SegLaunch>* laun
             if (u > mx) mx = u;
         }
         ExtentClass cls[kMaxExtentClasses];
-        const int n_cls = group_by_extent(end - at, mx, size.data(), order.data(), cls);
+        const int n_cls = group_by_extent(end - at, mx, size.data(), order.data(), cls, kWorthGrid);
         const int64_t count = last + 1 - t0 < group ? last + 1 - t0 : group;
-        for (int c = 0; c < n_cls; ++c)
-            launches->push_back(SegLaunch{at + cls[c].begin, cls[c].count, cls[c].max_used, (int32_t)t0, (int32_t)count});
+        SegLaunch l{{}, n_cls, (int32_t)t0, (int32_t)count};
+        for (int c = 0; c < n_cls; ++c) {
+            l.cls[c] = cls[c];
+            l.cls[c].begin += at;
+        }
+        launches->push_back(l);
         for (int64_t k = 0; k < end - at; ++k) {
             const apm_segment& g = plan.segs[(size_t)(at + order[(size_t)k])];
-            *recs++ = SegRec{g.tensor_off, g.page * plan.E + g.page_off, (int32_t)g.tensor, (int32_t)g.n};
+            *recs++ = SegRec{g.tensor_off, g.page * plan.E + g.page_off, (int32_t)g.tensor, (int32_t)g.n, 0};
         }
         at = end;
     }
@@ -283,7 +286,7 @@ int plan_of(const apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan* ou
     return make_plan(pool->desc.page_elems, numels.data(), n, out);
 }
 
-// Shared body of pack (to_pages) and unpack: the layout's segments, long and short ones launched apart.
+// Shared body of pack (to_pages) and unpack: the layout's segments.
 int move_segments(apm_pool* pool, int state, const apm_tensor* tensors, int64_t n, bool to_pages,
                   hipStream_t s) {
     const int eb = elem_bytes(state);
@@ -295,8 +298,12 @@ int move_segments(apm_pool* pool, int state, const apm_tensor* tensors, int64_t 
     }
     if (pool->plan.segs.empty()) return APM_OK;
     std::vector<uint64_t> ptrs((size_t)n);
-    for (int64_t i = 0; i < n; ++i) ptrs[(size_t)i] = reinterpret_cast<uint64_t>(tensors[i].data);
-    SegCopy c{pool->d_segs, static_cast<char*>(pool->base[state]), eb, to_pages, ptrs.data(), false};
+    uint64_t low = 0;
+    for (int64_t i = 0; i < n; ++i) {
+        ptrs[(size_t)i] = reinterpret_cast<uint64_t>(tensors[i].data);
+        if (tensors[i].numel > 0) low |= ptrs[(size_t)i];
+    }
+    SegCopy c{pool->d_segs, static_cast<char*>(pool->base[state]), eb, to_pages, ptrs.data(), false, (low & 15u) == 0};
     // Up to kMaxSegRanges launches carry the addresses themselves.  The staging ring costs the GPU 15 us
     // a call; each further launch costs the host 1.5 us, and a call with this many tensors takes the
     // host longer than the GPU when they are small (1024 each, staged / carried: 800 tensors

@@ -222,6 +222,51 @@ void launch_pieces(Rng& r) {
     if (apm::max_workgroups(64) * 64 >= (int64_t)1 << 32 || (apm::max_workgroups(64) + 1) * 64 < (int64_t)1 << 32) die("workgroup limit");
 }
 
+// Every workgroup of a common grid belongs to one (item, number), each of which has one workgroup; classes that do
+// not fit together go apart.  And the division by multiplication against the division.
+void common_grid(Rng& r) {
+    for (int i = 0; i < 200; ++i) {
+        const int64_t per = 1 + r.below((int64_t)1 << (1 + r.below(23)));
+        const apm::GridDiv d = apm::grid_div(per);
+        for (int k = 0; k < 200; ++k) {
+            const int64_t top = ((int64_t)1 << 26) - 1;
+            int64_t w = k < 3 ? top - k : r.below(top + 1);
+            if (k % 2) w = w / per * per + (k % 4 == 1 ? 0 : per - 1);
+            if (w > top) w = top;
+            if (d.quotient((uint32_t)w) != (uint32_t)(w / per)) die("quotient", w, per);
+        }
+    }
+    for (int i = 0; i < 300; ++i) {
+        apm::ExtentClass cls[apm::kMaxExtentClasses];
+        const int n_cls = (int)r.below(apm::kMaxExtentClasses + 1);
+        int64_t at = r.below(50);
+        int64_t per[apm::kMaxExtentClasses];
+        for (int c = 0; c < n_cls; ++c) {
+            cls[c] = apm::ExtentClass{at, 1 + r.below(40), 0, 0};
+            per[c] = cls[c].max_used = 1 + r.below(30);
+            at += cls[c].count;
+        }
+        const int64_t limit = r.below(3) ? 0 : 1 + r.below(500);
+        std::vector<std::vector<int>> seen((size_t)at);
+        for (int c = 0; c < n_cls; ++c)
+            for (int64_t k = 0; k < cls[c].count; ++k) seen[(size_t)(cls[c].begin + k)].assign((size_t)per[c], 0);
+        apm::for_each_grid(cls, n_cls, 64, limit, [](const apm::ExtentClass& e) { return e.max_used; },
+                           [&](const apm::GridMap& m, int64_t workgroups, int64_t first) {
+            for (int64_t w = 0; w < workgroups; ++w) {
+                int item;
+                uint32_t x;
+                apm::grid_item(m.large_at, m.large, m.small, (uint32_t)w, &item, &x);
+                const int64_t pos = first + item;
+                if (pos < 0 || pos >= at || x >= seen[(size_t)pos].size() || seen[(size_t)pos][x]++) die("workgroup", w, pos);
+            }
+            return 0;
+        });
+        for (auto& p : seen)
+            for (int n : p)
+                if (n != 1) die("slice without a workgroup", n);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -230,6 +275,7 @@ int main(int argc, char** argv) {
     pack_errors();
     plan_errors();
     launch_pieces(r);
+    common_grid(r);
     for (int i = 0; i < cases; ++i) pack_case(r);
     for (int i = 0; i < cases; ++i) plan_case(r);
     for (int i = 0; i < cases; ++i) group_case(r);

@@ -54,6 +54,32 @@ def test_pack_and_unpack_of_many_tensors_are_bit_exact(n_t):
     pool.destroy()
 
 
+@pytest.mark.parametrize("numels,align", [([1000, 17, 70000, 300001, 9] * 3, 1), ([1000, 17, 70000, 300001, 9] * 3, 4), ([5] * 3 + [4099] * 5 + [1 << 21], 16),
+                                          ([32 << 20, 12345, 7, (1 << 19) + 1, 300], 16), ([32 << 20, 12345, 7, (1 << 19) + 1, 300], 1)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_pack_and_unpack_of_long_and_short_segments_are_bit_exact(dtype, numels, align):
+    """Segments of all length classes in one grid; aligned lists below and above the size from which a
+    workgroup is one wavefront, and views of one flat buffer at odd distances."""
+    kind, st, dt = (apm.APM_BF16, apm.APM_G16, torch.int16) if dtype == "bf16" else (apm.APM_F32, apm.APM_P32, torch.int32)
+    E, n_t, off, at = 65536, len(numels), [], 0
+    for k, n in enumerate(numels):
+        at += -at % align + (k % 5 if align == 1 else 0)
+        off.append(at)
+        at += n
+    src = torch.randint(-30000, 30000, (at + 64,), device=DEV, dtype=dt, generator=torch.Generator(device=DEV).manual_seed(at))
+    out = torch.full_like(src, -7)
+    want = torch.full_like(src, -7)
+    pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, sum(-(-n // E) for n in numels), state_mask=1 << st)
+    lists = [apm.make_tensors(numels, kind, [t.data_ptr() + o * t.element_size() for o in off]) for t in (src, out)]
+    apm.apm_pack_tensors(pool, st, lists[0], n_t)
+    apm.apm_unpack(pool, st, lists[1], n_t)
+    torch.cuda.synchronize()
+    for o, n in zip(off, numels):
+        want[o:o + n] = src[o:o + n]
+    assert torch.equal(out, want)
+    pool.destroy()
+
+
 @pytest.mark.parametrize("clip", [0.0, 0.01])
 @pytest.mark.parametrize("n_t,listed", [(1, "all"), (147, "odd"), (219, "all"), (221, "reversed"), (441, "all"), (450, "reversed"),
                                         (700, "odd"), (900, "all"), (1500, "reversed")])
