@@ -17,10 +17,14 @@
 // (1 KiB for the 128-bit fp32 accesses, 512 B for the 64-bit bf16 accesses), each lane keeps
 // several independent loads in flight, and a workgroup never straddles a page.
 //
-// Work decomposition: grid.y walks the listed pages, grid.x the fixed-size slices of a page (the live and
-// clip kernels lay both out along grid.x); slices that start beyond the page's used extent exit at once.  The page table (`used`) is read
+// Work decomposition: one grid over the fixed-size slices of all listed pages (GridMap; for a run of pages
+// grid.y walks the pages); slices that start beyond the page's used extent exit at once.  The page table (`used`) is read
 // on the device; the host, which knows the extents from the layout, only sizes the grids (pages
-// grouped into extent classes) so that few workgroups are launched for nothing.
+// grouped into extent classes) so that few workgroups are launched for nothing.  All classes are one
+// grid, the nearly empty pages first: as a launch of their own they cost 8 to 11 us after the large
+// ones, and behind the large ones in the same grid their latencies come at the end of the call.  us a call from and
+// to tensors, launches of their own / one grid / nearly empty pages last: 124 M parameters 538 / 525 / 526; 4.8 M in 256 K
+// pages 31.3 / 26.2 / 25.8, with clipping 40.5 / 32.7 / 36.7; 11 M with clipping 67.9 / 59.5 / 62.7.
 #include <cstring>
 
 #include "apm_internal.h"
@@ -167,6 +171,25 @@ __device__ __forceinline__ void scatter_q4(const PageRec& r, int e, u32x2 o) {
     }
 }
 
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+static_assert(sizeof(PageRec) == sizeof(i32x16) && sizeof(PageRun) == sizeof(i32x2), "a record is one scalar load");
+
+// Through the constant address space these are scalar loads also in kernels that store before them; what
+// they read was written by an earlier kernel (the one-pass kernel does not use the scale it gets this way).
+// The empty statement keeps it one load: the compiler otherwise loads field by field where each is used, a round
+// trip after the other.
+__device__ __forceinline__ PageRec load_rec(const PageRec* at) {
+    typedef const i32x16 __attribute__((address_space(4))) * Const;
+    i32x16 w = *(Const)reinterpret_cast<const i32x16*>(at);
+    asm("" : "+s"(w));
+    return __builtin_bit_cast(PageRec, w);
+}
+__device__ __forceinline__ PageRun load_run(const PageRun* at) {
+    typedef const i32x2 __attribute__((address_space(4))) * Const;
+    return __builtin_bit_cast(PageRun, *(Const)reinterpret_cast<const i32x2*>(at));
+}
+
 // The workgroup's sum (wavefront butterfly, then wave 0..3) and OR, written by thread 0.
 __device__ __forceinline__ void block_sum(double acc, uint32_t nz, double* s_acc, uint32_t* s_nz, double* sum, uint32_t* flag) {
     acc = wave_sum_f64(acc);
@@ -191,7 +214,6 @@ __device__ __forceinline__ void block_sum(double acc, uint32_t nz, double* s_acc
 
 struct ReduceArgs {
     const uint16_t* g16;
-    const PageRec* recs;  // gather only
     const int32_t* used;
     const int64_t* grad_pages;
     int64_t grad_first;
@@ -201,26 +223,37 @@ struct ReduceArgs {
     uint32_t* nzflags;
     int32_t S;
     int32_t* live;        // nullable: its counts are to be cleared
+    GridClass small[kMaxExtentClasses - 1];
 };
 
 // Per (page, slice): sum of squares in fp64 and OR of the magnitude bits of the slice's used
 // gradient elements.  Slice 0 always writes (a zero for an empty page); other slices only when
 // they hold used elements.  The fixed order (lane-sequential, wavefront butterfly, wave 0..3)
-// makes the result independent of scheduling.
+// makes the result independent of scheduling.  recs (gather only): from position a.list_offset.
 template <bool GATHER>
-__global__ __launch_bounds__(kThreads) void apm_grad_reduce_kernel(ReduceArgs a) {
-    if (a.live && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kMaxExtentClasses) a.live[threadIdx.x] = 0;
-    const int64_t i = a.list_offset + blockIdx.y;
-    const int64_t page = a.grad_pages ? a.grad_pages[i] : a.grad_first + i;
-    const int used = a.used[page];
-    const int start = blockIdx.x * kReduceTile;
-    if (start >= used && blockIdx.x != 0) return;
+__global__ __launch_bounds__(kThreads) void apm_grad_reduce_kernel(const PageRec* recs, uint32_t large_at, uint32_t per, uint32_t mul,
+                                                                   uint32_t shift, ReduceArgs a) {
+    int item;
+    uint32_t tile;
+    grid_item(large_at, GridDiv{per, mul, shift}, a.small, blockIdx.x, &item, &tile);
+    const int64_t i = a.list_offset + item;
+    PageRec rec{};
+    int64_t page = 0;
+    int used;
+    if (GATHER) {
+        rec = load_rec(recs + item);
+        used = rec.used;
+    } else {
+        page = a.grad_pages ? a.grad_pages[i] : a.grad_first + i;
+        used = a.used[page];
+    }
+    if (a.live && blockIdx.x == 0 && threadIdx.x < kMaxExtentClasses) a.live[threadIdx.x] = 0;
+    const int start = (int)tile * kReduceTile;
+    if (start >= used && tile != 0) return;
     const int end = min(start + kReduceTile, used);
     const uint16_t* g = GATHER ? nullptr : a.g16 + page * a.E;
-    PageRec rec{};
     bool edge = false;  // gather only: this slice is not wholly inside one tenant
     if (GATHER) {
-        rec = a.recs[i];
         const int k = start >= rec.off1 ? 1 : 0;
         // Wholly inside tenant k, counted in whole 8-element vectors (the fast path below loads
         // 16 bytes at a time and must not read past the tensor's last element): the slice reads
@@ -273,7 +306,7 @@ __global__ __launch_bounds__(kThreads) void apm_grad_reduce_kernel(ReduceArgs a)
     }
     __shared__ double s_acc[kThreads / kWave];
     __shared__ uint32_t s_nz[kThreads / kWave];
-    block_sum(acc0 + acc1, nz, s_acc, s_nz, a.partials + i * a.S + blockIdx.x, a.nzflags + i * a.S + blockIdx.x);
+    block_sum(acc0 + acc1, nz, s_acc, s_nz, a.partials + i * a.S + tile, a.nzflags + i * a.S + tile);
 }
 
 struct FinalizeArgs {
@@ -660,30 +693,21 @@ __device__ __forceinline__ void update_slice(const UpdateArgs& a, const PageRec&
     else cut_slice<U, GATHER, SCATTER, STORE>(a, rec, (start >> 2) + lane, p, m, v);
 }
 
-typedef int i32x2 __attribute__((ext_vector_type(2)));
-typedef int i32x16 __attribute__((ext_vector_type(16)));
-static_assert(sizeof(PageRec) == sizeof(i32x16) && sizeof(PageRun) == sizeof(i32x2), "a record is one scalar load");
-
-// Through the constant address space these are scalar loads also in kernels that store before them; what
-// they read was written by an earlier kernel (the one-pass kernel does not use the scale it gets this way).
-__device__ __forceinline__ PageRec load_rec(const PageRec* at) {
-    typedef const i32x16 __attribute__((address_space(4))) * Const;
-    return __builtin_bit_cast(PageRec, *(Const)reinterpret_cast<const i32x16*>(at));
-}
-__device__ __forceinline__ PageRun load_run(const PageRun* at) {
-    typedef const i32x2 __attribute__((address_space(4))) * Const;
-    return __builtin_bit_cast(PageRun, *(Const)reinterpret_cast<const i32x2*>(at));
-}
-
-// The HBM-resident form: grid.y walks the list positions, grid.x the slices of a page.  The arguments
+// The HBM-resident form: one grid over the slices of all listed pages (GridMap: classes of extents).  The arguments
 // are single values, what the prologue needs first, because the hardware hands the leading 14 dwords
 // of such an argument list to every wavefront in registers: the record's load is then the only round
 // trip before the first vector load.
+struct SmallClasses {
+    GridClass small[kMaxExtentClasses - 1];
+};
 template <int U, bool GATHER, bool SCATTER>
-__global__ __launch_bounds__(kUpdThreads) void apm_adamw_kernel(const PageRec* recs, float* p32, float* m32, float* v32,
-                                                                UpdateArgs a) {
-    const PageRec rec = load_rec(recs + blockIdx.y);
-    const int start = (int)blockIdx.x * kTile<U>;
+__global__ __launch_bounds__(kUpdThreads) void apm_adamw_kernel(const PageRec* recs, float* p32, float* m32, float* v32, uint32_t large_at,
+                                                                uint32_t per, uint32_t mul, uint32_t shift, UpdateArgs a, SmallClasses classes) {
+    int item;
+    uint32_t x;
+    grid_item(large_at, GridDiv{per, mul, shift}, classes.small, blockIdx.x, &item, &x);
+    const PageRec rec = load_rec(recs + item);
+    const int start = (int)x * kTile<U>;
     if (rec.scale < 0.0f || start >= ((rec.used + 7) & ~7)) return;  // a skipped page, beyond the extent
     update_slice<U, GATHER, SCATTER>(a, rec, start, (int)threadIdx.x, p32 + rec.pofs, m32 + rec.pofs, v32 + rec.pofs);
 }
@@ -704,25 +728,42 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_run_kernel(const void* 
     update_slice<U, false, false>(a, rec, start, (int)threadIdx.x, p32 + at, m32 + at, v32 + at);
 }
 
-// Over the pages that the finalize pass noted, nx slices each.  positions: those of the launch's class;
+// Over the pages that the finalize pass noted, a class's `slices.per` slices each.  live: see kLiveInts;
 // recs (as PageRun if RUN) and, if RUN, the other pointers are those of list position 0.
+struct LiveClasses {  // the smallest pages first; unused entries (the last ones) start where the grid ends
+    struct Class {
+        uint32_t first;         // of its workgroups
+        int32_t begin, number;  // its first position, its count's place
+        GridDiv slices;
+        uint32_t di, dx;        // it has di * slices.per + dx workgroups
+    } cls[kMaxExtentClasses];
+};
+__device__ __forceinline__ LiveClasses::Class load_class(const LiveClasses::Class* at) {
+    typedef int i32x8 __attribute__((ext_vector_type(8)));
+    static_assert(sizeof(LiveClasses::Class) == sizeof(i32x8), "a class is one scalar load");
+    typedef const i32x8 __attribute__((address_space(4), aligned(4))) * Const;
+    i32x8 w = *(Const)reinterpret_cast<const i32x8*>(at);
+    asm("" : "+s"(w));
+    return __builtin_bit_cast(LiveClasses::Class, w);
+}
 template <int U, bool RUN, bool GATHER, bool SCATTER>
-__global__ __launch_bounds__(kUpdThreads) void apm_adamw_live_kernel(const int32_t* n_live, const int32_t* positions, int nx,
-                                                                     const PageRec* recs, float* p32, float* m32, float* v32,
-                                                                     const uint16_t* g16, uint16_t* p16, int64_t E, UpdateArgs a) {
+__global__ __launch_bounds__(kUpdThreads) void apm_adamw_live_kernel(const int32_t* live, const PageRec* recs, float* p32, float* m32, float* v32,
+                                                                     const uint16_t* g16, uint16_t* p16, int64_t E, UpdateArgs a, LiveClasses lc) {
     typedef const int32_t __attribute__((address_space(4))) * Const;
-    const uint32_t n = *(Const)n_live;
-    if ((uint64_t)n * (uint32_t)nx <= blockIdx.x) return;
-    // a wavefront's items are gridDim.x apart; page and slice advance by that without another division
-    uint32_t i = blockIdx.x / (uint32_t)nx, x = blockIdx.x - i * (uint32_t)nx;
-    const uint32_t di = gridDim.x / (uint32_t)nx, dx = gridDim.x - di * (uint32_t)nx;
+    uint32_t w = blockIdx.x;
+    const LiveClasses::Class c = load_class(lc.cls + ((w >= lc.cls[1].first) + (w >= lc.cls[2].first) + (w >= lc.cls[3].first)));
+    const uint32_t n = ((Const)live)[c.number], nx = c.slices.per;
+    const Const positions = (Const)live + kMaxExtentClasses + c.begin;
+    w -= c.first;
+    // a wavefront's items are the class's workgroups apart; page and slice advance by that without another division
+    uint32_t i = c.slices.quotient(w), x = w - i * nx;
 #pragma unroll 1
-    for (; i < n; i += di, x += dx) {
-        if (x >= (uint32_t)nx) {
-            x -= (uint32_t)nx;
+    for (; i < n; i += c.di, x += c.dx) {
+        if (x >= nx) {
+            x -= nx;
             if (++i >= n) return;
         }
-        const int64_t pos = ((Const)positions)[i];
+        const int64_t pos = positions[i];
         PageRec rec;
         int64_t at;
         if (RUN) {
@@ -796,7 +837,8 @@ __global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(Str
 //
 //     sums of pages 0 .. D-1 | for every page j: sums of page j+D, update slices of page j
 //
-// where the sums of a page are its kReduceTile-element tiles and one wavefront that adds them up and
+// for every class of extents, the smallest pages first (the largest class's sums run beside the small ones'
+// waiting), where the sums of a page are its kReduceTile-element tiles and one wavefront that adds them up and
 // publishes the page's scale.  The second reading of a page's gradient follows the first by D pages;
 // the first reading uses ordinary loads and all else is non-temporal, so the gradient is still in the
 // memory-side cache (256 MiB) then: D pages are kLookAhead elements, 32 MiB of gradient (4, 8, 16, 32, 64, 100 M
@@ -917,57 +959,75 @@ struct ClipArgs {
     int64_t out_first;
     double max_norm;
     int32_t S;
-    int32_t count;         // pages
-    int32_t ahead;         // D
-    int32_t n_tiles, n_slices;  // of the launch's largest page
-    int32_t wait_limit;
+    // The launch's classes of extents, the smallest pages first: class k has the workgroups from `first` on,
+    // those of unused entries (the last ones) starting where the grid ends.
+    struct Class {
+        uint32_t first;
+        uint32_t n_ahead, n_mixed;  // workgroups of the class's first part, and of its first two
+        int32_t begin;              // the class's first page, from the launch's first
+        int32_t ahead;              // D
+        int32_t wait_limit;
+        uint32_t after;             // count - D
+        GridDiv sum, both, slices;  // per page: the tiles of the largest and 1, that and the slices, the slices
+    } cls[kMaxExtentClasses];
 };
+
+// One scalar load, as load_rec.
+__device__ __forceinline__ ClipArgs::Class load_class(const ClipArgs::Class* at) {
+    static_assert(sizeof(ClipArgs::Class) == sizeof(i32x16), "a class is one scalar load");
+    typedef const i32x16 __attribute__((address_space(4), aligned(4))) * Const;
+    i32x16 w = *(Const)reinterpret_cast<const i32x16*>(at);
+    asm("" : "+s"(w));
+    return __builtin_bit_cast(ClipArgs::Class, w);
+}
 
 template <bool RUN, bool GATHER, bool SCATTER>
 __global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c, UpdateArgs a) {
     constexpr int U = APM_UPDATE_U;
     const int lane = (int)threadIdx.x;
-    // item -> page, index among the page's sums (tiles, then the adder) or among its slices
-    const uint32_t n_sum = (uint32_t)c.n_tiles + 1, n_both = n_sum + (uint32_t)c.n_slices;
     uint32_t w = blockIdx.x, i, x;
+    PageRec* recs = c.recs;  // with the first round trip
+    asm("" : "+s"(recs));
+    const ClipArgs::Class k_ = load_class(c.cls + ((w >= c.cls[1].first) + (w >= c.cls[2].first) + (w >= c.cls[3].first)));
+    // item -> page, index among the page's sums (tiles, then the adder) or among its slices
     bool sums = true;
-    if (w < (uint32_t)c.ahead * n_sum) {
-        i = w / n_sum;
-        x = w - i * n_sum;
+    w -= k_.first;
+    if (w < k_.n_ahead) {
+        i = k_.sum.quotient(w);
+        x = w - i * k_.sum.per;
+    } else if (w < k_.n_mixed) {
+        w -= k_.n_ahead;
+        i = k_.both.quotient(w);
+        x = w - i * k_.both.per;
+        sums = x < k_.sum.per;
+        if (sums) i += (uint32_t)k_.ahead;
+        else x -= k_.sum.per;
     } else {
-        w -= (uint32_t)c.ahead * n_sum;
-        const uint32_t mixed = (uint32_t)(c.count - c.ahead) * n_both;
-        if (w < mixed) {
-            i = w / n_both;
-            x = w - i * n_both;
-            sums = x < n_sum;
-            if (sums) i += (uint32_t)c.ahead;
-            else x -= n_sum;
-        } else {
-            w -= mixed;
-            i = w / (uint32_t)c.n_slices;
-            x = w - i * (uint32_t)c.n_slices;
-            i += (uint32_t)(c.count - c.ahead);
-            sums = false;
-        }
+        w -= k_.n_mixed;
+        i = k_.slices.quotient(w);
+        x = w - i * k_.slices.per;
+        i += k_.after;
+        sums = false;
     }
+    i += (uint32_t)k_.begin;
+    const int32_t wait_limit = k_.wait_limit;
     PageRec rec;
     int64_t at;
     float* scale_at;
     if (RUN) {
-        PageRun* r = reinterpret_cast<PageRun*>(c.recs) + i;
+        PageRun* r = reinterpret_cast<PageRun*>(recs) + i;
         at = (int64_t)i * c.E;
         rec = class_rec(load_run(r).used, 0.0f, 0, 0, 0, c.g16 + at, c.p16 + at);
         scale_at = &r->scale;
     } else {
-        rec = load_rec(c.recs + i);
+        rec = load_rec(recs + i);
         at = rec.pofs;
-        scale_at = &c.recs[i].scale;
+        scale_at = &recs[i].scale;
     }
     const GlobalU32 word = (GlobalU32) reinterpret_cast<uint32_t*>(scale_at);
     const GlobalU64 sum = (GlobalU64)(c.sums + (int64_t)i * c.S);
     const int n_tiles = max(1, (rec.used + kReduceTile - 1) / kReduceTile);
-    if (sums && x < (uint32_t)c.n_tiles) {
+    if (sums && x + 1 < k_.sum.per) {
         if ((int)x >= n_tiles) return;
         const double t = tile_sum<GATHER>(rec, (int)x, lane);
         if (lane == 0) __hip_atomic_store(sum + x, (uint64_t)__double_as_longlong(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -982,7 +1042,7 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c,
             for (int polls = 0;; ++polls) {
                 v = t + lane < n_tiles ? poll64(sum + t + lane) : 0;
                 all = __all(v != kNoSum);
-                if (all || polls >= c.wait_limit) break;
+                if (all || polls >= wait_limit) break;
                 __builtin_amdgcn_s_sleep(4);
             }
             if (t + lane < n_tiles) s += __longlong_as_double((long long)v);
@@ -1003,8 +1063,8 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c,
         uint32_t seen = kNoScale;
         auto look = [&] { return (seen = (uint32_t)__builtin_amdgcn_readfirstlane((int)poll32(word))) != kNoScale; };
         for (int polls = 0; !look(); ++polls) {
-            if (polls >= c.wait_limit) {
-                const double s = page_sum<GATHER>(rec, n_tiles, lane, [&] { return c.wait_limit > 0 && look(); });
+            if (polls >= wait_limit) {
+                const double s = page_sum<GATHER>(rec, n_tiles, lane, [&] { return wait_limit > 0 && look(); });
                 return seen == kNoScale ? clip_scale(sqrt(s), c.max_norm) : __uint_as_float(seen);
             }
             __builtin_amdgcn_s_sleep(2);
@@ -1025,12 +1085,14 @@ struct TakeArgs {
     uint16_t* dst;
     const uint16_t* src;
     const int32_t* used;
-    const int64_t* order;  // of the launch's first position, or nullptr: first + position
+    const int64_t* order;  // or nullptr: first + position
     int64_t first;
     int64_t E;
     double* sums;
     uint32_t* nzflags;
     int32_t S;
+    int32_t at;            // position of the map's first item
+    GridMap map;
 };
 struct TakeArgsInline {
     TakeArgs a;
@@ -1048,19 +1110,20 @@ struct TakeArgsInline {
 template <bool ACCUM, bool SUMS, class Args>
 __global__ __launch_bounds__(kThreads) void apm_grad_take_kernel(Args args) {
     const TakeArgs* ap;
-    int64_t page;
-    if constexpr (sizeof(Args) > sizeof(TakeArgs)) {
-        ap = &args.a;
-        page = args.page[blockIdx.y];
-    } else {
-        ap = &args;
-        page = ap->order ? ap->order[blockIdx.y] : ap->first + blockIdx.y;
-    }
+    if constexpr (sizeof(Args) > sizeof(TakeArgs)) ap = &args.a;
+    else ap = &args;
     const TakeArgs& a = *ap;
+    int pos;
+    uint32_t tile;
+    grid_item(a.map.large_at, a.map.large, a.map.small, blockIdx.x, &pos, &tile);
+    pos += a.at;
+    int64_t page;
+    if constexpr (sizeof(Args) > sizeof(TakeArgs)) page = args.page[pos];
+    else page = a.order ? a.order[pos] : a.first + pos;
     constexpr int U = SUMS ? APM_REDUCE_U : 1, kSpan = kThreads * 8 * U, kItem = SUMS ? kReduceTile : kSpan;
     const int used = a.used[page], used8 = (used + 7) & ~7;
-    const int start = blockIdx.x * kItem;
-    if (start >= used8 && !(SUMS && blockIdx.x == 0)) return;
+    const int start = (int)tile * kItem;
+    if (start >= used8 && !(SUMS && tile == 0)) return;
     const int end = min(start + kItem, used8);
     u32x4* dst = reinterpret_cast<u32x4*>(a.dst + page * a.E);
     const Rsrc D = make_rsrc(a.dst + page * a.E + start, end > start ? (end - start) * 2 : 0);
@@ -1109,7 +1172,7 @@ __global__ __launch_bounds__(kThreads) void apm_grad_take_kernel(Args args) {
     if (!SUMS) return;
     __shared__ double s_acc[kThreads / kWave];
     __shared__ uint32_t s_nz[kThreads / kWave];
-    block_sum(acc0 + acc1, nz, s_acc, s_nz, a.sums + page * a.S + blockIdx.x, a.nzflags + page * a.S + blockIdx.x);
+    block_sum(acc0 + acc1, nz, s_acc, s_nz, a.sums + page * a.S + tile, a.nzflags + page * a.S + tile);
 }
 
 constexpr int kMaxGridY = 65535;
@@ -1118,35 +1181,45 @@ constexpr int kMaxGridY = 65535;
 
 hipError_t launch_grad_take(const GradTake& t, hipStream_t s) {
     TakeArgsInline in;
-    in.a = TakeArgs{t.dst, t.src, t.used, nullptr, 0, t.E, t.sums, t.nzflags, t.S};
+    in.a = TakeArgs{t.dst, t.src, t.used, t.order, t.first, t.E, t.sums, t.nzflags, t.S, 0, {}};
     const int item = t.sums ? kReduceTile : kThreads * 8;
-    for (int k = 0; k < t.n_cls; ++k) {
-        const ExtentClass& c = t.cls[k];
-        if (c.max_used <= 0 && !t.sums) continue;
-        const int64_t piece = t.host_pages ? kTakePages : kMaxGridY;
-        for (int64_t off = 0; off < c.count; off += piece) {
-            const int64_t n = c.count - off < piece ? c.count - off : piece;
-            const int64_t nx = (c.max_used + item - 1) / item;
-            const dim3 grid((unsigned)(nx > 0 ? nx : 1), (unsigned)n);
-            if (t.host_pages) {
-                for (int64_t i = 0; i < n; ++i) in.page[i] = (int32_t)t.host_pages[c.begin + off + i];
-            } else {
-                in.a.order = t.order ? t.order + c.begin + off : nullptr;
-                in.a.first = t.first + c.begin + off;
-            }
+    // positions of the given classes in one grid
+    auto go = [&](const ExtentClass* cls, int n_cls) -> hipError_t {
+        while (n_cls > 0 && cls[n_cls - 1].max_used <= 0 && !t.sums) --n_cls;  // nothing to take
+        return (hipError_t)for_each_grid(cls, n_cls, kThreads, 0,
+            [&](const ExtentClass& c) { return c.max_used > 0 ? (c.max_used + item - 1) / item : 1; },
+            [&](const GridMap& m, int64_t workgroups, int64_t first) -> int {
+                in.a.at = (int32_t)first;
+                in.a.map = m;
+                const dim3 grid((unsigned)workgroups);
 #define APM_TAKE(ACCUM, SUMS)                                                                                       \
     do {                                                                                                           \
         if (t.host_pages) hipLaunchKernelGGL((apm_grad_take_kernel<ACCUM, SUMS, TakeArgsInline>), grid, dim3(kThreads), 0, s, in); \
         else hipLaunchKernelGGL((apm_grad_take_kernel<ACCUM, SUMS, TakeArgs>), grid, dim3(kThreads), 0, s, in.a);   \
     } while (0)
-            if (t.accumulate && t.sums) APM_TAKE(true, true);
-            else if (t.accumulate) APM_TAKE(true, false);
-            else if (t.sums) APM_TAKE(false, true);
-            else APM_TAKE(false, false);
+                if (t.accumulate && t.sums) APM_TAKE(true, true);
+                else if (t.accumulate) APM_TAKE(true, false);
+                else if (t.sums) APM_TAKE(false, true);
+                else APM_TAKE(false, false);
 #undef APM_TAKE
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
+                return (int)hipGetLastError();
+            });
+    };
+    if (!t.host_pages) return go(t.cls, t.n_cls);
+    // kTakePages positions a launch, whatever their classes
+    int64_t n = 0;
+    for (int k = 0; k < t.n_cls; ++k) n += t.cls[k].count;
+    for (int64_t at = 0; at < n; at += kTakePages) {
+        ExtentClass part[kMaxExtentClasses];
+        int n_part = 0;
+        for (int k = 0; k < t.n_cls; ++k) {
+            const int64_t b = t.cls[k].begin > at ? t.cls[k].begin : at, end = t.cls[k].begin + t.cls[k].count;
+            const int64_t e = end < at + kTakePages ? end : at + kTakePages;
+            if (b < e) part[n_part++] = ExtentClass{b - at, e - b, t.cls[k].max_used, 0};
         }
+        for (int64_t i = at; i < n && i < at + kTakePages; ++i) in.page[i - at] = (int32_t)t.host_pages[i];
+        const hipError_t e = go(part, n_part);
+        if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
@@ -1191,14 +1264,18 @@ static bool notes_live(const AdamwLaunch& L) {
 hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
     hipError_t e = hipSuccess;
     int32_t* live = notes_live(L) ? L.live : nullptr;
-    ReduceArgs a{L.g16, L.recs, L.used, L.grad_pages, L.grad_first, 0, L.E, L.partials, L.nzflags, L.S, live};
+    ReduceArgs a{L.g16, L.used, L.grad_pages, L.grad_first, 0, L.E, L.partials, L.nzflags, L.S, live, {}};
     if (L.sums_ready && live) hipLaunchKernelGGL(apm_live_clear_kernel, dim3(1), dim3(kWave), 0, s, live);
-    if (!L.sums_ready) e = for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used, int64_t sum_used) {
-        a.list_offset = begin;
-        const dim3 grid((unsigned)((max_used + kReduceTile - 1) / kReduceTile), (unsigned)ny);
-        if (L.gather) hipLaunchKernelGGL(apm_grad_reduce_kernel<true>, grid, dim3(kThreads), 0, s, a);
-        else hipLaunchKernelGGL(apm_grad_reduce_kernel<false>, grid, dim3(kThreads), 0, s, a);
-    });
+    const ExtentClass all{0, L.n_listed, L.E, L.n_listed * L.E};
+    if (!L.sums_ready) e = (hipError_t)for_each_grid(L.n_cls > 0 ? L.cls : &all, L.n_cls > 0 ? L.n_cls : 1, kThreads, 0,
+        [](const ExtentClass& c) { return c.max_used > 0 ? (c.max_used + kReduceTile - 1) / kReduceTile : 1; },
+        [&](const GridMap& m, int64_t workgroups, int64_t first) -> int {
+            a.list_offset = first;
+            std::memcpy(a.small, m.small, sizeof a.small);
+            hipLaunchKernelGGL(L.gather ? apm_grad_reduce_kernel<true> : apm_grad_reduce_kernel<false>, dim3((unsigned)workgroups), dim3(kThreads), 0, s,
+                               L.recs + first, m.large_at, m.large.per, m.large.mul, m.large.shift, a);
+            return (int)hipGetLastError();
+        });
     if (e != hipSuccess) return e;
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
                    L.partials, L.nzflags, L.S, L.skip_mode, L.max_norm, L.recs, L.g16, L.p16, L.E, live, {}, L.n_cls, L.sums_ready, L.is_run(),
@@ -1272,6 +1349,9 @@ hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s)
     return hipSuccess;
 }
 
+// Workgroups a page of the class takes.
+template <int U> int64_t slices_of(const ExtentClass& c) { return c.max_used > 0 ? (c.max_used + kTile<U> - 1) / kTile<U> : 1; }
+
 hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
     const UpdateArgs a{L.b1, L.omb1, L.b2, L.omb2, L.inv_sqrt_bc2, L.eps, L.step_size, L.lr_wd};
     const bool run = L.is_run();
@@ -1308,49 +1388,83 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         const int n_cls = L.n_cls > 0 ? L.n_cls : 1;
         const bool wide = run && L.wide;
         const int tile = wide ? kTile<kWideU> : kTile<U>;
+        const int64_t cap = L.max_workgroups > 0 ? L.max_workgroups : max_workgroups(kUpdThreads);
+        int64_t wgs[kMaxExtentClasses], total = 0;
         for (int c = 0; c < n_cls; ++c) {
-            const int nx = (int)((cls[c].max_used + tile - 1) / tile);
-            if (nx == 0) continue;
-            const int64_t slices = cls[c].count * nx;
-            int64_t wgs = (slices + kSkipSpread - 1) / kSkipSpread;
-            if (wgs < kSkipWaves) wgs = slices < kSkipWaves ? slices : kSkipWaves;
-            const int64_t cap = L.max_workgroups > 0 ? L.max_workgroups : max_workgroups(kUpdThreads);
-            if (wgs > cap) wgs = cap;  // each walks further
-            const dim3 grid((unsigned)wgs), block(kUpdThreads);
-            const int32_t *n_live = L.live + c, *positions = L.live + kMaxExtentClasses + cls[c].begin;
-#define APM_LAUNCH_LIVE(U, RUN, G, Q) hipLaunchKernelGGL((apm_adamw_live_kernel<U, RUN, G, Q>), grid, block, kSkipLds, s, n_live, positions, nx, \
+            const int64_t slices = cls[c].count * ((cls[c].max_used + tile - 1) / tile);
+            wgs[c] = (slices + kSkipSpread - 1) / kSkipSpread;
+            if (wgs[c] < kSkipWaves) wgs[c] = slices < kSkipWaves ? slices : kSkipWaves;
+            total += wgs[c];
+        }
+        const bool together = total <= cap;
+        for (int c0 = n_cls - 1; c0 >= 0; --c0) {  // all classes at once, or one after the other
+            LiveClasses lc{};
+            int64_t at = 0;
+            int k = 0;
+            for (int c = c0; c >= (together ? 0 : c0); --c) {
+                if (wgs[c] <= 0) continue;
+                if (wgs[c] > cap) wgs[c] = cap;  // each walks further
+                LiveClasses::Class& q = lc.cls[k++];
+                q.first = (uint32_t)at;
+                q.begin = (int32_t)cls[c].begin;
+                q.number = c;
+                q.slices = grid_div((cls[c].max_used + tile - 1) / tile);
+                q.di = (uint32_t)wgs[c] / q.slices.per;
+                q.dx = (uint32_t)wgs[c] - q.di * q.slices.per;
+                at += wgs[c];
+            }
+            for (; k < kMaxExtentClasses; ++k) lc.cls[k].first = (uint32_t)at;
+            if (at > 0) {
+                const dim3 grid((unsigned)at), block(kUpdThreads);
+#define APM_LAUNCH_LIVE(U, RUN, G, Q) hipLaunchKernelGGL((apm_adamw_live_kernel<U, RUN, G, Q>), grid, block, kSkipLds, s, L.live, \
                                                      L.recs, state(L.p32, 0), state(L.m32, 0), state(L.v32, 0), run ? g16(0) : nullptr,  \
-                                                     run ? p16(0) : nullptr, L.E, a)
-            if (wide) APM_LAUNCH_LIVE(kWideU, true, false, false);
-            else if (run) APM_LAUNCH_LIVE(U, true, false, false);
-            else if (L.gather && L.scatter) APM_LAUNCH_LIVE(U, false, true, true);
-            else if (L.gather) APM_LAUNCH_LIVE(U, false, true, false);
-            else if (L.scatter) APM_LAUNCH_LIVE(U, false, false, true);
-            else APM_LAUNCH_LIVE(U, false, false, false);
+                                                     run ? p16(0) : nullptr, L.E, a, lc)
+                if (wide) APM_LAUNCH_LIVE(kWideU, true, false, false);
+                else if (run) APM_LAUNCH_LIVE(U, true, false, false);
+                else if (L.gather && L.scatter) APM_LAUNCH_LIVE(U, false, true, true);
+                else if (L.gather) APM_LAUNCH_LIVE(U, false, true, false);
+                else if (L.scatter) APM_LAUNCH_LIVE(U, false, false, true);
+                else APM_LAUNCH_LIVE(U, false, false, false);
 #undef APM_LAUNCH_LIVE
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
+                const hipError_t e = hipGetLastError();
+                if (e != hipSuccess) return e;
+            }
+            if (together) break;
         }
         return hipSuccess;
     }
     constexpr int U = APM_UPDATE_U;
+    if (!run) {
+        const ExtentClass all{0, L.n_listed, L.E, L.n_listed * L.E};
+        const ExtentClass* cls = L.n_cls > 0 ? L.cls : &all;
+        const int n_cls = L.n_cls > 0 ? L.n_cls : 1;
+        int64_t elems = 0;
+        for (int c = 0; c < n_cls; ++c) elems += cls[c].sum_used;
+        const unsigned lds = update_lds(L.gather || L.scatter, elems, APM_UPDATE_LDS);
+        return (hipError_t)for_each_grid(cls, n_cls, kUpdThreads, L.max_workgroups, slices_of<U>, [&](const GridMap& m, int64_t workgroups, int64_t first) -> int {
+            SmallClasses classes;
+            std::memcpy(classes.small, m.small, sizeof classes.small);
+#define APM_LAUNCH_UPDATE(G, Q) hipLaunchKernelGGL((apm_adamw_kernel<U, G, Q>), dim3((unsigned)workgroups), dim3(kUpdThreads), lds, s, L.recs + first, \
+                                                   L.p32, L.m32, L.v32, m.large_at, m.large.per, m.large.mul, m.large.shift, a, classes)
+            if (L.gather && L.scatter) APM_LAUNCH_UPDATE(true, true);
+            else if (L.gather) APM_LAUNCH_UPDATE(true, false);
+            else if (L.scatter) APM_LAUNCH_UPDATE(false, true);
+            else APM_LAUNCH_UPDATE(false, false);
+#undef APM_LAUNCH_UPDATE
+            return (int)hipGetLastError();
+        });
+    }
     return for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used, int64_t sum_used) {
-        const bool wide = run && L.wide;
+        const bool wide = L.wide;
         const int tile = wide ? kTile<kWideU> : kTile<U>;
         const dim3 grid((unsigned)((max_used + tile - 1) / tile), (unsigned)ny), block(kUpdThreads);
-#define APM_LAUNCH_UPDATE(G, Q) hipLaunchKernelGGL((apm_adamw_kernel<U, G, Q>), grid, block, lds, s, L.recs + begin, L.p32, L.m32, L.v32, a)
-        const unsigned lds = update_lds(L.gather || L.scatter, sum_used, APM_UPDATE_LDS);
+        const unsigned lds = update_lds(false, sum_used, APM_UPDATE_LDS);
 #define APM_LAUNCH_RUN(U, BARE, RUNS) hipLaunchKernelGGL((apm_adamw_run_kernel<U, BARE>), grid, block, lds, s, RUNS, state(L.p32, begin), \
                                                          state(L.m32, begin), state(L.v32, begin), g16(begin), p16(begin), (int)L.E, a)
         if (wide && L.bare_run) APM_LAUNCH_RUN(kWideU, true, L.used + L.grad_first + begin);
         else if (wide) APM_LAUNCH_RUN(kWideU, false, runs + begin);
-        else if (run && L.bare_run) APM_LAUNCH_RUN(U, true, L.used + L.grad_first + begin);
-        else if (run) APM_LAUNCH_RUN(U, false, runs + begin);
-        else if (L.gather && L.scatter) APM_LAUNCH_UPDATE(true, true);
-        else if (L.gather) APM_LAUNCH_UPDATE(true, false);
-        else if (L.scatter) APM_LAUNCH_UPDATE(false, true);
-        else APM_LAUNCH_UPDATE(false, false);
-#undef APM_LAUNCH_UPDATE
+        else if (L.bare_run) APM_LAUNCH_RUN(U, true, L.used + L.grad_first + begin);
+        else APM_LAUNCH_RUN(U, false, runs + begin);
 #undef APM_LAUNCH_RUN
     });
 }
@@ -1376,43 +1490,74 @@ hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {
     const ExtentClass all{0, L.n_listed, L.E, L.n_listed * L.E};
     const ExtentClass* cls = L.n_cls > 0 ? L.cls : &all;
     const int n_cls = L.n_cls > 0 ? L.n_cls : 1;
+    struct Items { int64_t tiles, slices, all; };
+    auto items_of = [](const ExtentClass& e) {
+        const int64_t max_used = e.max_used > 0 ? e.max_used : 1;
+        const int64_t tiles = (max_used + kReduceTile - 1) / kReduceTile, slices = slices_of<APM_UPDATE_U>(e);
+        return Items{tiles, slices, tiles + 1 + slices};
+    };
+    int64_t total = 0, elems = 0;
     for (int k = 0; k < n_cls; ++k) {
-        const int64_t max_used = cls[k].max_used > 0 ? cls[k].max_used : 1;
+        total += cls[k].count * items_of(cls[k]).all;
+        elems += cls[k].sum_used;
+    }
+    const unsigned lds = update_lds(L.gather || L.scatter, elems, kClipLds);
+    // pages [begin, begin + count) of each of n classes, the largest first, in one grid
+    auto go = [&](const ExtentClass* part, int n) -> hipError_t {
+        const int64_t begin = part[0].begin;
         ClipArgs c{};
         c.E = L.E;
         c.S = L.S;
         c.grad_norm = L.grad_norm;
         c.skip_mask = L.skip_mask;
         c.max_norm = L.max_norm;
-        c.n_tiles = (int32_t)((max_used + kReduceTile - 1) / kReduceTile);
-        // a page's sums are added up 64 at a time, a round trip each
-        c.wait_limit = L.wait_limit + (int32_t)((int64_t)L.wait_limit * c.n_tiles / 4096);
-        c.n_slices = (int32_t)((max_used + kTile<APM_UPDATE_U> - 1) / kTile<APM_UPDATE_U>);
-        const int64_t items = c.n_tiles + 1 + c.n_slices;
-        const int64_t piece = pages_per_launch(items, kUpdThreads, L.max_workgroups);
+        int64_t at = 0;
+        for (int k = 0; k < n; ++k) {
+            const ExtentClass& e = part[n - 1 - k];
+            const Items it = items_of(e);
+            const int64_t max_used = e.max_used > 0 ? e.max_used : 1, want = (kLookAhead + max_used - 1) / max_used;
+            const int64_t ahead = want < e.count ? want : e.count;
+            ClipArgs::Class& q = c.cls[k];
+            q.first = (uint32_t)at;
+            q.n_ahead = (uint32_t)(ahead * (it.tiles + 1));
+            q.n_mixed = q.n_ahead + (uint32_t)((e.count - ahead) * it.all);
+            q.begin = (int32_t)(e.begin - begin);
+            q.ahead = (int32_t)ahead;
+            // a page's sums are added up 64 at a time, a round trip each
+            q.wait_limit = L.wait_limit + (int32_t)((int64_t)L.wait_limit * it.tiles / 4096);
+            q.after = (uint32_t)(e.count - ahead);
+            q.sum = grid_div(it.tiles + 1);
+            q.both = grid_div(it.all);
+            q.slices = grid_div(it.slices);
+            at += e.count * it.all;
+        }
+        for (int k = n; k < kMaxExtentClasses; ++k) c.cls[k].first = (uint32_t)at;
+        c.recs = run ? reinterpret_cast<PageRec*>(reinterpret_cast<PageRun*>(L.recs) + begin) : L.recs + begin;
+        c.sums = reinterpret_cast<uint64_t*>(L.partials) + begin * L.S;
+        c.out_index = L.out_index ? L.out_index + begin : nullptr;
+        c.out_first = begin;
+        const int64_t fp32 = run ? (L.state_first + begin) * L.E : 0, b16 = run ? (L.grad_first + begin) * L.E : 0;
+        c.p32 = L.p32 + fp32;
+        c.m32 = L.m32 + fp32;
+        c.v32 = L.v32 + fp32;
+        c.g16 = L.g16 + b16;
+        c.p16 = L.p16 + b16;
+        const dim3 grid((unsigned)at), block(kUpdThreads);
+        if (run) hipLaunchKernelGGL((apm_adamw_clip_kernel<true, false, false>), grid, block, lds, s, c, a);
+        else if (L.gather && L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, true>), grid, block, lds, s, c, a);
+        else if (L.gather) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, false>), grid, block, lds, s, c, a);
+        else if (L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, false, true>), grid, block, lds, s, c, a);
+        else hipLaunchKernelGGL((apm_adamw_clip_kernel<false, false, false>), grid, block, lds, s, c, a);
+        return hipGetLastError();
+    };
+    if (total <= (L.max_workgroups > 0 ? L.max_workgroups : max_workgroups(kUpdThreads))) return n_cls > 0 ? go(cls, n_cls) : hipSuccess;
+    for (int k = 0; k < n_cls; ++k) {
+        const int64_t piece = pages_per_launch(items_of(cls[k]).all, kUpdThreads, L.max_workgroups);
         for (int64_t off = 0; off < cls[k].count; off += piece) {
-            const int64_t begin = cls[k].begin + off, count = cls[k].count - off < piece ? cls[k].count - off : piece;
-            const int64_t ahead = (kLookAhead + max_used - 1) / max_used;
-            c.count = (int32_t)count;
-            c.ahead = (int32_t)(ahead < count ? ahead : count);
-            c.recs = run ? reinterpret_cast<PageRec*>(reinterpret_cast<PageRun*>(L.recs) + begin) : L.recs + begin;
-            c.sums = reinterpret_cast<uint64_t*>(L.partials) + begin * L.S;
-            c.out_index = L.out_index ? L.out_index + begin : nullptr;
-            c.out_first = begin;
-            const int64_t fp32 = run ? (L.state_first + begin) * L.E : 0, b16 = run ? (L.grad_first + begin) * L.E : 0;
-            c.p32 = L.p32 + fp32;
-            c.m32 = L.m32 + fp32;
-            c.v32 = L.v32 + fp32;
-            c.g16 = L.g16 + b16;
-            c.p16 = L.p16 + b16;
-            const dim3 grid((unsigned)(count * items)), block(kUpdThreads);
-            const unsigned lds = update_lds(L.gather || L.scatter, cls[k].sum_used, kClipLds);
-            if (run) hipLaunchKernelGGL((apm_adamw_clip_kernel<true, false, false>), grid, block, lds, s, c, a);
-            else if (L.gather && L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, true>), grid, block, lds, s, c, a);
-            else if (L.gather) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, false>), grid, block, lds, s, c, a);
-            else if (L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, false, true>), grid, block, lds, s, c, a);
-            else hipLaunchKernelGGL((apm_adamw_clip_kernel<false, false, false>), grid, block, lds, s, c, a);
-            hipError_t e = hipGetLastError();
+            ExtentClass part = cls[k];
+            part.begin += off;
+            part.count = cls[k].count - off < piece ? cls[k].count - off : piece;
+            const hipError_t e = go(&part, 1);
             if (e != hipSuccess) return e;
         }
     }

@@ -83,7 +83,8 @@ struct ExtentClass {
 // Sizes come as an array: a call's host time is spent here when its pages are many and small.
 // worth: idle spans of 1024 elements that a class has to save (kWorthLaunch, kWorthGrid).
 constexpr int64_t kWorthLaunch = 16384;  // for a launch, or a page list, of its own
-constexpr int64_t kWorthGrid = 64;       // for its part of a common grid
+constexpr int64_t kWorthGrid = 2048;     // for its part of the pages' common grid
+constexpr int64_t kWorthSegs = 64;       // and of the segments'
 int group_by_extent(int64_t n, int64_t E, const int32_t* size, int64_t* order, ExtentClass cls[kMaxExtentClasses],
                     int64_t worth = kWorthLaunch);
 
@@ -406,12 +407,17 @@ struct apm_pool {
     std::vector<apm::SegLaunch> seg_launches;
     int32_t seg_ranges = 0;         // groups of kArgWords tensors they are split into
     apm::TenantRec* d_tenants = nullptr;  // by page in use
-    // All pages in use, grouped by extent (see group_by_extent): launch order; d_order_out = the same as 32-bit
-    // output indices.  order_run: the order is 0, 1, 2, ... and has no tables.
+    // All pages in use, grouped by extent (see group_by_extent, kWorthGrid): launch order; d_order_out = the same as
+    // 32-bit output indices.  order_plain: the order is 0, 1, 2, ... and has no tables.
     int64_t* d_order = nullptr;
     int32_t* d_order_out = nullptr;
     apm::ExtentClass order_cls[apm::kMaxExtentClasses] = {};
     int order_n_cls = 0;
+    bool order_plain = false;
+    // With the classes that are worth a page list (kWorthLaunch) the order would be 0, 1, 2, ...: a step
+    // on the page classes takes the pages as a run, in these classes.
+    apm::ExtentClass run_cls[apm::kMaxExtentClasses] = {};
+    int run_n_cls = 0;
     bool order_run = false;
     int64_t layout_epoch = 0;  // counts the layouts installed
     double* d_partials = nullptr;   // reduce scratch, n_pages * S

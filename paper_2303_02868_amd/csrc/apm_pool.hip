@@ -166,7 +166,7 @@ void order_segments(const Plan& plan, SegRec* recs, std::vector<SegLaunch>* laun
             if (u > mx) mx = u;
         }
         ExtentClass cls[kMaxExtentClasses];
-        const int n_cls = group_by_extent(end - at, mx, size.data(), order.data(), cls, kWorthGrid);
+        const int n_cls = group_by_extent(end - at, mx, size.data(), order.data(), cls, kWorthSegs);
         const int64_t count = last + 1 - t0 < group ? last + 1 - t0 : group;
         SegLaunch l{{}, n_cls, (int32_t)t0, (int32_t)count};
         for (int c = 0; c < n_cls; ++c) {
@@ -193,16 +193,23 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     for (size_t k = 0; k < n_in_use; ++k) used_sum[k + 1] = used_sum[k] + used[k];
     std::vector<int64_t> order(n_in_use);
     ExtentClass cls[kMaxExtentClasses] = {};
-    const int n_cls = group_by_extent((int64_t)n_in_use, plan.E, used.data(), order.data(), cls);
-    bool run = true;
-    for (size_t k = 0; run && k < n_in_use; ++k) run = order[k] == (int64_t)k;
+    auto is_plain = [&] {
+        for (size_t k = 0; k < n_in_use; ++k)
+            if (order[k] != (int64_t)k) return false;
+        return true;
+    };
+    ExtentClass run_cls[kMaxExtentClasses] = {};
+    const int run_n_cls = group_by_extent((int64_t)n_in_use, plan.E, used.data(), order.data(), run_cls);
+    const bool run = is_plain();
+    const int n_cls = group_by_extent((int64_t)n_in_use, plan.E, used.data(), order.data(), cls, kWorthGrid);
+    const bool plain = is_plain();
     // Tables for the device, in one allocation and one upload; freed unless the pool takes it over at the end.
     struct Tables {
         char* d = nullptr;
         size_t at[4], bytes = 0;
         ~Tables() { if (d) (void)hipFree(d); }
     } tables;
-    const size_t n_order = run ? 0 : n_in_use;
+    const size_t n_order = plain ? 0 : n_in_use;
     const size_t len[4] = {plan.segs.size() * sizeof(SegRec), n_in_use * sizeof(TenantRec), n_order * sizeof(int64_t), n_order * sizeof(int32_t)};
     for (int k = 0; k < 4; ++k) {
         tables.at[k] = tables.bytes;
@@ -259,8 +266,13 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     if (pool->buffered && pool->buf_by_extent && pool->buf_extents.empty()) pool->buf_extents = std::move(used);
     pool->used_sum.swap(used_sum);
     pool->order_n_cls = n_cls;
+    pool->order_plain = plain;
+    pool->run_n_cls = run_n_cls;
     pool->order_run = run;
-    for (int c = 0; c < kMaxExtentClasses; ++c) pool->order_cls[c] = cls[c];
+    for (int c = 0; c < kMaxExtentClasses; ++c) {
+        pool->order_cls[c] = cls[c];
+        pool->run_cls[c] = run_cls[c];
+    }
     pool->layout_epoch += 1;
     pool->seg_launches.swap(launches);
     pool->seg_ranges = ranges;

@@ -45,12 +45,12 @@ int check_fused_list(const apm_pool* pool, const apm_tensor* t, int64_t n, const
 }
 
 // group_by_extent over the used extents of a call's pages.
-int group_pages(const apm_pool* pool, const int64_t* pages, int64_t n, int64_t* order, ExtentClass cls[kMaxExtentClasses]) {
+int group_pages(const apm_pool* pool, const int64_t* pages, int64_t n, int64_t* order, ExtentClass cls[kMaxExtentClasses], int64_t worth) {
     std::vector<int32_t> size;
     if (pool->used.empty()) size.assign((size_t)n, 0);
     else if (pages) size.resize((size_t)n);
     for (int64_t k = 0; pages && !pool->used.empty() && k < n; ++k) size[(size_t)k] = pool->used[(size_t)pages[k]];
-    return group_by_extent(n, pool->desc.page_elems, size.empty() ? pool->used.data() : size.data(), order, cls);
+    return group_by_extent(n, pool->desc.page_elems, size.empty() ? pool->used.data() : size.data(), order, cls, worth);
 }
 
 }  // namespace
@@ -128,19 +128,26 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
                 if (pages[k] >= in_use) return fail(APM_ERANGE, "pages[%lld] = %lld is not in use by the layout", (long long)k, (long long)pages[k]);
     }
     // The whole layout in its own order is the common case: its launch order came with the layout.
+    // An ascending run launched in the caller's order needs no indirection; on the page classes that is worth
+    // more than the finer classes of a common grid.
     const bool whole = !pages && n_pages == in_use;
+    const bool tensors = grad_tensors || p16_tensors;
     std::vector<int64_t> order;
-    bool run = whole && pool->order_run;  // an ascending run launched in the caller's order needs no indirection
+    bool run = whole && (tensors ? pool->order_plain : pool->order_run);
     if (whole) {
-        L.n_cls = pool->order_n_cls;
-        for (int c = 0; c < L.n_cls; ++c) L.cls[c] = pool->order_cls[c];
+        const bool as_run = run && !tensors;
+        L.n_cls = as_run ? pool->run_n_cls : pool->order_n_cls;
+        for (int c = 0; c < L.n_cls; ++c) L.cls[c] = as_run ? pool->run_cls[c] : pool->order_cls[c];
     } else {
         order.resize((size_t)n_pages);
-        L.n_cls = group_pages(pool, pages, n_pages, order.data(), L.cls);
-        run = true;
-        for (int64_t k = 0; run && k < n_pages; ++k) run = order[(size_t)k] == k && page_at(k) == page_at(0) + k;
+        auto group = [&](int64_t worth) {
+            L.n_cls = group_pages(pool, pages, n_pages, order.data(), L.cls, worth);
+            run = true;
+            for (int64_t k = 0; run && k < n_pages; ++k) run = order[(size_t)k] == k && page_at(k) == page_at(0) + k;
+        };
+        group(tensors ? kWorthGrid : kWorthLaunch);
+        if (!tensors && !run) group(kWorthGrid);
     }
-    const bool tensors = grad_tensors || p16_tensors;
     const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
     rc = ensure_scratch(pool, !run && !whole);
     if (rc != APM_OK) return rc;
@@ -368,7 +375,7 @@ static int take_gradient(apm_pool* pool, int k, const uint16_t* g16, const int64
     GradTake t{g16, pool->gbuf[k], accumulate, pool->d_used, pool->desc.page_elems, pool->S, sums ? pool->gsum[k] : nullptr,
                sums ? pool->gnz[k] : nullptr, nullptr, nullptr, 0, pool->order_cls, pool->order_n_cls};
     if (!pages && n_pages == in_use) {
-        t.order = pool->order_run ? nullptr : pool->d_order;
+        t.order = pool->order_plain ? nullptr : pool->d_order;
         APM_HIP(launch_grad_take(t, s));
         return APM_OK;
     }
@@ -378,8 +385,8 @@ static int take_gradient(apm_pool* pool, int k, const uint16_t* g16, const int64
     bool run = true;
     for (int64_t i = 1; run && pages && i < n_pages; ++i) run = pages[i] == pages[0] + i;
     // Consecutive pages need no list, and with the extents taken as the layout's largest no look-up, at the price of
-    // workgroups without work where pages differ much: a list in one launch per class is the better form then.
-    if (run && (n_pages > kTakePages || pool->order_n_cls <= 1)) {
+    // workgroups without work where pages differ much: a list is the better form then.
+    if (run && (n_pages > kTakePages || pool->run_n_cls <= 1)) {
         cls[0] = ExtentClass{0, n_pages, pool->order_n_cls > 0 ? pool->order_cls[0].max_used : 0, 0};
         t.n_cls = 1;
         t.first = page_at(0);
@@ -387,10 +394,9 @@ static int take_gradient(apm_pool* pool, int k, const uint16_t* g16, const int64
         return APM_OK;
     }
     std::vector<int64_t> order((size_t)n_pages);
-    t.n_cls = group_pages(pool, pages, n_pages, order.data(), cls);
+    t.n_cls = group_pages(pool, pages, n_pages, order.data(), cls, kWorthGrid);
     for (int64_t& i : order) i = page_at(i);
-    int64_t launches = 0;
-    for (int c = 0; c < t.n_cls; ++c) launches += (cls[c].count + kTakePages - 1) / kTakePages;
+    const int64_t launches = (n_pages + kTakePages - 1) / kTakePages;
     int slot = -1;
     if (launches > kMaxTakeLaunches) {
         const size_t bytes = (size_t)n_pages * sizeof(int64_t);

@@ -336,6 +336,59 @@ def test_updates_in_several_launches_equal_one_launch(form, skip, cap):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("clip,skip", [(0.0, 0), (0.05, 0), (0.05, 1)])
+@pytest.mark.parametrize("form", ["whole", "reversed", "fused", "fused reversed", "delayed"])
+def test_extents_of_every_class_in_one_grid_equal_steps_page_by_page(form, clip, skip):
+    """Full, quarter, small and nearly empty pages, as many of each as make a class of their own in the common
+    grid.  Same bits as one call for every page, which has no classes."""
+    E = 1 << 18
+    numels = [E * 2 + 9, 8000, 500] + [60000] * 12 + [8001] * 60 + [7, 500] * 250 + [E]
+    n_t, off, plan = len(numels), [0], oracle.plan_pack(numels, E)
+    for m in numels:
+        off.append(off[-1] + (m + 7) // 8 * 8)
+    gen = torch.Generator(device=DEV).manual_seed(7)
+    g = (torch.randn(off[-1], device=DEV, generator=gen) * 1e-2).bfloat16()
+    g[off[5]:off[9]] = 0
+    g[off[100]:off[300]] = 0
+    p0 = torch.randn(off[-1], device=DEV, generator=gen) * 0.02
+    lst = lambda t: apm.make_tensors(numels, apm.APM_F32 if t.dtype == torch.float32 else apm.APM_BF16,  # noqa: E731
+                                     [t.data_ptr() + t.element_size() * o for o in off[:-1]])
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, clip, skip)
+    got = []
+    for each in (True, False):
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, plan.n_pages)
+        apm.apm_pack_tensors(pool, apm.APM_P32, lst(p0), n_t)
+        apm.apm_pack_tensors(pool, apm.APM_G16, lst(g), n_t)
+        n = plan.n_pages
+        norm, mask, q = torch.full((n,), -1.0, device=DEV), torch.full((n,), 9, device=DEV, dtype=torch.uint8), torch.zeros_like(g)
+        pages = list(range(n))[::-1] if "reversed" in form else None
+        if each:
+            for k in range(n):
+                at = n - 1 - k if pages else k
+                apm.apm_page_adamw_step(pool, [k], 1, 1, hyper, norm[at:], mask[at:])
+        elif "fused" in form:
+            apm.apm_page_adamw_step_fused(pool, pages, n, 1, hyper, lst(g), lst(q), n_t, norm, mask)
+        elif form == "delayed":
+            g_pages = torch.as_tensor(_Region(pool, apm.APM_G16, n * E), device=DEV)
+            apm.apm_delayed_set_outputs(pool, norm, mask)
+            apm.apm_step_delayed(pool, None, n, g_pages.data_ptr(), hyper)
+            apm.apm_step_delayed(pool, None, n, None, hyper)
+        else:
+            apm.apm_page_adamw_step(pool, pages, n, 1, hyper, norm, mask)
+        if each or "fused" not in form:
+            apm.apm_unpack(pool, apm.APM_P16, lst(q), n_t)
+        out = [norm, mask, q]
+        for st in (apm.APM_P32, apm.APM_M32, apm.APM_V32):
+            out.append(torch.zeros_like(p0))
+            apm.apm_unpack(pool, st, lst(out[-1]), n_t)
+        torch.cuda.synchronize()
+        got.append(out)
+        pool.destroy()
+    assert (got[0][1].sum() > 0) == bool(skip)
+    for k, (a, b) in enumerate(zip(*got)):
+        assert torch.equal(a, b), k
+
+
 def _us(f, n):
     """Best of five batches of n calls, microseconds a call."""
     best = float("inf")
