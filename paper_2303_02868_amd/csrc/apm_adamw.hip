@@ -26,6 +26,7 @@
 // to tensors, launches of their own / one grid / nearly empty pages last: 124 M parameters 538 / 525 / 526; 4.8 M in 256 K
 // pages 31.3 / 26.2 / 25.8, with clipping 40.5 / 32.7 / 36.7; 11 M with clipping 67.9 / 59.5 / 62.7.
 #include <cstring>
+#include <type_traits>
 
 #include "apm_internal.h"
 
@@ -475,10 +476,17 @@ struct StageArgs {
     int32_t list_n;
     int32_t t_begin, t_n;       // the g / q words are those of tensors [t_begin, + t_n)
     int32_t has_g, has_q;
+    uint64_t g_base, q_base;    // StageArgsNarrow
 };
 struct StageArgsInline {
     StageArgs a;
     uint64_t word[kArgWords];
+};
+// Half words: pages, then output indices, of the list; addresses as multiples of 16 from their list's base.  A launch less for
+// 220 to 440 tensors, two for 150 listed pages of 274: 4 to 5 us each.
+struct StageArgsNarrow {
+    StageArgs a;
+    uint32_t word[2 * kArgWords];
 };
 
 template <class Args>
@@ -487,20 +495,23 @@ __global__ __launch_bounds__(kThreads) void apm_stage_kernel(Args args) {
     if constexpr (sizeof(Args) > sizeof(StageArgs)) ap = &args.a;
     else ap = &args;
     const StageArgs& a = *ap;
+    constexpr bool kNarrow = std::is_same<Args, StageArgsNarrow>::value;
     auto word = [&](int64_t k) -> uint64_t {
         if constexpr (sizeof(Args) > sizeof(StageArgs)) return args.word[k];
         else return a.words[k];
     };
+    auto address = [&](int64_t k, uint64_t base) -> uint64_t { return kNarrow ? base + (word(k) << 4) : word(k); };
+    const int64_t list_words = (kNarrow ? 2 : 1) * (int64_t)a.list_n;
     if (a.sums) clear_sums(a.sums, a.n_sums);
     int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     int64_t page;
     if (a.list_n > 0) {
         if (i >= a.list_n) return;
-        const uint64_t w = word(i);
+        const uint64_t w = word(i), out = kNarrow ? word(a.list_n + i) : w >> 32;
         i += a.list_begin;
         page = (int64_t)(uint32_t)w;
         a.list[i] = page;
-        a.out[i] = (int32_t)(w >> 32);
+        a.out[i] = (int32_t)out;
     } else {
         if (i >= a.n_listed) return;
         page = a.pages ? a.pages[i] : a.first + i;
@@ -527,8 +538,8 @@ __global__ __launch_bounds__(kThreads) void apm_stage_kernel(Args args) {
         } else if (at >= 0 && at < a.t_n) {
             const int off = k == 0 ? 0 : t.off1;
             out->end[k] = off + t.n[k];
-            out->g[k] = a.has_g ? reinterpret_cast<const uint16_t*>(word(a.list_n + at)) + t.tensor_off[k] - off : own.g[0];
-            out->q[k] = a.has_q ? reinterpret_cast<uint16_t*>(word(a.list_n + (a.has_g ? a.t_n : 0) + at)) + t.tensor_off[k] - off : own.q[0];
+            out->g[k] = a.has_g ? reinterpret_cast<const uint16_t*>(address(list_words + at, a.g_base)) + t.tensor_off[k] - off : own.g[0];
+            out->q[k] = a.has_q ? reinterpret_cast<uint16_t*>(address(list_words + (a.has_g ? a.t_n : 0) + at, a.q_base)) + t.tensor_off[k] - off : own.q[0];
         }
     }
 }
@@ -1299,9 +1310,10 @@ hipError_t launch_prepare(const AdamwLaunch& L, hipStream_t s) {
     return hipGetLastError();
 }
 
-int64_t stage_launches(int64_t n_list, int64_t lists, int64_t n_tensors) {
-    if (n_list + lists * n_tensors <= kArgWords) return 1;
-    const int64_t per = lists ? kArgWords / lists : kArgWords;
+int64_t stage_launches(int64_t n_list, int64_t lists, int64_t n_tensors, bool narrow) {
+    const int64_t room = narrow ? 2 * kArgWords : kArgWords;
+    if ((narrow ? 2 : 1) * n_list + lists * n_tensors <= room) return 1;
+    const int64_t per = lists ? room / lists : room;
     return (n_list + kArgWords - 1) / kArgWords + (lists ? (n_tensors + per - 1) / per : 0);
 }
 
@@ -1309,10 +1321,10 @@ hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s)
     const bool has_g = c.g_ptrs != nullptr, has_q = c.q_ptrs != nullptr;
     const int64_t n_list = c.list ? L.n_listed : 0, n_t = has_g || has_q ? c.n_tensors : 0;
     StageArgsInline in;
-    StageArgs& a = in.a;
-    a = StageArgs{L.used, c.list ? c.d_list : L.grad_pages, L.grad_first, L.n_listed, c.tenants, L.recs, L.g16, L.p16, L.E,
+    StageArgsNarrow half;
+    StageArgs a{L.used, c.list ? c.d_list : L.grad_pages, L.grad_first, L.n_listed, c.tenants, L.recs, L.g16, L.p16, L.E,
                   c.d_list, c.d_out, L.one_pass ? reinterpret_cast<uint64_t*>(L.partials) : nullptr,
-                  L.one_pass ? L.n_listed * L.S : 0, c.d_words, 0, 0, 0, 0, has_g, has_q};
+                  L.one_pass ? L.n_listed * L.S : 0, c.d_words, 0, 0, 0, 0, has_g, has_q, c.g_base, c.q_base};
     auto go = [&](int64_t list_begin, int64_t list_n, int64_t t_begin, int64_t t_n) -> hipError_t {
         a.list_begin = list_begin;
         a.list_n = (int32_t)list_n;
@@ -1323,7 +1335,17 @@ hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s)
         const dim3 grid(pages_grid > sums_grid ? pages_grid : sums_grid);
         if (c.d_words) {
             hipLaunchKernelGGL(apm_stage_kernel<StageArgs>, grid, dim3(kThreads), 0, s, a);
+        } else if (c.narrow) {
+            uint32_t* w = half.word;
+            for (int64_t k = 0; k < list_n; ++k) *w++ = (uint32_t)c.list[list_begin + k];
+            for (int64_t k = 0; k < list_n; ++k) *w++ = (uint32_t)(c.list[list_begin + k] >> 32);
+            // an empty tensor's address may be anything: it is nobody's tenant
+            for (int64_t k = 0; has_g && k < t_n; ++k) *w++ = (uint32_t)((c.g_ptrs[t_begin + k] - c.g_base) >> 4);
+            for (int64_t k = 0; has_q && k < t_n; ++k) *w++ = (uint32_t)((c.q_ptrs[t_begin + k] - c.q_base) >> 4);
+            half.a = a;
+            hipLaunchKernelGGL(apm_stage_kernel<StageArgsNarrow>, grid, dim3(kThreads), 0, s, half);
         } else {
+            in.a = a;
             uint64_t* w = in.word;
             if (list_n > 0) std::memcpy(w, c.list + list_begin, (size_t)list_n * sizeof(uint64_t));
             w += list_n;
@@ -1335,13 +1357,13 @@ hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s)
         a.sums = nullptr;  // marked by the first launch
         return hipGetLastError();
     };
-    if (c.d_words || stage_launches(n_list, has_g + has_q, n_t) == 1) return go(0, n_list, 0, n_t);
+    if (c.d_words || stage_launches(n_list, has_g + has_q, n_t, c.narrow) == 1) return go(0, n_list, 0, n_t);
     // list words first: the launches with the addresses read the list that they wrote
     for (int64_t k = 0; k < n_list; k += kArgWords) {
         hipError_t e = go(k, n_list - k < kArgWords ? n_list - k : kArgWords, 0, 0);
         if (e != hipSuccess) return e;
     }
-    const int64_t per = has_g && has_q ? kArgWords / 2 : kArgWords;
+    const int64_t per = (c.narrow ? 2 : 1) * kArgWords / (has_g && has_q ? 2 : 1);
     for (int64_t k = 0; k < n_t; k += per) {
         hipError_t e = go(0, 0, k, n_t - k < per ? n_t - k : per);
         if (e != hipSuccess) return e;

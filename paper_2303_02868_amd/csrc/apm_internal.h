@@ -299,10 +299,14 @@ struct StageCall {
     int64_t* d_list;              // written if `list`
     int32_t* d_out;
     const uint64_t* d_words;      // list, g_ptrs, q_ptrs one after the other in device memory, or nullptr
+    // Carried in kernel arguments, the words are halved if every address lies less than 64 GiB beyond its list's
+    // base, as they do but for lists that several allocations far apart make up.
+    bool narrow;
+    uint64_t g_base, q_base;      // multiples of 16, as all addresses are
 };
 // Launches it takes to carry a call's words in kernel arguments (StageCall::d_words == nullptr): n_list list
-// words and `lists` (0..2) lists of n_tensors addresses.
-int64_t stage_launches(int64_t n_list, int64_t lists, int64_t n_tensors);
+// words and `lists` (0..2) lists of n_tensors addresses.  narrow: as 32-bit words, two per list word.
+int64_t stage_launches(int64_t n_list, int64_t lists, int64_t n_tensors, bool narrow);
 hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s);
 hipError_t launch_adamw(const AdamwLaunch& a, hipStream_t s);
 // Norms, clip scales and update in one kernel, after the stage / prepare pass of a launch with

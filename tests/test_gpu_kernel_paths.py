@@ -389,6 +389,52 @@ def test_extents_of_every_class_in_one_grid_equal_steps_page_by_page(form, clip,
         assert torch.equal(a, b), k
 
 
+@pytest.mark.parametrize("listed", ["all", "reversed"])
+@pytest.mark.parametrize("n_t,apart", [(300, 0), (300, 66 << 30), (439, 0), (441, 0), (441, 66 << 30), (2000, 0)])
+def test_fused_step_with_tensors_near_and_far_apart(n_t, apart, listed):
+    """Addresses travel as half words where a list's tensors lie within 64 GiB, as whole words elsewhere; tensor counts
+    around what one launch carries either way, and empty tensors with any address.  Same bits as the page step."""
+    if apart and torch.cuda.mem_get_info()[0] < apart + (8 << 30):
+        pytest.skip("not enough free device memory")
+    E = 64
+    numels = [(0, 3, E, 2 * E + 5, 17)[k % 5] for k in range(n_t)]
+    off = [sum((m + 7) // 8 * 8 for m in numels[:k]) for k in range(n_t)]
+    room = off[-1] + 256
+    gen = torch.Generator(device=DEV).manual_seed(n_t)
+    raw = torch.empty(apart + 8 * room + 64, dtype=torch.uint8, device=DEV)
+    at = [(apart if k % 3 == 1 else 0) + 2 * o for k, o in enumerate(off)]  # every third tensor at the far end
+    place = lambda base: apm.make_tensors(numels, apm.APM_BF16, [base + x if m else 7 for x, m in zip(at, numels)])  # noqa: E731
+    g_flat = (torch.randn(room, device=DEV, generator=gen) * 1e-2).bfloat16()
+    near = raw[:2 * room].view(torch.bfloat16), raw[apart:apart + 2 * room].view(torch.bfloat16)
+    for part in near:
+        part.copy_(g_flat)
+    q_near = [raw[a + 2 * room:a + 4 * room].view(torch.bfloat16) for a in (0, apart)]
+    for part in q_near:
+        part.zero_()
+    n = oracle.plan_pack(numels, E).n_pages
+    pages = list(range(n))[::-1] if listed == "reversed" else None
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.05, 0)
+    p0, out = torch.randn(room, device=DEV, generator=gen), []
+    for fused in (False, True):
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n)
+        apm.apm_pack_tensors(pool, apm.APM_P32, apm.make_tensors(numels, apm.APM_F32, [p0.data_ptr() + 4 * o if m else 0 for o, m in zip(off, numels)]), n_t)
+        norm, q = torch.zeros(n, device=DEV), torch.zeros_like(g_flat)
+        if fused:
+            apm.apm_page_adamw_step_fused(pool, pages, n, 1, hyper, place(raw.data_ptr()), place(raw.data_ptr() + 2 * room), n_t, norm, None)
+            for k, (o, m) in enumerate(zip(off, numels)):
+                q[o:o + m] = q_near[k % 3 == 1][o:o + m]
+        else:
+            tight = lambda t: apm.make_tensors(numels, apm.APM_BF16, [t.data_ptr() + 2 * o if m else 0 for o, m in zip(off, numels)])  # noqa: E731
+            apm.apm_pack_tensors(pool, apm.APM_G16, tight(g_flat), n_t)
+            apm.apm_page_adamw_step(pool, pages, n, 1, hyper, norm, None)
+            apm.apm_unpack(pool, apm.APM_P16, tight(q), n_t)
+        torch.cuda.synchronize()
+        out.append((norm, q))
+        pool.destroy()
+    assert (out[0][0] > 0).all()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
 def _us(f, n):
     """Best of five batches of n calls, microseconds a call."""
     best = float("inf")
