@@ -577,7 +577,9 @@ template <int U> constexpr int kTile = kUpdThreads * 4 * U;  // elements per wav
 //               lines in the L2 until they are evicted, in another order than the slices': 201 M parameters
 //               876 us a call without, 868 with; with clipping 907 and 892 (written through alone: 867, but
 //               with clipping 946);
-//   kStoreHost  non-temporal, for state in host memory;
+//   kStoreHost  non-temporal, for state in host memory, and for state in device memory that is updated beside the
+//               staged pipeline's copy kernel (124 M parameters from pinned memory: 34.5 ms a step written through
+//               besides, 34.0 without);
 //   kStoreHostWT  written through, for the same while other kernels run on the GPU: a non-temporal store
 //               to host memory may rest in the L2 as a dirty line; the write-back that ends every kernel of any
 //               other stream then has to push it across PCIe, so those kernels pay for this kernel's writes.
@@ -726,7 +728,7 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_kernel(const PageRec* r
 // The same for a run of pages in the page classes; all pointers are those of the launch's first page.
 // BARE: nothing has written records, `runs` is the page table (int32_t) and the scale is 1: a launch less,
 // eight quarter pages 13.2 -> 10.8 us a call.
-template <int U, bool BARE>
+template <int U, bool BARE, int STORE>
 __global__ __launch_bounds__(kUpdThreads) void apm_adamw_run_kernel(const void* runs, float* p32, float* m32, float* v32,
                                                                     const uint16_t* g16, uint16_t* p16, int E, UpdateArgs a) {
     PageRun run{0, 1.0f};
@@ -736,7 +738,7 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_run_kernel(const void* 
     const PageRec rec = class_rec(run.used, run.scale, 0, 0, 0, g16 + at, p16 + at);
     const int start = (int)blockIdx.x * kTile<U>;
     if ((!BARE && rec.scale < 0.0f) || start >= rec.end[0]) return;
-    update_slice<U, false, false>(a, rec, start, (int)threadIdx.x, p32 + at, m32 + at, v32 + at);
+    update_slice<U, false, false, STORE>(a, rec, start, (int)threadIdx.x, p32 + at, m32 + at, v32 + at);
 }
 
 // Over the pages that the finalize pass noted, a class's `slices.per` slices each.  live: see kLiveInts;
@@ -757,7 +759,7 @@ __device__ __forceinline__ LiveClasses::Class load_class(const LiveClasses::Clas
     asm("" : "+s"(w));
     return __builtin_bit_cast(LiveClasses::Class, w);
 }
-template <int U, bool RUN, bool GATHER, bool SCATTER>
+template <int U, bool RUN, bool GATHER, bool SCATTER, int STORE = kStoreHbm>
 __global__ __launch_bounds__(kUpdThreads) void apm_adamw_live_kernel(const int32_t* live, const PageRec* recs, float* p32, float* m32, float* v32,
                                                                      const uint16_t* g16, uint16_t* p16, int64_t E, UpdateArgs a, LiveClasses lc) {
     typedef const int32_t __attribute__((address_space(4))) * Const;
@@ -787,7 +789,7 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_live_kernel(const int32
         }
         const int start = (int)x * kTile<U>;
         if (start < ((rec.used + 7) & ~7))
-            update_slice<U, GATHER, SCATTER>(a, rec, start, (int)threadIdx.x, p32 + at, m32 + at, v32 + at);
+            update_slice<U, GATHER, SCATTER, STORE>(a, rec, start, (int)threadIdx.x, p32 + at, m32 + at, v32 + at);
     }
 }
 
@@ -1438,10 +1440,12 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
             for (; k < kMaxExtentClasses; ++k) lc.cls[k].first = (uint32_t)at;
             if (at > 0) {
                 const dim3 grid((unsigned)at), block(kUpdThreads);
-#define APM_LAUNCH_LIVE(U, RUN, G, Q) hipLaunchKernelGGL((apm_adamw_live_kernel<U, RUN, G, Q>), grid, block, kSkipLds, s, L.live, \
+#define APM_LAUNCH_LIVE(...) hipLaunchKernelGGL((apm_adamw_live_kernel<__VA_ARGS__>), grid, block, kSkipLds, s, L.live, \
                                                      L.recs, state(L.p32, 0), state(L.m32, 0), state(L.v32, 0), run ? g16(0) : nullptr,  \
                                                      run ? p16(0) : nullptr, L.E, a, lc)
-                if (wide) APM_LAUNCH_LIVE(kWideU, true, false, false);
+                if (wide && L.beside_link) APM_LAUNCH_LIVE(kWideU, true, false, false, kStoreHost);
+                else if (wide) APM_LAUNCH_LIVE(kWideU, true, false, false);
+                else if (run && L.beside_link) APM_LAUNCH_LIVE(U, true, false, false, kStoreHost);
                 else if (run) APM_LAUNCH_LIVE(U, true, false, false);
                 else if (L.gather && L.scatter) APM_LAUNCH_LIVE(U, false, true, true);
                 else if (L.gather) APM_LAUNCH_LIVE(U, false, true, false);
@@ -1481,12 +1485,14 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         const int tile = wide ? kTile<kWideU> : kTile<U>;
         const dim3 grid((unsigned)((max_used + tile - 1) / tile), (unsigned)ny), block(kUpdThreads);
         const unsigned lds = update_lds(false, sum_used, APM_UPDATE_LDS);
-#define APM_LAUNCH_RUN(U, BARE, RUNS) hipLaunchKernelGGL((apm_adamw_run_kernel<U, BARE>), grid, block, lds, s, RUNS, state(L.p32, begin), \
+#define APM_LAUNCH_RUN(U, BARE, STORE, RUNS) hipLaunchKernelGGL((apm_adamw_run_kernel<U, BARE, STORE>), grid, block, lds, s, RUNS, state(L.p32, begin), \
                                                          state(L.m32, begin), state(L.v32, begin), g16(begin), p16(begin), (int)L.E, a)
-        if (wide && L.bare_run) APM_LAUNCH_RUN(kWideU, true, L.used + L.grad_first + begin);
-        else if (wide) APM_LAUNCH_RUN(kWideU, false, runs + begin);
-        else if (L.bare_run) APM_LAUNCH_RUN(U, true, L.used + L.grad_first + begin);
-        else APM_LAUNCH_RUN(U, false, runs + begin);
+        if (wide && L.beside_link) APM_LAUNCH_RUN(kWideU, false, kStoreHost, runs + begin);
+        else if (L.beside_link) APM_LAUNCH_RUN(U, false, kStoreHost, runs + begin);
+        else if (wide && L.bare_run) APM_LAUNCH_RUN(kWideU, true, kStoreHbm, L.used + L.grad_first + begin);
+        else if (wide) APM_LAUNCH_RUN(kWideU, false, kStoreHbm, runs + begin);
+        else if (L.bare_run) APM_LAUNCH_RUN(U, true, kStoreHbm, L.used + L.grad_first + begin);
+        else APM_LAUNCH_RUN(U, false, kStoreHbm, runs + begin);
 #undef APM_LAUNCH_RUN
     });
 }

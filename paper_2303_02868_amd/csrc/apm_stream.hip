@@ -300,6 +300,7 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
     apm_pool* host = s->host;
     if (!dev->has_layout) return fail(APM_ESTATE, "the GPU pool has no layout");
     AdamwLaunch L{};
+    L.beside_link = true;
     int rc = APM_OK;
     if (what & kDoUpdate) rc = prepare_hyper(hyper, step, &L);
     if (rc != APM_OK) return rc;
@@ -799,6 +800,7 @@ extern "C" int apm_streamer_step_scheduled(apm_streamer* s, const apm_task* task
         if (s->cache || s->host_first != 0 || s->page_limit >= 0) return fail(APM_ESTATE, "the scheduled step does not combine with a resident cache or a page range");
         if (s->host->desc.n_pages < N) return fail(APM_ESTATE, "the host pool holds fewer pages than are in use");
         AdamwLaunch L{};
+        L.beside_link = true;
         int rc = prepare_hyper(hyper, step, &L);
         if (rc != APM_OK) return rc;
         APM_HIP(hipSetDevice(dev->desc.hip_device));
