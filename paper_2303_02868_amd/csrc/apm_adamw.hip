@@ -1504,7 +1504,12 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         const unsigned lds = update_lds(false, sum_used, APM_UPDATE_LDS);
 #define APM_LAUNCH_RUN(U, BARE, STORE, RUNS) hipLaunchKernelGGL((apm_adamw_run_kernel<U, BARE, STORE>), grid, block, lds, s, RUNS, state(L.p32, begin), \
                                                          state(L.m32, begin), state(L.v32, begin), g16(begin), p16(begin), (int)L.E, a)
-        if (wide && L.beside_link) APM_LAUNCH_RUN(kWideU, false, kStoreHost, runs + begin);
+        // Few elements: what a call leaves in the L2s serves the next one, written through or not, but the stores end
+        // sooner (us a call, 2 M elements in 8 pages, written through / not: one state again and again 10.7 / 8.9, three
+        // in turn 10.75 / 10.6, eight 11.5 / 11.2).
+        const bool few = L.bare_run && sum_used <= kFewRunElems;
+        if (few && !wide) APM_LAUNCH_RUN(U, true, kStoreHost, L.used + L.grad_first + begin);
+        else if (wide && L.beside_link) APM_LAUNCH_RUN(kWideU, false, kStoreHost, runs + begin);
         else if (L.beside_link) APM_LAUNCH_RUN(U, false, kStoreHost, runs + begin);
         else if (wide && L.bare_run) APM_LAUNCH_RUN(kWideU, true, kStoreHbm, L.used + L.grad_first + begin);
         else if (wide) APM_LAUNCH_RUN(kWideU, false, kStoreHbm, runs + begin);
