@@ -135,14 +135,14 @@ APM_HOST_DEVICE inline void grid_item(uint32_t large_at, GridDiv d, const GridCl
     *x = w - q * d.per;
 }
 // Calls launch(map, workgroups, first position of the largest class in it) for all classes at once, or, where
-// that is more than one grid holds (or more than `limit` > 0), class by class in pieces that it holds.
-// per(class): workgroups an item takes, >= 1.  Returns the first non-zero result.
+// that is more than one grid holds (or more than `limit` > 0), class by class in pieces that it holds; not at all where
+// there are no items.  per(class): workgroups an item takes, >= 1.  Returns the first non-zero result.
 template <class Per, class Launch>
 int for_each_grid(const ExtentClass* cls, int n_cls, int threads, int64_t limit, Per&& per, Launch&& launch) {
     int64_t total = 0;
     const int64_t cap = limit > 0 ? limit : max_workgroups(threads);
     for (int c = 0; c < n_cls; ++c) total += cls[c].count * per(cls[c]);
-    if (n_cls <= 0) return 0;
+    if (total == 0) return 0;
     if (total <= cap) {
         GridMap m{};
         int64_t at = 0;

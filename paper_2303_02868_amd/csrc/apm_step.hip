@@ -384,6 +384,7 @@ constexpr int64_t kMaxTakeLaunches = 4;
 // Copies or adds the used extents of the listed pages of g16 into half k.
 static int take_gradient(apm_pool* pool, int k, const uint16_t* g16, const int64_t* pages, int64_t n_pages, bool accumulate,
                          bool sums, hipStream_t s) {
+    if (n_pages == 0) return APM_OK;
     const int64_t in_use = (int64_t)pool->plan.pages.size();
     GradTake t{g16, pool->gbuf[k], accumulate, pool->d_used, pool->desc.page_elems, pool->S, sums ? pool->gsum[k] : nullptr,
                sums ? pool->gnz[k] : nullptr, nullptr, nullptr, 0, pool->order_cls, pool->order_n_cls};

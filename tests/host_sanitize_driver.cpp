@@ -223,7 +223,8 @@ void launch_pieces(Rng& r) {
 }
 
 // Every workgroup of a common grid belongs to one (item, number), each of which has one workgroup; classes that do
-// not fit together go apart.  And the division by multiplication against the division.
+// not fit together go apart; where there is nothing to do there is no launch (a grid of zero is refused).  And the
+// division by multiplication against the division.
 void common_grid(Rng& r) {
     for (int i = 0; i < 200; ++i) {
         const int64_t per = 1 + r.below((int64_t)1 << (1 + r.below(23)));
@@ -242,7 +243,7 @@ void common_grid(Rng& r) {
         int64_t at = r.below(50);
         int64_t per[apm::kMaxExtentClasses];
         for (int c = 0; c < n_cls; ++c) {
-            cls[c] = apm::ExtentClass{at, 1 + r.below(40), 0, 0};
+            cls[c] = apm::ExtentClass{at, n_cls == 1 ? r.below(3) : 1 + r.below(40), 0, 0};
             per[c] = cls[c].max_used = 1 + r.below(30);
             at += cls[c].count;
         }
@@ -252,6 +253,7 @@ void common_grid(Rng& r) {
             for (int64_t k = 0; k < cls[c].count; ++k) seen[(size_t)(cls[c].begin + k)].assign((size_t)per[c], 0);
         apm::for_each_grid(cls, n_cls, 64, limit, [](const apm::ExtentClass& e) { return e.max_used; },
                            [&](const apm::GridMap& m, int64_t workgroups, int64_t first) {
+            if (workgroups <= 0) die("launch without workgroups", workgroups, first);
             for (int64_t w = 0; w < workgroups; ++w) {
                 int item;
                 uint32_t x;

@@ -230,6 +230,33 @@ def test_delayed_hand_over_equals_the_synchronous_step(E, n_t, listed, micro, sh
         pool.destroy()
 
 
+@pytest.mark.parametrize("clip", [0.0, 0.02])
+@pytest.mark.parametrize("numels", [[3 * 4096 + 5], [4096, 9, 9, 9]])
+def test_a_hand_over_of_no_pages_is_accepted(numels, clip):
+    """An iteration that touched no listed page: the gradient handed over before is applied, nothing is taken over and
+    the next call applies nothing (layouts of one extent class and of several)."""
+    E, n_t = 4096, len(numels)
+    n = oracle.plan_pack(numels, E).n_pages
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, clip, 0)
+    g = (torch.randn(n * E, device=DEV, generator=torch.Generator(device=DEV).manual_seed(n)) * 1e-2).bfloat16()
+    got = []
+    for empty in (None, [], "null"):
+        pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n)
+        apm.apm_pool_set_layout(pool, apm.make_tensors(numels, apm.APM_F32, [0] * n_t), n_t)
+        apm.apm_step_delayed(pool, None, n, g.data_ptr(), hyper)
+        if empty is not None:
+            pages = None if empty == "null" else empty
+            apm.apm_step_delayed(pool, pages, 0, g.data_ptr(), hyper)
+            apm.apm_delayed_accumulate(pool, pages, 0, g.data_ptr())
+        apm.apm_step_delayed(pool, None, n, None, hyper)
+        out = [torch.zeros(m, device=DEV) for m in numels]
+        apm.apm_unpack(pool, apm.APM_M32, apm.make_tensors(numels, apm.APM_F32, [o.data_ptr() for o in out]), n_t)
+        torch.cuda.synchronize()
+        got.append(torch.cat(out))
+        pool.destroy()
+    assert got[0].any() and torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+
+
 class _Region:
     """A 16-bit class region of a pool as an array torch can wrap."""
 
