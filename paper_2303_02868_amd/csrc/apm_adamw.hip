@@ -594,9 +594,9 @@ template <int U> constexpr int kTile = kUpdThreads * 4 * U;  // elements per wav
 //               lines in the L2 until they are evicted, in another order than the slices': 201 M parameters
 //               876 us a call without, 868 with; with clipping 907 and 892 (written through alone: 867, but
 //               with clipping 946);
-//   kStoreHost  non-temporal, for state in host memory, and for state in device memory that is updated beside the
-//               staged pipeline's copy kernel (124 M parameters from pinned memory: 34.5 ms a step written through
-//               besides, 34.0 without);
+//   kStoreNT    non-temporal, for state in host memory, and for state in device memory that is updated beside a
+//               kernel that moves pages across the link (124 M parameters from pinned memory, staged: 34.5 ms a
+//               step written through besides, 34.0 without; driven by a schedule: 42.2 and 41.9, 355 M 101.9 and 100.1);
 //   kStoreHostWT  written through, for the same while other kernels run on the GPU: a non-temporal store
 //               to host memory may rest in the L2 as a dirty line; the write-back that ends every kernel of any
 //               other stream then has to push it across PCIe, so those kernels pay for this kernel's writes.
@@ -607,7 +607,7 @@ template <int U> constexpr int kTile = kUpdThreads * 4 * U;  // elements per wav
 // merges or moves between this body and the checked one below: 124 M parameters 599 us a call without
 // the hint at one vector per lane, 548 with it.)
 constexpr int kNT = 2, kSC1 = 16;
-constexpr int kStoreHbm = kNT | kSC1, kStoreHost = kNT, kStoreHostWT = kSC1;
+constexpr int kStoreHbm = kNT | kSC1, kStoreNT = kNT, kStoreHostWT = kSC1;
 typedef __amdgpu_buffer_rsrc_t Rsrc;
 
 // [base, base + bytes): accesses beyond it read zero / are dropped.
@@ -714,7 +714,7 @@ __device__ __forceinline__ void cut_slice(const UpdateArgs& a, const PageRec& re
 // 12 B + 2 B read and 12 B + 2 B written per element.  Each lane keeps U 128-bit vectors per
 // fp32 class in flight; every wavefront-wide access is one contiguous 1 KiB (fp32) or 512 B (bf16)
 // span.  p, m, v: the page's first element.
-template <int U, bool GATHER, bool SCATTER, int STORE = kStoreHbm>
+template <int U, bool GATHER, bool SCATTER, int STORE>
 __device__ __forceinline__ void update_slice(const UpdateArgs& a, const PageRec& rec, int start, int lane,
                                              float* p, float* m, float* v) {
     const int k = start >= rec.off1 ? 1 : 0;
@@ -730,7 +730,7 @@ __device__ __forceinline__ void update_slice(const UpdateArgs& a, const PageRec&
 struct SmallClasses {
     GridClass small[kMaxExtentClasses - 1];
 };
-template <int U, bool GATHER, bool SCATTER>
+template <int U, bool GATHER, bool SCATTER, int STORE>
 __global__ __launch_bounds__(kUpdThreads) void apm_adamw_kernel(const PageRec* recs, float* p32, float* m32, float* v32, uint32_t large_at,
                                                                 uint32_t per, uint32_t mul, uint32_t shift, UpdateArgs a, SmallClasses classes) {
     int item;
@@ -739,7 +739,7 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_kernel(const PageRec* r
     const PageRec rec = load_rec(recs + item);
     const int start = (int)x * kTile<U>;
     if (rec.scale < 0.0f || start >= ((rec.used + 7) & ~7)) return;  // a skipped page, beyond the extent
-    update_slice<U, GATHER, SCATTER>(a, rec, start, (int)threadIdx.x, p32 + rec.pofs, m32 + rec.pofs, v32 + rec.pofs);
+    update_slice<U, GATHER, SCATTER, STORE>(a, rec, start, (int)threadIdx.x, p32 + rec.pofs, m32 + rec.pofs, v32 + rec.pofs);
 }
 
 // The same for a run of pages in the page classes; all pointers are those of the launch's first page.
@@ -776,7 +776,7 @@ __device__ __forceinline__ LiveClasses::Class load_class(const LiveClasses::Clas
     asm("" : "+s"(w));
     return __builtin_bit_cast(LiveClasses::Class, w);
 }
-template <int U, bool RUN, bool GATHER, bool SCATTER, int STORE = kStoreHbm>
+template <int U, bool RUN, bool GATHER, bool SCATTER, int STORE>
 __global__ __launch_bounds__(kUpdThreads) void apm_adamw_live_kernel(const int32_t* live, const PageRec* recs, float* p32, float* m32, float* v32,
                                                                      const uint16_t* g16, uint16_t* p16, int64_t E, UpdateArgs a, LiveClasses lc) {
     typedef const int32_t __attribute__((address_space(4))) * Const;
@@ -855,7 +855,7 @@ __global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(Str
             at = rec.pofs;
         }
         if (rec.scale < 0.0f || start >= rec.end[0]) continue;
-        update_slice<kStrideU, false, false, WT ? kStoreHostWT : kStoreHost>(a, rec, start, lane, s.p32 + at, s.m32 + at, s.v32 + at);
+        update_slice<kStrideU, false, false, WT ? kStoreHostWT : kStoreNT>(a, rec, start, lane, s.p32 + at, s.m32 + at, s.v32 + at);
     }
 }
 
@@ -1390,6 +1390,13 @@ hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s)
     return hipSuccess;
 }
 
+// f(the stores' policy as a constant)
+template <class F>
+static void with_stores(bool non_temporal_only, F&& f) {
+    if (non_temporal_only) f(std::integral_constant<int, kStoreNT>{});
+    else f(std::integral_constant<int, kStoreHbm>{});
+}
+
 // Workgroups a page of the class takes.
 template <int U> int64_t slices_of(const ExtentClass& c) { return c.max_used > 0 ? (c.max_used + kTile<U> - 1) / kTile<U> : 1; }
 
@@ -1460,14 +1467,15 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
 #define APM_LAUNCH_LIVE(...) hipLaunchKernelGGL((apm_adamw_live_kernel<__VA_ARGS__>), grid, block, kSkipLds, s, L.live, \
                                                      L.recs, state(L.p32, 0), state(L.m32, 0), state(L.v32, 0), run ? g16(0) : nullptr,  \
                                                      run ? p16(0) : nullptr, L.E, a, lc)
-                if (wide && L.beside_link) APM_LAUNCH_LIVE(kWideU, true, false, false, kStoreHost);
-                else if (wide) APM_LAUNCH_LIVE(kWideU, true, false, false);
-                else if (run && L.beside_link) APM_LAUNCH_LIVE(U, true, false, false, kStoreHost);
-                else if (run) APM_LAUNCH_LIVE(U, true, false, false);
-                else if (L.gather && L.scatter) APM_LAUNCH_LIVE(U, false, true, true);
-                else if (L.gather) APM_LAUNCH_LIVE(U, false, true, false);
-                else if (L.scatter) APM_LAUNCH_LIVE(U, false, false, true);
-                else APM_LAUNCH_LIVE(U, false, false, false);
+                with_stores(L.beside_link, [&](auto store) {
+                    constexpr int STORE = decltype(store)::value;
+                    if (wide) APM_LAUNCH_LIVE(kWideU, true, false, false, STORE);
+                    else if (run) APM_LAUNCH_LIVE(U, true, false, false, STORE);
+                    else if (L.gather && L.scatter) APM_LAUNCH_LIVE(U, false, true, true, kStoreHbm);
+                    else if (L.gather) APM_LAUNCH_LIVE(U, false, true, false, kStoreHbm);
+                    else if (L.scatter) APM_LAUNCH_LIVE(U, false, false, true, kStoreHbm);
+                    else APM_LAUNCH_LIVE(U, false, false, false, STORE);
+                });
 #undef APM_LAUNCH_LIVE
                 const hipError_t e = hipGetLastError();
                 if (e != hipSuccess) return e;
@@ -1487,12 +1495,13 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         return (hipError_t)for_each_grid(cls, n_cls, kUpdThreads, L.max_workgroups, slices_of<U>, [&](const GridMap& m, int64_t workgroups, int64_t first) -> int {
             SmallClasses classes;
             std::memcpy(classes.small, m.small, sizeof classes.small);
-#define APM_LAUNCH_UPDATE(G, Q) hipLaunchKernelGGL((apm_adamw_kernel<U, G, Q>), dim3((unsigned)workgroups), dim3(kUpdThreads), lds, s, L.recs + first, \
+#define APM_LAUNCH_UPDATE(G, Q, STORE) hipLaunchKernelGGL((apm_adamw_kernel<U, G, Q, STORE>), dim3((unsigned)workgroups), dim3(kUpdThreads), lds, s, L.recs + first, \
                                                    L.p32, L.m32, L.v32, m.large_at, m.large.per, m.large.mul, m.large.shift, a, classes)
-            if (L.gather && L.scatter) APM_LAUNCH_UPDATE(true, true);
-            else if (L.gather) APM_LAUNCH_UPDATE(true, false);
-            else if (L.scatter) APM_LAUNCH_UPDATE(false, true);
-            else APM_LAUNCH_UPDATE(false, false);
+            if (L.gather && L.scatter) APM_LAUNCH_UPDATE(true, true, kStoreHbm);
+            else if (L.gather) APM_LAUNCH_UPDATE(true, false, kStoreHbm);
+            else if (L.scatter) APM_LAUNCH_UPDATE(false, true, kStoreHbm);
+            else if (L.beside_link) APM_LAUNCH_UPDATE(false, false, kStoreNT);
+            else APM_LAUNCH_UPDATE(false, false, kStoreHbm);
 #undef APM_LAUNCH_UPDATE
             return (int)hipGetLastError();
         });
@@ -1508,13 +1517,13 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         // sooner (us a call, 2 M elements in 8 pages, written through / not: one state again and again 10.7 / 8.9, three
         // in turn 10.75 / 10.6, eight 11.5 / 11.2).
         const bool few = L.bare_run && sum_used <= kFewRunElems;
-        if (few && !wide) APM_LAUNCH_RUN(U, true, kStoreHost, L.used + L.grad_first + begin);
-        else if (wide && L.beside_link) APM_LAUNCH_RUN(kWideU, false, kStoreHost, runs + begin);
-        else if (L.beside_link) APM_LAUNCH_RUN(U, false, kStoreHost, runs + begin);
-        else if (wide && L.bare_run) APM_LAUNCH_RUN(kWideU, true, kStoreHbm, L.used + L.grad_first + begin);
-        else if (wide) APM_LAUNCH_RUN(kWideU, false, kStoreHbm, runs + begin);
-        else if (L.bare_run) APM_LAUNCH_RUN(U, true, kStoreHbm, L.used + L.grad_first + begin);
-        else APM_LAUNCH_RUN(U, false, kStoreHbm, runs + begin);
+        with_stores(few || L.beside_link, [&](auto store) {
+            constexpr int STORE = decltype(store)::value;
+            if (wide && L.bare_run) APM_LAUNCH_RUN(kWideU, true, kStoreHbm, L.used + L.grad_first + begin);
+            else if (wide) APM_LAUNCH_RUN(kWideU, false, STORE, runs + begin);
+            else if (L.bare_run) APM_LAUNCH_RUN(U, true, STORE, L.used + L.grad_first + begin);
+            else APM_LAUNCH_RUN(U, false, STORE, runs + begin);
+        });
 #undef APM_LAUNCH_RUN
     });
 }

@@ -270,7 +270,7 @@ struct AdamwLaunch {
     int32_t stride_wavefronts;    // > 0: the update runs as that many wavefronts striding over all
                                   // page slices (fp32 classes in host memory); 0: one per slice
     int32_t stride_waves_per_wg;  // how many of them share a workgroup, 1..16
-    bool beside_link;             // pages of the classes, while a kernel on another stream moves pages across PCIe
+    bool beside_link;             // g16 / p16 in the page classes, while a kernel on another stream moves pages across PCIe
     bool host_write_through;      // stride form: fp32 state stores written through at system scope
     bool wide;                    // a run whose grid holds many workgroups without work: fewer, larger slices
     bool bare_run;                // a run without a reduce or prepare pass: the update reads `used` itself
