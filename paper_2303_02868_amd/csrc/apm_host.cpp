@@ -65,50 +65,69 @@ int make_plan(int64_t E, const int64_t* numels, int64_t n, Plan* out) {
     return APM_OK;
 }
 
-int group_by_extent(int64_t n, int64_t E, const int32_t* size, int64_t* order, ExtentClass cls[kMaxExtentClasses],
-                    int64_t worth) {
-    const int64_t limit[kMaxExtentClasses - 1] = {E / 4, E / 32, E / 512};  // sizes above: classes 0, 1, 2
-    auto class_of = [&](int64_t used) { return (used <= limit[0]) + (used <= limit[1]) + (used <= limit[2]); };
-    int64_t cnt[kMaxExtentClasses] = {}, mx[kMaxExtentClasses] = {}, sum[kMaxExtentClasses] = {};
-    for (int64_t k = 0; k < n; ++k) {
+ExtentGroups::ExtentGroups(int64_t n, int64_t E, const int32_t* size) : n_(n), size_(size), limit_{E / 4, E / 32, E / 512} {
+    for (int64_t k = 0; k < n; ++k) {  // sizes above the limits: classes 0, 1, 2
         const int64_t u = size[k];
         const int c = class_of(u);
-        ++cnt[c];
-        sum[c] += u;
-        if (u > mx[c]) mx[c] = u;
+        ++cnt_[c];
+        sum_[c] += u;
+        if (u > mx_[c]) mx_[c] = u;
     }
+}
+
+int ExtentGroups::fold(int64_t worth, ExtentClass cls[kMaxExtentClasses]) {
     // A class that saves fewer idle workgroups than it is worth is folded into the next larger one.  With launches of its own:  Counted in spans of 1024 elements, four workgroups of the update or half a
     // copy's; from and to tensors, us a call with the line at 2048 / 4096 / 16384 / 65536 spans: 4.8 M elements in
     // 64 K pages with clipping 41 / 33 / 33 / 33, in 256 K pages 30 / 30 / 28 / 28, in 1 M pages 32 / 32 / 32 / 53;
     // 124 M 537 / 537 / 538 / 544; 350 M 1520 / 1518 / 1529 / 1555; packing 122 M 87 / 87 / 85 / 86.  In a common grid, line at 64 / 2048 /
     // 16384 spans: 124 M 524 / 525 / 529; 7 M in 64 K pages 28.5 / 28.5 / 27.4; 16 M in 1 M pages 22.6 / 21.0 / 23.2.
-    int into[kMaxExtentClasses];
-    for (int c = 0; c < kMaxExtentClasses; ++c) into[c] = c;
+    int64_t cnt[kMaxExtentClasses], sum[kMaxExtentClasses];
+    for (int c = 0; c < kMaxExtentClasses; ++c) {
+        into_[c] = c;
+        cnt[c] = cnt_[c];
+        sum[c] = sum_[c];
+    }
     constexpr int64_t kSpan = 1024;
     for (int c = kMaxExtentClasses - 1; c > 0; --c) {
         if (cnt[c] == 0) continue;
         int j = c - 1;
         while (j > 0 && cnt[j] == 0) --j;
         if (cnt[j] == 0) continue;
-        if (cnt[c] * ((mx[j] - mx[c]) / kSpan) < worth) {
-            for (int q = c; q < kMaxExtentClasses; ++q) if (into[q] == c) into[q] = j;
+        if (cnt[c] * ((mx_[j] - mx_[c]) / kSpan) < worth) {
+            for (int q = c; q < kMaxExtentClasses; ++q) if (into_[q] == c) into_[q] = j;
             cnt[j] += cnt[c];
             sum[j] += sum[c];
             cnt[c] = 0;
         }
     }
-    int64_t fill[kMaxExtentClasses];
-    int n_cls = 0;
+    n_cls_ = 0;
     for (int64_t c = 0, at = 0; c < kMaxExtentClasses; ++c) {
-        fill[c] = at;
-        if (cnt[c] > 0) cls[n_cls++] = ExtentClass{at, cnt[c], mx[c], sum[c]};
+        begin_[c] = at;
+        if (cnt[c] > 0) cls[n_cls_++] = ExtentClass{at, cnt[c], mx_[c], sum[c]};
         at += cnt[c];
     }
-    if (n_cls == 1)
-        for (int64_t k = 0; k < n; ++k) order[k] = k;
-    else
-        for (int64_t k = 0; k < n; ++k) order[fill[into[class_of(size[k])]]++] = k;
-    return n_cls;
+    return n_cls_;
+}
+
+void ExtentGroups::order(int64_t* out) const {
+    if (n_cls_ <= 1) {
+        for (int64_t k = 0; k < n_; ++k) out[k] = k;
+        return;
+    }
+    int64_t fill[kMaxExtentClasses];
+    for (int c = 0; c < kMaxExtentClasses; ++c) fill[c] = begin_[c];
+    for (int64_t k = 0; k < n_; ++k) out[fill[into_[class_of(size_[k])]]++] = k;
+}
+
+bool ExtentGroups::in_order() const {
+    if (n_cls_ <= 1) return true;
+    int last = 0;
+    for (int64_t k = 0; k < n_; ++k) {
+        const int c = into_[class_of(size_[k])];
+        if (c < last) return false;
+        last = c;
+    }
+    return true;
 }
 
 GridDiv grid_div(int64_t per) {

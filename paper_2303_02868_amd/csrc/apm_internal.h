@@ -78,15 +78,34 @@ struct ExtentClass {
     int64_t max_used;  // largest size among them (elements)
     int64_t sum_used;  // and the sum of their sizes
 };
-// order[pos] = index of the item at position pos (classes one after the other, the given order kept
-// inside each); returns the number of classes.  E = the size that the class limits are fractions of.
-// Sizes come as an array: a call's host time is spent here when its pages are many and small.
-// worth: idle spans of 1024 elements that a class has to save (kWorthLaunch, kWorthGrid).
 constexpr int64_t kWorthLaunch = 16384;  // for a launch, or a page list, of its own
 constexpr int64_t kWorthGrid = 2048;     // for its part of the pages' common grid
 constexpr int64_t kWorthSegs = 64;       // and of the segments'
-int group_by_extent(int64_t n, int64_t E, const int32_t* size, int64_t* order, ExtentClass cls[kMaxExtentClasses],
-                    int64_t worth = kWorthLaunch);
+// Sizes come as an array, and are counted once whatever is asked of them: a call's host time is spent here
+// when its pages are many and small.
+class ExtentGroups {
+public:
+    // E = the size that the class limits are fractions of; the sizes are read until the last call.
+    ExtentGroups(int64_t n, int64_t E, const int32_t* size);
+    // Returns the number of classes.  worth: idle spans of 1024 elements that a class has to save (kWorthLaunch,
+    // kWorthGrid, kWorthSegs).
+    int fold(int64_t worth, ExtentClass cls[kMaxExtentClasses]);
+    // With the classes of the last fold:
+    // out[pos] = index of the item at position pos (classes one after the other, the given order kept inside each);
+    void order(int64_t* out) const;
+    // whether that is 0, 1, 2, ...
+    bool in_order() const;
+
+private:
+    int class_of(int64_t used) const { return (used <= limit_[0]) + (used <= limit_[1]) + (used <= limit_[2]); }
+    int64_t n_;
+    const int32_t* size_;
+    int64_t limit_[kMaxExtentClasses - 1];
+    int64_t cnt_[kMaxExtentClasses] = {}, mx_[kMaxExtentClasses] = {}, sum_[kMaxExtentClasses] = {};
+    int into_[kMaxExtentClasses] = {};
+    int64_t begin_[kMaxExtentClasses] = {};
+    int n_cls_ = 0;
+};
 
 // One dimension of a grid holds fewer than 2^32 work-items (the runtime refuses more): the workgroups of
 // `threads` work-items that a one-dimensional launch can have.

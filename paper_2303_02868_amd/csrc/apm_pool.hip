@@ -166,7 +166,9 @@ void order_segments(const Plan& plan, SegRec* recs, std::vector<SegLaunch>* laun
             if (u > mx) mx = u;
         }
         ExtentClass cls[kMaxExtentClasses];
-        const int n_cls = group_by_extent(end - at, mx, size.data(), order.data(), cls, kWorthSegs);
+        ExtentGroups groups(end - at, mx, size.data());
+        const int n_cls = groups.fold(kWorthSegs, cls);
+        groups.order(order.data());
         const int64_t count = last + 1 - t0 < group ? last + 1 - t0 : group;
         SegLaunch l{{}, n_cls, (int32_t)t0, (int32_t)count};
         for (int c = 0; c < n_cls; ++c) {
@@ -193,16 +195,13 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     for (size_t k = 0; k < n_in_use; ++k) used_sum[k + 1] = used_sum[k] + used[k];
     std::vector<int64_t> order(n_in_use);
     ExtentClass cls[kMaxExtentClasses] = {};
-    auto is_plain = [&] {
-        for (size_t k = 0; k < n_in_use; ++k)
-            if (order[k] != (int64_t)k) return false;
-        return true;
-    };
     ExtentClass run_cls[kMaxExtentClasses] = {};
-    const int run_n_cls = group_by_extent((int64_t)n_in_use, plan.E, used.data(), order.data(), run_cls);
-    const bool run = is_plain();
-    const int n_cls = group_by_extent((int64_t)n_in_use, plan.E, used.data(), order.data(), cls, kWorthGrid);
-    const bool plain = is_plain();
+    ExtentGroups groups((int64_t)n_in_use, plan.E, used.data());
+    const int run_n_cls = groups.fold(kWorthLaunch, run_cls);
+    const bool run = groups.in_order();
+    const int n_cls = groups.fold(kWorthGrid, cls);
+    const bool plain = groups.in_order();
+    groups.order(order.data());
     // Tables for the device, in one allocation and one upload; freed unless the pool takes it over at the end.
     struct Tables {
         char* d = nullptr;

@@ -44,13 +44,18 @@ int check_fused_list(const apm_pool* pool, const apm_tensor* t, int64_t n, const
     return APM_OK;
 }
 
-// group_by_extent over the used extents of a call's pages.
-int group_pages(const apm_pool* pool, const int64_t* pages, int64_t n, int64_t* order, ExtentClass cls[kMaxExtentClasses], int64_t worth) {
-    std::vector<int32_t> size;
-    if (pool->used.empty()) size.assign((size_t)n, 0);
-    else if (pages) size.resize((size_t)n);
-    for (int64_t k = 0; pages && !pool->used.empty() && k < n; ++k) size[(size_t)k] = pool->used[(size_t)pages[k]];
-    return group_by_extent(n, pool->desc.page_elems, size.empty() ? pool->used.data() : size.data(), order, cls, worth);
+// The used extents of a call's pages; `room` holds them where the pool has no array of them.
+const int32_t* page_extents(const apm_pool* pool, const int64_t* pages, int64_t n, std::vector<int32_t>* room) {
+    if (pool->used.empty()) room->assign((size_t)n, 0);
+    else if (pages) room->resize((size_t)n);
+    for (int64_t k = 0; pages && !pool->used.empty() && k < n; ++k) (*room)[(size_t)k] = pool->used[(size_t)pages[k]];
+    return room->empty() ? pool->used.data() : room->data();
+}
+
+bool consecutive(const int64_t* pages, int64_t n) {
+    for (int64_t k = 1; pages && k < n; ++k)
+        if (pages[k] != pages[0] + k) return false;
+    return true;
 }
 
 }  // namespace
@@ -139,14 +144,17 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
         L.n_cls = as_run ? pool->run_n_cls : pool->order_n_cls;
         for (int c = 0; c < L.n_cls; ++c) L.cls[c] = as_run ? pool->run_cls[c] : pool->order_cls[c];
     } else {
-        order.resize((size_t)n_pages);
-        auto group = [&](int64_t worth) {
-            L.n_cls = group_pages(pool, pages, n_pages, order.data(), L.cls, worth);
-            run = true;
-            for (int64_t k = 0; run && k < n_pages; ++k) run = order[(size_t)k] == k && page_at(k) == page_at(0) + k;
-        };
-        group(tensors ? kWorthGrid : kWorthLaunch);
-        if (!tensors && !run) group(kWorthGrid);
+        std::vector<int32_t> room;
+        ExtentGroups groups(n_pages, E, page_extents(pool, pages, n_pages, &room));
+        if (consecutive(pages, n_pages)) {
+            L.n_cls = groups.fold(tensors ? kWorthGrid : kWorthLaunch, L.cls);
+            run = groups.in_order();
+        }
+        if (!run) {
+            L.n_cls = groups.fold(kWorthGrid, L.cls);
+            order.resize((size_t)n_pages);
+            groups.order(order.data());
+        }
     }
     const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
     rc = ensure_scratch(pool, !run && !whole);
@@ -396,8 +404,7 @@ static int take_gradient(apm_pool* pool, int k, const uint16_t* g16, const int64
     auto page_at = [&](int64_t i) { return pages ? pages[i] : i; };
     ExtentClass cls[kMaxExtentClasses];
     t.cls = cls;
-    bool run = true;
-    for (int64_t i = 1; run && pages && i < n_pages; ++i) run = pages[i] == pages[0] + i;
+    const bool run = consecutive(pages, n_pages);
     // Consecutive pages need no list, and with the extents taken as the layout's largest no look-up, at the price of
     // workgroups without work where pages differ much: a list is the better form then.
     if (run && (n_pages > kTakePages || pool->run_n_cls <= 1)) {
@@ -408,7 +415,10 @@ static int take_gradient(apm_pool* pool, int k, const uint16_t* g16, const int64
         return APM_OK;
     }
     std::vector<int64_t> order((size_t)n_pages);
-    t.n_cls = group_pages(pool, pages, n_pages, order.data(), cls, kWorthGrid);
+    std::vector<int32_t> room;
+    ExtentGroups groups(n_pages, pool->desc.page_elems, page_extents(pool, pages, n_pages, &room));
+    t.n_cls = groups.fold(kWorthGrid, cls);
+    groups.order(order.data());
     for (int64_t& i : order) i = page_at(i);
     const int64_t launches = (n_pages + kTakePages - 1) / kTakePages;
     int slot = -1;

@@ -2,6 +2,7 @@
 // malformed inputs.  Built with AddressSanitizer + UBSan by tests/test_host_sanitizers.py: a
 // memory error or undefined behaviour in the host logic aborts the run.  The checks in here are
 // structural only (bounds, counts, coverage); values are checked against the oracle elsewhere.
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -174,9 +175,14 @@ void group_case(Rng& r) {
     const int64_t E = 8 * (1 + r.below((int64_t)1 << r.below(24))), n = r.below(600) * (r.below(3) == 0 ? 50 : 1);
     std::vector<int32_t> size((size_t)n);
     for (auto& x : size) x = (int32_t)(r.below(4) == 0 ? E >> r.below(12) : r.below((E >> r.below(12)) + 1));
+    if (r.below(4) == 0) std::sort(size.rbegin(), size.rend());
     std::vector<int64_t> order((size_t)n, -1);
     apm::ExtentClass cls[apm::kMaxExtentClasses];
-    const int n_cls = apm::group_by_extent(n, E, size.data(), order.data(), cls);
+    apm::ExtentGroups groups(n, E, size.data());
+    const int64_t worth[] = {apm::kWorthLaunch, apm::kWorthGrid, apm::kWorthSegs};
+    for (int64_t k = r.below(3); k > 0; --k) groups.fold(worth[r.below(3)], cls);  // an earlier fold leaves nothing behind
+    const int n_cls = groups.fold(worth[r.below(3)], cls);
+    groups.order(order.data());
     if ((n == 0) != (n_cls == 0) || n_cls > apm::kMaxExtentClasses) die("class count", n_cls, n);
     std::vector<char> seen((size_t)n, 0);
     int64_t at = 0, above = INT64_MAX;
@@ -197,6 +203,9 @@ void group_case(Rng& r) {
         above = mn;
     }
     if (at != n) die("items left over", at, n);
+    bool plain = true;
+    for (int64_t k = 0; k < n; ++k) plain = plain && order[(size_t)k] == k;
+    if (groups.in_order() != plain) die("in_order", plain, n);
 }
 
 // The pieces that a pass over many pages is launched in: every launch within what one grid dimension

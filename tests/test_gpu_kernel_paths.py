@@ -530,6 +530,27 @@ def test_a_list_of_many_small_pages_is_grouped_quickly():
     assert general < 3 * whole, (general, whole)
 
 
+def test_a_list_that_is_no_run_is_grouped_once():
+    """131072 pages of 64 elements in reverse, bound by the host: the step on the page classes, which would take a
+    run in coarser classes, costs about what the step from a tensor does (grouped for both 1.5 times as much; bound 1.25)."""
+    E, n = 64, 131072
+    pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n)
+    L = apm.lib()
+    L.apm_pool_set_layout(pool.handle, apm.make_tensors([n * E], apm.APM_F32, [0]), 1, None, None, None, None, None)
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.0, 0)
+    g = torch.zeros(n * E, device=DEV, dtype=torch.bfloat16)
+    lst, g_list = (ctypes.c_int64 * n)(*range(n - 1, -1, -1)), apm.make_tensors([n * E], apm.APM_BF16, [g.data_ptr()])
+
+    def pages():
+        assert L.apm_page_adamw_step(pool.handle, lst, n, 3, ctypes.byref(hyper), None, None, None) == 0
+
+    def fused():
+        assert L.apm_page_adamw_step_fused(pool.handle, lst, n, 3, ctypes.byref(hyper), g_list, None, 1, None, None, None) == 0
+    us = [_us(f, 20) for f in (pages, fused)]
+    pool.destroy()
+    assert us[0] < 1.25 * us[1], us
+
+
 @pytest.mark.parametrize("listed", ["all", "reversed", "odd"])
 @pytest.mark.parametrize("n", [2047, 2048, 2049, 4100])
 @pytest.mark.parametrize("E", [8, 520, 4088, 4096])
