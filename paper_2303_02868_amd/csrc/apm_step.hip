@@ -165,6 +165,10 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     const int64_t n_list = run || whole ? 0 : n_pages;
     const int64_t n_g = grad_tensors ? n_tensors : 0, n_q = p16_tensors ? n_tensors : 0;
     int ring_slot = -1;
+    // Half words take a look at every address: only where they save launches and the call does not go through the ring.
+    const int64_t lists = (n_g > 0) + (n_q > 0), n_words = tensors ? n_tensors : 0;
+    int64_t launches = stage_launches(n_list, lists, n_words, false);
+    const int64_t narrow_launches = stage_launches(n_list, lists, n_words, true);
     auto base_of = [&](const apm_tensor* t, int64_t n, uint64_t* base) {
         uint64_t low = UINT64_MAX, high = 0;
         for (int64_t i = 0; i < n; ++i) {
@@ -176,9 +180,11 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
         *base = low <= high ? low : 0;
         return low > high || (high - low) >> 4 <= UINT32_MAX;
     };
-    const bool g_narrow = base_of(grad_tensors, n_g, &sc.g_base), q_narrow = base_of(p16_tensors, n_q, &sc.q_base);
-    sc.narrow = g_narrow && q_narrow;
-    const bool by_ring = stage_launches(n_list, (n_g > 0) + (n_q > 0), tensors ? n_tensors : 0, sc.narrow) > kMaxStageLaunches;
+    if (narrow_launches < launches && narrow_launches <= kMaxStageLaunches) {
+        sc.narrow = base_of(grad_tensors, n_g, &sc.g_base) && base_of(p16_tensors, n_q, &sc.q_base);
+        if (sc.narrow) launches = narrow_launches;
+    }
+    const bool by_ring = launches > kMaxStageLaunches;
     // A list alone that goes through the ring is read there by the step's kernels: no stage kernel.
     const bool staged = tensors || (n_list > 0 && !by_ring);
     const int64_t* d_list = whole ? pool->d_order : pool->d_list;
