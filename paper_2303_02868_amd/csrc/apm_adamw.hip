@@ -123,6 +123,7 @@ unsigned update_lds(bool tensors, int64_t elems, unsigned lds) { return elems <=
 //   128 K           157 / 49 / 43     180 / 40 / 18     170 / 42 / 22
 //   4 M            4877 / 1448 / 1194 5919 / 907 / 392 5424 / 999 / 537
 constexpr int kSkipU = 1, kSkipSpread = 12, kSkipWaves = 8192, kSkipLds = 14848;
+constexpr uint32_t kThroughSlack = 12288;  // see apm_adamw_live_kernel
 
 // Gradient elements [e, e+8) of a page, read from its tenant tensors; elements that belong to no
 // tenant (alignment gap, padding) read as zero.  e is a multiple of 8, as every tenant offset is,
@@ -790,27 +791,37 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_live_kernel(const int32
     w -= c.first;
     // a wavefront's items are the class's workgroups apart; page and slice advance by that without another division
     uint32_t i = c.slices.quotient(w), x = w - i * nx;
+    auto walk = [&](auto store) {
 #pragma unroll 1
-    for (; i < n; i += c.di, x += c.dx) {
-        if (x >= nx) {
-            x -= nx;
-            if (++i >= n) return;
+        for (; i < n; i += c.di, x += c.dx) {
+            if (x >= nx) {
+                x -= nx;
+                if (++i >= n) return;
+            }
+            const int64_t pos = positions[i];
+            PageRec rec;
+            int64_t at;
+            if (RUN) {
+                at = pos * E;
+                const PageRun run = load_run(reinterpret_cast<const PageRun*>(recs) + pos);
+                rec = class_rec(run.used, run.scale, 0, 0, 0, g16 + at, p16 + at);
+            } else {
+                rec = load_rec(recs + pos);
+                at = rec.pofs;
+            }
+            const int start = (int)x * kTile<U>;
+            if (start < ((rec.used + 7) & ~7))
+                update_slice<U, GATHER, SCATTER, decltype(store)::value>(a, rec, start, (int)threadIdx.x, p32 + at, m32 + at, v32 + at);
         }
-        const int64_t pos = positions[i];
-        PageRec rec;
-        int64_t at;
-        if (RUN) {
-            at = pos * E;
-            const PageRun run = load_run(reinterpret_cast<const PageRun*>(recs) + pos);
-            rec = class_rec(run.used, run.scale, 0, 0, 0, g16 + at, p16 + at);
-        } else {
-            rec = load_rec(recs + pos);
-            at = rec.pofs;
-        }
-        const int start = (int)x * kTile<U>;
-        if (start < ((rec.used + 7) & ~7))
-            update_slice<U, GATHER, SCATTER, STORE>(a, rec, start, (int)threadIdx.x, p32 + at, m32 + at, v32 + at);
-    }
+    };
+    // A wavefront waits for one slice's stores before the next slice's loads, and written through they take longer: with many
+    // slices a wavefront, of many wavefronts, that costs more than it gains.  us a call, written through / not, one GPU, elements
+    // (slices per wavefront): all live, 7 M (3.5) 46.7 / 47.7, 13 M (6.3) 79.2 / 79.9, 19 M (9.2) 116 / 116,
+    // 26 M (12) 151 / 148, 124 M (12) 707 / 691, 1.3 G (12) 7486 / 7353; 541 M, a quarter live (3) 804 / 806, 3 in 8 (4.5) 1164 / 1152, half
+    // (6) 1534 / 1514; 1.08 G, an eighth (1.5) 951 / 954.
+    const uint64_t wavefronts = c.di * nx + c.dx;
+    if (STORE == kStoreNT || (uint64_t)n * nx > 4 * (wavefronts + kThroughSlack)) walk(std::integral_constant<int, kStoreNT>{});
+    else walk(std::integral_constant<int, STORE>{});
 }
 
 // The form for fp32 classes that live in pinned host memory and are read and written across

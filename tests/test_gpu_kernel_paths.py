@@ -267,10 +267,11 @@ class _Region:
 @pytest.mark.parametrize("dead", ["none", "all", "most", "first"])
 @pytest.mark.parametrize("form", ["run", "reversed", "fused", "noalloc"])
 @pytest.mark.parametrize("E,n_t,per", [(8, 40, 8), (4104, 30, 4103), (1 << 20, 6, 3 << 19), (1 << 20, 40, 5000),
-                                     (4104, 1500, 4103), (512, 5000, 500)])
+                                     (4104, 1500, 4103), (512, 5000, 500), (1 << 20, 18, 3 << 19)])
 def test_skipping_updates_the_touched_pages_and_no_others(E, n_t, per, form, dead):
-    """The grid over the noted pages: none, all, few live pages, several extent classes.  Same bits as a step
-    without skipping on the live pages; the others keep theirs."""
+    """The grid over the noted pages: none, all, few live pages, several extent classes, and (the last size) so many slices a
+    wavefront that state is stored non-temporal only.  Same bits as a step without skipping on the live pages; the
+    others keep theirs."""
     numels = [per if k % 7 else max(1, per // 600) for k in range(n_t)]
     off = [0]
     for m in numels:
