@@ -105,6 +105,14 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float x) {
 // with clipping 14.3 / 13.9, 18.8 / 18.2, 45.2 / 45.5).
 constexpr int64_t kFewElems = (int64_t)24 << 20, kFewRunElems = (int64_t)2 << 20;
 constexpr int kFewLds = 9216;
+// Bare runs up to this size store state non-temporal only.  Their state fits the L2s (12 B an element of 32 MiB), where what a
+// call leaves serves the next one on the same pages, and written-through stores end later: one state again and again gains,
+// three states in turn lose, and the line is where the first stops gaining (us a call, written through / not, again and again; in turn:
+// 1 M elements 6.2 / 5.0; 6.4 / 6.0, 1.6 M 9.1 / 8.2; 8.9 / 9.0, 2.1 M 11.1 / 10.2; 11.0 / 11.5, 2.4 M 11.6 / 11.7; 11.9 / 12.5, 2.9 M 13.7 /
+// 14.0; 13.8 / 14.6, 3.7 M 16.6 / 17.6; 17.9 / 18.1).  The other forms are written through at every size: in turn they never
+// lose; again and again they take up to 0.7 us more below 1 M elements (0.6 M with clipping 12.5 / 12.2 in pages,
+// 14.0 / 14.1 from tensors; 0.9 M 14.0 / 14.1, 14.2 / 13.3), from there on the difference changes sign from layout to layout.
+constexpr int64_t kNtRunElems = (int64_t)2 << 20;
 constexpr int kWideU = 4;  // see wide_pays
 unsigned update_lds(bool tensors, int64_t elems, unsigned lds) { return elems <= (tensors ? kFewElems : kFewRunElems) ? kFewLds : lds; }
 
@@ -601,7 +609,7 @@ template <int U> constexpr int kTile = kUpdThreads * 4 * U;  // elements per wav
 //   kStoreHostWT  written through, for the same while other kernels run on the GPU: a non-temporal store
 //               to host memory may rest in the L2 as a dirty line; the write-back that ends every kernel of any
 //               other stream then has to push it across PCIe, so those kernels pay for this kernel's writes.
-// Gradients are read with the default policy when the state is in device memory: a slice of a tensor that does not
+// Gradients are read with the default policy where state is stored with kStoreHbm: a slice of a tensor that does not
 // start on a cache line shares its first and last line with its neighbours, and with clipping g is read a second time
 // (213 M parameters in tensors of odd sizes: 957 us non-temporal, 943 default; with clipping 987 and 967).
 // (As an operand because the compiler drops the hint of its non-temporal builtin from stores that it
@@ -663,7 +671,8 @@ __device__ __forceinline__ void full_slice(const UpdateArgs& a, GetScale&& get_s
     }
 }
 
-// A store of fp32 state outside the body above (slices that are few: written through, or non-temporal).  The write-through form is
+// A store of fp32 state outside the body above: written through for kStoreHostWT, non-temporal for the others (such
+// slices are few; kStoreHbm makes no difference there).  The write-through form is
 // hand-written because no builtin takes that policy for a 128-bit global store; the wait states keep
 // the next instruction off the data registers, which a store of more than 64 bits still reads right
 // after issue (the compiler does that for its own stores, not for this one).
@@ -1549,10 +1558,7 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         const unsigned lds = update_lds(false, sum_used, APM_UPDATE_LDS);
 #define APM_LAUNCH_RUN(U, BARE, STORE, RUNS) hipLaunchKernelGGL((apm_adamw_run_kernel<U, BARE, STORE>), grid, block, lds, s, RUNS, state(L.p32, begin), \
                                                          state(L.m32, begin), state(L.v32, begin), g16(begin), p16(begin), (int)L.E, a)
-        // Few elements: what a call leaves in the L2s serves the next one, written through or not, but the stores end
-        // sooner (us a call, 2 M elements in 8 pages, written through / not: one state again and again 10.7 / 8.9, three
-        // in turn 10.75 / 10.6, eight 11.5 / 11.2).
-        const bool few = L.bare_run && sum_used <= kFewRunElems;
+        const bool few = L.bare_run && sum_used <= kNtRunElems;
         with_stores(few || L.beside_link, [&](auto store) {
             constexpr int STORE = decltype(store)::value;
             if (wide && L.bare_run) APM_LAUNCH_RUN(kWideU, true, kStoreHbm, L.used + L.grad_first + begin);
