@@ -109,9 +109,9 @@ constexpr int kFewLds = 9216;
 // call leaves serves the next one on the same pages, and written-through stores end later: one state again and again gains,
 // three states in turn lose, and the line is where the first stops gaining (us a call, written through / not, again and again; in turn:
 // 1 M elements 6.2 / 5.0; 6.4 / 6.0, 1.6 M 9.1 / 8.2; 8.9 / 9.0, 2.1 M 11.1 / 10.2; 11.0 / 11.5, 2.4 M 11.6 / 11.7; 11.9 / 12.5, 2.9 M 13.7 /
-// 14.0; 13.8 / 14.6, 3.7 M 16.6 / 17.6; 17.9 / 18.1).  The other forms are written through at every size: in turn they never
-// lose; again and again they take up to 0.7 us more below 1 M elements (0.6 M with clipping 12.5 / 12.2 in pages,
-// 14.0 / 14.1 from tensors; 0.9 M 14.0 / 14.1, 14.2 / 13.3), from there on the difference changes sign from layout to layout.
+// 14.0; 13.8 / 14.6, 3.7 M 16.6 / 17.6; 17.9 / 18.1).  The other forms are written through at every size: in turn they gain
+// up to 4 % or lose up to 2; again and again they take up to 0.7 us more below 1 M elements (0.6 M with clipping 12.5 / 12.2 in pages,
+// 14.0 / 14.1 from tensors; 0.9 M 14.0 / 14.1, 14.2 / 13.3), from there on the sign of the difference varies with the layout.
 constexpr int64_t kNtRunElems = (int64_t)2 << 20;
 constexpr int kWideU = 4;  // see wide_pays
 unsigned update_lds(bool tensors, int64_t elems, unsigned lds) { return elems <= (tensors ? kFewElems : kFewRunElems) ? kFewLds : lds; }
@@ -1239,7 +1239,7 @@ hipError_t launch_grad_take(const GradTake& t, hipStream_t s) {
     // positions of the given classes in one grid
     auto go = [&](const ExtentClass* cls, int n_cls) -> hipError_t {
         while (n_cls > 0 && cls[n_cls - 1].max_used <= 0 && !t.sums) --n_cls;  // nothing to take
-        return (hipError_t)for_each_grid(cls, n_cls, kThreads, 0,
+        return (hipError_t)for_each_grid(cls, n_cls, kThreads, t.max_workgroups,
             [&](const ExtentClass& c) { return c.max_used > 0 ? (c.max_used + item - 1) / item : 1; },
             [&](const GridMap& m, int64_t workgroups, int64_t first) -> int {
                 in.a.at = (int32_t)first;
@@ -1340,7 +1340,7 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
     ReduceArgs a{L.g16, L.used, L.grad_pages, L.grad_first, 0, L.E, L.partials, L.nzflags, L.S, live, {}};
     if (L.sums_ready && live) hipLaunchKernelGGL(apm_live_clear_kernel, dim3(1), dim3(kWave), 0, s, live);
     const ExtentClass all{0, L.n_listed, L.E, L.n_listed * L.E};
-    if (!L.sums_ready) e = (hipError_t)for_each_grid(L.n_cls > 0 ? L.cls : &all, L.n_cls > 0 ? L.n_cls : 1, kThreads, 0,
+    if (!L.sums_ready) e = (hipError_t)for_each_grid(L.n_cls > 0 ? L.cls : &all, L.n_cls > 0 ? L.n_cls : 1, kThreads, L.max_workgroups,
         [](const ExtentClass& c) { return c.max_used > 0 ? (c.max_used + kReduceTile - 1) / kReduceTile : 1; },
         [&](const GridMap& m, int64_t workgroups, int64_t first) -> int {
             a.list_offset = first;

@@ -346,7 +346,7 @@ hipError_t launch_seg_copy(const SegCopy& c, const SegLaunch* launches, int64_t 
         auto go = [&](auto aligned, auto workgroup) -> int {
             constexpr bool kAligned = decltype(aligned)::value;
             constexpr int threads = decltype(workgroup)::value;
-            return for_each_grid(l.cls, l.n_cls, threads, 0,
+            return for_each_grid(l.cls, l.n_cls, threads, c.max_workgroups,
                 [&](const ExtentClass& e) { return (e.max_used * c.elem_bytes + kChunk<threads> - 1) / kChunk<threads>; },
                 [&](const GridMap& map, int64_t workgroups, int64_t first) -> int {
                     auto start = [&](auto kernel, auto& args, int32_t tensor_begin) {

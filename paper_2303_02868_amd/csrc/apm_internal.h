@@ -355,6 +355,7 @@ struct GradTake {
     int64_t first;
     const ExtentClass* cls;
     int n_cls;
+    int64_t max_workgroups;  // see AdamwLaunch
 };
 hipError_t launch_grad_take(const GradTake& t, hipStream_t s);
 
@@ -384,6 +385,7 @@ struct SegCopy {
     const uint64_t* ptrs;
     bool on_device;
     bool aligned;  // every tensor starts on a multiple of 16 bytes
+    int64_t max_workgroups;  // see AdamwLaunch
 };
 hipError_t launch_seg_copy(const SegCopy& c, const SegLaunch* launches, int64_t n_launches, hipStream_t s);
 
@@ -554,8 +556,8 @@ struct ScopedTiming {
 };
 }  // namespace apm
 
-// For tests, not part of the C ABI: caps the workgroups of the pool's one-dimensional update launches
-// (0: no cap), so that small pools exercise what otherwise takes tens of millions of pages.
+// For tests, not part of the C ABI: caps the workgroups of the pool's one-dimensional launches (0: no cap), so that
+// small pools exercise what otherwise takes tens of millions of pages.
 extern "C" int apm_test_set_max_workgroups(apm_pool* pool, int64_t max_workgroups);
 // The same for AdamwLaunch::wait_limit (0: wavefronts that would wait for another one's result never do).
 extern "C" int apm_test_set_wait_limit(apm_pool* pool, int32_t wait_limit);

@@ -314,7 +314,7 @@ int move_segments(apm_pool* pool, int state, const apm_tensor* tensors, int64_t 
         ptrs[(size_t)i] = reinterpret_cast<uint64_t>(tensors[i].data);
         if (tensors[i].numel > 0) low |= ptrs[(size_t)i];
     }
-    SegCopy c{pool->d_segs, static_cast<char*>(pool->base[state]), eb, to_pages, ptrs.data(), false, (low & 15u) == 0};
+    SegCopy c{pool->d_segs, static_cast<char*>(pool->base[state]), eb, to_pages, ptrs.data(), false, (low & 15u) == 0, pool->max_workgroups};
     // Up to kMaxSegRanges launches carry the addresses themselves.  The staging ring costs the GPU 15 us
     // a call; each further launch costs the host 1.5 us, and a call with this many tensors takes the
     // host longer than the GPU when they are small (1024 each, staged / carried: 800 tensors

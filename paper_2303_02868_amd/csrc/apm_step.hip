@@ -401,7 +401,7 @@ static int take_gradient(apm_pool* pool, int k, const uint16_t* g16, const int64
     if (n_pages == 0) return APM_OK;
     const int64_t in_use = (int64_t)pool->plan.pages.size();
     GradTake t{g16, pool->gbuf[k], accumulate, pool->d_used, pool->desc.page_elems, pool->S, sums ? pool->gsum[k] : nullptr,
-               sums ? pool->gnz[k] : nullptr, nullptr, nullptr, 0, pool->order_cls, pool->order_n_cls};
+               sums ? pool->gnz[k] : nullptr, nullptr, nullptr, 0, pool->order_cls, pool->order_n_cls, pool->max_workgroups};
     if (!pages && n_pages == in_use) {
         t.order = pool->order_plain ? nullptr : pool->d_order;
         APM_HIP(launch_grad_take(t, s));

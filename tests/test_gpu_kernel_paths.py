@@ -323,10 +323,11 @@ def test_skipping_updates_the_touched_pages_and_no_others(E, n_t, per, form, dea
 
 @pytest.mark.parametrize("cap", [1, 7, 1000])
 @pytest.mark.parametrize("skip", [0, 1])
-@pytest.mark.parametrize("form", ["run", "reversed", "fused"])
+@pytest.mark.parametrize("form", ["run", "reversed", "fused", "delayed", "delayed reversed"])
 def test_updates_in_several_launches_equal_one_launch(form, skip, cap):
     """Page counts beyond what one grid holds are launched in pieces; a low cap on the workgroups of a
-    launch gives several pieces per extent class at a small size.  Same bits as without the cap."""
+    launch gives several pieces per extent class at a small size (packing, sums, hand-overs, updates).  Same bits as
+    without the cap."""
     E, numels = 1 << 18, [3, (1 << 18) * 5 + 77, 100, 1, 2000] + [40] * 300
     n_t, off = len(numels), [0]
     for m in numels:
@@ -346,9 +347,16 @@ def test_updates_in_several_launches_equal_one_launch(form, skip, cap):
         apm.apm_pack_tensors(pool, apm.APM_G16, lst(g), n_t)
         n = apm.lib().apm_pool_pages_in_use(pool.handle)
         norm, q = torch.full((n,), -1.0, device=DEV), torch.zeros_like(g)
-        pages = list(range(n))[::-1] if form == "reversed" else None
+        pages = list(range(n))[::-1] if "reversed" in form else None
         if form == "fused":
             apm.apm_page_adamw_step_fused(pool, pages, n, 3, hyper, lst(g), lst(q), n_t, norm, None)
+        elif "delayed" in form:
+            g_pages = torch.as_tensor(_Region(pool, apm.APM_G16, n * E), device=DEV)
+            apm.apm_delayed_set_outputs(pool, norm, None)
+            apm.apm_step_delayed(pool, pages, n, g_pages.data_ptr(), hyper)
+            apm.apm_delayed_accumulate(pool, pages, n, g_pages.data_ptr())
+            apm.apm_step_delayed(pool, pages, n, None, hyper)
+            apm.apm_unpack(pool, apm.APM_P16, lst(q), n_t)
         else:
             apm.apm_page_adamw_step(pool, pages, n, 3, hyper, norm, None)
             apm.apm_unpack(pool, apm.APM_P16, lst(q), n_t)
