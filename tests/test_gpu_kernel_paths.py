@@ -55,11 +55,13 @@ def test_pack_and_unpack_of_many_tensors_are_bit_exact(n_t):
 
 
 @pytest.mark.parametrize("numels,align", [([1000, 17, 70000, 300001, 9] * 3, 1), ([1000, 17, 70000, 300001, 9] * 3, 4), ([5] * 3 + [4099] * 5 + [1 << 21], 16),
-                                          ([32 << 20, 12345, 7, (1 << 19) + 1, 300], 16), ([32 << 20, 12345, 7, (1 << 19) + 1, 300], 1)])
+                                          ([32 << 20, 12345, 7, (1 << 19) + 1, 300], 16), ([32 << 20, 12345, 7, (1 << 19) + 1, 300], 1),
+                                          ([(66 << 20) + 5, 300, (1 << 19) + 1], 16)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_pack_and_unpack_of_long_and_short_segments_are_bit_exact(dtype, numels, align):
     """Segments of all length classes in one grid; aligned lists below and above the size from which a
-    workgroup is one wavefront, and views of one flat buffer at odd distances."""
+    workgroup is one wavefront, and views of one flat buffer at odd distances.  The pages hold what the oracle's plan
+    says, and nothing else."""
     kind, st, dt = (apm.APM_BF16, apm.APM_G16, torch.int16) if dtype == "bf16" else (apm.APM_F32, apm.APM_P32, torch.int32)
     E, n_t, off, at = 65536, len(numels), [], 0
     for k, n in enumerate(numels):
@@ -69,11 +71,18 @@ def test_pack_and_unpack_of_long_and_short_segments_are_bit_exact(dtype, numels,
     src = torch.randint(-30000, 30000, (at + 64,), device=DEV, dtype=dt, generator=torch.Generator(device=DEV).manual_seed(at))
     out = torch.full_like(src, -7)
     want = torch.full_like(src, -7)
+    plan = oracle.plan_pack(numels, E)
     pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, sum(-(-n // E) for n in numels), state_mask=1 << st)
     lists = [apm.make_tensors(numels, kind, [t.data_ptr() + o * t.element_size() for o in off]) for t in (src, out)]
     apm.apm_pack_tensors(pool, st, lists[0], n_t)
     apm.apm_unpack(pool, st, lists[1], n_t)
     torch.cuda.synchronize()
+    pages = torch.as_tensor(_Region(pool, st, plan.n_pages * E * src.element_size() // 2), device=DEV).view(dt).view(plan.n_pages, E)
+    placed = torch.zeros_like(pages)
+    for s in plan.segments:
+        at = off[s.tensor] + s.tensor_off
+        placed[s.page, s.page_off:s.page_off + s.n] = src[at:at + s.n]
+    assert torch.equal(pages, placed)
     for o, n in zip(off, numels):
         want[o:o + n] = src[o:o + n]
     assert torch.equal(out, want)
@@ -258,7 +267,7 @@ def test_a_hand_over_of_no_pages_is_accepted(numels, clip):
 
 
 class _Region:
-    """A 16-bit class region of a pool as an array torch can wrap."""
+    """A class region of a pool as an array of half words that torch can wrap."""
 
     def __init__(self, pool, state, numel):
         self.__cuda_array_interface__ = {"shape": (numel,), "typestr": "<i2", "data": (apm.apm_pool_state_ptr(pool, state), False), "version": 3}
@@ -469,6 +478,9 @@ def test_fused_step_with_tensors_near_and_far_apart(n_t, apart, listed):
         pool.destroy()
     assert (out[0][0] > 0).all()
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    if apart:  # 66 GiB that no later test needs
+        del raw, near, q_near, part
+        torch.cuda.empty_cache()
 
 
 def _us(f, n):
