@@ -217,7 +217,8 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     std::vector<SegLaunch> launches;
     int32_t ranges = 0;
     if (tables.bytes > 0) {
-        std::unique_ptr<char[]> image(new char[tables.bytes]);
+        struct Free { void operator()(char* p) const { ::operator delete(p, std::align_val_t(alignof(SegRec))); } };
+        std::unique_ptr<char, Free> image(static_cast<char*>(::operator new(tables.bytes, std::align_val_t(alignof(SegRec)))));
         order_segments(plan, reinterpret_cast<SegRec*>(image.get() + tables.at[0]), &launches, &ranges);
         TenantRec* tenants = reinterpret_cast<TenantRec*>(image.get() + tables.at[1]);
         for (size_t k = 0; k < n_in_use; ++k) tenants[k] = TenantRec{{0, 0}, INT32_MAX, {0, 0}, {-1, -1}};
