@@ -76,11 +76,6 @@ ExtentGroups::ExtentGroups(int64_t n, int64_t E, const int32_t* size) : n_(n), s
 }
 
 int ExtentGroups::fold(int64_t worth, ExtentClass cls[kMaxExtentClasses]) {
-    // A class that saves fewer idle workgroups than it is worth is folded into the next larger one.  With launches of its own:  Counted in spans of 1024 elements, four workgroups of the update or half a
-    // copy's; from and to tensors, us a call with the line at 2048 / 4096 / 16384 / 65536 spans: 4.8 M elements in
-    // 64 K pages with clipping 41 / 33 / 33 / 33, in 256 K pages 30 / 30 / 28 / 28, in 1 M pages 32 / 32 / 32 / 53;
-    // 124 M 537 / 537 / 538 / 544; 350 M 1520 / 1518 / 1529 / 1555; packing 122 M 87 / 87 / 85 / 86.  In a common grid, line at 64 / 2048 /
-    // 16384 spans: 124 M 524 / 525 / 529; 7 M in 64 K pages 28.5 / 28.5 / 27.4; 16 M in 1 M pages 22.6 / 21.0 / 23.2.
     int64_t cnt[kMaxExtentClasses], sum[kMaxExtentClasses];
     for (int c = 0; c < kMaxExtentClasses; ++c) {
         into_[c] = c;

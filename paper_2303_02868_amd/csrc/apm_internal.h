@@ -14,7 +14,7 @@
 #if defined(__HIPCC__)
 #define APM_HOST_DEVICE __host__ __device__ __forceinline__
 #else
-#define APM_HOST_DEVICE
+#define APM_HOST_DEVICE inline
 #endif
 
 namespace apm {
@@ -78,17 +78,27 @@ struct ExtentClass {
     int64_t max_used;  // largest size among them (elements)
     int64_t sum_used;  // and the sum of their sizes
 };
-constexpr int64_t kWorthLaunch = 16384;  // for a launch, or a page list, of its own
-constexpr int64_t kWorthGrid = 2048;     // for its part of the pages' common grid
-constexpr int64_t kWorthSegs = 64;       // and of the segments'
+// A class that would save fewer idle workgroups than it is worth joins the next larger one.  Counted in spans of 1024 elements,
+// four workgroups of the update or half a copy's:
+//
+// For a launch, or a page list, of its own.  From and to tensors, us a call with the line at 2048 / 4096 / 16384 / 65536
+// spans: 4.8 M elements in 64 K pages with clipping 41 / 33 / 33 / 33, in 256 K pages 30 / 30 / 28 / 28, in 1 M pages
+// 32 / 32 / 32 / 53; 124 M 537 / 537 / 538 / 544; 350 M 1520 / 1518 / 1529 / 1555.
+constexpr int64_t kWorthLaunch = 16384;
+// For its part of the pages' common grid; line at 64 / 2048 / 16384 spans: 124 M 524 / 525 / 529; 7 M in 64 K pages
+// 28.5 / 28.5 / 27.4; 16 M in 1 M pages 22.6 / 21.0 / 23.2.
+constexpr int64_t kWorthGrid = 2048;
+// For its part of the segments' common grid, where a class costs nothing but its entry; line at 64 / 2048 / 16384 spans / one class:
+// 124 M fp32 out of pages 151.7 / 151.7 / 156.3 / 239, 73 M into 256 K pages 91.9 / 92.9 / 101 / 121, 122 M bf16 flat views
+// 81.5 / 81.5 / 83.2 / 88.7, 12 M out of 256 K pages 9.5 / 9.6 / 10.1 / 11.9.
+constexpr int64_t kWorthSegs = 64;
 // Sizes come as an array, and are counted once whatever is asked of them: a call's host time is spent here
 // when its pages are many and small.
 class ExtentGroups {
 public:
     // E = the size that the class limits are fractions of; the sizes are read until the last call.
     ExtentGroups(int64_t n, int64_t E, const int32_t* size);
-    // Returns the number of classes.  worth: idle spans of 1024 elements that a class has to save (kWorthLaunch,
-    // kWorthGrid, kWorthSegs).
+    // Returns the number of classes.  worth: spans that a class has to save (kWorthLaunch, kWorthGrid, kWorthSegs).
     int fold(int64_t worth, ExtentClass cls[kMaxExtentClasses]);
     // With the classes of the last fold:
     // out[pos] = index of the item at position pos (classes one after the other, the given order kept inside each);
@@ -139,7 +149,7 @@ struct GridMap {
 };
 // Workgroup w's item (a position, counted from the largest class's first) and its number within the item.
 // What the largest class needs are single kernel arguments: the leading ones arrive in registers.
-APM_HOST_DEVICE inline void grid_item(uint32_t large_at, GridDiv d, const GridClass* small, uint32_t w, int* item, uint32_t* x) {
+APM_HOST_DEVICE void grid_item(uint32_t large_at, GridDiv d, const GridClass* small, uint32_t w, int* item, uint32_t* x) {
     int begin = 0;
     uint32_t first = large_at;
     if (w < large_at) {
