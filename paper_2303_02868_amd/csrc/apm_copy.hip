@@ -69,8 +69,11 @@ __device__ __forceinline__ void copy_vectors_shifted(const char* base, int off, 
 // ALIGNED: every address is a multiple of 16; vector for vector, stores written through besides non-temporal: 840 M
 // bf16 elements 539 us a call without, 521 with.  From kManyBytes on in workgroups of one wavefront: 502
 // (of two, with one, two or four vectors a lane: 517 to 570); below, dispatching those takes longer than it gains (us, of one /
-// of four: 43 MB 20.3 / 16.6, 95 MB 34.6 / 33.5, 142 MB 45.2 / 47.4, 202 MB 64.1 / 65.7).
-// Otherwise (views of one flat buffer, odd numels) workgroups of four wavefronts; the stores are still aligned
+// of four: 43 MB 20.3 / 16.6, 95 MB 34.6 / 33.5, 142 MB 45.2 / 47.4, 202 MB 64.1 / 65.7).  In workgroups of one also
+// where no segment has more than kShortBytes, aligned or not: the other three would have nothing to do, but keep
+// their places until the stores of the first have gone through (us, of one / of four: 100 000 segments of 128 bytes 22.8 / 43.6, 65 536
+// of 1 KB 21.4 / 48.9, 30 000 of 1.2 KB 47 / 54, 65 536 of 2 KB 40.1 / 40.1, 8192 of 4 KB 10.7 / 10.0).
+// Otherwise (views of one flat buffer, odd numels) the stores are still aligned
 // 128-bit vectors, the destination's first and last bytes go byte by byte (by the segment's first
 // workgroup), and the vectors in between take whatever source alignment that leaves:
 //   into tensors  the stores start on a cache line, vectors are shifted between lanes, written through besides:
@@ -93,6 +96,7 @@ struct SegArgsInline {
 };
 constexpr int kThreads = 256, kManyThreads = 64;
 constexpr int64_t kManyBytes = (int64_t)128 << 20;
+constexpr int64_t kShortBytes = 2048;
 template <int THREADS> constexpr int64_t kChunk = (int64_t)THREADS * 16;
 
 template <int THREADS, bool ALIGNED, class Args>
@@ -136,7 +140,7 @@ __global__ __launch_bounds__(THREADS) void apm_seg_copy_kernel(const SegRec* seg
     if (x == 0) {
         const int64_t tail_at = head + body;
         const int tail = (int)(nbytes - tail_at), t = (int)threadIdx.x;
-        if (t < (int)head) dst[t] = src[t];
+        for (int k = t; k < (int)head; k += THREADS) dst[k] = src[k];
         if (t < tail) dst[tail_at + t] = src[tail_at + t];
     }
     if (start >= body) return;
@@ -360,9 +364,11 @@ hipError_t launch_seg_copy(const SegCopy& c, const SegLaunch* launches, int64_t 
                     return (int)hipGetLastError();
                 });
         };
-        const hipError_t e = (hipError_t)(!c.aligned ? go(std::false_type{}, std::integral_constant<int, kThreads>{})
-                                           : bytes < kManyBytes ? go(std::true_type{}, std::integral_constant<int, kThreads>{})
-                                                                : go(std::true_type{}, std::integral_constant<int, kManyThreads>{}));
+        const bool is_short = l.n_cls > 0 && l.cls[0].max_used * c.elem_bytes <= kShortBytes;
+        const std::integral_constant<int, kThreads> four;
+        const std::integral_constant<int, kManyThreads> one;
+        const hipError_t e = (hipError_t)(c.aligned ? (is_short || bytes >= kManyBytes ? go(std::true_type{}, one) : go(std::true_type{}, four))
+                                                    : (is_short ? go(std::false_type{}, one) : go(std::false_type{}, four)));
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
