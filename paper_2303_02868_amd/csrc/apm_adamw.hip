@@ -1159,7 +1159,10 @@ struct TakeArgsInline {
 // order of apm_grad_reduce_kernel, so that the update that follows does not read the gradient twice.
 // 355 M parameters with clipping, hand-over beside the update: 2041 us an iteration with copies of whole
 // pages and the sums worked out by the update, 1877 like this; 124 M, four micro-batches, no clipping: 1116
-// and 1030.  Stores written through as the state's are (355 M, hand-over beside the update: 1766 -> 1760 us).  A workgroup then takes a tile; without, 8 elements per lane, the fastest form of a copy.
+// and 1030.  A workgroup then takes a tile; without, 8 elements per lane, the fastest form of a copy.  Stores are written
+// through as the state's are (355 M, hand-over beside the update: 1766 -> 1760 us), but for sums over what is added, where a
+// workgroup goes through its tile in two spans and loads wait behind stores (added with clipping, written through / not:
+// 0.6 M elements 11.6 / 9.4 us, 4.8 M 14.2 / 12.8, 135 M 143.1 / 141.7; without clipping 26 M 25.8 / 27.6).
 template <bool ACCUM, bool SUMS, class Args>
 __global__ __launch_bounds__(kThreads) void apm_grad_take_kernel(Args args) {
     const TakeArgs* ap;
@@ -1207,7 +1210,7 @@ __global__ __launch_bounds__(kThreads) void apm_grad_take_kernel(Args args) {
                         x[u][j] = f32_to_bf16_rne(lo) | (f32_to_bf16_rne(hi) << 16);
                     }
                 }
-                __builtin_amdgcn_raw_buffer_store_b128(x[u], D, (e - start) * 2, 0, kStoreHbm);
+                __builtin_amdgcn_raw_buffer_store_b128(x[u], D, (e - start) * 2, 0, ACCUM && SUMS ? kStoreNT : kStoreHbm);
             }
             if (SUMS) {
                 const int left = used - e;  // boundary vector: elements at or beyond the extent do not count
