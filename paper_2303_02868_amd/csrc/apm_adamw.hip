@@ -1012,8 +1012,9 @@ struct ClipArgs {
     int64_t out_first;
     double max_norm;
     int32_t S;
-    // The launch's classes of extents, the smallest pages first: class k has the workgroups from `first` on,
-    // those of unused entries (the last ones) starting where the grid ends.
+    // The launch's classes of extents, each with the workgroups from `first` on.  Entry 0 is the class of the largest pages, which
+    // comes last in the grid and is there with the first load; the others follow, the smallest pages first; unused ones (the last)
+    // start where entry 0 does.
     struct Class {
         uint32_t first;
         uint32_t n_ahead, n_mixed;  // workgroups of the class's first part, and of its first two
@@ -1041,7 +1042,8 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c,
     uint32_t w = blockIdx.x, i, x;
     PageRec* recs = c.recs;  // with the first round trip
     asm("" : "+s"(recs));
-    const ClipArgs::Class k_ = load_class(c.cls + ((w >= c.cls[1].first) + (w >= c.cls[2].first) + (w >= c.cls[3].first)));
+    ClipArgs::Class k_ = load_class(c.cls);
+    if (w < k_.first) k_ = load_class(c.cls + 1 + (w >= c.cls[2].first) + (w >= c.cls[3].first));
     // item -> page, index among the page's sums (tiles, then the adder) or among its slices
     bool sums = true;
     w -= k_.first;
@@ -1623,7 +1625,7 @@ hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {
             const Items it = items_of(e);
             const int64_t max_used = e.max_used > 0 ? e.max_used : 1, want = (kLookAhead + max_used - 1) / max_used;
             const int64_t ahead = want < e.count ? want : e.count;
-            ClipArgs::Class& q = c.cls[k];
+            ClipArgs::Class& q = c.cls[k == n - 1 ? 0 : k + 1];
             q.first = (uint32_t)at;
             q.n_ahead = (uint32_t)(ahead * (it.tiles + 1));
             q.n_mixed = q.n_ahead + (uint32_t)((e.count - ahead) * it.all);
@@ -1637,7 +1639,7 @@ hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {
             q.slices = grid_div(it.slices);
             at += e.count * it.all;
         }
-        for (int k = n; k < kMaxExtentClasses; ++k) c.cls[k].first = (uint32_t)at;
+        for (int k = n; k < kMaxExtentClasses; ++k) c.cls[k].first = c.cls[0].first;
         c.recs = run ? reinterpret_cast<PageRec*>(reinterpret_cast<PageRun*>(L.recs) + begin) : L.recs + begin;
         c.sums = reinterpret_cast<uint64_t*>(L.partials) + begin * L.S;
         c.out_index = L.out_index ? L.out_index + begin : nullptr;
