@@ -299,9 +299,9 @@ int apm_page_copy_async(apm_pool* dst, int64_t dst_page, apm_pool* src, int64_t 
  * host:   HOST pool storing P32, M32, V32 (the layout is taken from `dev`); it must hold every
  *         page in use unless apm_streamer_set_host_first_page says otherwise (checked per step).
  * dev:    GPU pool storing G16 and P16 for the same pages, with an installed layout.
- * batch_pages: pages moved and updated per pipeline stage of the staged mode (>= 1).
- * n_slots: staging slots in HBM for the staged mode (>= 2); each holds batch_pages pages of the
- *          three fp32 classes.
+ * batch_pages: pages moved and updated per pipeline stage of the staged-DMA mode (>= 1).
+ * n_slots: staging slots in HBM for that mode (>= 2); each holds batch_pages pages of the three
+ *          fp32 classes.  The staged mode and the scheduled step use the same memory.
  * The streamer starts in APM_STREAM_DIRECT if the GPU can address the host pool's memory (pinned
  * memory: always), else in APM_STREAM_STAGED_DMA; see apm_streamer_set_mode.
  */
@@ -317,19 +317,13 @@ int apm_streamer_destroy(apm_streamer* s);
  *     workgroup and so a CU.  One per workgroup moves data fastest; more per workgroup occupy
  *     fewer CUs for the duration of the step, which disturbs concurrent kernels of the caller
  *     less (measured beside dense matrix products: 128 wavefronts, 16 per workgroup).
- *   APM_STREAM_STAGED: the double-buffered pipeline through HBM staging slots.  While batch b is
- *     updated in its slot, ONE copy kernel of the library (direct_wavefronts wavefronts, as above)
- *     brings batch b+1 from its host pages into the next slot and takes batch b-1 from the
- *     previous slot back to its host pages, both directions at once; with two slots the two
- *     directions are two kernels, one after the other.  A batch here is at most batch_pages
- *     pages: the batches are cut so that each holds about as many used elements as the emptiest
- *     run of batch_pages pages (an exchange lasts as long as its longer direction, and the kernel
- *     moves used extents only).  One copy stream and one compute stream;
- *     streams that share a hardware queue would run the update behind each copy kernel, so the
- *     copy stream is chosen, when the mode is first selected, by timing a pair of short kernels
- *     on each of a few candidates (about a millisecond each; synchronises the device).
- *     The staging memory is allocated when a staged mode is first selected.
- *   APM_STREAM_STAGED_DMA: the same slot ring moved by the runtime's asynchronous copies:
+ *   APM_STREAM_STAGED: the double-buffered pipeline through HBM staging slots, in ONE kernel: each of
+ *     its wavefronts (direct_wavefronts of them, as above, but at most as many as the staging memory has
+ *     two 4 KiB slots per class for, 48 or more) brings its next 1024 elements from the host pages into one
+ *     of its slots while it updates the ones in the other and writes them back, so both directions of
+ *     the link are busy for nearly all of the step.  Used extents only; pages that are skipped are not
+ *     moved.  The staging memory is allocated when a staged mode is first selected.
+ *   APM_STREAM_STAGED_DMA: a ring of slots of batch_pages pages moved by the runtime's asynchronous copies:
  *     copy-in / update / copy-out on three streams.  Which stream pairs overlap a host-to-device
  *     with a device-to-host copy depends on the runtime, so when this mode is first selected
  *     short concurrent copies are timed on a few candidate streams (the default stream among
@@ -344,9 +338,9 @@ int apm_streamer_set_mode(apm_streamer* s, int mode, int direct_wavefronts,
 int apm_streamer_get_mode(const apm_streamer* s);
 
 /*
- * One AdamW step over all pages in use.  Staged modes: for batch b, the copy-in of batch b+1 and
+ * One AdamW step over all pages in use.  Staged-DMA mode: for batch b, the copy-in of batch b+1 and
  * the copy-out of batch b-1 run beside update(b) on the compute stream, ordered by events.
- * Direct mode: one reduce pass and one update kernel on the compute stream.
+ * Direct and staged mode: one reduce pass and one update kernel on the compute stream.
  * The work starts after everything enqueued on `stream` so far, and `stream` is made to wait for
  * the step's completion; the host does not block.  grad_norm / skip_mask as in
  * apm_page_adamw_step (device pointers, one entry per page in use, nullable).
@@ -355,8 +349,8 @@ int apm_streamer_step(apm_streamer* s, int64_t step, const apm_hyper* hyper, flo
                       uint8_t* skip_mask, void* stream);
 
 /*
- * How the kernels that write the host pool (the direct mode's update kernel, the staged mode's and
- * the scheduled step's copy kernel) store: non-temporal (on = 0, the default: fastest when nothing
+ * How the kernels that write the host pool (the direct and the staged mode's update kernel, the
+ * scheduled step's copy kernel) store: non-temporal (on = 0, the default: fastest when nothing
  * else runs on the GPU) or written through at system scope (on != 0).  A non-temporal store to host
  * memory may rest in the GPU's L2 as a dirty line; the write-back at the end of every kernel of any
  * other stream then has to push such lines across PCIe, so kernels that run beside the update are
@@ -406,7 +400,7 @@ int apm_streamer_set_page_count(apm_streamer* s, int64_t n_pages);
 
 /*
  * Measurement aid (staged modes only): the same pipeline (streams, events, copy sizes, slot reuse)
- * with the kernels left out.  directions: 1 = copy-in only, 2 = copy-out only, 3 = both.  The data make a round
+ * with the update left out.  directions: 1 = copy-in only, 2 = copy-out only, 3 = both.  The data make a round
  * trip host -> staging -> host, so the host pool's contents are unchanged (with 2 alone, staging
  * contents left by an earlier step are written back: call it only after 1 or 3, or a full step).
  */

@@ -9,7 +9,8 @@
 //   apm_adamw_live_kernel     the same over the pages that the finalize pass did not skip
 //   apm_adamw_clip_kernel     norms, clip scales and the update in one grid
 //   apm_adamw_stride_kernel   the same slice body run by a fixed, small number of wavefronts that
-//                             stride over all slices (fp32 classes in host memory across PCIe)
+//                             stride over all slices (fp32 classes in host memory across PCIe);
+//                             apm_adamw_staged_kernel through staging slots in device memory
 //   apm_grad_take_kernel      g' <- g or g' += g for the buffered gradient of the delayed path
 //
 // All are HBM-bandwidth bound (no reuse, ~50 VALU operations per element at most), so the design
@@ -628,15 +629,29 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     return f32_to_bf16_rne(lo) | (f32_to_bf16_rne(hi) << 16);
 }
 
+// The update of a lane's vector; returns the bf16 parameters.
+__device__ __forceinline__ u32x2 update_vector(const UpdateArgs& a, float scale, u32x2 g, f32x4& p, f32x4& m, f32x4& v) {
+    const float gf[4] = {bf16lo(g[0]), bf16hi(g[0]), bf16lo(g[1]), bf16hi(g[1])};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        float pj = p[j], mj = m[j], vj = v[j];
+        adamw_elem(pj, mj, vj, gf[j], a, scale);
+        p[j] = pj;
+        m[j] = mj;
+        v[j] = vj;
+    }
+    return u32x2{pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3])};
+}
+
 // All loads are issued back to back, one wait, all stores back to back, in one basic block: on this
 // target loads and stores share one counter, and at the entry of a basic block the compiler must
 // assume the worst about what is outstanding.
-// get_scale() is called when the loads are under way.
+// get_scale() is called when the loads are under way.  n: elements of the slice (a multiple of 8), the rest is neither read nor written.
 template <int U, int STORE, class GetScale>
 __device__ __forceinline__ void full_slice(const UpdateArgs& a, GetScale&& get_scale, int lane, float* p_, float* m_, float* v_,
-                                           const uint16_t* g_, uint16_t* q_) {
-    const Rsrc P = make_rsrc(p_, kTile<U> * 4), M = make_rsrc(m_, kTile<U> * 4), V = make_rsrc(v_, kTile<U> * 4);
-    const Rsrc G = make_rsrc(g_, kTile<U> * 2), Q = make_rsrc(q_, kTile<U> * 2);
+                                           const uint16_t* g_, uint16_t* q_, int n = kTile<U>) {
+    const Rsrc P = make_rsrc(p_, n * 4), M = make_rsrc(m_, n * 4), V = make_rsrc(v_, n * 4);
+    const Rsrc G = make_rsrc(g_, n * 2), Q = make_rsrc(q_, n * 2);
     f32x4 p[U], m[U], v[U];
     u32x2 g[U];
 #pragma unroll
@@ -654,16 +669,7 @@ __device__ __forceinline__ void full_slice(const UpdateArgs& a, GetScale&& get_s
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int o = lane * 16 + u * (kWave * 16);
-        const float gf[4] = {bf16lo(g[u][0]), bf16hi(g[u][0]), bf16lo(g[u][1]), bf16hi(g[u][1])};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float pj = p[u][j], mj = m[u][j], vj = v[u][j];
-            adamw_elem(pj, mj, vj, gf[j], a, scale);
-            p[u][j] = pj;
-            m[u][j] = mj;
-            v[u][j] = vj;
-        }
-        const u32x2 q = {pack_bf16(p[u][0], p[u][1]), pack_bf16(p[u][2], p[u][3])};
+        const u32x2 q = update_vector(a, scale, g[u], p[u], m[u], v[u]);
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, p[u]), P, o, 0, STORE);
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, m[u]), M, o, 0, STORE);
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[u]), V, o, 0, STORE);
@@ -671,20 +677,9 @@ __device__ __forceinline__ void full_slice(const UpdateArgs& a, GetScale&& get_s
     }
 }
 
-// A store of fp32 state outside the body above: written through for kStoreHostWT, non-temporal for the others (such
-// slices are few; kStoreHbm makes no difference there).  The write-through form is
-// hand-written because no builtin takes that policy for a 128-bit global store; the wait states keep
-// the next instruction off the data registers, which a store of more than 64 bits still reads right
-// after issue (the compiler does that for its own stores, not for this one).
-template <int STORE>
-__device__ __forceinline__ void store_state(f32x4 x, f32x4* q) {
-    if (STORE == kStoreHostWT) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(q), "v"(x) : "memory");
-    else __builtin_nontemporal_store(x, q);
-}
-
 // A slice that a tenant's end or the page's used extent cuts: one vector at a time, each checked against
 // the used extent; with GATHER / SCATTER g is gathered / p16 scattered lane by lane through the tenants.
-template <int U, bool GATHER, bool SCATTER, int STORE>
+template <int U, bool GATHER, bool SCATTER>
 __device__ __forceinline__ void cut_slice(const UpdateArgs& a, const PageRec& rec, int v0, float* p_, float* m_, float* v_) {
     f32x4* P = reinterpret_cast<f32x4*>(p_);
     f32x4* M = reinterpret_cast<f32x4*>(m_);
@@ -702,19 +697,10 @@ __device__ __forceinline__ void cut_slice(const UpdateArgs& a, const PageRec& re
         if (vi >= nvec) break;
         const u32x2 g = GATHER ? gather_g4(rec, vi << 2) : __builtin_nontemporal_load(G + vi);
         f32x4 p = __builtin_nontemporal_load(P + vi), m = __builtin_nontemporal_load(M + vi), v = __builtin_nontemporal_load(V + vi);
-        const float gf[4] = {bf16lo(g[0]), bf16hi(g[0]), bf16lo(g[1]), bf16hi(g[1])};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float pj = p[j], mj = m[j], vj = v[j];
-            adamw_elem(pj, mj, vj, gf[j], a, rec.scale);
-            p[j] = pj;
-            m[j] = mj;
-            v[j] = vj;
-        }
-        const u32x2 q = {pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3])};
-        store_state<STORE>(p, P + vi);
-        store_state<STORE>(m, M + vi);
-        store_state<STORE>(v, V + vi);
+        const u32x2 q = update_vector(a, rec.scale, g, p, m, v);
+        __builtin_nontemporal_store(p, P + vi);  // whatever the slices' policy: such slices are few
+        __builtin_nontemporal_store(m, M + vi);
+        __builtin_nontemporal_store(v, V + vi);
         if (SCATTER) scatter_q4(rec, vi << 2, q);
         else __builtin_nontemporal_store(q, Q + vi);
     }
@@ -730,7 +716,7 @@ __device__ __forceinline__ void update_slice(const UpdateArgs& a, const PageRec&
     const int k = start >= rec.off1 ? 1 : 0;
     if (start + kTile<U> <= rec.end[k])
         full_slice<U, STORE>(a, [&] { return rec.scale; }, lane, p + start, m + start, v + start, rec.g[k] + start, rec.q[k] + start);
-    else cut_slice<U, GATHER, SCATTER, STORE>(a, rec, (start >> 2) + lane, p, m, v);
+    else cut_slice<U, GATHER, SCATTER>(a, rec, (start >> 2) + lane, p, m, v);
 }
 
 // The HBM-resident form: one grid over the slices of all listed pages (GridMap: classes of extents).  The arguments
@@ -833,16 +819,27 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_live_kernel(const int32
     else walk(std::integral_constant<int, STORE>{});
 }
 
-// The form for fp32 classes that live in pinned host memory and are read and written across
-// PCIe by the kernel itself: a fixed number of wavefronts walks all (position, slice) items of
-// `count` list positions with `nx` slices each, consecutive wavefronts taking consecutive slices.
-// The link needs only some hundred KiB in flight, so a few dozen wavefronts saturate it.  The
-// launch chooses how many of them share a workgroup (and with it a CU): one per workgroup gives
-// the highest transfer rate; packed 8 or 16 to a workgroup they occupy few CUs, which matters
-// beside kernels whose workgroups need a CU's whole register file or LDS (dense matrix
-// products), because a wavefront that lives as long as the whole transfer keeps those off its CU.
+// The form for fp32 classes that live in pinned host memory, read and written across PCIe by the kernel itself: a
+// fixed number of wavefronts shares all slices of `count` list positions.  The link needs only some hundred KiB in
+// flight, so a few dozen wavefronts saturate it.  The launch chooses how many of them share a workgroup (and with it a
+// CU): one per workgroup gives the highest transfer rate; packed 8 or 16 to a workgroup they occupy few CUs, which
+// matters beside kernels whose workgroups need a CU's whole register file or LDS (dense matrix products), because a
+// wavefront that lives as long as the whole transfer keeps those off its CU.
+//
+// The slices that hold used elements of pages not skipped are numbered in list order and dealt out in turn.  A wavefront
+// finds its own by a scan over the extents of 64 positions at a time, one lane each, fetched while it works on the 64
+// before: it never stands on a slice without elements (dealt out by position and slice of the largest page instead, 19 M
+// parameters of 230 pages, 154 of them nearly empty, 5.42 ms a step = 42.9 GB/s each way, like this 4.78 = 48.7; 31 M
+// 7.69 and 7.49; 124 M 30.5 and 30.3).
+//
+// STAGED: a wavefront brings its next slice into its staging slot in device memory while it updates the one before
+// from the other slot and writes it to the host, so both directions of the link are busy from the second slice to the
+// last but one and nothing but the wavefront itself orders the two.  (A batch of pages at a time instead, one copy
+// kernel for both directions beside the update's, each direction idle for two batches of the step: 124 M parameters
+// 34.1 ms a step, like this 30.7; 11 M 4.22 and 2.80; 5 M 1.83 and 1.34.)
 constexpr int kStrideMaxThreads = 1024;
 constexpr int kStrideU = 4;
+static_assert(kTile<kStrideU> * 4 == kLinkSlotBytes, "a staging slot holds a slice");
 
 struct StrideArgs {
     const PageRec* recs;  // as PageRun if RUN
@@ -853,32 +850,164 @@ struct StrideArgs {
     uint16_t* p16;
     int64_t E;
     int64_t count;
-    int nx, n_workers;
+    int n_workers;
+    float* slots[3];      // STAGED: two slices a wavefront
+    int parts;            // STAGED: AdamwLaunch::link_parts
 };
+
+struct LinkSlice {
+    int64_t page;  // list position
+    int start, n;  // elements; n == 0: none
+    int used;
+    float scale;
+};
+template <bool RUN>
+struct LinkWalk {
+    const PageRec* recs;
+    int64_t count, base;
+    int stride, total, t;      // t: of the worker's next slice, among the `total` of positions [base, base + 64)
+    int used, upto;            // lane by lane: extent (0: skipped), slices of [base, base + lane]
+    float scale;
+    PageRun ahead;             // of position base + 64 + lane
+
+    __device__ __forceinline__ PageRun fetch(int64_t at) const {
+        PageRun r{0, 1.0f};
+        at += (int)threadIdx.x & (kWave - 1);
+        if (at < count) r = RUN ? reinterpret_cast<const PageRun*>(recs)[at] : *reinterpret_cast<const PageRun*>(recs + at);
+        return r;
+    }
+    static __device__ __forceinline__ int slices(int used) { return (int)(((uint32_t)used + (kTile<kStrideU> - 1)) / kTile<kStrideU>); }
+    __device__ __forceinline__ void enter(const PageRun& r) {
+        used = r.scale < 0.0f ? 0 : (r.used + 7) & ~7;
+        scale = r.scale;
+        upto = slices(used);
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int x = __shfl_up(upto, off, kWave);
+            if (((int)threadIdx.x & (kWave - 1)) >= off) upto += x;
+        }
+        total = __builtin_amdgcn_readlane(upto, kWave - 1);
+        ahead = fetch(base + kWave);
+    }
+    __device__ __forceinline__ LinkWalk(const PageRec* r, int64_t n, int worker, int workers) : recs(r), count(n), base(0), stride(workers), t(worker) {
+        enter(fetch(0));
+    }
+    __device__ __forceinline__ LinkSlice next() {
+#pragma unroll 1
+        while (t >= total) {
+            if (base + kWave >= count) return LinkSlice{0, 0, 0, 0, 1.0f};
+            t -= total;
+            base += kWave;
+            enter(ahead);
+        }
+        const int l = __popcll(__ballot(upto <= t));  // < 64, as t < total
+        LinkSlice s;
+        s.page = base + l;
+        s.used = __builtin_amdgcn_readlane(used, l);
+        s.scale = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(scale), l));
+        s.start = (t - (__builtin_amdgcn_readlane(upto, l) - slices(s.used))) * kTile<kStrideU>;
+        s.n = min(kTile<kStrideU>, s.used - s.start);
+        t += stride;
+        return s;
+    }
+};
+
+// Where a slice lies.
+struct LinkPlace {
+    float *p, *m, *v;
+    const uint16_t* g;
+    uint16_t* q;
+};
+template <bool RUN>
+__device__ __forceinline__ LinkPlace link_place(const StrideArgs& s, const LinkSlice& x) {
+    if (RUN) {
+        const int64_t at = x.page * s.E + x.start;
+        return LinkPlace{s.p32 + at, s.m32 + at, s.v32 + at, s.g16 + at, s.p16 + at};
+    }
+    PageRec rec{};
+    if (x.n > 0) rec = load_rec(s.recs + x.page);
+    const int64_t at = rec.pofs + x.start;
+    return LinkPlace{s.p32 + at, s.m32 + at, s.v32 + at, rec.g[0] + x.start, rec.q[0] + x.start};
+}
 
 template <bool RUN, bool WT>
 __global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(StrideArgs s, UpdateArgs a) {
     const int lane = (int)threadIdx.x & (kWave - 1);
-    const int waves_per_wg = (int)blockDim.x / kWave;
-    const int worker = (int)blockIdx.x * waves_per_wg + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int worker = (int)blockIdx.x * ((int)blockDim.x / kWave) + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     if (worker >= s.n_workers) return;
-    const int64_t n_items = s.count * s.nx;
+    LinkWalk<RUN> walk(s.recs, s.count, worker, s.n_workers);
 #pragma unroll 1
-    for (int64_t w = worker; w < n_items; w += s.n_workers) {
-        const int64_t i = w / s.nx;
-        const int start = (int)(w % s.nx) * kTile<kStrideU>;
-        PageRec rec;
-        int64_t at;
-        if (RUN) {
-            const PageRun run = load_run(reinterpret_cast<const PageRun*>(s.recs) + i);
-            at = i * s.E;
-            rec = class_rec(run.used, run.scale, 0, 0, 0, s.g16 + at, s.p16 + at);
-        } else {
-            rec = load_rec(s.recs + i);
-            at = rec.pofs;
+    for (;;) {
+        const LinkSlice x = walk.next();
+        if (x.n == 0) return;
+        const LinkPlace at = link_place<RUN>(s, x);
+        full_slice<kStrideU, WT ? kStoreHostWT : kStoreNT>(a, [&] { return x.scale; }, lane, at.p, at.m, at.v, at.g, at.q, x.n);
+    }
+}
+
+// Loads and stores of both directions are one basic block, host reads first: a wait for the slice that came in before
+// then waits for nothing that is issued after it.  Accesses beyond a slice's elements, or of a direction that has no slice,
+// are dropped by the descriptors.
+// UPDATE: else the slices come and go as they are, of the directions in `parts` only.
+// THREADS: a workgroup's most; with 128 registers, which is what 16 wavefronts leave each other, a few are spilled.
+template <bool RUN, bool WT, bool UPDATE, int THREADS>
+__global__ __launch_bounds__(THREADS) void apm_adamw_staged_kernel(StrideArgs s, UpdateArgs a) {
+    constexpr int U = kStrideU, STORE = WT ? kStoreHostWT : kStoreNT;
+    const int lane = (int)threadIdx.x & (kWave - 1);
+    const int worker = (int)blockIdx.x * ((int)blockDim.x / kWave) + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    if (worker >= s.n_workers) return;
+    LinkWalk<RUN> walk(s.recs, s.count, worker, s.n_workers);
+    LinkSlice out{0, 0, 0, 0, 1.0f};
+    LinkPlace out_at{};
+    int slot = 2 * worker;
+    const int o = lane * 16;
+#pragma unroll 1
+    for (;;) {
+        const LinkSlice in = walk.next();
+        if (in.n == 0 && out.n == 0) return;
+        const LinkPlace in_at = link_place<RUN>(s, in);
+        const int n_in = UPDATE || (s.parts & kLinkIn) ? in.n * 4 : 0, n_out = UPDATE || (s.parts & kLinkOut) ? out.n : 0;
+        float* const src[3] = {in_at.p, in_at.m, in_at.v};
+        float* const dst[3] = {out_at.p, out_at.m, out_at.v};
+        u32x4 come[3][U], go[3][U];
+        u32x2 g[U];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                come[k][u] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(src[k], n_in), o + u * (kWave * 16), 0, kNT);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                go[k][u] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(s.slots[k] + (int64_t)(slot ^ 1) * kTile<U>, n_out * 4), o + u * (kWave * 16), 0, 0);
+            if (UPDATE) g[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(make_rsrc(out_at.g, n_out * 2), lane * 8 + u * (kWave * 8), 0, kNT));
         }
-        if (rec.scale < 0.0f || start >= rec.end[0]) continue;
-        update_slice<kStrideU, false, false, WT ? kStoreHostWT : kStoreNT>(a, rec, start, lane, s.p32 + at, s.m32 + at, s.v32 + at);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (UPDATE) {
+                f32x4 p = __builtin_bit_cast(f32x4, go[0][u]), m = __builtin_bit_cast(f32x4, go[1][u]), v = __builtin_bit_cast(f32x4, go[2][u]);
+                const u32x2 q = update_vector(a, out.scale, g[u], p, m, v);
+                go[0][u] = __builtin_bit_cast(u32x4, p);
+                go[1][u] = __builtin_bit_cast(u32x4, m);
+                go[2][u] = __builtin_bit_cast(u32x4, v);
+                __builtin_amdgcn_raw_buffer_store_b64(q, make_rsrc(out_at.q, n_out * 2), lane * 8 + u * (kWave * 8), 0, kNT);
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                __builtin_amdgcn_raw_buffer_store_b128(go[k][u], make_rsrc(dst[k], n_out * 4), o + u * (kWave * 16), 0, STORE);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                __builtin_amdgcn_raw_buffer_store_b128(come[k][u], make_rsrc(s.slots[k] + (int64_t)slot * kTile<U>, n_in), o + u * (kWave * 16), 0, 0);
+        out = in;
+        out_at = in_at;
+        slot ^= 1;
     }
 }
 
@@ -1132,7 +1261,7 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c,
         full_slice<U, kStoreHbm>(a, get_scale, lane, p + start, m + start, v + start, rec.g[k] + start, rec.q[k] + start);
     } else {
         rec.scale = get_scale();
-        cut_slice<U, GATHER, SCATTER, kStoreHbm>(a, rec, (start >> 2) + lane, p, m, v);
+        cut_slice<U, GATHER, SCATTER>(a, rec, (start >> 2) + lane, p, m, v);
     }
 }
 
@@ -1462,24 +1591,26 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
     auto p16 = [&](int64_t at) { return L.p16 + (L.grad_first + at) * L.E; };
     if (L.stride_wavefronts > 0) {
         if (L.gather || L.scatter) return hipErrorInvalidValue;  // host-resident state goes with the page classes
-        return for_each_launch(L, [&](int64_t begin, int64_t ny, int64_t max_used, int64_t sum_used) {
-            const int nx = (int)((max_used + kTile<kStrideU> - 1) / kTile<kStrideU>);
-            const int64_t items = ny * nx;
-            const int workers = (int)(items < L.stride_wavefronts ? items : L.stride_wavefronts);
-            const int per_wg = L.stride_waves_per_wg >= 1 && L.stride_waves_per_wg <= kStrideMaxThreads / kWave ? L.stride_waves_per_wg : 1;
-            const dim3 grid((unsigned)((workers + per_wg - 1) / per_wg)), block((unsigned)(per_wg * kWave));
-            StrideArgs t{run ? reinterpret_cast<const PageRec*>(runs + begin) : L.recs + begin, state(L.p32, begin), state(L.m32, begin),
-                         state(L.v32, begin), nullptr, nullptr, L.E, ny, nx, workers};
-            if (run) {
-                t.g16 = g16(begin);
-                t.p16 = p16(begin);
-                if (L.host_write_through) hipLaunchKernelGGL((apm_adamw_stride_kernel<true, true>), grid, block, 0, s, t, a);
-                else hipLaunchKernelGGL((apm_adamw_stride_kernel<true, false>), grid, block, 0, s, t, a);
-            } else {
-                if (L.host_write_through) hipLaunchKernelGGL((apm_adamw_stride_kernel<false, true>), grid, block, 0, s, t, a);
-                else hipLaunchKernelGGL((apm_adamw_stride_kernel<false, false>), grid, block, 0, s, t, a);
-            }
-        });
+        const int64_t slices = L.n_listed * ((L.E + kTile<kStrideU> - 1) / kTile<kStrideU>);
+        const int workers = (int)(slices < L.stride_wavefronts ? slices : L.stride_wavefronts);
+        const int per_wg = L.stride_waves_per_wg >= 1 && L.stride_waves_per_wg <= kStrideMaxThreads / kWave ? L.stride_waves_per_wg : 1;
+        const dim3 grid((unsigned)((workers + per_wg - 1) / per_wg)), block((unsigned)(per_wg * kWave));
+        const StrideArgs t{L.recs, state(L.p32, 0), state(L.m32, 0), state(L.v32, 0), run ? g16(0) : nullptr, run ? p16(0) : nullptr,
+                           L.E, L.n_listed, workers, {L.link_slots[0], L.link_slots[1], L.link_slots[2]}, L.link_parts};
+        auto go = [&](auto in_a_run, auto written_through) {
+            constexpr bool RUN = decltype(in_a_run)::value, WT = decltype(written_through)::value;
+            if (!L.link_slots[0]) hipLaunchKernelGGL((apm_adamw_stride_kernel<RUN, WT>), grid, block, 0, s, t, a);
+            else if (!(L.link_parts & kLinkUpdate)) hipLaunchKernelGGL((apm_adamw_staged_kernel<RUN, WT, false, kStrideMaxThreads>), grid, block, 0, s, t, a);
+            else if (block.x <= kStrideMaxThreads / 2) hipLaunchKernelGGL((apm_adamw_staged_kernel<RUN, WT, true, kStrideMaxThreads / 2>), grid, block, 0, s, t, a);
+            else hipLaunchKernelGGL((apm_adamw_staged_kernel<RUN, WT, true, kStrideMaxThreads>), grid, block, 0, s, t, a);
+        };
+        const std::true_type yes;
+        const std::false_type no;
+        if (run && L.host_write_through) go(yes, yes);
+        else if (run) go(yes, no);
+        else if (L.host_write_through) go(no, yes);
+        else go(no, no);
+        return hipGetLastError();
     }
     if (L.partials && notes_live(L)) {
         constexpr int U = kSkipU;

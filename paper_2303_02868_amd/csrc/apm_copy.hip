@@ -152,9 +152,9 @@ __global__ __launch_bounds__(THREADS) void apm_seg_copy_kernel(const SegRec* seg
     else copy_vectors_unaligned(src, dst, nvec);
 }
 
-// Both directions of a staged batch exchange in one kernel: the fp32 classes of an incoming batch
-// move from pinned host pages into a staging slot while those of an outgoing batch move from
-// another slot back to their host pages.  A fixed, small number of wavefronts strides over 4 KiB
+// Both directions of an exchange of the scheduled step in one kernel: the fp32 classes of incoming pages
+// move from pinned host pages into staging slots while those of outgoing pages move from
+// other slots back to their host pages.  A fixed, small number of wavefronts strides over 4 KiB
 // items (one 1 KiB span per wavefront instruction, 4 per class and direction in flight); the link
 // is the bound, not the GPU.  One kernel driving both directions keeps them balanced: measured on
 // 3 x 1 GiB each way, 49.3 GB/s each way with 48 wavefronts, against 40-42 when half of the

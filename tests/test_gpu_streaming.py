@@ -1054,3 +1054,45 @@ def test_three_levels_hbm_cache_host_memory_and_files_in_one_step(tmp_path, mode
     assert torch.equal(dev.reg[apm.APM_P16].view(torch.int16), res.reg[apm.APM_P16].view(torch.int16))
     for x in (bounce, host, cache, dev, res):
         x.destroy()
+
+
+@pytest.mark.parametrize("mode", ["direct:1", "direct:5", "direct", "direct:96:16", "staged:1", "staged:5", "staged", "staged:96:16", "staged:48:8+wt"])
+@pytest.mark.parametrize("E,clip,skip", [(1032, 1.0, 0), (64, 0.0, 0), (4104, 0.0, 1)])
+def test_slices_dealt_out_to_wavefronts_equal_resident_bit_exact(E, clip, skip, mode):
+    # what a wavefront of the streamed update finds its slices by: more positions than a scan takes (64), scans in which
+    # every page is skipped, pages of a few elements, slices cut by a page's end (E is no multiple of 1024), more wavefronts than slices
+    numels = [1 + (k * 37) % (E - 1) for k in range(150)] + [3 * E + 9, 1, E, 8, 2 * E + 1000 % E]
+    specs = [synth.TensorSpec(i, f"t{i}", n) for i, n in enumerate(numels)]
+    live = np.array([not skip or i % 5 == 0 and not 20 <= i < 149 for i in range(len(specs))])
+    model = Model(specs, E, seed=21, active_fn=(lambda t: live) if skip else None, align_elems=8)
+    n, n_t = model.plan.n_pages, len(specs)
+    hy = to_hyper(oracle.Hyper(max_grad_norm=clip, skip_mode=skip))
+    res = DevicePool(n, E)
+    apm.apm_pack_tensors(res.pool, apm.APM_P32, model.tensors(model.p_flat), n_t)
+    dev = DevicePool(n, E, states=(apm.APM_G16, apm.APM_P16))
+    apm.apm_pool_set_layout(dev.pool, model.tensors(model.p_flat), n_t)
+    host = apm.apm_pool_create(apm.APM_DEV_HOST, E, n, state_mask=apm.FP32_STATES)
+    apm.apm_page_copy_async(host, 0, res.pool, 0, n, apm.APM_P32)
+    st = apm.apm_streamer_create(host, dev.pool, 2, 2)
+    set_mode(st, mode)
+    norm_r, norm_s = torch.zeros(n, device=DEV), torch.zeros(n, device=DEV)
+    skip_r, skip_s = torch.zeros(n, dtype=torch.uint8, device=DEV), torch.ones(n, dtype=torch.uint8, device=DEV)
+    for t in (1, 2):
+        for pool in (res.pool, dev.pool):
+            apm.apm_pack_tensors(pool, apm.APM_G16, model.tensors(model.grad_flat(t)), n_t)
+        apm.apm_page_adamw_step(res.pool, None, n, t, hy, norm_r, skip_r)
+        apm.apm_streamer_step(st, t, hy, norm_s, skip_s)
+        torch.cuda.synchronize()
+        assert torch.equal(norm_r, norm_s) and torch.equal(skip_r, skip_s)
+        if skip:
+            assert int(skip_r.sum()) > 64
+    for s in (apm.APM_P32, apm.APM_M32, apm.APM_V32):
+        assert np.array_equal(host_view(host, s, n, E).view(np.uint32), res.reg[s].cpu().numpy().view(np.uint32)), f"state {s}"
+    assert torch.equal(dev.reg[apm.APM_P16].view(torch.int16), res.reg[apm.APM_P16].view(torch.int16))
+    if mode.startswith("staged"):  # the pages as they are make the round trip
+        before = host_view(host, apm.APM_P32, n, E).copy()
+        apm.apm_streamer_copy_only(st, 3)
+        torch.cuda.synchronize()
+        assert np.array_equal(before.view(np.uint32), host_view(host, apm.APM_P32, n, E).view(np.uint32))
+    for x in (st, host, dev, res):
+        x.destroy()
