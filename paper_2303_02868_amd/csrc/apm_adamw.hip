@@ -241,7 +241,10 @@ struct ReduceArgs {
 // gradient elements.  Slice 0 always writes (a zero for an empty page); other slices only when
 // they hold used elements.  The fixed order (lane-sequential, wavefront butterfly, wave 0..3)
 // makes the result independent of scheduling.  recs (gather only): from position a.list_offset.
-template <bool GATHER>
+// Without SUMS only whether any element is not zero is wanted: a slice whose first eighth says so is not read any further.
+// (Whole calls, us, with sums / without: 1.08 G elements, an eighth of them live 946 / 896; 541 M, all live 3008 / 2860; 27 M, half live 85.3 /
+// 78.2; 52 M, a tenth live 56.7 / 54.)
+template <bool GATHER, bool SUMS>
 __global__ __launch_bounds__(kThreads) void apm_grad_reduce_kernel(const PageRec* recs, uint32_t large_at, uint32_t per, uint32_t mul,
                                                                    uint32_t shift, ReduceArgs a) {
     int item;
@@ -274,6 +277,43 @@ __global__ __launch_bounds__(kThreads) void apm_grad_reduce_kernel(const PageRec
         else edge = true;
     }
 
+    // the vector at e; elements at or beyond the extent are zero
+    auto load = [&](int e) {
+        u32x4 w = u32x4{0u, 0u, 0u, 0u};
+        if (e < end) {
+            if (GATHER && edge) w = gather_g8(rec, e);
+            else w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(g + e));
+        }
+        return w;
+    };
+    auto cut = [&](u32x4& w, int e) {
+        if (e + 8 > end && e < end) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (e + 2 * j >= end) w[j] = 0u;
+                else if (e + 2 * j + 1 >= end) w[j] &= 0x0000FFFFu;
+            }
+        }
+    };
+    if (!SUMS) {
+        constexpr int kSpans = kReduceTile / (kThreads * 8);
+        const int e0 = start + (int)threadIdx.x * 8;
+        auto any = [&](u32x4 w, int e) {
+            cut(w, e);
+            return (w[0] | w[1] | w[2] | w[3]) & 0x7FFF7FFFu;
+        };
+        uint32_t nz = any(load(e0), e0);
+        if (!__syncthreads_or(nz != 0u) && start + kThreads * 8 < end) {
+            u32x4 w[kSpans - 1];
+#pragma unroll
+            for (int u = 1; u < kSpans; ++u) w[u - 1] = load(e0 + u * (kThreads * 8));
+#pragma unroll
+            for (int u = 1; u < kSpans; ++u) nz |= any(w[u - 1], e0 + u * (kThreads * 8));
+        }
+        const int found = __syncthreads_or(nz != 0u);
+        if (threadIdx.x == 0) a.nzflags[i * a.S + tile] = (uint32_t)found;
+        return;
+    }
     double acc0 = 0.0, acc1 = 0.0;
     uint32_t nz = 0;
     constexpr int U = APM_REDUCE_U;
@@ -285,26 +325,10 @@ __global__ __launch_bounds__(kThreads) void apm_grad_reduce_kernel(const PageRec
         if (e0 - (int)threadIdx.x * 8 >= end) break;   // uniform: the whole span is beyond the extent
         u32x4 w[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = e0 + u * (kThreads * 8);
-            w[u] = u32x4{0u, 0u, 0u, 0u};
-            if (e < end) {
-                if (GATHER && edge) w[u] = gather_g8(rec, e);
-                else w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(g + e));
-            }
-        }
+        for (int u = 0; u < U; ++u) w[u] = load(e0 + u * (kThreads * 8));
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int e = e0 + u * (kThreads * 8);
-            if (e + 8 > end && e < end) {  // boundary vector: drop elements at or beyond the extent
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    uint32_t x = w[u][j];
-                    if (e + 2 * j >= end) x = 0u;
-                    else if (e + 2 * j + 1 >= end) x &= 0x0000FFFFu;
-                    w[u][j] = x;
-                }
-            }
+            cut(w[u], e0 + u * (kThreads * 8));
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint32_t x = w[u][j];
@@ -346,6 +370,7 @@ struct FinalizeArgs {
     float* grad_norm;  // nullable
     uint8_t* skip_mask;  // nullable
     const int32_t* out_index;  // nullable: list position -> index into grad_norm / skip_mask
+    bool sums_wanted;  // else `partials` holds none
 };
 
 // The record of a page that is read from / written to the page classes.
@@ -403,7 +428,7 @@ __global__ __launch_bounds__(WAVES * kWave) void apm_grad_finalize_kernel(Finali
             uint32_t nz = 0;
             for (int k = lane; k < n_slices; k += kWave) {
                 const int64_t at = (a.by_page ? page : i) * a.S + k;
-                s += a.partials[at];
+                if (a.sums_wanted) s += a.partials[at];
                 nz |= a.nzflags[at];
             }
             s = wave_sum_f64(s);
@@ -1475,20 +1500,22 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
     int32_t* live = notes_live(L) ? L.live : nullptr;
     ReduceArgs a{L.g16, L.used, L.grad_pages, L.grad_first, 0, L.E, L.partials, L.nzflags, L.S, live, {}};
     if (L.sums_ready && live) hipLaunchKernelGGL(apm_live_clear_kernel, dim3(1), dim3(kWave), 0, s, live);
+    const bool sums = L.max_norm > 0.0 || L.grad_norm;
+    auto kernel = L.gather ? (sums ? apm_grad_reduce_kernel<true, true> : apm_grad_reduce_kernel<true, false>)
+                           : (sums ? apm_grad_reduce_kernel<false, true> : apm_grad_reduce_kernel<false, false>);
     const ExtentClass all{0, L.n_listed, L.E, L.n_listed * L.E};
     if (!L.sums_ready) e = (hipError_t)for_each_grid(L.n_cls > 0 ? L.cls : &all, L.n_cls > 0 ? L.n_cls : 1, kThreads, L.max_workgroups,
         [](const ExtentClass& c) { return c.max_used > 0 ? (c.max_used + kReduceTile - 1) / kReduceTile : 1; },
         [&](const GridMap& m, int64_t workgroups, int64_t first) -> int {
             a.list_offset = first;
             std::memcpy(a.small, m.small, sizeof a.small);
-            hipLaunchKernelGGL(L.gather ? apm_grad_reduce_kernel<true> : apm_grad_reduce_kernel<false>, dim3((unsigned)workgroups), dim3(kThreads), 0, s,
-                               L.recs + first, m.large_at, m.large.per, m.large.mul, m.large.shift, a);
+            hipLaunchKernelGGL(kernel, dim3((unsigned)workgroups), dim3(kThreads), 0, s, L.recs + first, m.large_at, m.large.per, m.large.mul, m.large.shift, a);
             return (int)hipGetLastError();
         });
     if (e != hipSuccess) return e;
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
                    L.partials, L.nzflags, L.S, L.skip_mode, L.max_norm, L.recs, L.g16, L.p16, L.E, live, {}, 0, L.sums_ready, L.is_run(),
-                   L.gather || L.scatter, nullptr, L.grad_norm, L.skip_mask, L.out_index};
+                   L.gather || L.scatter, nullptr, L.grad_norm, L.skip_mask, L.out_index, sums};
     ExtentClass live_cls[kMaxExtentClasses];
     f.n_cls = live_classes(L, live_cls);
     for (int c = 0; c < f.n_cls; ++c) f.cls_begin[c] = live_cls[c].begin;
@@ -1504,7 +1531,7 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
 hipError_t launch_prepare(const AdamwLaunch& L, hipStream_t s) {
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
                    nullptr, nullptr, L.S, L.skip_mode, 0.0, L.recs, L.g16, L.p16, L.E, nullptr, {}, 0, false, L.is_run(),
-                   false, L.one_pass ? reinterpret_cast<uint64_t*>(L.partials) : nullptr, nullptr, nullptr, nullptr};
+                   false, L.one_pass ? reinterpret_cast<uint64_t*>(L.partials) : nullptr, nullptr, nullptr, nullptr, false};
     hipLaunchKernelGGL(apm_page_recs_kernel, dim3(record_grid(L)),
                        dim3(kThreads), 0, s, f);
     return hipGetLastError();

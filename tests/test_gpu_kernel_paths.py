@@ -822,3 +822,33 @@ def test_a_small_tensor_alone_in_its_page_costs_the_steps_little(skip):
     us.append(_us(lambda: apm.apm_page_adamw_step_noalloc(pool, n, 3, hyper, norm, None), 20))
     pool.destroy()
     assert us[1] < 2 * us[0], us
+
+
+@pytest.mark.parametrize("bits", [0x0001, 0x7F80, 0xFFC1, 0x8000])
+@pytest.mark.parametrize("form", ["pages", "tensors"])
+def test_one_element_decides_whether_a_page_is_skipped(form, bits):
+    """Skipping without norms looks at an eighth of a tile first: one element in or behind it, at a tile's or tensor's end, the smallest subnormal,
+    infinity and NaN count, minus zero does not."""
+    E, T = 40960, 16384
+    at = [0, 2047, 2048, T - 1, T, T + 2047, T + 2048, 2 * T, E - 1]
+    n_t = len(at) + 2
+    numels = [E] * len(at) + [5, 2 * E + 3]     # the last tensors: all zero; one element in its last, partial vector
+    flat = torch.zeros(n_t, 2 * E + 8, dtype=torch.int16, device=DEV)
+    for k, e in enumerate(at):
+        flat[k, e] = bits - 65536 * (bits >> 15)
+    flat[n_t - 1, 2 * E + 2] = bits - 65536 * (bits >> 15)
+    assert flat.stride(0) % 8 == 0
+    g = apm.make_tensors(numels, apm.APM_BF16, [flat[k].data_ptr() for k in range(n_t)])
+    n = len(at) + 1 + 3
+    hy = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.0, apm.APM_SKIP_UNTOUCHED)
+    pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n)
+    apm.apm_pack_tensors(pool, apm.APM_G16, g, n_t)
+    skip = torch.full((n,), 9, dtype=torch.uint8, device=DEV)
+    if form == "pages":
+        apm.apm_page_adamw_step(pool, None, n, 1, hy, None, skip)
+    else:
+        apm.apm_page_adamw_step_fused(pool, None, n, 1, hy, g, None, n_t, None, skip)
+    torch.cuda.synchronize()
+    want = [int(bits == 0x8000)] * len(at) + [1, 1, 1, int(bits == 0x8000)]
+    assert skip.tolist() == want
+    pool.destroy()
