@@ -1319,8 +1319,20 @@ struct TakeArgsInline {
 // through as the state's are (355 M, hand-over beside the update: 1766 -> 1760 us), but for sums over what is added, where a
 // workgroup goes through its tile in two spans and loads wait behind stores (added with clipping, written through / not:
 // 0.6 M elements 11.6 / 9.4 us, 4.8 M 14.2 / 12.8, 135 M 143.1 / 141.7; without clipping 26 M 25.8 / 27.6).
+// It runs beside the update, where its wavefronts add to those in flight, which like the update's own lower the bandwidth
+// beyond some number: so it requests LDS as well, and shares a CU's with the update's (by itself, 21 of one wavefront, or 6 of four where
+// sums are worked out, fit a CU).  Without sums a workgroup is one wavefront: four of them end when the last one does.
+// us an iteration with four-wavefront workgroups / of one / of one with LDS of 5120 / 7680 / 10240: 124 M, one hand-over and three
+// additions 1026 / 1021 / 974 / 966 / 970; 303 M 1535 / 1515 / 1488 / 1495 / 1520; 355 M with sums and LDS of 0 / 14336 / 27136 / 40960: 1798 /
+// 1776 / 1772 / 1800.  From how many elements on: without / with LDS, three additions 6.6 M 77.3 / 76.9, 9.8 M 97.8 / 93.1, 22 M 192 / 177, one with
+// sums 9.8 M 69.2 / 69.8, 13 M 92.5 / 89.8 (4.8 M by itself 10.2 / 11.0); a hand-over alone 6.6 M 39.3 / 39.6, 22 M 116.4 / 116.8, 31 M 160.9 / 159.9, with
+// sums 13 M 72.4 / 74.6, 31 M 165.0 / 165.6.
+constexpr unsigned kTakeLds = 7680, kTakeSumsLds = 27136;
+constexpr int64_t kFewTaken = kFewElems, kFewAdded = (int64_t)8 << 20;
+template <bool SUMS> constexpr int kTakeThreads = SUMS ? kThreads : kWave;
+
 template <bool ACCUM, bool SUMS, class Args>
-__global__ __launch_bounds__(kThreads) void apm_grad_take_kernel(Args args) {
+__global__ __launch_bounds__(kTakeThreads<SUMS>) void apm_grad_take_kernel(Args args) {
     const TakeArgs* ap;
     if constexpr (sizeof(Args) > sizeof(TakeArgs)) ap = &args.a;
     else ap = &args;
@@ -1332,7 +1344,7 @@ __global__ __launch_bounds__(kThreads) void apm_grad_take_kernel(Args args) {
     int64_t page;
     if constexpr (sizeof(Args) > sizeof(TakeArgs)) page = args.page[pos];
     else page = a.order ? a.order[pos] : a.first + pos;
-    constexpr int U = SUMS ? APM_REDUCE_U : 1, kSpan = kThreads * 8 * U, kItem = SUMS ? kReduceTile : kSpan;
+    constexpr int T = kTakeThreads<SUMS>, U = SUMS ? APM_REDUCE_U : 1, kSpan = T * 8 * U, kItem = SUMS ? kReduceTile : kSpan;
     const int used = a.used[page], used8 = (used + 7) & ~7;
     const int start = (int)tile * kItem;
     if (start >= used8 && !(SUMS && tile == 0)) return;
@@ -1347,7 +1359,7 @@ __global__ __launch_bounds__(kThreads) void apm_grad_take_kernel(Args args) {
         u32x4 x[U], y[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int e = at + (u * kThreads + (int)threadIdx.x) * 8;
+            const int e = at + (u * T + (int)threadIdx.x) * 8;
             x[u] = u32x4{0u, 0u, 0u, 0u};
             if (e < end) {
                 x[u] = __builtin_nontemporal_load(src + (e >> 3));
@@ -1356,7 +1368,7 @@ __global__ __launch_bounds__(kThreads) void apm_grad_take_kernel(Args args) {
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int e = at + (u * kThreads + (int)threadIdx.x) * 8;
+            const int e = at + (u * T + (int)threadIdx.x) * 8;
             if (e < end) {
                 if (ACCUM) {
 #pragma unroll
@@ -1394,11 +1406,14 @@ constexpr int kMaxGridY = 65535;
 hipError_t launch_grad_take(const GradTake& t, hipStream_t s) {
     TakeArgsInline in;
     in.a = TakeArgs{t.dst, t.src, t.used, t.order, t.first, t.E, t.sums, t.nzflags, t.S, 0, {}};
-    const int item = t.sums ? kReduceTile : kThreads * 8;
+    const int threads = t.sums ? kTakeThreads<true> : kTakeThreads<false>, item = t.sums ? kReduceTile : threads * 8;
+    int64_t elems = 0;  // at most
+    for (int k = 0; k < t.n_cls; ++k) elems += t.cls[k].sum_used > 0 ? t.cls[k].sum_used : t.cls[k].count * t.cls[k].max_used;
+    const unsigned lds = elems <= (t.accumulate ? kFewAdded : kFewTaken) ? 0 : t.sums ? kTakeSumsLds : kTakeLds;
     // positions of the given classes in one grid
     auto go = [&](const ExtentClass* cls, int n_cls) -> hipError_t {
         while (n_cls > 0 && cls[n_cls - 1].max_used <= 0 && !t.sums) --n_cls;  // nothing to take
-        return (hipError_t)for_each_grid(cls, n_cls, kThreads, t.max_workgroups,
+        return (hipError_t)for_each_grid(cls, n_cls, threads, t.max_workgroups,
             [&](const ExtentClass& c) { return c.max_used > 0 ? (c.max_used + item - 1) / item : 1; },
             [&](const GridMap& m, int64_t workgroups, int64_t first) -> int {
                 in.a.at = (int32_t)first;
@@ -1406,8 +1421,8 @@ hipError_t launch_grad_take(const GradTake& t, hipStream_t s) {
                 const dim3 grid((unsigned)workgroups);
 #define APM_TAKE(ACCUM, SUMS)                                                                                       \
     do {                                                                                                           \
-        if (t.host_pages) hipLaunchKernelGGL((apm_grad_take_kernel<ACCUM, SUMS, TakeArgsInline>), grid, dim3(kThreads), 0, s, in); \
-        else hipLaunchKernelGGL((apm_grad_take_kernel<ACCUM, SUMS, TakeArgs>), grid, dim3(kThreads), 0, s, in.a);   \
+        if (t.host_pages) hipLaunchKernelGGL((apm_grad_take_kernel<ACCUM, SUMS, TakeArgsInline>), grid, dim3(threads), lds, s, in); \
+        else hipLaunchKernelGGL((apm_grad_take_kernel<ACCUM, SUMS, TakeArgs>), grid, dim3(threads), lds, s, in.a);   \
     } while (0)
                 if (t.accumulate && t.sums) APM_TAKE(true, true);
                 else if (t.accumulate) APM_TAKE(true, false);
