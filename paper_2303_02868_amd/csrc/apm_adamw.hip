@@ -6,6 +6,7 @@
 //   apm_adamw_kernel          the fused update (optionally gathering g16 from / scattering p16 to
 //                             the caller's tensors), one workgroup per page slice;
 //                             apm_adamw_run_kernel the same over consecutive pages of the classes
+//   apm_adamw_call_kernel     the same where a call's list and addresses fit its arguments: no pass before it
 //   apm_adamw_live_kernel     the same over the pages that the finalize pass did not skip
 //   apm_adamw_clip_kernel     norms, clip scales and the update in one grid
 //   apm_adamw_stride_kernel   the same slice body run by a fixed, small number of wavefronts that
@@ -199,6 +200,42 @@ __device__ __forceinline__ PageRec load_rec(const PageRec* at) {
 __device__ __forceinline__ PageRun load_run(const PageRun* at) {
     typedef const i32x2 __attribute__((address_space(4))) * Const;
     return __builtin_bit_cast(PageRun, *(Const)reinterpret_cast<const i32x2*>(at));
+}
+
+static_assert(sizeof(PagePlace) == sizeof(i32x16) && sizeof(CallTables) == sizeof(i32x16), "one scalar load each");
+__device__ __forceinline__ i32x16 load_16(const void* at) {
+    typedef const i32x16 __attribute__((address_space(4), aligned(4))) * Const;
+    return *(Const)reinterpret_cast<const i32x16*>(at);
+}
+// The record of a list position, which a stage kernel would have made (with GATHER / SCATTER the tensors' addresses): one dependent scalar
+// load more than a record in memory, two with a list, from tables that stay in the scalar caches.  All that a step needs is fetched
+// at once, the words of both tenants too.
+__device__ __forceinline__ uint32_t call_word(const CallWords* c, uint32_t k) {
+    typedef const uint32_t __attribute__((address_space(4))) * Const;
+    return ((Const)c->word)[k];
+}
+template <bool GATHER, bool SCATTER>
+__device__ __forceinline__ PageRec call_rec(const CallTables& t, const PagePlace& p, const CallWords* c) {
+    uint32_t g[2] = {0, 0}, q[2] = {0, 0};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        if (GATHER) g[k] = call_word(c, (uint32_t)(t.g_at + p.tensor[k]));
+        if (SCATTER) q[k] = call_word(c, (uint32_t)(t.q_at + p.tensor[k]));
+    }
+    if (GATHER || SCATTER) asm("" : "+s"(g[0]), "+s"(g[1]), "+s"(q[0]), "+s"(q[1]));
+    PageRec r;
+    r.used = p.used;
+    r.scale = 1.0f;
+    r.pofs = p.pofs;
+    r.off1 = GATHER || SCATTER ? p.off1 : INT32_MAX;
+    r.pad = 0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        r.end[k] = GATHER || SCATTER ? p.end[k] : k == 0 ? (p.used + 7) & ~7 : 0;
+        r.g[k] = reinterpret_cast<const uint16_t*>(t.g_base + ((uint64_t)g[k] << 4)) + (GATHER ? p.shift[k] : p.pofs);
+        r.q[k] = reinterpret_cast<uint16_t*>(t.q_base + ((uint64_t)q[k] << 4)) + (SCATTER ? p.shift[k] : p.pofs);
+    }
+    return r;
 }
 
 // The workgroup's sum (wavefront butterfly, then wave 0..3) and OR, written by thread 0.
@@ -763,6 +800,25 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_kernel(const PageRec* r
     update_slice<U, GATHER, SCATTER, STORE>(a, rec, start, (int)threadIdx.x, p32 + rec.pofs, m32 + rec.pofs, v32 + rec.pofs);
 }
 
+// The same with records made from the call's words.  first: list position of the map's first item.
+template <int U, bool GATHER, bool SCATTER>
+__global__ __launch_bounds__(kUpdThreads) void apm_adamw_call_kernel(const PagePlace* places, float* p32, float* m32, float* v32, uint32_t large_at,
+                                                                     uint32_t per, uint32_t mul, uint32_t shift, uint32_t first, int listed, UpdateArgs a,
+                                                                     SmallClasses classes, CallWords c) {
+    int item;
+    uint32_t x;
+    grid_item(large_at, GridDiv{per, mul, shift}, classes.small, blockIdx.x, &item, &x);
+    uint32_t place = first + (uint32_t)item;
+    if (listed) place = call_word(&c, 2 * place);
+    // side by side: issued as soon as its address is known, the first would be waited for before the second starts
+    i32x16 at = load_16(places + place), t = load_16(&c.t + (place >> 31));
+    asm("" : "+s"(t), "+s"(at));
+    const PageRec rec = call_rec<GATHER, SCATTER>(__builtin_bit_cast(CallTables, t), __builtin_bit_cast(PagePlace, at), &c);
+    const int start = (int)x * kTile<U>;
+    if (start >= ((rec.used + 7) & ~7)) return;
+    update_slice<U, GATHER, SCATTER, kStoreHbm>(a, rec, start, (int)threadIdx.x, p32 + rec.pofs, m32 + rec.pofs, v32 + rec.pofs);
+}
+
 // The same for a run of pages in the page classes; all pointers are those of the launch's first page.
 // BARE: nothing has written records, `runs` is the page table (int32_t) and the scale is 1: a launch less,
 // eight quarter pages 13.2 -> 10.8 us a call.
@@ -1137,6 +1193,56 @@ __device__ __forceinline__ double tile_sum(const PageRec& rec, int tile, int lan
     return t;
 }
 
+// What wavefront w of the reduce kernel's workgroup adds up of a tile, all loads under way at once.  In a small call every update slice is
+// on the chip before the first page's scale is there, so how long that takes is lost (us a call with a tile / a quarter of it a
+// wavefront: 0.6 M elements 10.9 / 9.4, 4.8 M 29.2 / 27.6, 18 M 88.9 / 84.9).
+constexpr int kTileParts = kThreads / kWave;
+template <bool GATHER>
+__device__ __forceinline__ double part_sum(const PageRec& rec, int tile, int w, int lane) {
+    constexpr int kVectors = kReduceTile / (kThreads * 8);  // of this lane; the next one is a workgroup's span further
+    const int start = tile * kReduceTile, end = min(start + kReduceTile, rec.used);
+    const int k = start >= rec.off1 ? 1 : 0;
+    const bool inside = !GATHER || start + (((end - start) + 7) & ~7) <= rec.end[k];
+    const int first = (w * kWave + lane) * 8;  // element of the tile
+    u32x4 x[kVectors];
+    if (inside) {
+        const Rsrc G = make_rsrc(rec.g[k] + start, end > start ? (((end - start) + 7) & ~7) * 2 : 0);
+#pragma unroll
+        for (int u = 0; u < kVectors; ++u)
+            x[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(G, (first + u * (kThreads * 8)) * 2, 0, 0));
+    } else {  // a tenant ends in this tile: its whole vectors (beyond them a descriptor reads zero), and the one with its last few elements
+#pragma unroll
+        for (int u = 0; u < kVectors; ++u) x[u] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const int low = kk == 0 ? start : max(start, rec.off1), high = min(end, rec.end[kk]);
+            if (high <= low) continue;
+            const Rsrc G = make_rsrc(rec.g[kk] + low, ((high - low) & ~7) * 2);
+#pragma unroll
+            for (int u = 0; u < kVectors; ++u)
+                x[u] |= __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(G, (start - low + first + u * (kThreads * 8)) * 2, 0, 0));
+            const int last = rec.end[kk] & ~7, at = (last - start) / 8;
+            if (last == rec.end[kk] || last < start || last >= end) continue;
+            const u32x4 y = at % kThreads == w * kWave + lane ? gather_g8(rec, last) : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int u = 0; u < kVectors; ++u) x[u] |= u == at / kThreads ? y : u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+    double acc0 = 0.0, acc1 = 0.0;
+#pragma unroll
+    for (int u = 0; u < kVectors; ++u) {
+        const int left = end - (start + first + u * (kThreads * 8));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t v = left >= 2 * j + 2 ? x[u][j] : left == 2 * j + 1 ? x[u][j] & 0x0000FFFFu : 0u;
+            const double lo = (double)bf16lo(v), hi = (double)bf16hi(v);
+            acc0 = fma(lo, lo, acc0);
+            acc1 = fma(hi, hi, acc1);
+        }
+    }
+    return wave_sum_f64(acc0 + acc1);
+}
+
 // A page's sum by one wavefront on its own, in the order of apm_grad_finalize_kernel.  needless() is asked
 // before every tile: if it says yes, the page's scale has come after all.
 template <bool GATHER, class Needless>
@@ -1189,14 +1295,72 @@ __device__ __forceinline__ ClipArgs::Class load_class(const ClipArgs::Class* at)
     return __builtin_bit_cast(ClipArgs::Class, w);
 }
 
-template <bool RUN, bool GATHER, bool SCATTER>
-__global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c, UpdateArgs a) {
+// How wavefronts hand results on: through words that an earlier kernel has marked ...
+struct CallMarked {};
+struct HandedMarked {
+    GlobalU64 sum;    // of the page's tiles
+    GlobalU32 scale;
+    __device__ __forceinline__ void put_sum(int t, double x) const { __hip_atomic_store(sum + t, (uint64_t)__double_as_longlong(x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ bool sum_there(int t, double* x) const {
+        const uint64_t v = poll64(sum + t);
+        *x = __longlong_as_double((long long)v);
+        return v != kNoSum;
+    }
+    __device__ __forceinline__ void put_scale(float x) const { __hip_atomic_store(scale, __float_as_uint(x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ bool scale_there(uint32_t* v) const { return (*v = (uint32_t)__builtin_amdgcn_readfirstlane((int)poll32(scale))) != kNoScale; }
+};
+// ... or that carry the call's number beside the value.  Pages share no cache line (with lines shared: 4.9 M elements 31.9 / 30.8 us a
+// call with words marked / tagged, 25 M 122 / 128; with lines of their own 29.6 and 121).
+struct HandedTagged {
+    GlobalU64 sum, scale;
+    uint32_t number;
+    __device__ __forceinline__ void put(GlobalU64 at, uint32_t x) const { __hip_atomic_store(at, (uint64_t)x << 32 | number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ void put_sum(int part, double x) const {  // of part % kTileParts of tile part / kTileParts
+        const uint64_t u = (uint64_t)__double_as_longlong(x);
+        put(sum + 2 * part, (uint32_t)(u >> 32));
+        put(sum + 2 * part + 1, (uint32_t)u);
+    }
+    __device__ __forceinline__ bool sum_there(int t, double* x) const {
+        uint64_t v[2 * kTileParts];
+#pragma unroll
+        for (int k = 0; k < 2 * kTileParts; ++k) v[k] = poll64(sum + t * (2 * kTileParts) + k);
+        bool there = true;
+#pragma unroll
+        for (int k = 0; k < 2 * kTileParts; ++k) there = there && (uint32_t)v[k] == number;
+#pragma unroll
+        for (int w = 0; w < kTileParts; ++w) {
+            const double s = __longlong_as_double((long long)((v[2 * w] & 0xFFFFFFFF00000000u) | v[2 * w + 1] >> 32));
+            *x = w == 0 ? s : *x + s;
+        }
+        return there;
+    }
+    __device__ __forceinline__ void put_scale(float x) const { put(scale, __float_as_uint(x)); }
+    __device__ __forceinline__ bool scale_there(uint32_t* v) const {
+        const uint64_t x = poll64(scale);
+        *v = (uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32));
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)x) == number;
+    }
+};
+
+// Call: CallMarked, or CallTables / CallWords if no other kernel has prepared anything (a run: `recs` is then the page table).
+template <bool RUN, bool GATHER, bool SCATTER, class Call>
+__global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c, UpdateArgs a, Call call) {
     constexpr int U = APM_UPDATE_U;
+    constexpr bool kMarked = std::is_same<Call, CallMarked>::value;
     const int lane = (int)threadIdx.x;
     uint32_t w = blockIdx.x, i, x;
     PageRec* recs = c.recs;  // with the first round trip
     asm("" : "+s"(recs));
-    ClipArgs::Class k_ = load_class(c.cls);
+    ClipArgs::Class k_;
+    CallTables tables{};
+    if constexpr (kMarked) {
+        k_ = load_class(c.cls);
+    } else {
+        i32x16 k0 = load_16(c.cls), t = load_16(&call);  // the tables come first
+        asm("" : "+s"(k0), "+s"(t));
+        k_ = __builtin_bit_cast(ClipArgs::Class, k0);
+        tables = __builtin_bit_cast(CallTables, t);
+    }
     if (w < k_.first) k_ = load_class(c.cls + 1 + (w >= c.cls[2].first) + (w >= c.cls[3].first));
     // item -> page, index among the page's sums (tiles, then the adder) or among its slices
     bool sums = true;
@@ -1222,24 +1386,39 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c,
     const int32_t wait_limit = k_.wait_limit;
     PageRec rec;
     int64_t at;
-    float* scale_at;
-    if (RUN) {
+    typename std::conditional<kMarked, HandedMarked, HandedTagged>::type hand;
+    if constexpr (RUN) {
         PageRun* r = reinterpret_cast<PageRun*>(recs) + i;
         at = (int64_t)i * c.E;
-        rec = class_rec(load_run(r).used, 0.0f, 0, 0, 0, c.g16 + at, c.p16 + at);
-        scale_at = &r->scale;
-    } else {
+        typedef const int32_t __attribute__((address_space(4))) * Const;
+        const int used = kMarked ? load_run(r).used : ((Const)reinterpret_cast<const int32_t*>(recs))[i];
+        rec = class_rec(used, 0.0f, 0, 0, 0, c.g16 + at, c.p16 + at);
+        if constexpr (kMarked) hand.scale = (GlobalU32) reinterpret_cast<uint32_t*>(&r->scale);
+    } else if constexpr (kMarked) {
         rec = load_rec(recs + i);
         at = rec.pofs;
-        scale_at = &recs[i].scale;
+        hand.scale = (GlobalU32) reinterpret_cast<uint32_t*>(&recs[i].scale);
+    } else {
+        uint32_t place = (uint32_t)tables.first + i;
+        if (tables.listed) place = call_word(&call, 2 * place);
+        rec = call_rec<GATHER, SCATTER>(tables, __builtin_bit_cast(PagePlace, load_rec(reinterpret_cast<const PageRec*>(tables.places) + place)), &call);
+        at = rec.pofs;
     }
-    const GlobalU32 word = (GlobalU32) reinterpret_cast<uint32_t*>(scale_at);
-    const GlobalU64 sum = (GlobalU64)(c.sums + (int64_t)i * c.S);
+    if constexpr (kMarked) {
+        hand.sum = (GlobalU64)(c.sums + (int64_t)i * c.S);
+    } else {
+        hand.sum = (GlobalU64)(tables.sums + (int64_t)i * tag_sums(c.S));
+        hand.scale = (GlobalU64)(tables.scales + (int64_t)i * kTagLine);
+        hand.number = tables.number;
+    }
     const int n_tiles = max(1, (rec.used + kReduceTile - 1) / kReduceTile);
     if (sums && x + 1 < k_.sum.per) {
-        if ((int)x >= n_tiles) return;
-        const double t = tile_sum<GATHER>(rec, (int)x, lane);
-        if (lane == 0) __hip_atomic_store(sum + x, (uint64_t)__double_as_longlong(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int tile = (int)x / (kMarked ? 1 : kTileParts);
+        if (tile >= n_tiles) return;
+        double t;
+        if constexpr (kMarked) t = tile_sum<GATHER>(rec, tile, lane);
+        else t = part_sum<GATHER>(rec, tile, (int)x % kTileParts, lane);
+        if (lane == 0) hand.put_sum((int)x, t);
         return;
     }
     if (sums) {
@@ -1247,20 +1426,23 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c,
         bool all = true;
 #pragma unroll 1
         for (int t = 0; t < n_tiles && all; t += kWave) {
-            uint64_t v = 0;
+            double v = 0.0;
             for (int polls = 0;; ++polls) {
-                v = t + lane < n_tiles ? poll64(sum + t + lane) : 0;
-                all = __all(v != kNoSum);
+                bool there = true;
+                if (t + lane < n_tiles) there = hand.sum_there(t + lane, &v);
+                all = __all(there);
                 if (all || polls >= wait_limit) break;
                 __builtin_amdgcn_s_sleep(4);
             }
-            if (t + lane < n_tiles) s += __longlong_as_double((long long)v);
+            if (t + lane < n_tiles) s += v;
         }
         s = all ? wave_sum_f64(s) : page_sum<GATHER>(rec, n_tiles, lane, [] { return false; });
         const double norm = sqrt(s);
         if (lane != 0) return;
-        __hip_atomic_store(word, __float_as_uint(clip_scale(norm, c.max_norm)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int64_t o = c.out_index ? (int64_t)c.out_index[i] : c.out_first + i;
+        hand.put_scale(clip_scale(norm, c.max_norm));
+        int64_t o = c.out_first + i;
+        if constexpr (!RUN && !kMarked) o = tables.listed ? (int64_t)call_word(&call, 2 * (uint32_t)o + 1) : (int64_t)tables.places[o].page;
+        else if (c.out_index) o = (int64_t)c.out_index[i];
         if (c.grad_norm) c.grad_norm[o] = (float)norm;
         if (c.skip_mask) c.skip_mask[o] = 0;
         return;
@@ -1269,12 +1451,13 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_clip_kernel(ClipArgs c,
     if (start >= ((rec.used + 7) & ~7)) return;
     // called when the slice's loads are under way: the first poll comes back with them
     auto get_scale = [&]() -> float {
-        uint32_t seen = kNoScale;
-        auto look = [&] { return (seen = (uint32_t)__builtin_amdgcn_readfirstlane((int)poll32(word))) != kNoScale; };
+        uint32_t seen = 0;
+        bool there = false;
+        auto look = [&] { return there = hand.scale_there(&seen); };
         for (int polls = 0; !look(); ++polls) {
             if (polls >= wait_limit) {
                 const double s = page_sum<GATHER>(rec, n_tiles, lane, [&] { return wait_limit > 0 && look(); });
-                return seen == kNoScale ? clip_scale(sqrt(s), c.max_norm) : __uint_as_float(seen);
+                return there ? __uint_as_float(seen) : clip_scale(sqrt(s), c.max_norm);
             }
             __builtin_amdgcn_s_sleep(2);
         }
@@ -1722,12 +1905,19 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
             std::memcpy(classes.small, m.small, sizeof classes.small);
 #define APM_LAUNCH_UPDATE(G, Q, STORE) hipLaunchKernelGGL((apm_adamw_kernel<U, G, Q, STORE>), dim3((unsigned)workgroups), dim3(kUpdThreads), lds, s, L.recs + first, \
                                                    L.p32, L.m32, L.v32, m.large_at, m.large.per, m.large.mul, m.large.shift, a, classes)
-            if (L.gather && L.scatter) APM_LAUNCH_UPDATE(true, true, kStoreHbm);
+#define APM_LAUNCH_CALL(G, Q) hipLaunchKernelGGL((apm_adamw_call_kernel<U, G, Q>), dim3((unsigned)workgroups), dim3(kUpdThreads), lds, s, L.call->t.places, \
+                                                 L.p32, L.m32, L.v32, m.large_at, m.large.per, m.large.mul, m.large.shift, (uint32_t)first, L.call->t.listed, a, classes, *L.call)
+            if (L.call && L.gather && L.scatter) APM_LAUNCH_CALL(true, true);
+            else if (L.call && L.gather) APM_LAUNCH_CALL(true, false);
+            else if (L.call && L.scatter) APM_LAUNCH_CALL(false, true);
+            else if (L.call) APM_LAUNCH_CALL(false, false);
+            else if (L.gather && L.scatter) APM_LAUNCH_UPDATE(true, true, kStoreHbm);
             else if (L.gather) APM_LAUNCH_UPDATE(true, false, kStoreHbm);
             else if (L.scatter) APM_LAUNCH_UPDATE(false, true, kStoreHbm);
             else if (L.beside_link) APM_LAUNCH_UPDATE(false, false, kStoreNT);
             else APM_LAUNCH_UPDATE(false, false, kStoreHbm);
 #undef APM_LAUNCH_UPDATE
+#undef APM_LAUNCH_CALL
             return (int)hipGetLastError();
         });
     }
@@ -1771,11 +1961,12 @@ hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {
     const ExtentClass all{0, L.n_listed, L.E, L.n_listed * L.E};
     const ExtentClass* cls = L.n_cls > 0 ? L.cls : &all;
     const int n_cls = L.n_cls > 0 ? L.n_cls : 1;
-    struct Items { int64_t tiles, slices, all; };
-    auto items_of = [](const ExtentClass& e) {
+    struct Items { int64_t sums, slices, all; };
+    const int64_t per_tile = L.call ? kTileParts : 1;
+    auto items_of = [&](const ExtentClass& e) {
         const int64_t max_used = e.max_used > 0 ? e.max_used : 1;
-        const int64_t tiles = (max_used + kReduceTile - 1) / kReduceTile, slices = slices_of<APM_UPDATE_U>(e);
-        return Items{tiles, slices, tiles + 1 + slices};
+        const int64_t sums = (max_used + kReduceTile - 1) / kReduceTile * per_tile + 1, slices = slices_of<APM_UPDATE_U>(e);
+        return Items{sums, slices, sums + slices};
     };
     int64_t total = 0, elems = 0;
     for (int k = 0; k < n_cls; ++k) {
@@ -1800,14 +1991,14 @@ hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {
             const int64_t ahead = want < e.count ? want : e.count;
             ClipArgs::Class& q = c.cls[k == n - 1 ? 0 : k + 1];
             q.first = (uint32_t)at;
-            q.n_ahead = (uint32_t)(ahead * (it.tiles + 1));
+            q.n_ahead = (uint32_t)(ahead * it.sums);
             q.n_mixed = q.n_ahead + (uint32_t)((e.count - ahead) * it.all);
             q.begin = (int32_t)(e.begin - begin);
             q.ahead = (int32_t)ahead;
             // a page's sums are added up 64 at a time, a round trip each
-            q.wait_limit = L.wait_limit + (int32_t)((int64_t)L.wait_limit * it.tiles / 4096);
+            q.wait_limit = L.wait_limit + (int32_t)((int64_t)L.wait_limit * ((max_used + kReduceTile - 1) / kReduceTile) / 4096);
             q.after = (uint32_t)(e.count - ahead);
-            q.sum = grid_div(it.tiles + 1);
+            q.sum = grid_div(it.sums);
             q.both = grid_div(it.all);
             q.slices = grid_div(it.slices);
             at += e.count * it.all;
@@ -1824,11 +2015,25 @@ hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {
         c.g16 = L.g16 + b16;
         c.p16 = L.p16 + b16;
         const dim3 grid((unsigned)at), block(kUpdThreads);
-        if (run) hipLaunchKernelGGL((apm_adamw_clip_kernel<true, false, false>), grid, block, lds, s, c, a);
-        else if (L.gather && L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, true>), grid, block, lds, s, c, a);
-        else if (L.gather) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, false>), grid, block, lds, s, c, a);
-        else if (L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, false, true>), grid, block, lds, s, c, a);
-        else hipLaunchKernelGGL((apm_adamw_clip_kernel<false, false, false>), grid, block, lds, s, c, a);
+        auto start = [&](auto call) {
+            typedef decltype(call) Call;
+            if (L.gather && L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, true, Call>), grid, block, lds, s, c, a, call);
+            else if (L.gather) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, true, false, Call>), grid, block, lds, s, c, a, call);
+            else if (L.scatter) hipLaunchKernelGGL((apm_adamw_clip_kernel<false, false, true, Call>), grid, block, lds, s, c, a, call);
+            else hipLaunchKernelGGL((apm_adamw_clip_kernel<false, false, false, Call>), grid, block, lds, s, c, a, call);
+        };
+        if (!L.call) {
+            if (run) hipLaunchKernelGGL((apm_adamw_clip_kernel<true, false, false, CallMarked>), grid, block, lds, s, c, a, CallMarked{});
+            else start(CallMarked{});
+        } else {
+            CallWords call = *L.call;
+            call.t.sums += begin * tag_sums(L.S);
+            call.t.scales += begin * kTagLine;
+            call.t.first = (int32_t)begin;
+            if (run) c.recs = reinterpret_cast<PageRec*>(const_cast<int32_t*>(L.used + L.grad_first + begin));
+            if (run) hipLaunchKernelGGL((apm_adamw_clip_kernel<true, false, false, CallTables>), grid, block, lds, s, c, a, call.t);
+            else start(call);
+        }
         return hipGetLastError();
     };
     if (total <= (L.max_workgroups > 0 ? L.max_workgroups : max_workgroups(kUpdThreads))) return n_cls > 0 ? go(cls, n_cls) : hipSuccess;

@@ -258,6 +258,46 @@ struct __attribute__((aligned(64))) PageRec {
     int32_t pad;
 };
 
+// A page in use as the layout has it, in launch order (apm_pool::d_places): element e of the page is element e + shift[k] of tensor
+// tensor[k], where k = 1 from off1 on, and tenant k ends before page element end[k] (0, and some tensor: no such tenant).
+struct __attribute__((aligned(64))) PagePlace {
+    int64_t shift[2];
+    int64_t pofs;  // the page's first element in the classes
+    int32_t used;
+    int32_t page;
+    int32_t off1;
+    int32_t end[2];
+    int32_t tensor[2];
+    int32_t pad[3];
+};
+// A call whose words fit the arguments of its one launch needs no stage kernel before it: the wavefronts make the records they need
+// from the layout's table and the words.  What one wavefront of the clipped update hands to another (a tile's sum, a page's scale) then
+// carries the call's number, so nothing needs marking either.
+constexpr int kTagLine = 8;  // words of a cache line: pages share none, they are polled from all over the chip
+APM_HOST_DEVICE int tag_sums(int S) { return kTagLine * S; }  // a tile is summed up in four parts
+struct CallTables {
+    const PagePlace* places;
+    uint64_t g_base, q_base;  // the tensors' addresses are multiples of 16 from there; or the page class, if it is not the caller's tensors
+    uint64_t* sums;           // [n_listed * tag_sums(S)] per tile: upper and lower half of each part's sum above the call's number
+    uint64_t* scales;         // [n_listed * kTagLine] a page's scale above the call's number
+    uint32_t number;          // never 0, which is what the words hold at first
+    int32_t g_at, q_at;       // words of the tensors' addresses
+    int32_t listed;           // words 2 i, 2 i + 1: place in the table and output index of list position i; else the position itself and its page
+    int32_t first;            // list position of the launch's first page
+    int32_t pad;
+};
+constexpr int kCallWords = 2 * kArgWords;
+// Up to how many elements: where a call is large, a longer way to a wavefront's first load costs as much as the stage kernel did (us a
+// call, with a stage / prepare kernel / without; no norms, from and to tensors, and a reversed list: 0.6 M 9.3 / 6.3, 8 M - and 41.7 / 38.5, 10 M 49.7 /
+// 47.9 and 52.0 / 50.7, 22 M 97.9 / 95.9 and 101.1 / 99.6, 49 M 212 / 211 and 213 / 211, 67 M 299 / 298 and 292 / 289, 124 M 528 / 531 and - ; with norms:
+// 0.6 M 13.3 / 9.4, 2.5 M 26.8 / 20.6, 4.9 M 32.3 / 28.0 and 31.4 / 27.5, 18 M 90.6 / 84.9 and 90.1 / 86.4, 25 M 122 / 120 and 132 / 132, 49 M 226 / 232 and
+// 222 / 223).
+constexpr int64_t kCallElems = (int64_t)64 << 20, kCallSumElems = (int64_t)24 << 20;
+struct CallWords {
+    CallTables t;
+    uint32_t word[kCallWords];
+};
+
 // Wavefronts of the update kernel when it reads and writes fp32 classes in host memory across
 // PCIe (the streamer's direct mode, the file tier's window); see apm_stream.hip for the sweep.
 constexpr int kDirectWavefronts = 48;
@@ -314,6 +354,7 @@ struct AdamwLaunch {
                                   // every sum in `partials` as not there yet
     int32_t wait_limit;           // polls after which a wavefront of it computes what it waits for by itself
     int64_t max_workgroups;       // of a one-dimensional launch; 0: what the hardware takes
+    const CallWords* call;        // nullptr: recs (and sums) are written by a stage / prepare pass
     bool is_run() const { return !state_pages && !grad_pages && !gather && !scatter; }
 };
 
@@ -448,6 +489,8 @@ struct apm_pool {
     std::vector<apm::SegLaunch> seg_launches;
     int32_t seg_ranges = 0;         // groups of kArgWords tensors they are split into
     apm::TenantRec* d_tenants = nullptr;  // by page in use
+    apm::PagePlace* d_places = nullptr;   // pages in use in launch order; nullptr: more than kMaxPlaces
+    std::vector<int32_t> place_of;        // by page in use: its index there
     // All pages in use, grouped by extent (see group_by_extent, kWorthGrid): launch order; d_order_out = the same as
     // 32-bit output indices.  order_plain: the order is 0, 1, 2, ... and has no tables.
     int64_t* d_order = nullptr;
@@ -464,6 +507,8 @@ struct apm_pool {
     double* d_partials = nullptr;   // reduce scratch, n_pages * S
     uint32_t* d_nzflags = nullptr;
     apm::PageRec* d_recs = nullptr;   // n_pages entries
+    uint64_t* d_tagged = nullptr;     // CallTables: scales, then sums, of n_pages each; allocated on first use
+    uint32_t call_number = 0;         // of the last call that used it
     int32_t* d_live = nullptr;        // kLiveInts(n_pages) entries
     // what a call's list comes to (apm_stage_kernel), n_pages entries each, allocated on first use; like the scratch above they belong to the one step that is running on the pool
     int64_t* d_list = nullptr;
@@ -523,6 +568,10 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
                  const apm_tensor* p16_tensors = nullptr, int64_t n_tensors = 0,
                  double* page_sums = nullptr, uint32_t* page_nzflags = nullptr);
 int ensure_scratch(apm_pool* pool, bool list = false);
+// The number of the next call, on stream s, and where it hands results on; false if there is no memory for that.
+bool next_call(apm_pool* pool, hipStream_t s, CallTables* out);
+// Pages in use beyond which a call's words do not fit its arguments, or a launch more costs it little.
+constexpr int64_t kMaxPlaces = 16384;
 // Pages [first, first + n) as one class, each launched with the grid of the layout's largest page.
 ExtentClass run_class(const apm_pool* pool, int64_t first, int64_t n);
 bool wide_pays(const ExtentClass& c);  // AdamwLaunch::wide for it
@@ -576,3 +625,5 @@ struct ScopedTiming {
 extern "C" int apm_test_set_max_workgroups(apm_pool* pool, int64_t max_workgroups);
 // The same for AdamwLaunch::wait_limit (0: wavefronts that would wait for another one's result never do).
 extern "C" int apm_test_set_wait_limit(apm_pool* pool, int32_t wait_limit);
+// The number of the pool's last call that handed results on under one (0: the next one clears them).
+extern "C" int apm_test_set_call_number(apm_pool* pool, uint32_t number);

@@ -79,6 +79,29 @@ int ensure_scratch(apm_pool* pool, bool list) {
     return rc;
 }
 
+bool next_call(apm_pool* pool, hipStream_t s, CallTables* out) {
+    const size_t n = (size_t)pool->desc.n_pages, words = n * (size_t)(kTagLine + tag_sums(pool->S));
+    if (!pool->d_tagged) {
+        if (hipMalloc((void**)&pool->d_tagged, words * sizeof(uint64_t)) != hipSuccess) {
+            (void)hipGetLastError();
+            pool->d_tagged = nullptr;
+            return false;
+        }
+        pool->call_number = 0;
+    }
+    // cleared when new, and when the numbers come round: there is no telling when a word was last written
+    if (++pool->call_number == 0) pool->call_number = 1;
+    if (pool->call_number == 1 && hipMemsetAsync(pool->d_tagged, 0, words * sizeof(uint64_t), s) != hipSuccess) {
+        (void)hipGetLastError();
+        pool->call_number = 0;  // the next call clears
+        return false;
+    }
+    out->scales = pool->d_tagged;
+    out->sums = pool->d_tagged + n * kTagLine;
+    out->number = pool->call_number;
+    return true;
+}
+
 namespace {
 
 size_t region_bytes(const apm_pool* p, int state) {
@@ -124,6 +147,7 @@ void free_pool(apm_pool* pool) {
     if (pool->d_partials) (void)hipFree(pool->d_partials);
     if (pool->d_nzflags) (void)hipFree(pool->d_nzflags);
     if (pool->d_recs) (void)hipFree(pool->d_recs);
+    if (pool->d_tagged) (void)hipFree(pool->d_tagged);
     if (pool->d_live) (void)hipFree(pool->d_live);
     if (pool->d_list) (void)hipFree(pool->d_list);
     if (pool->d_list_out) (void)hipFree(pool->d_list_out);
@@ -205,20 +229,24 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     // Tables for the device, in one allocation and one upload; freed unless the pool takes it over at the end.
     struct Tables {
         char* d = nullptr;
-        size_t at[4], bytes = 0;
+        size_t at[5], bytes = 0;
         ~Tables() { if (d) (void)hipFree(d); }
     } tables;
     const size_t n_order = plain ? 0 : n_in_use;
-    const size_t len[4] = {plan.segs.size() * sizeof(SegRec), n_in_use * sizeof(TenantRec), n_order * sizeof(int64_t), n_order * sizeof(int32_t)};
-    for (int k = 0; k < 4; ++k) {
+    const size_t n_places = n_in_use <= (size_t)kMaxPlaces ? n_in_use : 0;
+    const size_t len[5] = {plan.segs.size() * sizeof(SegRec), n_in_use * sizeof(TenantRec), n_order * sizeof(int64_t), n_order * sizeof(int32_t),
+                           n_places * sizeof(PagePlace)};
+    for (int k = 0; k < 5; ++k) {
         tables.at[k] = tables.bytes;
         tables.bytes += (len[k] + 255) / 256 * 256;
     }
     std::vector<SegLaunch> launches;
+    std::vector<int32_t> place_of(n_places);
     int32_t ranges = 0;
     if (tables.bytes > 0) {
-        struct Free { void operator()(char* p) const { ::operator delete(p, std::align_val_t(alignof(SegRec))); } };
-        std::unique_ptr<char, Free> image(static_cast<char*>(::operator new(tables.bytes, std::align_val_t(alignof(SegRec)))));
+        static_assert(alignof(PagePlace) >= alignof(SegRec), "the image is aligned for every table");
+        struct Free { void operator()(char* p) const { ::operator delete(p, std::align_val_t(alignof(PagePlace))); } };
+        std::unique_ptr<char, Free> image(static_cast<char*>(::operator new(tables.bytes, std::align_val_t(alignof(PagePlace)))));
         order_segments(plan, reinterpret_cast<SegRec*>(image.get() + tables.at[0]), &launches, &ranges);
         TenantRec* tenants = reinterpret_cast<TenantRec*>(image.get() + tables.at[1]);
         for (size_t k = 0; k < n_in_use; ++k) tenants[k] = TenantRec{{0, 0}, INT32_MAX, {0, 0}, {-1, -1}};
@@ -235,6 +263,20 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
         for (size_t k = 0; k < n_order; ++k) {
             d_order[k] = order[k];
             d_order_out[k] = (int32_t)order[k];
+        }
+        PagePlace* places = reinterpret_cast<PagePlace*>(image.get() + tables.at[4]);
+        for (size_t k = 0; k < n_places; ++k) {
+            const TenantRec& t = tenants[order[k]];
+            PagePlace p{{0, 0}, order[k] * plan.E, used[(size_t)order[k]], (int32_t)order[k], t.off1, {0, 0}, {0, 0}, {}};
+            for (int j = 0; j < 2; ++j) {
+                if (t.tensor[j] < 0) continue;
+                const int32_t off = j == 0 ? 0 : t.off1;
+                p.shift[j] = t.tensor_off[j] - off;
+                p.end[j] = off + t.n[j];
+                p.tensor[j] = t.tensor[j];
+            }
+            places[k] = p;
+            place_of[(size_t)order[k]] = (int32_t)k;
         }
         hipError_t e = hipMalloc((void**)&tables.d, tables.bytes);
         if (e == hipSuccess) e = hipMemcpy(tables.d, image.get(), tables.bytes, hipMemcpyHostToDevice);
@@ -262,6 +304,8 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     pool->d_tenants = reinterpret_cast<TenantRec*>(pool->d_tables + tables.at[1]);
     pool->d_order = reinterpret_cast<int64_t*>(pool->d_tables + tables.at[2]);
     pool->d_order_out = reinterpret_cast<int32_t*>(pool->d_tables + tables.at[3]);
+    pool->d_places = n_places ? reinterpret_cast<PagePlace*>(pool->d_tables + tables.at[4]) : nullptr;
+    pool->place_of.swap(place_of);
     pool->used.swap(used);  // `used`: the old layout's
     if (pool->buffered && pool->buf_by_extent && pool->buf_extents.empty()) pool->buf_extents = std::move(used);
     pool->used_sum.swap(used_sum);

@@ -86,6 +86,45 @@ namespace {
 constexpr int64_t kMaxStageLaunches = 4;
 }  // namespace
 
+// The base from which a list's addresses are multiples of 16 that fit half words, if there is one.
+static bool base_of(const apm_tensor* t, int64_t n, uint64_t* base) {
+    uint64_t low = UINT64_MAX, high = 0;
+    for (int64_t i = 0; i < n; ++i) {
+        if (t[i].numel == 0) continue;
+        const uint64_t at = reinterpret_cast<uint64_t>(t[i].data);
+        if (at < low) low = at;
+        if (at > high) high = at;
+    }
+    *base = low <= high ? low : 0;
+    return low > high || (high - low) >> 4 <= UINT32_MAX;
+}
+
+// The words of a call: the list (in launch order) and the addresses.  False if they do not go into half words, if a page is not the
+// layout's, or if the launch is captured: a replay would carry the same number, so there the words have to be marked.
+static bool fill_call(const apm_pool* pool, const int64_t* pages, int64_t n_placed, const std::vector<int64_t>& order, const apm_tensor* g,
+                      int64_t n_g, const apm_tensor* q, int64_t n_q, hipStream_t stream, CallWords* call) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (capture != hipStreamCaptureStatusNone || !base_of(g, n_g, &call->t.g_base) || !base_of(q, n_q, &call->t.q_base)) return false;
+    uint32_t* w = call->word;
+    for (int64_t k = 0; k < n_placed; ++k) {
+        const int64_t at = order.empty() ? k : order[(size_t)k], page = pages ? pages[at] : at;
+        if (page >= (int64_t)pool->place_of.size()) return false;
+        *w++ = (uint32_t)pool->place_of[(size_t)page];
+        *w++ = (uint32_t)at;
+    }
+    // an empty tensor's address may be anything: it is nobody's tenant
+    call->t.g_at = (int32_t)(w - call->word);
+    for (int64_t i = 0; i < n_g; ++i) *w++ = (uint32_t)((reinterpret_cast<uint64_t>(g[i].data) - call->t.g_base) >> 4);
+    call->t.q_at = (int32_t)(w - call->word);
+    for (int64_t i = 0; i < n_q; ++i) *w++ = (uint32_t)((reinterpret_cast<uint64_t>(q[i].data) - call->t.q_base) >> 4);
+    call->t.places = pool->d_places;
+    return true;
+}
+
 int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t step,
                  const apm_hyper* hyper, const uint16_t* g16_override, float* grad_norm,
                  uint8_t* skip_mask, hipStream_t stream, const apm_tensor* grad_tensors,
@@ -138,7 +177,10 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     const bool whole = !pages && n_pages == in_use;
     const bool tensors = grad_tensors || p16_tensors;
     std::vector<int64_t> order;
-    bool run = whole && (tensors ? pool->order_plain : pool->order_run);
+    // (With norms in one launch that makes its own records finer classes are worth more: 4.9 M elements in 256 K pages with clipping, us a call,
+    // as a run 34.1, in classes 27.9; 24 M 114.3 and 107.2.)
+    const bool norms = (L.max_norm > 0.0 || grad_norm) && L.skip_mode == APM_SKIP_NONE && !page_sums;
+    bool run = whole && (tensors || (norms && pool->d_places && pool->used_sum.back() <= kCallSumElems) ? pool->order_plain : pool->order_run);
     if (whole) {
         const bool as_run = run && !tensors;
         L.n_cls = as_run ? pool->run_n_cls : pool->order_n_cls;
@@ -169,24 +211,32 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     const int64_t lists = (n_g > 0) + (n_q > 0), n_words = tensors ? n_tensors : 0;
     int64_t launches = stage_launches(n_list, lists, n_words, false);
     const int64_t narrow_launches = stage_launches(n_list, lists, n_words, true);
-    auto base_of = [&](const apm_tensor* t, int64_t n, uint64_t* base) {
-        uint64_t low = UINT64_MAX, high = 0;
-        for (int64_t i = 0; i < n; ++i) {
-            if (t[i].numel == 0) continue;
-            const uint64_t at = reinterpret_cast<uint64_t>(t[i].data);
-            if (at < low) low = at;
-            if (at > high) high = at;
-        }
-        *base = low <= high ? low : 0;
-        return low > high || (high - low) >> 4 <= UINT32_MAX;
-    };
     if (narrow_launches < launches && narrow_launches <= kMaxStageLaunches) {
         sc.narrow = base_of(grad_tensors, n_g, &sc.g_base) && base_of(p16_tensors, n_q, &sc.q_base);
         if (sc.narrow) launches = narrow_launches;
     }
     const bool by_ring = launches > kMaxStageLaunches;
     // A list alone that goes through the ring is read there by the step's kernels: no stage kernel.
-    const bool staged = tensors || (n_list > 0 && !by_ring);
+    bool staged = tensors || (n_list > 0 && !by_ring);
+    L.n_listed = n_pages;
+    // One launch whose arguments hold all the words needs no kernel before it.
+    CallWords call;
+    const bool places = !run || tensors;  // else the page table will do
+    call.t.listed = places && !whole;
+    const int64_t n_placed = call.t.listed ? n_pages : 0;
+    int64_t elems = 0;
+    for (int c = 0; c < L.n_cls; ++c) elems += L.cls[c].sum_used;
+    const bool in_call = (need_reduce ? norms && elems <= kCallSumElems : places && elems <= kCallElems) &&  // a bare run has nothing to save
+                         2 * n_placed + n_g + n_q <= kCallWords && (!places || pool->d_places);
+    L.one_pass = need_reduce && !page_sums && one_pass_pays(L, staged || in_call);
+    if (in_call && (!need_reduce || L.one_pass)) {
+        if (fill_call(pool, pages, n_placed, order, grad_tensors, n_g, p16_tensors, n_q, stream, &call) && (!L.one_pass || next_call(pool, stream, &call.t))) {
+            if (!grad_tensors) call.t.g_base = reinterpret_cast<uint64_t>(g16_override ? g16_override : static_cast<const uint16_t*>(pool->base[APM_G16]));
+            if (!p16_tensors) call.t.q_base = reinterpret_cast<uint64_t>(pool->base[APM_P16]);
+            L.call = &call;
+            staged = false;
+        }
+    }
     const int64_t* d_list = whole ? pool->d_order : pool->d_list;
     const int32_t* d_out = whole ? pool->d_order_out : pool->d_list_out;
     std::vector<uint64_t> words(staged ? (size_t)(n_list + n_g + n_q) : 0);
@@ -203,7 +253,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
         for (int64_t i = 0; i < n_g; ++i) words[(size_t)(n_list + i)] = reinterpret_cast<uint64_t>(grad_tensors[i].data);
         for (int64_t i = 0; i < n_q; ++i) words[(size_t)(n_list + n_g + i)] = reinterpret_cast<uint64_t>(p16_tensors[i].data);
     }
-    if (by_ring) {
+    if (by_ring && !L.call) {
         const size_t bytes = staged ? words.size() * sizeof(uint64_t) : (size_t)n_list * (sizeof(int64_t) + sizeof(int32_t));
         rc = pool->ring.acquire(bytes, &ring_slot);
         if (rc != APM_OK) return rc;
@@ -239,7 +289,6 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     L.state_first = L.grad_first = page_at(0);
     L.gather = grad_tensors != nullptr;
     L.scatter = p16_tensors != nullptr;
-    L.n_listed = n_pages;
     L.E = E;
     L.S = pool->S;
     L.grad_norm = grad_norm;
@@ -247,7 +296,6 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     L.recs = pool->d_recs;
     L.live = pool->d_live;
     L.sums_ready = need_reduce && page_sums;
-    L.one_pass = need_reduce && !page_sums && one_pass_pays(L, staged);
     L.wait_limit = pool->wait_limit;
     L.max_workgroups = pool->max_workgroups;
     if (need_reduce) {
@@ -258,7 +306,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     if (need_reduce && !L.one_pass) {
         ScopedTiming t(pool, APM_K_REDUCE, stream);
         APM_HIP(launch_grad_reduce(L, stream));
-    } else if (!staged) {
+    } else if (!staged && !L.call) {
         L.bare_run = run && !need_reduce;
         if (!L.bare_run) APM_HIP(launch_prepare(L, stream));
     }
@@ -646,5 +694,11 @@ extern "C" int apm_test_set_max_workgroups(apm_pool* pool, int64_t max_workgroup
 extern "C" int apm_test_set_wait_limit(apm_pool* pool, int32_t wait_limit) {
     if (!pool || wait_limit < 0) return fail(APM_EINVAL, "bad argument");
     pool->wait_limit = wait_limit;
+    return APM_OK;
+}
+
+extern "C" int apm_test_set_call_number(apm_pool* pool, uint32_t number) {
+    if (!pool) return fail(APM_EINVAL, "bad argument");
+    pool->call_number = number;
     return APM_OK;
 }

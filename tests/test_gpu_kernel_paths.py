@@ -852,3 +852,102 @@ def test_one_element_decides_whether_a_page_is_skipped(form, bits):
     want = [int(bits == 0x8000)] * len(at) + [1, 1, 1, int(bits == 0x8000)]
     assert skip.tolist() == want
     pool.destroy()
+
+
+def _pages_and_tensors(E, numels, seed, n_pools):
+    """Pools with the same masters, the tensors' lists, and a function that draws a gradient, into the tensors and the pages."""
+    n_t, off = len(numels), [0]
+    for m in numels:
+        off.append(off[-1] + (m + 7) // 8 * 8)
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    p0 = torch.randn(off[-1], device=DEV, generator=gen) * 0.02
+    lst = lambda t: apm.make_tensors(numels, apm.APM_F32 if t.dtype == torch.float32 else apm.APM_BF16,  # noqa: E731
+                                     [t.data_ptr() + t.element_size() * o for o in off[:-1]])
+    n = oracle.plan_pack(numels, E).n_pages
+    pools = [apm.apm_pool_create(apm.APM_DEV_GPU, E, n) for _ in range(n_pools)]
+    g = torch.zeros(off[-1], device=DEV, dtype=torch.bfloat16)
+    for pool in pools:
+        apm.apm_pack_tensors(pool, apm.APM_P32, lst(p0), n_t)
+
+    def draw():
+        g.copy_(torch.randn(off[-1], device=DEV, generator=gen) * 1e-2)
+        for pool in pools:
+            apm.apm_pack_tensors(pool, apm.APM_G16, lst(g), n_t)
+        torch.cuda.synchronize()
+
+    def state(pool):
+        out = [torch.zeros(off[-1], device=DEV, dtype=torch.float32 if st < 3 else torch.bfloat16) for st in (0, 1, 2, apm.APM_P16)]
+        for st, t in zip((0, 1, 2, apm.APM_P16), out):
+            apm.apm_unpack(pool, st, lst(t), n_t)
+        torch.cuda.synchronize()
+        return out
+    return pools, n, g, lst, draw, state
+
+
+@pytest.mark.parametrize("clip", [0.0, 0.05])
+@pytest.mark.parametrize("form", ["run", "reversed", "fused", "fused odd"])
+def test_captured_steps_replay_as_they_run(form, clip):
+    """A step that makes its own records hands results on under a number that a replay would repeat: captured, the words are
+    marked instead.  Replays with eager steps of the same pool between them, against eager steps."""
+    E, numels = 4104, [(3, 4104, 9000, 17, 2051)[(3 * k) % 5] for k in range(40)]
+    pools, n, g, lst, draw, state = _pages_and_tensors(E, numels, 3, 2)
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, clip, 0)
+    pages = {"reversed": list(range(n))[::-1], "fused odd": list(range(1, n, 2))}.get(form)
+    count = len(pages) if pages else n
+    norm = [torch.zeros(n, device=DEV) for _ in range(2)]
+
+    def step(k, stream=None):
+        out = norm[k] if clip else None
+        if form.startswith("fused"):
+            apm.apm_page_adamw_step_fused(pools[k], pages, count, 3, hyper, lst(g), None, len(numels), out, None, stream)
+        else:
+            apm.apm_page_adamw_step(pools[k], pages, count, 3, hyper, out, None, stream)
+    draw()
+    for k in range(2):
+        step(k)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step(1, torch.cuda.current_stream())
+    for r in range(4):
+        draw()
+        step(0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(*norm)
+        for a, b in zip(state(pools[0]), state(pools[1])):
+            assert torch.equal(a, b)
+        if r % 2:
+            draw()
+            for k in range(2):
+                step(k)
+    for pool in pools:
+        pool.destroy()
+
+
+@pytest.mark.parametrize("form", ["run", "listed", "tensors"])
+@pytest.mark.parametrize("E", [520, 16384, 40968])
+def test_norms_handed_on_in_parts_equal_the_marked_ones(E, form):
+    """A tile's four parts (512 elements in turn), ends of tensors and pages in each of them, two tenants in one part; against the
+    step whose wavefronts take whole tiles; across the call numbers' end."""
+    ends = [1, 7, 511, 513, 1024 + 9, 1536 - 1, 2048 + 1, 8 * 2048 - 3, 8 * 2048 + 515]
+    numels = [min(m, E - 1) for m in ends] + [E + m for m in ends] + [2 * E]
+    pools, n, g, lst, draw, state = _pages_and_tensors(E, numels, E, 2)
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.05, 0)
+    norm = [torch.zeros(n, device=DEV) for _ in range(2)]
+    pages = list(range(n))[::-1] if form == "listed" else None
+    for t in range(1, 6):
+        if t == 3:
+            assert apm.lib().apm_test_set_call_number(ctypes.c_void_p(pools[0].handle), ctypes.c_uint32(0xFFFFFFFE)) == 0
+        draw()
+        if form == "tensors":
+            apm.apm_page_adamw_step_fused(pools[0], None, n, t, hyper, lst(g), None, len(numels), norm[0], None)
+        else:
+            apm.apm_page_adamw_step(pools[0], pages, n, t, hyper, norm[0], None)
+        apm.apm_page_adamw_step_noalloc(pools[1], n, t, hyper, norm[1], None)
+        torch.cuda.synchronize()
+        assert torch.equal(norm[0].flip(0) if pages else norm[0], norm[1])
+        for a, b in zip(state(pools[0]), state(pools[1])):
+            assert torch.equal(a, b)
+    for pool in pools:
+        pool.destroy()
