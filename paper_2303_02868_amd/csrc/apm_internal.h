@@ -290,9 +290,9 @@ constexpr int kCallWords = 2 * kArgWords;
 // Up to how many elements: where a call is large, a longer way to a wavefront's first load costs as much as the stage kernel did (us a
 // call, with a stage / prepare kernel / without; no norms, from and to tensors, and a reversed list: 0.6 M 9.3 / 6.3, 8 M - and 41.7 / 38.5, 10 M 49.7 /
 // 47.9 and 52.0 / 50.7, 22 M 97.9 / 95.9 and 101.1 / 99.6, 49 M 212 / 211 and 213 / 211, 67 M 299 / 298 and 292 / 289, 124 M 528 / 531 and - ; with norms:
-// 0.6 M 13.3 / 9.4, 2.5 M 26.8 / 20.6, 4.9 M 32.3 / 28.0 and 31.4 / 27.5, 18 M 90.6 / 84.9 and 90.1 / 86.4, 25 M 122 / 120 and 132 / 132, 49 M 226 / 232 and
-// 222 / 223).
-constexpr int64_t kCallElems = (int64_t)64 << 20, kCallSumElems = (int64_t)24 << 20;
+// 0.6 M 13.3 / 9.4, 2.5 M 26.8 / 20.6, 4.9 M 32.3 / 28.0 and 31.4 / 27.5, 18 M 90.6 / 84.9 and 90.1 / 86.4, 25 M 122 / 120 and 132 / 132, 31 M 150 / 149 and
+// 147.5 / 145.2, 39 M 180 / 185 and 180 / 180, 49 M 226 / 232 and 222 / 223).
+constexpr int64_t kCallElems = (int64_t)64 << 20, kCallSumElems = (int64_t)32 << 20;
 struct CallWords {
     CallTables t;
     uint32_t word[kCallWords];

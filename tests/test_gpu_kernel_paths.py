@@ -951,3 +951,31 @@ def test_norms_handed_on_in_parts_equal_the_marked_ones(E, form):
             assert torch.equal(a, b)
     for pool in pools:
         pool.destroy()
+
+
+@pytest.mark.parametrize("clip,skip", [(0.0, 0), (0.05, 0), (0.05, 1), (0.0, 1)])
+@pytest.mark.parametrize("n_small", [20, 5000])
+def test_noalloc_step_by_launch_order_equals_the_step(n_small, clip, skip):
+    """Full and nearly empty pages: with 20 small tensors the no-alloc step goes through the layout's launch order, with 5000 its records
+    would not fit the scratch; per-page outputs in the caller's order either way."""
+    E = 1 << 19
+    numels = [E + 11, 300, 4 * E + 9] + [(7, 900, 20000)[k % 3] for k in range(n_small)] + [3 * E]
+    pools, n, g, lst, draw, state = _pages_and_tensors(E, numels, 5, 2) if n_small < 1000 else _pages_and_tensors(16384, numels, 5, 2)
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, clip, skip)
+    norm = [torch.full((n,), -1.0, device=DEV) for _ in range(2)]
+    mask = [torch.full((n,), 9, dtype=torch.uint8, device=DEV) for _ in range(2)]
+    for t in (1, 2):
+        draw()
+        if skip:
+            for pool in pools:
+                page = torch.as_tensor(_Region(pool, apm.APM_G16, n * pool.desc.page_elems), device=DEV).view(n, -1)
+                page[::3] = 0
+        out = [x if clip or skip else None for x in norm]
+        apm.apm_page_adamw_step(pools[0], None, n, t, hyper, out[0], mask[0] if skip else None)
+        apm.apm_page_adamw_step_noalloc(pools[1], n, t, hyper, out[1], mask[1] if skip else None)
+        torch.cuda.synchronize()
+        assert torch.equal(*norm) and torch.equal(*mask)
+        for a, b in zip(state(pools[0]), state(pools[1])):
+            assert torch.equal(a, b)
+    for pool in pools:
+        pool.destroy()
