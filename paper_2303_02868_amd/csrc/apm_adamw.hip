@@ -1507,11 +1507,17 @@ struct TakeArgsInline {
 // sums are worked out, fit a CU).  Without sums a workgroup is one wavefront: four of them end when the last one does.
 // us an iteration with four-wavefront workgroups / of one / of one with LDS of 5120 / 7680 / 10240: 124 M, one hand-over and three
 // additions 1026 / 1021 / 974 / 966 / 970; 303 M 1535 / 1515 / 1488 / 1495 / 1520; 355 M with sums and LDS of 0 / 14336 / 27136 / 40960: 1798 /
-// 1776 / 1772 / 1800.  From how many elements on: without / with LDS, three additions 6.6 M 77.3 / 76.9, 9.8 M 97.8 / 93.1, 22 M 192 / 177, one with
-// sums 9.8 M 69.2 / 69.8, 13 M 92.5 / 89.8 (4.8 M by itself 10.2 / 11.0); a hand-over alone 6.6 M 39.3 / 39.6, 22 M 116.4 / 116.8, 31 M 160.9 / 159.9, with
-// sums 13 M 72.4 / 74.6, 31 M 165.0 / 165.6.
-constexpr unsigned kTakeLds = 7680, kTakeSumsLds = 27136;
-constexpr int64_t kFewTaken = kFewElems, kFewAdded = (int64_t)8 << 20;
+// 1776 / 1772 / 1800.  From how many elements on, without / with LDS: three additions 6.6 M 77.3 / 76.9, 9.8 M 97.8 / 93.1, 22 M 192 / 177 (4.8 M by
+// itself 10.2 / 11.0), with sums (0 / 14336 / 27136) 13 M 144 / 138 / 146, in 64 K pages 15 M 143 / 141 / 148, 93 M 813 / 783 / 794; a hand-over alone 6.6 M
+// 39.3 / 39.6, 22 M 116.4 / 116.8, 31 M 160.9 / 159.9, with sums 30 M 155 / 159 / 156, 93 M 477 / 489 / 491 and 474 / 471 / 472, 231 M 1211 / 1194 / 1177.
+struct TakeCap {
+    int64_t few;   // elements up to which no LDS is requested
+    unsigned lds;
+};
+constexpr TakeCap take_cap(bool accumulate, bool sums) {
+    const int64_t m = (int64_t)1 << 20;
+    return accumulate ? TakeCap{8 * m, sums ? 14336u : 7680u} : sums ? TakeCap{128 * m, 27136u} : TakeCap{24 * m, 7680u};
+}
 template <bool SUMS> constexpr int kTakeThreads = SUMS ? kThreads : kWave;
 
 template <bool ACCUM, bool SUMS, class Args>
@@ -1592,7 +1598,8 @@ hipError_t launch_grad_take(const GradTake& t, hipStream_t s) {
     const int threads = t.sums ? kTakeThreads<true> : kTakeThreads<false>, item = t.sums ? kReduceTile : threads * 8;
     int64_t elems = 0;  // at most
     for (int k = 0; k < t.n_cls; ++k) elems += t.cls[k].sum_used > 0 ? t.cls[k].sum_used : t.cls[k].count * t.cls[k].max_used;
-    const unsigned lds = elems <= (t.accumulate ? kFewAdded : kFewTaken) ? 0 : t.sums ? kTakeSumsLds : kTakeLds;
+    const TakeCap cap = take_cap(t.accumulate, t.sums != nullptr);
+    const unsigned lds = elems <= cap.few ? 0 : cap.lds;
     // positions of the given classes in one grid
     auto go = [&](const ExtentClass* cls, int n_cls) -> hipError_t {
         while (n_cls > 0 && cls[n_cls - 1].max_used <= 0 && !t.sums) --n_cls;  // nothing to take
