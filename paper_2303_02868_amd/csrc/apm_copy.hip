@@ -31,8 +31,8 @@ __device__ __forceinline__ void copy_vectors(const char* src, char* dst, int nve
 typedef u32x4 __attribute__((aligned(1))) u32x4_any;
 __device__ __forceinline__ void copy_vectors_unaligned(const char* src, char* dst, int nvec) {
     if ((int)threadIdx.x >= nvec) return;
-    const u32x4 x = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(src + (int)threadIdx.x * 16));
-    __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(dst) + (int)threadIdx.x);
+    const u32x4 x = *reinterpret_cast<const u32x4_any*>(src + (int)threadIdx.x * 16);
+    __builtin_amdgcn_raw_buffer_store_b128(x, make_rsrc(dst, nvec * 16), (int)threadIdx.x * 16, 0, kNT | kSC1);
 }
 
 // The same from a source `off` bytes (1 .. 15) beyond the aligned address `base`; the vectors base[0 .. nvec] are
@@ -78,8 +78,10 @@ __device__ __forceinline__ void copy_vectors_shifted(const char* base, int off, 
 // workgroup), and the vectors in between take whatever source alignment that leaves:
 //   into tensors  the stores start on a cache line, vectors are shifted between lanes, written through besides:
 //                 840 M bf16 elements, odd widths, 574 -> 544 us, 122 M fp32 162 -> 157;
-//   into pages    that is slower (561 -> 601 us, 159 -> 168): 128-bit loads at the address itself, plain
-//                 non-temporal stores.
+//   into pages    that is slower (561 -> 601 us, 159 -> 168): 128-bit loads at the address itself, with the default policy, as a
+//                 wavefront's first and last line are its neighbours' too, and stores written through (non-temporal loads and plain
+//                 non-temporal stores / like this, bf16: 17 M elements 14.9 / 14.2 us, 34 M 26.2 / 24.0, 47 M 37.4 / 35.9, 122 M 81.5 / 81.1, 869 M
+//                 548 / 541).
 //
 // A call brings nothing but the tensors' addresses, and these travel in the kernel arguments
 // (SegArgsInline): descriptors staged through a pinned ring cost the GPU an upload and two event packets,
