@@ -281,9 +281,11 @@ struct ReduceArgs {
 // Without SUMS only whether any element is not zero is wanted: a slice whose first eighth says so is not read any further.
 // (Whole calls, us, with sums / without: 1.08 G elements, an eighth of them live 946 / 896; 541 M, all live 3008 / 2860; 27 M, half live 85.3 /
 // 78.2; 52 M, a tenth live 56.7 / 54.)
-template <bool GATHER, bool SUMS>
+// Call: CallWords if the records are made from those (`recs` is not used then).
+struct CallNone {};
+template <bool GATHER, bool SUMS, class Call>
 __global__ __launch_bounds__(kThreads) void apm_grad_reduce_kernel(const PageRec* recs, uint32_t large_at, uint32_t per, uint32_t mul,
-                                                                   uint32_t shift, ReduceArgs a) {
+                                                                   uint32_t shift, ReduceArgs a, Call call) {
     int item;
     uint32_t tile;
     grid_item(large_at, GridDiv{per, mul, shift}, a.small, blockIdx.x, &item, &tile);
@@ -291,7 +293,14 @@ __global__ __launch_bounds__(kThreads) void apm_grad_reduce_kernel(const PageRec
     PageRec rec{};
     int64_t page = 0;
     int used;
-    if (GATHER) {
+    if constexpr (!std::is_same<Call, CallNone>::value) {
+        uint32_t place = (uint32_t)i;
+        if (call.t.listed) place = call_word(&call, 2 * place);
+        const i32x16 at = load_16(call.t.places + place);
+        rec = call_rec<GATHER, false>(call.t, __builtin_bit_cast(PagePlace, at), &call);
+        used = rec.used;
+        page = __builtin_bit_cast(PagePlace, at).page;
+    } else if (GATHER) {
         rec = load_rec(recs + item);
         used = rec.used;
     } else {
@@ -408,6 +417,7 @@ struct FinalizeArgs {
     uint8_t* skip_mask;  // nullable
     const int32_t* out_index;  // nullable: list position -> index into grad_norm / skip_mask
     bool sums_wanted;  // else `partials` holds none
+    bool gather, scatter;
 };
 
 // The record of a page that is read from / written to the page classes.
@@ -446,10 +456,12 @@ constexpr uint32_t kNoScale = ~(uint32_t)0;
 // class: each atomic takes 10 ns of the one counter's time (131 072 pages of 64 elements, one atomic a page
 // 1780 us a call, 64 pages 330; 32 768 of 512 elements 522 and 159).  Small workgroups for few pages, where
 // the launch's own latency counts.
-template <int WAVES, int R>
-__global__ __launch_bounds__(WAVES * kWave) void apm_grad_finalize_kernel(FinalizeArgs a) {
+// Call: CallWords if no stage kernel has written the records (a.gather, a.scatter: what of them is the caller's tensors).
+template <int WAVES, int R, class Call>
+__global__ __launch_bounds__(WAVES * kWave) void apm_grad_finalize_kernel(FinalizeArgs a, Call call) {
     static_assert(WAVES * R <= kWave, "one wavefront notes a workgroup's pages");
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    constexpr bool kCall = std::is_same<Call, CallWords>::value;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int64_t first = (int64_t)blockIdx.x * (WAVES * R);
     __shared__ int32_t s_cls[WAVES * R];  // extent class of a page to note, or -1
 #pragma unroll 1
@@ -458,8 +470,23 @@ __global__ __launch_bounds__(WAVES * kWave) void apm_grad_finalize_kernel(Finali
         const int64_t i = first + slot;
         int c = -1;
         if (i < a.n_listed) {
-            const int64_t page = a.grad_pages ? a.grad_pages[i] : a.grad_first + i;
-            const int used = a.used[page];
+            PagePlace place{};
+            int64_t page, o = i;
+            int used;
+            if constexpr (kCall) {
+                uint32_t k = (uint32_t)i;
+                if (call.t.listed) {
+                    k = call_word(&call, 2 * (uint32_t)i);
+                    o = (int64_t)call_word(&call, 2 * (uint32_t)i + 1);
+                }
+                place = __builtin_bit_cast(PagePlace, load_16(call.t.places + k));
+                page = place.page;
+                if (!call.t.listed) o = page;
+                used = place.used;
+            } else {
+                page = a.grad_pages ? a.grad_pages[i] : a.grad_first + i;
+                used = a.used[page];
+            }
             const int n_slices = max(1, (used + kReduceTile - 1) / kReduceTile);
             double s = 0.0;
             uint32_t nz = 0;
@@ -475,10 +502,18 @@ __global__ __launch_bounds__(WAVES * kWave) void apm_grad_finalize_kernel(Finali
                 const double norm = sqrt(s);
                 const float scale = clip_scale(norm, a.max_norm);
                 const float sc = skip ? -1.0f : scale;
-                if (a.run) reinterpret_cast<PageRun*>(a.recs)[i] = PageRun{used, sc};
+                if constexpr (kCall) {
+                    PageRec rec;
+                    if (a.gather && a.scatter) rec = call_rec<true, true>(call.t, place, &call);
+                    else if (a.gather) rec = call_rec<true, false>(call.t, place, &call);
+                    else if (a.scatter) rec = call_rec<false, true>(call.t, place, &call);
+                    else rec = call_rec<false, false>(call.t, place, &call);
+                    rec.scale = sc;
+                    a.recs[i] = rec;
+                } else if (a.run) reinterpret_cast<PageRun*>(a.recs)[i] = PageRun{used, sc};
                 else if (a.staged) a.recs[i].scale = sc;
                 else a.recs[i] = class_rec(used, sc, page, a.state_pages ? a.state_pages[i] : a.state_first + i, a.E, a.g16, a.p16);
-                const int64_t o = a.out_index ? (int64_t)a.out_index[i] : i;
+                if (!kCall && a.out_index) o = (int64_t)a.out_index[i];
                 if (a.grad_norm) a.grad_norm[o] = skip ? 0.0f : (float)norm;
                 if (a.skip_mask) a.skip_mask[o] = skip ? 1 : 0;
             }
@@ -1706,37 +1741,48 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
     ReduceArgs a{L.g16, L.used, L.grad_pages, L.grad_first, 0, L.E, L.partials, L.nzflags, L.S, live, {}};
     if (L.sums_ready && live) hipLaunchKernelGGL(apm_live_clear_kernel, dim3(1), dim3(kWave), 0, s, live);
     const bool sums = L.max_norm > 0.0 || L.grad_norm;
-    auto kernel = L.gather ? (sums ? apm_grad_reduce_kernel<true, true> : apm_grad_reduce_kernel<true, false>)
-                           : (sums ? apm_grad_reduce_kernel<false, true> : apm_grad_reduce_kernel<false, false>);
     const ExtentClass all{0, L.n_listed, L.E, L.n_listed * L.E};
     if (!L.sums_ready) e = (hipError_t)for_each_grid(L.n_cls > 0 ? L.cls : &all, L.n_cls > 0 ? L.n_cls : 1, kThreads, L.max_workgroups,
         [](const ExtentClass& c) { return c.max_used > 0 ? (c.max_used + kReduceTile - 1) / kReduceTile : 1; },
         [&](const GridMap& m, int64_t workgroups, int64_t first) -> int {
             a.list_offset = first;
             std::memcpy(a.small, m.small, sizeof a.small);
-            hipLaunchKernelGGL(kernel, dim3((unsigned)workgroups), dim3(kThreads), 0, s, L.recs + first, m.large_at, m.large.per, m.large.mul, m.large.shift, a);
+            auto go = [&](const auto& call) {
+                typedef typename std::decay<decltype(call)>::type Call;
+                auto kernel = L.gather ? (sums ? apm_grad_reduce_kernel<true, true, Call> : apm_grad_reduce_kernel<true, false, Call>)
+                                       : (sums ? apm_grad_reduce_kernel<false, true, Call> : apm_grad_reduce_kernel<false, false, Call>);
+                hipLaunchKernelGGL(kernel, dim3((unsigned)workgroups), dim3(kThreads), 0, s, L.recs + first, m.large_at, m.large.per, m.large.mul, m.large.shift,
+                                   a, call);
+            };
+            if (L.call) go(*L.call);
+            else go(CallNone{});
             return (int)hipGetLastError();
         });
     if (e != hipSuccess) return e;
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
                    L.partials, L.nzflags, L.S, L.skip_mode, L.max_norm, L.recs, L.g16, L.p16, L.E, live, {}, 0, L.sums_ready, L.is_run(),
-                   L.gather || L.scatter, nullptr, L.grad_norm, L.skip_mask, L.out_index, sums};
+                   L.gather || L.scatter, nullptr, L.grad_norm, L.skip_mask, L.out_index, sums, L.gather, L.scatter};
     ExtentClass live_cls[kMaxExtentClasses];
     f.n_cls = live_classes(L, live_cls);
     for (int c = 0; c < f.n_cls; ++c) f.cls_begin[c] = live_cls[c].begin;
-    auto go = [&](auto kernel, int waves, int pages) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)((L.n_listed + pages - 1) / pages)), dim3((unsigned)(waves * kWave)), 0, s, f);
+    auto go = [&](const auto& call) {
+        typedef typename std::decay<decltype(call)>::type Call;
+        auto start = [&](auto kernel, int waves, int pages) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((L.n_listed + pages - 1) / pages)), dim3((unsigned)(waves * kWave)), 0, s, f, call);
+        };
+        if (L.n_listed <= 1024) start(apm_grad_finalize_kernel<4, 1, Call>, 4, 4);
+        else if (L.n_listed <= 4096) start(apm_grad_finalize_kernel<16, 1, Call>, 16, 16);
+        else start(apm_grad_finalize_kernel<16, 4, Call>, 16, 64);
     };
-    if (L.n_listed <= 1024) go(apm_grad_finalize_kernel<4, 1>, 4, 4);
-    else if (L.n_listed <= 4096) go(apm_grad_finalize_kernel<16, 1>, 16, 16);
-    else go(apm_grad_finalize_kernel<16, 4>, 16, 64);
+    if (L.call) go(*L.call);
+    else go(CallNone{});
     return hipGetLastError();
 }
 
 hipError_t launch_prepare(const AdamwLaunch& L, hipStream_t s) {
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
                    nullptr, nullptr, L.S, L.skip_mode, 0.0, L.recs, L.g16, L.p16, L.E, nullptr, {}, 0, false, L.is_run(),
-                   false, L.one_pass ? reinterpret_cast<uint64_t*>(L.partials) : nullptr, nullptr, nullptr, nullptr, false};
+                   false, L.one_pass ? reinterpret_cast<uint64_t*>(L.partials) : nullptr, nullptr, nullptr, nullptr, false, false, false};
     hipLaunchKernelGGL(apm_page_recs_kernel, dim3(record_grid(L)),
                        dim3(kThreads), 0, s, f);
     return hipGetLastError();
@@ -1907,6 +1953,7 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         int64_t elems = 0;
         for (int c = 0; c < n_cls; ++c) elems += cls[c].sum_used;
         const unsigned lds = update_lds(L.gather || L.scatter, elems, APM_UPDATE_LDS);
+        const bool by_call = L.call && !L.partials;  // after a reduce pass the records are there
         return (hipError_t)for_each_grid(cls, n_cls, kUpdThreads, L.max_workgroups, slices_of<U>, [&](const GridMap& m, int64_t workgroups, int64_t first) -> int {
             SmallClasses classes;
             std::memcpy(classes.small, m.small, sizeof classes.small);
@@ -1914,10 +1961,10 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
                                                    L.p32, L.m32, L.v32, m.large_at, m.large.per, m.large.mul, m.large.shift, a, classes)
 #define APM_LAUNCH_CALL(G, Q) hipLaunchKernelGGL((apm_adamw_call_kernel<U, G, Q>), dim3((unsigned)workgroups), dim3(kUpdThreads), lds, s, L.call->t.places, \
                                                  L.p32, L.m32, L.v32, m.large_at, m.large.per, m.large.mul, m.large.shift, (uint32_t)first, L.call->t.listed, a, classes, *L.call)
-            if (L.call && L.gather && L.scatter) APM_LAUNCH_CALL(true, true);
-            else if (L.call && L.gather) APM_LAUNCH_CALL(true, false);
-            else if (L.call && L.scatter) APM_LAUNCH_CALL(false, true);
-            else if (L.call) APM_LAUNCH_CALL(false, false);
+            if (by_call && L.gather && L.scatter) APM_LAUNCH_CALL(true, true);
+            else if (by_call && L.gather) APM_LAUNCH_CALL(true, false);
+            else if (by_call && L.scatter) APM_LAUNCH_CALL(false, true);
+            else if (by_call) APM_LAUNCH_CALL(false, false);
             else if (L.gather && L.scatter) APM_LAUNCH_UPDATE(true, true, kStoreHbm);
             else if (L.gather) APM_LAUNCH_UPDATE(true, false, kStoreHbm);
             else if (L.scatter) APM_LAUNCH_UPDATE(false, true, kStoreHbm);

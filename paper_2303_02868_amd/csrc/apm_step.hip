@@ -226,10 +226,11 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     const int64_t n_placed = call.t.listed ? n_pages : 0;
     int64_t elems = 0;
     for (int c = 0; c < L.n_cls; ++c) elems += L.cls[c].sum_used;
-    const bool in_call = (need_reduce ? norms && elems <= kCallSumElems : places && elems <= kCallElems) &&  // a bare run has nothing to save
-                         2 * n_placed + n_g + n_q <= kCallWords && (!places || pool->d_places);
-    L.one_pass = need_reduce && !page_sums && one_pass_pays(L, staged || in_call);
-    if (in_call && (!need_reduce || L.one_pass)) {
+    const bool words_fit = 2 * n_placed + n_g + n_q <= kCallWords && (!places || pool->d_places);
+    const bool one_launch = words_fit && (need_reduce ? norms && elems <= kCallSumElems : places && elems <= kCallElems);  // a bare run has nothing to save
+    L.one_pass = need_reduce && !page_sums && one_pass_pays(L, staged || one_launch);
+    // As passes the finalize pass writes the records.
+    if (need_reduce && !L.one_pass ? words_fit && staged && elems <= kCallPassElems : one_launch) {
         if (fill_call(pool, pages, n_placed, order, grad_tensors, n_g, p16_tensors, n_q, stream, &call) && (!L.one_pass || next_call(pool, stream, &call.t))) {
             if (!grad_tensors) call.t.g_base = reinterpret_cast<uint64_t>(g16_override ? g16_override : static_cast<const uint16_t*>(pool->base[APM_G16]));
             if (!p16_tensors) call.t.q_base = reinterpret_cast<uint64_t>(pool->base[APM_P16]);
