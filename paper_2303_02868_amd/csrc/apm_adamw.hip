@@ -582,6 +582,7 @@ struct StageArgs {
     const uint64_t* words;      // list, g, q words, unless they follow inline
     int64_t list_begin;         // the list words are those of positions [list_begin, + list_n)
     int32_t list_n;
+    int32_t n_runs;             // StageArgsRuns: runs that the positions come in
     int32_t t_begin, t_n;       // the g / q words are those of tensors [t_begin, + t_n)
     int32_t has_g, has_q;
     uint64_t g_base, q_base;    // StageArgsNarrow
@@ -597,19 +598,26 @@ struct StageArgsNarrow {
     uint32_t word[2 * kArgWords];
 };
 
+// The same with the list as runs (StageRun) in the first words.
+struct StageArgsRuns {
+    StageArgs a;
+    uint32_t word[2 * kArgWords];
+};
+
 template <class Args>
 __global__ __launch_bounds__(kThreads) void apm_stage_kernel(Args args) {
     const StageArgs* ap;
     if constexpr (sizeof(Args) > sizeof(StageArgs)) ap = &args.a;
     else ap = &args;
     const StageArgs& a = *ap;
-    constexpr bool kNarrow = std::is_same<Args, StageArgsNarrow>::value;
+    constexpr bool kRuns = std::is_same<Args, StageArgsRuns>::value, kNarrow = kRuns || std::is_same<Args, StageArgsNarrow>::value;
+    constexpr int kRunWords = sizeof(StageRun) / sizeof(uint32_t);
     constexpr bool kInline = sizeof(Args) > sizeof(StageArgs);
     auto word = [&](int64_t k) -> uint64_t {
         if constexpr (kInline) return args.word[k];
         else return a.words[k];
     };
-    const int64_t list_words = (kNarrow ? 2 : 1) * (int64_t)a.list_n;
+    const int64_t list_words = kRuns ? (int64_t)kRunWords * a.n_runs : (kNarrow ? 2 : 1) * (int64_t)a.list_n;
     int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x, page = 0;
     const bool mine = i < (a.list_n > 0 ? a.list_n : a.n_listed), tenants = (a.has_g || a.has_q) && a.t_n > 0;
     // Argument words read lane by lane come from as far as anything else: all addresses are fetched beside the page's
@@ -618,7 +626,26 @@ __global__ __launch_bounds__(kThreads) void apm_stage_kernel(Args args) {
     __shared__ Word s_address[kInline ? (kNarrow ? 2 : 1) * kArgWords : 1];
     if (kInline && tenants && (int64_t)blockIdx.x * kThreads < a.n_listed)
         for (int k = (int)threadIdx.x; k < (a.has_g + a.has_q) * a.t_n; k += kThreads) s_address[k] = (Word)word(list_words + k);
-    if (mine) {
+    if constexpr (kRuns) {
+        __shared__ StageRun s_run[2 * kArgWords / kRunWords];
+        for (int k = (int)threadIdx.x; k < (int)list_words; k += kThreads) reinterpret_cast<uint32_t*>(s_run)[k] = args.word[k];
+        __syncthreads();
+        if (mine && a.list_n > 0) {
+            i += a.list_begin;
+            int low = 0, high = a.n_runs;  // the last run that begins at or before i
+            while (high - low > 1) {
+                const int mid = (low + high) / 2;
+                if ((int64_t)s_run[mid].at <= i) low = mid;
+                else high = mid;
+            }
+            const StageRun r = s_run[low];
+            const int64_t k = i - (int64_t)r.at;
+            page = (int64_t)(r.page & 0x7FFFFFFFu) + (r.page >> 31 ? -k : k);
+            a.list[i] = page;
+            a.out[i] = (int32_t)(r.out + (uint32_t)k);
+        }
+    }
+    if (mine && !(kRuns && a.list_n > 0)) {
         if (a.list_n > 0) {
             const uint64_t w = word(i), out = kNarrow ? word(a.list_n + i) : w >> 32;
             i += a.list_begin;
@@ -1788,6 +1815,12 @@ hipError_t launch_prepare(const AdamwLaunch& L, hipStream_t s) {
     return hipGetLastError();
 }
 
+int64_t stage_launches_runs(int64_t n_runs, int64_t lists, int64_t n_tensors) {
+    if (run_words(n_runs) + lists * n_tensors <= 2 * kArgWords) return 1;
+    const int64_t per = lists ? 2 * kArgWords / lists : 1;
+    return (n_runs + kStageRuns - 1) / kStageRuns + (lists ? (n_tensors + per - 1) / per : 0);
+}
+
 int64_t stage_launches(int64_t n_list, int64_t lists, int64_t n_tensors, bool narrow) {
     const int64_t room = narrow ? 2 * kArgWords : kArgWords;
     if ((narrow ? 2 : 1) * n_list + lists * n_tensors <= room) return 1;
@@ -1800,9 +1833,10 @@ hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s)
     const int64_t n_list = c.list ? L.n_listed : 0, n_t = has_g || has_q ? c.n_tensors : 0;
     StageArgsInline in;
     StageArgsNarrow half;
+    StageArgsRuns runs;
     StageArgs a{L.used, c.list ? c.d_list : L.grad_pages, L.grad_first, L.n_listed, c.tenants, L.recs, L.g16, L.p16, L.E,
                   c.d_list, c.d_out, L.one_pass ? reinterpret_cast<uint64_t*>(L.partials) : nullptr,
-                  L.one_pass ? L.n_listed * L.S : 0, c.d_words, 0, 0, 0, 0, has_g, has_q, c.g_base, c.q_base};
+                  L.one_pass ? L.n_listed * L.S : 0, c.d_words, 0, 0, 0, 0, 0, has_g, has_q, c.g_base, c.q_base};
     auto go = [&](int64_t list_begin, int64_t list_n, int64_t t_begin, int64_t t_n) -> hipError_t {
         a.list_begin = list_begin;
         a.list_n = (int32_t)list_n;
@@ -1835,9 +1869,32 @@ hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s)
         a.sums = nullptr;  // marked by the first launch
         return hipGetLastError();
     };
-    if (c.d_words || stage_launches(n_list, has_g + has_q, n_t, c.narrow) == 1) return go(0, n_list, 0, n_t);
+    // runs [r, r + n) and, with the last of them, all addresses
+    auto go_runs = [&](int64_t r, int64_t n, int64_t t_n) -> hipError_t {
+        const int64_t begin = (int64_t)c.runs[r].at, end = r + n < c.n_runs ? (int64_t)c.runs[r + n].at : n_list;
+        uint32_t* w = runs.word;
+        std::memcpy(w, c.runs + r, (size_t)n * sizeof(StageRun));
+        w += n * (int64_t)(sizeof(StageRun) / sizeof(uint32_t));
+        for (int64_t k = 0; has_g && k < t_n; ++k) *w++ = (uint32_t)((c.g_ptrs[k] - c.g_base) >> 4);
+        for (int64_t k = 0; has_q && k < t_n; ++k) *w++ = (uint32_t)((c.q_ptrs[k] - c.q_base) >> 4);
+        runs.a = a;
+        runs.a.list_begin = begin;
+        runs.a.list_n = (int32_t)(end - begin);
+        runs.a.n_runs = (int32_t)n;
+        runs.a.t_n = (int32_t)t_n;
+        const unsigned pages_grid = (unsigned)((end - begin + kThreads - 1) / kThreads), sums_grid = a.sums ? record_grid(L) : 0u;
+        hipLaunchKernelGGL(apm_stage_kernel<StageArgsRuns>, dim3(pages_grid > sums_grid ? pages_grid : sums_grid), dim3(kThreads), 0, s, runs);
+        a.sums = nullptr;
+        return hipGetLastError();
+    };
+    if (c.runs && run_words(c.n_runs) + (has_g + has_q) * n_t <= 2 * kArgWords) return go_runs(0, c.n_runs, n_t);
+    if (c.d_words || (!c.runs && stage_launches(n_list, has_g + has_q, n_t, c.narrow) == 1)) return go(0, n_list, 0, n_t);
     // list words first: the launches with the addresses read the list that they wrote
-    for (int64_t k = 0; k < n_list; k += kArgWords) {
+    for (int64_t k = 0; c.runs && k < c.n_runs; k += kStageRuns) {
+        hipError_t e = go_runs(k, c.n_runs - k < kStageRuns ? c.n_runs - k : kStageRuns, 0);
+        if (e != hipSuccess) return e;
+    }
+    for (int64_t k = 0; !c.runs && k < n_list; k += kArgWords) {
         hipError_t e = go(k, n_list - k < kArgWords ? n_list - k : kArgWords, 0, 0);
         if (e != hipSuccess) return e;
     }

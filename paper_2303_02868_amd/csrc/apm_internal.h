@@ -382,7 +382,18 @@ struct StageCall {
     // base, as they do but for lists that several allocations far apart make up.
     bool narrow;
     uint64_t g_base, q_base;      // multiples of 16, as all addresses are
+    // The list as runs in place of a word per position, or nullptr; the addresses then as half words.
+    const struct StageRun* runs;
+    int64_t n_runs;
 };
+// List positions at, at + 1, ... up to the next run's: pages one after the other, downwards if the upper bit of `page` is set, output indices
+// out, out + 1, ...
+struct StageRun {
+    uint32_t at, page, out;
+};
+constexpr int64_t run_words(int64_t n_runs) { return n_runs * (int64_t)(sizeof(StageRun) / sizeof(uint32_t)); }
+constexpr int64_t kStageRuns = 2 * kArgWords * sizeof(uint32_t) / sizeof(StageRun);  // that a launch carries
+int64_t stage_launches_runs(int64_t n_runs, int64_t lists, int64_t n_tensors);  // as stage_launches
 // Launches it takes to carry a call's words in kernel arguments (StageCall::d_words == nullptr): n_list list
 // words and `lists` (0..2) lists of n_tensors addresses.  narrow: as 32-bit words, two per list word.
 int64_t stage_launches(int64_t n_list, int64_t lists, int64_t n_tensors, bool narrow);

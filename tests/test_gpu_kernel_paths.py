@@ -979,3 +979,49 @@ def test_noalloc_step_by_launch_order_equals_the_step(n_small, clip, skip):
             assert torch.equal(a, b)
     for pool in pools:
         pool.destroy()
+
+
+@pytest.mark.parametrize("clip", [0.0, 0.05])
+@pytest.mark.parametrize("form", ["pages", "tensors"])
+@pytest.mark.parametrize("listed", ["down", "up and down", "pieces", "many pieces", "alternating"])
+def test_long_lists_as_runs_equal_the_whole_step(listed, form, clip):
+    """Lists beyond what a launch carries word by word: runs upwards and downwards, runs of one and two pages, more runs than a launch
+    carries, hardly any runs; outputs by list position."""
+    E, numels = 520, [(3, 1040, 519, 520 * 9 + 7)[k % 4] for k in range(600)]
+    pools, n, g, lst, draw, state = _pages_and_tensors(E, numels, 9, 2)
+    pages = {"down": list(range(n))[::-1], "up and down": list(range(n // 2, n)) + list(range(n // 2))[::-1],
+             "pieces": [p for k in range(0, n - 40, 40) for p in ([k + 30, k + 31] + list(range(k, k + 20))[::-1] + [k + 39])],
+             "many pieces": [p for k in range(0, n - 5, 5) for p in (k + 3, k + 2, k)],
+             "alternating": [p ^ 1 for p in range(n // 2 * 2)]}[listed]
+    assert len(pages) > 440
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, clip, 0)
+    draw()
+    before = state(pools[0])
+    norm = [torch.zeros(len(pages), device=DEV), torch.zeros(n, device=DEV)]
+    q = [torch.zeros_like(g) for _ in range(2)]
+    for pool, lst_, m, out, qq in zip(pools, (pages, None), (len(pages), n), norm, q):
+        out = out if clip else None
+        if form == "tensors":
+            apm.apm_page_adamw_step_fused(pool, lst_, m, 3, hyper, lst(g), lst(qq), len(numels), out, None)
+        else:
+            apm.apm_page_adamw_step(pool, lst_, m, 3, hyper, out, None)
+    torch.cuda.synchronize()
+    at = torch.tensor(pages, device=DEV)
+    if clip:
+        assert torch.equal(norm[0], norm[1][at])
+    touched = torch.zeros(n, E, device=DEV)
+    touched[at] = 1
+    mask = apm.apm_pool_create(apm.APM_DEV_GPU, E, n, state_mask=1)
+    apm.apm_pool_set_layout(mask, lst(before[0]), len(numels))
+    torch.as_tensor(_Region(mask, apm.APM_P32, 2 * n * E), device=DEV).view(torch.float32).copy_(touched.flatten())
+    on = torch.zeros_like(before[0])
+    apm.apm_unpack(mask, apm.APM_P32, lst(on), len(numels))
+    torch.cuda.synchronize()
+    want = [torch.where(on > 0, new, old) for new, old in zip(state(pools[1]), before)]
+    got = state(pools[0])
+    if form == "tensors":
+        got, want = got[:3] + [q[0]], want[:3] + [torch.where(on > 0, q[1], torch.zeros_like(q[1]))]
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+    for pool in pools + [mask]:
+        pool.destroy()
