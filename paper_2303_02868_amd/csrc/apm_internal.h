@@ -518,6 +518,7 @@ struct apm_pool {
     int run_n_cls = 0;
     bool order_run = false;
     int64_t layout_epoch = 0;  // counts the layouts installed
+    char* d_scratch = nullptr;      // the four below, allocated on first use
     double* d_partials = nullptr;   // reduce scratch, n_pages * S
     uint32_t* d_nzflags = nullptr;
     apm::PageRec* d_recs = nullptr;   // n_pages entries

@@ -69,11 +69,18 @@ int ensure_scratch(apm_pool* pool, bool list) {
         *p = nullptr;
         return fail(APM_ENOMEM, "allocating %zu bytes of per-page scratch failed: %s", bytes, hipGetErrorString(e));
     };
-    int rc = get((void**)&pool->d_partials, n * sizeof(double));
-    if (rc == APM_OK) rc = get((void**)&pool->d_nzflags, n * sizeof(uint32_t));
+    // one allocation: a pool's first call waits for each
     const size_t n_pages = (size_t)pool->desc.n_pages;
-    if (rc == APM_OK) rc = get((void**)&pool->d_recs, n_pages * sizeof(PageRec));
-    if (rc == APM_OK) rc = get((void**)&pool->d_live, (size_t)kLiveInts(pool->desc.n_pages) * sizeof(int32_t));
+    const size_t len[4] = {n_pages * sizeof(PageRec), n * sizeof(double), n * sizeof(uint32_t), (size_t)kLiveInts(pool->desc.n_pages) * sizeof(int32_t)};
+    size_t at[5] = {};
+    for (int k = 0; k < 4; ++k) at[k + 1] = at[k] + (len[k] + 255) / 256 * 256;
+    int rc = get((void**)&pool->d_scratch, at[4]);
+    if (rc == APM_OK) {
+        pool->d_recs = reinterpret_cast<PageRec*>(pool->d_scratch + at[0]);
+        pool->d_partials = reinterpret_cast<double*>(pool->d_scratch + at[1]);
+        pool->d_nzflags = reinterpret_cast<uint32_t*>(pool->d_scratch + at[2]);
+        pool->d_live = reinterpret_cast<int32_t*>(pool->d_scratch + at[3]);
+    }
     if (rc == APM_OK && list) rc = get((void**)&pool->d_list, n_pages * sizeof(int64_t));
     if (rc == APM_OK && list) rc = get((void**)&pool->d_list_out, n_pages * sizeof(int32_t));
     return rc;
@@ -144,11 +151,8 @@ void free_pool(apm_pool* pool) {
     }
     if (pool->d_used) (void)hipFree(pool->d_used);
     if (pool->d_tables) (void)hipFree(pool->d_tables);
-    if (pool->d_partials) (void)hipFree(pool->d_partials);
-    if (pool->d_nzflags) (void)hipFree(pool->d_nzflags);
-    if (pool->d_recs) (void)hipFree(pool->d_recs);
+    if (pool->d_scratch) (void)hipFree(pool->d_scratch);
     if (pool->d_tagged) (void)hipFree(pool->d_tagged);
-    if (pool->d_live) (void)hipFree(pool->d_live);
     if (pool->d_list) (void)hipFree(pool->d_list);
     if (pool->d_list_out) (void)hipFree(pool->d_list_out);
     pool->ring.destroy();
