@@ -583,6 +583,8 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
                  const apm_tensor* p16_tensors = nullptr, int64_t n_tensors = 0,
                  double* page_sums = nullptr, uint32_t* page_nzflags = nullptr);
 int ensure_scratch(apm_pool* pool, bool list = false);
+// Whether work enqueued on the stream now is captured, as far as that can be told.
+bool is_captured(hipStream_t s);
 // The number of the next call, on stream s, and where it hands results on; false if there is no memory for that.
 bool next_call(apm_pool* pool, hipStream_t s, CallTables* out);
 // Pages in use beyond which a call's words do not fit its arguments, or a launch more costs it little.

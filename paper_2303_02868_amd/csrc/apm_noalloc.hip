@@ -100,14 +100,7 @@ extern "C" int apm_page_adamw_step_noalloc(apm_pool* pool, int64_t n_pages, int6
         bool listed = pool->has_layout && n == pool->plan.pages.size() && !pool->order_run && (need_reduce || pool->d_places) &&
                       (L.skip_mode == APM_SKIP_NONE || pool->used_sum.back() <= kCallElems) &&
                       round256(n * sizeof(PageRec) + (size_t)kLiveInts(n_pages) * sizeof(int32_t)) + sums <= kScratchBytes;
-        if (listed) {
-            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-            if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
-                (void)hipGetLastError();
-                capture = hipStreamCaptureStatusActive;
-            }
-            listed = capture == hipStreamCaptureStatusNone;
-        }
+        listed = listed && !is_captured(s);
         const size_t recs = n * (listed ? sizeof(PageRec) : sizeof(PageRun));
         L.recs = reinterpret_cast<PageRec*>(base);  // a run: n PageRun entries
         L.live = reinterpret_cast<int32_t*>(base + recs);

@@ -117,16 +117,18 @@ static void runs_of(const int64_t* pages, const std::vector<int64_t>& order, std
     }
 }
 
-// The words of a call: the list (in launch order) and the addresses.  False if they do not go into half words, if a page is not the
-// layout's, or if the launch is captured: a replay would carry the same number, so there the words have to be marked.
-static bool fill_call(const apm_pool* pool, const int64_t* pages, int64_t n_placed, const std::vector<int64_t>& order, const apm_tensor* g,
-                      int64_t n_g, const apm_tensor* q, int64_t n_q, hipStream_t stream, CallWords* call) {
+bool is_captured(hipStream_t s) {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    if (capture != hipStreamCaptureStatusNone || !base_of(g, n_g, &call->t.g_base) || !base_of(q, n_q, &call->t.q_base)) return false;
+    if (hipStreamIsCapturing(s, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+// The words of a call: the list (in launch order) and the addresses.  False if they do not go into half words or a page is not the
+// layout's.
+static bool fill_call(const apm_pool* pool, const int64_t* pages, int64_t n_placed, const std::vector<int64_t>& order, const apm_tensor* g,
+                      int64_t n_g, const apm_tensor* q, int64_t n_q, CallWords* call) {
+    if (!base_of(g, n_g, &call->t.g_base) || !base_of(q, n_q, &call->t.q_base)) return false;
     uint32_t* w = call->word;
     for (int64_t k = 0; k < n_placed; ++k) {
         const int64_t at = order.empty() ? k : order[(size_t)k], page = pages ? pages[at] : at;
@@ -198,7 +200,10 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     // (With norms in one launch that makes its own records finer classes are worth more: 4.9 M elements in 256 K pages with clipping, us a call,
     // as a run 34.1, in classes 27.9; 24 M 114.3 and 107.2.)
     const bool norms = (L.max_norm > 0.0 || grad_norm) && L.skip_mode == APM_SKIP_NONE && !page_sums;
-    bool run = whole && (tensors || (norms && pool->d_places && pool->used_sum.back() <= kCallSumElems) ? pool->order_plain : pool->order_run);
+    // A captured launch makes no records of its own: a replay would hand results on under the same number, and may come after a layout that
+    // replaces the tables.
+    const bool captured = is_captured(stream);
+    bool run = whole && (tensors || (norms && !captured && pool->d_places && pool->used_sum.back() <= kCallSumElems) ? pool->order_plain : pool->order_run);
     if (whole) {
         const bool as_run = run && !tensors;
         L.n_cls = as_run ? pool->run_n_cls : pool->order_n_cls;
@@ -258,12 +263,12 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     const int64_t n_placed = call.t.listed ? n_pages : 0;
     int64_t elems = 0;
     for (int c = 0; c < L.n_cls; ++c) elems += L.cls[c].sum_used;
-    const bool words_fit = 2 * n_placed + n_g + n_q <= kCallWords && (!places || pool->d_places);
+    const bool words_fit = !captured && 2 * n_placed + n_g + n_q <= kCallWords && (!places || pool->d_places);
     const bool one_launch = words_fit && (need_reduce ? norms && elems <= kCallSumElems : places && elems <= kCallElems);  // a bare run has nothing to save
     L.one_pass = need_reduce && !page_sums && one_pass_pays(L, staged || one_launch);
     // As passes the finalize pass writes the records.
     if (need_reduce && !L.one_pass ? words_fit && staged && elems <= kCallPassElems : one_launch) {
-        if (fill_call(pool, pages, n_placed, order, grad_tensors, n_g, p16_tensors, n_q, stream, &call) && (!L.one_pass || next_call(pool, stream, &call.t))) {
+        if (fill_call(pool, pages, n_placed, order, grad_tensors, n_g, p16_tensors, n_q, &call) && (!L.one_pass || next_call(pool, stream, &call.t))) {
             if (!grad_tensors) call.t.g_base = reinterpret_cast<uint64_t>(g16_override ? g16_override : static_cast<const uint16_t*>(pool->base[APM_G16]));
             if (!p16_tensors) call.t.q_base = reinterpret_cast<uint64_t>(pool->base[APM_P16]);
             L.call = &call;
