@@ -1004,7 +1004,7 @@ struct LinkSlice {
     int used;
     float scale;
 };
-template <bool RUN>
+template <bool RUN, int U>
 struct LinkWalk {
     const PageRec* recs;
     int64_t count, base;
@@ -1019,7 +1019,7 @@ struct LinkWalk {
         if (at < count) r = RUN ? reinterpret_cast<const PageRun*>(recs)[at] : *reinterpret_cast<const PageRun*>(recs + at);
         return r;
     }
-    static __device__ __forceinline__ int slices(int used) { return (int)(((uint32_t)used + (kTile<kStrideU> - 1)) / kTile<kStrideU>); }
+    static __device__ __forceinline__ int slices(int used) { return (int)(((uint32_t)used + (kTile<U> - 1)) / kTile<U>); }
     __device__ __forceinline__ void enter(const PageRun& r) {
         used = r.scale < 0.0f ? 0 : (r.used + 7) & ~7;
         scale = r.scale;
@@ -1048,8 +1048,8 @@ struct LinkWalk {
         s.page = base + l;
         s.used = __builtin_amdgcn_readlane(used, l);
         s.scale = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(scale), l));
-        s.start = (t - (__builtin_amdgcn_readlane(upto, l) - slices(s.used))) * kTile<kStrideU>;
-        s.n = min(kTile<kStrideU>, s.used - s.start);
+        s.start = (t - (__builtin_amdgcn_readlane(upto, l) - slices(s.used))) * kTile<U>;
+        s.n = min(kTile<U>, s.used - s.start);
         t += stride;
         return s;
     }
@@ -1078,7 +1078,7 @@ __global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(Str
     const int lane = (int)threadIdx.x & (kWave - 1);
     const int worker = (int)blockIdx.x * ((int)blockDim.x / kWave) + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     if (worker >= s.n_workers) return;
-    LinkWalk<RUN> walk(s.recs, s.count, worker, s.n_workers);
+    LinkWalk<RUN, kStrideU> walk(s.recs, s.count, worker, s.n_workers);
 #pragma unroll 1
     for (;;) {
         const LinkSlice x = walk.next();
@@ -1092,14 +1092,17 @@ __global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(Str
 // then waits for nothing that is issued after it.  Accesses beyond a slice's elements, or of a direction that has no slice,
 // are dropped by the descriptors.
 // UPDATE: else the slices come and go as they are, of the directions in `parts` only.
-// THREADS: a workgroup's most; with 128 registers, which is what 16 wavefronts leave each other, a few are spilled.
+// THREADS: a workgroup's most.  More than 8 wavefronts leave each other 128 registers: there the slice that comes is read when the one
+// that goes is on its way (356 M parameters, 128 wavefronts, 16 a workgroup, GB/s each way: 46.3; read first, with registers spilled, 39; slices
+// of half the size 42).
 template <bool RUN, bool WT, bool UPDATE, int THREADS>
 __global__ __launch_bounds__(THREADS) void apm_adamw_staged_kernel(StrideArgs s, UpdateArgs a) {
     constexpr int U = kStrideU, STORE = WT ? kStoreHostWT : kStoreNT;
+    constexpr bool kTight = THREADS > kStrideMaxThreads / 2;
     const int lane = (int)threadIdx.x & (kWave - 1);
     const int worker = (int)blockIdx.x * ((int)blockDim.x / kWave) + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     if (worker >= s.n_workers) return;
-    LinkWalk<RUN> walk(s.recs, s.count, worker, s.n_workers);
+    LinkWalk<RUN, U> walk(s.recs, s.count, worker, s.n_workers);
     LinkSlice out{0, 0, 0, 0, 1.0f};
     LinkPlace out_at{};
     int slot = 2 * worker;
@@ -1114,11 +1117,14 @@ __global__ __launch_bounds__(THREADS) void apm_adamw_staged_kernel(StrideArgs s,
         float* const dst[3] = {out_at.p, out_at.m, out_at.v};
         u32x4 come[3][U], go[3][U];
         u32x2 g[U];
+        auto load_in = [&] {
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
+            for (int k = 0; k < 3; ++k)
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                come[k][u] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(src[k], n_in), o + u * (kWave * 16), 0, kNT);
+                for (int u = 0; u < U; ++u)
+                    come[k][u] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(src[k], n_in), o + u * (kWave * 16), 0, kNT);
+        };
+        if (!kTight) load_in();
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -1143,6 +1149,7 @@ __global__ __launch_bounds__(THREADS) void apm_adamw_staged_kernel(StrideArgs s,
                 __builtin_amdgcn_raw_buffer_store_b128(go[k][u], make_rsrc(dst[k], n_out * 4), o + u * (kWave * 16), 0, STORE);
         }
         __builtin_amdgcn_sched_barrier(0);
+        if (kTight) load_in();
 #pragma unroll
         for (int k = 0; k < 3; ++k)
 #pragma unroll
@@ -1935,9 +1942,13 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         auto go = [&](auto in_a_run, auto written_through) {
             constexpr bool RUN = decltype(in_a_run)::value, WT = decltype(written_through)::value;
             if (!L.link_slots[0]) hipLaunchKernelGGL((apm_adamw_stride_kernel<RUN, WT>), grid, block, 0, s, t, a);
-            else if (!(L.link_parts & kLinkUpdate)) hipLaunchKernelGGL((apm_adamw_staged_kernel<RUN, WT, false, kStrideMaxThreads>), grid, block, 0, s, t, a);
-            else if (block.x <= kStrideMaxThreads / 2) hipLaunchKernelGGL((apm_adamw_staged_kernel<RUN, WT, true, kStrideMaxThreads / 2>), grid, block, 0, s, t, a);
-            else hipLaunchKernelGGL((apm_adamw_staged_kernel<RUN, WT, true, kStrideMaxThreads>), grid, block, 0, s, t, a);
+            else {
+                constexpr int kMost = kStrideMaxThreads, kHalf = kMost / 2;
+                const bool update = L.link_parts & kLinkUpdate;
+                auto kernel = (int)block.x <= kHalf ? (update ? apm_adamw_staged_kernel<RUN, WT, true, kHalf> : apm_adamw_staged_kernel<RUN, WT, false, kHalf>)
+                                                    : (update ? apm_adamw_staged_kernel<RUN, WT, true, kMost> : apm_adamw_staged_kernel<RUN, WT, false, kMost>);
+                hipLaunchKernelGGL(kernel, grid, block, 0, s, t, a);
+            }
         };
         const std::true_type yes;
         const std::false_type no;

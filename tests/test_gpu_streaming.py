@@ -37,12 +37,12 @@ def set_mode(streamer, mode):
         apm.apm_streamer_set_mode(streamer, apm.APM_STREAM_DIRECT, n, per)
         assert apm.apm_streamer_get_mode(streamer) == apm.APM_STREAM_DIRECT
     else:
-        # "staged[:<wavefronts>]": the library's duplex copy kernel moves the batches;
+        # "staged[:<wavefronts>[:<per workgroup>]]": slices pass through the wavefronts' staging slots;
         # "staged_dma": the runtime's asynchronous copies do
         assert apm.apm_streamer_get_mode(streamer) == apm.APM_STREAM_DIRECT   # pinned pool: the default
         parts = mode.split(":")
         want = apm.APM_STREAM_STAGED_DMA if parts[0] == "staged_dma" else apm.APM_STREAM_STAGED
-        apm.apm_streamer_set_mode(streamer, want, int(parts[1]) if len(parts) > 1 else 0)
+        apm.apm_streamer_set_mode(streamer, want, int(parts[1]) if len(parts) > 1 else 0, int(parts[2]) if len(parts) > 2 else 0)
         assert apm.apm_streamer_get_mode(streamer) == want
 
 
@@ -1056,7 +1056,7 @@ def test_three_levels_hbm_cache_host_memory_and_files_in_one_step(tmp_path, mode
         x.destroy()
 
 
-@pytest.mark.parametrize("mode", ["direct:1", "direct:5", "direct", "direct:96:16", "staged:1", "staged:5", "staged", "staged:96:16", "staged:48:8+wt"])
+@pytest.mark.parametrize("mode", ["direct:1", "direct:5", "direct", "direct:96:16", "staged:1", "staged:5", "staged", "staged:36:12", "staged:48:8+wt", "staged:48:16+wt"])
 @pytest.mark.parametrize("E,clip,skip", [(1032, 1.0, 0), (64, 0.0, 0), (4104, 0.0, 1)])
 def test_slices_dealt_out_to_wavefronts_equal_resident_bit_exact(E, clip, skip, mode):
     # what a wavefront of the streamed update finds its slices by: more positions than a scan takes (64), scans in which
