@@ -1837,11 +1837,12 @@ int64_t stage_launches(int64_t n_list, int64_t lists, int64_t n_tensors, bool na
 
 hipError_t launch_stage(const AdamwLaunch& L, const StageCall& c, hipStream_t s) {
     const bool has_g = c.g_ptrs != nullptr, has_q = c.q_ptrs != nullptr;
-    const int64_t n_list = c.list ? L.n_listed : 0, n_t = has_g || has_q ? c.n_tensors : 0;
+    const bool listed = c.list || c.runs;
+    const int64_t n_list = listed ? L.n_listed : 0, n_t = has_g || has_q ? c.n_tensors : 0;
     StageArgsInline in;
     StageArgsNarrow half;
     StageArgsRuns runs;
-    StageArgs a{L.used, c.list ? c.d_list : L.grad_pages, L.grad_first, L.n_listed, c.tenants, L.recs, L.g16, L.p16, L.E,
+    StageArgs a{L.used, listed ? c.d_list : L.grad_pages, L.grad_first, L.n_listed, c.tenants, L.recs, L.g16, L.p16, L.E,
                   c.d_list, c.d_out, L.one_pass ? reinterpret_cast<uint64_t*>(L.partials) : nullptr,
                   L.one_pass ? L.n_listed * L.S : 0, c.d_words, 0, 0, 0, 0, 0, has_g, has_q, c.g_base, c.q_base};
     auto go = [&](int64_t list_begin, int64_t list_n, int64_t t_begin, int64_t t_n) -> hipError_t {

@@ -370,19 +370,19 @@ hipError_t launch_prepare(const AdamwLaunch& a, hipStream_t s);
 // index of its outputs in the upper half) and its tensors' addresses.  Written to where the step's
 // kernels read it (list / out / L.recs, with scale 1) by apm_stage_kernel.
 struct StageCall {
-    const uint64_t* list;         // n_listed words, or nullptr: positions as L.grad_pages / L.grad_first say
+    const uint64_t* list;         // n_listed words, or nullptr: as `runs`, or as L.grad_pages / L.grad_first say
     const uint64_t* g_ptrs;       // n_tensors addresses each, nullptr if not gathered / scattered
     const uint64_t* q_ptrs;
     int64_t n_tensors;
     const TenantRec* tenants;
-    int64_t* d_list;              // written if `list`
+    int64_t* d_list;              // written if `list` or `runs`
     int32_t* d_out;
     const uint64_t* d_words;      // list, g_ptrs, q_ptrs one after the other in device memory, or nullptr
     // Carried in kernel arguments, the words are halved if every address lies less than 64 GiB beyond its list's
     // base, as they do but for lists that several allocations far apart make up.
     bool narrow;
     uint64_t g_base, q_base;      // multiples of 16, as all addresses are
-    // The list as runs in place of a word per position, or nullptr; the addresses then as half words.
+    // The list as runs in place of `list`, or nullptr; the addresses then as half words.
     const struct StageRun* runs;
     int64_t n_runs;
 };

@@ -1,5 +1,6 @@
 // Host side of the update: scalar preparation, page-list handling, the synchronous step and the
 // one-step-stale (delayed) step.
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -99,22 +100,22 @@ static bool base_of(const apm_tensor* t, int64_t n, uint64_t* base) {
     return low > high || (high - low) >> 4 <= UINT32_MAX;
 }
 
-// A list in launch order as runs.
-static void runs_of(const int64_t* pages, const std::vector<int64_t>& order, std::vector<StageRun>* out) {
-    int64_t down = 0;  // of the last run, once it has two pages
-    for (size_t k = 0; k < order.size(); ++k) {
-        const int64_t page = pages ? pages[order[k]] : order[k];
-        if (k > 0 && order[k] == order[k - 1] + 1) {
-            const int64_t step = page - (pages ? pages[order[k - 1]] : order[k - 1]);
-            if ((step == 1 || step == -1) && (down == 0 || step == down)) {
-                if (down == 0 && step == -1) out->back().page |= 0x80000000u;
-                down = step;
-                continue;
-            }
-        }
-        out->push_back(StageRun{(uint32_t)k, (uint32_t)page, (uint32_t)order[k]});
-        down = 0;
+// A list in launch order as runs; their number, or -1 if there are more than `most`.  A run's pages are compared with where its first two lead, not
+// each with the one before: 100 000 pages last to first 62 us in place of 180 (a word a page: 67).
+static int64_t runs_of(const int64_t* pages, const std::vector<int64_t>& order, int64_t most, StageRun* out) {
+    auto page_at = [&](int64_t i) { return pages ? pages[i] : i; };
+    const int64_t n = (int64_t)order.size(), *o = order.data();
+    int64_t n_runs = 0;
+    for (int64_t k = 0, end; k < n; k = end) {
+        if (n_runs == most) return -1;
+        const int64_t at = o[k], page = page_at(at);
+        const int64_t step = k + 1 < n && o[k + 1] == at + 1 ? page_at(at + 1) - page : 0;
+        end = k + 1;
+        if (step == 1 || step == -1)
+            for (++end; end < n && o[end] - end == at - k && page_at(at + (end - k)) - page == step * (end - k); ++end) {}
+        out[n_runs++] = StageRun{(uint32_t)k, (uint32_t)page | (step == -1 ? 0x80000000u : 0u), (uint32_t)at};
     }
+    return n_runs;
 }
 
 bool is_captured(hipStream_t s) {
@@ -241,13 +242,13 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     // A long list that is mostly runs (a model's pages last to first, the pages of some experts) goes as those.  us a call, word by word / as
     // runs: 57 M elements in 64 K pages last to first 262 / 250, with clipping 269 / 262, 216 M (word by word through the ring) 955 / 945 and
     // 994 / 981; of 1.08 G elements of 64 experts in 64 K pages an eighth, from and to tensors, 656 / 614.
-    std::vector<StageRun> runs;
-    if (n_list > 0 && launches > 1) {
-        runs_of(pages, order, &runs);
-        const int64_t as_runs = stage_launches_runs((int64_t)runs.size(), lists, n_words);
+    StageRun runs[kStageRuns * kMaxStageLaunches];  // not on the heap: most lists that come here are no runs
+    const int64_t n_runs = n_list > 0 && launches > 1 ? runs_of(pages, order, kStageRuns * std::min<int64_t>(launches - 1, kMaxStageLaunches), runs) : -1;
+    if (n_runs > 0) {
+        const int64_t as_runs = stage_launches_runs(n_runs, lists, n_words);
         if (as_runs < launches && as_runs <= kMaxStageLaunches && base_of(grad_tensors, n_g, &sc.g_base) && base_of(p16_tensors, n_q, &sc.q_base)) {
-            sc.runs = runs.data();
-            sc.n_runs = (int64_t)runs.size();
+            sc.runs = runs;
+            sc.n_runs = n_runs;
             sc.narrow = true;
             launches = as_runs;
         }
@@ -277,34 +278,40 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     }
     const int64_t* d_list = whole ? pool->d_order : pool->d_list;
     const int32_t* d_out = whole ? pool->d_order_out : pool->d_list_out;
-    std::vector<uint64_t> words(staged ? (size_t)(n_list + n_g + n_q) : 0);
-    sc.list = n_list ? words.data() : nullptr;
-    sc.g_ptrs = n_g ? words.data() + n_list : nullptr;
-    sc.q_ptrs = n_q ? words.data() + n_list + n_g : nullptr;
+    const int64_t list_words = sc.runs ? 0 : n_list;
+    const bool ring = by_ring && !L.call;
+    size_t bytes = (size_t)(list_words + n_g + n_q) * sizeof(uint64_t);
+    std::vector<uint64_t> own;
+    uint64_t* words = nullptr;
+    if (ring) {  // written where they are read from
+        if (!staged) bytes = (size_t)n_list * (sizeof(int64_t) + sizeof(int32_t));
+        rc = pool->ring.acquire(bytes, &ring_slot);
+        if (rc != APM_OK) return rc;
+        words = static_cast<uint64_t*>(pool->ring.h[ring_slot]);
+    } else if (staged) {
+        own.resize((size_t)(list_words + n_g + n_q));
+        words = own.data();
+    }
+    sc.list = list_words ? words : nullptr;
+    sc.g_ptrs = n_g ? words + list_words : nullptr;
+    sc.q_ptrs = n_q ? words + list_words + n_g : nullptr;
     sc.n_tensors = tensors ? n_tensors : 0;
     sc.tenants = pool->d_tenants;
     sc.d_list = pool->d_list;
     sc.d_out = pool->d_list_out;
     if (staged) {
-        for (int64_t k = 0; k < n_list; ++k)
-            words[(size_t)k] = (uint64_t)page_at(order[(size_t)k]) | (uint64_t)order[(size_t)k] << 32;
-        for (int64_t i = 0; i < n_g; ++i) words[(size_t)(n_list + i)] = reinterpret_cast<uint64_t>(grad_tensors[i].data);
-        for (int64_t i = 0; i < n_q; ++i) words[(size_t)(n_list + n_g + i)] = reinterpret_cast<uint64_t>(p16_tensors[i].data);
-    }
-    if (by_ring && !L.call) {
-        const size_t bytes = staged ? words.size() * sizeof(uint64_t) : (size_t)n_list * (sizeof(int64_t) + sizeof(int32_t));
-        rc = pool->ring.acquire(bytes, &ring_slot);
-        if (rc != APM_OK) return rc;
-        if (staged) {
-            std::memcpy(pool->ring.h[ring_slot], words.data(), bytes);
-        } else {
-            int64_t* list = static_cast<int64_t*>(pool->ring.h[ring_slot]);
-            int32_t* out = reinterpret_cast<int32_t*>(list + n_list);
-            for (int64_t k = 0; k < n_list; ++k) {
-                list[k] = page_at(order[(size_t)k]);
-                out[k] = (int32_t)order[(size_t)k];
-            }
+        for (int64_t k = 0; k < list_words; ++k) words[k] = (uint64_t)page_at(order[(size_t)k]) | (uint64_t)order[(size_t)k] << 32;
+        for (int64_t i = 0; i < n_g; ++i) words[list_words + i] = reinterpret_cast<uint64_t>(grad_tensors[i].data);
+        for (int64_t i = 0; i < n_q; ++i) words[list_words + n_g + i] = reinterpret_cast<uint64_t>(p16_tensors[i].data);
+    } else if (ring) {
+        int64_t* list = reinterpret_cast<int64_t*>(words);
+        int32_t* out = reinterpret_cast<int32_t*>(list + n_list);
+        for (int64_t k = 0; k < n_list; ++k) {
+            list[k] = page_at(order[(size_t)k]);
+            out[k] = (int32_t)order[(size_t)k];
         }
+    }
+    if (ring) {
         rc = pool->ring.commit(ring_slot, bytes, stream);
         if (rc != APM_OK) return rc;
         if (staged) {
