@@ -492,8 +492,8 @@ def scheduled_leg(args, wl, host, dev_pool, hyper, n_pages, first_step):
 def one_way_traffic_beside_a_producer(streamer, iters):
     """Why the overlap is incomplete: an elementwise producer (gelu over 2^28 bf16 values, many short
     HBM-bound kernels) timed alone and beside the staged pipeline's page traffic in one direction
-    only, then both (the copy-only pipeline: no update kernels).  Pages arriving (PCIe reads) barely
-    disturb it; pages leaving (a kernel's writes to host memory) stretch it."""
+    only, then both (the staged kernel without the update).  Pages arriving (PCIe reads) disturb it
+    less than pages leaving (a kernel's writes to host memory)."""
     import torch
     import paper_2303_02868_amd as apm
     side = _stream_beside_the_current_one()
