@@ -125,6 +125,22 @@ bool ExtentGroups::in_order() const {
     return true;
 }
 
+LayoutOrder layout_order(int64_t n, int64_t E, const int32_t* used, int64_t* order) {
+    LayoutOrder o{};
+    ExtentGroups groups(n, E, used);
+    o.run_n_cls = groups.fold(kWorthLaunch, o.run_cls);
+    o.run = groups.in_order();
+    o.n_cls = groups.fold(kWorthGrid, o.cls);
+    o.plain = groups.in_order();
+    groups.order(order);
+    if (o.plain && !o.run) {
+        o.run = true;
+        o.run_n_cls = o.n_cls;
+        for (int c = 0; c < o.n_cls; ++c) o.run_cls[c] = o.cls[c];
+    }
+    return o;
+}
+
 GridDiv grid_div(int64_t per) {
     uint32_t log2 = 0;
     while (((int64_t)1 << log2) < per) ++log2;

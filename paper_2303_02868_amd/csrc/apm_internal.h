@@ -117,6 +117,22 @@ private:
     int n_cls_ = 0;
 };
 
+// In which classes, and in which order, the pages of a whole layout are launched: decided here, once, for every call over all of it.
+struct LayoutOrder {
+    // In one grid (kWorthGrid): list positions, whose pages `order` names.  plain: position k is page k, and there is no table of it.
+    ExtentClass cls[kMaxExtentClasses];
+    int n_cls;
+    bool plain;
+    // As a run (position k is page k, class after class) if `run`, in these classes: those that are worth a launch of their own
+    // (kWorthLaunch) or, where they would not leave the pages in order, the ones above if they do.  The two do not nest: a class that
+    // joins the next larger one at the higher line can make that one large enough to stay apart, in another order.  So that plain
+    // implies run, and who has neither has an `order`.
+    ExtentClass run_cls[kMaxExtentClasses];
+    int run_n_cls;
+    bool run;
+};
+LayoutOrder layout_order(int64_t n, int64_t E, const int32_t* used, int64_t* order);
+
 // One dimension of a grid holds fewer than 2^32 work-items (the runtime refuses more): the workgroups of
 // `threads` work-items that a one-dimensional launch can have.
 constexpr int64_t max_workgroups(int threads) { return (((int64_t)1 << 32) - 1) / threads; }
@@ -505,18 +521,10 @@ struct apm_pool {
     apm::TenantRec* d_tenants = nullptr;  // by page in use
     apm::PagePlace* d_places = nullptr;   // pages in use in launch order; nullptr: more than kMaxPlaces
     std::vector<int32_t> place_of;        // by page in use: its index there
-    // All pages in use, grouped by extent (see group_by_extent, kWorthGrid): launch order; d_order_out = the same as
-    // 32-bit output indices.  order_plain: the order is 0, 1, 2, ... and has no tables.
+    // All pages in use.  The launch order of whole.cls, and the same as 32-bit output indices; nullptr if whole.plain.
+    apm::LayoutOrder whole{};
     int64_t* d_order = nullptr;
     int32_t* d_order_out = nullptr;
-    apm::ExtentClass order_cls[apm::kMaxExtentClasses] = {};
-    int order_n_cls = 0;
-    bool order_plain = false;
-    // With the classes that are worth a page list (kWorthLaunch) the order would be 0, 1, 2, ...: a step
-    // on the page classes takes the pages as a run, in these classes.
-    apm::ExtentClass run_cls[apm::kMaxExtentClasses] = {};
-    int run_n_cls = 0;
-    bool order_run = false;
     int64_t layout_epoch = 0;  // counts the layouts installed
     char* d_scratch = nullptr;      // the four below, allocated on first use
     double* d_partials = nullptr;   // reduce scratch, n_pages * S

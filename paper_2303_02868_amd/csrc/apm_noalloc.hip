@@ -97,7 +97,7 @@ extern "C" int apm_page_adamw_step_noalloc(apm_pool* pool, int64_t n_pages, int6
         const bool need_reduce = grad_norm || skip_mask || L.max_norm > 0.0 || L.skip_mode != APM_SKIP_NONE;
         const size_t sums = round256(n * S * sizeof(double)) + n * S * sizeof(uint32_t);
         hipStream_t s = static_cast<hipStream_t>(stream);
-        bool listed = pool->has_layout && n == pool->plan.pages.size() && !pool->order_run && (need_reduce || pool->d_places) &&
+        bool listed = pool->has_layout && n == pool->plan.pages.size() && !pool->whole.run && (need_reduce || pool->d_places) &&
                       (L.skip_mode == APM_SKIP_NONE || pool->used_sum.back() <= kCallElems) &&
                       round256(n * sizeof(PageRec) + (size_t)kLiveInts(n_pages) * sizeof(int32_t)) + sums <= kScratchBytes;
         listed = listed && !is_captured(s);
@@ -121,8 +121,8 @@ extern "C" int apm_page_adamw_step_noalloc(apm_pool* pool, int64_t n_pages, int6
         if (listed) {
             L.state_pages = L.grad_pages = pool->d_order;
             L.out_index = pool->d_order_out;
-            L.n_cls = pool->order_n_cls;
-            for (int c = 0; c < L.n_cls; ++c) L.cls[c] = pool->order_cls[c];
+            L.n_cls = pool->whole.n_cls;
+            for (int c = 0; c < L.n_cls; ++c) L.cls[c] = pool->whole.cls[c];
         } else {  // pages [0, n_pages) in order: no list, no output permutation, one launch geometry sized for the largest page
             L.n_cls = 1;
             L.cls[0] = run_class(pool, 0, n_pages);

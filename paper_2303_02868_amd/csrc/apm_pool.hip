@@ -222,21 +222,14 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     std::vector<int64_t> used_sum(n_in_use + 1, 0);
     for (size_t k = 0; k < n_in_use; ++k) used_sum[k + 1] = used_sum[k] + used[k];
     std::vector<int64_t> order(n_in_use);
-    ExtentClass cls[kMaxExtentClasses] = {};
-    ExtentClass run_cls[kMaxExtentClasses] = {};
-    ExtentGroups groups((int64_t)n_in_use, plan.E, used.data());
-    const int run_n_cls = groups.fold(kWorthLaunch, run_cls);
-    const bool run = groups.in_order();
-    const int n_cls = groups.fold(kWorthGrid, cls);
-    const bool plain = groups.in_order();
-    groups.order(order.data());
+    const LayoutOrder whole = layout_order((int64_t)n_in_use, plan.E, used.data(), order.data());
     // Tables for the device, in one allocation and one upload; freed unless the pool takes it over at the end.
     struct Tables {
         char* d = nullptr;
         size_t at[5], bytes = 0;
         ~Tables() { if (d) (void)hipFree(d); }
     } tables;
-    const size_t n_order = plain ? 0 : n_in_use;
+    const size_t n_order = whole.plain ? 0 : n_in_use;
     const size_t n_places = n_in_use <= (size_t)kMaxPlaces ? n_in_use : 0;
     const size_t len[5] = {plan.segs.size() * sizeof(SegRec), n_in_use * sizeof(TenantRec), n_order * sizeof(int64_t), n_order * sizeof(int32_t),
                            n_places * sizeof(PagePlace)};
@@ -306,21 +299,14 @@ int install_layout(apm_pool* pool, const apm_tensor* tensors, int64_t n, Plan&& 
     std::swap(pool->d_tables, tables.d);  // the old tables go with `tables`; hipFree waits for their readers
     pool->d_segs = reinterpret_cast<SegRec*>(pool->d_tables + tables.at[0]);
     pool->d_tenants = reinterpret_cast<TenantRec*>(pool->d_tables + tables.at[1]);
-    pool->d_order = reinterpret_cast<int64_t*>(pool->d_tables + tables.at[2]);
-    pool->d_order_out = reinterpret_cast<int32_t*>(pool->d_tables + tables.at[3]);
+    pool->d_order = n_order ? reinterpret_cast<int64_t*>(pool->d_tables + tables.at[2]) : nullptr;
+    pool->d_order_out = n_order ? reinterpret_cast<int32_t*>(pool->d_tables + tables.at[3]) : nullptr;
     pool->d_places = n_places ? reinterpret_cast<PagePlace*>(pool->d_tables + tables.at[4]) : nullptr;
     pool->place_of.swap(place_of);
     pool->used.swap(used);  // `used`: the old layout's
     if (pool->buffered && pool->buf_by_extent && pool->buf_extents.empty()) pool->buf_extents = std::move(used);
     pool->used_sum.swap(used_sum);
-    pool->order_n_cls = n_cls;
-    pool->order_plain = plain;
-    pool->run_n_cls = run_n_cls;
-    pool->order_run = run;
-    for (int c = 0; c < kMaxExtentClasses; ++c) {
-        pool->order_cls[c] = cls[c];
-        pool->run_cls[c] = run_cls[c];
-    }
+    pool->whole = whole;
     pool->layout_epoch += 1;
     pool->seg_launches.swap(launches);
     pool->seg_ranges = ranges;

@@ -77,7 +77,7 @@ bool wide_pays(const ExtentClass& c) {
 ExtentClass run_class(const apm_pool* pool, int64_t first, int64_t n) {
     const int64_t in_use = (int64_t)pool->used_sum.size() - 1;
     auto upto = [&](int64_t k) { return in_use < 0 ? (int64_t)0 : pool->used_sum[(size_t)(k < in_use ? k : in_use)]; };
-    return ExtentClass{0, n, pool->order_n_cls > 0 ? pool->order_cls[0].max_used : 0, upto(first + n) - upto(first)};
+    return ExtentClass{0, n, pool->whole.n_cls > 0 ? pool->whole.cls[0].max_used : 0, upto(first + n) - upto(first)};
 }
 
 namespace {
@@ -204,11 +204,11 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     // A captured launch makes no records of its own: a replay would hand results on under the same number, and may come after a layout that
     // replaces the tables.
     const bool captured = is_captured(stream);
-    bool run = whole && (tensors || (norms && !captured && pool->d_places && pool->used_sum.back() <= kCallSumElems) ? pool->order_plain : pool->order_run);
+    bool run = whole && (tensors || (norms && !captured && pool->d_places && pool->used_sum.back() <= kCallSumElems) ? pool->whole.plain : pool->whole.run);
     if (whole) {
         const bool as_run = run && !tensors;
-        L.n_cls = as_run ? pool->run_n_cls : pool->order_n_cls;
-        for (int c = 0; c < L.n_cls; ++c) L.cls[c] = as_run ? pool->run_cls[c] : pool->order_cls[c];
+        L.n_cls = as_run ? pool->whole.run_n_cls : pool->whole.n_cls;
+        for (int c = 0; c < L.n_cls; ++c) L.cls[c] = as_run ? pool->whole.run_cls[c] : pool->whole.cls[c];
     } else {
         std::vector<int32_t> room;
         ExtentGroups groups(n_pages, E, page_extents(pool, pages, n_pages, &room));
@@ -494,9 +494,9 @@ static int take_gradient(apm_pool* pool, int k, const uint16_t* g16, const int64
     if (n_pages == 0) return APM_OK;
     const int64_t in_use = (int64_t)pool->plan.pages.size();
     GradTake t{g16, pool->gbuf[k], accumulate, pool->d_used, pool->desc.page_elems, pool->S, sums ? pool->gsum[k] : nullptr,
-               sums ? pool->gnz[k] : nullptr, nullptr, nullptr, 0, pool->order_cls, pool->order_n_cls, pool->max_workgroups};
+               sums ? pool->gnz[k] : nullptr, nullptr, nullptr, 0, pool->whole.cls, pool->whole.n_cls, pool->max_workgroups};
     if (!pages && n_pages == in_use) {
-        t.order = pool->order_plain ? nullptr : pool->d_order;
+        t.order = pool->whole.plain ? nullptr : pool->d_order;
         APM_HIP(launch_grad_take(t, s));
         return APM_OK;
     }
@@ -506,8 +506,8 @@ static int take_gradient(apm_pool* pool, int k, const uint16_t* g16, const int64
     const bool run = consecutive(pages, n_pages);
     // Consecutive pages need no list, and with the extents taken as the layout's largest no look-up, at the price of
     // workgroups without work where pages differ much: a list is the better form then.
-    if (run && (n_pages > kTakePages || pool->run_n_cls <= 1)) {
-        cls[0] = ExtentClass{0, n_pages, pool->order_n_cls > 0 ? pool->order_cls[0].max_used : 0, 0};
+    if (run && (n_pages > kTakePages || pool->whole.run_n_cls <= 1)) {
+        cls[0] = ExtentClass{0, n_pages, pool->whole.n_cls > 0 ? pool->whole.cls[0].max_used : 0, 0};
         t.n_cls = 1;
         t.first = page_at(0);
         APM_HIP(launch_grad_take(t, s));

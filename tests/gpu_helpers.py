@@ -180,7 +180,8 @@ def run_resident(model: Model, steps: int, h: oracle.Hyper, sample: Optional[Seq
     """Runs `steps` AdamW steps through the HIP path on all pages (or `page_list`) and through the
     oracle on the sampled pages (default: all), then applies the parity gates.
     stepper: "sync" = pack g16 + apm_page_adamw_step, "fused" = apm_page_adamw_step_fused reading g16
-    from and writing p16 to tensors (the form bench.py times), "delayed" = apm_step_delayed + flush."""
+    from and writing p16 to tensors (the form bench.py times), "delayed" = apm_step_delayed + flush, "noalloc" =
+    pack g16 + apm_page_adamw_step_noalloc, "captured" = "sync" with every step after the first captured and replayed."""
     plan = model.plan
     n_pages, E = plan.n_pages, model.E
     sample = list(range(n_pages)) if sample is None else list(sample)
@@ -211,9 +212,19 @@ def run_resident(model: Model, steps: int, h: oracle.Hyper, sample: Optional[Seq
     for t in range(1, steps + 1):
         g_flat = model.grad_flat(t)
         g_rows = model.host_pages(g_flat, sample)
-        if stepper == "sync":
+        if stepper in ("sync", "noalloc", "captured"):
             apm.apm_pack_tensors(dp.pool, apm.APM_G16, model.tensors(g_flat), len(model.specs))
-            apm.apm_page_adamw_step(dp.pool, pages_arg, len(listed), t, hy, norm_d, skip_d)
+            if stepper == "noalloc":
+                assert page_list is None
+                apm.apm_page_adamw_step_noalloc(dp.pool, len(listed), t, hy, norm_d, skip_d)
+            elif stepper == "captured" and t > 1:
+                torch.cuda.synchronize()
+                graph = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graph):
+                    apm.apm_page_adamw_step(dp.pool, pages_arg, len(listed), t, hy, norm_d, skip_d, torch.cuda.current_stream())
+                graph.replay()
+            else:
+                apm.apm_page_adamw_step(dp.pool, pages_arg, len(listed), t, hy, norm_d, skip_d)
         elif stepper == "fused":
             apm.apm_page_adamw_step_fused(dp.pool, pages_arg, len(listed), t, hy, model.tensors(g_flat),
                                           model.tensors(q_flat), len(model.specs), norm_d, skip_d)
@@ -224,14 +235,14 @@ def run_resident(model: Model, steps: int, h: oracle.Hyper, sample: Optional[Seq
             apm.apm_step_delayed(dp.pool, pages_arg, len(listed), dp.reg[apm.APM_G16], hy)
             assert apm.apm_delayed_applied(dp.pool) == t - 1
         torch.cuda.synchronize()
-        if stepper == "sync":
+        if stepper in ("sync", "noalloc", "captured"):
             assert np.array_equal(dp.rows_b16(apm.APM_G16, sample), g_rows), "pack g16 not bit-exact"
         upd = [r for r, p in enumerate(sample) if p in listed_set]
         norms, skips = st.step(g_rows, t, h, pages=upd, threads=HOST_THREADS)
         last_outputs = (upd, norms, skips)
         for r, sk in zip(upd, skips):
             touched[r] = touched[r] or not sk
-        if want_outputs and stepper in ("sync", "fused"):
+        if want_outputs and stepper != "delayed":
             check_outputs(norm_d, skip_d, listed, sample, upd, norms, skips)
         del g_flat
     if stepper == "delayed":

@@ -208,6 +208,53 @@ void group_case(Rng& r) {
     if (groups.in_order() != plain) die("in_order", plain, n);
 }
 
+// The forms a call over a whole layout is launched in: every page in one of them with a class that holds it, and in its own place where
+// there is no table to look it up in.
+void whole_layout(const std::vector<int64_t>& numels, int64_t E) {
+    apm::Plan plan;
+    if (apm::make_plan(E, numels.data(), (int64_t)numels.size(), &plan) != APM_OK) die("plan", E);
+    const int64_t n = (int64_t)plan.pages.size();
+    std::vector<int32_t> used((size_t)n);
+    for (int64_t k = 0; k < n; ++k) used[(size_t)k] = (int32_t)plan.pages[(size_t)k].used;
+    std::vector<int64_t> order((size_t)n, -1);
+    const apm::LayoutOrder o = apm::layout_order(n, E, used.data(), order.data());
+    auto covered = [&](const apm::ExtentClass* cls, int n_cls, bool by_order) {
+        std::vector<char> seen((size_t)n, 0);
+        int64_t at = 0;
+        for (int c = 0; c < n_cls; ++c) {
+            if (cls[c].begin != at) die("classes of a whole layout", c, cls[c].begin);
+            for (; at < cls[c].begin + cls[c].count; ++at) {
+                const int64_t page = by_order ? order[(size_t)at] : at;
+                if (page < 0 || page >= n || seen[(size_t)page]++) die("page lost or listed twice", at, page);
+                if (used[(size_t)page] > cls[c].max_used) die("page larger than its class", page, cls[c].max_used);
+            }
+        }
+        if (at != n) die("pages left over", at, n);
+    };
+    covered(o.cls, o.n_cls, true);
+    if (o.plain) covered(o.cls, o.n_cls, false);
+    if (o.run) covered(o.run_cls, o.run_n_cls, false);
+    if (o.plain && !o.run) die("neither a run nor a table of the order", n, E);
+}
+
+void whole_layouts(Rng& r, int cases) {
+    {  // the two groupings disagree: a full page beside a class of small ones
+        std::vector<int64_t> a = {200000, (int64_t)4 << 20}, b = {32768, 262144};
+        a.insert(a.end(), 30, 20000);
+        b.insert(b.end(), 100, 1024);
+        whole_layout(a, (int64_t)1 << 20);
+        whole_layout(b, (int64_t)1 << 20);
+    }
+    for (int i = 0; i < cases; ++i) {  // a few sizes, each a number of times, most of them in order
+        const int64_t E = (int64_t)1 << (13 + r.below(9));
+        std::vector<int64_t> numels;
+        for (int64_t k = 1 + r.below(5); k > 0; --k) numels.insert(numels.end(), (size_t)(1 + r.below((int64_t)1 << r.below(11))), 1 + (E >> r.below(12)) * (1 + r.below(3)));
+        if (r.below(4) != 0) std::sort(numels.rbegin(), numels.rend());
+        for (int64_t k = r.below(3); k > 0; --k) std::swap(numels[(size_t)r.below((int64_t)numels.size())], numels[(size_t)r.below((int64_t)numels.size())]);
+        whole_layout(numels, E);
+    }
+}
+
 // The pieces that a pass over many pages is launched in: every launch within what one grid dimension
 // holds (fewer than 2^32 work-items), every page in one of them.
 void launch_pieces(Rng& r) {
@@ -290,6 +337,7 @@ int main(int argc, char** argv) {
     for (int i = 0; i < cases; ++i) pack_case(r);
     for (int i = 0; i < cases; ++i) plan_case(r);
     for (int i = 0; i < cases; ++i) group_case(r);
+    whole_layouts(r, cases);
     std::printf("ok %d\n", cases);
     return 0;
 }

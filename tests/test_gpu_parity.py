@@ -432,6 +432,21 @@ def test_pages_of_very_different_extents_in_a_permuted_list(stepper):
     dp.destroy()
 
 
+@pytest.mark.parametrize("stepper", ["sync", "noalloc", "captured", "delayed", "fused"])
+@pytest.mark.parametrize("clip,skip", [(0.0, 0), (0.01, 0), (0.0, 1), (0.01, 1)])
+@pytest.mark.parametrize("sizes,sample", [((200000, 4 << 20, *[20000] * 30), [0, 1, 3, 4, 5, 34]),
+                                          ((32768, 262144, *[1024] * 100), [0, 1, 2, 101])])
+def test_layouts_in_order_by_one_grouping_and_not_by_the_other(sizes, sample, clip, skip, stepper):
+    """The pages are in launch order by the classes of a common grid, but not by those that are worth a launch of their own: a small
+    tensor, full pages, many nearly empty ones.  Every form a call over the whole layout takes, against the oracle."""
+    specs = [synth.TensorSpec(i, f"t{i}", n) for i, n in enumerate(sizes)]
+    live = np.array([i % 4 != 2 for i in range(len(specs))])
+    model = Model(specs, 1 << 20, seed=31, active_fn=(lambda t: live) if skip else None, align_elems=8)
+    dp, _, _ = run_resident(model, 2, oracle.Hyper(max_grad_norm=clip, skip_mode=skip), sample=sample,
+                            want_outputs=bool(clip or skip), stepper=stepper)
+    dp.destroy()
+
+
 @pytest.mark.parametrize("clip", [0.0, 0.5])
 def test_non_finite_gradients_propagate_as_in_the_oracle(clip):
     # inf and NaN gradients get no special treatment: the same elements become NaN on both sides
