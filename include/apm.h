@@ -299,8 +299,9 @@ int apm_page_copy_async(apm_pool* dst, int64_t dst_page, apm_pool* src, int64_t 
  * host:   HOST pool storing P32, M32, V32 (the layout is taken from `dev`); it must hold every
  *         page in use unless apm_streamer_set_host_first_page says otherwise (checked per step).
  * dev:    GPU pool storing G16 and P16 for the same pages, with an installed layout.
- * batch_pages: pages moved and updated per pipeline stage of the staged-DMA mode (>= 1).
- * n_slots: staging slots in HBM for that mode (>= 2); each holds batch_pages pages of the three
+ * batch_pages: pages moved and updated per pipeline stage of a ring (>= 1): the staged-DMA mode, and the
+ *          staged mode with stores written through.
+ * n_slots: staging slots in HBM for that ring (>= 2); each holds batch_pages pages of the three
  *          fp32 classes.  The staged mode and the scheduled step use the same memory.
  * The streamer starts in APM_STREAM_DIRECT if the GPU can address the host pool's memory (pinned
  * memory: always), else in APM_STREAM_STAGED_DMA; see apm_streamer_set_mode.
@@ -322,8 +323,13 @@ int apm_streamer_destroy(apm_streamer* s);
  *     two 4 KiB slots per class for, 48 or more) brings its next 1024 elements from the host pages into one
  *     of its slots while it updates the ones in the other and writes them back, so both directions of
  *     the link are busy for nearly all of the step.  Used extents only; pages that are skipped are not
- *     moved.  The staging memory is allocated when a staged mode is first selected.
- *   APM_STREAM_STAGED_DMA: a ring of slots of batch_pages pages moved by the runtime's asynchronous copies:
+ *     moved.  With stores written through (apm_streamer_set_host_write_through) it is a ring of slots
+ *     instead, which disturbs the caller's kernels less: while batch b (at most batch_pages pages, of about
+ *     the same number of used elements) is updated in its slot, one copy kernel of as many wavefronts
+ *     brings batch b+1 in and takes batch b-1 out (two kernels, one after the other, with two slots); all pages
+ *     move, used extents only.  The staging memory is allocated, and the copy stream chosen (by timing
+ *     short kernels, a millisecond; synchronises the device), when a staged mode is first selected.
+ *   APM_STREAM_STAGED_DMA: the same ring, its whole pages moved by the runtime's asynchronous copies:
  *     copy-in / update / copy-out on three streams.  Which stream pairs overlap a host-to-device
  *     with a device-to-host copy depends on the runtime, so when this mode is first selected
  *     short concurrent copies are timed on a few candidate streams (the default stream among
@@ -340,6 +346,7 @@ int apm_streamer_get_mode(const apm_streamer* s);
 /*
  * One AdamW step over all pages in use.  Staged-DMA mode: for batch b, the copy-in of batch b+1 and
  * the copy-out of batch b-1 run beside update(b) on the compute stream, ordered by events.
+ * Staged mode with stores written through: the same with one copy kernel for both directions.
  * Direct and staged mode: one reduce pass and one update kernel on the compute stream.
  * The work starts after everything enqueued on `stream` so far, and `stream` is made to wait for
  * the step's completion; the host does not block.  grad_norm / skip_mask as in
@@ -350,12 +357,12 @@ int apm_streamer_step(apm_streamer* s, int64_t step, const apm_hyper* hyper, flo
 
 /*
  * How the kernels that write the host pool (the direct and the staged mode's update kernel, the
- * scheduled step's copy kernel) store: non-temporal (on = 0, the default: fastest when nothing
+ * staged mode's and the scheduled step's copy kernel) store: non-temporal (on = 0, the default: fastest when nothing
  * else runs on the GPU) or written through at system scope (on != 0).  A non-temporal store to host
  * memory may rest in the GPU's L2 as a dirty line; the write-back at the end of every kernel of any
  * other stream then has to push such lines across PCIe, so kernels that run beside the update are
- * stretched by its writes (measured: elementwise kernels beside the outbound half of the staged
- * pipeline ran 150 ms longer per 290 ms of traffic, beside written-through stores 10 ms).  Written
+ * stretched by its writes (measured: elementwise kernels beside the outbound half of the copy kernel's
+ * traffic ran 150 ms longer per 290 ms of it, beside written-through stores 10 ms).  Written
  * through, the step alone is about a tenth slower.  Meant for the one-step-stale forms, whose
  * update runs beside the caller's kernels.  Results are bit-identical.  Takes effect from the next
  * step.

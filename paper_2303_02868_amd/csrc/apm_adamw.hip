@@ -1091,18 +1091,19 @@ __global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(Str
 // Loads and stores of both directions are one basic block, host reads first: a wait for the slice that came in before
 // then waits for nothing that is issued after it.  Accesses beyond a slice's elements, or of a direction that has no slice,
 // are dropped by the descriptors.
+// For a run of pages, and stores that are not written through (the streamer has another form of those).
 // UPDATE: else the slices come and go as they are, of the directions in `parts` only.
 // THREADS: a workgroup's most.  More than 8 wavefronts leave each other 128 registers: there the slice that comes is read when the one
 // that goes is on its way (356 M parameters, 128 wavefronts, 16 a workgroup, GB/s each way: 46.3; read first, with registers spilled, 39; slices
 // of half the size 42).
-template <bool RUN, bool WT, bool UPDATE, int THREADS>
+template <bool UPDATE, int THREADS>
 __global__ __launch_bounds__(THREADS) void apm_adamw_staged_kernel(StrideArgs s, UpdateArgs a) {
-    constexpr int U = kStrideU, STORE = WT ? kStoreHostWT : kStoreNT;
+    constexpr int U = kStrideU;
     constexpr bool kTight = THREADS > kStrideMaxThreads / 2;
     const int lane = (int)threadIdx.x & (kWave - 1);
     const int worker = (int)blockIdx.x * ((int)blockDim.x / kWave) + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     if (worker >= s.n_workers) return;
-    LinkWalk<RUN, U> walk(s.recs, s.count, worker, s.n_workers);
+    LinkWalk<true, U> walk(s.recs, s.count, worker, s.n_workers);
     LinkSlice out{0, 0, 0, 0, 1.0f};
     LinkPlace out_at{};
     int slot = 2 * worker;
@@ -1111,7 +1112,7 @@ __global__ __launch_bounds__(THREADS) void apm_adamw_staged_kernel(StrideArgs s,
     for (;;) {
         const LinkSlice in = walk.next();
         if (in.n == 0 && out.n == 0) return;
-        const LinkPlace in_at = link_place<RUN>(s, in);
+        const LinkPlace in_at = link_place<true>(s, in);
         const int n_in = UPDATE || (s.parts & kLinkIn) ? in.n * 4 : 0, n_out = UPDATE || (s.parts & kLinkOut) ? out.n : 0;
         float* const src[3] = {in_at.p, in_at.m, in_at.v};
         float* const dst[3] = {out_at.p, out_at.m, out_at.v};
@@ -1146,7 +1147,7 @@ __global__ __launch_bounds__(THREADS) void apm_adamw_staged_kernel(StrideArgs s,
             }
 #pragma unroll
             for (int k = 0; k < 3; ++k)
-                __builtin_amdgcn_raw_buffer_store_b128(go[k][u], make_rsrc(dst[k], n_out * 4), o + u * (kWave * 16), 0, STORE);
+                __builtin_amdgcn_raw_buffer_store_b128(go[k][u], make_rsrc(dst[k], n_out * 4), o + u * (kWave * 16), 0, kStoreNT);
         }
         __builtin_amdgcn_sched_barrier(0);
         if (kTight) load_in();
@@ -1942,18 +1943,18 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
                            L.E, L.n_listed, workers, {L.link_slots[0], L.link_slots[1], L.link_slots[2]}, L.link_parts};
         auto go = [&](auto in_a_run, auto written_through) {
             constexpr bool RUN = decltype(in_a_run)::value, WT = decltype(written_through)::value;
-            if (!L.link_slots[0]) hipLaunchKernelGGL((apm_adamw_stride_kernel<RUN, WT>), grid, block, 0, s, t, a);
-            else {
-                constexpr int kMost = kStrideMaxThreads, kHalf = kMost / 2;
-                const bool update = L.link_parts & kLinkUpdate;
-                auto kernel = (int)block.x <= kHalf ? (update ? apm_adamw_staged_kernel<RUN, WT, true, kHalf> : apm_adamw_staged_kernel<RUN, WT, false, kHalf>)
-                                                    : (update ? apm_adamw_staged_kernel<RUN, WT, true, kMost> : apm_adamw_staged_kernel<RUN, WT, false, kMost>);
-                hipLaunchKernelGGL(kernel, grid, block, 0, s, t, a);
-            }
+            hipLaunchKernelGGL((apm_adamw_stride_kernel<RUN, WT>), grid, block, 0, s, t, a);
         };
         const std::true_type yes;
         const std::false_type no;
-        if (run && L.host_write_through) go(yes, yes);
+        if (L.link_slots[0]) {
+            if (!run || L.host_write_through) return hipErrorInvalidValue;  // the streamer's pages are a run; written through it takes the ring
+            constexpr int kMost = kStrideMaxThreads, kHalf = kMost / 2;
+            const bool update = L.link_parts & kLinkUpdate;
+            auto kernel = (int)block.x <= kHalf ? (update ? apm_adamw_staged_kernel<true, kHalf> : apm_adamw_staged_kernel<false, kHalf>)
+                                                : (update ? apm_adamw_staged_kernel<true, kMost> : apm_adamw_staged_kernel<false, kMost>);
+            hipLaunchKernelGGL(kernel, grid, block, 0, s, t, a);
+        } else if (run && L.host_write_through) go(yes, yes);
         else if (run) go(yes, no);
         else if (L.host_write_through) go(no, yes);
         else go(no, no);

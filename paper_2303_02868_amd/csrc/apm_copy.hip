@@ -154,7 +154,7 @@ __global__ __launch_bounds__(THREADS) void apm_seg_copy_kernel(const SegRec* seg
     else copy_vectors_unaligned(src, dst, nvec);
 }
 
-// Both directions of an exchange of the scheduled step in one kernel: the fp32 classes of incoming pages
+// Both directions of an exchange of the staged mode's ring or the scheduled step in one kernel: the fp32 classes of incoming pages
 // move from pinned host pages into staging slots while those of outgoing pages move from
 // other slots back to their host pages.  A fixed, small number of wavefronts strides over 4 KiB
 // items (one 1 KiB span per wavefront instruction, 4 per class and direction in flight); the link

@@ -4,8 +4,10 @@
 //
 // Staged mode: the pages pass through HBM staging slots, slice by slice: each of a fixed, small number of wavefronts
 // brings its next slice into one of its two slots while it updates the slice in the other and writes it back
-// (apm_adamw_staged_kernel).  Staged-DMA mode: a ring of slots of a batch of pages each, moved by the runtime's
-// asynchronous copies: copy-in, update and copy-out each on its own stream.
+// (apm_adamw_staged_kernel).  With stores written through: a ring of slots of a batch of pages each; while batch b is
+// updated in its slot, one copy kernel brings batch b+1 into the next slot and takes batch b-1 out of the previous one,
+// both directions at once (apm_duplex_copy_kernel), see run_pipeline.  Staged-DMA mode: the same ring, moved by the
+// runtime's asynchronous copies: copy-in, update and copy-out each on its own stream.
 //
 // Mixed residency (Sec. 4.2, the GPU cache of optimizer states): the first R pages may keep their
 // fp32 classes in a GPU pool; they are updated in place, in chunks interleaved with the streamed
@@ -40,7 +42,7 @@ struct apm_streamer {
     float* stage[3] = {nullptr, nullptr, nullptr};  // each n_slots * B * E floats
     hipStream_t s_in = nullptr, s_cmp = nullptr, s_out = nullptr;
     bool host_wt = false;  // stores to the host pool written through at system scope (see apm.h)
-    hipStream_t s_copy = nullptr;  // the stream of the scheduled step's copy kernels
+    hipStream_t s_copy = nullptr;  // the stream of the copy kernels (staged mode, scheduled step)
     hipStream_t s_res = nullptr;  // direct mode: the resident pages' update, beside the host pages'
     hipEvent_t ev_res = nullptr;
     std::vector<hipEvent_t> ev_h2d, ev_cmp, ev_d2h;
@@ -180,7 +182,7 @@ int pick_copy_streams(apm_streamer* s, hipStream_t beside = nullptr, bool use_be
 int ensure_staging(apm_streamer* s);
 int64_t staging_elems(const apm_streamer* s);
 
-// Staging slots, the copy streams and the per-slot events: set up when the staged-DMA mode or the scheduled step
+// Staging slots, the copy streams and the per-slot events: set up when a staged mode or the scheduled step
 // is first asked for.  dma: the runtime's copies need their calibrated stream pair; the copy kernel needs one more
 // stream only.
 int ensure_staged(apm_streamer* s, bool dma) {
@@ -322,7 +324,14 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
     if (!staged && !dma && !(what & kDoUpdate)) return fail(APM_ESTATE, "the copy-only measurement belongs to the staged modes; this streamer is in direct mode");
     APM_HIP(hipEventRecord(s->ev_start, caller));
     APM_HIP(hipStreamWaitEvent(s->s_cmp, s->ev_start, 0));
-    if (dma) {
+    // Written through, the staged mode is there for the kernels that run beside it, and goes by the ring: an elementwise producer twice
+    // as long as the update (268 M parameters) gets 12 ms longer beside it, beside the one kernel 30, although that one ends sooner by itself (85 and
+    // 70 ms; beside the pages going out only 1 and 30, coming in only 10 and 27).  Why the copy kernel is the gentler one is open.  Not written
+    // through the two are alike (46 and 44-48).
+    const bool kcopy = staged && s->host_wt;
+    if (kcopy) {
+        APM_HIP(hipStreamWaitEvent(s->s_copy, s->ev_start, 0));
+    } else if (dma) {
         APM_HIP(hipStreamWaitEvent(s->s_in, s->ev_start, 0));
         APM_HIP(hipStreamWaitEvent(s->s_out, s->ev_start, 0));
     }
@@ -348,7 +357,7 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
     const int64_t H0 = s->host_first;
     if (R < H0 && N > 0) return fail(APM_ESTATE, "model pages [%lld, %lld) are neither resident in the cache nor held by the host pool", (long long)R, (long long)H0);
     if (N - H0 > host->desc.n_pages) return fail(APM_ESTATE, "the host pool holds %lld pages, %lld are needed from model page %lld on", (long long)host->desc.n_pages, (long long)(N - H0), (long long)H0);
-    if (!dma) {
+    if (!dma && !kcopy) {
         // The resident pages (HBM speed) and the host pages (PCIe speed) are updated side by side
         // on two streams; each part has its own range of the per-page scratch.
         const bool two = R > 0 && R < N && (what & kDoUpdate);
@@ -376,7 +385,7 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
                 C.stride_wavefronts = s->direct_waves;
                 C.stride_waves_per_wg = s->direct_per_wg;
                 C.host_write_through = s->host_wt;
-                if (staged) {
+                if (staged) {  // in one kernel
                     const int64_t room = staging_elems(s) * (int64_t)sizeof(float) / (2 * kLinkSlotBytes);
                     if (room < C.stride_wavefronts) C.stride_wavefronts = (int32_t)room;
                     for (int k = 0; k < 3; ++k) C.link_slots[k] = s->stage[k];
@@ -409,11 +418,36 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
         APM_HIP(hipStreamWaitEvent(caller, s->ev_done, 0));
         return APM_OK;
     }
-    // Batches: runs of at most B consecutive pages from page R on.
+    // Batches: runs of at most B consecutive pages from page R on.  The runtime's copies move
+    // whole pages, so there every batch has B pages.  The copy kernel moves used extents, and an
+    // exchange takes as long as its longer direction, so there the batches are cut to hold about
+    // the same number of used elements each: as many as the emptiest window of B pages holds (a
+    // GPT layout has a nearly empty page in every seven or eight; with B pages per batch the two
+    // directions of an exchange differed by 7 % on average, and the step was that much longer).
     std::vector<int64_t> batch_at;  // first page of batch b; one entry more than there are batches
     batch_at.push_back(R);
-    for (int64_t p = R + s->B; p < N; p += s->B) batch_at.push_back(p);
-    if (N > R) batch_at.push_back(N);
+    if (kcopy && N - R > s->B) {
+        const auto used_of = [&](int64_t p) { return (int64_t)dev->plan.pages[(size_t)p].used; };
+        int64_t window = 0, emptiest = INT64_MAX;
+        for (int64_t p = R; p < N; ++p) {
+            window += used_of(p);
+            if (p - R >= s->B) window -= used_of(p - s->B);
+            if (p - R >= s->B - 1 && window < emptiest) emptiest = window;
+        }
+        int64_t in_batch = 0;
+        for (int64_t p = R; p < N; ++p) {
+            const int64_t u = used_of(p), n_here = p - batch_at.back();
+            if (n_here > 0 && (n_here == s->B || in_batch + u / 2 > emptiest)) {  // nearest to the target
+                batch_at.push_back(p);
+                in_batch = 0;
+            }
+            in_batch += u;
+        }
+        batch_at.push_back(N);
+    } else {
+        for (int64_t p = R + s->B; p < N; p += s->B) batch_at.push_back(p);
+        if (N > R) batch_at.push_back(N);
+    }
     const int64_t n_batches = (int64_t)batch_at.size() - 1;
     // resident pages are updated in n_batches chunks (one chunk if nothing is streamed)
     const int64_t chunk = n_batches > 0 ? (R + n_batches - 1) / n_batches : R;
@@ -438,11 +472,12 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
         r_done += nr;
         return APM_OK;
     };
+    hipStream_t s_last = kcopy ? s->s_copy : s->s_out;  // the stream the step ends on
     if (n_batches == 0) {
         rc = resident_chunk();
         if (rc != APM_OK) return rc;
         APM_HIP(hipEventRecord(s->ev_cmp[0], s->s_cmp));
-        APM_HIP(hipStreamWaitEvent(s->s_out, s->ev_cmp[0], 0));
+        APM_HIP(hipStreamWaitEvent(s_last, s->ev_cmp[0], 0));
     }
     auto update_batch = [&](int64_t b) -> int {
         const size_t slot = (size_t)(b % s->n_slots);
@@ -465,6 +500,64 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
         APM_HIP(hipEventRecord(s->ev_cmp[slot], s->s_cmp));
         return APM_OK;
     };
+    if (kcopy) {
+        // Iteration b: one copy kernel brings batch b+1 in and takes batch b-1 out while batch b is
+        // updated.  With three or more slots the three batches sit in different slots; with two,
+        // the incoming batch reuses the outgoing batch's slot, so the two directions become two
+        // kernels, one after the other.
+        auto exchange = [&](int64_t b_in, int64_t b_out) -> int {
+            DuplexCopy d{};
+            auto fill = [&](int64_t b, bool in) {
+                const size_t slot = (size_t)(b % s->n_slots);
+                const int64_t first = batch_at[(size_t)b];
+                const int64_t nb = batch_at[(size_t)b + 1] - first;
+                const size_t slot_off = slot * (size_t)s->B * (size_t)E;  // floats
+                for (int k = 0; k < 3; ++k) {
+                    char* h = reinterpret_cast<char*>(s->host_dev[k]) + (size_t)(first - H0) * pb;
+                    char* g = reinterpret_cast<char*>(s->stage[k] + slot_off);
+                    if (in) { d.in_src[k] = h; d.in_dst[k] = g; }
+                    else { d.out_src[k] = g; d.out_dst[k] = h; }
+                }
+                (in ? d.in_bytes : d.out_bytes) = (int64_t)(pb * (size_t)nb);
+                (in ? d.in_first_page : d.out_first_page) = first;
+            };
+            d.used = dev->d_used;  // only the used extents cross the link
+            d.page_bytes = (int64_t)pb;
+            d.host_store_policy = s->host_wt ? 3 : 0;
+            if (b_in >= 0 && (what & kDoH2D)) fill(b_in, true);
+            if (b_out >= 0 && (what & kDoD2H)) fill(b_out, false);
+            APM_HIP(launch_duplex_copy(d, s->direct_waves, s->direct_per_wg, s->s_copy));
+            return APM_OK;
+        };
+        if (n_batches > 0) {
+            rc = exchange(0, -1);
+            if (rc != APM_OK) return rc;
+            APM_HIP(hipEventRecord(s->ev_h2d[0], s->s_copy));
+        }
+        for (int64_t b = 0; b < n_batches; ++b) {
+            const bool has_in = b + 1 < n_batches, has_out = b >= 1;
+            if (has_out) APM_HIP(hipStreamWaitEvent(s->s_copy, s->ev_cmp[(size_t)((b - 1) % s->n_slots)], 0));
+            if (has_in && has_out && s->n_slots < 3) {
+                rc = exchange(-1, b - 1);
+                if (rc == APM_OK) rc = exchange(b + 1, -1);
+            } else if (has_in || has_out) {
+                rc = exchange(has_in ? b + 1 : -1, has_out ? b - 1 : -1);
+            }
+            if (rc != APM_OK) return rc;
+            if (has_in) APM_HIP(hipEventRecord(s->ev_h2d[(size_t)((b + 1) % s->n_slots)], s->s_copy));
+            rc = resident_chunk();  // runs while this batch's neighbours are in flight
+            if (rc == APM_OK) rc = update_batch(b);
+            if (rc != APM_OK) return rc;
+        }
+        if (n_batches > 0) {
+            APM_HIP(hipStreamWaitEvent(s->s_copy, s->ev_cmp[(size_t)((n_batches - 1) % s->n_slots)], 0));
+            rc = exchange(-1, n_batches - 1);
+            if (rc != APM_OK) return rc;
+        }
+        APM_HIP(hipEventRecord(s->ev_done, s->s_copy));
+        APM_HIP(hipStreamWaitEvent(caller, s->ev_done, 0));
+        return APM_OK;
+    }
     // Copy-in is enqueued one batch ahead of the update that consumes it: when this was written the
     // runtime's device-to-host copy was a kernel whose enqueue blocked the host until the event it
     // waits for had fired, and without the look-ahead the copy-in stream idled during each update.  (A
@@ -546,16 +639,18 @@ int pair_with_producer(apm_streamer* s, hipStream_t producer) {
         if (rc != APM_OK) return rc;
         all = a && b;
     }
-    {
+    hipStream_t* pipeline[2] = {&s->s_cmp, s->mode == APM_STREAM_STAGED ? &s->s_copy : nullptr};
+    for (hipStream_t* st : pipeline) {
+        if (!st || !*st) continue;
         bool ok = false;
-        int rc = streams_overlap(producer, s->s_cmp, &ok);
+        int rc = streams_overlap(producer, *st, &ok);
         if (rc != APM_OK) return rc;
         if (!ok) {
             hipStream_t fresh = nullptr;
             rc = make_overlapping_stream(producer, &fresh, &ok);
             if (rc != APM_OK) return rc;
-            (void)hipStreamDestroy(s->s_cmp);
-            s->s_cmp = fresh;
+            (void)hipStreamDestroy(*st);
+            *st = fresh;
         }
         all = all && ok;
     }
@@ -617,7 +712,7 @@ extern "C" int apm_streamer_set_mode(apm_streamer* s, int mode, int direct_wavef
             s->direct_per_wg = wavefronts_per_workgroup > 0 ? wavefronts_per_workgroup : 1;
         }
         if (mode != APM_STREAM_DIRECT) {
-            int rc = mode == APM_STREAM_STAGED_DMA ? ensure_staged(s, true) : ensure_staging(s);
+            int rc = ensure_staged(s, mode == APM_STREAM_STAGED_DMA);
             if (rc != APM_OK) return rc;
         }
         s->mode = mode;

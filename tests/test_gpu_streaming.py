@@ -2,6 +2,7 @@
 streamed step is bit-identical to the resident step."""
 import ctypes
 import os
+import time
 
 import numpy as np
 import pytest
@@ -1096,3 +1097,56 @@ def test_slices_dealt_out_to_wavefronts_equal_resident_bit_exact(E, clip, skip, 
         assert np.array_equal(before.view(np.uint32), host_view(host, apm.APM_P32, n, E).view(np.uint32))
     for x in (st, host, dev, res):
         x.destroy()
+
+
+def test_a_written_through_staged_update_leaves_an_elementwise_producer_its_bandwidth():
+    """What stores written through are for: a producer of elementwise kernels, twice as long as the update, gets longer by a fraction of it
+    (a seventh by the copy kernel's ring; by the staged mode's one kernel it would be nearly half)."""
+    E, n = 1 << 20, 128
+    host = apm.apm_pool_create(apm.APM_DEV_HOST, E, n, state_mask=apm.FP32_STATES)
+    dev = apm.apm_pool_create(apm.APM_DEV_GPU, E, n, state_mask=apm.B16_STATES)
+    g = torch.zeros(n * E, device=DEV, dtype=torch.bfloat16)
+    apm.apm_pool_set_layout(dev, apm.make_tensors([n * E], apm.APM_BF16, [g.data_ptr()]), 1)
+    st = apm.apm_streamer_create(host, dev, 16, 3)
+    apm.apm_streamer_set_mode(st, apm.APM_STREAM_STAGED)
+    apm.apm_streamer_set_host_write_through(st, True)
+    hy = to_hyper(oracle.Hyper(max_grad_norm=1.0))
+    x = torch.zeros(1 << 27, device=DEV, dtype=torch.bfloat16)
+    step = [0]
+
+    def timed(fn, times=5):
+        out = []
+        for _ in range(times):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            fn()
+            torch.cuda.synchronize()
+            out.append(time.perf_counter() - t0)
+        return sorted(out)[times // 2]
+
+    def update():
+        step[0] += 1
+        apm.apm_streamer_step(st, step[0], hy, None, None)
+
+    def produce(reps):
+        for _ in range(reps):
+            torch.nn.functional.gelu(x)
+
+    def stale(reps):
+        apm.apm_streamer_step_delayed(st, g, hy)
+        produce(reps)
+
+    update()
+    produce(20)
+    alone = timed(update)
+    reps = int(2 * alone / (timed(lambda: produce(50)) / 50))
+    producer = timed(lambda: produce(reps))
+    stale(reps)
+    both = timed(lambda: stale(reps))
+    apm.apm_streamer_step_delayed(st, None, hy)
+    torch.cuda.synchronize()
+    if apm.apm_streamer_overlap_report(st) != (1, 1):
+        pytest.skip("no streams that run beside the producer's")
+    assert both - producer < 0.28 * alone, (alone, producer, both)
+    for pool in (st, host, dev):
+        pool.destroy()
