@@ -406,10 +406,11 @@ int apm_streamer_set_host_first_page(apm_streamer* s, int64_t first_model_page);
 int apm_streamer_set_page_count(apm_streamer* s, int64_t n_pages);
 
 /*
- * Measurement aid (staged modes only): the same pipeline (streams, events, copy sizes, slot reuse)
- * with the update left out.  directions: 1 = copy-in only, 2 = copy-out only, 3 = both.  The data make a round
- * trip host -> staging -> host, so the host pool's contents are unchanged (with 2 alone, staging
- * contents left by an earlier step are written back: call it only after 1 or 3, or a full step).
+ * Measurement aid (staged modes only): the step's page traffic with the update left out.  directions: 1 = copy-in only,
+ * 2 = copy-out only, 3 = both.  With 3 the data make a round trip host -> staging -> host, so the host pool's contents are
+ * unchanged.  One direction goes by the ring of slots in every mode (streams, events, copy sizes and slot reuse as in a step); 2 writes
+ * what the slots hold, which is the pages themselves only if 1 came right before it and the pages make no more than n_slots
+ * batches: otherwise it overwrites the host pool's fp32 classes with other pages' contents.
  */
 int apm_streamer_copy_only(apm_streamer* s, int directions, void* stream);
 

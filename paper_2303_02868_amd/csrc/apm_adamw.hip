@@ -995,7 +995,6 @@ struct StrideArgs {
     int64_t count;
     int n_workers;
     float* slots[3];      // STAGED: two slices a wavefront
-    int parts;            // STAGED: AdamwLaunch::link_parts
 };
 
 struct LinkSlice {
@@ -1092,7 +1091,7 @@ __global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(Str
 // then waits for nothing that is issued after it.  Accesses beyond a slice's elements, or of a direction that has no slice,
 // are dropped by the descriptors.
 // For a run of pages, and stores that are not written through (the streamer has another form of those).
-// UPDATE: else the slices come and go as they are, of the directions in `parts` only.
+// UPDATE: else the slices come and go as they are.
 // THREADS: a workgroup's most.  More than 8 wavefronts leave each other 128 registers: there the slice that comes is read when the one
 // that goes is on its way (356 M parameters, 128 wavefronts, 16 a workgroup, GB/s each way: 46.3; read first, with registers spilled, 39; slices
 // of half the size 42).
@@ -1113,7 +1112,7 @@ __global__ __launch_bounds__(THREADS) void apm_adamw_staged_kernel(StrideArgs s,
         const LinkSlice in = walk.next();
         if (in.n == 0 && out.n == 0) return;
         const LinkPlace in_at = link_place<true>(s, in);
-        const int n_in = UPDATE || (s.parts & kLinkIn) ? in.n * 4 : 0, n_out = UPDATE || (s.parts & kLinkOut) ? out.n : 0;
+        const int n_in = in.n * 4, n_out = out.n;
         float* const src[3] = {in_at.p, in_at.m, in_at.v};
         float* const dst[3] = {out_at.p, out_at.m, out_at.v};
         u32x4 come[3][U], go[3][U];
@@ -1940,7 +1939,7 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         const int per_wg = L.stride_waves_per_wg >= 1 && L.stride_waves_per_wg <= kStrideMaxThreads / kWave ? L.stride_waves_per_wg : 1;
         const dim3 grid((unsigned)((workers + per_wg - 1) / per_wg)), block((unsigned)(per_wg * kWave));
         const StrideArgs t{L.recs, state(L.p32, 0), state(L.m32, 0), state(L.v32, 0), run ? g16(0) : nullptr, run ? p16(0) : nullptr,
-                           L.E, L.n_listed, workers, {L.link_slots[0], L.link_slots[1], L.link_slots[2]}, L.link_parts};
+                           L.E, L.n_listed, workers, {L.link_slots[0], L.link_slots[1], L.link_slots[2]}};
         auto go = [&](auto in_a_run, auto written_through) {
             constexpr bool RUN = decltype(in_a_run)::value, WT = decltype(written_through)::value;
             hipLaunchKernelGGL((apm_adamw_stride_kernel<RUN, WT>), grid, block, 0, s, t, a);
@@ -1950,9 +1949,8 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         if (L.link_slots[0]) {
             if (!run || L.host_write_through) return hipErrorInvalidValue;  // the streamer's pages are a run; written through it takes the ring
             constexpr int kMost = kStrideMaxThreads, kHalf = kMost / 2;
-            const bool update = L.link_parts & kLinkUpdate;
-            auto kernel = (int)block.x <= kHalf ? (update ? apm_adamw_staged_kernel<true, kHalf> : apm_adamw_staged_kernel<false, kHalf>)
-                                                : (update ? apm_adamw_staged_kernel<true, kMost> : apm_adamw_staged_kernel<false, kMost>);
+            auto kernel = (int)block.x <= kHalf ? (L.link_update ? apm_adamw_staged_kernel<true, kHalf> : apm_adamw_staged_kernel<false, kHalf>)
+                                                : (L.link_update ? apm_adamw_staged_kernel<true, kMost> : apm_adamw_staged_kernel<false, kMost>);
             hipLaunchKernelGGL(kernel, grid, block, 0, s, t, a);
         } else if (run && L.host_write_through) go(yes, yes);
         else if (run) go(yes, no);

@@ -320,9 +320,8 @@ struct CallWords {
 // Wavefronts of the update kernel when it reads and writes fp32 classes in host memory across
 // PCIe (the streamer's direct mode, the file tier's window); see apm_stream.hip for the sweep.
 constexpr int kDirectWavefronts = 48;
-// The staged form of it: what a wavefront has in one slot of a class, and what the launch does.
+// The staged form of it: what a wavefront has in one slot of a class.
 constexpr int kLinkSlotBytes = 4096;
-enum { kLinkIn = 1, kLinkOut = 2, kLinkUpdate = 4 };
 
 // Where the pages that a launch does not skip are noted: a count per extent class, then their positions,
 // those of a class from its first position on.  Part of a pool's array belongs to every page
@@ -362,7 +361,7 @@ struct AdamwLaunch {
                                   // page slices (fp32 classes in host memory); 0: one per slice
     int32_t stride_waves_per_wg;  // how many of them share a workgroup, 1..16
     float* link_slots[3];         // stride form: per class two staging slots of kLinkSlotBytes per wavefront; nullptr: none
-    int32_t link_parts;           // with slots: kLinkIn | kLinkOut | kLinkUpdate, the update with both directions only
+    bool link_update;             // with slots: else the pages come and go as they are
     bool beside_link;             // g16 / p16 in the page classes, while a kernel on another stream moves pages across PCIe
     bool host_write_through;      // stride form: fp32 state stores written through at system scope
     bool wide;                    // a run whose grid holds many workgroups without work: fewer, larger slices

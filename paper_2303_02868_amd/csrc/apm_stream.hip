@@ -301,7 +301,7 @@ namespace {
 enum { kDoH2D = 1, kDoD2H = 2, kDoUpdate = 4 };
 
 // The pipeline.  `what` selects its parts: the full step uses all three; the copy-only
-// measurement entry point drops the update (and optionally one direction) but keeps the streams,
+// measurement entry point drops the update (and optionally one direction) but keeps the rest: of a ring the streams,
 // the event structure and the copy sizes.
 int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper, float* grad_norm,
                  uint8_t* skip_mask, void* stream, const uint16_t* g16_override = nullptr) {
@@ -328,7 +328,9 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
     // as long as the update (268 M parameters) gets 12 ms longer beside it, beside the one kernel 30, although that one ends sooner by itself (85 and
     // 70 ms; beside the pages going out only 1 and 30, coming in only 10 and 27).  Why the copy kernel is the gentler one is open.  Not written
     // through the two are alike (46 and 44-48).
-    const bool kcopy = staged && s->host_wt;
+    // One direction by itself goes by the ring as well: its slots keep what came in for the pass that takes it out.
+    const int both = kDoH2D | kDoD2H;
+    const bool kcopy = staged && (s->host_wt || (what & both) != both);
     if (kcopy) {
         APM_HIP(hipStreamWaitEvent(s->s_copy, s->ev_start, 0));
     } else if (dma) {
@@ -389,7 +391,7 @@ int run_pipeline(apm_streamer* s, int what, int64_t step, const apm_hyper* hyper
                     const int64_t room = staging_elems(s) * (int64_t)sizeof(float) / (2 * kLinkSlotBytes);
                     if (room < C.stride_wavefronts) C.stride_wavefronts = (int32_t)room;
                     for (int k = 0; k < 3; ++k) C.link_slots[k] = s->stage[k];
-                    C.link_parts = (what & kDoH2D ? kLinkIn : 0) | (what & kDoD2H ? kLinkOut : 0) | (what & kDoUpdate ? kLinkUpdate : 0);
+                    C.link_update = what & kDoUpdate;
                 }
             }
             C.recs = L.recs + first;

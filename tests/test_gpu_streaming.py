@@ -1150,3 +1150,27 @@ def test_a_written_through_staged_update_leaves_an_elementwise_producer_its_band
     assert both - producer < 0.28 * alone, (alone, producer, both)
     for pool in (st, host, dev):
         pool.destroy()
+
+
+@pytest.mark.parametrize("mode", ["staged", "staged:5", "staged+wt", "staged_dma"])
+def test_pages_that_fit_the_slots_survive_copies_one_way_and_then_the_other(mode):
+    # six pages in three slots of two: what comes in stays there for the pass that takes it out; slices of a page cut by its end
+    E, n = 5000, 6
+    numel = n * E
+    host = apm.apm_pool_create(apm.APM_DEV_HOST, E, n, state_mask=apm.FP32_STATES)
+    dev = apm.apm_pool_create(apm.APM_DEV_GPU, E, n, state_mask=apm.B16_STATES)
+    apm.apm_pool_set_layout(dev, apm.make_tensors([numel], apm.APM_BF16, None), 1)
+    want = np.arange(3 * numel, dtype=np.float32).reshape(3, numel)
+    pages = [host_view(host, s, n, E).reshape(-1)[:numel] for s in (apm.APM_P32, apm.APM_M32, apm.APM_V32)]
+    for k in range(3):
+        pages[k][:] = want[k]
+    st = apm.apm_streamer_create(host, dev, 2, 3)
+    set_mode(st, mode)
+    for directions in ((1, 2), (3, 1, 2)):
+        for d in directions:
+            apm.apm_streamer_copy_only(st, d)
+        torch.cuda.synchronize()
+        for k in range(3):
+            assert np.array_equal(pages[k], want[k])
+    for pool in (st, host, dev):
+        pool.destroy()
