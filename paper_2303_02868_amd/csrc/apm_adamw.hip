@@ -2073,7 +2073,7 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
 bool one_pass_pays(const AdamwLaunch& L, bool staged) {
     int64_t elems = 0;
     for (int c = 0; c < L.n_cls; ++c) elems += L.cls[c].sum_used;
-    return L.skip_mode == APM_SKIP_NONE && (elems >= 4096 * L.n_listed || (staged && L.n_listed <= 2048));
+    return L.skip_mode == APM_SKIP_NONE && (elems >= kOnePassElems * L.n_listed || (staged && L.n_listed <= kOnePassPages));
 }
 
 hipError_t launch_clip_update(const AdamwLaunch& L, hipStream_t s) {

@@ -309,6 +309,11 @@ constexpr int kCallWords = 2 * kArgWords;
 // 0.6 M 13.3 / 9.4, 2.5 M 26.8 / 20.6, 4.9 M 32.3 / 28.0 and 31.4 / 27.5, 18 M 90.6 / 84.9 and 90.1 / 86.4, 25 M 122 / 120 and 132 / 132, 31 M 150 / 149 and
 // 147.5 / 145.2, 39 M 180 / 185 and 180 / 180, 49 M 226 / 232 and 222 / 223).
 constexpr int64_t kCallElems = (int64_t)64 << 20, kCallSumElems = (int64_t)32 << 20;
+// Elements a page from which norms, scales and update go in one grid, and pages up to which they do whatever they hold (one_pass_pays); so that
+// no call in which results are handed on has more pages than this.
+constexpr int64_t kOnePassElems = 4096, kOnePassPages = 2048;
+constexpr int64_t kTaggedPages = kCallSumElems / kOnePassElems;
+static_assert(kOnePassPages <= kTaggedPages, "pages of any extents count as well");
 // The passes of a step that skips (or of norms of many small pages), whose finalize pass then writes the records: with a stage kernel / without, 4.5 M
 // elements 20.9 / 17.8 us, 52 M 55.1 / 51.7, 153 M 134.4 / 130.5, 382 M 295 / 291 and with clipping 312 / 313, 541 M 469 / 468, 1.08 G 915 / 919.
 constexpr int64_t kCallPassElems = (int64_t)512 << 20;
@@ -525,11 +530,11 @@ struct apm_pool {
     int64_t* d_order = nullptr;
     int32_t* d_order_out = nullptr;
     int64_t layout_epoch = 0;  // counts the layouts installed
-    char* d_scratch = nullptr;      // the four below, allocated on first use
+    char* d_scratch = nullptr;      // the five below, allocated on first use
     double* d_partials = nullptr;   // reduce scratch, n_pages * S
     uint32_t* d_nzflags = nullptr;
     apm::PageRec* d_recs = nullptr;   // n_pages entries
-    uint64_t* d_tagged = nullptr;     // CallTables: scales, then sums, of n_pages each; allocated on first use
+    uint64_t* d_tagged = nullptr;     // CallTables: scales, then sums, of up to kTaggedPages each; nullptr: there was no memory for them
     uint32_t call_number = 0;         // of the last call that used it
     int32_t* d_live = nullptr;        // kLiveInts(n_pages) entries
     // what a call's list comes to (apm_stage_kernel), n_pages entries each, allocated on first use; like the scratch above they belong to the one step that is running on the pool
@@ -592,7 +597,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
 int ensure_scratch(apm_pool* pool, bool list = false);
 // Whether work enqueued on the stream now is captured, as far as that can be told.
 bool is_captured(hipStream_t s);
-// The number of the next call, on stream s, and where it hands results on; false if there is no memory for that.
+// The number of the next call, on stream s, and where it hands results on (kTaggedPages); false if there is no memory for that.
 bool next_call(apm_pool* pool, hipStream_t s, CallTables* out);
 // Pages in use beyond which a call's words do not fit its arguments, or a launch more costs it little.
 constexpr int64_t kMaxPlaces = 16384;

@@ -59,8 +59,13 @@ void StageRing::destroy() {
     }
 }
 
+// Pages that a call may hand results on for, and the words they take.
+static size_t tagged_pages(const apm_pool* pool) {
+    return (size_t)(pool->desc.n_pages < kTaggedPages ? pool->desc.n_pages : kTaggedPages);
+}
+static size_t tagged_words(const apm_pool* pool) { return tagged_pages(pool) * (size_t)(kTagLine + tag_sums(pool->S)); }
+
 int ensure_scratch(apm_pool* pool, bool list) {
-    const size_t n = (size_t)pool->desc.n_pages * (size_t)pool->S;
     auto get = [](void** p, size_t bytes) -> int {  // a buffer an earlier, failed attempt got is kept
         if (*p) return APM_OK;
         hipError_t e = hipMalloc(p, bytes);
@@ -69,17 +74,29 @@ int ensure_scratch(apm_pool* pool, bool list) {
         *p = nullptr;
         return fail(APM_ENOMEM, "allocating %zu bytes of per-page scratch failed: %s", bytes, hipGetErrorString(e));
     };
-    // one allocation: a pool's first call waits for each
     const size_t n_pages = (size_t)pool->desc.n_pages;
-    const size_t len[4] = {n_pages * sizeof(PageRec), n * sizeof(double), n * sizeof(uint32_t), (size_t)kLiveInts(pool->desc.n_pages) * sizeof(int32_t)};
-    size_t at[5] = {};
-    for (int k = 0; k < 4; ++k) at[k + 1] = at[k] + (len[k] + 255) / 256 * 256;
-    int rc = get((void**)&pool->d_scratch, at[4]);
-    if (rc == APM_OK) {
-        pool->d_recs = reinterpret_cast<PageRec*>(pool->d_scratch + at[0]);
-        pool->d_partials = reinterpret_cast<double*>(pool->d_scratch + at[1]);
-        pool->d_nzflags = reinterpret_cast<uint32_t*>(pool->d_scratch + at[2]);
-        pool->d_live = reinterpret_cast<int32_t*>(pool->d_scratch + at[3]);
+    int rc = APM_OK;
+    if (!pool->d_scratch) {
+        // One allocation: a pool's first call waits for each, and no later call for any.  It goes without the handed-on words if there is no
+        // memory for them.
+        const size_t n = n_pages * (size_t)pool->S;
+        const size_t len[5] = {n_pages * sizeof(PageRec), n * sizeof(double), n * sizeof(uint32_t), (size_t)kLiveInts(pool->desc.n_pages) * sizeof(int32_t),
+                               tagged_words(pool) * sizeof(uint64_t)};
+        size_t at[6] = {};
+        for (int k = 0; k < 5; ++k) at[k + 1] = at[k] + (len[k] + 255) / 256 * 256;
+        const bool tagged = hipMalloc((void**)&pool->d_scratch, at[5]) == hipSuccess;
+        if (!tagged) {
+            (void)hipGetLastError();
+            pool->d_scratch = nullptr;
+            rc = get((void**)&pool->d_scratch, at[4]);
+        }
+        if (rc == APM_OK) {
+            pool->d_recs = reinterpret_cast<PageRec*>(pool->d_scratch + at[0]);
+            pool->d_partials = reinterpret_cast<double*>(pool->d_scratch + at[1]);
+            pool->d_nzflags = reinterpret_cast<uint32_t*>(pool->d_scratch + at[2]);
+            pool->d_live = reinterpret_cast<int32_t*>(pool->d_scratch + at[3]);
+            pool->d_tagged = tagged ? reinterpret_cast<uint64_t*>(pool->d_scratch + at[4]) : nullptr;
+        }
     }
     if (rc == APM_OK && list) rc = get((void**)&pool->d_list, n_pages * sizeof(int64_t));
     if (rc == APM_OK && list) rc = get((void**)&pool->d_list_out, n_pages * sizeof(int32_t));
@@ -87,24 +104,16 @@ int ensure_scratch(apm_pool* pool, bool list) {
 }
 
 bool next_call(apm_pool* pool, hipStream_t s, CallTables* out) {
-    const size_t n = (size_t)pool->desc.n_pages, words = n * (size_t)(kTagLine + tag_sums(pool->S));
-    if (!pool->d_tagged) {
-        if (hipMalloc((void**)&pool->d_tagged, words * sizeof(uint64_t)) != hipSuccess) {
-            (void)hipGetLastError();
-            pool->d_tagged = nullptr;
-            return false;
-        }
-        pool->call_number = 0;
-    }
-    // cleared when new, and when the numbers come round: there is no telling when a word was last written
+    if (!pool->d_tagged) return false;
+    // cleared by the first call, and when the numbers come round: there is no telling when a word was last written
     if (++pool->call_number == 0) pool->call_number = 1;
-    if (pool->call_number == 1 && hipMemsetAsync(pool->d_tagged, 0, words * sizeof(uint64_t), s) != hipSuccess) {
+    if (pool->call_number == 1 && hipMemsetAsync(pool->d_tagged, 0, tagged_words(pool) * sizeof(uint64_t), s) != hipSuccess) {
         (void)hipGetLastError();
         pool->call_number = 0;  // the next call clears
         return false;
     }
     out->scales = pool->d_tagged;
-    out->sums = pool->d_tagged + n * kTagLine;
+    out->sums = pool->d_tagged + tagged_pages(pool) * kTagLine;
     out->number = pool->call_number;
     return true;
 }
@@ -152,7 +161,6 @@ void free_pool(apm_pool* pool) {
     if (pool->d_used) (void)hipFree(pool->d_used);
     if (pool->d_tables) (void)hipFree(pool->d_tables);
     if (pool->d_scratch) (void)hipFree(pool->d_scratch);
-    if (pool->d_tagged) (void)hipFree(pool->d_tagged);
     if (pool->d_list) (void)hipFree(pool->d_list);
     if (pool->d_list_out) (void)hipFree(pool->d_list_out);
     pool->ring.destroy();

@@ -265,7 +265,7 @@ int enqueue_step(apm_pool* pool, const int64_t* pages, int64_t n_pages, int64_t 
     int64_t elems = 0;
     for (int c = 0; c < L.n_cls; ++c) elems += L.cls[c].sum_used;
     const bool words_fit = !captured && 2 * n_placed + n_g + n_q <= kCallWords && (!places || pool->d_places);
-    const bool one_launch = words_fit && (need_reduce ? norms && elems <= kCallSumElems : places && elems <= kCallElems);  // a bare run has nothing to save
+    const bool one_launch = words_fit && (need_reduce ? norms && elems <= kCallSumElems && n_pages <= kTaggedPages : places && elems <= kCallElems);  // a bare run has nothing to save
     L.one_pass = need_reduce && !page_sums && one_pass_pays(L, staged || one_launch);
     // As passes the finalize pass writes the records.
     if (need_reduce && !L.one_pass ? words_fit && staged && elems <= kCallPassElems : one_launch) {

@@ -1025,3 +1025,21 @@ def test_long_lists_as_runs_equal_the_whole_step(listed, form, clip):
         assert torch.equal(a, b)
     for pool in pools + [mask]:
         pool.destroy()
+
+
+def test_a_later_step_with_norms_takes_no_more_memory():
+    """What small steps with norms hand results on through comes with the pool's first call and is sized by the pages such a step
+    can list: a pool of very many small pages, the first such step after others."""
+    E, n = 64, 1 << 20
+    numels = [40 + k % 20 for k in range(300)]
+    pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n)
+    apm.apm_pool_set_layout(pool, apm.make_tensors(numels, apm.APM_BF16, None), len(numels))
+    apm.apm_page_adamw_step(pool, None, 300, 1, apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.0, 0))
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    norm = torch.full((300,), -1.0, device=DEV)
+    apm.apm_page_adamw_step(pool, None, 300, 2, apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 1.0, 0), norm)
+    torch.cuda.synchronize()
+    assert (norm == 0).all()
+    assert before - torch.cuda.mem_get_info()[0] < 32 << 20   # of the pool's pages: 128 bytes each, 128 MiB
+    pool.destroy()
