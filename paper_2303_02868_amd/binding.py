@@ -228,9 +228,8 @@ class PlanResult:
     def __getattr__(self, name):          # `segments` that nobody has looked at yet
         if name != "segments" or "_segs" not in self.__dict__:
             raise AttributeError(name)
-        self.segments = [self._segs[i].astuple() for i in range(self._n)]
-        del self._segs
-        return self.segments
+        # the array stays: another thread may be at it, and the first of them to end gives the list to all
+        return self.__dict__.setdefault("segments", [self._segs[i].astuple() for i in range(self._n)])
 
 
 def apm_pack_plan(page_elems: int, numels: Sequence[int]) -> PlanResult:

@@ -93,6 +93,25 @@ def test_planner_reproduces_the_hand_worked_layout_with_two_handovers(golden_dir
     assert abs(res.fragmentation - (1 - total / (len(pages) * E))) < 1e-15
 
 
+def test_segments_are_there_for_every_thread_that_looks():
+    """A plan's segments become a list when they are first looked at: a look that begins while another one, which ends first,
+    is under way gets the same list."""
+    seen = []
+
+    class Segments:
+        def __getitem__(self, i):
+            if not seen:                 # the other thread's look, from beginning to end
+                seen.append(None)
+                seen.append(plan.segments)
+            return real[i]
+    real = [apm.apm_segment(k, 0, k, 0, 8) for k in range(3)]
+    plan = apm.PlanResult(Segments(), 3, 0.0, 3)
+    assert plan.segments == [(k, 0, k, 0, 8) for k in range(3)]
+    assert plan.segments is seen[1] and plan.segments is plan.segments
+    with pytest.raises(AttributeError):
+        plan.no_such_thing
+
+
 def test_planner_argument_errors():
     L = apm.lib()
     n_segs = ctypes.c_int64(0)
