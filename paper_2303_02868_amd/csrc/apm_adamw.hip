@@ -336,8 +336,10 @@ __global__ __launch_bounds__(kThreads) void apm_grad_reduce_kernel(const PageRec
         if (e + 8 > end && e < end) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (e + 2 * j >= end) w[j] = 0u;
-                else if (e + 2 * j + 1 >= end) w[j] &= 0x0000FFFFu;
+                uint32_t x = w[j];  // selected: written in place, the compiler branches for every one of them
+                if (e + 2 * j >= end) x = 0u;
+                else if (e + 2 * j + 1 >= end) x &= 0x0000FFFFu;
+                w[j] = x;
             }
         }
     };
@@ -416,7 +418,6 @@ struct FinalizeArgs {
     float* grad_norm;  // nullable
     uint8_t* skip_mask;  // nullable
     const int32_t* out_index;  // nullable: list position -> index into grad_norm / skip_mask
-    bool sums_wanted;  // else `partials` holds none
     bool gather, scatter;
 };
 
@@ -457,7 +458,9 @@ constexpr uint32_t kNoScale = ~(uint32_t)0;
 // 1780 us a call, 64 pages 330; 32 768 of 512 elements 522 and 159).  Small workgroups for few pages, where
 // the launch's own latency counts.
 // Call: CallWords if no stage kernel has written the records (a.gather, a.scatter: what of them is the caller's tensors).
-template <int WAVES, int R, class Call>
+// SUMS: else `partials` holds none.  (Asked at run time, a page's sums and flags come one after the other: norms of 100 000 pages of 64 elements 250 us a
+// call, like this 244.)
+template <int WAVES, int R, bool SUMS, class Call>
 __global__ __launch_bounds__(WAVES * kWave) void apm_grad_finalize_kernel(FinalizeArgs a, Call call) {
     static_assert(WAVES * R <= kWave, "one wavefront notes a workgroup's pages");
     constexpr bool kCall = std::is_same<Call, CallWords>::value;
@@ -492,7 +495,7 @@ __global__ __launch_bounds__(WAVES * kWave) void apm_grad_finalize_kernel(Finali
             uint32_t nz = 0;
             for (int k = lane; k < n_slices; k += kWave) {
                 const int64_t at = (a.by_page ? page : i) * a.S + k;
-                if (a.sums_wanted) s += a.partials[at];
+                if (SUMS) s += a.partials[at];
                 nz |= a.nzflags[at];
             }
             s = wave_sum_f64(s);
@@ -1795,7 +1798,7 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
     if (e != hipSuccess) return e;
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
                    L.partials, L.nzflags, L.S, L.skip_mode, L.max_norm, L.recs, L.g16, L.p16, L.E, live, {}, 0, L.sums_ready, L.is_run(),
-                   L.gather || L.scatter, nullptr, L.grad_norm, L.skip_mask, L.out_index, sums, L.gather, L.scatter};
+                   L.gather || L.scatter, nullptr, L.grad_norm, L.skip_mask, L.out_index, L.gather, L.scatter};
     ExtentClass live_cls[kMaxExtentClasses];
     f.n_cls = live_classes(L, live_cls);
     for (int c = 0; c < f.n_cls; ++c) f.cls_begin[c] = live_cls[c].begin;
@@ -1804,9 +1807,14 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
         auto start = [&](auto kernel, int waves, int pages) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)((L.n_listed + pages - 1) / pages)), dim3((unsigned)(waves * kWave)), 0, s, f, call);
         };
-        if (L.n_listed <= 1024) start(apm_grad_finalize_kernel<4, 1, Call>, 4, 4);
-        else if (L.n_listed <= 4096) start(apm_grad_finalize_kernel<16, 1, Call>, 16, 16);
-        else start(apm_grad_finalize_kernel<16, 4, Call>, 16, 64);
+        auto sized = [&](auto with_sums) {
+            constexpr bool SUMS = decltype(with_sums)::value;
+            if (L.n_listed <= 1024) start(apm_grad_finalize_kernel<4, 1, SUMS, Call>, 4, 4);
+            else if (L.n_listed <= 4096) start(apm_grad_finalize_kernel<16, 1, SUMS, Call>, 16, 16);
+            else start(apm_grad_finalize_kernel<16, 4, SUMS, Call>, 16, 64);
+        };
+        if (sums) sized(std::true_type{});
+        else sized(std::false_type{});
     };
     if (L.call) go(*L.call);
     else go(CallNone{});
@@ -1816,7 +1824,7 @@ hipError_t launch_grad_reduce(const AdamwLaunch& L, hipStream_t s) {
 hipError_t launch_prepare(const AdamwLaunch& L, hipStream_t s) {
     FinalizeArgs f{L.used, L.grad_pages, L.state_pages, L.grad_first, L.state_first, L.n_listed,
                    nullptr, nullptr, L.S, L.skip_mode, 0.0, L.recs, L.g16, L.p16, L.E, nullptr, {}, 0, false, L.is_run(),
-                   false, L.one_pass ? reinterpret_cast<uint64_t*>(L.partials) : nullptr, nullptr, nullptr, nullptr, false, false, false};
+                   false, L.one_pass ? reinterpret_cast<uint64_t*>(L.partials) : nullptr, nullptr, nullptr, nullptr, false, false};
     hipLaunchKernelGGL(apm_page_recs_kernel, dim3(record_grid(L)),
                        dim3(kThreads), 0, s, f);
     return hipGetLastError();
