@@ -1576,7 +1576,7 @@ struct TakeArgsInline {
 // 0.6 M elements 11.6 / 9.4 us, 4.8 M 14.2 / 12.8, 135 M 143.1 / 141.7; without clipping 26 M 25.8 / 27.6).
 // It runs beside the update, where its wavefronts add to those in flight, which like the update's own lower the bandwidth
 // beyond some number: so it requests LDS as well, and shares a CU's with the update's (by itself, 21 of one wavefront, or 6 of four where
-// sums are worked out, fit a CU).  Without sums a workgroup is one wavefront: four of them end when the last one does.
+// sums are worked out, fit a CU).  Without sums a workgroup is one wavefront: four of them end when the last one does (but see take_by_four).
 // us an iteration with four-wavefront workgroups / of one / of one with LDS of 5120 / 7680 / 10240: 124 M, one hand-over and three
 // additions 1026 / 1021 / 974 / 966 / 970; 303 M 1535 / 1515 / 1488 / 1495 / 1520; 355 M with sums and LDS of 0 / 14336 / 27136 / 40960: 1798 /
 // 1776 / 1772 / 1800.  From how many elements on, without / with LDS: three additions 6.6 M 77.3 / 76.9, 9.8 M 97.8 / 93.1, 22 M 192 / 177 (4.8 M by
@@ -1590,10 +1590,22 @@ constexpr TakeCap take_cap(bool accumulate, bool sums) {
     const int64_t m = (int64_t)1 << 20;
     return accumulate ? TakeCap{8 * m, sums ? 14336u : 7680u} : sums ? TakeCap{128 * m, 27136u} : TakeCap{24 * m, 7680u};
 }
-template <bool SUMS> constexpr int kTakeThreads = SUMS ? kThreads : kWave;
+// With sums, pages that hold less than a quarter of a tile on average go without LDS: their workgroups end after a load or two, and more of them have
+// to be on a CU.  us an iteration with clipping and one / three additions, without / with it: 9 M elements, 300 a page, 159 / 172 and 286 / 284;
+// 24 M, 300 a page, 477 / 477 and 680 / 711; 8.6 M, 2867 on average, 106.7 / 108.1 and 126.6 / 130.0; 20 M, 4096 a page, 140.6 / 139.5 and 186.4 / 182.8.
+//
+// Without sums, small calls over pages that hold much less than their class's largest (`spanned` elements in all, if they did not) take four
+// wavefronts a workgroup, as there are four times fewer that find nothing to do: in pages of up to 8 K elements always, where those come between the
+// others, in larger ones, where they come in long rows, if they are most of the grid.  us an iteration with one / three additions, a workgroup of
+// one wavefront / of four, spanned / elems 2 but where stated: 6 M elements in pages of 2048 61.2 / 61.1 and 75.3 / 70.8, 4096 60.7 / 56.2 and 75.0 / 73.4
+// (1.3: 60.0 / 57.8 and 78.7 / 78.5), 8192 59.3 / 57.4 and 75.1 / 74.3, 16 K 50.4 / 50.7 and 68.6 / 69.2, 32 K 46.3 / 47.5 and 64.9 / 70.3, 64 K 48.6 / 50.3 and
+// 66.7 / 74.1; 4.8 M in 1 M pages (2.6) 40.2 / 40.0 and 60.6 / 57.6, an addition alone 9.9 / 8.8; full pages of 64 elements, an addition alone 26.8 / 40.8.
+constexpr bool take_by_four(int64_t elems, int64_t spanned, int64_t largest) {
+    return elems <= (int64_t)8 << 20 && (largest <= 8192 ? 4 * spanned > 5 * elems : 4 * spanned > 9 * elems);
+}
 
-template <bool ACCUM, bool SUMS, class Args>
-__global__ __launch_bounds__(kTakeThreads<SUMS>) void apm_grad_take_kernel(Args args) {
+template <bool ACCUM, bool SUMS, int T, class Args>
+__global__ __launch_bounds__(T) void apm_grad_take_kernel(Args args) {
     const TakeArgs* ap;
     if constexpr (sizeof(Args) > sizeof(TakeArgs)) ap = &args.a;
     else ap = &args;
@@ -1605,7 +1617,7 @@ __global__ __launch_bounds__(kTakeThreads<SUMS>) void apm_grad_take_kernel(Args 
     int64_t page;
     if constexpr (sizeof(Args) > sizeof(TakeArgs)) page = args.page[pos];
     else page = a.order ? a.order[pos] : a.first + pos;
-    constexpr int T = kTakeThreads<SUMS>, U = SUMS ? APM_REDUCE_U : 1, kSpan = T * 8 * U, kItem = SUMS ? kReduceTile : kSpan;
+    constexpr int U = SUMS ? APM_REDUCE_U : 1, kSpan = T * 8 * U, kItem = SUMS ? kReduceTile : kSpan;
     const int used = a.used[page], used8 = (used + 7) & ~7;
     const int start = (int)tile * kItem;
     if (start >= used8 && !(SUMS && tile == 0)) return;
@@ -1667,11 +1679,15 @@ constexpr int kMaxGridY = 65535;
 hipError_t launch_grad_take(const GradTake& t, hipStream_t s) {
     TakeArgsInline in;
     in.a = TakeArgs{t.dst, t.src, t.used, t.order, t.first, t.E, t.sums, t.nzflags, t.S, 0, {}};
-    const int threads = t.sums ? kTakeThreads<true> : kTakeThreads<false>, item = t.sums ? kReduceTile : threads * 8;
-    int64_t elems = 0;  // at most
-    for (int k = 0; k < t.n_cls; ++k) elems += t.cls[k].sum_used > 0 ? t.cls[k].sum_used : t.cls[k].count * t.cls[k].max_used;
+    int64_t elems = 0, spanned = 0, pages = 0;
+    for (int k = 0; k < t.n_cls; ++k) {
+        spanned += t.cls[k].count * t.cls[k].max_used;
+        elems += t.cls[k].sum_used > 0 ? t.cls[k].sum_used : t.cls[k].count * t.cls[k].max_used;  // at most
+        pages += t.cls[k].count;
+    }
     const TakeCap cap = take_cap(t.accumulate, t.sums != nullptr);
-    const unsigned lds = elems <= cap.few ? 0 : cap.lds;
+    const unsigned lds = elems <= cap.few || (t.sums && elems < kOnePassElems * pages) ? 0 : cap.lds;
+    const int threads = t.sums || take_by_four(elems, spanned, t.n_cls > 0 ? t.cls[0].max_used : 0) ? kThreads : kWave, item = t.sums ? kReduceTile : threads * 8;
     // positions of the given classes in one grid
     auto go = [&](const ExtentClass* cls, int n_cls) -> hipError_t {
         while (n_cls > 0 && cls[n_cls - 1].max_used <= 0 && !t.sums) --n_cls;  // nothing to take
@@ -1681,15 +1697,17 @@ hipError_t launch_grad_take(const GradTake& t, hipStream_t s) {
                 in.a.at = (int32_t)first;
                 in.a.map = m;
                 const dim3 grid((unsigned)workgroups);
-#define APM_TAKE(ACCUM, SUMS)                                                                                       \
+#define APM_TAKE(ACCUM, SUMS, T)                                                                                    \
     do {                                                                                                           \
-        if (t.host_pages) hipLaunchKernelGGL((apm_grad_take_kernel<ACCUM, SUMS, TakeArgsInline>), grid, dim3(threads), lds, s, in); \
-        else hipLaunchKernelGGL((apm_grad_take_kernel<ACCUM, SUMS, TakeArgs>), grid, dim3(threads), lds, s, in.a);   \
+        if (t.host_pages) hipLaunchKernelGGL((apm_grad_take_kernel<ACCUM, SUMS, T, TakeArgsInline>), grid, dim3(T), lds, s, in); \
+        else hipLaunchKernelGGL((apm_grad_take_kernel<ACCUM, SUMS, T, TakeArgs>), grid, dim3(T), lds, s, in.a);      \
     } while (0)
-                if (t.accumulate && t.sums) APM_TAKE(true, true);
-                else if (t.accumulate) APM_TAKE(true, false);
-                else if (t.sums) APM_TAKE(false, true);
-                else APM_TAKE(false, false);
+                if (t.accumulate && t.sums) APM_TAKE(true, true, kThreads);
+                else if (t.sums) APM_TAKE(false, true, kThreads);
+                else if (t.accumulate && threads == kThreads) APM_TAKE(true, false, kThreads);
+                else if (t.accumulate) APM_TAKE(true, false, kWave);
+                else if (threads == kThreads) APM_TAKE(false, false, kThreads);
+                else APM_TAKE(false, false, kWave);
 #undef APM_TAKE
                 return (int)hipGetLastError();
             });

@@ -507,7 +507,7 @@ static int take_gradient(apm_pool* pool, int k, const uint16_t* g16, const int64
     // Consecutive pages need no list, and with the extents taken as the layout's largest no look-up, at the price of
     // workgroups without work where pages differ much: a list is the better form then.
     if (run && (n_pages > kTakePages || pool->whole.run_n_cls <= 1)) {
-        cls[0] = ExtentClass{0, n_pages, pool->whole.n_cls > 0 ? pool->whole.cls[0].max_used : 0, 0};
+        cls[0] = run_class(pool, page_at(0), n_pages);
         t.n_cls = 1;
         t.first = page_at(0);
         APM_HIP(launch_grad_take(t, s));

@@ -1043,3 +1043,30 @@ def test_a_later_step_with_norms_takes_no_more_memory():
     assert (norm == 0).all()
     assert before - torch.cuda.mem_get_info()[0] < 32 << 20   # of the pool's pages: 128 bytes each, 128 MiB
     pool.destroy()
+
+
+@pytest.mark.parametrize("listed", ["all", "head", "odd"])
+@pytest.mark.parametrize("E,numels", [(4104, [1 + k * 7919 % 4100 for k in range(90)]), (49160, [49001] + [1600 + k for k in range(40)])])
+def test_hand_overs_of_pages_that_hold_little_equal_the_synchronous_step(E, numels, listed):
+    """Additions and copies without sums by four wavefronts a workgroup: pages well below their class's largest, ends in each wavefront's part."""
+    pools, n, g, lst, draw, state = _pages_and_tensors(E, numels, E, 2)
+    pages = {"all": None, "head": list(range(n - 1)), "odd": list(range(1, n, 2))}[listed]
+    count = len(pages) if pages else n
+    hyper = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 0.0, 0)
+    for t in (1, 2, 3):
+        parts = []
+        for _ in range(2):
+            draw()
+            parts.append((torch.as_tensor(_Region(pools[0], apm.APM_G16, n * E), device=DEV).clone(), g.clone()))
+        g.copy_((parts[0][1].float() + parts[1][1].float()).bfloat16())
+        apm.apm_pack_tensors(pools[0], apm.APM_G16, lst(g), len(numels))
+        apm.apm_page_adamw_step(pools[0], pages, count, t, hyper)
+        apm.apm_step_delayed(pools[1], pages, count, parts[0][0].data_ptr(), hyper)
+        apm.apm_delayed_accumulate(pools[1], pages, count, parts[1][0].data_ptr())
+        torch.cuda.synchronize()
+    apm.apm_step_delayed(pools[1], pages, count, None, hyper)
+    torch.cuda.synchronize()
+    for a, b in zip(state(pools[0]), state(pools[1])):
+        assert torch.equal(a, b)
+    for pool in pools:
+        pool.destroy()
