@@ -875,8 +875,10 @@ __global__ __launch_bounds__(kUpdThreads) void apm_adamw_call_kernel(const PageP
     grid_item(large_at, GridDiv{per, mul, shift}, classes.small, blockIdx.x, &item, &x);
     uint32_t place = first + (uint32_t)item;
     if (listed) place = call_word(&c, 2 * place);
-    // side by side: issued as soon as its address is known, the first would be waited for before the second starts
-    i32x16 at = load_16(places + place), t = load_16(&c.t + (place >> 31));
+    // Side by side: issued as soon as its address is known, the second would be waited for before the first starts.
+    uint32_t none = 0;
+    asm("" : "+s"(none) : "s"(place));
+    i32x16 at = load_16(places + place), t = load_16(reinterpret_cast<const char*>(&c.t) + none);
     asm("" : "+s"(t), "+s"(at));
     const PageRec rec = call_rec<GATHER, SCATTER>(__builtin_bit_cast(CallTables, t), __builtin_bit_cast(PagePlace, at), &c);
     const int start = (int)x * kTile<U>;
