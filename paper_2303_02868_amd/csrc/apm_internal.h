@@ -309,11 +309,13 @@ constexpr int kCallWords = 2 * kArgWords;
 // 0.6 M 13.3 / 9.4, 2.5 M 26.8 / 20.6, 4.9 M 32.3 / 28.0 and 31.4 / 27.5, 18 M 90.6 / 84.9 and 90.1 / 86.4, 25 M 122 / 120 and 132 / 132, 31 M 150 / 149 and
 // 147.5 / 145.2, 39 M 180 / 185 and 180 / 180, 49 M 226 / 232 and 222 / 223).
 constexpr int64_t kCallElems = (int64_t)64 << 20, kCallSumElems = (int64_t)32 << 20;
-// Elements a page from which norms, scales and update go in one grid, and pages up to which they do whatever they hold (one_pass_pays); so that
-// no call in which results are handed on has more pages than this.
+// Elements a page from which norms, scales and update go in one grid, and pages up to which they do whatever they hold (one_pass_pays).
 constexpr int64_t kOnePassElems = 4096, kOnePassPages = 2048;
-constexpr int64_t kTaggedPages = kCallSumElems / kOnePassElems;
-static_assert(kOnePassPages <= kTaggedPages, "pages of any extents count as well");
+// Pages up to which that grid hands results on under the call's number: it has three wavefronts more a page, and a page two cache lines more that are
+// polled.  us a call with a stage / prepare kernel / without, from and to tensors, and consecutive pages: 1000 of 4096 elements 26.2 / 22.7 and 27.2 / 23.5,
+// 1984 of 16 K 149.7 / 147.1 and 146.7 / 142.3, 2000 of 4096 46.7 / 44.2 and 46.2 / 46.7, 2560 of 8192 99.3 / 98.1 and 100.0 / 100.7, 3072 of 4096 67.1 / 67.0 and
+// 68.2 / 69.7, 3584 of 8192 138.8 / 144.4 and 135.5 / 138.4, 4096 of 4096 85.4 / 86.7 and 87.7 / 90.6, 7168 147.7 / 164.0 and 144.5 / 155.5.
+constexpr int64_t kTaggedPages = 2048;
 // The passes of a step that skips (or of norms of many small pages), whose finalize pass then writes the records: with a stage kernel / without, 4.5 M
 // elements 20.9 / 17.8 us, 52 M 55.1 / 51.7, 153 M 134.4 / 130.5, 382 M 295 / 291 and with clipping 312 / 313, 541 M 469 / 468, 1.08 G 915 / 919.
 constexpr int64_t kCallPassElems = (int64_t)512 << 20;

@@ -1070,3 +1070,18 @@ def test_hand_overs_of_pages_that_hold_little_equal_the_synchronous_step(E, nume
         assert torch.equal(a, b)
     for pool in pools:
         pool.destroy()
+
+
+def test_norms_of_thousands_of_pages_cost_what_they_do_with_marked_words():
+    """Beyond some pages, handing results on under the call's number costs more than the kernel that it saves (11 % here); the no-alloc step
+    takes the marked form at every size."""
+    E, n = 4096, 7168
+    pool = apm.apm_pool_create(apm.APM_DEV_GPU, E, n)
+    g, q = (torch.full((n * E,), 1e-3, device=DEV, dtype=torch.bfloat16) for _ in range(2))
+    gl, ql = (apm.make_tensors([n * E], apm.APM_BF16, [t.data_ptr()]) for t in (g, q))
+    apm.apm_pack_tensors(pool, apm.APM_G16, gl, 1)
+    hyper, norm = apm.make_hyper(1e-3, 0.9, 0.999, 1e-8, 0.01, 1.0, 0), torch.zeros(n, device=DEV)
+    fused = _us(lambda: apm.apm_page_adamw_step_fused(pool, None, n, 1, hyper, gl, ql, 1, norm, None), 50)
+    marked = _us(lambda: apm.apm_page_adamw_step_noalloc(pool, n, 1, hyper, norm, None), 50)
+    assert fused < 1.08 * marked, (fused, marked)
+    pool.destroy()
