@@ -323,12 +323,13 @@ int apm_streamer_destroy(apm_streamer* s);
  *     two 4 KiB slots per class for, 48 or more) brings its next 1024 elements from the host pages into one
  *     of its slots while it updates the ones in the other and writes them back, so both directions of
  *     the link are busy for nearly all of the step.  Used extents only; pages that are skipped are not
- *     moved.  With stores written through (apm_streamer_set_host_write_through) it is a ring of slots
- *     instead, which disturbs the caller's kernels less: while batch b (at most batch_pages pages, of about
- *     the same number of used elements) is updated in its slot, one copy kernel of as many wavefronts
- *     brings batch b+1 in and takes batch b-1 out (two kernels, one after the other, with two slots); all pages
- *     move, used extents only.  The staging memory is allocated, and the copy stream chosen (by timing
- *     short kernels, a millisecond; synchronises the device), when a staged mode is first selected.
+ *     moved.  With stores written through (apm_streamer_set_host_write_through) and without
+ *     APM_SKIP_UNTOUCHED it is a ring of slots instead, which disturbs the caller's kernels less: while
+ *     batch b (at most batch_pages pages, of about the same number of used elements each) is updated in
+ *     its slot, one copy kernel of as many wavefronts brings batch b+1 in and takes batch b-1 out (with
+ *     two slots two kernels, one after the other).  The staging memory is allocated, and the copy stream
+ *     chosen (by timing short kernels, a millisecond; synchronises the device), when a staged mode is
+ *     first selected.
  *   APM_STREAM_STAGED_DMA: the same ring, its whole pages moved by the runtime's asynchronous copies:
  *     copy-in / update / copy-out on three streams.  Which stream pairs overlap a host-to-device
  *     with a device-to-host copy depends on the runtime, so when this mode is first selected
@@ -346,7 +347,7 @@ int apm_streamer_get_mode(const apm_streamer* s);
 /*
  * One AdamW step over all pages in use.  Staged-DMA mode: for batch b, the copy-in of batch b+1 and
  * the copy-out of batch b-1 run beside update(b) on the compute stream, ordered by events.
- * Staged mode with stores written through: the same with one copy kernel for both directions.
+ * Staged mode's ring (stores written through): the same with one copy kernel for both directions.
  * Direct and staged mode: one reduce pass and one update kernel on the compute stream.
  * The work starts after everything enqueued on `stream` so far, and `stream` is made to wait for
  * the step's completion; the host does not block.  grad_norm / skip_mask as in

@@ -1117,14 +1117,14 @@ __global__ __launch_bounds__(kStrideMaxThreads) void apm_adamw_stride_kernel(Str
 // Loads and stores of both directions are one basic block, host reads first: a wait for the slice that came in before
 // then waits for nothing that is issued after it.  Accesses beyond a slice's elements, or of a direction that has no slice,
 // are dropped by the descriptors.
-// For a run of pages, and stores that are not written through (the streamer has another form of those).
+// For a run of pages.
 // UPDATE: else the slices come and go as they are.
 // THREADS: a workgroup's most.  More than 8 wavefronts leave each other 128 registers: there the slice that comes is read when the one
 // that goes is on its way (356 M parameters, 128 wavefronts, 16 a workgroup, GB/s each way: 46.3; read first, with registers spilled, 39; slices
 // of half the size 42).
-template <bool UPDATE, int THREADS>
+template <bool WT, bool UPDATE, int THREADS>
 __global__ __launch_bounds__(THREADS) void apm_adamw_staged_kernel(StrideArgs s, UpdateArgs a) {
-    constexpr int U = kStrideU;
+    constexpr int U = kStrideU, STORE = WT ? kStoreHostWT : kStoreNT;
     constexpr bool kTight = THREADS > kStrideMaxThreads / 2;
     const int lane = (int)threadIdx.x & (kWave - 1);
     const int worker = (int)blockIdx.x * ((int)blockDim.x / kWave) + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
@@ -1173,7 +1173,7 @@ __global__ __launch_bounds__(THREADS) void apm_adamw_staged_kernel(StrideArgs s,
             }
 #pragma unroll
             for (int k = 0; k < 3; ++k)
-                __builtin_amdgcn_raw_buffer_store_b128(go[k][u], make_rsrc(dst[k], n_out * 4), o + u * (kWave * 16), 0, kStoreNT);
+                __builtin_amdgcn_raw_buffer_store_b128(go[k][u], make_rsrc(dst[k], n_out * 4), o + u * (kWave * 16), 0, STORE);
         }
         __builtin_amdgcn_sched_barrier(0);
         if (kTight) load_in();
@@ -1997,10 +1997,13 @@ hipError_t launch_adamw(const AdamwLaunch& L, hipStream_t s) {
         const std::true_type yes;
         const std::false_type no;
         if (L.link_slots[0]) {
-            if (!run || L.host_write_through) return hipErrorInvalidValue;  // the streamer's pages are a run; written through it takes the ring
+            // the streamer's pages are a run, and without the update they are not written through (it has another form of that)
+            if (!run || (L.host_write_through && !L.link_update)) return hipErrorInvalidValue;
             constexpr int kMost = kStrideMaxThreads, kHalf = kMost / 2;
-            auto kernel = (int)block.x <= kHalf ? (L.link_update ? apm_adamw_staged_kernel<true, kHalf> : apm_adamw_staged_kernel<false, kHalf>)
-                                                : (L.link_update ? apm_adamw_staged_kernel<true, kMost> : apm_adamw_staged_kernel<false, kMost>);
+            const bool half = (int)block.x <= kHalf;
+            auto kernel = L.host_write_through ? (half ? apm_adamw_staged_kernel<true, true, kHalf> : apm_adamw_staged_kernel<true, true, kMost>)
+                          : L.link_update      ? (half ? apm_adamw_staged_kernel<false, true, kHalf> : apm_adamw_staged_kernel<false, true, kMost>)
+                                               : (half ? apm_adamw_staged_kernel<false, false, kHalf> : apm_adamw_staged_kernel<false, false, kMost>);
             hipLaunchKernelGGL(kernel, grid, block, 0, s, t, a);
         } else if (run && L.host_write_through) go(yes, yes);
         else if (run) go(yes, no);

@@ -1197,3 +1197,27 @@ def test_pages_of_a_few_elements_cross_the_link_without_a_walk():
         for pool in (st, host, dev):
             pool.destroy()
     assert took[0] < 3.4 * took[1], took
+
+
+@pytest.mark.parametrize("mode", ["direct", "staged", "staged+wt"])
+def test_steps_that_skip_every_page_do_not_move_them(mode):
+    E, n = 1 << 20, 32
+    host = apm.apm_pool_create(apm.APM_DEV_HOST, E, n, state_mask=apm.FP32_STATES)
+    dev = apm.apm_pool_create(apm.APM_DEV_GPU, E, n, state_mask=apm.B16_STATES)
+    apm.apm_pool_set_layout(dev, apm.make_tensors([n * E], apm.APM_BF16, None), 1)
+    st = apm.apm_streamer_create(host, dev, 4, 3)
+    set_mode(st, mode)
+    took = []
+    for skip in (0, 1):
+        hy = to_hyper(oracle.Hyper(skip_mode=skip))
+        best = 1e9
+        for t in range(1, 5):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            apm.apm_streamer_step(st, t, hy, None, None)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t0)
+        took.append(best)
+    assert took[1] < 0.2 * took[0], took
+    for pool in (st, host, dev):
+        pool.destroy()
