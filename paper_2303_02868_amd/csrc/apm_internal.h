@@ -536,7 +536,8 @@ struct apm_pool {
     double* d_partials = nullptr;   // reduce scratch, n_pages * S
     uint32_t* d_nzflags = nullptr;
     apm::PageRec* d_recs = nullptr;   // n_pages entries
-    uint64_t* d_tagged = nullptr;     // CallTables: scales, then sums, of up to kTaggedPages each; nullptr: there was no memory for them
+    uint64_t* d_tagged = nullptr;     // CallTables: scales, then sums, of up to kTaggedPages each; d_tagged_own if it is not part of the
+    uint64_t* d_tagged_own = nullptr; // scratch, which the first call that hands results on then allocates
     uint32_t call_number = 0;         // of the last call that used it
     int32_t* d_live = nullptr;        // kLiveInts(n_pages) entries
     // what a call's list comes to (apm_stage_kernel), n_pages entries each, allocated on first use; like the scratch above they belong to the one step that is running on the pool

@@ -77,19 +77,15 @@ int ensure_scratch(apm_pool* pool, bool list) {
     const size_t n_pages = (size_t)pool->desc.n_pages;
     int rc = APM_OK;
     if (!pool->d_scratch) {
-        // One allocation: a pool's first call waits for each, and no later call for any.  It goes without the handed-on words if there is no
-        // memory for them.
-        const size_t n = n_pages * (size_t)pool->S;
+        // One allocation, as a pool's first call waits for each.  The words that small calls hand results on through are part of it where they are
+        // few: a large pool may never make such a call, and they would cost its first one 50 us (1046 pages of 1 M elements, 4 MiB of them).
+        const size_t n = n_pages * (size_t)pool->S, few = (size_t)1 << 20, words = tagged_words(pool) * sizeof(uint64_t);
+        const bool tagged = words <= few;
         const size_t len[5] = {n_pages * sizeof(PageRec), n * sizeof(double), n * sizeof(uint32_t), (size_t)kLiveInts(pool->desc.n_pages) * sizeof(int32_t),
-                               tagged_words(pool) * sizeof(uint64_t)};
+                               tagged ? words : 0};
         size_t at[6] = {};
         for (int k = 0; k < 5; ++k) at[k + 1] = at[k] + (len[k] + 255) / 256 * 256;
-        const bool tagged = hipMalloc((void**)&pool->d_scratch, at[5]) == hipSuccess;
-        if (!tagged) {
-            (void)hipGetLastError();
-            pool->d_scratch = nullptr;
-            rc = get((void**)&pool->d_scratch, at[4]);
-        }
+        rc = get((void**)&pool->d_scratch, at[5]);
         if (rc == APM_OK) {
             pool->d_recs = reinterpret_cast<PageRec*>(pool->d_scratch + at[0]);
             pool->d_partials = reinterpret_cast<double*>(pool->d_scratch + at[1]);
@@ -104,7 +100,14 @@ int ensure_scratch(apm_pool* pool, bool list) {
 }
 
 bool next_call(apm_pool* pool, hipStream_t s, CallTables* out) {
-    if (!pool->d_tagged) return false;
+    if (!pool->d_tagged) {
+        if (hipMalloc((void**)&pool->d_tagged_own, tagged_words(pool) * sizeof(uint64_t)) != hipSuccess) {
+            (void)hipGetLastError();
+            pool->d_tagged_own = nullptr;
+            return false;
+        }
+        pool->d_tagged = pool->d_tagged_own;
+    }
     // cleared by the first call, and when the numbers come round: there is no telling when a word was last written
     if (++pool->call_number == 0) pool->call_number = 1;
     if (pool->call_number == 1 && hipMemsetAsync(pool->d_tagged, 0, tagged_words(pool) * sizeof(uint64_t), s) != hipSuccess) {
@@ -161,6 +164,7 @@ void free_pool(apm_pool* pool) {
     if (pool->d_used) (void)hipFree(pool->d_used);
     if (pool->d_tables) (void)hipFree(pool->d_tables);
     if (pool->d_scratch) (void)hipFree(pool->d_scratch);
+    if (pool->d_tagged_own) (void)hipFree(pool->d_tagged_own);
     if (pool->d_list) (void)hipFree(pool->d_list);
     if (pool->d_list_out) (void)hipFree(pool->d_list_out);
     pool->ring.destroy();
