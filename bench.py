@@ -11,7 +11,7 @@ resident in HBM before the timed region.
 Streamed leg (reported under "streamed"): the fp32 master / momentum / variance pages live in
 pinned host memory.  Measured: the direct mode (the update kernel reads and writes the host pages
 across PCIe itself), the staged mode (pages pass through HBM staging slots, both directions and the
-update in one kernel) with its copy-only pipeline, the schedule-driven mode ("scheduled"),
+update in one kernel) with its copy-only pass, the schedule-driven mode ("scheduled"),
 mixed residency, and the one-step-stale update beside a matrix-product producer ("lock_free").
 The PCIe rates are held against plain pinned copies measured in the same run.
 
@@ -491,9 +491,9 @@ def scheduled_leg(args, wl, host, dev_pool, hyper, n_pages, first_step):
 
 def one_way_traffic_beside_a_producer(streamer, iters):
     """Why the overlap is incomplete: an elementwise producer (gelu over 2^28 bf16 values, many short
-    HBM-bound kernels) timed alone and beside the staged pipeline's page traffic in one direction
-    only, then both (the staged kernel without the update).  Pages arriving (PCIe reads) disturb it
-    less than pages leaving (a kernel's writes to host memory)."""
+    HBM-bound kernels) timed alone and beside the staged mode's page traffic: in one direction only (the
+    copy kernel of its ring), both ways in one kernel, and, written through, one way and both by the ring.
+    Pages arriving (PCIe reads) disturb it less than pages leaving (a kernel's writes to host memory)."""
     import torch
     import paper_2303_02868_amd as apm
     side = _stream_beside_the_current_one()

@@ -80,8 +80,8 @@ __device__ __forceinline__ void copy_vectors_shifted(const char* base, int off, 
 //                 840 M bf16 elements, odd widths, 574 -> 544 us, 122 M fp32 162 -> 157;
 //   into pages    that is slower (561 -> 601 us, 159 -> 168): 128-bit loads at the address itself, with the default policy, as a
 //                 wavefront's first and last line are its neighbours' too, and stores written through (non-temporal loads and plain
-//                 non-temporal stores / like this, bf16: 17 M elements 14.9 / 14.2 us, 34 M 26.2 / 24.0, 47 M 37.4 / 35.9, 122 M 81.5 / 81.1, 869 M
-//                 548 / 541).
+//                 non-temporal stores / like this, bf16, the same buffers again and again: 17 M elements 14.6 / 11.8 us, 34 M 24.4 / 21.2, 47 M
+//                 32.6 / 27.4, 122 M 78.4 / 64.8, 870 M 551 / 538; several in turn, 122 M 82.6 / 82.2).
 //
 // A call brings nothing but the tensors' addresses, and these travel in the kernel arguments
 // (SegArgsInline): descriptors staged through a pinned ring cost the GPU an upload and two event packets,
