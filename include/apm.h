@@ -261,9 +261,10 @@ int apm_page_adamw_step_fused(apm_pool* pool, const int64_t* pages, int64_t n_pa
 /*
  * apm_page_adamw_step for callers that cannot allocate: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same kernels and bit-identical results for the pages
- * [0, n_pages) of a GPU pool that stores all five classes (no page list).  The whole layout is launched
- * in its own classes of extents; under capture, or for other page counts, every page with the largest
- * page's grid, so that nearly empty pages cost idle workgroups.  The per-page scratch
+ * [0, n_pages) of a GPU pool that stores all five classes (no page list).  Every page is launched
+ * with the largest page's grid, so that nearly empty pages cost idle workgroups; a whole layout whose pages
+ * do not lie in order of their extents goes, outside a capture, by those as in apm_page_adamw_step (but
+ * not when a large one may skip pages).  The per-page scratch
  * of the reduce and update kernels (page records, per-slice sums of squares and non-zero flags)
  * lives in a fixed device array of apm_noalloc_scratch_bytes() bytes that the library holds on
  * every GPU it runs on until the process ends, instead of buffers the pool allocates on first use;
